@@ -168,6 +168,7 @@ class Engine:
         self.stage_in_bytes, self.stage_out_bytes = list(ib)[:n.value], list(ob)[:n.value]
         self.tdtype = torch.int8 if self.dtype == EE_I8 else torch.int16
         self.esize = 1 if self.dtype == EE_I8 else 2
+        self._counts = torch.zeros(2, dtype=torch.int32, pin_memory=True)
 
     def close(self):
         if getattr(self, "_h", None) and _lib is not None:      # module globals are gone at interpreter exit
@@ -210,16 +211,18 @@ class Engine:
         t = self.torch
         b, dev = act_src.shape[0], act_src.device
         b_incr = 0 if refill_act is None else refill_act.shape[0]
-        dst = t.zeros((b + b_incr,) + tuple(act_src.shape[1:]), dtype=act_src.dtype, device=dev)
-        ids_dst = t.full((b + b_incr,), -1, dtype=t.int32, device=dev)
-        counts = t.zeros(2, dtype=t.int32, device=dev)
+        # the call writes every row that is handed back; rows whose id nobody gives stay -1
+        dst = t.empty((b + b_incr,) + tuple(act_src.shape[1:]), dtype=act_src.dtype, device=dev)
+        ids_dst = (t.full((b + b_incr,), -1, dtype=t.int32, device=dev) if b_incr and refill_ids is None
+                   else t.empty(b + b_incr, dtype=t.int32, device=dev))
+        counts = self._counts                           # pinned: written by the kernel, read without a copy
         _chk(_lib.ee_compact_refill(self._h, stage, b, flags.data_ptr(), act_src.data_ptr(), dst.data_ptr(),
                                     ids_src.data_ptr(), ids_dst.data_ptr(),
                                     None if refill_act is None else refill_act.data_ptr(),
                                     None if refill_ids is None else refill_ids.data_ptr(), b_incr,
                                     counts.data_ptr(), counts.data_ptr() + 4))
         self.stream.synchronize()
-        b_rem, b_merged = int(counts[0]), int(counts[1])
+        b_rem, b_merged = counts.tolist()
         return dst[:b_merged], ids_dst[:b_merged], b_rem, b_merged
 
     # -- stream serving ----------------------------------------------------------------------

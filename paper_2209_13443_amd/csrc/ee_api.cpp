@@ -589,7 +589,6 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
         if (ctx->stage_out_bytes(s) % 16 != 0 || ctx->stage_in_bytes(s) % 16 != 0) return fail(EE_ERR_UNSUPPORTED);
     }
     ctx->c_max = (size_t)c_max;
-    if ((rc = dev_alloc(ctx, &ctx->d_count, 64))) return fail(rc);
     if ((rc = dev_alloc(ctx, &ctx->zero_page, 256))) return fail(rc);
     if ((rc = dev_alloc(ctx, &ctx->d_ids, sizeof(int32_t) * (size_t)b_max))) return fail(rc);
 
@@ -1294,30 +1293,22 @@ extern "C" int ee_compact_refill(ee_ctx* ctx, int stage, int b_act, const uint8_
     if ((b_act > 0 || b_incr > 0) && (!act_dst || !aligned16(act_dst) || act_dst == act_src || act_dst == refill_act)) return EE_ERR_ARG;
     const int64_t sb = ctx->stage_out_bytes(stage);
     hipStream_t s = ctx->stream;
-    if (b_act > 0) {
-        // only the survivors move: B_rem samples read and written.  The host does not know B_rem here, so a timed run
-        // (and only a timed run) reads the flags back to count them.
-        double bytes = 2.0 * sb * b_act;
-        if (ctx->profiling) {
+    if (b_act + b_incr > 0) {
+        // only the survivors and the newcomers move: B_merged samples read and written.  The host does not know B_rem here, so a
+        // timed run (and only a timed run) reads the flags back to count them.
+        double bytes = 2.0 * sb * (b_act + b_incr);
+        if (ctx->profiling && b_act > 0) {
             std::vector<uint8_t> hf((size_t)b_act);
             if (hipStreamSynchronize(s) != hipSuccess || hipMemcpy(hf.data(), exit_flag, (size_t)b_act, hipMemcpyDeviceToHost) != hipSuccess) return EE_ERR_DEVICE;
-            bytes = 2.0 * sb * (double)std::count(hf.begin(), hf.end(), (uint8_t)0);
+            bytes = 2.0 * sb * (double)(std::count(hf.begin(), hf.end(), (uint8_t)0) + b_incr);
         }
         if (ctx->timed(EE_K_COMPACT, 0.0, bytes, [&] {
-                return launch_compact(exit_flag, act_src, act_dst, ids_src, ids_dst, b_act, sb, 0, 0, ctx->d_count, b_rem_out, s);
+                return launch_compact(exit_flag, act_src, act_dst, ids_src, ids_dst, b_act, refill_act, refill_ids, b_incr, sb, 0, 0, b_rem_out, b_merged_out, s);
             }) != hipSuccess)
             return EE_ERR_DEVICE;
-    } else {
-        if (hipMemsetAsync(ctx->d_count, 0, sizeof(int), s) != hipSuccess) return EE_ERR_DEVICE;
+    } else {                                                           // nothing to move: both counts are zero
         if (b_rem_out && hipMemsetAsync(b_rem_out, 0, sizeof(int), s) != hipSuccess) return EE_ERR_DEVICE;
-    }
-    if (b_incr > 0) {
-        if (ctx->timed(EE_K_COMPACT, 0.0, 2.0 * sb * b_incr, [&] {
-                return launch_append(refill_act, act_dst, refill_ids, ids_dst, ctx->d_count, 0, b_incr, sb, b_merged_out, s);
-            }) != hipSuccess)
-            return EE_ERR_DEVICE;
-    } else if (b_merged_out) {
-        if (hipMemcpyAsync(b_merged_out, ctx->d_count, sizeof(int), hipMemcpyDefault, s) != hipSuccess) return EE_ERR_DEVICE;
+        if (b_merged_out && hipMemsetAsync(b_merged_out, 0, sizeof(int), s) != hipSuccess) return EE_ERR_DEVICE;
     }
     return EE_OK;
 }
@@ -1360,7 +1351,7 @@ extern "C" int ee_measure_lut(ee_ctx* ctx, int reps, int64_t* lut_ns)
                     if (!rc) rc = ctx->run_stage(s, b, ctx->in_buf[s], ctx->out_buf[s], s == 0 && fold != nullptr);
                     ctx->gap_fuse_dst = nullptr;
                     if (!rc) rc = ctx->run_head(s, b, ctx->out_buf[s], 2.0f, ctx->d_label, ctx->d_conf, ctx->d_score, ctx->d_flag, true, nullptr, nullptr, ctx->gap_fused);
-                    if (!rc && s + 1 < n_st && launch_compact(ctx->d_flag, ctx->out_buf[s], ctx->in_buf[s + 1], nullptr, nullptr, b, sb_out, 0, 0, nullptr, nullptr, ctx->stream) != hipSuccess) rc = EE_ERR_DEVICE;
+                    if (!rc && s + 1 < n_st && launch_compact(ctx->d_flag, ctx->out_buf[s], ctx->in_buf[s + 1], nullptr, nullptr, b, nullptr, nullptr, 0, sb_out, 0, 0, nullptr, nullptr, ctx->stream) != hipSuccess) rc = EE_ERR_DEVICE;
                     if (!rc) rc = ctx->wait_head();
                 }
                 if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = EE_ERR_DEVICE;

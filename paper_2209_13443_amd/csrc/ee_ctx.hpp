@@ -78,7 +78,6 @@ struct ee_ctx {
     int32_t* gap_partial = nullptr;              // [(b_max + 1024)][C_max] partial rows of the pooling splits
     void* logits = nullptr;                      // [b_max][n_cls]
     void* zero_page = nullptr;                   // zero bytes read in place of padding taps
-    int* d_count = nullptr;                      // device int scratch (B_rem)
     // stream serving workspace
     std::vector<void*> in_buf, out_buf;          // per segment: packed input slots, raw output slots
     int32_t* d_ids = nullptr;                    // admission ids

@@ -240,12 +240,11 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s);
 hipError_t launch_head_fc(const HeadArgs& a, int dtype, hipStream_t s);
 hipError_t launch_head_softmax(const HeadArgs& a, int dtype, hipStream_t s);
 
-// Stable compaction + append.  dst_off: first destination slot of the survivors; ring_rows > 0: dst is a ring of that
-// many slots and destination slots wrap around its end.
-hipError_t launch_compact(const uint8_t* flag, const void* src, void* dst, const int32_t* ids_src, int32_t* ids_dst,
-                          int b_act, int64_t sample_bytes, int dst_off, int ring_rows, int* b_rem_out, int* b_rem_out2, hipStream_t s);
-hipError_t launch_append(const void* refill, void* dst, const int32_t* refill_ids, int32_t* ids_dst, const int* b_rem_dev,
-                         int b_rem_host, int b_incr, int64_t sample_bytes, int* b_merged_out, hipStream_t s);
+// Stable compaction + refill: the survivors of src[b_act], then the b_incr samples of refill.  dst_off: first destination slot
+// of the survivors; ring_rows > 0: dst is a ring of that many slots and destination slots wrap around its end.
+hipError_t launch_compact(const uint8_t* flag, const void* src, void* dst, const int32_t* ids_src, int32_t* ids_dst, int b_act,
+                          const void* refill, const int32_t* refill_ids, int b_incr, int64_t sample_bytes, int dst_off, int ring_rows,
+                          int* b_rem_out, int* b_merged_out, hipStream_t s);
 // Admission: pool rows ids[k] -> slots [0, b)
 hipError_t launch_admit(const void* pool, void* dst, const int32_t* ids, int b, int64_t sample_bytes, hipStream_t s);
 

@@ -203,7 +203,7 @@ struct GpuExec {
             const int64_t sb = ctx->stage_out_bytes(stage);
             if (ctx->profiling) compact_rec = (long long)ctx->prof_used;
             hipError_t e = ctx->timed(EE_K_COMPACT, 0.0, 2.0 * sb * b, [&] {
-                return launch_compact(ctx->d_flag, ctx->out_buf[stage], ctx->in_buf[stage + 1], nullptr, nullptr, b, sb, dst_off, ring_rows, nullptr, nullptr, ctx->stream);
+                return launch_compact(ctx->d_flag, ctx->out_buf[stage], ctx->in_buf[stage + 1], nullptr, nullptr, b, nullptr, nullptr, 0, sb, dst_off, ring_rows, nullptr, nullptr, ctx->stream);
             });
             if (e != hipSuccess) return EE_ERR_DEVICE;
         }
@@ -263,7 +263,7 @@ struct GpuExec {
         ctx->bind_lane(lane);
         const int64_t sb = ctx->stage_out_bytes(stage);
         hipError_t e = ctx->timed(EE_K_COMPACT, 0.0, 2.0 * sb * (kept >= 0 ? kept : b), [&] {
-            return launch_compact(ctx->d_flag, ctx->out_buf[stage], ctx->in_buf[stage + 1], nullptr, nullptr, b, sb, dst_off, ring_rows, nullptr, nullptr, ctx->stream);
+            return launch_compact(ctx->d_flag, ctx->out_buf[stage], ctx->in_buf[stage + 1], nullptr, nullptr, b, nullptr, nullptr, 0, sb, dst_off, ring_rows, nullptr, nullptr, ctx->stream);
         });
         if (e != hipSuccess) return EE_ERR_DEVICE;
         pack_rec[lane] = ctx->profiling ? (long long)ctx->prof_used - 1 : -1;
