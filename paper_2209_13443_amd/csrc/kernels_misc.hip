@@ -2,6 +2,8 @@
 // pool, FC, softmax top-1 and the exit decision), slot compaction / refill and admission.
 // All of them move 16 bytes per lane per access along the channel (NHWC) or sample axis so
 // that a wavefront touches whole cache lines.
+#include <algorithm>
+
 #include "ee_internal.hpp"
 
 namespace ee {
@@ -475,13 +477,15 @@ hipError_t launch_avgpool(const PoolArgs& a, int dtype, hipStream_t s)
 // atomic per channel (int32 addition is exact in any order; the buffer is zero on entry, the softmax
 // kernel of every head clears what it used).  bf16: the S partial rows of a sample are stored and a
 // second small kernel adds them in split order, so the float means never depend on the order in which
-// workgroups ran.  (A last-arriving-workgroup reduction inside one kernel would need a device-scope
-// release per workgroup, which on this chip writes back the whole L2 of its XCD.)
+// workgroups ran.  (Handing the rows to the last-arriving workgroup of the same kernel was measured with a device-scope
+// release per workgroup, which writes back the whole L2 of its XCD, and with agent-scope stores that need none: either way the
+// hand-over takes some 4 us longer than the second launch.)
+// Bound by HBM on large batches, by latency on small ones; eight loads in flight per lane, also for the last rows.
 // Needs C * ES / 16 <= 256.
 template <int ES>
 __global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block)
 {
-    constexpr int NE = 16 / ES;
+    constexpr int NE = 16 / ES, U = 8;
     __shared__ int red[256 * NE];
     const int cchunks = a.C * ES / 16;
     const int npl = 256 / cchunks;
@@ -495,32 +499,33 @@ __global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block)
     float accf[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) { acci[e] = 0; accf[e] = 0.f; }
+    auto add = [&](const v4i& xv) {
+        if constexpr (ES == 1) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acci[e] += __builtin_amdgcn_sbfe(xv[e >> 2], 8 * (e & 3), 8);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) accf[e] += bf16_to_f32_m((uint16_t)((unsigned)xv[e >> 1] >> (16 * (e & 1))));
+        }
+    };
     if (active) {
+        const v4i* row = (const v4i*)(x + q * 16);
+        const long long pitch = cchunks;                       // 16-byte chunks per pixel
         int p = p0 + pl;
-        for (; p + 3 * npl < p1; p += 4 * npl) {           // four rows in flight per lane
+        for (; p + (U - 1) * npl < p1; p += U * npl) {
+            v4i xv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) xv[u] = row[(p + u * npl) * pitch];
+#pragma unroll
+            for (int u = 0; u < U; ++u) add(xv[u]);
+        }
+        for (; p < p1; p += 4 * npl) {                         // what is left, four at a time: rows past the end read the last one and count nothing
             v4i xv[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) xv[u] = *(const v4i*)(x + ((long long)(p + u * npl) * a.C) * ES + q * 16);
+            for (int u = 0; u < 4; ++u) xv[u] = row[min(p + u * npl, p1 - 1) * pitch];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if constexpr (ES == 1) {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acci[e] += __builtin_amdgcn_sbfe(xv[u][e >> 2], 8 * (e & 3), 8);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) accf[e] += bf16_to_f32_m((uint16_t)((unsigned)xv[u][e >> 1] >> (16 * (e & 1))));
-                }
-            }
-        }
-        for (; p < p1; p += npl) {
-            const v4i xv = *(const v4i*)(x + ((long long)p * a.C) * ES + q * 16);
-            if constexpr (ES == 1) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acci[e] += __builtin_amdgcn_sbfe(xv[e >> 2], 8 * (e & 3), 8);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) accf[e] += bf16_to_f32_m((uint16_t)((unsigned)xv[e >> 1] >> (16 * (e & 1))));
-            }
+            for (int u = 0; u < 4; ++u)
+                if (p + u * npl < p1) add(xv[u]);
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
@@ -553,19 +558,26 @@ __global__ __launch_bounds__(256) void gap_reduce_kernel(HeadArgs a, int S)
     const int c = (int)(idx - b * c4) * 4;
     const int* rows = a.gap_partial + b * S * a.C + c;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    for (int k = 0; k < S; ++k) {
-        const v4i v = *(const v4i*)(rows + (long long)k * a.C);
-        s0 += __int_as_float(v[0]); s1 += __int_as_float(v[1]); s2 += __int_as_float(v[2]); s3 += __int_as_float(v[3]);
+    constexpr int U = 8;                                                    // rows in flight
+    for (int k0 = 0; k0 < S; k0 += U) {
+        v4i v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = *(const v4i*)(rows + (long long)min(k0 + u, S - 1) * a.C);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k0 + u < S) { s0 += __int_as_float(v[u][0]); s1 += __int_as_float(v[u][1]); s2 += __int_as_float(v[u][2]); s3 += __int_as_float(v[u][3]); }
     }
     // the same rounding as the single-split path: one division per channel
     v4i out = {__float_as_int(s0 / (float)a.HW), __float_as_int(s1 / (float)a.HW), __float_as_int(s2 / (float)a.HW), __float_as_int(s3 / (float)a.HW)};
     *(v4i*)(a.sums + b * a.C + c) = out;
 }
 
+// Workgroups: 512 where the pixels allow it (256-512 measured equal, 1024 and more slower: every workgroup ends with one atomic
+// or a partial row per channel), at most 32 per sample (on a batch of 5, adding up 103 partial rows per sample took 13.7 us) and
+// at least 16 pixels each.
 static int gap_pixels_per_block(int B, int HW)
 {
-    const int splits = (512 + B - 1) / B;                    // aim at >= 512 workgroups (256-512 measured equal; 1024 and more are slower:
-                                                             // every workgroup ends with one atomic per channel); B * splits <= B + 1024
+    const int splits = std::min(32, (512 + B - 1) / B);      // B * splits <= B + 511
     int ppb = (HW + splits - 1) / splits;
     if (ppb < 16) ppb = HW < 16 ? HW : 16;
     return ppb;
@@ -605,17 +617,18 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
 // logits[b][j] = b_j + sum_c g[b][c] * W[j][c] as a 16 x 16 matrix-core tile per workgroup: rows = 16
 // classes (A operand, weight rows read straight from global memory, 16 bytes per lane), columns = 16
 // samples (B operand, the pooled features: requantised on the fly for int8; split into a bf16 head and
-// a bf16 remainder for bf16 so that the float mean loses nothing that matters).  The 4 wavefronts take
-// every 4th 64-byte step of the reduction and add their partial tiles through LDS.
+// a bf16 remainder for bf16 so that the float mean loses nothing that matters).  The NW wavefronts take
+// every NWth 64-byte step of the reduction and add their partial tiles through LDS.  Bound by latency: NW is chosen so that
+// every wavefront has all its loads in flight at once (up to four steps each).
 //   v_mfma_i32_16x16x64_i8 / v_mfma_f32_16x16x32_bf16, lane l: row l%16, k-bytes [16*(l/16), +16);
 //   D: column l%16, rows 4*(l/16) + v for accumulator register v = 0..3.
 typedef float v4f_m __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf_m __attribute__((ext_vector_type(8)));
 
-template <int ES>
-__global__ __launch_bounds__(256) void fc_kernel(HeadArgs a)
+template <int ES, int NW>
+__global__ __launch_bounds__(64 * NW) void fc_kernel(HeadArgs a)
 {
-    __shared__ int part[4][256];
+    __shared__ int part[NW][256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j0 = blockIdx.x * 16, b0 = blockIdx.y * 16;
     const int r = lane & 15, kq = lane >> 4;
@@ -627,11 +640,13 @@ __global__ __launch_bounds__(256) void fc_kernel(HeadArgs a)
     const v4i zero4 = {0, 0, 0, 0};
     v4i acci = zero4;
     v4f_m accf = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = wave; s0 < nsteps; s0 += 16) {
+    const int jj = j0 + 4 * kq + (wave & 3);                    // a thread of the first four wavefronts finishes element (class jj, sample r)
+    const int bias = ((const int*)a.bfc)[min(jj, a.n_cls - 1)];
+    for (int s0 = wave; s0 < nsteps; s0 += 4 * NW) {
         v4i wv[4], gv[4][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {                           // all loads of 4 steps first
-            const int kb = (s0 + 4 * u) * 64 + kq * 16;
+            const int kb = (s0 + NW * u) * 64 + kq * 16;
             const bool kin = kb < CB;
             wv[u] = kin && jin ? *(const v4i*)(wrow + kb) : zero4;
             const int* sp = a.sums + (long long)min(b, a.B - 1) * a.C + kb / ES;
@@ -668,16 +683,17 @@ __global__ __launch_bounds__(256) void fc_kernel(HeadArgs a)
 #pragma unroll
     for (int v = 0; v < 4; ++v) part[wave][v * 64 + lane] = ES == 1 ? acci[v] : __float_as_int(accf[v]);
     __syncthreads();
-    const int v = threadIdx.x >> 6;                             // this thread finishes element (class 4*kq + v, sample r)
-    const int jj = j0 + 4 * kq + v;
-    if (jj >= a.n_cls || !bin) return;
+    if (threadIdx.x >= 256 || jj >= a.n_cls || !bin) return;
     if constexpr (ES == 1) {
-        const int t = part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
-        ((int*)a.logits)[(long long)b * a.n_cls + jj] = t + ((const int*)a.bfc)[jj];
+        int t = bias;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += part[w][threadIdx.x];
+        ((int*)a.logits)[(long long)b * a.n_cls + jj] = t;
     } else {
-        const float t = (__int_as_float(part[0][threadIdx.x]) + __int_as_float(part[1][threadIdx.x])) +
-                        (__int_as_float(part[2][threadIdx.x]) + __int_as_float(part[3][threadIdx.x]));
-        ((float*)a.logits)[(long long)b * a.n_cls + jj] = a.logit_scale * (t + ((const float*)a.bfc)[jj]);
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += __int_as_float(part[w][threadIdx.x]);
+        ((float*)a.logits)[(long long)b * a.n_cls + jj] = a.logit_scale * (t + __int_as_float(bias));
     }
 }
 
@@ -685,8 +701,14 @@ hipError_t launch_head_fc(const HeadArgs& a, int dtype, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
     dim3 grid((a.n_cls + 15) / 16, (a.B + 15) / 16);
-    if (dtype == EE_I8) EE_LAUNCH(fc_kernel<1>, grid, dim3(256), 0, s, a);
-    else EE_LAUNCH(fc_kernel<2>, grid, dim3(256), 0, s, a);
+    const bool wide = a.C * (dtype == EE_I8 ? 1 : 2) > 1024;      // more than the 16 steps four wavefronts have in flight
+    if (dtype == EE_I8) {
+        if (wide) EE_LAUNCH((fc_kernel<1, 8>), grid, dim3(512), 0, s, a);
+        else EE_LAUNCH((fc_kernel<1, 4>), grid, dim3(256), 0, s, a);
+    } else {
+        if (wide) EE_LAUNCH((fc_kernel<2, 8>), grid, dim3(512), 0, s, a);
+        else EE_LAUNCH((fc_kernel<2, 4>), grid, dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 
@@ -736,8 +758,11 @@ __global__ __launch_bounds__(256) void softmax_kernel(HeadArgs a)
 {
     __shared__ long long scratch[8];
     __shared__ int scratch_arg[4];
+    __shared__ uint32_t exp2_lds[256];
     const int b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t exp2_mine = 0;
+    if constexpr (ES == 1) exp2_mine = kExp2[threadIdx.x];       // on its way with the logits: the terms then look it up in LDS
     constexpr int PER = 8;
     int vi[PER];
 #pragma unroll
@@ -749,21 +774,21 @@ __global__ __launch_bounds__(256) void softmax_kernel(HeadArgs a)
         int m = INT32_MIN;
 #pragma unroll
         for (int i = 0; i < PER; ++i) m = max(m, vi[i]);
+        exp2_lds[threadIdx.x] = exp2_mine;                      // complete behind the barriers of the reduction
         m = block_reduce<int>(m, (int*)scratch, true);
         int arg = INT32_MAX;
         long long S = 0;
-        const int f = a.frac_bits;
+        const int f = a.frac_bits;                              // 0 .. 30
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int j = threadIdx.x + 256 * i;
             if (j >= a.n_cls) continue;
             const int v = vi[i];
             if (v == m) arg = min(arg, j);
-            const long long d = (long long)m - v;
-            const long long q = d >> f;
-            const long long frac = d & ((1ll << f) - 1);
-            const int r = (int)(f >= 8 ? frac >> (f - 8) : frac << (8 - f));
-            S += q >= 31 ? 0 : (long long)(kExp2[r] >> q);
+            const unsigned d = (unsigned)m - (unsigned)v;        // 0 .. 2^32 - 1
+            const unsigned q = d >> f, frac = d & ((1u << f) - 1u);
+            const unsigned r = f >= 8 ? frac >> (f - 8) : frac << (8 - f);
+            S += q >= 31 ? 0u : exp2_lds[r] >> q;
         }
         for (int o = 32; o > 0; o >>= 1) {                  // integer sums and minima: exact in any order
             S += __shfl_xor(S, o, 64);
