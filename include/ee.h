@@ -230,7 +230,8 @@ int ee_tune_conv_tile(int cfg);
  * tile | step << 4 | stages << 8 | groups << 12 with tile 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128 (pixels x
  * channels), step 1: 64, 2: 128, 3: 256 bytes of the reduction axis per stage, groups 0: one group of 4
  * wavefronts, 2 or 4: that many groups sharing the reduction of a tile; the entry 7 alone selects the streaming
- * kernel.  EE_ERR_ARG for bad arguments. */
+ * kernel; groups 2 or 4 with step 1 or 2 name the kernel for few output pixels (32- resp. 16-pixel tiles, step = blocks of
+ * channels, tile = log2 of the wavefronts + 1).  EE_ERR_ARG for bad arguments. */
 int ee_autotune(ee_ctx* ctx, int reps);
 int ee_config_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);
 /* Loads a stored table for layer `layer` (n <= 16 entries as ee_config_table returns them; n = 0 clears it):

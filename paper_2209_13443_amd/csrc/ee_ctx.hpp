@@ -8,12 +8,16 @@
 namespace ee {
 
 enum Impl { IMPL_MFMA = 0, IMPL_MFMA_C4 = 1, IMPL_DIRECT = 2, IMPL_DW = 3, IMPL_POOL = 4, IMPL_MFMA_CPAD = 5, IMPL_MFMA_S2D = 6, IMPL_AVGPOOL = 7, IMPL_THIN = 8 };
+// ee_autotune tries the few-pixel kernel up to this many output pixels: every operand byte it loads feeds one instruction, so with
+// more it is never the fastest
+constexpr long long EE_SKINNY_MAX_ROWS = 8192;
 enum { BUF_EXT_IN = -1, BUF_EXT_OUT = -2 };
 
 struct OpPlan {
     OpDesc d;
     int impl = IMPL_DIRECT;
     void* w_dev = nullptr;      // packed weights
+    void* wo_dev = nullptr;     // matrix-core convolutions: the packed weights once more, as ready operands (see ConvArgs::wo)
     void* b_dev = nullptr;      // bias, padded to the weight rows
     void* w3_dev = nullptr;     // int8 3x3 depthwise: weights packed per kernel row for the dot-product kernel
     int Kp = 0, kwp = 0, Hp = 0, Wp = 0;
@@ -22,6 +26,7 @@ struct OpPlan {
     int ci_eff = 0;             // input channels the matrix-core kernel sees (c_in, or c_in padded to a 16-byte multiple)
     // IMPL_MFMA_S2D: stride-2 first layer over <= 4 channels, run as a stride-1 convolution with a ks2 x ks2 kernel over the
     // zero-padded image folded into Hp x Wp super-pixels of 2 x 2 pixels x 4 channels (Hp, Wp, ks2 reuse the fields above)
+    bool cfg_table() const { return impl == IMPL_MFMA || impl == IMPL_MFMA_CPAD || impl == IMPL_MFMA_S2D; }   // the layer has a table of kernel configurations
     std::vector<int> cfg;       // kernel configuration per batch bucket (see ee_autotune); empty = by shape
     bool pair = false;          // this layer and the next one (a 1x1 layer that alone reads it) can run as one fused launch
     std::vector<int> pair_cfg;  // per batch bucket: configuration of the fused launch, 0 = run the two layers separately; empty = not tuned

@@ -64,6 +64,7 @@ hipError_t launch_upload_slots(const SlotTab& in, const SlotTab& out, uint16_t* 
 // loader uses (see pack_weights in ee_api.cpp), zero padded.
 struct ConvArgs {
     const void* x; const void* w; const void* bias; const void* res; void* y;
+    const void* wo;      // the same weights as ready matrix-instruction operands [32 rows][step of 32 bytes][lane][16] (conv_skinny_kernel), or null
     const void* zeros;   // >= 16 readable zero bytes: what padding taps and rows past the batch read
     int M, H, W, Ci, Ho, Wo, Co;
     int kh, kw, stride, pad;   // pad: rows
@@ -77,9 +78,9 @@ struct ConvArgs {
     int Hp, Wp, kwp;     // mode 1: padded input dims and padded kernel width
     int shift, res_shift, lo, hi;
     float f_lo, f_hi;
-    int* gap_sums;       // not null (int8, conv_igemm_kernel, last layer of a segment): also add the per-sample channel sums of the output into gap_sums[n][Co]
-    const uint16_t* xs;  // not null: sample n of the input is slot xs[n] of x (device memory; conv_igemm_kernel only)
-    const uint16_t* ys;  // not null: sample n of the output is slot ys[n] of y (device memory; conv_igemm_kernel only)
+    int* gap_sums;       // not null (int8, conv_igemm_kernel or conv_skinny_kernel, last layer of a segment): also add the per-sample channel sums of the output into gap_sums[n][Co]
+    const uint16_t* xs;  // not null: sample n of the input is slot xs[n] of x (device memory; conv_igemm_kernel and conv_skinny_kernel only)
+    const uint16_t* ys;  // not null: sample n of the output is slot ys[n] of y (device memory; conv_igemm_kernel and conv_skinny_kernel only)
 };
 
 // Two chained convolutions in one launch (kernels_pair.hip): c2 is the first layer (its y and res are unused, its
@@ -145,6 +146,19 @@ bool conv_pair_supported(int es, int co2, int kh, int kw, int ci, int co3);
 bool conv_slab_supported(const ConvArgs& a, int es);
 template <int ES> hipError_t launch_conv_slab(const ConvArgs& a, int cfg, hipStream_t s);
 enum { EE_CFG_SLAB = 0x10000 };     // configuration words with this bit name the slab kernel
+// few output pixels: the reduction split over a workgroup's wavefronts, operands straight from global memory (kernels_skinny.hip)
+// Its configuration words are those whose fields ask for wavefront groups (bits 12-15: 2 = tiles of 32 pixels, 4 = of 16) with a step
+// field of 1 or 2 (bits 4-7: blocks of channels per workgroup), which the staged kernel does not have; bits 0-3: log2 of the
+// wavefronts + 1 (with ring field 2 in bits 8-11), or 4 with ring field 3 for 16 wavefronts.
+constexpr int skinny_cfg(int t, int tn, int lw) { return (lw < 4 ? lw + 1 : 4) | tn << 4 | (lw < 4 ? 2 : 3) << 8 | (t == 32 ? 2 : 4) << 12; }
+inline bool cfg_is_skinny(int cfg)
+{
+    const int step = (cfg >> 4) & 15, groups = cfg >> 12;
+    return cfg > 0 && (groups == 2 || groups == 4) && (step == 1 || step == 2);
+}
+bool conv_skinny_config_ok(int cfg);
+int conv_skinny_default(const ConvArgs& a, int es);    // configuration of an untuned launch it is the faster one for, else 0
+template <int ES> hipError_t launch_conv_skinny(const ConvArgs& a, int cfg, hipStream_t s);
 enum { EE_CFG_IR_BLOCK = 0x20000 }; // ee_time_layer: the fused inverted-residual block headed by the layer
 // streaming kernel for large, thin int8 layers (es = element bytes); hipErrorInvalidValue for a layer it does not cover
 bool conv_stream_supported(const ConvArgs& a, int es);

@@ -72,6 +72,30 @@ def test_int8_segments_and_heads_bit_exact(torch, ee, orc, name):
     eng.close()
 
 
+SKINNY = [0x2211, 0x2212, 0x2213, 0x2214, 0x2314, 0x2221, 0x2222, 0x2223, 0x2224, 0x4213, 0x4214, 0x4314]
+
+
+@pytest.mark.parametrize("cfg", SKINNY)
+def test_few_pixel_convolution_bit_exact(torch, ee, orc, cfg):
+    """The convolution kernel that splits the reduction over its wavefronts, forced on every matrix-core layer: reductions shorter than
+    the wavefronts and of odd length, channel counts that fill no block, slices, residuals, strides, rectangular kernels, the folded first layer."""
+    old = ee.tune_conv_tile(cfg)
+    try:
+        for blob in [W.load_net("zoo_i8"), W.load_net("resnet50_small_i8"), W.load_net("inception_small_i8"), W.random_net(3, W.DT_I8), W.random_net(11, W.DT_I8)]:
+            eng = ee.Engine(blob, 4)
+            for b in (3, 1):
+                act = W.input_pool(blob, b)
+                for s in range(blob.n_stages):
+                    say(f"[case] cfg {cfg:#x} {len(blob.ops)} layers segment {s} b={b}")
+                    ref = orc.stage_forward(blob, s, act)
+                    got = host(eng.stage_forward(s, dev(torch, act), ref.shape[1:]), ref)
+                    assert np.array_equal(got, ref), f"segment {s} b={b}: {np.count_nonzero(got != ref)} of {ref.size} differ"
+                    act = ref
+            eng.close()
+    finally:
+        ee.tune_conv_tile(old)
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_random_networks_bit_exact(torch, ee, orc, seed):
     """Generated networks (rectangular kernels, per-axis padding, strides, residuals, depthwise, pooling, concatenated
