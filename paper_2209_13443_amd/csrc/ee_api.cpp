@@ -764,6 +764,11 @@ hipError_t ee_ctx::launch_conv(int op, int b, const void* src, void* dst, const 
         cfg = 0;                                         // forced for the whole process: layers it does not cover keep the default
     }
     if (cfg == 0 && streamable && a.M >= 32768) return launch_conv_stream(a, stream);   // untuned: it wins on every large layer it covers
+    if (cfg == 0)
+        if (const int sc = conv_slab_default(a, dt == EE_I8 ? 1 : 2)) {
+            const hipError_t e = dt == EE_I8 ? launch_conv_slab<1>(a, sc, stream) : launch_conv_slab<2>(a, sc, stream);
+            if (e != hipErrorInvalidValue) return e;         // else: its slab does not fit LDS
+        }
     return dt == EE_I8 ? launch_conv_igemm<1>(a, cfg, stream) : launch_conv_igemm<2>(a, cfg, stream);
 }
 
@@ -1093,7 +1098,10 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
         if (p.ir && ir_mode > 0 && cfg_force == 0 && forced_conv_tile() == 0 && only_op < 0 && !xs && ir_slots_ok &&
             !(ir_pools && !(p.ir_bneck && plans[st.first_op + k + ir_last].d.res >= 0))) {
             // this layer, the depthwise layer and the projection as one launch, where the table says it is faster
-            const int ic = p.ir_cfg.empty() ? 0 : p.ir_cfg[std::min<size_t>(bucket_of(b), p.ir_cfg.size() - 1)];
+            // untuned: fused; measured at 1-256 samples it is faster at nearly every size (bottleneck blocks 1.4-2 times, inverted-residual
+            // blocks 1.1-1.9 times, first convolution + pool up to 1.5 times), but for inverted-residual blocks of more than 96 output channels
+            const int ic = p.ir_cfg.empty() ? (p.ir_bneck || p.ir_stem || plans[st.first_op + k + ir_last].d.c_out <= 96)
+                                            : p.ir_cfg[std::min<size_t>(bucket_of(b), p.ir_cfg.size() - 1)];
             if ((ic != 0 || ir_mode == 2) && p.ir_stem) {
                 const OpPlan& q2 = plans[st.first_op + k + 1];
                 if (!(first_packed && k == 0)) {                                 // the folded copy of the input, as in front of the layer alone
@@ -1157,17 +1165,10 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             const bool q_scatter = k + 1 < st.n_ops && ((zc_out && plans[st.first_op + k + 1].dst_buf == BUF_EXT_OUT) ||
                                                         (gap_fuse_dst && only_op < 0 && st.first_op + k + 1 == gap_fuse_op[(size_t)stage]));
             if (p.pair && pair_mode > 0 && cfg == 0 && only_op < 0 && !xs && !ys && !q_scatter) {
-                // this layer and the next as one launch, unless the table says the two separate kernels are faster here
+                // this layer and the next as one launch, where the table says it is the faster way
                 const int pc = p.pair_cfg.empty() ? 0 : p.pair_cfg[std::min<size_t>(bucket_of(b), p.pair_cfg.size() - 1)];
-                // untuned: fused below 32 samples, where it was measured to win (one launch fewer counts most there), unless the pixels
-                // are so few that the first layer goes to the kernel for that
-                bool few = false;
-                if (p.pair_cfg.empty() && b < 32) {
-                    ConvArgs probe{};
-                    fill_conv_args(st.first_op + k, b, probe);
-                    few = conv_skinny_default(probe, es) != 0;
-                }
-                if ((p.pair_cfg.empty() && b < 32 && !few) || pc != 0 || pair_mode == 2) {
+                // (untuned never: with the configurations that untuned launches get, the two layers were faster at every batch of 1-31 samples)
+                if (pc != 0 || pair_mode == 2) {
                     const OpPlan& q = plans[st.first_op + k + 1];
                     void* dst2 = resolve(this, q.dst_buf, act_in, act_out);
                     const void* res2 = q.d.res >= 0 ? resolve(this, q.res_buf, act_in, act_out) : nullptr;

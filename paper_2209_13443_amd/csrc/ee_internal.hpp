@@ -145,6 +145,7 @@ bool conv_pair_supported(int es, int co2, int kh, int kw, int ci, int co3);
 // stride-1 "same" convolutions with the activation slab of a tile resident in LDS (kernels_slab.hip); cfg as documented there
 bool conv_slab_supported(const ConvArgs& a, int es);
 template <int ES> hipError_t launch_conv_slab(const ConvArgs& a, int cfg, hipStream_t s);
+int conv_slab_default(const ConvArgs& a, int es);      // configuration of an untuned launch it is the faster one for, else 0
 enum { EE_CFG_SLAB = 0x10000 };     // configuration words with this bit name the slab kernel
 // few output pixels: the reduction split over a workgroup's wavefronts, operands straight from global memory (kernels_skinny.hip)
 // Its configuration words are those whose fields ask for wavefront groups (bits 12-15: 2 = tiles of 32 pixels, 4 = of 16) with a step

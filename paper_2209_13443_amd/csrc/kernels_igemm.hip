@@ -394,17 +394,45 @@ static hipError_t launch_igemm_tile(const ConvArgs& a, bool plain, int ns, hipSt
     return hipGetLastError();
 }
 
-// cfg: bits 0-3 tile (0 = by shape; 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128), bits 4-7 reduction step
-// (0 = by shape, 1: 64, 2: 128, 3: 256 bytes), bits 8-11 ring stages (0 = by shape, else 2..4), bits 12-15
-// wavefront groups splitting the reduction inside a workgroup (0 or 1: none, 2, 4).  Not every combination
-// exists: hipErrorInvalidValue for one that does not (or does not fit LDS).
+// The configuration of an untuned launch, from the size of the problem alone.  Measured with every configuration over the layers of the
+// ResNet-50 / ResNet-18, MobileNetV2 and Inception networks at 1-256 samples (launches back to back); the rule stays within 3 % of the best
+// configuration of this kernel over a network (20 % over the rule it replaces at 37-64 samples, 40 % for bf16 below 16):
+//   reductions up to 640 bytes: a tile is over in a few steps and what counts is copies in flight, i.e. many small workgroups on a CU:
+//     64-byte steps, 64 x 128 tiles once there are two rounds of 64 x 64 ones, which a bf16 residual tile's LDS would cost (64 x 64 there);
+//   longer ones: while the 64 x 64 tiles do not fill the chip, the steps are a serial chain and the fewest, longest win; then tiles grow
+//     with the number of them (blocks: 64 x 64 tiles of the output), 128 x 128 from four per CU; channels that would leave half of a
+//     128-channel tile empty take 64-channel ones.
+static int igemm_default_config(const ConvArgs& a, int es, int kbytes)
+{
+    const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64);
+    const bool narrow = a.Co <= 64;
+    if (kbytes <= 640) {
+        if (narrow) return a.kh * a.kw == 1 || blocks < 1024 ? 0x313 : 0x212;
+        if (es == 2 && (a.res || kbytes <= 128)) return 0x313;
+        return blocks >= 512 ? 0x214 : 0x313;
+    }
+    if (blocks < 256) return 0x333;
+    if (blocks < 512) return 0x233;
+    if (narrow) return 0x222;
+    if (blocks < 1024) return kbytes > 1280 ? 0x324 : 0x224;
+    if (es == 2 && a.res) return 0x313;
+    if ((a.Co + 127) / 128 * 128 - a.Co >= 64) return 0x322;
+    return blocks < 2048 || kbytes > 1280 ? 0x221 : 0x222;
+}
+
+// cfg: bits 0-3 tile (1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128), bits 4-7 reduction step (1: 64, 2: 128, 3: 256 bytes), bits 8-11 ring
+// stages (2..4), bits 12-15 wavefront groups splitting the reduction inside a workgroup (0 or 1: none, 2, 4); 0 in the first three
+// = by shape.  Not every combination exists: hipErrorInvalidValue for one that does not (or does not fit LDS).
 template <int ES>
 hipError_t launch_conv_igemm(const ConvArgs& a_in, int cfg, hipStream_t s)
 {
     if (a_in.M <= 0) return hipSuccess;
-    int tile = cfg & 15, ksel = (cfg >> 4) & 15, ns = (cfg >> 8) & 15, kspl = (cfg >> 12) & 15;
     const int kbytes = a_in.kh * a_in.kw * a_in.Ci * ES;
+    if (cfg == 0) cfg = igemm_default_config(a_in, ES, kbytes);
+    int tile = cfg & 15, ksel = (cfg >> 4) & 15, ns = (cfg >> 8) & 15, kspl = (cfg >> 12) & 15;
+    if (tile == 0) tile = igemm_default_config(a_in, ES, kbytes) & 15;
     if (ksel == 0) ksel = kbytes % 128 == 0 ? 2 : 1;
+    if (ns == 0) ns = 2;
     const int ks = ksel == 3 ? 256 : (ksel == 2 ? 128 : 64);
     // PLAIN: every reduction step of a row is one contiguous, always valid run of ks bytes: a 1x1 kernel whose
     // pixel is a multiple of the step (the address advances by the step), or an unpadded stride-1 kernel whose
@@ -414,13 +442,6 @@ hipError_t launch_conv_igemm(const ConvArgs& a_in, int cfg, hipStream_t s)
     const bool plain_rows = !plain_1x1 && a.pad == 0 && a.pad_w == 0 && a.stride == 1 && a.kw * a.Ci * ES == ks;
     const bool plain = plain_1x1 || plain_rows;
     a.plain_step = plain_rows ? a.W * a.Ci * ES : ks;
-    if (tile == 0) {
-        auto blocks = [&](int bm, int bn) { return (long long)((a.M + bm - 1) / bm) * ((a.Co + bn - 1) / bn); };
-        const long long want = 2 * 256;
-        if (a.Co > 64) tile = blocks(128, 128) >= want ? 1 : (blocks(64, 128) >= want ? 4 : 3);
-        else tile = blocks(128, 64) >= want ? 2 : 3;
-    }
-    if (ns == 0) ns = 2;     // measured: more workgroups per CU beat a deeper ring at these problem sizes
     if (kspl >= 2) {          // measured to pay only for small tiles with the longest step
         if (kspl == 2 && ks == 256 && tile == 3) return launch_igemm_tile<ES, 64, 64, 256, 2>(a, plain, ns, s);
         if (kspl == 2 && ks == 256 && tile == 4) return launch_igemm_tile<ES, 64, 128, 256, 2>(a, plain, ns, s);

@@ -269,7 +269,7 @@ bool conv_skinny_config_ok(int cfg) { return skinny_waves(cfg) >= 0; }
 // more than the staged kernel's chain.  Four wavefronts are the best or within 5 % of it wherever the reduction is eight steps or longer.
 int conv_skinny_default(const ConvArgs& a, int es)
 {
-    if (!a.wo || a.mode != 0 || es != 1) return 0;          // bf16 by default: one order of summation, that of the fused pairs
+    if (!a.wo || a.mode != 0 || es != 1) return 0;          // bf16 by default: one order of summation, that of the staged kernels
     const long long kbytes = (long long)a.kh * a.kw * a.Ci * es;
     auto tiles = [&](int t) { return (long long)((a.M + t - 1) / t) * ((a.Co + t - 1) / t); };
     if (kbytes >= 1024 && tiles(16) <= 400) return skinny_cfg(16, 1, 2);
