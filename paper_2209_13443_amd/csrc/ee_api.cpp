@@ -1243,6 +1243,10 @@ int ee_ctx::run_head(int stage, int b, const void* act, float thr, int32_t* labe
         a.host_out = h_out; a.tag = ee::outcome_tag(++seq); head_b = b;
     }
     const double act_bytes = (double)b * a.HW * a.C * es;
+    if (head_small(a, dt, pooled)) {
+        const double by = (pooled ? 8.0 * b * a.C : act_bytes) + (double)a.C * a.n_cls * es + 17.0 * b;
+        return timed(EE_K_SOFTMAX, 2.0 * b * a.C * a.n_cls, by, [&] { return launch_head_small(a, dt, pooled, stream); }) == hipSuccess ? EE_OK : EE_ERR_DEVICE;
+    }
     if (!pooled && timed(EE_K_GAP, 0.0, act_bytes + 4.0 * b * a.C, [&] { return launch_head_gap(a, dt, stream); }) != hipSuccess) return EE_ERR_DEVICE;
     if (timed(EE_K_FC, 2.0 * b * a.C * a.n_cls, (double)a.C * a.n_cls * es + 4.0 * b * (a.C + a.n_cls),
               [&] { return launch_head_fc(a, dt, stream); }) != hipSuccess) return EE_ERR_DEVICE;

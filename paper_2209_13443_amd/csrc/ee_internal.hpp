@@ -254,6 +254,9 @@ int head_gap_splits(int B, int HW);
 hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s);
 hipError_t launch_head_fc(const HeadArgs& a, int dtype, hipStream_t s);
 hipError_t launch_head_softmax(const HeadArgs& a, int dtype, hipStream_t s);
+// all of it in one launch, for heads small enough (pooled: a.sums holds the sums already)
+bool head_small(const HeadArgs& a, int dtype, bool pooled);
+hipError_t launch_head_small(const HeadArgs& a, int dtype, bool pooled, hipStream_t s);
 
 // Stable compaction + refill: the survivors of src[b_act], then the b_incr samples of refill.  dst_off: first destination slot
 // of the survivors; ring_rows > 0: dst is a ring of that many slots and destination slots wrap around its end.

@@ -398,6 +398,32 @@ def test_autotuned_configuration_table_keeps_results(torch, ee, orc):
         eng.close()
 
 
+HEAD_SHAPES = [(1, 1, 16, 1), (3, 5, 48, 17), (8, 8, 16, 256), (16, 16, 128, 100), (2, 2, 2048, 16), (16, 17, 128, 100), (4, 4, 128, 257)]   # the last two: past the limits
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("h, w, c, n_cls", HEAD_SHAPES)
+def test_small_exit_heads(torch, ee, orc, h, w, c, n_cls, dtype):
+    """Heads around the limits of the one-launch kernel: fewer classes than a group of lanes and 256 of them, one pixel, the most channels."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8 if dtype == "i8" else W.DT_BF16, h, w, c, n_cls)
+    net.begin_stage()
+    net.end_stage(net.maxpool(0, 3, 1, 1))
+    blob = N._assemble(net, net.dtype, 7)
+    eng = ee.Engine(blob, 5)
+    act = W.input_pool(blob, 5)
+    for b in (5, 1):
+        lab, conf, score, flag, logits = orc.exit_head(blob, 0, act[:b], 0.5, want_logits=True)
+        glab, gconf, gscore, gflag = eng.exit_head(0, dev(torch, act[:b]), 0.5)
+        glog = eng.last_logits(b, n_cls)
+        if dtype == "i8":
+            assert np.array_equal(glog, logits) and np.array_equal(glab.cpu().numpy(), lab) and np.array_equal(gscore.cpu().numpy(), score)
+            assert np.array_equal(gflag.cpu().numpy(), flag) and np.allclose(gconf.cpu().numpy(), conf, rtol=1e-6, atol=0)
+        else:
+            assert np.all(np.abs(glog - logits) <= 1e-3 * np.abs(logits).max() + 1e-6) and np.all(np.abs(gconf.cpu().numpy() - conf) <= 1e-3)
+    eng.close()
+
+
 def test_thresholds_zero_and_above_one(torch, ee, orc):
     blob = W.load_net("tiny_i8")
     eng = ee.Engine(blob, 8)
