@@ -727,6 +727,9 @@ void ee_ctx::fill_conv_args(int op, int b, ConvArgs& a) const
     a.shift = d.shift; a.res_shift = d.res_shift; a.lo = d.lo; a.hi = d.hi; a.f_lo = d.f_lo; a.f_hi = d.f_hi;
 }
 
+// untuned layers that the streaming kernel covers: it wins on every large one; a reduction of more than two blocks pays later (measured)
+static bool stream_by_default(const ConvArgs& a) { return a.M >= (a.kh * a.kw * a.Ci > 64 ? 196608 : 32768); }
+
 hipError_t ee_ctx::launch_conv(int op, int b, const void* src, void* dst, const void* res, int cfg, const uint16_t* xs, const uint16_t* ys, int32_t* gap_sums)
 {
     const OpPlan& p = plans[op];
@@ -763,7 +766,7 @@ hipError_t ee_ctx::launch_conv(int op, int b, const void* src, void* dst, const 
         (void)hipGetLastError();
         cfg = 0;                                         // forced for the whole process: layers it does not cover keep the default
     }
-    if (cfg == 0 && streamable && a.M >= 32768) return launch_conv_stream(a, stream);   // untuned: it wins on every large layer it covers
+    if (cfg == 0 && streamable && stream_by_default(a)) return launch_conv_stream(a, stream);
     if (cfg == 0)
         if (const int sc = conv_slab_default(a, dt == EE_I8 ? 1 : 2)) {
             const hipError_t e = dt == EE_I8 ? launch_conv_slab<1>(a, sc, stream) : launch_conv_slab<2>(a, sc, stream);
@@ -803,36 +806,55 @@ hipError_t ee_ctx::launch_pair(int op, int b, const void* src, void* dst, const 
 }
 
 // ---- per-(layer, B_act) kernel configuration table ----------------------------------------------------
-// The GPU face of the paper's run-time configuration look-up (Sec. III-A: one entry per layer and active
-// batch size, fetched at run time): for every matrix-core convolution and every batch bucket 2^k the
-// candidate tilings / reduction steps / ring depths are timed on the workspace buffers and the fastest
-// is kept.  Results never depend on the choice.
+// A candidate is timed as it will run: behind the layer in front of it and with the L2 full of something else (a fill of twice its
+// size), by the time stamps of its own dispatch.  Launched back to back, a layer finds its weights and inputs in the L2 and two-stage
+// rings with many small workgroups win that then wait for the last-level cache at every step of the real pass (14x14, 1x1, 1024 -> 256
+// int8 at 64 samples: 7.4 us back to back, 12 us in the network).
+constexpr size_t EE_TUNE_EVICT_BYTES = 64u << 20;
 extern "C" int ee_autotune(ee_ctx* ctx, int reps)
 {
     if (!ctx || reps < 1 || reps > 1000) return EE_ERR_ARG;
     ctx->bind_lane(0);
     const bool was = ctx->profiling;
+    const size_t prof_was = ctx->prof_used;
     ctx->profiling = false;
-    hipEvent_t e0, e1;
-    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return EE_ERR_DEVICE;
+    void* evict = nullptr;
+    if (hipMalloc(&evict, EE_TUNE_EVICT_BYTES) != hipSuccess) { ctx->profiling = was; return EE_ERR_DEVICE; }
     const int es = ctx->net.elem_bytes();
     int rc = EE_OK;
     std::vector<int> buckets;
     for (int k = 0; (1 << k) < 2 * ctx->b_max; ++k) buckets.push_back(std::min(1 << k, ctx->b_max));
-    // ms of `reps` launches back to back behind one that warms up; negative when the launch does not exist here (or rc is set)
-    auto time_launches = [&](int n, auto&& launch) -> float {
-        if (launch()) { (void)hipGetLastError(); return -1.f; }
-        hipEventRecord(e0, ctx->stream);
-        for (int r = 0; r < n; ++r) launch();
-        hipEventRecord(e1, ctx->stream);
-        if (hipEventSynchronize(e1) != hipSuccess) { rc = EE_ERR_DEVICE; return -1.f; }
-        float ms = 0.f;
-        hipEventElapsedTime(&ms, e0, e1);
-        return ms;
+    // ms of `launch`'s kernels, the best of n times; negative when the launch does not exist here (or rc is set)
+    auto time_launch = [&](int n, auto&& before, auto&& launch) -> float {
+        if (launch()) { (void)hipGetLastError(); return -1.f; }          // also warms up
+        std::vector<size_t> end;
+        for (int r = 0; r < n; ++r) {
+            if (launch_fill_zero(evict, EE_TUNE_EVICT_BYTES, ctx->stream) != hipSuccess) { rc = EE_ERR_DEVICE; return -1.f; }
+            before();
+            ctx->profiling = true;
+            launch();
+            ctx->profiling = false;
+            end.push_back(ctx->prof_used);
+        }
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess) { rc = EE_ERR_DEVICE; return -1.f; }
+        float best = 1e30f;
+        size_t i = prof_was;
+        for (const size_t e : end) {
+            float sum = 0.f, ms = 0.f;
+            for (; i < e; ++i)
+                if (hipEventElapsedTime(&ms, ctx->prof[i].e0, ctx->prof[i].e1) == hipSuccess) sum += ms;
+            best = std::min(best, sum);
+        }
+        ctx->prof_used = prof_was;
+        return best;
     };
-    std::vector<std::vector<float>> best_time(ctx->plans.size());       // per layer and bucket: ms of `reps` launches of the best configuration
+    std::vector<std::vector<float>> best_time(ctx->plans.size());       // per layer and bucket: ms of the best configuration
     for (size_t s = 0; s < ctx->net.stages.size() && !rc; ++s) {
         const StageDesc& st = ctx->net.stages[s];
+        // what runs in front of layer k, with the configurations found for it
+        auto layer_before = [&](int k, int b) {
+            return [=] { if (k > 0) ctx->run_stage((int)s, b, ctx->in_buf[s], ctx->out_buf[s], false, st.first_op + k - 1); };
+        };
         for (int k = 0; k < st.n_ops && !rc; ++k) {
             OpPlan& p = ctx->plans[st.first_op + k];
             if (!p.cfg_table()) continue;
@@ -864,21 +886,26 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                             const int cfg = skinny_cfg(shape < 2 ? 32 : 16, shape == 1 ? 2 : 1, lw);
                             if (conv_skinny_config_ok(cfg) && (kbytes + 31) / 32 >= 1 << lw) cands.push_back(cfg);
                         }
+                const auto before = layer_before(k, buckets[bi]);
+                auto timed_cfg = [&](int n, int cfg) {
+                    return time_launch(n, before, [&] {
+                        return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] { return ctx->launch_conv(st.first_op + k, buckets[bi], src, dst, res, cfg); }) == hipSuccess ? EE_OK : EE_ERR_ARG;
+                    });
+                };
                 std::vector<std::pair<float, int>> timed;                               // candidates that exist, with their times
                 for (const int cfg : cands) {
-                    const float ms = time_launches(reps, [&] { return ctx->launch_conv(st.first_op + k, buckets[bi], src, dst, res, cfg) == hipSuccess ? EE_OK : EE_ERR_ARG; });
+                    const float ms = timed_cfg(1, cfg);
                     if (rc) break;
                     if (ms >= 0.f) timed.emplace_back(ms, cfg);
                 }
-                // launches of a few microseconds are issued hardly faster than they run, and a hiccup of the host counts as kernel time:
                 // the fastest few are timed again and each keeps its best
                 std::sort(timed.begin(), timed.end());
                 if (timed.size() > 6) timed.resize(6);
-                for (int again = 0; again < 3 && !rc; ++again)
-                    for (auto& t : timed) {
-                        const float ms = time_launches(reps, [&] { return ctx->launch_conv(st.first_op + k, buckets[bi], src, dst, res, t.second) == hipSuccess ? EE_OK : EE_ERR_ARG; });
-                        if (ms >= 0.f) t.first = std::min(t.first, ms);
-                    }
+                for (auto& t : timed) {
+                    if (rc) break;
+                    const float ms = timed_cfg(reps, t.second);
+                    if (ms >= 0.f) t.first = std::min(t.first, ms);
+                }
                 for (const auto& t : timed)
                     if (t.first < best_ms) { best_ms = t.first; best[bi] = t.second; }
             }
@@ -897,13 +924,12 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 float best_ms = best_time[st.first_op + k][bi] + best_time[st.first_op + k + 1][bi];
                 for (int tile = 1; tile <= 2; ++tile)
                     for (int ksel = 1; ksel <= 2; ++ksel)
-                        for (int ns = 2; ns <= 4; ++ns) {
+                        for (int ns = 2; ns <= 4 && !rc; ++ns) {
                             const int cfg = tile | (ksel << 4) | (ns << 8);
-                            for (int again = 0; again < 2 && !rc; ++again) {
-                                const float ms = time_launches(reps, [&] { return ctx->launch_pair(st.first_op + k, buckets[bi], src, dst, res, cfg) == hipSuccess ? EE_OK : EE_ERR_ARG; });
-                                if (ms < 0.f) break;
-                                if (ms < best_ms) { best_ms = ms; best[bi] = cfg; }
-                            }
+                            const float ms = time_launch(reps, layer_before(k, buckets[bi]), [&] {
+                                return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] { return ctx->launch_pair(st.first_op + k, buckets[bi], src, dst, res, cfg); }) == hipSuccess ? EE_OK : EE_ERR_ARG;
+                            });
+                            if (ms >= 0.f && ms < best_ms) { best_ms = ms; best[bi] = cfg; }
                         }
             }
             if (!rc) p.pair_cfg = best;
@@ -926,15 +952,10 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                         ctx->ir_mode = fused ? 2 : (p.ir_sc ? 1 : 0);
                         p.ir_cfg.assign(buckets.size(), 0);                  // table mode: this head stays separate, the block behind it as tuned
                         if (fused || !p.ir_sc) p.ir_cfg.clear();
-                        auto block = [&]() -> int {                          // the block alone: its head runs all its layers when fused
+                        ms[fused] = time_launch(reps, [] {}, [&]() -> int {   // the block alone: its head runs all its layers when fused
                             return ctx->run_stage((int)s, buckets[bi], ctx->in_buf[s], ctx->out_buf[s], false, -2 - (st.first_op + k));
-                        };
-                        ms[fused] = 1e30f;
-                        for (int again = 0; again < 3 && !rc; ++again) {
-                            const float t = time_launches(reps, block);
-                            if (t < 0.f && !rc) rc = EE_ERR_DEVICE;
-                            if (!rc) ms[fused] = std::min(ms[fused], t);
-                        }
+                        });
+                        if (ms[fused] < 0.f && !rc) rc = EE_ERR_DEVICE;
                     }
                     best[bi] = ms[1] < ms[0] ? 1 : 0;
                 }
@@ -943,8 +964,7 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
             }
         }
     ctx->ir_mode = ir_was;
-    hipEventDestroy(e0);
-    hipEventDestroy(e1);
+    hipFree(evict);
     ctx->profiling = was;
     return rc;
 }
@@ -1186,7 +1206,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 ConvArgs probe{};
                 fill_conv_args(st.first_op + k, b, probe);
                 probe.res = res;
-                if (conv_stream_supported(probe, es) && ((cfg & 15) == 7 || probe.M >= 32768)) cls = EE_K_CONV_STREAM;
+                if (conv_stream_supported(probe, es) && ((cfg & 15) == 7 || stream_by_default(probe))) cls = EE_K_CONV_STREAM;
             }
             e = timed(cls, ops, bytes, [&] { return launch_conv(st.first_op + k, b, src, dst, res, cfg, xs, ys, gap_dst); }, st.first_op + k);
             if (gap_dst && e == hipSuccess) gap_fused = true;

@@ -395,8 +395,8 @@ static hipError_t launch_igemm_tile(const ConvArgs& a, bool plain, int ns, hipSt
 }
 
 // The configuration of an untuned launch, from the size of the problem alone.  Measured with every configuration over the layers of the
-// ResNet-50 / ResNet-18, MobileNetV2 and Inception networks at 1-256 samples (launches back to back); the rule stays within 3 % of the best
-// configuration of this kernel over a network (20 % over the rule it replaces at 37-64 samples, 40 % for bf16 below 16):
+// ResNet-50 / ResNet-18, MobileNetV2 and Inception networks at 1-256 samples, each launch behind the layer in front of it and with a cold
+// L2; the rule stays within 3-8 % of the best configuration over a network:
 //   reductions up to 640 bytes: a tile is over in a few steps and what counts is copies in flight, i.e. many small workgroups on a CU:
 //     64-byte steps, 64 x 128 tiles once there are two rounds of 64 x 64 ones, which a bf16 residual tile's LDS would cost (64 x 64 there);
 //   longer ones: while the 64 x 64 tiles do not fill the chip, the steps are a serial chain and the fewest, longest win; then tiles grow
@@ -407,14 +407,15 @@ static int igemm_default_config(const ConvArgs& a, int es, int kbytes)
     const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64);
     const bool narrow = a.Co <= 64;
     if (kbytes <= 640) {
+        if (kbytes > 256 && blocks < 256) return 0x423;
         if (narrow) return a.kh * a.kw == 1 || blocks < 1024 ? 0x313 : 0x212;
         if (es == 2 && (a.res || kbytes <= 128)) return 0x313;
         return blocks >= 512 ? 0x214 : 0x313;
     }
     if (blocks < 256) return 0x333;
-    if (blocks < 512) return 0x233;
+    if (blocks < 512) return kbytes > 1280 ? 0x334 : 0x323;
     if (narrow) return 0x222;
-    if (blocks < 1024) return kbytes > 1280 ? 0x324 : 0x224;
+    if (blocks < 1024) return kbytes > 1280 ? 0x324 : 0x322;
     if (es == 2 && a.res) return 0x313;
     if ((a.Co + 127) / 128 * 128 - a.Co >= 64) return 0x322;
     return blocks < 2048 || kbytes > 1280 ? 0x221 : 0x222;

@@ -264,17 +264,19 @@ static int skinny_waves(int cfg)
 
 bool conv_skinny_config_ok(int cfg) { return skinny_waves(cfg) >= 0; }
 
-// Untuned: the configuration of a launch this kernel is the faster one for, else 0.  Measured over the layers of ResNet-50 at 1, 3, 5 and 8
-// samples: with up to 400 workgroups (one or two per CU) it wins or draws; beyond, operands that are used once per load cost
-// more than the staged kernel's chain.  Four wavefronts are the best or within 5 % of it wherever the reduction is eight steps or longer.
+// Untuned: the configuration of a launch this kernel is the faster one for, else 0.  Measured over the layers of the networks at 1-64
+// samples with a cold L2: up to 400 tiles of 32 x 32 (one or two per CU) it wins or draws; beyond, operands that are used once per load
+// cost more than the staged kernel's chain.  16 x 16 tiles while those of 32 would leave half of the chip idle; four wavefronts are the
+// best or within 5 % of it, but for long reductions in a full round, where eight and twice the channels per activation load are.
 int conv_skinny_default(const ConvArgs& a, int es)
 {
     if (!a.wo || a.mode != 0 || es != 1) return 0;          // bf16 by default: one order of summation, that of the staged kernels
     const long long kbytes = (long long)a.kh * a.kw * a.Ci * es;
-    auto tiles = [&](int t) { return (long long)((a.M + t - 1) / t) * ((a.Co + t - 1) / t); };
-    if (kbytes >= 1024 && tiles(16) <= 400) return skinny_cfg(16, 1, 2);
-    if (tiles(32) <= 400) return skinny_cfg(32, 1, kbytes >= 256 ? 2 : 1);
-    return 0;
+    const long long tiles = (long long)((a.M + 31) / 32) * ((a.Co + 31) / 32);
+    if (tiles > (kbytes > 128 ? 400 : 200)) return 0;
+    if (tiles <= 100 && kbytes > 128) return skinny_cfg(16, 1, 2);
+    if (tiles > 200 && kbytes > 640) return skinny_cfg(32, 2, 3);
+    return skinny_cfg(32, 1, 2);
 }
 
 template <int ES>

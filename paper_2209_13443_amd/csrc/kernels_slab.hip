@@ -280,7 +280,7 @@ int conv_slab_default(const ConvArgs& a, int es)
 {
     const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64), kbytes = (long long)a.kh * a.kw * a.Ci * es;
     if (blocks < 512 || kbytes < 1024 || a.Ci * es > 256 || !conv_slab_supported(a, es)) return 0;
-    return blocks < 1024 && kbytes > 1280 ? 0x231 : es == 2 ? 0x222 : 0x221;
+    return blocks < 1024 && kbytes > 1280 ? 0x232 : es == 2 ? 0x222 : 0x221;
 }
 
 template <int ES, int BM, int BN, int KS>
