@@ -26,7 +26,7 @@ namespace ee {
 struct BnTile {
     int tiles_x, tiles_y;      // tiles of 8 x 8 output pixels per image
     int total;                 // tiles in all
-    int per_xcd, nslots;       // tiles per XCD (a contiguous run), workgroups per XCD
+    int per_xcd, nslots;       // most tiles of an XCD (a contiguous run), workgroups per XCD
     int xp, x_bytes;           // bytes per staged input pixel, per buffer of staged pixels
     int gap_rows;              // pooling: rows of 256 channel sums in LDS, one per tile of a workgroup
 };
@@ -54,10 +54,10 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool front = wave < 4;
     const int xcd = (int)(blockIdx.x & 7), slot = (int)(blockIdx.x >> 3);
-    const int cnt = min(t.per_xcd, t.total - xcd * t.per_xcd);         // tiles of this XCD
+    const int u_xcd = xcd_first(xcd, t.total), cnt = xcd_first(xcd + 1, t.total) - u_xcd;      // tiles of this XCD
     if (cnt <= slot) return;                                           // whole workgroup: no barrier is skipped by a part of it
     const int T = (cnt - slot + t.nslots - 1) / t.nslots;              // tiles of this workgroup: u0, u0 + nslots, ...
-    const int u0 = xcd * t.per_xcd + slot;
+    const int u0 = u_xcd + slot;
     const int tpi = t.tiles_x * t.tiles_y;
     int* const l_b1 = (int*)bn_lds;
     int* const l_b2 = l_b1 + 64;

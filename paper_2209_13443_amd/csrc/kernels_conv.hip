@@ -59,7 +59,7 @@ __device__ __forceinline__ int requant_i8(int t, int shift, int lo, int hi)
 // channel tiles of a pixel tile run back to back on the same XCD, so the activation rows a tile
 // reads (and the halo rows its neighbours share) stay in one L2.
 template <int ES, int BM, int BN, int WM, int WN, int MODE>
-__global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a, int gm, int gn, int per_xcd)
+__global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a, int gm, int gn)
 {
     constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN;
     static_assert(WAVES_M * WAVES_N == 4, "4 wavefronts per workgroup");
@@ -70,8 +70,8 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a, int gm, int 
     __shared__ __attribute__((aligned(16))) unsigned char lds[kMainBytes > kEpiBytes ? kMainBytes : kEpiBytes];
 
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int mt = xcd * per_xcd + slot / gn, nt = slot % gn;
-    if (mt >= gm || slot / gn >= per_xcd) return;
+    const int mt = xcd_unit((unsigned)(slot / gn << 3 | xcd), gm), nt = slot % gn;
+    if (mt < 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm0 = (wave % WAVES_M) * WM, wn0 = (wave / WAVES_M) * WN;
     const int m0 = mt * BM, n0 = nt * BN;
@@ -275,12 +275,12 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a, int gm, int 
 template <int ES, int BM, int BN, int WM, int WN>
 static hipError_t launch_tile(const ConvArgs& a, hipStream_t s)
 {
-    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, per_xcd = (gm + 7) / 8;
-    dim3 grid((unsigned)(8 * per_xcd * gn));
+    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN;
+    dim3 grid(xcd_grid(gm) * (unsigned)gn);
     if (a.mode == 0)
-        EE_LAUNCH((conv_mfma_kernel<ES, BM, BN, WM, WN, 0>), grid, dim3(256), 0, s, a, gm, gn, per_xcd);
+        EE_LAUNCH((conv_mfma_kernel<ES, BM, BN, WM, WN, 0>), grid, dim3(256), 0, s, a, gm, gn);
     else
-        EE_LAUNCH((conv_mfma_kernel<ES, BM, BN, WM, WN, 1>), grid, dim3(256), 0, s, a, gm, gn, per_xcd);
+        EE_LAUNCH((conv_mfma_kernel<ES, BM, BN, WM, WN, 1>), grid, dim3(256), 0, s, a, gm, gn);
     return hipGetLastError();
 }
 
@@ -444,10 +444,12 @@ __global__ __launch_bounds__(256) void space_to_depth_kernel(const T* x, T* y, c
 // pinned host memory, where every read crosses the bus) serves larger batches.
 struct IdTab { int32_t id[256]; };
 template <typename T, int RS>
-__global__ __launch_bounds__(256) void space_to_depth_rows_kernel(IdTab, const T* x, T* y, const int32_t* gather, int by_value, int H, int W, int C, int Hs, int Ws, int pad)
+__global__ __launch_bounds__(256) void space_to_depth_rows_kernel(IdTab, const T* x, T* y, const int32_t* gather, int by_value, int B, int H, int W, int C, int Hs, int Ws, int pad)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char s2d_lds[];
-    const int ys0 = blockIdx.x * RS, n = blockIdx.y;
+    const int per_sample = (Hs + RS - 1) / RS, unit = xcd_unit(blockIdx.x, B * per_sample);
+    if (unit < 0) return;
+    const int n = unit / per_sample, ys0 = (unit - n * per_sample) * RS;
     const __attribute__((address_space(4))) int* tab = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
     const long long row = by_value ? tab[n] : (gather ? gather[n] : n);
     const int row_words = W * C * (int)sizeof(T) / 4;
@@ -491,11 +493,13 @@ __global__ __launch_bounds__(256) void space_to_depth_rows_kernel(IdTab, const T
 // neighbouring super-pixels: four pixels are 12 contiguous bytes of an image row, read as four dwords around them, shifted into place
 // and spread to 4 bytes per pixel with byte permutes.
 template <int RS>
-__global__ __launch_bounds__(256) void space_to_depth_rows_c3_kernel(IdTab, const signed char* x, signed char* y, const int32_t* gather, int by_value, int H, int W, int Hs, int Ws, int pad)
+__global__ __launch_bounds__(256) void space_to_depth_rows_c3_kernel(IdTab, const signed char* x, signed char* y, const int32_t* gather, int by_value, int B, int H, int W, int Hs, int Ws, int pad)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char s2d3_lds[];
     typedef int v4i_ __attribute__((ext_vector_type(4)));
-    const int ys0 = blockIdx.x * RS, n = blockIdx.y, tid = threadIdx.x;
+    const int tid = threadIdx.x, per_sample = (Hs + RS - 1) / RS, unit = xcd_unit(blockIdx.x, B * per_sample);
+    if (unit < 0) return;
+    const int n = unit / per_sample, ys0 = (unit - n * per_sample) * RS;
     const __attribute__((address_space(4))) int* tab = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
     const long long row = by_value ? tab[n] : (gather ? gather[n] : n);
     const int row_bytes = 3 * W, pitch = row_bytes + 64, row_chunks = row_bytes >> 4, pitch_chunks = pitch >> 4;
@@ -543,19 +547,19 @@ hipError_t launch_space_to_depth(const void* x, void* y, const int32_t* gather, 
     const size_t row_bytes = (size_t)W * C * es;
     constexpr int RS = 4;
     if (row_bytes % 4 == 0 && ((size_t)H * row_bytes) % 4 == 0 && 2 * RS * row_bytes <= 64 * 1024 && B <= 65535) {
-        const dim3 grid((unsigned)((Hs + RS - 1) / RS), (unsigned)B);
+        const dim3 grid(xcd_grid((long long)((Hs + RS - 1) / RS) * B));
         IdTab tab{};
         const bool host_ids = gather_on_host && gather && B <= 256;      // ids the host can read: by value
         if (host_ids) std::memcpy(tab.id, gather, sizeof(int32_t) * (size_t)B);
         if (dtype == EE_I8 && C == 3 && row_bytes % 16 == 0 && ((uintptr_t)x & 15) == 0 && pad >= 0 && pad <= 5 && RS * ((Ws + 1) / 2) <= 256 &&
             2 * RS * (row_bytes + 64) <= 64 * 1024 && Ws <= (W + 2 * pad + 1) / 2 + 1) {
-            EE_LAUNCH((space_to_depth_rows_c3_kernel<RS>), grid, dim3(256), 2 * RS * (row_bytes + 64), s, tab, (const signed char*)x, (signed char*)y, gather, (int)host_ids, H, W, Hs, Ws, pad);
+            EE_LAUNCH((space_to_depth_rows_c3_kernel<RS>), grid, dim3(256), 2 * RS * (row_bytes + 64), s, tab, (const signed char*)x, (signed char*)y, gather, (int)host_ids, B, H, W, Hs, Ws, pad);
             return hipGetLastError();
         }
         if (dtype == EE_I8)
-            EE_LAUNCH((space_to_depth_rows_kernel<signed char, RS>), grid, dim3(256), 2 * RS * row_bytes, s, tab, (const signed char*)x, (signed char*)y, gather, (int)host_ids, H, W, C, Hs, Ws, pad);
+            EE_LAUNCH((space_to_depth_rows_kernel<signed char, RS>), grid, dim3(256), 2 * RS * row_bytes, s, tab, (const signed char*)x, (signed char*)y, gather, (int)host_ids, B, H, W, C, Hs, Ws, pad);
         else
-            EE_LAUNCH((space_to_depth_rows_kernel<uint16_t, RS>), grid, dim3(256), 2 * RS * row_bytes, s, tab, (const uint16_t*)x, (uint16_t*)y, gather, (int)host_ids, H, W, C, Hs, Ws, pad);
+            EE_LAUNCH((space_to_depth_rows_kernel<uint16_t, RS>), grid, dim3(256), 2 * RS * row_bytes, s, tab, (const uint16_t*)x, (uint16_t*)y, gather, (int)host_ids, B, H, W, C, Hs, Ws, pad);
         return hipGetLastError();
     }
     const unsigned blocks = (unsigned)((total + 255) / 256);
@@ -568,9 +572,11 @@ hipError_t launch_space_to_depth(const void* x, void* y, const int32_t* gather, 
 
 // ---- [rows][c_bytes] -> [rows][cp_bytes], zero tail: gives layers whose pixels are not 16-byte multiples
 // the row alignment the matrix-core loader needs ----------------------------------------------------------
-__global__ __launch_bounds__(256) void pad_channels_kernel(const int* x, int* y, long long rows, int c_words, int cp_words)
+__global__ __launch_bounds__(256) void pad_channels_kernel(const int* x, int* y, long long rows, int c_words, int cp_words, int units)
 {
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int unit = xcd_unit(blockIdx.x, units);
+    const long long idx = (long long)unit * 256 + threadIdx.x;
+    if (unit < 0) return;
     if (idx >= rows * cp_words) return;
     const long long r = idx / cp_words;
     const int w = (int)(idx - r * cp_words);
@@ -581,7 +587,7 @@ hipError_t launch_pad_channels(const void* x, void* y, long long rows, int c_byt
 {
     const long long total = rows * (cp_bytes / 4);
     if (total <= 0) return hipSuccess;
-    EE_LAUNCH(pad_channels_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (const int*)x, (int*)y, rows, c_bytes / 4, cp_bytes / 4);
+    EE_LAUNCH(pad_channels_kernel, dim3(xcd_grid((total + 255) / 256)), dim3(256), 0, s, (const int*)x, (int*)y, rows, c_bytes / 4, cp_bytes / 4, (int)((total + 255) / 256));
     return hipGetLastError();
 }
 

@@ -51,7 +51,7 @@ namespace ee {
 // the array (Sec. III-A, Eq. 1: samples mapped along P instead of R): with few output pixels the
 // reduction axis supplies the parallelism that keeps a CU's matrix cores and copy queue busy.
 template <int ES, int BM, int BN, int KS, int KSPL, bool PLAIN>
-__global__ __launch_bounds__(256 * KSPL) void conv_igemm_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, int per_xcd, int ns)
+__global__ __launch_bounds__(256 * KSPL) void conv_igemm_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, int ns)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
@@ -69,8 +69,8 @@ __global__ __launch_bounds__(256 * KSPL) void conv_igemm_kernel(ConvArgs a, int 
 
     const int xcd = blockIdx.x & 7, wslot = blockIdx.x >> 3;
     const int mslot = (int)fast_div((unsigned)wslot, (unsigned)gn, magic_gn);
-    const int mt = xcd * per_xcd + mslot, nt = wslot - mslot * gn;
-    if (mt >= gm || mslot >= per_xcd) return;
+    const int mt = xcd_unit((unsigned)(mslot << 3 | xcd), gm), nt = wslot - mslot * gn;
+    if (mt < 0) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -368,8 +368,8 @@ __global__ __launch_bounds__(256 * KSPL) void conv_igemm_kernel(ConvArgs a, int 
 template <int ES, int BM, int BN, int KS, int KSPL>
 static hipError_t launch_igemm_tile(const ConvArgs& a, bool plain, int ns, hipStream_t s)
 {
-    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, per_xcd = (gm + 7) / 8;
-    const dim3 grid((unsigned)(8 * per_xcd * gn));
+    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN;
+    const dim3 grid(xcd_grid(gm) * (unsigned)gn);
     const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1));
     const bool res_tile = a.res != nullptr && (a.Co * ES) % 16 == 0;
     const int nk = (a.kh * a.kw * a.Ci * ES + KS - 1) / KS;
@@ -388,9 +388,9 @@ static hipError_t launch_igemm_tile(const ConvArgs& a, bool plain, int ns, hipSt
     if (granted != hipSuccess) return granted;
     if (lds_bytes > 160 * 1024) return hipErrorInvalidValue;
     if (plain)
-        EE_LAUNCH((conv_igemm_kernel<ES, BM, BN, KS, KSPL, true>), grid, dim3(256 * KSPL), lds_bytes, s, a, gm, gn, magic_gn, per_xcd, ns);
+        EE_LAUNCH((conv_igemm_kernel<ES, BM, BN, KS, KSPL, true>), grid, dim3(256 * KSPL), lds_bytes, s, a, gm, gn, magic_gn, ns);
     else
-        EE_LAUNCH((conv_igemm_kernel<ES, BM, BN, KS, KSPL, false>), grid, dim3(256 * KSPL), lds_bytes, s, a, gm, gn, magic_gn, per_xcd, ns);
+        EE_LAUNCH((conv_igemm_kernel<ES, BM, BN, KS, KSPL, false>), grid, dim3(256 * KSPL), lds_bytes, s, a, gm, gn, magic_gn, ns);
     return hipGetLastError();
 }
 

@@ -48,7 +48,7 @@ struct IrTile {
     unsigned magic_cpp, magic_iw;   // floor(2^32 / d) + 1: n / d for n < 2^16
     int xp;                // bytes per staged input pixel
     int x_bytes, e_bytes;  // LDS: staged input, one buffer of expanded pixels
-    int per_xcd, total;    // workgroups per XCD, workgroups with work
+    int total;             // workgroups with work
     int gp;                // 4 or 8: that many wavefronts share the channel groups (small images), 0: four share the pixels
 };
 
@@ -68,8 +68,8 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     extern __shared__ __attribute__((aligned(16))) unsigned char ir_lds[];
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int u = (int)(blockIdx.x & 7) * t.per_xcd + (int)(blockIdx.x >> 3);
-    if (u >= t.total) return;                                          // whole workgroup: no barrier is skipped by a part of it
+    const int u = xcd_unit(blockIdx.x, t.total);
+    if (u < 0) return;                                          // whole workgroup: no barrier is skipped by a part of it
     const int tx_i = u % t.tiles_x, ty_i = (u / t.tiles_x) % t.tiles_y, n = u / (t.tiles_x * t.tiles_y);
     const int ox0 = tx_i * t.pbw * t.nbw, oy0 = ty_i * t.pbh * t.nbh;
     const int ix0 = ox0 * STRIDE - a.pad, iy0 = oy0 * STRIDE - a.pad;
@@ -376,7 +376,6 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
     const long long total = (long long)a.B * t.tiles_x * t.tiles_y;
     if (total > 0x3fffffff) return false;
     t.total = (int)total;
-    t.per_xcd = (t.total + 7) / 8;
     // small images: the wavefronts share the channel groups (instantiated for 2 or more output blocks and 2 or more reduction steps)
     const int nw = a.Ce32 >= 320 ? 8 : 4;                               // ten or more groups: eight wavefronts
     t.gp = nco >= 2 && a.Ce32 >= 128 && t.pbw * t.pbh <= maxb && total <= 2048 && 8 * a.Ce32 + t.x_bytes + nw * t.e_bytes + maxb * nco * 4096 <= 64 * 1024 &&
@@ -396,7 +395,7 @@ bool ir_block_supported(const IrArgs& a)
 template <int STRIDE, int NCO, int MAXB, int MAXK, int GP>
 static void ir_launch5(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t s)
 {
-    EE_LAUNCH((ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP>), dim3((unsigned)(t.per_xcd * 8)), dim3(GP ? 64 * GP : 256), lds, s, a, t);
+    EE_LAUNCH((ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP>), dim3(xcd_grid(t.total)), dim3(GP ? 64 * GP : 256), lds, s, a, t);
 }
 
 template <int STRIDE, int NCO, int MAXB>

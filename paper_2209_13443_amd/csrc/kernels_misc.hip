@@ -29,10 +29,11 @@ __device__ __forceinline__ int byte_of(int word, int e) { return (int)(signed ch
 // ---- depthwise k x k: one lane = one output pixel x 16 bytes of channels ---------------------------
 // weights repacked [k*k][C]; int8: int32 accumulate + bias, round-shift, clamp; bf16: float accumulate.
 template <int ES>
-__global__ __launch_bounds__(256) void depthwise_kernel(PoolArgs a)
+__global__ __launch_bounds__(256) void depthwise_kernel(PoolArgs a, int units)
 {
-    const int cchunks = a.C * ES / 16;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int cchunks = a.C * ES / 16, unit = xcd_unit(blockIdx.x, units);
+    const long long idx = (long long)unit * 256 + threadIdx.x;
+    if (unit < 0) return;
     if (idx >= (long long)a.B * a.Ho * a.Wo * cchunks) return;
     const int q = (int)(idx % cchunks);
     const long long pix = idx / cchunks;
@@ -112,8 +113,10 @@ __global__ __launch_bounds__(256) void depthwise3x3_i8_kernel(PoolArgs a, int gr
     v4i* dw_lds = (v4i*)dw_lds_raw;                    // per 16-channel chunk: 12 weight quads, then 4 bias quads
     const int cchunks = a.C / 16;
     const long long total = (long long)a.B * a.Ho * groups_x * cchunks;
-    const long long idx = min((long long)blockIdx.x * 256 + threadIdx.x, total - 1);      // lanes past the end redo the last item
-    const bool active = (long long)blockIdx.x * 256 + threadIdx.x < total;
+    const int unit = xcd_unit(blockIdx.x, (int)((total + 255) / 256));
+    if (unit < 0) return;
+    const long long idx = min((long long)unit * 256 + threadIdx.x, total - 1);      // lanes past the end redo the last item
+    const bool active = (long long)unit * 256 + threadIdx.x < total;
     const int q = (int)(idx % cchunks);
     const int g = (int)(idx / cchunks);
     const int ox0 = (g % groups_x) * PX, oy = (g / groups_x) % a.Ho, n = g / (groups_x * a.Ho);
@@ -213,7 +216,7 @@ hipError_t launch_depthwise(const PoolArgs& a, int dtype, hipStream_t s)
         if (total <= 0) return hipSuccess;
         PoolArgs b = a;
         b.w = a.w3;
-        const dim3 grid((unsigned)((total + 255) / 256));
+        const dim3 grid(xcd_grid((total + 255) / 256));
         if (a.C <= 192) {                   // the table in LDS: measured to pay up to 192 channels (see the kernel)
             const size_t lds_bytes = (size_t)a.C * 16;
             if (a.stride == 1) EE_LAUNCH((depthwise3x3_i8_kernel<1, true>), grid, dim3(256), lds_bytes, s, b, groups_x);
@@ -226,18 +229,19 @@ hipError_t launch_depthwise(const PoolArgs& a, int dtype, hipStream_t s)
     }
     const long long total = (long long)a.B * a.Ho * a.Wo * (a.C * es / 16);
     if (total <= 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((total + 255) / 256);
-    if (dtype == EE_I8) EE_LAUNCH(depthwise_kernel<1>, dim3(blocks), dim3(256), 0, s, a);
-    else EE_LAUNCH(depthwise_kernel<2>, dim3(blocks), dim3(256), 0, s, a);
+    const int units = (int)((total + 255) / 256);
+    if (dtype == EE_I8) EE_LAUNCH(depthwise_kernel<1>, dim3(xcd_grid(units)), dim3(256), 0, s, a, units);
+    else EE_LAUNCH(depthwise_kernel<2>, dim3(xcd_grid(units)), dim3(256), 0, s, a, units);
     return hipGetLastError();
 }
 
 // ---- max-pool k x k over the in-range taps ---------------------------------------------------------
 template <int ES>
-__global__ __launch_bounds__(256) void maxpool_kernel(PoolArgs a)
+__global__ __launch_bounds__(256) void maxpool_kernel(PoolArgs a, int units)
 {
-    const int cchunks = a.C * ES / 16;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int cchunks = a.C * ES / 16, unit = xcd_unit(blockIdx.x, units);
+    const long long idx = (long long)unit * 256 + threadIdx.x;
+    if (unit < 0) return;
     if (idx >= (long long)a.B * a.Ho * a.Wo * cchunks) return;
     const int q = (int)(idx % cchunks);
     const long long pix = idx / cchunks;
@@ -286,10 +290,11 @@ __global__ __launch_bounds__(256) void maxpool_kernel(PoolArgs a)
 // 128 * k*k to the sum (and 128 is taken off the quotient), the division is a multiply-high with
 // floor(2^32 / (2 k*k)) and one correction step.  bf16: float sum in tap order / (k*k), rounded to bf16.
 template <int ES>
-__global__ __launch_bounds__(256) void avgpool_kernel(PoolArgs a, unsigned magic)
+__global__ __launch_bounds__(256) void avgpool_kernel(PoolArgs a, unsigned magic, int units)
 {
-    const int cchunks = a.C * ES / 16;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int cchunks = a.C * ES / 16, unit = xcd_unit(blockIdx.x, units);
+    const long long idx = (long long)unit * 256 + threadIdx.x;
+    if (unit < 0) return;
     if (idx >= (long long)a.B * a.Ho * a.Wo * cchunks) return;
     const int q = (int)(idx % cchunks);
     const long long pix = idx / cchunks;
@@ -359,11 +364,12 @@ __device__ __forceinline__ unsigned pk_add_i16(unsigned a, unsigned b)
 }
 
 template <int STRIDE, bool AVG>
-__global__ __launch_bounds__(256) void pool3x3_i8_kernel(PoolArgs a, int groups_x)
+__global__ __launch_bounds__(256) void pool3x3_i8_kernel(PoolArgs a, int groups_x, int units)
 {
     constexpr int PX = 4, COLS = (PX - 1) * STRIDE + 3;
-    const int cchunks = a.C / 16;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int cchunks = a.C / 16, unit = xcd_unit(blockIdx.x, units);
+    const long long idx = (long long)unit * 256 + threadIdx.x;
+    if (unit < 0) return;
     if (idx >= (long long)a.B * a.Ho * groups_x * cchunks) return;
     const int q = (int)(idx % cchunks);
     const int g = (int)(idx / cchunks);
@@ -439,9 +445,9 @@ static hipError_t launch_pool3x3_i8(const PoolArgs& a, hipStream_t s)
     const int groups_x = (a.Wo + 3) / 4;
     const long long total = (long long)a.B * a.Ho * groups_x * (a.C / 16);
     if (total <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((total + 255) / 256));
-    if (a.stride == 1) EE_LAUNCH((pool3x3_i8_kernel<1, AVG>), grid, dim3(256), 0, s, a, groups_x);
-    else EE_LAUNCH((pool3x3_i8_kernel<2, AVG>), grid, dim3(256), 0, s, a, groups_x);
+    const int units = (int)((total + 255) / 256);
+    if (a.stride == 1) EE_LAUNCH((pool3x3_i8_kernel<1, AVG>), dim3(xcd_grid(units)), dim3(256), 0, s, a, groups_x, units);
+    else EE_LAUNCH((pool3x3_i8_kernel<2, AVG>), dim3(xcd_grid(units)), dim3(256), 0, s, a, groups_x, units);
     return hipGetLastError();
 }
 
@@ -451,9 +457,9 @@ hipError_t launch_maxpool(const PoolArgs& a, int dtype, hipStream_t s)
     const int es = dtype == EE_I8 ? 1 : 2;
     const long long total = (long long)a.B * a.Ho * a.Wo * (a.C * es / 16);
     if (total <= 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((total + 255) / 256);
-    if (dtype == EE_I8) EE_LAUNCH(maxpool_kernel<1>, dim3(blocks), dim3(256), 0, s, a);
-    else EE_LAUNCH(maxpool_kernel<2>, dim3(blocks), dim3(256), 0, s, a);
+    const int units = (int)((total + 255) / 256);
+    if (dtype == EE_I8) EE_LAUNCH(maxpool_kernel<1>, dim3(xcd_grid(units)), dim3(256), 0, s, a, units);
+    else EE_LAUNCH(maxpool_kernel<2>, dim3(xcd_grid(units)), dim3(256), 0, s, a, units);
     return hipGetLastError();
 }
 
@@ -464,15 +470,15 @@ hipError_t launch_avgpool(const PoolArgs& a, int dtype, hipStream_t s)
     const long long total = (long long)a.B * a.Ho * a.Wo * (a.C * es / 16);
     if (total <= 0) return hipSuccess;
     if (a.k < 1 || a.k > 15) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)((total + 255) / 256);
+    const int units = (int)((total + 255) / 256);
     const unsigned magic = (unsigned)(0x100000000ull / (unsigned)(2 * a.k * a.k));
-    if (dtype == EE_I8) EE_LAUNCH(avgpool_kernel<1>, dim3(blocks), dim3(256), 0, s, a, magic);
-    else EE_LAUNCH(avgpool_kernel<2>, dim3(blocks), dim3(256), 0, s, a, magic);
+    if (dtype == EE_I8) EE_LAUNCH(avgpool_kernel<1>, dim3(xcd_grid(units)), dim3(256), 0, s, a, magic, units);
+    else EE_LAUNCH(avgpool_kernel<2>, dim3(xcd_grid(units)), dim3(256), 0, s, a, magic, units);
     return hipGetLastError();
 }
 
 // ---- exit head, step 1: global average pool ----------------------------------------------------------
-// grid (S pixel splits, B).  Lane = (pixel lane pl, 16-byte channel chunk q); the pixel lanes are reduced
+// One workgroup per (sample, one of S pixel splits).  Lane = (pixel lane pl, 16-byte channel chunk q); the pixel lanes are reduced
 // through LDS into one partial row per workgroup.  int8: the row is added into sums[B][C] with one
 // atomic per channel (int32 addition is exact in any order; the buffer is zero on entry, the softmax
 // kernel of every head clears what it used).  bf16: the S partial rows of a sample are stored and a
@@ -483,16 +489,18 @@ hipError_t launch_avgpool(const PoolArgs& a, int dtype, hipStream_t s)
 // Bound by HBM on large batches, by latency on small ones; eight loads in flight per lane, also for the last rows.
 // Needs C * ES / 16 <= 256.
 template <int ES>
-__global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block)
+__global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block, int S)
 {
     constexpr int NE = 16 / ES, U = 8;
     __shared__ int red[256 * NE];
     const int cchunks = a.C * ES / 16;
     const int npl = 256 / cchunks;
-    const int b = blockIdx.y, S = gridDim.x;
+    const int unit = xcd_unit(blockIdx.x, a.B * S);
+    if (unit < 0) return;
+    const int b = unit / S, split = unit - b * S;
     const int q = (int)threadIdx.x % cchunks, pl = (int)threadIdx.x / cchunks;
     const bool active = pl < npl;
-    const int p0 = blockIdx.x * pix_per_block, p1 = min(a.HW, p0 + pix_per_block);
+    const int p0 = split * pix_per_block, p1 = min(a.HW, p0 + pix_per_block);
     const long long bs = a.slots ? (long long)a.slots[b] : (long long)b;      // zero-copy compaction: sample b of the batch is slot slots[b] of act
     const unsigned char* x = (const unsigned char*)a.act + bs * a.HW * a.C * ES;
     int acci[NE];
@@ -543,7 +551,7 @@ __global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block)
             float s = 0.f;
             for (int l = 0; l < npl; ++l) s += __int_as_float(red[l * a.C + c]);
             if (S == 1) a.sums[(long long)b * a.C + c] = __float_as_int(s / (float)a.HW);
-            else a.gap_partial[((long long)b * S + blockIdx.x) * a.C + c] = __float_as_int(s);
+            else a.gap_partial[((long long)b * S + split) * a.C + c] = __float_as_int(s);
         }
     }
 }
@@ -596,12 +604,12 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
     const int ppb = gap_pixels_per_block(a.B, a.HW);
     const int splits = (a.HW + ppb - 1) / ppb;
     if (dtype == EE_I8) {
-        EE_LAUNCH(gap_kernel<1>, dim3(splits, a.B), dim3(256), 0, s, a, ppb);
+        EE_LAUNCH(gap_kernel<1>, dim3(xcd_grid(a.B * splits)), dim3(256), 0, s, a, ppb, splits);
     } else {
         // two kernels when the pooling is split: a timed launch takes the first one's begin and the second one's end
         const hipEvent_t t0 = g_launch_start, t1 = g_launch_stop;
         if (splits > 1) g_launch_stop = nullptr;
-        EE_LAUNCH(gap_kernel<2>, dim3(splits, a.B), dim3(256), 0, s, a, ppb);
+        EE_LAUNCH(gap_kernel<2>, dim3(xcd_grid(a.B * splits)), dim3(256), 0, s, a, ppb, splits);
         if (splits > 1) {
             const long long total = (long long)a.B * (a.C / 4);
             g_launch_start = nullptr;
@@ -882,7 +890,8 @@ __global__ __launch_bounds__(256) void head_small_kernel(HeadArgs a, int pooled)
     __shared__ __attribute__((aligned(16))) unsigned char feat[ES == 1 ? HEAD_SMALL_C : 2 * HEAD_SMALL_C];    // int8 features, or floats (C <= HEAD_SMALL_C / ES)
     __shared__ int lg[HEAD_SMALL_CLS];
     __shared__ uint32_t exp2_lds[256];
-    const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, b = xcd_unit(blockIdx.x, a.B);
+    if (b < 0) return;
     const int cchunks = a.C * ES / 16, CB = a.C * ES;
     const int part = tid & 15, j0 = tid >> 4;                   // FC: the lane's share of the row of classes j0, j0 + 16, ...
     const v4i zero4 = {0, 0, 0, 0};
@@ -1024,8 +1033,8 @@ bool head_small(const HeadArgs& a, int dtype, bool pooled)
 hipError_t launch_head_small(const HeadArgs& a, int dtype, bool pooled, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
-    if (dtype == EE_I8) EE_LAUNCH(head_small_kernel<1>, dim3(a.B), dim3(256), 0, s, a, (int)pooled);
-    else EE_LAUNCH(head_small_kernel<2>, dim3(a.B), dim3(256), 0, s, a, (int)pooled);
+    if (dtype == EE_I8) EE_LAUNCH(head_small_kernel<1>, dim3(xcd_grid(a.B)), dim3(256), 0, s, a, (int)pooled);
+    else EE_LAUNCH(head_small_kernel<2>, dim3(xcd_grid(a.B)), dim3(256), 0, s, a, (int)pooled);
     return hipGetLastError();
 }
 
@@ -1085,7 +1094,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s)
 }
 
 // ---- compaction and refill: survivors keep their order, newcomers follow behind them ------------------------
-// grid (chunks of 16 KiB, b_act + b_incr): row b < b_act is a slot of the batch, the rows behind are the newcomers.  Bound by
+// A workgroup per (row, chunk of 16 KiB), b_act + b_incr rows: row b < b_act is a slot of the batch, the rows behind are the newcomers.  Bound by
 // HBM: every sample that stays is read and written once.  A workgroup's four 16-byte loads per lane are on their way before it
 // works out where its sample goes (each wavefront by itself: number of survivors in front of the slot by ballots over the
 // flags, no barrier), and the stores are non-temporal: a line that is only written does not displace the sources in L2.
@@ -1097,12 +1106,14 @@ __global__ __launch_bounds__(256) void compact_kernel(const uint8_t* flag, const
                                                       const int32_t* refill_ids, int b_incr, long long sample_bytes, int dst_off, int ring_rows,
                                                       int* b_rem_out, int* b_merged_out)
 {
-    const int b = blockIdx.y, lane = threadIdx.x & 63;
+    const int chunks = (int)((sample_bytes + 16383) / 16384), unit = xcd_unit(blockIdx.x, (b_act + b_incr) * chunks);
+    if (unit < 0) return;
+    const int b = unit / chunks, chunk = unit - b * chunks, lane = threadIdx.x & 63;
     const bool fresh = b >= b_act;
-    const bool books = blockIdx.x == 0 && b == 0 && (b_rem_out || b_merged_out);      // this workgroup also reports the counts
+    const bool books = chunk == 0 && b == 0 && (b_rem_out || b_merged_out);      // this workgroup also reports the counts
     const bool gone = !fresh && flag[b] != 0;
     if (gone && !books) return;
-    const long long c0 = (long long)blockIdx.x * 16384;
+    const long long c0 = (long long)chunk * 16384;
     const v4i* s4 = (const v4i*)((fresh ? refill + (long long)(b - b_act) * sample_bytes : src + (long long)b * sample_bytes) + c0) + threadIdx.x;
     const long long n16 = (sample_bytes - c0) / 16;
     v4i v[4];
@@ -1125,7 +1136,7 @@ __global__ __launch_bounds__(256) void compact_kernel(const uint8_t* flag, const
     if (gone) return;
     int d = dst_off + before + (fresh ? b - b_act : 0);
     if (ring_rows > 0 && d >= ring_rows) d -= ring_rows;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && ids_dst) {
+    if (chunk == 0 && threadIdx.x == 0 && ids_dst) {
         if (fresh ? refill_ids != nullptr : ids_src != nullptr) ids_dst[d] = fresh ? refill_ids[b - b_act] : ids_src[b];
     }
     v4i* d4 = (v4i*)(dst + (long long)d * sample_bytes + c0) + threadIdx.x;
@@ -1142,7 +1153,7 @@ hipError_t launch_compact(const uint8_t* flag, const void* src, void* dst, const
                           int* b_rem_out, int* b_merged_out, hipStream_t s)
 {
     if (b_act + b_incr <= 0) return hipSuccess;
-    dim3 grid((unsigned)((sample_bytes + 16383) / 16384), b_act + b_incr);
+    const dim3 grid(xcd_grid((sample_bytes + 16383) / 16384 * (b_act + b_incr)));
     EE_LAUNCH(compact_kernel, grid, dim3(256), 0, s, flag, (const unsigned char*)src, (unsigned char*)dst, ids_src, ids_dst, b_act,
               (const unsigned char*)refill, refill_ids, b_incr, (long long)sample_bytes, dst_off, ring_rows, b_rem_out, b_merged_out);
     return hipGetLastError();
@@ -1150,11 +1161,13 @@ hipError_t launch_compact(const uint8_t* flag, const void* src, void* dst, const
 
 // ---- admission: whole samples copied to given slots ------------------------------------------------------------
 // slot k = pool row ids[k]
-__global__ __launch_bounds__(256) void copy_rows_kernel(const unsigned char* src, unsigned char* dst, const int32_t* gather_ids, long long sample_bytes)
+__global__ __launch_bounds__(256) void copy_rows_kernel(const unsigned char* src, unsigned char* dst, const int32_t* gather_ids, int rows, long long sample_bytes)
 {
-    const int k = blockIdx.y;
+    const int chunks = (int)((sample_bytes + 16383) / 16384), unit = xcd_unit(blockIdx.x, rows * chunks);
+    if (unit < 0) return;
+    const int k = unit / chunks;
     const long long row = gather_ids[k];
-    const long long c0 = (long long)blockIdx.x * 16384;
+    const long long c0 = (long long)(unit - k * chunks) * 16384;
     const v4i* s4 = (const v4i*)(src + row * sample_bytes + c0);
     v4i* d4 = (v4i*)(dst + (long long)k * sample_bytes + c0);
     const long long n16 = min((long long)1024, (sample_bytes - c0) / 16);
@@ -1164,8 +1177,8 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const unsigned char* src
 hipError_t launch_admit(const void* pool, void* dst, const int32_t* ids, int b, int64_t sample_bytes, hipStream_t s)
 {
     if (b <= 0) return hipSuccess;
-    dim3 grid((unsigned)((sample_bytes + 16383) / 16384), b);
-    EE_LAUNCH(copy_rows_kernel, grid, dim3(256), 0, s, (const unsigned char*)pool, (unsigned char*)dst, ids, (long long)sample_bytes);
+    const dim3 grid(xcd_grid((sample_bytes + 16383) / 16384 * b));
+    EE_LAUNCH(copy_rows_kernel, grid, dim3(256), 0, s, (const unsigned char*)pool, (unsigned char*)dst, ids, b, (long long)sample_bytes);
     return hipGetLastError();
 }
 

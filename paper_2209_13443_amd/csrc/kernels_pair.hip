@@ -24,7 +24,7 @@ namespace ee {
 // ES: element bytes.  BM: pixel rows per workgroup.  BN1: output channels of the first layer (all of them).
 // KS: bytes of the first reduction per ring stage.  BN2: output channels of the second layer per chunk.
 template <int ES, int BM, int BN1, int KS, int BN2>
-__global__ __launch_bounds__(256) void conv_pair_kernel(PairArgs p, int gm, int per_xcd, int ns)
+__global__ __launch_bounds__(256) void conv_pair_kernel(PairArgs p, int gm, int ns)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int WM = BM / 2, WN = BN1 / 2, TM = WM / 32, TN = WN / 32;
@@ -45,9 +45,8 @@ __global__ __launch_bounds__(256) void conv_pair_kernel(PairArgs p, int gm, int 
     static_assert(BN1 * 4 <= 1024, "first-layer bias is copied by one wavefront");
 
     const ConvArgs& a = p.c2;
-    const int xcd = blockIdx.x & 7, mslot = blockIdx.x >> 3;
-    const int mt = xcd * per_xcd + mslot;
-    if (mt >= gm || mslot >= per_xcd) return;
+    const int mt = xcd_unit(blockIdx.x, gm);
+    if (mt < 0) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -359,7 +358,7 @@ static hipError_t launch_pair_tile(const PairArgs& p, int ns, hipStream_t s)
 {
     constexpr int BN2 = 128;
     const ConvArgs& a = p.c2;
-    const int gm = (a.M + BM - 1) / BM, per_xcd = (gm + 7) / 8;
+    const int gm = (a.M + BM - 1) / BM;
     const int nk = (a.kh * a.kw * a.Ci * ES + KS - 1) / KS;
     ns = ns < 2 ? 2 : (ns > 4 ? 4 : ns);
     const size_t lds_bytes = conv_pair_lds_bytes(ES, BM, BN1, KS, BN2, ns, nk, p.Co3);
@@ -367,7 +366,7 @@ static hipError_t launch_pair_tile(const PairArgs& p, int ns, hipStream_t s)
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (granted != hipSuccess) return granted;
     if (lds_bytes > 160 * 1024) return hipErrorInvalidValue;
-    EE_LAUNCH((conv_pair_kernel<ES, BM, BN1, KS, BN2>), dim3((unsigned)(8 * per_xcd)), dim3(256), lds_bytes, s, p, gm, per_xcd, ns);
+    EE_LAUNCH((conv_pair_kernel<ES, BM, BN1, KS, BN2>), dim3(xcd_grid(gm)), dim3(256), lds_bytes, s, p, gm, ns);
     return hipGetLastError();
 }
 

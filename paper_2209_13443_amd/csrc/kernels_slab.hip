@@ -26,7 +26,7 @@ namespace ee {
 // reduction axis per weight stage (128 or 256; a pixel's bytes CiB = Ci * ES are a power of two >= 64, so a 32-byte
 // sub-step never straddles two taps).  ns: weight stages in the ring (2..4).
 template <int ES, int BM, int BN, int KS>
-__global__ __launch_bounds__(256) void conv_slab_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, int per_xcd, int ns, int cib_log2)
+__global__ __launch_bounds__(256) void conv_slab_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, int ns, int cib_log2)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
@@ -44,8 +44,8 @@ __global__ __launch_bounds__(256) void conv_slab_kernel(ConvArgs a, int gm, int 
 
     const int xcd = blockIdx.x & 7, wslot = blockIdx.x >> 3;
     const int mslot = (int)fast_div((unsigned)wslot, (unsigned)gn, magic_gn);
-    const int mt = xcd * per_xcd + mslot, nt = wslot - mslot * gn;
-    if (mt >= gm || mslot >= per_xcd) return;
+    const int mt = xcd_unit((unsigned)(mslot << 3 | xcd), gm), nt = wslot - mslot * gn;
+    if (mt < 0) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -286,8 +286,8 @@ int conv_slab_default(const ConvArgs& a, int es)
 template <int ES, int BM, int BN, int KS>
 static hipError_t launch_slab_tile(const ConvArgs& a, int ns, hipStream_t s)
 {
-    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, per_xcd = (gm + 7) / 8;
-    const dim3 grid((unsigned)(8 * per_xcd * gn));
+    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN;
+    const dim3 grid(xcd_grid(gm) * (unsigned)gn);
     const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1));
     const int cib = a.Ci * ES, cib_log2 = log2_exact(cib);
     const bool res_tile = a.res != nullptr && (a.Co * ES) % 16 == 0;
@@ -307,7 +307,7 @@ static hipError_t launch_slab_tile(const ConvArgs& a, int ns, hipStream_t s)
     static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_slab_kernel<ES, BM, BN, KS>),
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (granted != hipSuccess) return granted;
-    EE_LAUNCH((conv_slab_kernel<ES, BM, BN, KS>), grid, dim3(256), lds_bytes, s, a, gm, gn, magic_gn, per_xcd, ns, cib_log2);
+    EE_LAUNCH((conv_slab_kernel<ES, BM, BN, KS>), grid, dim3(256), lds_bytes, s, a, gm, gn, magic_gn, ns, cib_log2);
     return hipGetLastError();
 }
 

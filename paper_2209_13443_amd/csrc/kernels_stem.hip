@@ -125,16 +125,18 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
     // strips wave, wave + 4, wave + 8, wave + 12 of a tile through four operand sets; a strip's operands are requested two strips
     // before it is computed, the first two of the next tile behind this tile's last two
     v4i_r xs[4][NKB];
-    int u = (int)blockIdx.x;                                            // the same trip count for the whole workgroup
-    if (u < t.total) {
+    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
+    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
+    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3);
+    if (u < u_end) {
         const Tile t0 = tile_at(u);
         load_strip(t0, wave, xs[0]);
         load_strip(t0, wave + 4, xs[1]);
     }
-    for (; u < t.total; u += (int)gridDim.x) {
+    for (; u < u_end; u += u_step) {
         const Tile tl = tile_at(u);
-        const bool more = u + (int)gridDim.x < t.total;
-        const Tile tn = tile_at(more ? u + (int)gridDim.x : u);
+        const bool more = u + u_step < u_end;
+        const Tile tn = tile_at(more ? u + u_step : u);
         const int n = tl.n, py0 = tl.py0, px0 = tl.px0;
         __builtin_amdgcn_sched_barrier(0);
         load_strip(tl, wave + 8, xs[2]);
@@ -195,7 +197,7 @@ hipError_t launch_stem_pool(const ConvArgs& a, void* yq, int Hq, int Wq, hipStre
     const long long total = (long long)(a.M / (a.Ho * a.Wo)) * t.tiles_x * t.tiles_y;
     if (total > 0x3fffffff) return hipErrorInvalidValue;
     t.total = (int)total;
-    const unsigned blocks = (unsigned)(total < 512 ? total : 512);      // two workgroups on every CU (what matters is the CU's share, not the workgroup's); the loop takes the rest
+    const unsigned blocks = total < 512 ? xcd_grid(total) : 512u;      // two workgroups on every CU (what matters is the CU's share, not the workgroup's); the loop takes the rest
     EE_LAUNCH(stem_pool_i8_kernel, dim3(blocks), dim3(256), (size_t)ST_RPIX * ST_PITCH + 256, s, a, yq, t);
     return hipGetLastError();
 }

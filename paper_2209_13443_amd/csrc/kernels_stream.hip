@@ -35,7 +35,7 @@ __device__ __forceinline__ unsigned stream_div(unsigned n, unsigned d, unsigned 
 
 // KH kernel rows of BPR 32-byte blocks each; NT tiles of 32 output channels
 template <int KH, int BPR, int NT>
-__global__ __launch_bounds__(256) void conv_stream_i8_kernel(ConvArgs a, long long nstrips)
+__global__ __launch_bounds__(256) void conv_stream_i8_kernel(ConvArgs a, int nstrips)
 {
     constexpr int NKB = KH * BPR, ROW_PITCH = NT * 32 + 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char stream_lds[];
@@ -112,26 +112,26 @@ __global__ __launch_bounds__(256) void conv_stream_i8_kernel(ConvArgs a, long lo
     };
     // Two operand buffers used in turn: while strip i is computed out of one, the loads of strip i + 1 fill the other.
     // The fences keep the compiler from moving the loads behind the work they are meant to overlap.
-    const long long step = (long long)gridDim.x * 4;
-    long long strip = (long long)blockIdx.x * 4 + wave;
-    if (strip >= nstrips) return;
+    const long long step = (long long)(gridDim.x >> 3) * 4, end = xcd_first((int)(blockIdx.x & 7) + 1, nstrips);      // this XCD's strips
+    long long strip = xcd_first((int)(blockIdx.x & 7), nstrips) + (long long)(blockIdx.x >> 3) * 4 + wave;
+    if (strip >= end) return;
     v4i_s xa[NKB], xb[NKB];
     unsigned oka = 0, okb = 0;
     load_strip(strip, xa, oka);
     for (;;) {
         // always issued (past the end: the last strip once more), so that the number of loads in flight is fixed
-        load_strip(strip + step < nstrips ? strip + step : nstrips - 1, xb, okb);
+        load_strip(strip + step < end ? strip + step : end - 1, xb, okb);
         __builtin_amdgcn_sched_barrier(0);
         compute_strip(strip, xa, oka);
         __builtin_amdgcn_sched_barrier(0);
         strip += step;
-        if (strip >= nstrips) break;
-        load_strip(strip + step < nstrips ? strip + step : nstrips - 1, xa, oka);
+        if (strip >= end) break;
+        load_strip(strip + step < end ? strip + step : end - 1, xa, oka);
         __builtin_amdgcn_sched_barrier(0);
         compute_strip(strip, xb, okb);
         __builtin_amdgcn_sched_barrier(0);
         strip += step;
-        if (strip >= nstrips) break;
+        if (strip >= end) break;
     }
 }
 
@@ -147,8 +147,8 @@ bool conv_stream_supported(const ConvArgs& a, int es)
 template <int KH, int BPR, int NT>
 static hipError_t launch_stream_inst(const ConvArgs& a, hipStream_t s)
 {
-    const long long nstrips = ((long long)a.M + 31) / 32;
-    const long long want = (nstrips + 3) / 4;
+    const int nstrips = (a.M + 31) / 32;
+    const long long want = xcd_grid((nstrips + 3) / 4);
     const long long cap = KH * BPR * NT <= 6 ? 1024 : 512;            // workgroups per CU the registers allow (4 or 2) x 256 CUs; the loop takes the rest
     const unsigned blocks = (unsigned)(want < cap ? want : cap);
     const size_t lds_bytes = (size_t)4 * 32 * (NT * 32 + 16);

@@ -26,15 +26,17 @@ __device__ __forceinline__ int thin_med3(int v, int lo, int hi)       // lo <= h
     return r;
 }
 
-__global__ __launch_bounds__(256) void conv_thin_i8_kernel(ThinConvArgs a, int nt, int row_pitch)
+__global__ __launch_bounds__(256) void conv_thin_i8_kernel(ThinConvArgs a, int nt, int row_pitch, int units)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char thin_lds[];
+    const int unit = xcd_unit(blockIdx.x, units);
+    if (unit < 0) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int p = lane & 31, hi = lane >> 5;
     // the bias of all channels once per workgroup: every lane needs 16 of them per tile, the same for all pixels
     int* lbias = (int*)(thin_lds + 4 * 32 * row_pitch);
     for (int i = threadIdx.x; i < nt * 32; i += 256) lbias[i] = ((const int*)a.bias)[i];
-    const long long m0 = ((long long)blockIdx.x * 4 + wave) * 32;
+    const long long m0 = ((long long)unit * 4 + wave) * 32;
     const long long m = m0 + p < a.M ? m0 + p : a.M - 1;           // rows past the end read the last pixel and are not stored
     const unsigned char* xr = (const unsigned char*)a.x + m * a.Ci + 16 * hi;
     v4i_t xb = {0, 0, 0, 0};
@@ -84,7 +86,7 @@ hipError_t launch_conv_thin(const ThinConvArgs& a, hipStream_t s)
     static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_thin_i8_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (granted != hipSuccess) return granted;
     const long long strips = (a.M + 31) / 32;
-    EE_LAUNCH(conv_thin_i8_kernel, dim3((unsigned)((strips + 3) / 4)), dim3(256), lds_bytes, s, a, nt, row_pitch);
+    EE_LAUNCH(conv_thin_i8_kernel, dim3(xcd_grid((strips + 3) / 4)), dim3(256), lds_bytes, s, a, nt, row_pitch, (int)((strips + 3) / 4));
     return hipGetLastError();
 }
 
