@@ -283,6 +283,12 @@ int ee_ir_mode(ee_ctx* ctx, int mode);
 int ee_ir_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);
 int ee_ir_set(ee_ctx* ctx, int layer, const int* cfg, int n);
 
+/* Sibling layers in one launch (int8): the branches of a concatenating block, a block's first layer and the convolution on its shortcut.
+ * ee_autotune times the joint launch against the layers one after the other.  ee_group_table / ee_group_set: the table of the launch that
+ * `layer` heads, one entry per batch bucket, a configuration word or 0 = separate (ee_group_set: EE_ERR_ARG when `layer` heads none). */
+int ee_group_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);
+int ee_group_set(ee_ctx* ctx, int layer, const int* cfg, int n);
+
 /* Host copy of the 256-entry table round(2^30 * 2^(-i/256)) used by the integer softmax. */
 const uint32_t* ee_exp2_table(void);
 

@@ -341,31 +341,66 @@ int pack_bneck_shortcut(ee_ctx* ctx, const unsigned char* blob, const StageDesc&
     return EE_OK;
 }
 
+// The order a segment's layers are launched in.  A layer's level is one more than that of its inputs; the layers of a level (the branches of
+// a concatenating block, a block's first layer and the convolution on its shortcut) read nothing of one another and run one behind
+// the other: those that read the same tensor find it in the L2 (Inception-style network, 256 samples: 3670 -> 3560 us).  Segments
+// with layers that can be fused keep the network's order (fused layers are neighbours in it), which for residual networks is the order
+// by level anyway.
+void plan_order(ee_ctx* ctx)
+{
+    ctx->order.assign(ctx->plans.size(), 0);
+    for (const StageDesc& st : ctx->net.stages) {
+        std::vector<int> level_of(st.n_tensors, 0), level(st.n_ops, 0), order(st.n_ops);
+        bool fused = false;
+        for (int k = 0; k < st.n_ops; ++k) {
+            const OpPlan& p = ctx->plans[st.first_op + k];
+            level[k] = 1 + std::max(level_of[p.d.src], p.d.res >= 0 ? level_of[p.d.res] : 0);
+            level_of[p.d.dst] = std::max(level_of[p.d.dst], level[k]);
+            fused |= p.pair || p.ir;
+            order[k] = k;
+        }
+        if (!fused) std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return level[x] < level[y]; });
+        int group = 0;
+        for (int i = 0; i < st.n_ops; ++i) {
+            if (i > 0 && level[order[i]] != level[order[i - 1]]) ++group;
+            ctx->plans[st.first_op + order[i]].group = group;
+            ctx->order[st.first_op + i] = order[i];
+        }
+        auto plan = [&](int i) -> OpPlan& { return ctx->plans[st.first_op + order[i]]; };
+        for (int i = 0, n; ctx->net.dtype == EE_I8 && i < st.n_ops; i += n) {
+            for (n = 0; i + n < st.n_ops && n < EE_GROUP_MAX && plan(i + n).impl == IMPL_MFMA && plan(i + n).group == plan(i).group; ++n) {}
+            plan(i).group_n = n;
+            n = std::max(n, 1);
+        }
+    }
+}
+
 // Assigns the intermediate tensors of every segment to a small pool of reusable buffers
-// (greedy by liveness); the segment input and output stay with the caller.
+// (greedy by liveness, counted in groups of layers that may overlap); the segment input and output stay with the caller.
 void plan_buffers(ee_ctx* ctx)
 {
     const int es = ctx->net.elem_bytes();
     for (const StageDesc& st : ctx->net.stages) {
-        std::vector<int> last_use(st.n_tensors, -1), buf(st.n_tensors, -3);
+        std::vector<int> last_use(st.n_tensors, -1), buf(st.n_tensors, -3);       // group of the last reader
+        auto read_by = [&](int tensor, int k) { last_use[tensor] = std::max(last_use[tensor], ctx->plans[st.first_op + k].group); };
         for (int k = 0; k < st.n_ops; ++k) {
             const OpDesc& d = ctx->plans[st.first_op + k].d;
-            last_use[d.src] = k;
-            if (d.res >= 0) last_use[d.res] = k;
+            read_by(d.src, k);
+            if (d.res >= 0) read_by(d.res, k);
             // the head of a fused pair: the one launch reads this layer's input while it writes the next layer's
             // output, so the input's buffer must stay reserved over both
-            if (k > 0 && ctx->plans[st.first_op + k - 1].pair) last_use[ctx->plans[st.first_op + k - 1].d.src] = k;
+            if (k > 0 && ctx->plans[st.first_op + k - 1].pair) read_by(ctx->plans[st.first_op + k - 1].d.src, k);
             // likewise the head of a fused inverted-residual block, over its three layers
-            if (k > 1 && ctx->plans[st.first_op + k - 2].ir && ctx->plans[st.first_op + k - 2].ir_last() == 2) last_use[ctx->plans[st.first_op + k - 2].d.src] = k;
-            if (k > 2 && ctx->plans[st.first_op + k - 3].ir_sc) last_use[ctx->plans[st.first_op + k - 3].d.src] = k;
-            if (k > 0 && (ctx->plans[st.first_op + k - 1].ir_noexp || ctx->plans[st.first_op + k - 1].ir_stem)) last_use[ctx->plans[st.first_op + k - 1].d.src] = k;
+            if (k > 1 && ctx->plans[st.first_op + k - 2].ir && ctx->plans[st.first_op + k - 2].ir_last() == 2) read_by(ctx->plans[st.first_op + k - 2].d.src, k);
+            if (k > 2 && ctx->plans[st.first_op + k - 3].ir_sc) read_by(ctx->plans[st.first_op + k - 3].d.src, k);
+            if (k > 0 && (ctx->plans[st.first_op + k - 1].ir_noexp || ctx->plans[st.first_op + k - 1].ir_stem)) read_by(ctx->plans[st.first_op + k - 1].d.src, k);
         }
         buf[0] = BUF_EXT_IN;
         buf[st.out_tensor] = BUF_EXT_OUT;
         std::vector<int> free_list;
         std::vector<char> in_use(ctx->pool_sample_bytes.size(), 0);
-        for (int k = 0; k < st.n_ops; ++k) {
-            OpPlan& p = ctx->plans[st.first_op + k];
+        for (int i = 0; i < st.n_ops; ++i) {
+            OpPlan& p = ctx->plans[st.first_op + ctx->order[st.first_op + i]];
             const OpDesc& d = p.d;
             if (buf[d.dst] == -3) {
                 const size_t need = (size_t)d.h_out * d.w_out * d.c_tot * es;      // the whole tensor, also when this op writes a slice of it
@@ -384,9 +419,10 @@ void plan_buffers(ee_ctx* ctx)
             p.src_buf = buf[d.src];
             p.dst_buf = buf[d.dst];
             p.res_buf = d.res >= 0 ? buf[d.res] : -3;
-            // release tensors whose last reader was this op (the destination is never released here)
-            for (int t = 1; t < st.n_tensors; ++t)
-                if (t != d.dst && buf[t] >= 0 && last_use[t] == k) in_use[buf[t]] = 0;
+            // behind the last layer of a group: release the tensors whose last reader was in it
+            if (i + 1 == st.n_ops || ctx->plans[st.first_op + ctx->order[st.first_op + i + 1]].group != p.group)
+                for (int t = 1; t < st.n_tensors; ++t)
+                    if (buf[t] >= 0 && last_use[t] == p.group) in_use[buf[t]] = 0;
         }
     }
 }
@@ -571,6 +607,7 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
                 p.ir = true;
                 p.ir_stem = true;
             }
+    plan_order(ctx);
     plan_buffers(ctx);
     ctx->pool.resize(ctx->pool_sample_bytes.size(), nullptr);
     for (size_t i = 0; i < ctx->pool.size(); ++i)
@@ -793,6 +830,52 @@ void ee_ctx::fill_ir_args(int op, int b, IrArgs& a) const
     a.sh_p = pr.shift; a.lo_p = pr.lo; a.hi_p = pr.hi; a.res_shift = pr.res_shift;
 }
 
+// untuned: fused; measured at 1-256 samples it is faster at nearly every size (bottleneck blocks 1.4-2 times, inverted-residual
+// blocks 1.1-1.9 times, first convolution + pool up to 1.5 times), but for inverted-residual blocks of more than 96 output channels
+bool ee_ctx::ir_wanted(int op, int b) const
+{
+    const OpPlan& p = plans[(size_t)op];
+    if (!p.ir || ir_mode == 0) return false;
+    if (ir_mode == 2) return true;
+    if (!p.ir_cfg.empty()) return p.ir_cfg[std::min<size_t>(bucket_of(b), p.ir_cfg.size() - 1)] != 0;
+    return p.ir_bneck || p.ir_stem || plans[(size_t)op + p.ir_last()].d.c_out <= 96;
+}
+
+// The configuration of an untuned launch of several layers: as for one layer of their joint size and the longest reduction.
+static int group_default(const ConvArgs* a, int n)
+{
+    long long blocks = 0, tiles = 0;
+    int longest = 0;
+    bool few = true;
+    auto kbytes = [&](int i) { return a[i].kh * a[i].kw * a[i].Ci; };
+    for (int i = 0; i < n; ++i) {
+        blocks += (long long)((a[i].M + 63) / 64) * ((a[i].Co + 63) / 64);
+        tiles += (long long)((a[i].M + 31) / 32) * ((a[i].Co + 31) / 32);
+        few &= conv_skinny_default(a[i], 1) != 0;
+        if (kbytes(i) > kbytes(longest)) longest = i;
+    }
+    if (few && tiles <= 400) return tiles <= 100 ? skinny_cfg(16, 1, 2) : skinny_cfg(32, 1, 2);
+    return conv_igemm_default(a[longest], 1, blocks);
+}
+
+hipError_t ee_ctx::launch_group(int stage, int at, int n, int b, const void* act_in, void* act_out, int cfg)
+{
+    const StageDesc& st = net.stages[(size_t)stage];
+    ConvArgs a[EE_GROUP_MAX] = {};
+    for (int j = 0; j < n; ++j) {
+        const int op = st.first_op + order[(size_t)(st.first_op + at + j)];
+        const OpPlan& p = plans[(size_t)op];
+        fill_conv_args(op, b, a[j]);
+        a[j].x = resolve(this, p.src_buf, act_in, act_out);
+        a[j].y = resolve(this, p.dst_buf, act_in, act_out);
+        a[j].res = p.d.res >= 0 ? resolve(this, p.res_buf, act_in, act_out) : nullptr;
+        a[j].xs = p.src_buf == BUF_EXT_IN ? zc_in : nullptr;
+        a[j].ys = p.dst_buf == BUF_EXT_OUT ? zc_out : nullptr;
+        if ((a[j].xs || a[j].ys) && b > EE_ZC_MAX_B) return hipErrorInvalidValue;
+    }
+    return launch_conv_group(a, n, cfg ? cfg : group_default(a, n), stream);
+}
+
 hipError_t ee_ctx::launch_pair(int op, int b, const void* src, void* dst, const void* res, int cfg)
 {
     const OpPlan& q = plans[op + 1];
@@ -935,6 +1018,51 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
             if (!rc) p.pair_cfg = best;
         }
     }
+    // layers that can share a launch: every configuration of that launch against the layers one after the other
+    for (size_t s = 0; s < ctx->net.stages.size() && !rc; ++s) {
+        const StageDesc& st = ctx->net.stages[s];
+        for (int at = 0; at < st.n_ops && !rc; ++at) {
+            const int head = st.first_op + ctx->order[(size_t)(st.first_op + at)];
+            OpPlan& p = ctx->plans[(size_t)head];
+            if (p.group_n < 2) continue;
+            std::vector<int> best(buckets.size(), 0);
+            for (size_t bi = 0; bi < buckets.size() && !rc; ++bi) {
+                const int b = buckets[bi];
+                float best_ms = 0.f;
+                bool few = true;
+                for (int j = 0; j < p.group_n; ++j) {
+                    const int op = st.first_op + ctx->order[(size_t)(st.first_op + at + j)];
+                    best_ms += best_time[(size_t)op][bi];
+                    few &= (long long)b * ctx->plans[(size_t)op].d.h_out * ctx->plans[(size_t)op].d.w_out <= EE_SKINNY_MAX_ROWS;
+                }
+                std::vector<int> cands;
+                for (int tile = 1; tile <= 4; ++tile)
+                    for (int ksel = 1; ksel <= 3; ++ksel)
+                        for (int ns = 2; ns <= 4; ++ns) cands.push_back(tile | (ksel << 4) | (ns << 8));
+                if (few)
+                    for (const int cfg : {skinny_cfg(16, 1, 2), skinny_cfg(16, 1, 3), skinny_cfg(32, 1, 2), skinny_cfg(32, 1, 3), skinny_cfg(32, 2, 2), skinny_cfg(32, 2, 3)}) cands.push_back(cfg);
+                auto timed_cfg = [&](int n, int cfg) {
+                    return time_launch(n, [=] { if (head > st.first_op) ctx->run_stage((int)s, b, ctx->in_buf[s], ctx->out_buf[s], false, head - 1); }, [&] {
+                        return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] { return ctx->launch_group((int)s, at, p.group_n, b, ctx->in_buf[s], ctx->out_buf[s], cfg); }) == hipSuccess ? EE_OK : EE_ERR_ARG;
+                    });
+                };
+                std::vector<std::pair<float, int>> timed;
+                for (const int cfg : cands) {
+                    const float ms = timed_cfg(1, cfg);
+                    if (rc) break;
+                    if (ms >= 0.f) timed.emplace_back(ms, cfg);
+                }
+                std::sort(timed.begin(), timed.end());
+                if (timed.size() > 4) timed.resize(4);
+                for (const auto& t : timed) {
+                    if (rc) break;
+                    const float ms = std::min(t.first, timed_cfg(reps, t.second));
+                    if (ms >= 0.f && ms < best_ms) { best_ms = ms; best[bi] = t.second; }
+                }
+            }
+            if (!rc) p.group_cfg = best;
+        }
+    }
     // fused blocks: the one launch against the block's layers with their tuned configurations.  A block of four layers (a
     // convolution on the shortcut in front of a bottleneck block) is tuned after the others, against that convolution followed
     // by whatever the table says for the block of three behind it.
@@ -1070,6 +1198,25 @@ extern "C" int ee_ir_set(ee_ctx* ctx, int op, const int* cfg, int n)
     return EE_OK;
 }
 
+extern "C" int ee_group_table(const ee_ctx* ctx, int op, int* cfg_out, int n)
+{
+    if (!ctx || op < 0 || op >= (int)ctx->plans.size() || n < 0 || (n > 0 && !cfg_out)) return EE_ERR_ARG;
+    const std::vector<int>& c = ctx->plans[op].group_cfg;
+    for (int i = 0; i < n && i < (int)c.size(); ++i) cfg_out[i] = c[i];
+    return (int)c.size();
+}
+
+extern "C" int ee_group_set(ee_ctx* ctx, int op, const int* cfg, int n)
+{
+    if (!ctx || op < 0 || op >= (int)ctx->plans.size() || n < 0 || n > 16 || (n > 0 && !cfg)) return EE_ERR_ARG;
+    OpPlan& p = ctx->plans[op];
+    if (p.group_n < 2) return EE_ERR_ARG;
+    for (int i = 0; i < n; ++i)
+        if (cfg[i] != 0 && !conv_group_config_ok(cfg[i])) return EE_ERR_ARG;
+    p.group_cfg.assign(cfg, cfg + n);
+    return EE_OK;
+}
+
 extern "C" int ee_pair_mode(ee_ctx* ctx, int mode)
 {
     if (!ctx || mode < 0 || mode > 2) return EE_ERR_ARG;
@@ -1094,7 +1241,8 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
     gap_fused = false;
     const StageDesc& st = net.stages[stage];
     const int dt = net.dtype, es = net.elem_bytes();
-    for (int k = 0; k < st.n_ops; ++k) {
+    for (int i = 0; i < st.n_ops; ++i) {
+        const int k = order[(size_t)(st.first_op + i)];
         if (only_op >= 0 && st.first_op + k != only_op) continue;
         if (only_block >= 0 && (st.first_op + k < only_block || st.first_op + k > only_block + plans[(size_t)only_block].ir_last())) continue;
         OpPlan& p = plans[st.first_op + k];
@@ -1118,11 +1266,8 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
         if (p.ir && ir_mode > 0 && cfg_force == 0 && forced_conv_tile() == 0 && only_op < 0 && !xs && ir_slots_ok &&
             !(ir_pools && !(p.ir_bneck && plans[st.first_op + k + ir_last].d.res >= 0))) {
             // this layer, the depthwise layer and the projection as one launch, where the table says it is faster
-            // untuned: fused; measured at 1-256 samples it is faster at nearly every size (bottleneck blocks 1.4-2 times, inverted-residual
-            // blocks 1.1-1.9 times, first convolution + pool up to 1.5 times), but for inverted-residual blocks of more than 96 output channels
-            const int ic = p.ir_cfg.empty() ? (p.ir_bneck || p.ir_stem || plans[st.first_op + k + ir_last].d.c_out <= 96)
-                                            : p.ir_cfg[std::min<size_t>(bucket_of(b), p.ir_cfg.size() - 1)];
-            if ((ic != 0 || ir_mode == 2) && p.ir_stem) {
+            const bool fuse = ir_wanted(st.first_op + k, b);
+            if (fuse && p.ir_stem) {
                 const OpPlan& q2 = plans[st.first_op + k + 1];
                 if (!(first_packed && k == 0)) {                                 // the folded copy of the input, as in front of the layer alone
                     const double pb = (double)b * ((double)d.h_in * d.w_in * d.c_in + (double)p.Hp * p.Wp * 16) * es;
@@ -1137,10 +1282,10 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 e = timed(EE_K_CONV_STREAM, ops + q2.ops_per_sample * b, bytes + q2.bytes_per_sample * b + q2.weight_bytes - mid,
                           [&] { return launch_stem_pool(ca, yq, q2.d.h_out, q2.d.w_out, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
-                ++k;                                                             // the pool is done
+                ++i;                                                             // the pool is done
                 continue;
             }
-            if (ic != 0 || ir_mode == 2) {
+            if (fuse) {
                 const OpPlan& q2 = plans[st.first_op + k + ir_last];
                 IrArgs ia{};
                 fill_ir_args(st.first_op + k, b, ia);
@@ -1159,7 +1304,28 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 e = timed(EE_K_CONV_MFMA, f_ops, f_bytes, [&] { return p.ir_bneck ? launch_bneck_block(ia, stream) : launch_ir_block(ia, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
                 if (ia.gap_sums) gap_fused = true;
-                k += ir_last;                                                    // the block's other layers are done
+                i += ir_last;                                                    // the block's other layers are done
+                continue;
+            }
+        }
+        if (p.group_n > 1 && cfg_force == 0 && only_op < 0 && forced_conv_tile() == 0) {
+            // this layer and its siblings behind it as one launch, unless the table says otherwise or one of them is part of something else
+            const int gc = p.group_cfg.empty() ? 0 : p.group_cfg[std::min<size_t>(bucket_of(b), p.group_cfg.size() - 1)];
+            bool together = p.group_cfg.empty() || gc != 0;
+            double g_ops = 0, g_bytes = 0;
+            for (int j = 0; j < p.group_n && together; ++j) {
+                const int op = st.first_op + order[(size_t)(st.first_op + i + j)];
+                const OpPlan& m = plans[(size_t)op];
+                together = !ir_wanted(op, b) && !pair_wanted(m, b) && !(gap_fuse_dst && op == gap_fuse_op[(size_t)stage]) &&
+                           (only_block < 0 || (op >= only_block && op <= only_block + plans[(size_t)only_block].ir_last())) &&
+                           !(zc_in && m.d.res >= 0 && m.res_buf == BUF_EXT_IN);
+                g_ops += m.ops_per_sample * b;
+                g_bytes += m.bytes_per_sample * b + m.weight_bytes;
+            }
+            if (together) {
+                e = timed(EE_K_CONV_MFMA, g_ops, g_bytes, [&] { return launch_group(stage, i, p.group_n, b, act_in, act_out, gc); }, st.first_op + k);
+                if (e != hipSuccess) return EE_ERR_DEVICE;
+                i += p.group_n - 1;
                 continue;
             }
         }
@@ -1186,9 +1352,9 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                                                         (gap_fuse_dst && only_op < 0 && st.first_op + k + 1 == gap_fuse_op[(size_t)stage]));
             if (p.pair && pair_mode > 0 && cfg == 0 && only_op < 0 && !xs && !ys && !q_scatter) {
                 // this layer and the next as one launch, where the table says it is the faster way
-                const int pc = p.pair_cfg.empty() ? 0 : p.pair_cfg[std::min<size_t>(bucket_of(b), p.pair_cfg.size() - 1)];
                 // (untuned never: with the configurations that untuned launches get, the two layers were faster at every batch of 1-31 samples)
-                if (pc != 0 || pair_mode == 2) {
+                if (pair_wanted(p, b)) {
+                    const int pc = p.pair_cfg.empty() ? 0 : p.pair_cfg[std::min<size_t>(bucket_of(b), p.pair_cfg.size() - 1)];
                     const OpPlan& q = plans[st.first_op + k + 1];
                     void* dst2 = resolve(this, q.dst_buf, act_in, act_out);
                     const void* res2 = q.d.res >= 0 ? resolve(this, q.res_buf, act_in, act_out) : nullptr;
@@ -1196,7 +1362,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                     e = timed(EE_K_CONV_MFMA, ops + q.ops_per_sample * b, bytes + q.bytes_per_sample * b + q.weight_bytes - mid,
                               [&] { return launch_pair(st.first_op + k, b, src, dst2, res2, pc); }, st.first_op + k);
                     if (e != hipSuccess) return EE_ERR_DEVICE;
-                    ++k;                                                             // the next layer is done
+                    ++i;                                                             // the next layer is done
                     continue;
                 }
             }

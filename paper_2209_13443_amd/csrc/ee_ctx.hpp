@@ -23,6 +23,9 @@ struct OpPlan {
     int Kp = 0, kwp = 0, Hp = 0, Wp = 0;
     int src_buf = 0, dst_buf = 0, res_buf = 0;   // BUF_EXT_* or an index into Ctx::pool
     int pad_buf = -1;           // padded copy of the input: 4 channels + spatial border (IMPL_MFMA_C4), channels to 16 bytes (IMPL_MFMA_CPAD)
+    int group = 0;              // layers of a segment with the same number read nothing of one another: they may run at the same time (see plan_order)
+    int group_n = 0;            // > 1: this layer and the group_n - 1 behind it in the launch order can run as one launch (int8)
+    std::vector<int> group_cfg; // per batch bucket: configuration of that launch, 0 = every layer by itself; empty = not tuned
     int ci_eff = 0;             // input channels the matrix-core kernel sees (c_in, or c_in padded to a 16-byte multiple)
     // IMPL_MFMA_S2D: stride-2 first layer over <= 4 channels, run as a stride-1 convolution with a ks2 x ks2 kernel over the
     // zero-padded image folded into Hp x Wp super-pixels of 2 x 2 pixels x 4 channels (Hp, Wp, ks2 reuse the fields above)
@@ -74,6 +77,7 @@ struct ee_ctx {
     int b_max = 0;
     hipStream_t stream = nullptr;
     std::vector<ee::OpPlan> plans;               // same order as net.ops
+    std::vector<int> order;                      // per segment the order its layers are launched in: order[first_op + i] is the i-th one, counted from first_op
     std::vector<void*> pool;                     // intermediate activations, b_max samples each
     std::vector<size_t> pool_sample_bytes;
     std::vector<void*> pad_bufs;                 // zero-padded 4-channel input copies (first layers)
@@ -148,6 +152,13 @@ struct ee_ctx {
     }
     // launches layer `op` (an index into plans) on b samples with the given kernel configuration (0 = by shape)
     hipError_t launch_conv(int op, int b, const void* src, void* dst, const void* res, int cfg, const uint16_t* xs = nullptr, const uint16_t* ys = nullptr, int32_t* gap_sums = nullptr);
+    // the layers at positions [at, at + n) of a segment's launch order in one launch (see OpPlan::group_n); cfg 0 = by shape
+    hipError_t launch_group(int stage, int at, int n, int b, const void* act_in, void* act_out, int cfg);
+    bool pair_wanted(const ee::OpPlan& p, int b) const
+    {
+        return p.pair && pair_mode > 0 && (pair_mode == 2 || (!p.pair_cfg.empty() && p.pair_cfg[std::min<size_t>(bucket_of(b), p.pair_cfg.size() - 1)] != 0));
+    }
+    bool ir_wanted(int op, int b) const;                         // the fused block headed by layer op, by mode, table or (untuned) rule
     // layers op and op + 1 as one fused launch: src feeds layer op, res and dst belong to layer op + 1
     hipError_t launch_pair(int op, int b, const void* src, void* dst, const void* res, int cfg);
     void fill_ir_args(int op, int b, ee::IrArgs& a) const;      // the block headed by layer `op`; x, res and y are left to the caller

@@ -152,6 +152,7 @@ hipError_t launch_conv_mfma_i8(const ConvArgs& a, hipStream_t s);
 hipError_t launch_conv_mfma_bf16(const ConvArgs& a, hipStream_t s);
 // asynchronous-copy implicit GEMM (ES = element bytes); tile 0 = chosen by shape, 1..4 forced
 template <int ES> hipError_t launch_conv_igemm(const ConvArgs& a, int tile, hipStream_t s);
+int conv_igemm_default(const ConvArgs& a, int es, long long blocks);      // its configuration for an untuned launch of that many 64 x 64 tiles
 // the fused pair (ES = element bytes); cfg 0 = chosen by shape
 template <int ES> hipError_t launch_conv_pair(const PairArgs& p, int cfg, hipStream_t s);
 bool conv_pair_supported(int es, int co2, int kh, int kw, int ci, int co3);
@@ -173,6 +174,10 @@ inline bool cfg_is_skinny(int cfg)
 bool conv_skinny_config_ok(int cfg);
 int conv_skinny_default(const ConvArgs& a, int es);    // configuration of an untuned launch it is the faster one for, else 0
 template <int ES> hipError_t launch_conv_skinny(const ConvArgs& a, int cfg, hipStream_t s);
+// several independent int8 layers in one launch with one configuration (kernels_group.hip)
+enum { EE_GROUP_MAX = 4 };
+bool conv_group_config_ok(int cfg);
+hipError_t launch_conv_group(const ConvArgs* a, int n, int cfg, hipStream_t s);
 enum { EE_CFG_IR_BLOCK = 0x20000 }; // ee_time_layer: the fused inverted-residual block headed by the layer
 // streaming kernel for large, thin int8 layers (es = element bytes); hipErrorInvalidValue for a layer it does not cover
 bool conv_stream_supported(const ConvArgs& a, int es);

@@ -424,6 +424,36 @@ def test_small_exit_heads(torch, ee, orc, h, w, c, n_cls, dtype):
     eng.close()
 
 
+GROUP_CFGS = [0x211, 0x331, 0x422, 0x232, 0x313, 0x423, 0x333, 0x214, 0x324, 0x434] + [0x2213, 0x2214, 0x2223, 0x2224, 0x4213, 0x4214]
+
+
+@pytest.mark.parametrize("cfg", GROUP_CFGS)
+def test_sibling_layers_in_one_launch_bit_exact(torch, ee, orc, cfg):
+    """Every configuration of the launch that runs a block's branches (or a first layer and its shortcut) together: branches of different
+    kernels, widths and reductions, channel slices at odd offsets, tiles and eighths of the batch that do not divide."""
+    for blob in [W.load_net("inception_small_i8"), W.load_net("resnet50_small_i8"), W.random_net(5, W.DT_I8), W.random_net(9, W.DT_I8)]:
+        eng = ee.Engine(blob, 5)
+        eng.ir_mode(0)
+        heads = 0
+        for layer in range(len(blob.ops)):
+            try:
+                eng.load_tables({"group": {str(layer): [cfg]}})
+                heads += 1
+            except ee.EEError:
+                pass
+        for b in (5, 1):
+            act = W.input_pool(blob, b)
+            for s in range(blob.n_stages):
+                say(f"[case] cfg {cfg:#x} {len(blob.ops)} layers, {heads} joint launches, segment {s} b={b}")
+                ref = orc.stage_forward(blob, s, act)
+                got = host(eng.stage_forward(s, dev(torch, act), ref.shape[1:]), ref)
+                assert np.array_equal(got, ref), f"segment {s} b={b}: {np.count_nonzero(got != ref)} of {ref.size} differ"
+                act = ref
+        if len(blob.ops) > 40:
+            assert heads > 0
+        eng.close()
+
+
 def test_thresholds_zero_and_above_one(torch, ee, orc):
     blob = W.load_net("tiny_i8")
     eng = ee.Engine(blob, 8)
