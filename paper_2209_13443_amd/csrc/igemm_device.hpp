@@ -70,12 +70,13 @@ __device__ __forceinline__ unsigned fast_div(unsigned m, unsigned d, unsigned ma
     return q;
 }
 
-__device__ __forceinline__ uint32_t to_bf16_rne(float v)
+// two floats as bf16, a lowest: one v_cvt_pk_bf16_f32 (round to nearest even; the same bits as rounding by hand for every float, NaNs
+// included) instead of five instructions per value
+__device__ __forceinline__ uint32_t pack2_bf16(float a, float b)
 {
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40;
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{a, b}), v2bf));
 }
 
 __device__ __forceinline__ int clamp_i32(int v, int lo, int hi)       // lo <= hi

@@ -117,8 +117,8 @@ __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsi
                         t0 = fminf(fmaxf(t0, a.f_lo), a.f_hi); t1 = fminf(fmaxf(t1, a.f_lo), a.f_hi);
                         t2 = fminf(fmaxf(t2, a.f_lo), a.f_hi); t3 = fminf(fmaxf(t3, a.f_lo), a.f_hi);
                         uint2 out;
-                        out.x = to_bf16_rne(t0) | (to_bf16_rne(t1) << 16);
-                        out.y = to_bf16_rne(t2) | (to_bf16_rne(t3) << 16);
+                        out.x = pack2_bf16(t0, t1);
+                        out.y = pack2_bf16(t2, t3);
                         if (WIDE) *(uint2*)cell = out;
                         else if (inside) *(uint2*)((uint16_t*)a.y + oy_) = out;
                     }

@@ -35,13 +35,7 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 constexpr int kStep = 128;                 // bytes of the reduction axis staged per barrier
 constexpr int kLdsRow = kStep + 16;        // staged row + 16 bytes of padding (conflict-free ds_read_b128)
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float v)
-{
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x40);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+__device__ __forceinline__ uint16_t f32_to_bf16_rne(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 __device__ __forceinline__ int requant_i8(int t, int shift, int lo, int hi)

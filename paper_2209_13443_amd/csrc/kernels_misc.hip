@@ -10,13 +10,7 @@ namespace ee {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne_m(float v)
-{
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x40);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+__device__ __forceinline__ uint16_t f32_to_bf16_rne_m(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
 __device__ __forceinline__ float bf16_to_f32_m(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ int med3_i32(int v, int lo, int hi)       // lo <= hi: v clamped to [lo, hi]
 {

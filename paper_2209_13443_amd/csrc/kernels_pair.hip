@@ -248,8 +248,8 @@ __global__ __launch_bounds__(256) void conv_pair_kernel(PairArgs p, int gm, int 
 #pragma unroll
                         for (int e = 0; e < 4; ++e) t[e] = fminf(fmaxf(acc[j][i][4 * g + e] + __int_as_float(b4[e]), a.f_lo), a.f_hi);
                         uint2 out;
-                        out.x = to_bf16_rne(t[0]) | (to_bf16_rne(t[1]) << 16);
-                        out.y = to_bf16_rne(t[2]) | (to_bf16_rne(t[3]) << 16);
+                        out.x = pack2_bf16(t[0], t[1]);
+                        out.y = pack2_bf16(t[2], t[3]);
                         *(uint2*)cell = out;
                     }
                 }
@@ -330,8 +330,8 @@ __global__ __launch_bounds__(256) void conv_pair_kernel(PairArgs p, int gm, int 
                         t0 = fminf(fmaxf(t0, p.f_lo), p.f_hi); t1 = fminf(fmaxf(t1, p.f_lo), p.f_hi);
                         t2 = fminf(fmaxf(t2, p.f_lo), p.f_hi); t3 = fminf(fmaxf(t3, p.f_lo), p.f_hi);
                         uint2 out;
-                        out.x = to_bf16_rne(t0) | (to_bf16_rne(t1) << 16);
-                        out.y = to_bf16_rne(t2) | (to_bf16_rne(t3) << 16);
+                        out.x = pack2_bf16(t0, t1);
+                        out.y = pack2_bf16(t2, t3);
                         *(uint2*)cell = out;
                     }
                 }

@@ -231,8 +231,8 @@ __device__ __forceinline__ void skinny_tile(const ConvArgs& a, int gn, unsigned 
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = fminf(fmaxf(v[e], a.f_lo), a.f_hi);
             uint2 out;
-            out.x = to_bf16_rne(v[0]) | (to_bf16_rne(v[1]) << 16);
-            out.y = to_bf16_rne(v[2]) | (to_bf16_rne(v[3]) << 16);
+            out.x = pack2_bf16(v[0], v[1]);
+            out.y = pack2_bf16(v[2], v[3]);
             *(uint2*)((uint16_t*)a.y + o) = out;
         }
     }
