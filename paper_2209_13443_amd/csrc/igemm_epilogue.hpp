@@ -7,6 +7,7 @@
 
 #include "ee_internal.hpp"
 #include "igemm_device.hpp"
+#include "ir_device.hpp"
 
 namespace ee {
 namespace {
@@ -42,10 +43,30 @@ __device__ __forceinline__ void igemm_stage_bias_res(const ConvArgs& a, unsigned
     }
 }
 
+// Where the accumulators start: int8 at the bias (staged in LDS by then, the rounding constant part of it), so that the epilogue has no
+// addition for it; bf16 at zero (its bias is added behind the sum).  The wavefront groups that share a reduction: only one has the bias.
+template <int ES, int TN, int TM, typename ACC>
+__device__ __forceinline__ void igemm_init_acc(ACC& acc, const unsigned char* lds, unsigned bias_off, int wn0, int lane, bool with_bias)
+{
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            v4i b4 = {0, 0, 0, 0};
+            if (ES == 1 && with_bias) b4 = *(const v4i*)(lds + bias_off + (wn0 + 32 * j + 8 * g + 4 * (lane >> 5)) * 4);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[j][i][4 * g + e] = b4[e];
+        }
+}
+
 // Bias, residual, requantisation / clamp and packing in the accumulator layout, the tile through LDS (at ro_off; with a
 // staged residual tile the results replace it in place), then 16-byte stores along the channels.  Every wavefront of the
 // workgroup calls it (it contains a barrier); `active` says whether this wavefront holds accumulators to write.
 // Layers whose pixels are not whole 16-byte chunks (wide == false) store straight from the registers.
+// The short reductions are bound by the instructions here: an int8 value costs two (clamp on the unshifted accumulator, a shift that writes
+// its byte in place: ir_requant_pack) and two more with a residual; 3.75 and 4.75 before, with the bias added here and packing permutes.
 template <int ES, int BM, int BN, int NT, typename ACC>
 __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsigned char* lds, unsigned ro_off, unsigned bias_off, int m0, int n0,
                                                int wm0, int wn0, int tid, bool has_res, bool wide, bool active)
@@ -75,38 +96,56 @@ __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsi
         return (long long)a.ys[n] * howo + ((unsigned)m - n * howo);
     };
     const int swz_l = oswz(frow);
+    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
     auto finish = [&](auto res_tag, auto wide_tag) {
         constexpr bool RES = decltype(res_tag)::value, WIDE = decltype(wide_tag)::value;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int r = wm0 + 32 * i + frow;
             const int m = m0 + r;
+            if constexpr (ES == 1 && WIDE) {
+                // a lane's share of a block in the tile: 16 consecutive channels of its pixel, one chunk
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    unsigned char* cell = ro + r * OROW + ((((wn0 >> 4) + 2 * j + hi) ^ swz_l) << 4);
+                    if constexpr (RES) {
+                        const v4i rv = *(const v4i*)cell;
+                        const auto s02 = __builtin_amdgcn_permlane32_swap((unsigned)rv[0], (unsigned)rv[1], false, false);
+                        const auto s13 = __builtin_amdgcn_permlane32_swap((unsigned)rv[2], (unsigned)rv[3], false, false);
+                        const unsigned rq[4] = {s02[0], s13[0], s02[1], s13[1]};             // the accumulator layout's quads
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[j][i][4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << a.res_shift;
+                    }
+                    *(v4i*)cell = ir_requant_pack<!RES>(acc[j][i], cl);
+                }
+                continue;
+            }
             unsigned char* rowp = ro + r * OROW + 4 * hi * ES;
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int cl = wn0 + 32 * j + 8 * g + 4 * hi;                     // first of this lane's 4 channels
+                    const int ch0 = wn0 + 32 * j + 8 * g + 4 * hi;                    // first of this lane's 4 channels
                     const int chunk = (wn0 * ES >> 4) + ((32 * j + 8 * g) * ES >> 4);  // 4*hi*ES stays inside the chunk
                     unsigned char* cell = rowp + ((chunk ^ swz_l) << 4) + (((32 * j + 8 * g) * ES) & 15);
-                    const long long o = (long long)m * a.Co + n0 + cl;                  // in the residual (never a slice)
-                    const long long oy_ = (WIDE ? 0ll : out_row(m) * a.ldc) + a.c_off + n0 + cl;   // in the output (used by the direct stores only)
-                    const bool inside = WIDE || (m < a.M && n0 + cl < a.Co);
-                    const v4i b4 = *(const v4i*)(lbias + cl);
+                    const long long o = (long long)m * a.Co + n0 + ch0;                  // in the residual (never a slice)
+                    const long long oy_ = (WIDE ? 0ll : out_row(m) * a.ldc) + a.c_off + n0 + ch0;   // in the output (used by the direct stores only)
+                    const bool inside = WIDE || (m < a.M && n0 + ch0 < a.Co);
                     if constexpr (ES == 1) {
                         int packed = 0;
-                        if (RES) packed = WIDE ? *(const int*)cell : (inside ? *(const int*)((const signed char*)a.res + o) : 0);
+                        if (RES) packed = inside ? *(const int*)((const signed char*)a.res + o) : 0;
                         int q[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            int t = acc[j][i][4 * g + e] + b4[e];                     // the rounding constant is part of the bias
+                            int t = acc[j][i][4 * g + e];
                             if (RES) t += __builtin_amdgcn_sbfe(packed, 8 * e, 8) << a.res_shift;
                             q[e] = clamp_i32(t >> a.shift, a.lo, a.hi);
                         }
-                        const unsigned out = pack4_i8(q[0], q[1], q[2], q[3]);
-                        if (WIDE) *(unsigned*)cell = out;
-                        else if (inside) *(unsigned*)((signed char*)a.y + oy_) = out;
+                        if (inside) *(unsigned*)((signed char*)a.y + oy_) = pack4_i8(q[0], q[1], q[2], q[3]);
                     } else {
+                        const v4i b4 = *(const v4i*)(lbias + ch0);
                         uint2 packed = {0u, 0u};
                         if (RES) packed = WIDE ? *(const uint2*)cell : (inside ? *(const uint2*)((const uint16_t*)a.res + o) : packed);
                         const float r0 = __uint_as_float(packed.x << 16), r1 = __uint_as_float(packed.x & 0xFFFF0000u);

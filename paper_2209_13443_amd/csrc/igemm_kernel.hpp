@@ -170,12 +170,6 @@ __device__ __forceinline__ void igemm_tile(const ConvArgs& a, int gm, int gn, un
 
     using acc_t = typename std::conditional<ES == 1, v16i, v16f>::type;
     acc_t acc[TN][TM];
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][i][v] = 0;
 
     // One reduction step out of stage `sc`; with ISSUE the copies of a later step into stage `si` are
     // spread between the matrix instructions so that the copy queue fills while the matrix cores work.
@@ -286,11 +280,14 @@ __device__ __forceinline__ void igemm_tile(const ConvArgs& a, int gm, int gn, un
     for (int s = 0; s < ns - 1; ++s)
         if (s < nk) issue_all(s);
     int st_c = 0, st_i = ns - 1, ks = 0;
-    if constexpr (V2) {
+    {
         const int ahead = (ns - 1 < nk ? ns - 1 : nk) - 1;      // stages issued behind the first one
         if (ahead <= 0) wait_copies_then_barrier<0>();
         else if (ahead == 1) wait_copies_then_barrier<LPT>();
         else wait_copies_then_barrier<2 * LPT>();
+    }
+    igemm_init_acc<ES, TN, TM>(acc, lds, bias_off, wn0, lane, KSPL == 1 || kpart == 0);
+    if constexpr (V2) {
         static_for<FD>([&](auto u_tag) {                // fragments of the first FD sub-steps
             constexpr int U = decltype(u_tag)::value;
 #pragma unroll

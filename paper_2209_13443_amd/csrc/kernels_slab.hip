@@ -162,12 +162,6 @@ __global__ __launch_bounds__(256) void conv_slab_kernel(ConvArgs a, int gm, int 
 
     using acc_t = typename std::conditional<ES == 1, v16i, v16f>::type;
     acc_t acc[TN][TM];
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][i][v] = 0;
 
     v4i gw[NFB][TN], gx[NFB][TM];
     auto read_x = [&](v4i* x) {                     // the reader's current sub-step, then one further
@@ -230,6 +224,7 @@ __global__ __launch_bounds__(256) void conv_slab_kernel(ConvArgs a, int gm, int 
         else if (ahead == 1) wait_all_then_barrier<LPT>();
         else wait_all_then_barrier<2 * LPT>();
     }
+    igemm_init_acc<ES, TN, TM>(acc, lds, bias_off, wn0, lane, true);
     static_for<FD>([&](auto u_tag) {                // fragments of the first FD sub-steps
         constexpr int U = decltype(u_tag)::value;
 #pragma unroll
