@@ -12,6 +12,14 @@
 namespace ee {
 namespace {
 
+// Every argument a workgroup needs before its first copy, requested at once: one scalar round trip instead of one per first use
+// (ResNet-50 at batch 32: int8 416 -> 407 us, bf16 855 -> 830).
+__device__ __forceinline__ void preload(const ConvArgs& a)
+{
+    asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.bias), "s"(a.res), "s"(a.zeros), "s"(a.xs), "s"(a.M), "s"(a.H), "s"(a.W), "s"(a.Ci), "s"(a.Ho), "s"(a.Wo), "s"(a.Co));
+    asm volatile("" ::"s"(a.kh), "s"(a.kw), "s"(a.stride), "s"(a.pad), "s"(a.pad_w), "s"(a.ldc), "s"(a.c_off), "s"(a.Kp), "s"(a.magic_howo), "s"(a.magic_wo), "s"(a.tap_rows), "s"(a.plain_step));
+}
+
 // The output tile in LDS: rows of BN elements, chunk c of row r at c ^ oswz(r), oswz(r) = (r / rows per 256 bytes)
 // & (chunks per row - 1): the 32 rows a wavefront touches with one 4- or 8-byte access per lane then spread over
 // the banks as evenly as the row length allows.

@@ -70,6 +70,7 @@ __device__ __forceinline__ void igemm_tile(const ConvArgs& a, int gm, int gn, un
     static_assert(NA >= 1 && NB >= 1 && BM % RPP == 0 && BN % RPP == 0, "tile too small for this many lanes");
     static_assert(SPW >= 1 && SPW * KSPL == NSUB, "more wavefront groups than sub-steps");
 
+    preload(a);
     const int xcd = block & 7, wslot = block >> 3;
     const int mslot = (int)fast_div((unsigned)wslot, (unsigned)gn, magic_gn);
     const int mt = xcd_unit((unsigned)(mslot << 3 | xcd), gm), nt = wslot - mslot * gn;

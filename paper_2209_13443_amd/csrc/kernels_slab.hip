@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256) void conv_slab_kernel(ConvArgs a, int gm, int 
     constexpr int ZERO_BYTES = 1024;               // what taps outside the image read; at least one pixel long
     static_assert(LPT >= 1 && BN % RPP == 0 && SPW >= 4 && SPW % NFB == 0, "tile / step not supported");
 
+    preload(a);
     const int xcd = blockIdx.x & 7, wslot = blockIdx.x >> 3;
     const int mslot = (int)fast_div((unsigned)wslot, (unsigned)gn, magic_gn);
     const int mt = xcd_unit((unsigned)(mslot << 3 | xcd), gm), nt = wslot - mslot * gn;
