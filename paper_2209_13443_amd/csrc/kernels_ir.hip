@@ -32,6 +32,10 @@
 // expands, filters and projects every pixel of the tile for the groups g = wavefront, wavefront + 4 (or 8), ... through a buffer
 // of its own, with no barrier inside the loop; the partial projection sums are added in LDS (integer adds,
 // exact in any order) and the epilogue is shared out by (pixel block, output block).
+// What bounds it: the blocks on large images issue vector instructions for 55-60 % of their time and matrix instructions for
+// 15-30 % (112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels, 64 images: 31.5 us, from 35.7 before divisions became multiplications,
+// only tiles with a frame cleared their buffers and the output blocks went to the wavefronts with less of the expansion; 112 x 112,
+// 32 -> 16 without expansion: 27.4 -> 22.4 us); those on small images wait for their chain of loads, matrix instructions and barriers.
 // Every accumulation is int32 and exact, rounding points are those of the three separate layers: results are equal
 // bit for bit.
 #include "ee_internal.hpp"
@@ -46,6 +50,8 @@ struct IrTile {
     int iw, ih;            // staged pixels under a tile
     int cpp;               // 8-byte chunks per input pixel
     unsigned magic_cpp, magic_iw;   // floor(2^32 / d) + 1: n / d for n < 2^16
+    unsigned magic_tx, magic_ty;    // the same for tiles_x, tiles_y (n * d < 2^32: checked by ir_block_plan)
+    int magic_nbw, magic_pbw;       // floor(2^16 / d) + 1: n / d for n < 2^8
     int xp;                // bytes per staged input pixel
     int x_bytes, e_bytes;  // LDS: staged input, one buffer of expanded pixels
     int total;             // workgroups with work
@@ -70,7 +76,10 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int u = xcd_unit(blockIdx.x, t.total);
     if (u < 0) return;                                          // whole workgroup: no barrier is skipped by a part of it
-    const int tx_i = u % t.tiles_x, ty_i = (u / t.tiles_x) % t.tiles_y, n = u / (t.tiles_x * t.tiles_y);
+    // divisions by host-made factors: a division by a value the compiler does not know is some 25 instructions, and the
+    // blocks on large images are bound by instruction issue
+    const int uq = t.tiles_x == 1 ? u : (int)__umulhi((unsigned)u, t.magic_tx), n = t.tiles_y == 1 ? uq : (int)__umulhi((unsigned)uq, t.magic_ty);
+    const int tx_i = u - uq * t.tiles_x, ty_i = uq - n * t.tiles_y;
     const int ox0 = tx_i * t.pbw * t.nbw, oy0 = ty_i * t.pbh * t.nbh;
     const int ix0 = ox0 * STRIDE - a.pad, iy0 = oy0 * STRIDE - a.pad;
     unsigned char* const l_be = ir_lds;                                 // expansion bias, depthwise bias (int32 per expanded channel)
@@ -81,8 +90,20 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     const int kx32 = a.Kx >> 5;
     const IrClamp cl_e = ir_clamp(a.sh_e, a.lo_e, a.hi_e), cl_d = ir_clamp(a.sh_d, a.lo_d, a.hi_d), cl_p = ir_clamp(a.sh_p, a.lo_p, a.hi_p);
 
+    // ---- the pixels inside the image under the tile --------------------------------------------------------------------------
+    const int y0 = max(0, -iy0), y1 = min(t.ih, a.H - iy0), x0 = max(0, -ix0), x1 = min(t.iw, a.W - ix0);
+    const int sw = max(x1 - x0, 1), npix = max(x1 - x0, 0) * max(y1 - y0, 0);
+    const bool frame = npix < t.ih * t.iw;                              // a part of the tile's window is outside the image
+    const int ngroups = a.Ce32 >> 5;
+
     // ---- stage the input pixels under the tile; clear the expanded-pixel buffers; biases to LDS ----------------------------
     {
+        v4i_r bias_e{}, bias_d{};                                       // up to 4 * NT channels with the first trip
+        const bool bias_in = tid * 16 < 4 * a.Ce32;
+        if (bias_in) {
+            if constexpr (EXP) bias_e = *(const v4i_r*)((const unsigned char*)a.be + tid * 16);
+            bias_d = *(const v4i_r*)((const unsigned char*)a.bd + tid * 16);
+        }
         const unsigned char* x = (const unsigned char*)a.x + (size_t)n * a.H * a.W * a.Cin;
         const int nchunks = EXP ? t.ih * t.iw * t.cpp : 0;
         v2i_r stage[IR_BATCH];
@@ -107,9 +128,16 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
                 }
             }
             if (batch == 0) {
-                // the buffers of expanded pixels (two, or one per wavefront) and, behind them, the projection sums (GP)
-                for (int o = tid * 16; o < (GP ? NW * t.e_bytes + MAXB * NCO * 4096 : 2 * t.e_bytes); o += 16 * NT) *(v4i_r*)(l_e + o) = v4i_r{0, 0, 0, 0};
-                for (int o = tid * 16; o < 4 * a.Ce32; o += 16 * NT) {
+                // the buffers of expanded pixels (two, or one per wavefront) where the tile reaches over the image's edge, the only
+                // bytes the groups do not write, and, behind them, the projection sums (GP)
+                const int bufs = (GP ? NW : ngroups > 1 ? 2 : 1) * t.e_bytes;
+                const int c0 = EXP && frame ? 0 : bufs, c1 = bufs + (GP ? MAXB * NCO * 4096 : 0);
+                for (int o = c0 + tid * 16; o < c1; o += 16 * NT) *(v4i_r*)(l_e + o) = v4i_r{0, 0, 0, 0};
+                if (bias_in) {
+                    if constexpr (EXP) *(v4i_r*)(l_be + tid * 16) = bias_e;
+                    *(v4i_r*)(l_bd + tid * 16) = bias_d;
+                }
+                for (int o = (NT + tid) * 16; o < 4 * a.Ce32; o += 16 * NT) {
                     if constexpr (EXP) *(v4i_r*)(l_be + o) = *(const v4i_r*)((const unsigned char*)a.be + o);
                     *(v4i_r*)(l_bd + o) = *(const v4i_r*)((const unsigned char*)a.bd + o);
                 }
@@ -121,26 +149,27 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     }
 
     // ---- the staged pixels inside the image, in blocks of 32 for the expansion -----------------------------------------
-    const int y0 = max(0, -iy0), y1 = min(t.ih, a.H - iy0), x0 = max(0, -ix0), x1 = min(t.iw, a.W - ix0);
-    const int sw = max(x1 - x0, 1), npix = max(x1 - x0, 0) * max(y1 - y0, 0);
     const int ncb = (npix + 31) >> 5;
+    const float inv_sw = __builtin_amdgcn_rcpf((float)sw);              // hp < 2^9: (hp + 1/2) / sw is further from a whole number than the product's error
     int xoff[IR_MAXCB], eoff[IR_MAXCB];                                 // this lane's pixel in the wavefront's j-th block: byte offsets (eoff < 0: none)
 #pragma unroll
     for (int j = 0; j < IR_MAXCB; ++j) {
         const int hp = (GP ? j : wave + 4 * j) * 32 + m, hpc = min(hp, max(npix - 1, 0));
-        const int ry = hpc / sw, rx = hpc - ry * sw;
+        const int ry = (int)(((float)hpc + 0.5f) * inv_sw), rx = hpc - ry * sw;
         xoff[j] = ((y0 + ry) * t.iw + x0 + rx) * t.xp + 16 * hi;
         eoff[j] = hp < npix ? (y0 + ry) * e_row + (x0 + rx) * 32 + 16 * hi : -1;
     }
     // ---- this lane's output pixel in the wavefront's s-th block ---------------------------------------------------------
-    const int ty = m / t.nbw, tx = m - ty * t.nbw;
+    const int ty = (m * t.magic_nbw) >> 16, tx = m - ty * t.nbw;
     const bool lane_px = ty < t.nbh;
     const int tyc = lane_px ? ty : 0, txc = lane_px ? tx : 0;
     const int nblocks = t.pbw * t.pbh;
+    // the last wavefronts take the first output blocks: the first ones have more of the expansion where it does not come out even
+    const int dwave = 3 - wave;
     int woff[MAXB];                                                     // window origin of the lane's pixel in the expanded-pixel buffer
 #pragma unroll
     for (int s = 0; s < MAXB; ++s) {
-        const int b = min(GP ? s : wave + 4 * s, nblocks - 1), by = b / t.pbw, bx = b - by * t.pbw;
+        const int b = min(GP ? s : dwave + 4 * s, nblocks - 1), by = (b * t.magic_pbw) >> 16, bx = b - by * t.pbw;
         woff[s] = (by * t.nbh + tyc) * STRIDE * e_row + (bx * t.nbw + txc) * STRIDE * 32 + 16 * hi;
     }
 
@@ -154,7 +183,12 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
 #pragma unroll
         for (int c = 0; c < NCO; ++c)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) accp[s][c][i] = 0;
+            for (int q = 0; q < 4; ++q) {                               // pixels shared out: the sums start at the bias; it is padded to whole
+                v4i_r b4 = v4i_r{0, 0, 0, 0};                           // blocks of 32, rounding constant included
+                if constexpr (!GP) b4 = *(const v4i_r*)(a.bp + 32 * c + 8 * q + 4 * hi);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) accp[s][c][4 * q + e] = b4[e];
+            }
 
     auto load_we = [&](int g) {
 #pragma unroll
@@ -190,7 +224,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
             }
     };
     // without expansion: the group's 32 channels of the tile's input pixels, 16 bytes per lane and load, zeros past the last
-    // channel; pixels outside the image are never written and stay zero.  Loads and stores are separate so that the loads of
+    // channel and outside the image.  Loads and stores are separate so that the loads of
     // the next group can be in flight over the work on this one.
     constexpr int FT = GP ? 64 : NT;                                    // lanes that fill one buffer: a wavefront's own (GP) or the workgroup's
     v4i_r fl[EXP ? 1 : IR_FILL];
@@ -208,10 +242,10 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
                     const int py = (int)__umulhi((unsigned)p, t.magic_iw), px = p - py * t.iw;
                     const int iy = iy0 + py, ix = ix0 + px;
                     const bool in_img = FT * i + ft < nch && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-                    const bool ok = in_img && g * 32 + 16 * half < a.Cin;
+                    const bool ok = in_img && (a.Cin % 32 == 0 || g * 32 + 16 * half < a.Cin);
                     fl[i] = *(const v4i_r*)(x + (ok ? (unsigned)((iy * a.W + ix) * a.Cin + g * 32 + 16 * half) : 0u));      // unconditional, in range
                     if (!ok) fl[i] = v4i_r{0, 0, 0, 0};
-                    if (in_img) fdst[i] = (unsigned)(py * e_row + px * 32 + 16 * half);
+                    if (FT * i + ft < nch) fdst[i] = (unsigned)(py * e_row + px * 32 + 16 * half);
                 }
             }
         }
@@ -226,7 +260,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     auto dw_project = [&](int g, const unsigned char* ebuf) {
 #pragma unroll
         for (int s = 0; s < MAXB; ++s)
-            if ((GP ? s : wave + 4 * s) < nblocks) {                    // wave-uniform
+            if ((GP ? s : dwave + 4 * s) < nblocks) {                   // wave-uniform
                 v16i_r acc = bias16(l_bd, g);
                 const unsigned char* win = ebuf + woff[s];
 #pragma unroll
@@ -239,7 +273,6 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
             }
     };
 
-    const int ngroups = a.Ce32 >> 5;
     int* const l_r = (int*)(l_e + NW * t.e_bytes);                       // GP: projection sums [block][output block][register][lane]
     if constexpr (GP) {
         unsigned char* const my_e = l_e + wave * t.e_bytes;
@@ -260,8 +293,8 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
         __syncthreads();                                                // all four partial sums are in
     } else {
         if constexpr (EXP) load_we(0); else fill_load(0);
-        __syncthreads();                                                // staged pixels, cleared buffers and biases are in LDS
         load_wd_wp(0);
+        __syncthreads();                                                // staged pixels, cleared buffers and biases are in LDS
         if constexpr (EXP) expand(0, l_e); else fill_store(l_e);
         for (int g = 0; g < ngroups; ++g) {
             if (g + 1 < ngroups) {
@@ -279,8 +312,8 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     // ---- epilogue: bias, residual, requantisation, stores ------------------------------------------------------------------
 #pragma unroll
     for (int s = 0; s < MAXB; ++s)
-        if ((GP ? s : wave + 4 * s) < nblocks) {                        // wave-uniform
-            const int b = GP ? s : wave + 4 * s, by = b / t.pbw, bx = b - by * t.pbw;
+        if ((GP ? s : dwave + 4 * s) < nblocks) {                       // wave-uniform
+            const int b = GP ? s : dwave + 4 * s, by = (b * t.magic_pbw) >> 16, bx = b - by * t.pbw;
             const int oy = oy0 + by * t.nbh + tyc, ox = ox0 + bx * t.nbw + txc;
             const bool px_ok = lane_px && oy < a.Ho && ox < a.Wo;
             const unsigned pix = px_ok ? (unsigned)(((n * a.Ho + oy) * a.Wo + ox) * a.Cout) : 0u;      // < 2^31: checked by the launcher
@@ -292,13 +325,11 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
                 v16i_r acc = accp[s][c];
                 if constexpr (GP) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[i] = l_r[((s * NCO + c) * 16 + i) * 64 + lane];
-                }
+                    for (int q = 0; q < 4; ++q) {
+                        const v4i_r b4 = *(const v4i_r*)(a.bp + 32 * c + 8 * q + 4 * hi);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4i_r b4 = *(const v4i_r*)(a.bp + 32 * c + 8 * q + 4 * hi);      // padded to whole blocks of 32, rounding constant included
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[4 * q + e] += b4[e];
+                        for (int e = 0; e < 4; ++e) acc[4 * q + e] = l_r[((s * NCO + c) * 16 + 4 * q + e) * 64 + lane] + b4[e];
+                    }
                 }
                 if (a.res) {
                     // the residual in the store layout, unconditional and in range, then back into the accumulator layout
@@ -374,7 +405,11 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
     t.magic_cpp = t.cpp > 1 ? (unsigned)(4294967296.0 / t.cpp) + 1u : 0u;
     t.magic_iw = (unsigned)(4294967296.0 / t.iw) + 1u;
     const long long total = (long long)a.B * t.tiles_x * t.tiles_y;
-    if (total > 0x3fffffff) return false;
+    if (total > 0x3fffffff || total * std::max(t.tiles_x, t.tiles_y) > 0xffffffffLL) return false;
+    t.magic_tx = t.tiles_x > 1 ? (unsigned)(4294967296.0 / t.tiles_x) + 1u : 0u;
+    t.magic_ty = t.tiles_y > 1 ? (unsigned)(4294967296.0 / t.tiles_y) + 1u : 0u;
+    t.magic_nbw = 65536 / t.nbw + 1;
+    t.magic_pbw = 65536 / t.pbw + 1;
     t.total = (int)total;
     // small images: the wavefronts share the channel groups (instantiated for 2 or more output blocks and 2 or more reduction steps)
     const int nw = a.Ce32 >= 320 ? 8 : 4;                               // ten or more groups: eight wavefronts
@@ -432,7 +467,7 @@ hipError_t launch_ir_block(const IrArgs& a, hipStream_t s)
     IrTile t;
     int nco, maxb;
     if (!ir_block_plan(a, t, nco, maxb)) return hipErrorInvalidValue;
-    const size_t lds = (size_t)8 * a.Ce32 + t.x_bytes + (t.gp ? t.gp * (size_t)t.e_bytes + (size_t)maxb * nco * 4096 : 2 * (size_t)t.e_bytes);
+    const size_t lds = (size_t)8 * a.Ce32 + t.x_bytes + (t.gp ? t.gp * (size_t)t.e_bytes + (size_t)maxb * nco * 4096 : (a.Ce32 > 32 ? 2 : 1) * (size_t)t.e_bytes);
     const int v = (a.stride - 1) * 4 + (nco == 1 ? 0 : nco == 2 ? 1 : nco == 3 ? 2 : 3);
     switch (v) {
     case 0: ir_launch<1, 1, 2>(a, t, lds, s); break;
