@@ -858,6 +858,33 @@ static int group_default(const ConvArgs* a, int n)
     return conv_igemm_default(a[longest], 1, blocks);
 }
 
+// Without a table for the joint launch: together, unless
+//   a member has a table of its own: that names the configuration it runs with (256 samples, tuned layers of the int8 ResNet-50 and no
+//     joint table: 2040 us one after the other, 2087 with the siblings together);
+//   the streaming kernel would run a member on 2^19 pixels or more (112x112, 1x3 + 3x1 + 3x3, 32 -> 32, 64 samples: 51 us one after
+//     the other, 69 together; 32 samples 33 / 38, 16 samples 24 / 22);
+//   the slab kernel would run a member of 128-byte pixels on 1024 or more 64 x 64 tiles (28x28, 3x3, 128 -> 128 twice, 64 samples: 24 us
+//     one after the other, 28 together; with 1x1, 128 -> 512 23 / 31; 32 samples 20 / 13 and 18 / 18; with pixels of 64 bytes the
+//     joint launch is the faster one at 1-256 samples, with pixels of 256 bytes between 4 us slower and 33 us faster).
+// Everything else was 0-60 % faster together at 1-256 samples, sums of the dispatches alone: over all segments Inception-style 1 sample 452
+// -> 283 us, 64 samples 1181 -> 1020, 256 samples 3460 -> 3243; ResNet-50 203 -> 193, 652 -> 652, 2067 -> 2064; ResNet-18 89 -> 79, 275 -> 263, 867 -> 855.
+bool ee_ctx::group_by_default(int stage, int at, int n, int b) const
+{
+    const StageDesc& st = net.stages[(size_t)stage];
+    for (int j = 0; j < n; ++j) {
+        const int op = st.first_op + order[(size_t)(st.first_op + at + j)];
+        const OpPlan& p = plans[(size_t)op];
+        if (!p.cfg.empty()) return false;
+        if ((p.src_buf == BUF_EXT_IN && zc_in) || (p.dst_buf == BUF_EXT_OUT && zc_out)) continue;      // neither kernel takes slot tables
+        ConvArgs a{};
+        fill_conv_args(op, b, a);
+        a.res = p.d.res >= 0 ? (const void*)this : nullptr;                                            // only whether there is one matters
+        if (a.M >= 1 << 19 && conv_stream_supported(a, 1)) return false;
+        if (a.Ci == 128 && (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64) >= 1024 && conv_slab_default(a, 1)) return false;
+    }
+    return true;
+}
+
 hipError_t ee_ctx::launch_group(int stage, int at, int n, int b, const void* act_in, void* act_out, int cfg)
 {
     const StageDesc& st = net.stages[(size_t)stage];
@@ -1309,9 +1336,9 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             }
         }
         if (p.group_n > 1 && cfg_force == 0 && only_op < 0 && forced_conv_tile() == 0) {
-            // this layer and its siblings behind it as one launch, unless the table says otherwise or one of them is part of something else
+            // this layer and its siblings behind it as one launch, where the table (without one: the rule) says so and none of them is part of something else
             const int gc = p.group_cfg.empty() ? 0 : p.group_cfg[std::min<size_t>(bucket_of(b), p.group_cfg.size() - 1)];
-            bool together = p.group_cfg.empty() || gc != 0;
+            bool together = p.group_cfg.empty() ? group_by_default(stage, i, p.group_n, b) : gc != 0;
             double g_ops = 0, g_bytes = 0;
             for (int j = 0; j < p.group_n && together; ++j) {
                 const int op = st.first_op + order[(size_t)(st.first_op + i + j)];

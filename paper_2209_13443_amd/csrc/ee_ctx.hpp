@@ -152,6 +152,7 @@ struct ee_ctx {
     }
     // launches layer `op` (an index into plans) on b samples with the given kernel configuration (0 = by shape)
     hipError_t launch_conv(int op, int b, const void* src, void* dst, const void* res, int cfg, const uint16_t* xs = nullptr, const uint16_t* ys = nullptr, int32_t* gap_sums = nullptr);
+    bool group_by_default(int stage, int at, int n, int b) const;    // whether those layers go together when no table for the joint launch is set
     // the layers at positions [at, at + n) of a segment's launch order in one launch (see OpPlan::group_n); cfg 0 = by shape
     hipError_t launch_group(int stage, int at, int n, int b, const void* act_in, void* act_out, int cfg);
     bool pair_wanted(const ee::OpPlan& p, int b) const

@@ -454,6 +454,69 @@ def test_sibling_layers_in_one_launch_bit_exact(torch, ee, orc, cfg):
         eng.close()
 
 
+def sibling_net(h, c, branches):
+    """One segment: a 1x1 layer, then int8 branches [(kernel, channels)] over its output that fill one tensor."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, h, h, c, 10)
+    t = net.conv(net.begin_stage(), c, 1, 1, 0)
+    cat, off = net.new_concat(h, h, sum(co for _, co in branches)), 0
+    for (kh, kw), co in branches:
+        net.conv(t, co, (kh, kw), 1, (kh // 2, kw // 2), into=(cat, off))
+        off += co
+    net.end_stage(cat)
+    blob = N._assemble(net, W.DT_I8, 77)
+    for op in blob.ops:
+        op["shift"] = 6 + int(op["kh"]) // 2 + int(op["kw"]) // 2
+    return blob
+
+
+def launches_per_layer(torch, eng, blob, x):
+    eng.profile(True)
+    eng.profile_read(len(blob.ops))
+    out = eng.stage_forward(0, x, blob.stage_out_shape(0))
+    lay = eng.profile_read(len(blob.ops))[1]
+    eng.profile(False)
+    torch.cuda.synchronize()
+    return [v["launches"] for v in lay], out
+
+
+def test_loaded_layer_tables_without_a_joint_one_are_used(torch, ee):
+    """Layers whose own table was loaded run with it, one after the other, unless a table for their joint launch says otherwise."""
+    blob = sibling_net(14, 64, [((1, 1), 32), ((3, 3), 48)])
+    eng = ee.Engine(blob, 4)
+    x = torch.randint(-128, 128, (4, 14, 14, 64), dtype=torch.int8, device="cuda")
+    n, ref = launches_per_layer(torch, eng, blob, x)
+    assert n == [1, 1, 0]                                  # no table at all: together
+    for tables, want in (({"config": {"2": [0x313] * 3}}, [1, 1, 1]), ({"group": {"1": [0x313] * 3}}, [1, 1, 0]), ({"group": {"1": [0] * 3}}, [1, 1, 1]),
+                         ({"group": {"1": []}}, [1, 1, 1]), ({"config": {"2": []}}, [1, 1, 0])):
+        eng.load_tables(tables)
+        n, out = launches_per_layer(torch, eng, blob, x)
+        assert n == want, tables
+        assert torch.equal(out, ref)
+    eng.close()
+
+
+# image, channels, branches, batch, whether they go together without tables: below and from the sizes at which the streaming kernel
+# (2^19 pixels) and the slab kernel (128-byte pixels, 1024 tiles of 64 x 64) win as launches of their own
+SIBLING_DEFAULTS = [(112, 32, [((3, 3), 32), ((1, 3), 16)], 41, True), (112, 32, [((3, 3), 32), ((1, 3), 16)], 42, False),
+                    (28, 128, [((3, 3), 128), ((1, 1), 32)], 41, True), (28, 128, [((3, 3), 128), ((1, 1), 32)], 42, False),
+                    (28, 64, [((3, 3), 128), ((1, 1), 32)], 64, True)]
+
+
+@pytest.mark.parametrize("h, c, branches, b, together", SIBLING_DEFAULTS)
+def test_sibling_layers_without_tables(torch, ee, h, c, branches, b, together):
+    blob = sibling_net(h, c, branches)
+    eng = ee.Engine(blob, b)
+    x = torch.randint(-128, 128, (b, h, h, c), dtype=torch.int8, device="cuda")
+    n, out = launches_per_layer(torch, eng, blob, x)
+    assert n == ([1, 1, 0] if together else [1, 1, 1])
+    eng.load_tables({"group": {"1": [0 if together else 0x313]}})
+    n, other = launches_per_layer(torch, eng, blob, x)
+    assert n == ([1, 1, 1] if together else [1, 1, 0])
+    assert torch.equal(out, other)
+    eng.close()
+
+
 def test_thresholds_zero_and_above_one(torch, ee, orc):
     blob = W.load_net("tiny_i8")
     eng = ee.Engine(blob, 8)
