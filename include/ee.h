@@ -215,8 +215,8 @@ const char* ee_kernel_name(int kernel_class);
  * per workgroup), 7 = the streaming kernel for the layers it covers (many pixels, a reduction of at most nine
  * 32-byte blocks, at most 64 output channels; other layers keep the default).  A whole configuration word as
  * in ee_config_set (tile | reduction step << 4 | ring stages << 8 | wavefront groups << 12) forces that one on
- * every matrix-core layer; a ring deeper than LDS allows runs with the deepest that fits.  Results never depend
- * on it.  Returns the previous setting, EE_ERR_ARG if out of range. */
+ * every matrix-core layer; a ring deeper than LDS allows runs with the deepest that fits.  int8 results never depend
+ * on it; bf16 results do within their rounding (see ee_autotune).  Returns the previous setting, EE_ERR_ARG if out of range. */
 int ee_tune_conv_tile(int cfg);
 
 /* Kernel-configuration table, one entry per (convolution layer, active-batch bucket 2^k): the GPU
@@ -224,8 +224,10 @@ int ee_tune_conv_tile(int cfg);
  * configuration buffer of the Fluid Batching engine).  ee_autotune times the candidate workgroup tiles,
  * reduction steps and LDS ring depths of every matrix-core convolution on the context's own workspace
  * (`reps` launches per candidate, synchronous, overwrites the workspace activations) and keeps the
- * fastest; until it is called the configuration is chosen from the layer shape alone.  Results never
- * depend on the table.  ee_config_table copies layer `layer`'s entries to cfg_out[0..n) (host) and
+ * fastest; until it is called the configuration is chosen from the layer shape alone.  int8 results never depend on
+ * the table.  bf16 results do within their rounding: wavefronts that share a reduction add their float sums in an order of their own (the
+ * kernel for few output pixels, wavefront groups), and every layer rounds to bf16.  Which of them is the fastest is a measurement, so
+ * two tunings may differ in the last bits of a bf16 network's activations; a stored table gives the same ones each time.  ee_config_table copies layer `layer`'s entries to cfg_out[0..n) (host) and
  * returns how many the layer has (0 = not tuned or not a matrix-core convolution); an entry is
  * tile | step << 4 | stages << 8 | groups << 12 with tile 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128 (pixels x
  * channels), step 1: 64, 2: 128, 3: 256 bytes of the reduction axis per stage, groups 0: one group of 4

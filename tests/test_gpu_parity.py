@@ -1000,6 +1000,50 @@ def test_bf16_within_tolerance(torch, ee, orc, name):
     eng.close()
 
 
+# h, w, c_in, kernel, stride, padding, c_out: reductions shorter than the 16 wavefronts and long ones, steps that do not fill the last group of
+# loads, channels that fill no block of 32 or 64, taps outside the image, strides
+FEW_PIXEL_BF16 = [(7, 7, 512, 3, 1, 1, 72), (5, 6, 24, 1, 1, 0, 40), (9, 9, 8, 5, 2, 2, 16), (14, 14, 64, 1, 2, 0, 136), (6, 4, 40, 3, 1, 0, 8)]
+
+
+@pytest.mark.parametrize("cfg", SKINNY)
+def test_few_pixel_convolution_bf16(torch, ee, orc, cfg):
+    """The few-pixel kernel forced on bf16 layers.  One layer against the oracle (double sums, rounded to bf16): the K products of a sum are exact
+    in float, every addition of any order errs by at most 2^-23 of the sum of their magnitudes, and the two roundings to bf16 by at
+    most 2^-8 of the value each.  Then whole networks (slices, residuals, rectangular kernels) under the tolerance of the tiling tests."""
+    old = ee.tune_conv_tile(cfg)
+    try:
+        for h, w, c, k, stride, pad, co in FEW_PIXEL_BF16:
+            blob = W.single_layer_net("conv", h, w, c, k, stride, pad, W.DT_BF16, seed=co, co=co)
+            mag = W.Blob(blob.tobytes())
+            mag.op_weights(mag.ops[0])[0][:] &= 0x7FFF
+            eng = ee.Engine(blob, 3)
+            x = W.input_pool(blob, 3)
+            for b in (3, 1):
+                say(f"[case] cfg {cfg:#x} {h}x{w}x{c} k{k} s{stride} p{pad} -> {co} b={b}")
+                ref = orc.stage_forward(blob, 0, x[:b])
+                total = bf16_to_f32(orc.stage_forward(mag, 0, x[:b] & 0x7FFF)).astype(np.float64) * (1 + 2.0 ** -8)
+                got = bf16_to_f32(host(eng.stage_forward(0, dev(torch, x[:b]), ref.shape[1:]), ref)).astype(np.float64)
+                r = bf16_to_f32(ref).astype(np.float64)
+                bound = 2 * 2.0 ** -8 * np.maximum(np.abs(r), np.abs(got)) + k * k * c * 2.0 ** -23 * total
+                assert np.all(np.abs(got - r) <= bound), f"{np.max(np.abs(got - r) / bound)} of the bound"
+            eng.close()
+        for name in ("zoo_bf16", "resnet50_small_bf16", "inception_small_bf16"):
+            blob = W.load_net(name)
+            eng = ee.Engine(blob, 4)
+            act = W.input_pool(blob, 3)
+            for s in range(blob.n_stages):
+                say(f"[case] cfg {cfg:#x} {name} segment {s}")
+                ref = orc.stage_forward(blob, s, act)
+                got = host(eng.stage_forward(s, dev(torch, act), ref.shape[1:]), ref)
+                r, g = bf16_to_f32(ref).astype(np.float64), bf16_to_f32(got).astype(np.float64)
+                scale = np.abs(r).reshape(r.shape[0], -1).max(axis=1).reshape(-1, 1, 1, 1) + 1e-30
+                assert np.all(np.abs(g - r) <= 2e-2 * scale), f"segment {s}: {np.max(np.abs(g - r) / scale)}"
+                act = ref
+            eng.close()
+    finally:
+        ee.tune_conv_tile(old)
+
+
 def test_bf16_serve_stream_decisions(torch, ee, orc):
     name, n, b_max = "tiny_bf16", 64, 8
     blob = W.load_net(name)
