@@ -13,8 +13,8 @@
  *     pinned host memory;
  *   - device work is enqueued on the HIP stream given to ee_create and is asynchronous unless
  *     stated otherwise: device outputs are valid once the caller has synchronised that stream;
- *   - no device or pinned memory is allocated after ee_create (ee_lanes excepted, which adds a
- *     lane's workspace): activation workspaces are sized for b_max at
+ *   - no device or pinned memory is allocated after ee_create (but for the set-up calls ee_lanes, which
+ *     adds a lane's workspace, and ee_autotune, which holds 64 MiB while it runs): activation workspaces are sized for b_max at
  *     creation, as the paper pre-allocates its buffers for the largest activation matrix at
  *     B_max (Sec. III-B, "Overhead").  ee_serve_stream and ee_schedule_sim keep their queues in
  *     ordinary host containers that may grow during a call;
@@ -53,6 +53,8 @@ int ee_blob_check(const void* model_blob, size_t blob_bytes);
 /* Parse the blob, repack the weights for the matrix cores into device memory and size the
  * workspace for b_max slots (1..1024).  `dtype` must match the blob.  `hip_stream` is a
  * hipStream_t (NULL = the default stream).  The blob may be freed after the call.
+ * Matrix-core layers hold their weights twice, as rows that tiles are staged from and as ready operands of the kernel for
+ * few output pixels (ResNet-50 in bf16: 2 x 47 MB).
  * EE_ERR_OVERFLOW if b_max samples of some layer's tensor reach 2 GiB (the kernels address a
  * batch tensor with 32-bit byte offsets). */
 int ee_create(const void* model_blob, size_t blob_bytes, int b_max, int dtype, void* hip_stream, ee_ctx** out);
@@ -247,8 +249,8 @@ int ee_config_set(ee_ctx* ctx, int layer, const int* cfg, int n);
  * one layer only, the next, a 1x1 stride-1 convolution (conv2 -> conv3 of a bottleneck block), can run as ONE
  * launch that keeps the intermediate tensor in LDS; results are those of the two separate kernels, bit for bit on
  * the int8 path.  ee_pair_count: how many layers of the network head such a pair.  ee_pair_mode: 0 = never fuse,
- * 1 = as the table says (default; until ee_autotune has run: fused below 32 samples, configuration by shape; it then
- * times every fused configuration against the two best separate kernels per batch bucket), 2 = fuse every pair.
+ * 1 = as the table says (default; nothing is fused until ee_autotune has timed every fused configuration against the
+ * two best separate kernels per batch bucket, or a table was loaded), 2 = fuse every pair.
  * ee_pair_table: like ee_config_table for the fused launch of the pair headed by `layer`; an entry is
  * rows | step << 4 | stages << 8 with rows 1: 128, 2: 64 pixels per workgroup, step 1: 64, 2: 128 bytes, or 0 = the
  * two layers run separately for that bucket.  EE_ERR_ARG for bad arguments. */
@@ -265,8 +267,9 @@ int ee_pair_set(ee_ctx* ctx, int layer, const int* cfg, int n);
  * channels a multiple of 8 up to 160, depthwise stride 1 or 2.  A 3x3 depthwise layer that no such block covers and the 1x1
  * convolution that alone reads it are fused the same way (a block without expansion, headed by the depthwise layer; its
  * channels a multiple of 16).  ee_ir_count: how many layers of the network head such a
- * block.  ee_ir_mode: 0 = never fuse, 1 = as the table says (default; nothing is fused until ee_autotune has timed the
- * fused launch against the three tuned layers per batch bucket, or a table was loaded), 2 = fuse every block.
+ * block.  ee_ir_mode: 0 = never fuse, 1 = as the table says (default; ee_autotune times the fused launch against the block's
+ * tuned layers per batch bucket; until it has run or a table was loaded every block is fused but the inverted-residual ones of more than
+ * 96 output channels), 2 = fuse every block.
  * ee_ir_table / ee_ir_set: the table of the block headed by `layer`, one entry per batch bucket, 1 = fused, 0 = separate
  * (ee_ir_set: EE_ERR_ARG when `layer` heads no block).
  * Bottleneck blocks of the same three-layer shape (int8) go through the same switches and tables with a kernel of their own: a

@@ -517,6 +517,40 @@ def test_sibling_layers_without_tables(torch, ee, h, c, branches, b, together):
     eng.close()
 
 
+def test_untuned_fusion_defaults(torch, ee):
+    """What the header promises of a context that was never tuned: fused blocks on, but for inverted-residual ones of more than 96 output
+    channels, and no fused pairs."""
+    for blob, want in ((W.bottleneck_net(8, 8, 256), [1, 0, 0]), (W.inverted_residual_net(8, 8, 16, 48, 96, 1), [1, 0, 0]),
+                       (W.inverted_residual_net(8, 8, 16, 48, 112, 1), [1, 1, 1])):
+        eng = ee.Engine(blob, 2)
+        assert eng.ir_count() > 0
+        x = dev(torch, W.input_pool(blob, 2))
+        n, _ = launches_per_layer(torch, eng, blob, x)
+        assert n == want
+        eng.close()
+    blob = W.load_net("resnet50_small_i8")
+    eng = ee.Engine(blob, 2)
+    assert eng.pair_count() > 0
+    eng.ir_mode(0)
+    eng.load_tables({"group": {str(k): [0] for k in group_heads(ee, eng, len(blob.ops))}})
+    n, _ = launches_per_layer(torch, eng, blob, dev(torch, W.input_pool(blob, 2)))
+    k = int(blob.stages[0]["n_ops"])
+    assert n[:k] == [1] * k
+    eng.close()
+
+
+def group_heads(ee, eng, n_layers):
+    """layers that head a joint launch of siblings"""
+    heads = []
+    for layer in range(n_layers):
+        try:
+            eng.load_tables({"group": {str(layer): []}})
+            heads.append(layer)
+        except ee.EEError:
+            pass
+    return heads
+
+
 def test_thresholds_zero_and_above_one(torch, ee, orc):
     blob = W.load_net("tiny_i8")
     eng = ee.Engine(blob, 8)
