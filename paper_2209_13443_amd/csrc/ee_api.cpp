@@ -1121,7 +1121,7 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                         ctx->ir_mode = fused ? 2 : (p.ir_sc ? 1 : 0);
                         p.ir_cfg.assign(buckets.size(), 0);                  // table mode: this head stays separate, the block behind it as tuned
                         if (fused || !p.ir_sc) p.ir_cfg.clear();
-                        ms[fused] = time_all({0}, reps, true, [] {}, [&](int) {    // the block alone: its head runs all its layers when fused
+                        ms[fused] = time_all({0}, reps, true, layer_before(s, k, buckets[bi]), [&](int) {    // the block alone: its head runs all its layers when fused
                             return ctx->run_stage((int)s, buckets[bi], ctx->in_buf[s], ctx->out_buf[s], false, -2 - (st.first_op + k));
                         })[0];
                         if (ms[fused] < 0.f && !rc) rc = EE_ERR_DEVICE;
