@@ -863,9 +863,9 @@ static int group_default(const ConvArgs* a, int n)
 //     joint table: 2040 us one after the other, 2087 with the siblings together);
 //   the streaming kernel would run a member on 2^19 pixels or more (112x112, 1x3 + 3x1 + 3x3, 32 -> 32, 64 samples: 51 us one after
 //     the other, 69 together; 32 samples 33 / 38, 16 samples 24 / 22);
-//   the slab kernel would run a member of 128-byte pixels on 1024 or more 64 x 64 tiles (28x28, 3x3, 128 -> 128 twice, 64 samples: 24 us
-//     one after the other, 28 together; with 1x1, 128 -> 512 23 / 31; 32 samples 20 / 13 and 18 / 18; with pixels of 64 bytes the
-//     joint launch is the faster one at 1-256 samples, with pixels of 256 bytes between 4 us slower and 33 us faster).
+//   the slab kernel would run a member of 128-byte or larger pixels on 1024 or more 64 x 64 tiles (28x28, 3x3, 128 -> 128 twice, 64 samples:
+//     24 us one after the other, 28 together; with 1x1, 128 -> 512 23 / 31; 32 samples 20 / 13 and 18 / 18; 14x14, 256 -> 256 twice, 128
+//     samples 36 / 40; with pixels of 64 bytes the joint launch is the faster one at 1-256 samples).
 // Everything else was 0-60 % faster together at 1-256 samples, sums of the dispatches alone: over all segments Inception-style 1 sample 452
 // -> 283 us, 64 samples 1181 -> 1020, 256 samples 3460 -> 3243; ResNet-50 203 -> 193, 652 -> 652, 2067 -> 2064; ResNet-18 89 -> 79, 275 -> 263, 867 -> 855.
 bool ee_ctx::group_by_default(int stage, int at, int n, int b) const
@@ -880,7 +880,7 @@ bool ee_ctx::group_by_default(int stage, int at, int n, int b) const
         fill_conv_args(op, b, a);
         a.res = p.d.res >= 0 ? (const void*)this : nullptr;                                            // only whether there is one matters
         if (a.M >= 1 << 19 && conv_stream_supported(a, 1)) return false;
-        if (a.Ci == 128 && (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64) >= 1024 && conv_slab_default(a, 1)) return false;
+        if (a.Ci >= 128 && (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64) >= 1024 && conv_slab_default(a, 1)) return false;
     }
     return true;
 }

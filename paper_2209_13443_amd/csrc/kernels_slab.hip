@@ -270,13 +270,28 @@ bool conv_slab_supported(const ConvArgs& a, int es)
     return (long long)a.M * cib < (1ll << 31);
 }
 
-// Untuned: the configuration of a layer this kernel is the faster one for, else 0.  Measured like the rule of the general kernel: with
-// two rounds of 64 x 64 tiles or more and 256 or fewer bytes per pixel (longer pixels leave one workgroup per CU) it is 5 to 30 % faster.
+// bytes of LDS of a workgroup with bm x bn tiles, steps of ks bytes of the weights and a ring of ns of them
+static size_t slab_lds_bytes(const ConvArgs& a, int es, int bm, int bn, int ks, int ns)
+{
+    const int cib = a.Ci * es, nk = (a.kh * a.kw * cib + ks - 1) / ks, srows = bm + (a.kh - 1) * a.W + (a.kw - 1), tile = bm * bn * es;
+    const size_t slab = ((((size_t)srows << (log2_exact(cib) - 4)) + 255) & ~(size_t)255) * 16 + 1024;
+    const size_t front = slab + (size_t)(ns < nk ? ns : nk) * bn * ks;
+    return (front > (size_t)tile ? front : (size_t)tile) + (a.res != nullptr && (a.Co * es) % 16 == 0 ? tile : 0) + 1024;
+}
+
+// Untuned: the configuration of a layer this kernel is the faster one for, else 0.  Measured like the rule of the general kernel, from
+// two rounds of 64 x 64 tiles.  Below four rounds 128 x 64 tiles and long steps, then int8 128 x 128, bf16 128 x 64 ones.  What decides is how
+// many workgroups a CU holds, and with it the slab, which grows with the pixel and the rows of the image under the window: while two fit
+// (three of the small bf16 tiles) it is up to 19 % faster than the best configuration of the general kernel (3x3 int8: 28x28, 128 -> 128, 64
+// samples 12.0 us against 13.4; 56x56, 64 -> 64 16.4 / 17.5; 20x20, 256 -> 256 17.7 / 20.2; bf16 56x56, 64 -> 64, 64 samples 25.6 / 30.1), beyond
+// it is up to 1.9 times as slow (int8 28x28, 256 -> 256 50.6 / 39.0, 56x56, 256 -> 64 86.0 / 46.3; bf16 28x28, 128 -> 128 27.0 / 23.2).
 int conv_slab_default(const ConvArgs& a, int es)
 {
     const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64), kbytes = (long long)a.kh * a.kw * a.Ci * es;
-    if (blocks < 512 || kbytes < 1024 || a.Ci * es > 256 || !conv_slab_supported(a, es)) return 0;
-    return blocks < 1024 && kbytes > 1280 ? 0x232 : es == 2 ? 0x222 : 0x221;
+    if (blocks < 512 || kbytes < 1024 || !conv_slab_supported(a, es)) return 0;
+    if (blocks < 1024) return slab_lds_bytes(a, es, 128, 64, 256, 2) <= 80 * 1024 ? 0x232 : 0;
+    if (es == 2) return slab_lds_bytes(a, es, 128, 64, 128, 2) <= 160 * 1024 / 3 ? 0x222 : 0;
+    return slab_lds_bytes(a, es, 128, 128, 128, 2) <= 80 * 1024 ? 0x221 : 0;
 }
 
 template <int ES, int BM, int BN, int KS>
@@ -286,19 +301,11 @@ static hipError_t launch_slab_tile(const ConvArgs& a, int ns, hipStream_t s)
     const dim3 grid(xcd_grid(gm) * (unsigned)gn);
     const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1));
     const int cib = a.Ci * ES, cib_log2 = log2_exact(cib);
-    const bool res_tile = a.res != nullptr && (a.Co * ES) % 16 == 0;
     const int nk = (a.kh * a.kw * cib + KS - 1) / KS;
     if (nk * KS > a.Kp * ES) return hipErrorInvalidValue;      // a step may not reach past the padded weight row
     ns = ns < 2 ? 2 : (ns > 4 ? 4 : ns);
-    const int srows = BM + (a.kh - 1) * a.W + (a.kw - 1);
-    const size_t slab = ((((size_t)srows << (cib_log2 - 4)) + 255) & ~(size_t)255) * 16 + 1024;
-    constexpr int TILE_O = BM * BN * ES;
-    auto lds_need = [&](int stages) {
-        const size_t front = slab + (size_t)(stages < nk ? stages : nk) * BN * KS;
-        return (front > (size_t)TILE_O ? front : (size_t)TILE_O) + (res_tile ? (size_t)TILE_O : 0) + 1024;
-    };
-    while (ns > 2 && lds_need(ns) > 160 * 1024) --ns;      // the deepest ring that fits
-    const size_t lds_bytes = lds_need(ns);
+    while (ns > 2 && slab_lds_bytes(a, ES, BM, BN, KS, ns) > 160 * 1024) --ns;      // the deepest ring that fits
+    const size_t lds_bytes = slab_lds_bytes(a, ES, BM, BN, KS, ns);
     if (lds_bytes > 160 * 1024) return hipErrorInvalidValue;
     static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_slab_kernel<ES, BM, BN, KS>),
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);

@@ -497,10 +497,12 @@ def test_loaded_layer_tables_without_a_joint_one_are_used(torch, ee):
 
 
 # image, channels, branches, batch, whether they go together without tables: below and from the sizes at which the streaming kernel
-# (2^19 pixels) and the slab kernel (128-byte pixels, 1024 tiles of 64 x 64) win as launches of their own
+# (2^19 pixels) and the slab kernel (128-byte pixels, 1024 tiles of 64 x 64, two workgroups on a CU: 256 channels up to 23 pixels wide)
+# win as launches of their own
 SIBLING_DEFAULTS = [(112, 32, [((3, 3), 32), ((1, 3), 16)], 41, True), (112, 32, [((3, 3), 32), ((1, 3), 16)], 42, False),
                     (28, 128, [((3, 3), 128), ((1, 1), 32)], 41, True), (28, 128, [((3, 3), 128), ((1, 1), 32)], 42, False),
-                    (28, 64, [((3, 3), 128), ((1, 1), 32)], 64, True)]
+                    (28, 64, [((3, 3), 128), ((1, 1), 32)], 64, True), (23, 256, [((3, 3), 128), ((1, 1), 32)], 62, False),
+                    (24, 256, [((3, 3), 128), ((1, 1), 32)], 62, True)]
 
 
 @pytest.mark.parametrize("h, c, branches, b, together", SIBLING_DEFAULTS)
