@@ -841,7 +841,9 @@ bool ee_ctx::ir_wanted(int op, int b) const
     return p.ir_bneck || p.ir_stem || plans[(size_t)op + p.ir_last()].d.c_out <= 96;
 }
 
-// The configuration of an untuned launch of several layers: as for one layer of their joint size and the longest reduction.
+// The configuration of an untuned launch of several layers: as for one layer of their joint size and the longest reduction, of equally
+// short 1x1 ones the widest (56x56, 256 -> 64 + 256 + 128, 256 samples: 330 us with the first one's, 315 with the widest one's; 64 -> 64 + 256
+// 85 / 80; longer or larger reductions keep the narrow tiles: 28x28, 3x3, 64 -> 48 + 96 38 / 49).
 static int group_default(const ConvArgs* a, int n)
 {
     long long blocks = 0, tiles = 0;
@@ -852,7 +854,7 @@ static int group_default(const ConvArgs* a, int n)
         blocks += (long long)((a[i].M + 63) / 64) * ((a[i].Co + 63) / 64);
         tiles += (long long)((a[i].M + 31) / 32) * ((a[i].Co + 31) / 32);
         few &= conv_skinny_default(a[i], 1) != 0;
-        if (kbytes(i) > kbytes(longest)) longest = i;
+        if (kbytes(i) > kbytes(longest) || (kbytes(i) == kbytes(longest) && kbytes(i) <= 640 && a[i].kh * a[i].kw == 1 && a[i].Co > a[longest].Co)) longest = i;
     }
     if (few && tiles <= 400) return tiles <= 100 ? skinny_cfg(16, 1, 2) : skinny_cfg(32, 1, 2);
     return conv_igemm_default(a[longest], 1, blocks);
@@ -866,8 +868,9 @@ static int group_default(const ConvArgs* a, int n)
 //   the slab kernel would run a member of 128-byte or larger pixels on 1024 or more 64 x 64 tiles (28x28, 3x3, 128 -> 128 twice, 64 samples:
 //     24 us one after the other, 28 together; with 1x1, 128 -> 512 23 / 31; 32 samples 20 / 13 and 18 / 18; 14x14, 256 -> 256 twice, 128
 //     samples 36 / 40; with pixels of 64 bytes the joint launch is the faster one at 1-256 samples).
-// Everything else was 0-60 % faster together at 1-256 samples, sums of the dispatches alone: over all segments Inception-style 1 sample 452
-// -> 283 us, 64 samples 1181 -> 1020, 256 samples 3460 -> 3243; ResNet-50 203 -> 193, 652 -> 652, 2067 -> 2064; ResNet-18 89 -> 79, 275 -> 263, 867 -> 855.
+// Otherwise together, measured at 1-256 samples by the sums of the dispatches alone: over all segments Inception-style 1 sample 452 -> 283 us, 64
+// samples 1181 -> 1020, 256 samples 3460 -> 3243; ResNet-50 203 -> 193, 652 -> 652, 2067 -> 2064; ResNet-18 89 -> 79, 275 -> 263, 867 -> 855.  Of 33
+// joint launches at 15 sizes 9 lost, by 1-3 us (one by 6 of 27); of synthetic blocks a narrow 1x1 layer beside a wide one at 256 samples (80 us, 72 apart).
 bool ee_ctx::group_by_default(int stage, int at, int n, int b) const
 {
     const StageDesc& st = net.stages[(size_t)stage];
