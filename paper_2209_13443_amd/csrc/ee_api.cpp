@@ -923,9 +923,10 @@ hipError_t ee_ctx::launch_pair(int op, int b, const void* src, void* dst, const 
 // size), by the time stamps of its own dispatch.  Launched back to back, a layer finds its weights and inputs in the L2 and two-stage
 // rings with many small workgroups win that then wait for the last-level cache at every step of the real pass (14x14, 1x1, 1024 -> 256
 // int8 at 64 samples: 7.4 us back to back, 12 us in the network).
-// The candidates of a layer are queued together and waited for once, and none is tried that cannot differ from a shorter ring or that the
-// layer's kind rules out: tuning took up to twice as long with a wait per candidate (MobileNetV2 at 1 sample 70 -> 39 ms, ResNet-50 int8 at
-// 64 slots 1.51 -> 1.04 s, bf16 at 256 3.3 -> 2.7 s, Inception-style at 64 2.75 -> 1.94 s; passes afterwards equal).
+// The first pass over a layer's candidates is queued and waited for once, and none is tried that cannot differ from a shorter ring or that
+// the layer's kind rules out; with a wait per candidate tuning took MobileNetV2 at 1 sample 70 ms (now 48), ResNet-50 int8 at 64 slots 1.51 s
+// (1.14), bf16 at 256 3.3 s (2.8), Inception-style at 64 2.75 s (2.1).  The finalists are timed apart: queued too (39 ms, 1.04, 2.7, 1.94 s),
+// the tables found were 1 % slower (all segments and heads, bf16 ResNet-50 at 5 samples 407 -> 412 us, MobileNetV2 at 1 177.5 -> 180).
 constexpr size_t EE_TUNE_EVICT_BYTES = 64u << 20;
 extern "C" int ee_autotune(ee_ctx* ctx, int reps)
 {
@@ -941,11 +942,11 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
     std::vector<int> buckets;
     for (int k = 0; (1 << k) < 2 * ctx->b_max; ++k) buckets.push_back(std::min(1 << k, ctx->b_max));
     // ms of the kernels of launch(cfg) for every candidate, the best of n times; negative for one that does not exist here (or when rc is
-    // set).  The candidates of a list are queued one behind the other and waited for once.  cold: launched once before, untimed, so that
-    // a kernel's first run does not count the fetch of its code.
+    // set).  cold: launched once before, untimed, so that a kernel's first run does not count the fetch of its code.  apart: every launch is
+    // waited for; otherwise all are queued one behind the other and waited for once, which is quicker but scatters the times more.
     std::vector<std::pair<size_t, size_t>> spans;                        // per timed launch: its events
     std::vector<int> owner;                                             // and its candidate
-    auto time_all = [&](const std::vector<int>& cands, int n, bool cold, auto&& before, auto&& launch) {
+    auto time_all = [&](const std::vector<int>& cands, int n, bool cold, bool apart, auto&& before, auto&& launch) {
         std::vector<float> ms(cands.size(), -1.f);
         spans.clear();
         owner.clear();
@@ -966,6 +967,7 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                     ctx->prof_used = from;
                     break;
                 }
+                if (apart && hipStreamSynchronize(ctx->stream) != hipSuccess) rc = EE_ERR_DEVICE;
                 spans.emplace_back(from, ctx->prof_used);
                 owner.push_back((int)c);
             }
@@ -981,17 +983,17 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
         ctx->prof_used = prof_was;
         return ms;
     };
-    // the fastest candidate and its time: all of them once, then the fastest few again, each keeping its best
+    // the fastest candidate and its time: all of them once, then the fastest few again and apart, each keeping its best
     auto fastest = [&](const std::vector<int>& cands, size_t few, auto&& before, auto&& launch) {
         std::vector<std::pair<float, int>> timed;
-        const std::vector<float> once = time_all(cands, 1, true, before, launch);
+        const std::vector<float> once = time_all(cands, 1, true, false, before, launch);
         for (size_t c = 0; c < cands.size(); ++c)
             if (once[c] >= 0.f) timed.emplace_back(once[c], cands[c]);
         std::sort(timed.begin(), timed.end());
         if (timed.size() > few) timed.resize(few);
         std::vector<int> again;
         for (const auto& t : timed) again.push_back(t.second);
-        const std::vector<float> more = time_all(again, reps, false, before, launch);
+        const std::vector<float> more = time_all(again, reps, false, true, before, launch);
         std::pair<float, int> best(1e30f, 0);
         for (size_t c = 0; c < again.size(); ++c) {
             const float t = more[c] < 0.f ? timed[c].first : std::min(timed[c].first, more[c]);
@@ -1124,7 +1126,7 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                         ctx->ir_mode = fused ? 2 : (p.ir_sc ? 1 : 0);
                         p.ir_cfg.assign(buckets.size(), 0);                  // table mode: this head stays separate, the block behind it as tuned
                         if (fused || !p.ir_sc) p.ir_cfg.clear();
-                        ms[fused] = time_all({0}, reps, true, layer_before(s, k, buckets[bi]), [&](int) {    // the block alone: its head runs all its layers when fused
+                        ms[fused] = time_all({0}, reps, true, true, layer_before(s, k, buckets[bi]), [&](int) {    // the block alone: its head runs all its layers when fused
                             return ctx->run_stage((int)s, buckets[bi], ctx->in_buf[s], ctx->out_buf[s], false, -2 - (st.first_op + k));
                         })[0];
                         if (ms[fused] < 0.f && !rc) rc = EE_ERR_DEVICE;
