@@ -1570,10 +1570,8 @@ extern "C" int ee_compact_refill(ee_ctx* ctx, int stage, int b_act, const uint8_
                 return launch_compact(exit_flag, act_src, act_dst, ids_src, ids_dst, b_act, refill_act, refill_ids, b_incr, sb, 0, 0, b_rem_out, b_merged_out, s);
             }) != hipSuccess)
             return EE_ERR_DEVICE;
-    } else {                                                           // nothing to move: both counts are zero
-        if (b_rem_out && hipMemsetAsync(b_rem_out, 0, sizeof(int), s) != hipSuccess) return EE_ERR_DEVICE;
-        if (b_merged_out && hipMemsetAsync(b_merged_out, 0, sizeof(int), s) != hipSuccess) return EE_ERR_DEVICE;
-    }
+    } else if (launch_compact(nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, 0, sb, 0, 0, b_rem_out, b_merged_out, s) != hipSuccess)
+        return EE_ERR_DEVICE;                                          // nothing to move: both counts are zero
     return EE_OK;
 }
 

@@ -1065,7 +1065,6 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(v4i* p, long long n16)
     if (i < n16) p[i] = z;
 }
 
-// bytes [0, round-up-to-16(bytes)) of p become zero; a kernel, not a memset node, so that it may be captured
 // ---- slot tables of a step: kernel arguments -> device memory ---------------------------------------------
 __global__ __launch_bounds__(256) void upload_slots_kernel(SlotTab in, SlotTab out, uint16_t* dst)
 {
@@ -1079,6 +1078,7 @@ hipError_t launch_upload_slots(const SlotTab& in, const SlotTab& out, uint16_t* 
     return hipGetLastError();
 }
 
+// bytes [0, round-up-to-16(bytes)) of p become zero; a kernel, not a memset node, so that it may be captured
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s)
 {
     const long long n16 = (long long)((bytes + 15) / 16);
@@ -1142,11 +1142,22 @@ __global__ __launch_bounds__(256) void compact_kernel(const uint8_t* flag, const
     }
 }
 
+// the counts of an empty batch (a kernel, not a memset node, so that it may be captured)
+__global__ void zero_counts_kernel(int* b_rem_out, int* b_merged_out)
+{
+    if (b_rem_out) *b_rem_out = 0;
+    if (b_merged_out) *b_merged_out = 0;
+}
+
 hipError_t launch_compact(const uint8_t* flag, const void* src, void* dst, const int32_t* ids_src, int32_t* ids_dst, int b_act,
                           const void* refill, const int32_t* refill_ids, int b_incr, int64_t sample_bytes, int dst_off, int ring_rows,
                           int* b_rem_out, int* b_merged_out, hipStream_t s)
 {
-    if (b_act + b_incr <= 0) return hipSuccess;
+    if (b_act + b_incr <= 0) {
+        if (!b_rem_out && !b_merged_out) return hipSuccess;
+        EE_LAUNCH(zero_counts_kernel, dim3(1), dim3(1), 0, s, b_rem_out, b_merged_out);
+        return hipGetLastError();
+    }
     const dim3 grid(xcd_grid((sample_bytes + 16383) / 16384 * (b_act + b_incr)));
     EE_LAUNCH(compact_kernel, grid, dim3(256), 0, s, flag, (const unsigned char*)src, (unsigned char*)dst, ids_src, ids_dst, b_act,
               (const unsigned char*)refill, refill_ids, b_incr, (long long)sample_bytes, dst_off, ring_rows, b_rem_out, b_merged_out);

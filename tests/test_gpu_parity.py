@@ -604,6 +604,52 @@ def test_compaction_and_refill(torch, ee, orc):
     eng.close()
 
 
+def test_steps_captured_in_a_graph(torch, ee):
+    """Segment, exit head without allocations, compaction and an empty compaction captured once: every replay, with eager work and other inputs
+    in between, gives what eager calls give."""
+    blob = W.load_net("zoo_i8")
+    lib, b, s = ee.raw(), 6, torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        eng = ee.Engine(blob, b)
+        shape, thr = blob.stage_out_shape(0), float(blob.exits[0]["thr"])
+        x = dev(torch, W.input_pool(blob, b))
+        act, dst = (torch.zeros((b,) + shape, dtype=torch.int8, device="cuda") for _ in range(2))
+        label, conf = torch.zeros(b, dtype=torch.int32, device="cuda"), torch.zeros(b, dtype=torch.float32, device="cuda")
+        score, flag = torch.zeros(b, dtype=torch.int64, device="cuda"), torch.zeros(b, dtype=torch.uint8, device="cuda")
+        ids, ids_dst = torch.arange(b, dtype=torch.int32, device="cuda"), torch.zeros(b, dtype=torch.int32, device="cuda")
+        counts = torch.zeros(4, dtype=torch.int32, device="cuda")
+
+        def steps():
+            assert lib.ee_stage_forward(eng._h, 0, b, x.data_ptr(), act.data_ptr()) == ee.EE_OK
+            eng.exit_head_static(0, act, thr, label, conf, score, flag)
+            p = counts.data_ptr()
+            assert lib.ee_compact_refill(eng._h, 0, b, flag.data_ptr(), act.data_ptr(), dst.data_ptr(), ids.data_ptr(), ids_dst.data_ptr(),
+                                         None, None, 0, p, p + 4) == ee.EE_OK
+            assert lib.ee_compact_refill(eng._h, 0, 0, None, None, None, None, None, None, None, 0, p + 8, p + 12) == ee.EE_OK
+
+        outs = (act, dst, label, conf, score, flag, ids_dst, counts)
+
+        def cleared(run):
+            for t in outs:
+                t.fill_(3)
+            run()
+            s.synchronize()
+            return [t.clone() for t in outs]
+
+        cleared(steps)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            steps()
+        for k in range(4):
+            x.copy_(dev(torch, W.input_pool(blob, b, first=b * k)))
+            want = cleared(steps)
+            got = cleared(graph.replay)
+            assert want[-1].tolist()[2:] == [0, 0] and 0 <= want[-1][0] <= b
+            assert all(torch.equal(g, w) for g, w in zip(got, want)), f"replay {k}"
+        del graph
+        eng.close()
+
+
 def synthetic_lut(n_stages, b_max):
     return (np.arange(1, n_stages + 1)[:, None] * 1000 + np.arange(b_max)[None, :] * 37).astype(np.int64)
 
