@@ -32,10 +32,11 @@
 // expands, filters and projects every pixel of the tile for the groups g = wavefront, wavefront + 4 (or 8), ... through a buffer
 // of its own, with no barrier inside the loop; the partial projection sums are added in LDS (integer adds,
 // exact in any order) and the epilogue is shared out by (pixel block, output block).
-// What bounds it: the blocks on large images issue vector instructions for 55-60 % of their time and matrix instructions for
-// 15-30 % (112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels, 64 images: 31.5 us, from 35.7 before divisions became multiplications,
-// only tiles with a frame cleared their buffers and the output blocks went to the wavefronts with less of the expansion; 112 x 112,
-// 32 -> 16 without expansion: 27.4 -> 22.4 us); those on small images wait for their chain of loads, matrix instructions and barriers.
+// What bounds it: the blocks on large images issue vector instructions for 40-50 % of their time and matrix instructions for
+// 13-26 % (64 images, 2.3 GHz; 112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels: 8.3 M vector and 0.28 M matrix instructions in 29.7 us; 56 x 56,
+// 24 -> 144 -> 24: 5.7 M and 0.45 M in 24.1 us); those on small images wait for their chain of loads, matrix instructions and barriers.
+// With integer divisions, buffers cleared by every tile and output blocks dealt out regardless of the expansion the first took 32.6 us
+// back to back, now 28.5, and 112 x 112, 32 -> 16 without expansion 26.0, now 20.6.
 // Every accumulation is int32 and exact, rounding points are those of the three separate layers: results are equal
 // bit for bit.
 #include "ee_internal.hpp"

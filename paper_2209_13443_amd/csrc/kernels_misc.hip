@@ -1092,9 +1092,9 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s)
 // HBM: every sample that stays is read and written once.  A workgroup's four 16-byte loads per lane are on their way before it
 // works out where its sample goes (each wavefront by itself: number of survivors in front of the slot by ballots over the
 // flags, no barrier), and the stores are non-temporal: a line that is only written does not displace the sources in L2.
-// 144 of 200 samples of 1.6 MB: 99 us (4 loads behind two barriers, plain stores) -> 71 us = 7.0 TB/s; eight loads
-// per lane 74 us, non-temporal loads too 80 us.  ring_rows > 0: dst is a ring of that many sample rows and the destination row
-// wraps around its end.
+// 144 of 200 samples of 1.6 MB: 99 us (4 loads behind two barriers, plain stores) -> 69 us = 6.7 TB/s, with 56 newcomers behind them 108 us =
+// 6.0 TB/s (torch's copy of 1 GiB: 5.2 TB/s); eight loads per lane and non-temporal loads were 4 and 13 % slower.  ring_rows > 0: dst is
+// a ring of that many sample rows and the destination row wraps around its end.
 __global__ __launch_bounds__(256) void compact_kernel(const uint8_t* flag, const unsigned char* src, unsigned char* dst,
                                                       const int32_t* ids_src, int32_t* ids_dst, int b_act, const unsigned char* refill,
                                                       const int32_t* refill_ids, int b_incr, long long sample_bytes, int dst_off, int ring_rows,
