@@ -27,7 +27,10 @@ PEAK = {"i8": 5000.0, "bf16": 2500.0}          # dense MFMA peak of MI355X, TOP/
 HBM_PEAK = 8000.0                               # GB/s
 
 
-CONV_SOURCES = ("kernels_igemm.hip", "kernels_slab.hip", "kernels_pair.hip", "kernels_bneck.hip", "kernels_ir.hip", "igemm_device.hpp", "igemm_epilogue.hpp", "ir_device.hpp")
+# every source file of the kernels booked as matrix-core convolutions (class conv_mfma)
+CONV_SOURCES = ("kernels_igemm.hip", "kernels_skinny.hip", "kernels_group.hip", "kernels_slab.hip", "kernels_pair.hip", "kernels_bneck.hip", "kernels_ir.hip",
+                "igemm_kernel.hpp", "skinny_kernel.hpp", "igemm_device.hpp", "igemm_epilogue.hpp", "ir_device.hpp")
+CONV_KERNELS = "conv_igemm_kernel, conv_skinny_kernel, conv_group_kernel, conv_group_skinny_kernel, conv_slab_kernel, conv_pair_kernel, bneck_block_i8_kernel, ir_block_i8_kernel"
 
 
 def conv_sources_digest():
@@ -340,7 +343,7 @@ def run_stream(args, name, steps, warmup, full=True):
     roofline = None
     if conv["launches"]:
         achieved = conv["ops"] / (conv["ms"] * 1e-3) / 1e12
-        roofline = dict(bound="mfma", kernel="conv_igemm_kernel, conv_slab_kernel, conv_pair_kernel, bneck_block_i8_kernel, ir_block_i8_kernel", achieved=round(achieved, 2), peak=PEAK[dtype],
+        roofline = dict(bound="mfma", kernel=CONV_KERNELS, achieved=round(achieved, 2), peak=PEAK[dtype],
                         unit="TOP/s" if dtype == "i8" else "TFLOP/s", frac=round(achieved / PEAK[dtype], 4), traffic=None,
                         launches=conv["launches"], avg_launch_us=round(conv["ms"] * 1e3 / conv["launches"], 2),
                         algorithmic_gops_per_launch=round(conv["ops"] / conv["launches"] / 1e9, 3),

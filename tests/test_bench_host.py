@@ -1,6 +1,7 @@
 """Host-only checks of bench.py: the one-GPU rule, the traffic record and the workload table."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -26,6 +27,24 @@ def test_traffic_record_is_used_only_for_the_sources_it_was_measured_on(monkeypa
     assert bench.measured_traffic("no_such_workload") is None
     monkeypatch.setattr(bench, "conv_sources_digest", lambda: "0" * 64)          # the kernel has changed: no figure
     assert bench.measured_traffic("resnet50_i8_stream") is None
+
+
+# sources without a kernel of that class: other layers' kernels, declarations, the table of powers
+OTHER_SOURCES = {"kernels_conv.hip", "kernels_stem.hip", "kernels_stream.hip", "kernels_thin.hip", "kernels_misc.hip", "ee_internal.hpp", "ee_ctx.hpp"}
+
+
+def test_every_convolution_source_counts_for_the_traffic_record():
+    csrc = os.path.join(ROOT, "paper_2209_13443_amd", "csrc")
+    listed = set(bench.CONV_SOURCES)
+    assert len(listed) == len(bench.CONV_SOURCES) and not listed & OTHER_SOURCES
+    assert listed | OTHER_SOURCES == {f for f in os.listdir(csrc) if f.endswith((".hip", ".hpp"))}
+    kernels = set()
+    for name in listed:
+        with open(os.path.join(csrc, name)) as f:
+            text = f.read()
+        assert set(re.findall(r'#include "(.*)"', text)) <= listed | {"ee_internal.hpp"}, name
+        kernels |= set(re.findall(r"__global__[^;{]*?(\w+_kernel)\(", text))
+    assert kernels == set(bench.CONV_KERNELS.split(", "))
 
 
 def test_every_workload_names_a_calibrated_network():
