@@ -139,7 +139,8 @@ typedef struct {
 } ee_serve_opts;
 
 /* 1 when the context can serve with zero_copy = 1: b_max <= 256 and every tensor that crosses a segment boundary is read
- * and written by the general matrix-core convolution kernel only; else 0. */
+ * and written only by layers that kernels with slot tables can run (the general matrix-core convolution and the one for few
+ * output pixels; a fused bottleneck block may write it); else 0. */
 int ee_zero_copy_supported(const ee_ctx* ctx);
 
 /* refill = 2, stage pools, is an extension that is not in the paper.  Algorithm 1 keeps one active batch
@@ -221,21 +222,25 @@ const char* ee_kernel_name(int kernel_class);
  * on it; bf16 results do within their rounding (see ee_autotune).  Returns the previous setting, EE_ERR_ARG if out of range. */
 int ee_tune_conv_tile(int cfg);
 
-/* Kernel-configuration table, one entry per (convolution layer, active-batch bucket 2^k): the GPU
- * counterpart of the run-time look-up the paper keeps per layer and batch size (Sec. III-A, the
- * configuration buffer of the Fluid Batching engine).  ee_autotune times the candidate workgroup tiles,
- * reduction steps and LDS ring depths of every matrix-core convolution on the context's own workspace
- * (`reps` launches per candidate, synchronous, overwrites the workspace activations) and keeps the
- * fastest; until it is called the configuration is chosen from the layer shape alone.  int8 results never depend on
- * the table.  bf16 results do within their rounding: wavefronts that share a reduction add their float sums in an order of their own (the
- * kernel for few output pixels, wavefront groups), and every layer rounds to bf16.  Which of them is the fastest is a measurement, so
- * two tunings may differ in the last bits of a bf16 network's activations; a stored table gives the same ones each time.  ee_config_table copies layer `layer`'s entries to cfg_out[0..n) (host) and
- * returns how many the layer has (0 = not tuned or not a matrix-core convolution); an entry is
- * tile | step << 4 | stages << 8 | groups << 12 with tile 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128 (pixels x
- * channels), step 1: 64, 2: 128, 3: 256 bytes of the reduction axis per stage, groups 0: one group of 4
- * wavefronts, 2 or 4: that many groups sharing the reduction of a tile; the entry 7 alone selects the streaming
- * kernel; groups 2 or 4 with step 1 or 2 name the kernel for few output pixels (32- resp. 16-pixel tiles, step = blocks of
- * channels, tile = log2 of the wavefronts + 1).  EE_ERR_ARG for bad arguments. */
+/* Kernel-configuration table, one entry per (convolution layer, active-batch bucket 2^k): the GPU counterpart of
+ * the run-time look-up the paper keeps per layer and batch size (Sec. III-A, the configuration buffer of the Fluid
+ * Batching engine).  ee_autotune times the candidate kernels, workgroup tiles, reduction steps and LDS ring depths
+ * of every matrix-core convolution on the context's own workspace, then the fused pairs, joint launches and fused
+ * blocks below against the layers by themselves (every candidate once, the fastest few `reps` times more;
+ * synchronous, overwrites the workspace activations) and keeps the fastest; until it is called the configuration
+ * is chosen from the layer shape alone.  int8 results never depend on the table.  bf16 results do within their
+ * rounding: wavefronts that share a reduction add their float sums in an order of their own (the kernel for few
+ * output pixels, wavefront groups), and every layer rounds to bf16.  Which of them is the fastest is a
+ * measurement, so two tunings may differ in the last bits of a bf16 network's activations; a stored table gives
+ * the same ones each time.  ee_config_table copies layer `layer`'s entries to cfg_out[0..n) (host) and returns how
+ * many the layer has (0 = not tuned or not a matrix-core convolution); an entry is tile | step << 4 | stages << 8
+ * | groups << 12 with tile 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128 (pixels x channels), step 1: 64, 2: 128, 3:
+ * 256 bytes of the reduction axis per stage, groups 0: one group of 4 wavefronts, 2 or 4: that many groups sharing
+ * the reduction of a tile; bit 16 selects the kernel that keeps a tile's input rows in LDS (stride-1 layers whose
+ * output is as large as their input; tile 1: 128x128, 2: 128x64, 3: 256x64, 4: 256x128, step 2 or 3 of the
+ * weights); the entry 7 alone selects the streaming kernel; groups 2 or 4 with step 1 or 2 name the kernel for few
+ * output pixels (32- resp. 16-pixel tiles, step = blocks of channels, tile = log2 of the wavefronts + 1).
+ * EE_ERR_ARG for bad arguments. */
 int ee_autotune(ee_ctx* ctx, int reps);
 int ee_config_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);
 /* Loads a stored table for layer `layer` (n <= 16 entries as ee_config_table returns them; n = 0 clears it):
