@@ -588,25 +588,24 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
             for (int k = 0; k + 3 < st.n_ops; ++k)
                 if ((rc = pack_bneck_shortcut(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
     // the folded first convolution with the max-pool that alone reads it (nothing to pack: the kernel takes the layer's own weights)
-    if (es == 1)
-        for (const StageDesc& st : ctx->net.stages)
-            for (int k = 0; k + 1 < st.n_ops; ++k) {
-                OpPlan& p = ctx->plans[st.first_op + k];
-                const OpDesc& c = p.d;
-                const OpDesc& q = ctx->plans[st.first_op + k + 1].d;
-                if (p.ir || p.impl != IMPL_MFMA_S2D || c.res >= 0 || c.dst == st.out_tensor || q.kind != OP_MAXPOOL || q.src != c.dst) continue;
-                if (q.kh != 3 || q.kw != 3 || q.stride != 2 || q.pad != 1 || q.pad_w != 1 || q.c_tot != q.c_out || q.c_off != 0 || q.dst == st.out_tensor) continue;
-                int readers = 0;
-                for (int j = 0; j < st.n_ops; ++j) {
-                    const OpDesc& o = ctx->plans[st.first_op + j].d;
-                    readers += (o.src == c.dst) + (o.res == c.dst);
-                }
-                ConvArgs probe{};
-                ctx->fill_conv_args(st.first_op + k, b_max, probe);
-                if (readers != 1 || !stem_pool_supported(probe, q.h_out, q.w_out)) continue;
-                p.ir = true;
-                p.ir_stem = true;
+    for (const StageDesc& st : ctx->net.stages)
+        for (int k = 0; k + 1 < st.n_ops; ++k) {
+            OpPlan& p = ctx->plans[st.first_op + k];
+            const OpDesc& c = p.d;
+            const OpDesc& q = ctx->plans[st.first_op + k + 1].d;
+            if (p.ir || p.impl != IMPL_MFMA_S2D || c.res >= 0 || c.dst == st.out_tensor || q.kind != OP_MAXPOOL || q.src != c.dst) continue;
+            if (q.kh != 3 || q.kw != 3 || q.stride != 2 || q.pad != 1 || q.pad_w != 1 || q.c_tot != q.c_out || q.c_off != 0 || q.dst == st.out_tensor) continue;
+            int readers = 0;
+            for (int j = 0; j < st.n_ops; ++j) {
+                const OpDesc& o = ctx->plans[st.first_op + j].d;
+                readers += (o.src == c.dst) + (o.res == c.dst);
             }
+            ConvArgs probe{};
+            ctx->fill_conv_args(st.first_op + k, b_max, probe);
+            if (readers != 1 || !stem_pool_supported(probe, es, q.h_out, q.w_out)) continue;
+            p.ir = true;
+            p.ir_stem = true;
+        }
     plan_order(ctx);
     plan_buffers(ctx);
     ctx->pool.resize(ctx->pool_sample_bytes.size(), nullptr);
@@ -1324,9 +1323,9 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 fill_conv_args(st.first_op + k, b, ca);
                 ca.x = pad_bufs[p.pad_buf]; ca.mode = 0;
                 void* yq = resolve(this, q2.dst_buf, act_in, act_out);
-                const double mid = 2.0 * b * (double)d.h_out * d.w_out * d.c_out;      // the tensor that stays on chip
+                const double mid = 2.0 * es * b * (double)d.h_out * d.w_out * d.c_out; // the tensor that stays on chip
                 e = timed(EE_K_CONV_STREAM, ops + q2.ops_per_sample * b, bytes + q2.bytes_per_sample * b + q2.weight_bytes - mid,
-                          [&] { return launch_stem_pool(ca, yq, q2.d.h_out, q2.d.w_out, stream); }, st.first_op + k);
+                          [&] { return launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
                 ++i;                                                             // the pool is done
                 continue;
@@ -1675,7 +1674,7 @@ extern "C" int ee_time_layer(ee_ctx* ctx, int layer, int b, int cfg, int reps, d
             const OpPlan& q = ctx->plans[layer + j];
             const OpDesc& prev = ctx->plans[layer + j - 1].d;
             if (ops_out) *ops_out += q.ops_per_sample * b;
-            if (bytes_out) *bytes_out += q.bytes_per_sample * b + q.weight_bytes - 2.0 * b * (double)prev.h_out * prev.w_out * prev.c_out;
+            if (bytes_out) *bytes_out += q.bytes_per_sample * b + q.weight_bytes - 2.0 * ctx->net.elem_bytes() * b * (double)prev.h_out * prev.w_out * prev.c_out;
         }
     hipEventDestroy(e0);
     hipEventDestroy(e1);

@@ -210,8 +210,8 @@ hipError_t launch_ir_block(const IrArgs& a, hipStream_t s);
 // layers' operands and biases, Kx = Cin, Ce32 = the middle channels
 // first convolution (folded stride-2 layer, 4 x 4 taps over 16-channel super-pixels, 64 output channels: a as for the streaming
 // kernel, a.y unused) and the 3x3 / 2 max-pool with padding 1 behind it in one launch; yq: the pooled output [B][Hq][Wq][64]
-bool stem_pool_supported(const ConvArgs& a, int Hq, int Wq);
-hipError_t launch_stem_pool(const ConvArgs& a, void* yq, int Hq, int Wq, hipStream_t s);
+bool stem_pool_supported(const ConvArgs& a, int es, int Hq, int Wq);
+hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq, hipStream_t s);
 bool bneck_block_supported(const IrArgs& a);
 bool bneck_block_pools(const IrArgs& a);     // with a.gap_sums the launch also pools: only where its rows of sums fit into LDS
 hipError_t launch_bneck_block(const IrArgs& a, hipStream_t s);

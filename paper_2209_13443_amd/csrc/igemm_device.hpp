@@ -79,6 +79,9 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{a, b}), v2bf));
 }
 
+// lo <= hi; a NaN becomes lo, as with fminf(fmaxf(v, lo), hi)
+__device__ __forceinline__ float clamp_f32(float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); }
+
 __device__ __forceinline__ int clamp_i32(int v, int lo, int hi)       // lo <= hi
 {
     int r;

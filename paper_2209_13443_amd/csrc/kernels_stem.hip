@@ -1,4 +1,4 @@
-// First convolution and max-pool of a ResNet-style network (int8) in one launch, for gfx950: the folded stride-2 first layer
+// First convolution and max-pool of a ResNet-style network in one launch (int8, and a bf16 form further down), for gfx950: the folded stride-2 first layer
 // (4 x 4 taps over 16-channel super-pixels, 64 output channels; what conv_stream_i8_kernel runs alone) and the 3 x 3 / 2 max-pool
 // with padding 1 behind it.  Layer by layer the convolution's output, the largest tensor of the network, is written once and read
 // once for a quarter of its size to come out of the pool; here it only exists in LDS, a tile at a time.
@@ -12,6 +12,7 @@
 // LDS reads, byte-wise maximum on 16-bit halves, one 16-byte store.  A seventh of the convolution is computed twice (the windows'
 // overlap between tiles and the last strip's padding); results are those of the two layers bit for bit.
 #include "ee_internal.hpp"
+#include "igemm_device.hpp"
 #include "ir_device.hpp"
 
 namespace ee {
@@ -178,27 +179,168 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
     }
 }
 
-// the convolution as the launcher of the streaming kernel sees it (folded input), the pool behind it by its output size
-bool stem_pool_supported(const ConvArgs& a, int Hq, int Wq)
+// The bf16 form.  A super-pixel has 32 bytes and the reduction sixteen steps of one tap each, so a strip's operands are twice the bytes and
+// its matrix instructions twice as many; read from global memory per strip they would be eight times the folded image (1.9 GB for 256
+// samples through the 64 bytes per clock of the CU's vector memory path: 50 us by themselves).  Here the folded pixels under a tile are copied
+// to LDS once, asynchronously and a tile ahead, and a strip's operands are LDS reads (32 neighbouring pixels are 1 KiB in a row: no bank
+// conflicts).  Tiles of 7 x 8 pooled pixels: the 15 x 17 convolution outputs under them are 255, eight strips of 32 with one lane to
+// spare, two per wavefront, both blocks of 32 output channels per operand; 62 KB of LDS let two workgroups share a CU, so that one
+// pools while the other multiplies.  Weights stay in registers (128).
+// Sums, bias, clamp and rounding are those of the staged kernel, step by step; a clamp at or above zero (ReLU) is what the rule asks for:
+// bf16 values >= 0 order like 16-bit integers, the pool is packed integer maxima, and 0 stands where the convolution has no output.
+// 256 samples of 224 x 224, with the folded copy in front: 374 us as two launches behind it (252 and 121 us by themselves; the tensor
+// between them, 411 MB, written once and read two and a quarter times), 173 fused.  What bounds it: matrix instructions 49 us, vector issue (epilogue and pool)
+// about as much, LDS operand reads 25 us, 211 MB of HBM traffic 38 us, shared out over two workgroups per CU.
+constexpr int SB_TW = 7, SB_TH = 8;
+constexpr int SB_RW = 2 * SB_TW + 1, SB_RH = 2 * SB_TH + 1, SB_RPIX = SB_RW * SB_RH;      // 15 x 17 convolution outputs
+constexpr int SB_SW = SB_RW + 3, SB_SH = SB_RH + 3, SB_CHUNKS = 2 * SB_SW * SB_SH;        // 18 x 20 folded pixels of two 16-byte chunks
+constexpr int SB_PASSES = (SB_CHUNKS + 255) / 256, SB_STAGE = SB_PASSES * 4096;           // whole copy passes of the workgroup
+constexpr int SB_PITCH = 128 + 16;                                                        // bytes per convolution output in LDS
+constexpr int SB_LDS = 2 * SB_STAGE + SB_RPIX * SB_PITCH + 256;
+constexpr int SB_ITEMS = 8 * SB_TW * SB_TH;                                               // (pooled pixel, 8 channels)
+static_assert((SB_RPIX + 31) / 32 == 8, "two strips per wavefront");
+static_assert(2 * SB_LDS <= 160 * 1024, "two workgroups per CU");
+
+__global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void* yq, StemTile t)
 {
+    constexpr int NK = 16;                                              // taps = reduction steps of 16 channels
+    extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned lds0 = lds_addr(stem_lds);
+    unsigned char* const l_conv = stem_lds + 2 * SB_STAGE;
+    float* const l_bias = (float*)(l_conv + SB_RPIX * SB_PITCH);
+    v4i wreg[2][NK];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < NK; ++k) wreg[j][k] = *(const v4i*)((const unsigned char*)a.w + (size_t)(32 * j + p) * a.Kp * 2 + k * 32 + 16 * hi);
+    if (tid < 64) l_bias[tid] = ((const float*)a.bias)[tid];
+    // this lane's chunks of a staged tile: row | column << 8 of the folded pixel, half of it
+    int spos[SB_PASSES];
+#pragma unroll
+    for (int i = 0; i < SB_PASSES; ++i) {
+        const int q = min(256 * i + tid, SB_CHUNKS - 1), row = q / (2 * SB_SW), c = q - row * 2 * SB_SW;
+        spos[i] = row | (c >> 1) << 8 | (c & 1) << 16;
+    }
+    // pooling: this lane's items (pooled pixel, channels): tid and tid + 256
+    int pty[2], ptx[2], poff[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int pp = min(tid + 256 * i, SB_ITEMS - 1) >> 3;
+        pty[i] = pp / SB_TW; ptx[i] = pp - pty[i] * SB_TW;
+        poff[i] = (2 * pty[i] * SB_RW + 2 * ptx[i]) * SB_PITCH + 16 * (tid & 7);
+    }
+    const int tpi = t.tiles_x * t.tiles_y;
+    struct Tile { int n, py0, px0; };
+    auto tile_at = [&](int u) {
+        const int n = u / tpi, r0 = u - n * tpi, tyi = r0 / t.tiles_x;
+        return Tile{n, SB_TH * tyi, SB_TW * (r0 - tyi * t.tiles_x)};
+    };
+    auto stage = [&](const Tile& tl, int buf) {                         // asynchronous; clamped pixels are only ever read by outputs that do not exist
+        const unsigned char* xn = (const unsigned char*)a.x + (size_t)tl.n * a.H * a.W * 32;
+#pragma unroll
+        for (int i = 0; i < SB_PASSES; ++i) {
+            const int cy = min(max(2 * tl.py0 - 1 + (spos[i] & 255), 0), a.H - 1), cx = min(max(2 * tl.px0 - 1 + ((spos[i] >> 8) & 255), 0), a.W - 1);
+            dma16(lds0 + buf * SB_STAGE + i * 4096 + wave * 1024, xn + (unsigned)((cy * a.W + cx) * 32 + 16 * (spos[i] >> 16)));
+        }
+    };
+    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(wreg[j][k]));
+    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
+    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
+    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3), buf = 0;
+    Tile tl = tile_at(u);
+    if (u < u_end) stage(tl, 0);
+    for (; u < u_end; u += u_step, buf ^= 1) {
+        wait_all_then_barrier<0>();                                     // the tile is staged, the pooling of the one before has read its convolution outputs
+        const Tile tn = tile_at(u + u_step);
+        if (u + u_step < u_end) stage(tn, buf ^ 1);
+        const unsigned char* xl = stem_lds + buf * SB_STAGE + 16 * hi;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int r = 32 * (wave + 4 * s) + p, rc = min(r, SB_RPIX - 1), ry = rc / SB_RW, rx = rc - ry * SB_RW;
+            const bool exists = (unsigned)(2 * tl.py0 - 1 + ry) < (unsigned)a.Ho && (unsigned)(2 * tl.px0 - 1 + rx) < (unsigned)a.Wo;
+            const unsigned char* px = xl + (ry * SB_SW + rx) * 32;
+            v16f acc[2];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
+            // the operands in batches of four through two sets of registers, a batch ahead of its matrix instructions
+            v4i xs[2][4];
+            auto read = [&](int k0, v4i* x) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = *(const v4i*)(px + ((k0 >> 2) * SB_SW + k) * 32);
+            };
+            read(0, xs[0]);
+#pragma unroll
+            for (int k0 = 0; k0 < NK; k0 += 4) {
+                if (k0 + 4 < NK) read(k0 + 4, xs[(k0 >> 2 & 1) ^ 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, wreg[j][k0 + k]), __builtin_bit_cast(v8bf, xs[k0 >> 2 & 1][k]), acc[j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            unsigned char* cell = l_conv + rc * SB_PITCH + 8 * hi;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const v4i b4 = *(const v4i*)(l_bias + 32 * j + 8 * g + 4 * hi);
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = clamp_f32(acc[j][4 * g + e] + __int_as_float(b4[e]), a.f_lo, a.f_hi);
+                    uint2 o = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+                    if (!exists) o = uint2{0u, 0u};
+                    if (r < SB_RPIX) *(uint2*)(cell + 64 * j + 16 * g) = o;
+                }
+        }
+        lds_barrier();                                                  // the tile's convolution outputs are in LDS
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (tid + 256 * i >= SB_ITEMS) continue;
+            typedef short v8s __attribute__((ext_vector_type(8)));
+            const unsigned char* win = l_conv + poff[i];
+            v8s mx = *(const v8s*)win;
+#pragma unroll
+            for (int k = 1; k < 9; ++k) mx = __builtin_elementwise_max(mx, *(const v8s*)(win + ((k / 3) * SB_RW + (k % 3)) * SB_PITCH));
+            const int py = tl.py0 + pty[i], px = tl.px0 + ptx[i];
+            if (py < t.Hq && px < t.Wq)
+                *(v8s*)((unsigned char*)yq + ((size_t)(tl.n * t.Hq + py) * t.Wq + px) * 128 + 16 * (tid & 7)) = mx;
+        }
+        tl = tn;
+    }
+}
+
+// the convolution as the launcher of the streaming kernel sees it (folded input), the pool behind it by its output size
+bool stem_pool_supported(const ConvArgs& a, int es, int Hq, int Wq)
+{
+    if (es == 2 && !(a.f_lo >= 0.f)) return false;
     if (a.mode != 0 || a.res != nullptr || a.M <= 0 || a.Ci != 16 || a.kh != 4 || a.kw != 4 || a.stride != 1 || a.pad != 0 || a.pad_w != 0) return false;
     if (a.Co != 64 || a.ldc != 64 || a.c_off != 0 || a.Kp < 256 || a.H < a.Ho + 3 || a.W < a.Wo + 3) return false;
     if (Hq != (a.Ho + 2 - 3) / 2 + 1 || Wq != (a.Wo + 2 - 3) / 2 + 1 || Hq < 1 || Wq < 1) return false;
-    return (double)(a.M / (a.Ho * a.Wo)) * a.H * a.W * 16 < 2147483648.0;
+    return (double)(a.M / (a.Ho * a.Wo)) * a.H * a.W * 16 * es < 2147483648.0;
 }
 
-hipError_t launch_stem_pool(const ConvArgs& a, void* yq, int Hq, int Wq, hipStream_t s)
+hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq, hipStream_t s)
 {
-    if (!stem_pool_supported(a, Hq, Wq)) return hipErrorInvalidValue;
+    if (!stem_pool_supported(a, es, Hq, Wq)) return hipErrorInvalidValue;
+    const int tw = es == 1 ? ST_TW : SB_TW, th = es == 1 ? ST_TH : SB_TH;
     StemTile t;
     t.Hq = Hq; t.Wq = Wq;
-    t.tiles_x = (Wq + ST_TW - 1) / ST_TW;
-    t.tiles_y = (Hq + ST_TH - 1) / ST_TH;
+    t.tiles_x = (Wq + tw - 1) / tw;
+    t.tiles_y = (Hq + th - 1) / th;
     const long long total = (long long)(a.M / (a.Ho * a.Wo)) * t.tiles_x * t.tiles_y;
     if (total > 0x3fffffff) return hipErrorInvalidValue;
     t.total = (int)total;
     const unsigned blocks = total < 512 ? xcd_grid(total) : 512u;      // two workgroups on every CU (what matters is the CU's share, not the workgroup's); the loop takes the rest
-    EE_LAUNCH(stem_pool_i8_kernel, dim3(blocks), dim3(256), (size_t)ST_RPIX * ST_PITCH + 256, s, a, yq, t);
+    if (es == 2) EE_LAUNCH(stem_pool_bf16_kernel, dim3(blocks), dim3(256), SB_LDS, s, a, yq, t);
+    else EE_LAUNCH(stem_pool_i8_kernel, dim3(blocks), dim3(256), (size_t)ST_RPIX * ST_PITCH + 256, s, a, yq, t);
     return hipGetLastError();
 }
 

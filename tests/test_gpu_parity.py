@@ -813,6 +813,36 @@ def test_fused_first_convolution_and_pool_equal_separate_layers_and_oracle(torch
     eng.close()
 
 
+SB_CASES = [(224, 224, 5), (57, 80, 7), (32, 32, 9), (17, 16, 3), (7, 16, 2), (116, 60, 9)]      # pooled 56 x 56, 15 x 20, 8 x 8, 5 x 4, 2 x 4, 29 x 15: whole tiles of 7 x 8 and not
+
+
+@pytest.mark.parametrize("case", SB_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_fused_first_convolution_and_pool_bf16(torch, ee, orc, case):
+    """The bf16 form of the launch above, on inputs of both signs and with whole images of zeros and of large values.  The sums run in the
+    staged kernel's order and every value is rounded where the layers round it, so fused and separate layers agree exactly; the
+    oracle adds in double: every value within one bf16 rounding (2^-8 of it) plus the pool's layer behind it."""
+    h, w, n = case
+    blob = W.stem_net(h, w, seed=h + w, dtype=W.DT_BF16)
+    say(f"[case] bf16 first convolution + pool on {h}x{w}, {n} samples")
+    x = W.input_pool(blob, n)
+    x[0] = 0
+    if n > 2:
+        x[2] = np.where(x[2] >> 15, 0xC380, 0x4380)                        # -256, 256
+    eng = ee.Engine(blob, n)
+    assert eng.ir_count() == 1 and eng.ir_layers(0) == 2
+    for b in sorted({n, 1}, reverse=True):
+        ref = orc.stage_forward(blob, 0, x[:b])
+        out = []
+        for mode in (2, 0, 2):
+            eng.ir_mode(mode)
+            out.append(bf16_to_f32(host(eng.stage_forward(0, dev(torch, x[:b]), ref.shape[1:]), ref)).astype(np.float64))
+        assert np.array_equal(out[0], out[2]) and np.array_equal(out[0], out[1]), f"b={b}: {np.count_nonzero(out[0] != out[1])} of {ref.size} differ"
+        r = bf16_to_f32(ref).astype(np.float64)
+        for k in range(b):
+            assert np.abs(out[0][k] - r[k]).max() <= 2.0 ** -7 * max(np.abs(r[k]).max(), 1e-30), f"sample {k}: {np.abs(out[0][k] - r[k]).max()} of {np.abs(r[k]).max()}"
+    eng.close()
+
+
 BN_SERVE_CASES = [  # h, w, c_in, seed, frac_bits, thresholds of the first two exits, lanes
     (12, 10, 64, 3, 11, (0.782, 0.955), 1), (16, 16, 256, 5, 12, (0.8371, 0.8453), 2),
 ]

@@ -448,15 +448,15 @@ def inverted_residual_net(h, w, ci, ce, co, stride, seed=0, blocks=1):
     return blob
 
 
-def stem_net(h, w, seed=0):
-    """The first layers of a ResNet-style network alone on an h x w x 3 input, int8: 7x7 stride-2 convolution to 64 channels, 3x3 stride-2
+def stem_net(h, w, seed=0, dtype=DT_I8):
+    """The first layers of a ResNet-style network alone on an h x w x 3 input: 7x7 stride-2 convolution to 64 channels, 3x3 stride-2
     max-pool, and a 1x1 convolution to 32 channels as the segment's output: the fused first-layer kernel's shapes, for edge cases.  Data only."""
-    net = _Net(DT_I8, h, w, 3, 10)
+    net = _Net(dtype, h, w, 3, 10)
     t = net.begin_stage()
     t = net.conv(t, 64, 7, 2, 3)
     t = net.maxpool(t, 3, 2, 1)
     net.end_stage(net.conv(t, 32, 1, 1, 0))
-    blob = _assemble(net, DT_I8, BASE_SEED + 0x7c00 + seed)
+    blob = _assemble(net, dtype, BASE_SEED + 0x7c00 + seed)
     for op in blob.ops:
         if int(op["kind"]) == OP_CONV:
             fan_in = int(op["c_in"]) * int(op["kh"]) * int(op["kw"])
