@@ -170,9 +170,14 @@ int pack_op(ee_ctx* ctx, const unsigned char* blob, OpPlan& p)
     return rc;
 }
 
-std::vector<unsigned char> ir_rounded_bias(const unsigned char* blob, const OpDesc& d, int n, int n_pad)
+// a layer's bias for a fused block, padded with zeros: int8 with the rounding constant of its shift, bf16 the floats as they are
+std::vector<unsigned char> ir_rounded_bias(const unsigned char* blob, const OpDesc& d, int n, int n_pad, int es = 1)
 {
     std::vector<unsigned char> out(4 * (size_t)n_pad, 0);
+    if (es == 2) {
+        std::memcpy(out.data(), blob + d.b_off, 4 * (size_t)n);
+        return out;
+    }
     for (int o = 0; o < n; ++o) {
         int32_t v;
         std::memcpy(&v, blob + d.b_off + 4 * (size_t)o, 4);
@@ -297,13 +302,14 @@ int pack_bneck(ee_ctx* ctx, const unsigned char* blob, const StageDesc& st, int 
     IrArgs probe{};
     probe.B = ctx->b_max; probe.H = c1.h_in; probe.W = c1.w_in; probe.Cin = c1.c_in; probe.Kx = c1.c_in; probe.Ce32 = c1.c_out; probe.Cout = c3.c_out;
     probe.Ho = c2.h_out; probe.Wo = c2.w_out; probe.stride = 1; probe.pad = 1;
-    if (c2.c_in != c1.c_out || c2.c_out != c1.c_out || !bneck_block_supported(probe)) return EE_OK;
-    int rc = upload(ctx, &p.ir_we, bn_operands(blob + c1.w_off, c1.c_out, c1.c_in));
-    if (!rc) rc = upload(ctx, &p.ir_be, ir_rounded_bias(blob, c1, c1.c_out, c1.c_out));
-    if (!rc) rc = upload(ctx, &p.ir_wd, bn_operands(blob + c2.w_off, c2.c_out, 9 * c2.c_in));
-    if (!rc) rc = upload(ctx, &p.ir_bd, ir_rounded_bias(blob, c2, c2.c_out, c2.c_out));
-    if (!rc) rc = upload(ctx, &p.ir_wp, bn_operands(blob + c3.w_off, c3.c_out, c3.c_in));
-    if (!rc) rc = upload(ctx, &p.ir_bp, ir_rounded_bias(blob, c3, c3.c_out, c3.c_out));
+    const int es = ctx->net.elem_bytes();
+    if (c2.c_in != c1.c_out || c2.c_out != c1.c_out || !(es == 1 ? bneck_block_supported(probe) : c3.res >= 0 && bneck_block_bf16_supported(probe))) return EE_OK;
+    int rc = upload(ctx, &p.ir_we, bn_operands(blob + c1.w_off, c1.c_out, c1.c_in * es));
+    if (!rc) rc = upload(ctx, &p.ir_be, ir_rounded_bias(blob, c1, c1.c_out, c1.c_out, es));
+    if (!rc) rc = upload(ctx, &p.ir_wd, bn_operands(blob + c2.w_off, c2.c_out, 9 * c2.c_in * es));
+    if (!rc) rc = upload(ctx, &p.ir_bd, ir_rounded_bias(blob, c2, c2.c_out, c2.c_out, es));
+    if (!rc) rc = upload(ctx, &p.ir_wp, bn_operands(blob + c3.w_off, c3.c_out, c3.c_in * es));
+    if (!rc) rc = upload(ctx, &p.ir_bp, ir_rounded_bias(blob, c3, c3.c_out, c3.c_out, es));
     if (rc) return rc;
     p.ir_kx = c1.c_in; p.ir_ce32 = c1.c_out;
     p.ir = true;
@@ -330,8 +336,9 @@ int pack_bneck_shortcut(ee_ctx* ctx, const unsigned char* blob, const StageDesc&
         readers += (o.src == sc.dst) + (o.res == sc.dst);
     }
     if (readers != 1) return EE_OK;
-    int rc = upload(ctx, &p.ir_ws, bn_operands(blob + sc.w_off, sc.c_out, sc.c_in));
-    if (!rc) rc = upload(ctx, &p.ir_bs, ir_rounded_bias(blob, sc, sc.c_out, sc.c_out));
+    const int es = ctx->net.elem_bytes();
+    int rc = upload(ctx, &p.ir_ws, bn_operands(blob + sc.w_off, sc.c_out, sc.c_in * es));
+    if (!rc) rc = upload(ctx, &p.ir_bs, ir_rounded_bias(blob, sc, sc.c_out, sc.c_out, es));
     if (rc) return rc;
     p.ir_we = h.ir_we; p.ir_be = h.ir_be; p.ir_wd = h.ir_wd; p.ir_bd = h.ir_bd; p.ir_wp = h.ir_wp; p.ir_bp = h.ir_bp;
     p.ir_kx = h.ir_kx; p.ir_ce32 = h.ir_ce32;
@@ -576,17 +583,15 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
     // inverted-residual blocks one fused launch can take (int8): a 1x1 stride-1 convolution without residual whose output
     // is read only by the next layer, a 3x3 depthwise layer with padding 1, whose output is read only by the layer after
     // it, a 1x1 stride-1 convolution (with or without residual); none of the three writes a channel slice
-    if (es == 1)
-        for (const StageDesc& st : ctx->net.stages)
-            for (int k = 0; k + 1 < st.n_ops; ++k) {
-                if ((rc = pack_ir(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
-                // likewise bottleneck blocks: 1x1 -> 3x3 (stride 1, padding 1) -> 1x1 (+ residual), each read only by the next
-                if (!ctx->plans[st.first_op + k].ir && (rc = pack_bneck(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
-            }
-    if (es == 1)
-        for (const StageDesc& st : ctx->net.stages)
-            for (int k = 0; k + 3 < st.n_ops; ++k)
-                if ((rc = pack_bneck_shortcut(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
+    for (const StageDesc& st : ctx->net.stages)
+        for (int k = 0; k + 1 < st.n_ops; ++k) {
+            if (es == 1 && (rc = pack_ir(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
+            // likewise bottleneck blocks (int8 and bf16): 1x1 -> 3x3 (stride 1, padding 1) -> 1x1 (+ residual), each read only by the next
+            if (!ctx->plans[st.first_op + k].ir && (rc = pack_bneck(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
+        }
+    for (const StageDesc& st : ctx->net.stages)
+        for (int k = 0; k + 3 < st.n_ops; ++k)
+            if ((rc = pack_bneck_shortcut(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
     // the folded first convolution with the max-pool that alone reads it (nothing to pack: the kernel takes the layer's own weights)
     for (const StageDesc& st : ctx->net.stages)
         for (int k = 0; k + 1 < st.n_ops; ++k) {
@@ -827,9 +832,10 @@ void ee_ctx::fill_ir_args(int op, int b, IrArgs& a) const
     a.sh_e = e.shift; a.lo_e = e.lo; a.hi_e = e.hi;
     a.sh_d = dw.shift; a.lo_d = dw.lo; a.hi_d = dw.hi;
     a.sh_p = pr.shift; a.lo_p = pr.lo; a.hi_p = pr.hi; a.res_shift = pr.res_shift;
+    a.f_lo_e = e.f_lo; a.f_hi_e = e.f_hi; a.f_lo_d = dw.f_lo; a.f_hi_d = dw.f_hi; a.f_lo_p = pr.f_lo; a.f_hi_p = pr.f_hi; a.f_lo_s = p.d.f_lo; a.f_hi_s = p.d.f_hi;
 }
 
-// untuned: fused; measured at 1-256 samples it is faster at nearly every size (bottleneck blocks 1.4-2 times, inverted-residual
+// untuned: fused; measured at 1-256 samples it is faster at nearly every size (bottleneck blocks 1.4-2 times in int8 and in bf16, inverted-residual
 // blocks 1.1-1.9 times, first convolution + pool up to 1.5 times), but for inverted-residual blocks of more than 96 output channels
 bool ee_ctx::ir_wanted(int op, int b) const
 {
@@ -1338,15 +1344,15 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 ia.y = resolve(this, q2.dst_buf, act_in, act_out);
                 ia.res = q2.d.res >= 0 && !p.ir_sc ? resolve(this, q2.res_buf, act_in, act_out) : nullptr;   // the kernel computes the shortcut itself
                 ia.ys = q2.dst_buf == BUF_EXT_OUT ? zc_out : nullptr;
-                ia.gap_sums = ir_pools && bneck_block_pools(ia) ? gap_fuse_dst : nullptr;       // else the head pools the output itself
+                ia.gap_sums = ir_pools && es == 1 && bneck_block_pools(ia) ? gap_fuse_dst : nullptr;       // else the head pools the output itself
                 double f_ops = ops, f_bytes = bytes;                             // the block's layers; the tensors between them stay on chip
                 for (int j = 1; j <= ir_last; ++j) {
                     const OpPlan& q = plans[st.first_op + k + j];
                     const OpDesc& prev = plans[st.first_op + k + j - 1].d;
                     f_ops += q.ops_per_sample * b;
-                    f_bytes += q.bytes_per_sample * b + q.weight_bytes - 2.0 * b * (double)prev.h_out * prev.w_out * prev.c_out;
+                    f_bytes += q.bytes_per_sample * b + q.weight_bytes - 2.0 * es * b * (double)prev.h_out * prev.w_out * prev.c_out;
                 }
-                e = timed(EE_K_CONV_MFMA, f_ops, f_bytes, [&] { return p.ir_bneck ? launch_bneck_block(ia, stream) : launch_ir_block(ia, stream); }, st.first_op + k);
+                e = timed(EE_K_CONV_MFMA, f_ops, f_bytes, [&] { return !p.ir_bneck ? launch_ir_block(ia, stream) : es == 1 ? launch_bneck_block(ia, stream) : launch_bneck_block_bf16(ia, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
                 if (ia.gap_sums) gap_fused = true;
                 i += ir_last;                                                    // the block's other layers are done

@@ -109,6 +109,7 @@ struct IrArgs {
     int* gap_sums;       // bottleneck block only; not null: also add the per-sample channel sums of the output into gap_sums[n][Cout]
     const void* ws; const int* bs;   // bottleneck block only; not null: the residual is the 1x1 convolution of x with these operands and biases
     int sh_s, lo_s, hi_s;            // (res is null then), requantised with these
+    float f_lo_e, f_hi_e, f_lo_d, f_hi_d, f_lo_p, f_hi_p, f_lo_s, f_hi_s;      // bf16 bottleneck block: the layers' bounds, the biases are floats
 };
 
 struct DirectConvArgs {   // one thread per output element; any shape (correctness fallback)
@@ -215,6 +216,9 @@ hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq,
 bool bneck_block_supported(const IrArgs& a);
 bool bneck_block_pools(const IrArgs& a);     // with a.gap_sums the launch also pools: only where its rows of sums fit into LDS
 hipError_t launch_bneck_block(const IrArgs& a, hipStream_t s);
+// its bf16 form (kernels_bneck16.hip): always with a residual, or with the convolution on the shortcut; does not pool
+bool bneck_block_bf16_supported(const IrArgs& a);
+hipError_t launch_bneck_block_bf16(const IrArgs& a, hipStream_t s);
 hipError_t launch_maxpool(const PoolArgs& a, int dtype, hipStream_t s);
 hipError_t launch_avgpool(const PoolArgs& a, int dtype, hipStream_t s);
 

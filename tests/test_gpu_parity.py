@@ -877,6 +877,62 @@ def test_serve_stream_with_fused_bottleneck_blocks(torch, ee, orc, case):
     eng.close()
 
 
+@pytest.mark.parametrize("case", BN_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_fused_bottleneck_blocks_bf16(torch, ee, orc, case):
+    """The bf16 form: every sum runs in the staged kernel's order and every layer's result is rounded where the layer stores it, so fused and
+    separate layers agree bit for bit; against the oracle (double sums) under the tolerance of the tiling tests.  Biases that are not zero."""
+    h, w, ci, blocks, n = case
+    blob = W.bottleneck_net(h, w, ci, seed=h * 7 + w, blocks=blocks, dtype=W.DT_BF16)
+    say(f"[case] bf16 bottleneck {h}x{w} {ci} -> 64 -> 64 -> 256, {blocks} block(s), {n} samples")
+    r = np.random.default_rng(h * 100 + w)
+    for op in blob.ops:
+        blob.op_weights(op)[1][:] = r.normal(size=int(op["c_out"])) * 0.3
+    x = W.input_pool(blob, n)
+    eng = ee.Engine(blob, max(n, 2))
+    heads = {i: eng.ir_layers(i) for i in range(len(blob.ops)) if eng.ir_layers(i)}
+    assert sorted(heads.values()) == ([3] * blocks + [4] if ci == 64 else [3] * blocks) and eng.ir_count() == len(heads)
+    for b in sorted({n, 1}, reverse=True):
+        ref = orc.stage_forward(blob, 0, x[:b])
+        out = {}
+        for mode in (2, 0, 1, 2):
+            eng.ir_mode(mode)
+            if mode == 1:                                                  # by table: the blocks of three fused, the block of four not
+                eng.load_tables({"ir": {str(i): [0 if span == 4 else 1] for i, span in heads.items()}})
+            out[mode] = host(eng.stage_forward(0, dev(torch, x[:b]), ref.shape[1:]), ref)
+            assert np.array_equal(out[mode], out[2]), f"mode {mode} b={b}: {np.count_nonzero(out[mode] != out[2])} of {ref.size} differ, first at {np.argwhere(out[mode] != out[2])[:3].tolist()}"
+        rf, g = bf16_to_f32(ref).astype(np.float64), bf16_to_f32(out[2]).astype(np.float64)
+        scale = np.abs(rf).reshape(b, -1).max(axis=1).reshape(-1, 1, 1, 1) + 1e-30
+        assert np.all(np.abs(g - rf) <= 2e-2 * scale), f"b={b}: {np.max(np.abs(g - rf) / scale)}"
+    eng.close()
+
+
+@pytest.mark.parametrize("h,w,ci", [(12, 10, 64), (16, 16, 256)])
+def test_serve_stream_with_fused_bottleneck_blocks_bf16(torch, ee, orc, h, w, ci):
+    """Three segments of two bf16 bottleneck blocks served with every block fused, with and without zero-copy compaction (the block that ends a
+    segment writes its samples to their slots), on two lanes: what every request gets is that of the separate layers, bit for bit."""
+    blob = W.bottleneck_net(h, w, ci, seed=h, blocks=2, stages=3, dtype=W.DT_BF16)
+    n, b_max = 96, 8
+    pool = W.input_pool(blob, n)
+    act = pool[:24]
+    for s in range(2):                                                     # thresholds that split the requests at both exits
+        act = orc.stage_forward(blob, s, act)
+        blob.exits[s]["thr"] = float(np.median(orc.exit_head(blob, s, act, 0.5)[1]))
+    say(f"[case] serve bf16 bottleneck net {h}x{w}x{ci}")
+    eng = ee.Engine(blob, b_max)
+    assert eng.zero_copy_supported() and eng.set_lanes(2) == 2
+    lut = synthetic_lut(blob.n_stages, b_max)
+    dpool = dev(torch, pool)
+    want = None
+    for mode, zc in ((0, 0), (2, 1), (0, 1), (2, 0), (2, 1)):
+        eng.ir_mode(mode)
+        got = eng.serve_stream(np.zeros(n, np.int64), dpool, lut, refill=2, lanes=2, zero_copy=zc)[0]
+        want = got if want is None else want
+        for f in ("exit_idx", "label", "conf"):
+            assert np.array_equal(got[f], want[f]), (f, mode, zc)
+    assert np.all(np.bincount(want["exit_idx"], minlength=3) > 0)
+    eng.close()
+
+
 def test_zero_copy_is_refused_where_it_cannot_run(torch, ee, orc):
     blob = W.load_net("mobilenetv2_small_i8")                               # depthwise / thin layers at the segment boundaries
     eng = ee.Engine(blob, 8)

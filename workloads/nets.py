@@ -466,11 +466,11 @@ def stem_net(h, w, seed=0, dtype=DT_I8):
     return blob
 
 
-def bottleneck_net(h, w, ci, seed=0, blocks=1, mid=64, stages=1):
+def bottleneck_net(h, w, ci, seed=0, blocks=1, mid=64, stages=1, dtype=DT_I8):
     """`stages` segments (each with an exit) of `blocks` bottleneck blocks (1x1 to `mid` channels, 3x3 stride 1, 1x1 to 4 * mid channels with a residual:
-    the block's input where it has 4 * mid channels, else a 1x1 convolution of it) on an h x w x ci input, int8: the fused-block
-    kernel's shapes alone, for edge cases.  Data only."""
-    net = _Net(DT_I8, h, w, ci, 10)
+    the block's input where it has 4 * mid channels, else a 1x1 convolution of it) on an h x w x ci input: the fused-block
+    kernels' shapes alone, for edge cases.  Data only."""
+    net = _Net(dtype, h, w, ci, 10)
     cin = ci
     for _ in range(stages):
         t = net.begin_stage()
@@ -482,7 +482,7 @@ def bottleneck_net(h, w, ci, seed=0, blocks=1, mid=64, stages=1):
             t = net.conv(u, 4 * mid, 1, 1, 0, res=short)
             cin = 4 * mid
         net.end_stage(t)
-    blob = _assemble(net, DT_I8, BASE_SEED + 0x7800 + seed)
+    blob = _assemble(net, dtype, BASE_SEED + 0x7800 + seed)
     for op in blob.ops:
         if int(op["kind"]) == OP_CONV:
             fan_in = int(op["c_in"]) * int(op["kh"]) * int(op["kw"])
