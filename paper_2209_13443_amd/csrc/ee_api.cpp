@@ -789,11 +789,19 @@ hipError_t ee_ctx::launch_conv(int op, int b, const void* src, void* dst, const 
         if (p.impl != IMPL_MFMA || ((xs || ys) && b > EE_ZC_MAX_B)) return hipErrorInvalidValue;
         a.xs = xs; a.ys = ys;
         a.gap_sums = gap_sums;
+        if (cfg == 0) cfg = conv_rows_default(a, dt == EE_I8 ? 1 : 2);
         if (cfg_is_skinny(cfg)) return dt == EE_I8 ? launch_conv_skinny<1>(a, cfg, stream) : launch_conv_skinny<2>(a, cfg, stream);
-        if ((cfg & EE_CFG_SLAB) || (cfg & 15) == 7) cfg = 0;
+        if (cfg_is_rows(cfg) && conv_rows_supported(a, dt == EE_I8 ? 1 : 2)) return dt == EE_I8 ? launch_conv_rows<1>(a, cfg, stream) : launch_conv_rows<2>(a, cfg, stream);
+        if ((cfg & EE_CFG_SLAB) || (cfg & 15) == 7 || cfg_is_rows(cfg)) cfg = 0;
         return dt == EE_I8 ? launch_conv_igemm<1>(a, cfg, stream) : launch_conv_igemm<2>(a, cfg, stream);
     }
     if (cfg_is_skinny(cfg)) return dt == EE_I8 ? launch_conv_skinny<1>(a, cfg, stream) : launch_conv_skinny<2>(a, cfg, stream);
+    if (cfg == 0) cfg = conv_rows_default(a, dt == EE_I8 ? 1 : 2);
+    if (cfg_is_rows(cfg)) {
+        const hipError_t e = dt == EE_I8 ? launch_conv_rows<1>(a, cfg, stream) : launch_conv_rows<2>(a, cfg, stream);
+        if (e != hipErrorInvalidValue || forced_conv_tile() != cfg) return e;
+        cfg = 0;                                         // forced for the whole process: layers it does not cover keep the default
+    }
     const bool streamable = conv_stream_supported(a, dt == EE_I8 ? 1 : 2);
     if ((cfg & 15) == 7) {
         if (streamable) return launch_conv_stream(a, stream);
@@ -872,7 +880,9 @@ static int group_default(const ConvArgs* a, int n)
 //     the other, 69 together; 32 samples 33 / 38, 16 samples 24 / 22);
 //   the slab kernel would run a member of 128-byte or larger pixels on 1024 or more 64 x 64 tiles (28x28, 3x3, 128 -> 128 twice, 64 samples:
 //     24 us one after the other, 28 together; with 1x1, 128 -> 512 23 / 31; 32 samples 20 / 13 and 18 / 18; 14x14, 256 -> 256 twice, 128
-//     samples 36 / 40; with pixels of 64 bytes the joint launch is the faster one at 1-256 samples).
+//     samples 36 / 40; with pixels of 64 bytes the joint launch is the faster one at 1-256 samples);
+//   the 1x1 kernel with resident weights would run a member of 6144 or more 64 x 64 blocks of output (ResNet-50, segments 1 and 2: 128 samples 16 and 3 us
+//     longer together, 256 samples 36 and 18; 64 samples 0.6 and 7 us shorter).
 // Otherwise together, measured at 1-256 samples by the sums of the dispatches alone: over all segments Inception-style 1 sample 452 -> 283 us, 64
 // samples 1181 -> 1020, 256 samples 3460 -> 3243; ResNet-50 203 -> 193, 652 -> 652, 2067 -> 2064; ResNet-18 89 -> 79, 275 -> 263, 867 -> 855.  Of 33
 // joint launches at 15 sizes 9 lost, by 1-3 us (one by 6 of 27); of synthetic blocks a narrow 1x1 layer beside a wide one at 256 samples (80 us, 72 apart).
@@ -888,6 +898,7 @@ bool ee_ctx::group_by_default(int stage, int at, int n, int b) const
         fill_conv_args(op, b, a);
         a.res = p.d.res >= 0 ? (const void*)this : nullptr;                                            // only whether there is one matters
         if (a.M >= 1 << 19 && conv_stream_supported(a, 1)) return false;
+        if ((long long)((a.M + 63) / 64) * ((a.Co + 63) / 64) >= 6144 && conv_rows_default(a, 1)) return false;
         if (a.Ci >= 128 && (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64) >= 1024 && conv_slab_default(a, 1)) return false;
     }
     return true;
@@ -1044,6 +1055,9 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                         for (int kspl = 2; kspl <= (tile == 3 ? 4 : 2); kspl *= 2) cands.push_back(cfg | kspl << 12);
                 });
                 if (conv_stream_supported(probe, es)) cands.push_back(7);               // it has one configuration
+                // not for the layer that carries the exit head's pooling when it serves: that launch needs another kernel
+                if (p.impl == IMPL_MFMA && conv_rows_supported(probe, es) && st.first_op + k != ctx->gap_fuse_op[s])
+                    for (const int cfg : {EE_CFG_ROWS32, EE_CFG_ROWS64}) cands.push_back(cfg);
                 if (p.impl == IMPL_MFMA && conv_slab_supported(probe, es))
                     staged(kbytes, [&](int cfg) { if ((cfg >> 4 & 15) > 1) cands.push_back(EE_CFG_SLAB | cfg); });
                 if ((long long)buckets[bi] * d.h_out * d.w_out <= EE_SKINNY_MAX_ROWS)          // few pixels: the kernel that splits the reduction over its wavefronts

@@ -161,6 +161,13 @@ bool conv_pair_supported(int es, int co2, int kh, int kw, int ci, int co3);
 bool conv_slab_supported(const ConvArgs& a, int es);
 template <int ES> hipError_t launch_conv_slab(const ConvArgs& a, int cfg, hipStream_t s);
 int conv_slab_default(const ConvArgs& a, int es);      // configuration of an untuned launch it is the faster one for, else 0
+// 1x1 layers with resident weights (kernels_rows.hip): tiles of 32 or 64 pixels.  Its configuration words ask for four wavefront groups with
+// 256-byte steps on a large tile, which the staged kernel does not have
+enum { EE_CFG_ROWS32 = 0x4231, EE_CFG_ROWS64 = 0x4232 };
+inline bool cfg_is_rows(int cfg) { return cfg == EE_CFG_ROWS32 || cfg == EE_CFG_ROWS64; }
+bool conv_rows_supported(const ConvArgs& a, int es);
+int conv_rows_default(const ConvArgs& a, int es);      // configuration of an untuned launch it is the faster one for, else 0
+template <int ES> hipError_t launch_conv_rows(const ConvArgs& a, int cfg, hipStream_t s);
 enum { EE_CFG_SLAB = 0x10000 };     // configuration words with this bit name the slab kernel
 // few output pixels: the reduction split over a workgroup's wavefronts, operands straight from global memory (kernels_skinny.hip)
 // Its configuration words are those whose fields ask for wavefront groups (bits 12-15: 2 = tiles of 32 pixels, 4 = of 16) with a step

@@ -424,6 +424,84 @@ def test_small_exit_heads(torch, ee, orc, h, w, c, n_cls, dtype):
     eng.close()
 
 
+ROWS_CASES = [  # h, w, input bytes per pixel, output channels, stride, samples: no whole tile, ragged last tiles, several tiles per workgroup, every channel grouping
+    (1, 1, 128, 256, 1, 1), (5, 7, 128, 512, 1, 3), (9, 11, 256, 128, 2, 5), (56, 56, 128, 256, 1, 25), (13, 6, 256, 1024, 1, 4), (28, 28, 256, 256, 2, 9),
+    (14, 14, 512, 512, 1, 7), (8, 8, 512, 128, 1, 3), (10, 10, 1024, 2048, 1, 20), (7, 7, 1024, 128, 1, 2),
+]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("case", ROWS_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_resident_weights_1x1(torch, ee, orc, case, dtype):
+    """The 1x1 kernel with resident weights, both tile sizes, with and without a residual: int8 against the oracle bit for bit; bf16 against the
+    staged kernel bit for bit (its sums run in the same order) and the oracle under the tolerance of the tiling tests."""
+    from workloads import nets as N
+    h, w, kb, co, stride, n = case
+    i8 = dtype == "i8"
+    net = N._Net(W.DT_I8 if i8 else W.DT_BF16, h, w, kb // (1 if i8 else 2), 10)
+    t = net.begin_stage()
+    res = net.conv(t, co, 1, stride, 0, act="linear")
+    net.end_stage(net.conv(t, co, 1, stride, 0, res=res))
+    blob = N._assemble(net, net.dtype, 40 + h)
+    r = np.random.default_rng(co + kb)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"])) / 127))))
+        op["res_shift"] = int(op["shift"]) - 2 if int(op["res"]) >= 0 else 0
+        if not i8:
+            blob.op_weights(op)[1][:] = r.normal(size=co) * 0.3
+    x = W.input_pool(blob, n)
+    eng = ee.Engine(blob, n)
+    ref = orc.stage_forward(blob, 0, x)
+    staged = None
+    for cfg in (0x221, 0x4231, 0x4232):
+        say(f"[case] {dtype} {case} cfg {cfg:#x}")
+        old = ee.tune_conv_tile(cfg)
+        try:
+            got = host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref)
+        finally:
+            ee.tune_conv_tile(old)
+        if i8:
+            assert np.array_equal(got, ref), f"{np.count_nonzero(got != ref)} of {ref.size} differ, first at {np.argwhere(got != ref)[:3].tolist()}"
+        else:
+            staged = got if staged is None else staged
+            assert np.array_equal(got, staged), f"{np.count_nonzero(got != staged)} of {ref.size} differ, first at {np.argwhere(got != staged)[:3].tolist()}"
+            rf, g = bf16_to_f32(ref).astype(np.float64), bf16_to_f32(got).astype(np.float64)
+            assert np.all(np.abs(g - rf) <= 2e-2 * (np.abs(rf).reshape(n, -1).max(axis=1).reshape(-1, 1, 1, 1) + 1e-30))
+    assert np.unique(ref).size > 8
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+def test_resident_weights_1x1_takes_slot_tables(torch, ee, orc, dtype):
+    """Zero-copy serving with the kernel forced wherever it runs (the layers that read a segment's input, bf16 also those that write its output)."""
+    blob = W.bottleneck_net(11, 9, 256, seed=3, blocks=2, stages=3, dtype=W.DT_I8 if dtype == "i8" else W.DT_BF16)
+    n, b_max = 64, 8
+    pool = W.input_pool(blob, n)
+    act = pool[:24]
+    for s in range(2):
+        act = orc.stage_forward(blob, s, act)
+        blob.exits[s]["frac_bits"] = 12 if dtype == "i8" else blob.exits[s]["frac_bits"]
+        blob.exits[s]["thr"] = float(np.median(orc.exit_head(blob, s, act, 0.5)[1]))
+    say(f"[case] {dtype} slots")
+    eng = ee.Engine(blob, b_max)
+    eng.ir_mode(0)
+    assert eng.zero_copy_supported()
+    lut = synthetic_lut(blob.n_stages, b_max)
+    dpool = dev(torch, pool)
+    want = None
+    for cfg, zc in ((0x221, 0), (0x4231, 1), (0x4232, 1), (0x4232, 0)):
+        old = ee.tune_conv_tile(cfg)
+        try:
+            got = eng.serve_stream(np.zeros(n, np.int64), dpool, lut, refill=2, zero_copy=zc)[0]
+        finally:
+            ee.tune_conv_tile(old)
+        want = got if want is None else want
+        for f in ("exit_idx", "label", "conf", "score"):
+            assert np.array_equal(got[f], want[f]), (f, cfg, zc)
+    assert np.count_nonzero(np.bincount(want["exit_idx"], minlength=3)) > 1
+    eng.close()
+
+
 GROUP_CFGS = [0x211, 0x331, 0x422, 0x232, 0x313, 0x423, 0x333, 0x214, 0x324, 0x434] + [0x2213, 0x2214, 0x2223, 0x2224, 0x4213, 0x4214]
 
 
