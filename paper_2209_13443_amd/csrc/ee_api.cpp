@@ -434,6 +434,123 @@ void plan_buffers(ee_ctx* ctx)
     }
 }
 
+// Small segments (int8) that run with their exit head as one launch, a workgroup per sample: a chain of convolutions of 16-channel multiples
+// (residuals from any earlier tensor of the segment), the first one possibly on the folded image, whose operands and tensors of one
+// sample fit 64 KiB of LDS (two workgroups per CU) and whose matrix instructions (at most 512: 2 us on the four SIMDs of one CU) are
+// less than the launches they replace; the head as for head_small_kernel.  Measured at 1-256 samples (kernels_segment.hip): faster at every size.
+int plan_segments(ee_ctx* ctx)
+{
+    const int n_st = (int)ctx->net.stages.size();
+    auto magic = [](int d) { return (unsigned)(0x100000000ull / (unsigned)d - (d == 1)); };
+    ctx->seg.assign((size_t)n_st, SegPlan{});
+    ctx->seg_dev.assign((size_t)n_st, nullptr);
+    for (int s = 0; s < n_st && ctx->net.dtype == EE_I8; ++s) {
+        const StageDesc& st = ctx->net.stages[s];
+        const ExitDesc& e = ctx->net.exits[s];
+        if (st.n_ops < 1 || st.n_ops > EE_SEG_LAYERS) continue;
+        HeadArgs probe{};
+        probe.B = 1; probe.HW = e.h * e.w; probe.C = e.c; probe.n_cls = e.n_cls;
+        if (!head_small(probe, EE_I8, false)) continue;
+        SegPlan a{};
+        int at = 0;                                                       // LDS, handed out in multiples of 16 bytes
+        auto take = [&](int bytes) { const int p = at; at += round_up(bytes, 16); return p; };
+        auto pitch_of = [](int c) { return c == 16 ? 16 : c + 16; };      // bytes per pixel: neighbours in different banks
+        std::vector<int> off(st.n_tensors, -1), pitch(st.n_tensors, 0), writers(st.n_tensors, 0);
+        long long mfma = 0;
+        int chunks = 0;
+        bool ok = true;
+        const OpPlan& p0 = ctx->plans[st.first_op];
+        const int in_bytes = (int)ctx->stage_in_bytes(s);
+        for (int k = 0; k < st.n_ops && ok; ++k) {                        // weights first: copies of whole KiB
+            const OpPlan& p = ctx->plans[st.first_op + k];
+            const OpDesc& d = p.d;
+            ok = (p.impl == IMPL_MFMA || (p.impl == IMPL_MFMA_S2D && k == 0 && d.src == 0)) && p.wo_dev && d.c_tot == d.c_out && d.c_off == 0 && d.c_out % 16 == 0 && d.c_out <= 512;
+            if (!ok) break;
+            SegLayer& L = a.layer[k];
+            const int kh = p.impl == IMPL_MFMA_S2D ? p.kwp : d.kh, kw = p.impl == IMPL_MFMA_S2D ? p.kwp : d.kw;
+            L.wo = p.wo_dev; L.bias = (const int*)p.b_dev;
+            L.steps = (kh * kw * p.ci_eff + 31) / 32;
+            L.pitch = p.Kp / 32;
+            L.blocks = (d.c_out + 31) / 32;
+            L.magic_blocks = magic(L.blocks); L.magic_steps = magic(L.steps); L.magic_wo = magic(d.w_out);
+            L.w_off = take(L.blocks * L.steps * 1024);
+            mfma += (long long)((d.h_out * d.w_out + 31) / 32) * L.blocks * L.steps;
+            chunks += 2 * L.steps;
+            ok = at <= 64 * 1024 && mfma <= 512 && chunks <= EE_SEG_CHUNKS && kh * kw <= 31;
+        }
+        if (!ok || in_bytes > 32 * 1024) continue;
+        a.in_bytes = in_bytes; a.in_chunks = in_bytes / 16;
+        if (p0.impl == IMPL_MFMA_S2D) {
+            if (st.in_c > 4) continue;
+            a.fold = 1; a.fold_h = p0.Hp; a.fold_w = p0.Wp; a.fold_pad = p0.d.pad; a.img_h = st.in_h; a.img_w = st.in_w; a.img_c = st.in_c;
+            a.in_cpp = 1; a.in_pitch = 16;
+            a.in_off = take(round_up(in_bytes, 1024));                    // copied in whole KiB
+            a.fold_off = take(p0.Hp * p0.Wp * 16);
+        } else {
+            if (st.in_c % 16 != 0) continue;
+            a.in_cpp = st.in_c / 16; a.in_pitch = pitch_of(st.in_c);
+            a.in_off = take(round_up(st.in_h * st.in_w * a.in_pitch, 1024));
+            off[0] = a.in_off; pitch[0] = a.in_pitch;
+        }
+        int n_tab = 0;
+        for (int k = 0; k < st.n_ops && ok; ++k) {
+            const OpPlan& p = ctx->plans[st.first_op + k];
+            const OpDesc& d = p.d;
+            SegLayer& L = a.layer[k];
+            const bool folded = p.impl == IMPL_MFMA_S2D, last = k == st.n_ops - 1;
+            ok = (folded || off[d.src] >= 0) && (d.res < 0 || off[d.res] >= 0) && ++writers[d.dst] == 1 && (d.dst == st.out_tensor) == last;
+            if (!ok) break;
+            L.src = folded ? a.fold_off : off[d.src];
+            L.src_pitch = folded ? 16 : pitch[d.src];
+            L.cpp = p.ci_eff / 16;
+            L.H = folded ? p.Hp : d.h_in; L.W = folded ? p.Wp : d.w_in; L.Ho = d.h_out; L.Wo = d.w_out;
+            L.kh = folded ? p.kwp : d.kh; L.kw = folded ? p.kwp : d.kw; L.stride = folded ? 1 : d.stride; L.pad = folded ? 0 : d.pad; L.pad_w = folded ? 0 : d.pad_w;
+            L.co = d.c_out; L.shift = d.shift; L.res_shift = d.res_shift; L.lo = d.lo; L.hi = d.hi;
+            L.res = d.res >= 0 ? off[d.res] : -1;
+            L.res_pitch = d.res >= 0 ? pitch[d.res] : 0;
+            L.bias_kib = (L.blocks * 128 + 1023) / 1024;                  // the padded biases reach 256 entries past the last block
+            L.bias_off = take(L.bias_kib * 1024);
+            for (int r = 0; r < L.kh; ++r) L.tap_rows |= 1u << (r * L.kw);
+            for (int q = 0; q < 2 * L.steps; ++q) {
+                const int tap = q / L.cpp, r = tap / L.kw, sx = tap - r * L.kw;
+                a.tab[n_tab + q] = tap < L.kh * L.kw ? SegChunk{(r * L.W + sx) * L.src_pitch + 16 * (q - tap * L.cpp), tap} : SegChunk{0, 31};
+            }
+            L.tab = n_tab * (int)sizeof(SegChunk);                        // from the table's place, added below
+            n_tab += 2 * L.steps;
+            if (!last) {
+                pitch[d.dst] = pitch_of(d.c_out);
+                off[d.dst] = take(d.h_out * d.w_out * pitch[d.dst]);
+                L.dst = off[d.dst]; L.dst_pitch = pitch[d.dst];
+            } else {
+                ok = d.c_out == e.c && d.h_out * d.w_out == e.h * e.w;
+                a.sums_off = take(L.blocks * 128);
+            }
+            ok = ok && at <= 96 * 1024;
+        }
+        if (!ok) continue;
+        a.tab_kib = (n_tab * (int)sizeof(SegChunk) + 1023) / 1024;
+        a.tab_off = take(a.tab_kib * 1024);
+        for (int k = 0; k < st.n_ops; ++k) a.layer[k].tab += a.tab_off;
+        a.zero_off = take(16);
+        a.feat_off = take(e.c);
+        a.logits_off = take(4 * e.n_cls);
+        a.exp2_off = take(1024);
+        a.out_bytes = (int)ctx->stage_out_bytes(s);
+        a.lds_bytes = at;
+        if (at > 80 * 1024) continue;
+        a.n = st.n_ops;
+        a.magic_cpp = magic(a.in_cpp);
+        a.magic_fold_w = magic(std::max(a.fold_w, 1));
+        const unsigned char* bytes = reinterpret_cast<const unsigned char*>(&a);
+        void* dev = nullptr;
+        const int rc = upload(ctx, &dev, std::vector<unsigned char>(bytes, bytes + sizeof a));
+        if (rc) return rc;
+        ctx->seg[(size_t)s] = a;
+        ctx->seg_dev[(size_t)s] = static_cast<const SegPlan*>(dev);
+    }
+    return EE_OK;
+}
+
 // The per-lane part of the workspace (the lane's stream, intermediate tensors and padded input copies are set by the
 // caller when they exist already).
 int alloc_lane(ee_ctx* ctx, LaneState& L)
@@ -633,6 +750,13 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
     }
     ctx->c_max = (size_t)c_max;
     if ((rc = dev_alloc(ctx, &ctx->zero_page, 256))) return fail(rc);
+    {
+        const unsigned char* t = reinterpret_cast<const unsigned char*>(exp2_table_host());
+        void* p = nullptr;
+        if ((rc = upload(ctx, &p, std::vector<unsigned char>(t, t + 1024)))) return fail(rc);
+        ctx->exp2_dev = static_cast<uint32_t*>(p);
+    }
+    if ((rc = plan_segments(ctx))) return fail(rc);
     if ((rc = dev_alloc(ctx, &ctx->d_ids, sizeof(int32_t) * (size_t)b_max))) return fail(rc);
 
     // stream-serving workspace.  Shared by all lanes: the packed input slots of every segment behind the first, a ring of
@@ -1466,16 +1590,16 @@ extern "C" int ee_stage_forward(ee_ctx* ctx, int stage, int b_act, const void* a
     ctx->bind_lane(0);
     if (b_act == 0) return EE_OK;
     if (!act_in || !act_out || act_in == act_out || !aligned16(act_in) || !aligned16(act_out)) return EE_ERR_ARG;
+    if (ctx->seg_fused(stage)) return ctx->run_segment(stage, b_act, act_in, act_out, nullptr, nullptr, nullptr, nullptr, nullptr);
     return ctx->run_stage(stage, b_act, act_in, act_out);
 }
 
 // ---- one exit head ------------------------------------------------------------------------------------
-int ee_ctx::run_head(int stage, int b, const void* act, float thr, int32_t* label, float* conf, int64_t* score, uint8_t* flag, bool to_host,
-                     const ee::HeadScratch* own, const uint16_t* slots, bool pooled)
+HeadArgs ee_ctx::head_args(int stage, int b, const void* act, float thr, int32_t* label, float* conf, int64_t* score, uint8_t* flag, bool to_host, const ee::HeadScratch* own)
 {
     const ExitDesc& e = net.exits[stage];
-    const int dt = net.dtype, es = net.elem_bytes();
     HeadArgs a{};
+    a.exp2 = exp2_dev; a.es = net.elem_bytes();
     a.act = act; a.B = b; a.HW = e.h * e.w; a.C = e.c; a.n_cls = e.n_cls;
     a.gap_shift = e.gap_shift; a.frac_bits = e.frac_bits; a.logit_scale = e.logit_scale;
     a.wfc = wfc_dev[stage]; a.bfc = bfc_dev[stage];
@@ -1484,7 +1608,6 @@ int ee_ctx::run_head(int stage, int b, const void* act, float thr, int32_t* labe
     a.s_thr = !(thr > 0.0f) ? INT64_MAX : (thr > 1.0f ? 0 : (int64_t)std::floor(1073741824.0 / (double)thr));
     a.last = stage == (int)net.stages.size() - 1;
     a.label = label; a.conf = conf; a.score = score; a.flag = flag;
-    a.slots = slots;
     if (to_host) {
         // cleared records match no tag: the host takes none of an earlier launch for one of this
         for (int k = 0; k < b; ++k) {
@@ -1493,6 +1616,26 @@ int ee_ctx::run_head(int stage, int b, const void* act, float thr, int32_t* labe
         }
         a.host_out = h_out; a.tag = ee::outcome_tag(++seq); head_b = b;
     }
+    return a;
+}
+
+int ee_ctx::run_segment(int stage, int b, const void* act_in, void* act_out, const SegRows* rows, const int32_t* ids, const uint16_t* xs, const uint16_t* ys, const HeadArgs* h)
+{
+    const StageDesc& st = net.stages[stage];
+    double ops = h ? 2.0 * b * h->C * h->n_cls : 0.0, bytes = (double)b * (stage_in_bytes(stage) + stage_out_bytes(stage)) + (h ? (double)h->C * h->n_cls + 17.0 * b : 0.0);
+    for (int k = 0; k < st.n_ops; ++k) {
+        ops += plans[(size_t)(st.first_op + k)].ops_per_sample * b;
+        bytes += plans[(size_t)(st.first_op + k)].weight_bytes;
+    }
+    return timed(EE_K_CONV_MFMA, ops, bytes, [&] { return launch_segment_small(seg[(size_t)stage], seg_dev[(size_t)stage], act_in, act_out, b, rows, ids, xs, ys, h, stream); }, st.first_op) == hipSuccess ? EE_OK : EE_ERR_DEVICE;
+}
+
+int ee_ctx::run_head(int stage, int b, const void* act, float thr, int32_t* label, float* conf, int64_t* score, uint8_t* flag, bool to_host,
+                     const ee::HeadScratch* own, const uint16_t* slots, bool pooled)
+{
+    const int dt = net.dtype, es = net.elem_bytes();
+    HeadArgs a = head_args(stage, b, act, thr, label, conf, score, flag, to_host, own);
+    a.slots = slots;
     const double act_bytes = (double)b * a.HW * a.C * es;
     if (head_small(a, dt, pooled)) {
         const double by = (pooled ? 8.0 * b * a.C : act_bytes) + (double)a.C * a.n_cls * es + 17.0 * b;
@@ -1624,6 +1767,10 @@ extern "C" int ee_measure_lut(ee_ctx* ctx, int reps, int64_t* lut_ns)
                 if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = EE_ERR_DEVICE;
                 const auto t0 = std::chrono::steady_clock::now();
                 for (int r = 0; r < n && !rc; ++r) {
+                    if (ctx->seg_fused(s)) {
+                        const HeadArgs h = ctx->head_args(s, b, ctx->out_buf[s], 2.0f, ctx->d_label, ctx->d_conf, ctx->d_score, ctx->d_flag, true, nullptr);
+                        rc = ctx->run_segment(s, b, ctx->in_buf[s], ctx->out_buf[s], nullptr, s == 0 ? ctx->h_ids[0] : nullptr, nullptr, nullptr, &h);
+                    } else {
                     if (s == 0 && fold) {
                         const OpDesc& d = fold->d;
                         if (launch_space_to_depth(ctx->in_buf[0], ctx->pad_bufs[fold->pad_buf], ctx->h_ids[0], b, d.h_in, d.w_in, d.c_in, fold->Hp, fold->Wp, d.pad, ctx->net.dtype, ctx->stream, true) != hipSuccess) rc = EE_ERR_DEVICE;
@@ -1632,6 +1779,7 @@ extern "C" int ee_measure_lut(ee_ctx* ctx, int reps, int64_t* lut_ns)
                     if (!rc) rc = ctx->run_stage(s, b, ctx->in_buf[s], ctx->out_buf[s], s == 0 && fold != nullptr);
                     ctx->gap_fuse_dst = nullptr;
                     if (!rc) rc = ctx->run_head(s, b, ctx->out_buf[s], 2.0f, ctx->d_label, ctx->d_conf, ctx->d_score, ctx->d_flag, true, nullptr, nullptr, ctx->gap_fused);
+                    }
                     if (!rc && s + 1 < n_st && launch_compact(ctx->d_flag, ctx->out_buf[s], ctx->in_buf[s + 1], nullptr, nullptr, b, nullptr, nullptr, 0, sb_out, 0, 0, nullptr, nullptr, ctx->stream) != hipSuccess) rc = EE_ERR_DEVICE;
                     if (!rc) rc = ctx->wait_head();
                 }

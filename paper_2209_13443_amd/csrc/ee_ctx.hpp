@@ -83,6 +83,11 @@ struct ee_ctx {
     std::vector<void*> pad_bufs;                 // zero-padded 4-channel input copies (first layers)
     std::vector<void*> owned;                    // every device allocation, for ee_destroy
     std::vector<void*> wfc_dev, bfc_dev;         // exit heads
+    uint32_t* exp2_dev = nullptr;                // the integer softmax's table
+    // segments small enough to run with their exit head as one launch (int8): the launch's plan, n = 0 for the others
+    std::vector<ee::SegPlan> seg;
+    std::vector<const ee::SegPlan*> seg_dev;     // the same in device memory
+    bool seg_fused(int s) const { return seg[(size_t)s].n > 0 && ir_mode > 0 && ee::forced_conv_tile() == 0; }
     int32_t* sums = nullptr;                     // [b_max][C_max]
     int32_t* gap_partial = nullptr;              // [(b_max + 1024)][C_max] partial rows of the pooling splits
     void* logits = nullptr;                      // [b_max][n_cls]
@@ -169,6 +174,10 @@ struct ee_ctx {
     // own: scratch memory to use instead of the context's (sums, gap_partial, logits)
     int run_head(int stage, int b_act, const void* act, float thr, int32_t* label, float* conf, int64_t* score, uint8_t* flag,
                  bool to_host = false, const ee::HeadScratch* own = nullptr, const uint16_t* slots = nullptr, bool pooled = false);
+    // the head's arguments; with to_host the records are cleared and tagged
+    ee::HeadArgs head_args(int stage, int b_act, const void* act, float thr, int32_t* label, float* conf, int64_t* score, uint8_t* flag, bool to_host, const ee::HeadScratch* own);
+    // a segment with seg_fused: one launch, with the exit head when h is given.  rows (b <= EE_SEG_ROWS) or ids / xs and ys as launch_segment_small takes them
+    int run_segment(int stage, int b_act, const void* act_in, void* act_out, const ee::SegRows* rows, const int32_t* ids, const uint16_t* xs, const uint16_t* ys, const ee::HeadArgs* h);
     // the bound lane's latest exit head with to_host has written all its records; wait_head spins until it has (EE_ERR_DEVICE
     // when the stream has failed or nothing has come after two seconds)
     bool head_reported() const { return ee::outcomes_ready(h_out, head_b, ee::outcome_tag(seq)); }

@@ -241,6 +241,8 @@ struct HeadArgs {
     // stream serving: per-slot outcomes written straight into pinned host memory, each with the launch's tag (null otherwise)
     struct HostOutcome* host_out; unsigned tag;
     const uint16_t* slots;   // pooling: not null: sample b of the batch is slot slots[b] of act (device memory)
+    const uint32_t* exp2;    // the softmax's table in device memory (segment_small_i8_kernel)
+    int es;                  // element bytes
 };
 // w0: bits 0-43 the score S (int8: S <= n_cls * 2^30 < 2^44; the host derives the confidence 2^30 / S) or the confidence's
 // float bits (bf16); w1: bits 0-31 the label, bit 32 the exit flag; bits 44-63 of both: the launch's tag (never 0: a record the
@@ -286,6 +288,37 @@ hipError_t launch_head_softmax(const HeadArgs& a, int dtype, hipStream_t s);
 // all of it in one launch, for heads small enough (pooled: a.sums holds the sums already)
 bool head_small(const HeadArgs& a, int dtype, bool pooled);
 hipError_t launch_head_small(const HeadArgs& a, int dtype, bool pooled, hipStream_t s);
+
+// A small segment and its exit head in one launch (int8, kernels_segment.hip).  Tensors of one sample live in LDS: offsets and bytes per pixel.
+enum { EE_SEG_LAYERS = 6, EE_SEG_ROWS = 64, EE_SEG_CHUNKS = 256 };
+struct SegChunk { int off, tap; };       // bytes from the patch's corner in the source tensor, tap r * kw + s (31: past the end)
+// What never changes is in device memory: the argument segment of a launch is host memory, where every cache line costs a round trip over the bus.
+struct alignas(64) SegLayer {
+    const void* wo; const int* bias;     // ready operands (ConvArgs::wo), biases with the rounding constant
+    int w_off, bias_off, bias_kib;       // where they go in LDS; whole KiB of biases
+    int tab;                             // in LDS: the layer's part of the table below
+    unsigned tap_rows;                   // bit r * kw of every kernel row r
+    int steps, pitch;                    // reduction steps of 32 bytes: of the layer, of a weight row
+    int blocks, co;                      // blocks of 32 output channels, output channels (a multiple of 16)
+    int src, src_pitch, dst, dst_pitch, res, res_pitch;      // res < 0: none
+    int H, W, Ho, Wo, kh, kw, stride, pad, pad_w, cpp;       // cpp: 16-byte chunks per input pixel
+    int shift, res_shift, lo, hi;
+    unsigned magic_wo, magic_blocks, magic_steps;            // floor(2^32 / d): fast_div
+};
+struct alignas(64) SegPlan {
+    int n;                                                   // layers; 0: the segment is not one of these
+    int in_bytes, in_chunks, in_cpp, in_off, in_pitch;       // the input sample
+    int fold, fold_off, fold_h, fold_w, fold_pad, img_h, img_w, img_c;      // folded first layer: the super-pixels and the raw image
+    int zero_off, sums_off, feat_off, logits_off, exp2_off, lds_bytes, out_bytes;
+    int tab_off, tab_kib;
+    unsigned magic_cpp, magic_fold_w;
+    SegLayer layer[EE_SEG_LAYERS];
+    SegChunk tab[EE_SEG_CHUNKS];         // per layer and 16-byte chunk of its reduction (two per step): where it is
+};
+struct SegRows { int32_t src[EE_SEG_ROWS], dst[EE_SEG_ROWS]; };
+// rows (host memory, up to EE_SEG_ROWS samples): input and output row of every sample, by value; else ids / xs and ys (device-visible, may be null)
+// plan, dev_plan: the same on the host and on the device
+hipError_t launch_segment_small(const SegPlan& plan, const SegPlan* dev_plan, const void* x, void* y, int B, const SegRows* rows, const int32_t* ids, const uint16_t* xs, const uint16_t* ys, const HeadArgs* h, hipStream_t s);
 
 // Stable compaction + refill: the survivors of src[b_act], then the b_incr samples of refill.  dst_off: first destination slot
 // of the survivors; ring_rows > 0: dst is a ring of that many slots and destination slots wrap around its end.

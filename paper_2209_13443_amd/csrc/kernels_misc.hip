@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "ee_internal.hpp"
+#include "head_device.hpp"
 
 namespace ee {
 
@@ -740,47 +741,6 @@ __device__ __forceinline__ T block_reduce(T v, T* scratch, bool is_max)
     return r;
 }
 
-// A sample's record for the host: one 16-byte store into pinned host memory.  Both 64-bit words carry the launch's tag, so
-// the host sees by itself when a record is complete (an aligned 64-bit word arrives whole): no fence, no counter of
-// workgroups and no word behind them on the device side, and the host reads a record as soon as it lands.
-__device__ __forceinline__ void host_record(HostOutcome* dst, uint64_t payload, int label, unsigned flag, unsigned tag)
-{
-    const uint64_t w0 = payload | (uint64_t)tag << EE_OUTCOME_TAG_SHIFT;
-    const uint64_t w1 = (uint64_t)(unsigned)label | (uint64_t)(flag & 1u) << 32 | (uint64_t)tag << EE_OUTCOME_TAG_SHIFT;
-    const v4i rec = {(int)(unsigned)w0, (int)(unsigned)(w0 >> 32), (int)(unsigned)w1, (int)(unsigned)(w1 >> 32)};
-    *(v4i*)dst = rec;
-}
-
-// term of the base-2 softmax denominator: T[frac(d)] >> (d >> f), d = m - v
-__device__ __forceinline__ unsigned softmax_term_i8(int m, int v, int f, const uint32_t* table)
-{
-    const unsigned d = (unsigned)m - (unsigned)v;                // 0 .. 2^32 - 1
-    const unsigned q = d >> f, frac = d & ((1u << f) - 1u);
-    const unsigned r = f >= 8 ? frac >> (f - 8) : frac << (8 - f);
-    return q >= 31 ? 0u : table[r] >> q;
-}
-// the exit decision of sample b and its outcome (one lane)
-__device__ __forceinline__ void head_decide_i8(const HeadArgs& a, int b, int arg, long long S)
-{
-    const float conf = (float)(1073741824.0 / (double)S);
-    const uint8_t flag = (uint8_t)(a.last || S <= a.s_thr);
-    a.label[b] = arg;
-    a.score[b] = S;
-    a.conf[b] = conf;
-    a.flag[b] = flag;
-    if (a.host_out) host_record(a.host_out + b, (uint64_t)S, arg, flag, a.tag);
-}
-__device__ __forceinline__ void head_decide_bf16(const HeadArgs& a, int b, int arg, float den)
-{
-    const float conf = 1.0f / den;
-    const uint8_t flag = (uint8_t)(a.last || conf >= a.thr);
-    a.label[b] = arg;
-    a.score[b] = 0;
-    a.conf[b] = conf;
-    a.flag[b] = flag;
-    if (a.host_out) host_record(a.host_out + b, (uint64_t)__float_as_uint(conf), arg, flag, a.tag);
-}
-
 // one workgroup per sample.  int8: m = max logit, label = lowest arg-max, S = sum_j T[frac(d_j)] >> (d_j >> f)
 // with d_j = m - a_j (a base-2 softmax denominator in Q30); exits iff S <= s_thr.  bf16: float softmax.
 // The sample's logits are read once into registers (up to 8 per lane: n_cls <= 2048); the arg-max and the
@@ -875,7 +835,6 @@ hipError_t launch_head_softmax(const HeadArgs& a, int dtype, hipStream_t s)
 // Same integers as the three kernels; bf16: float features times bf16 weights in float.
 // Measured: int8, 16x16x16 and 10 classes, 8 samples, the three kernels take 5.9 + 2.6 + 3.6 us; with this one launch and none for slot
 // tables a stream of 64 requests in 8 slots (24 exit boundaries) went from 824 to 586 us.
-constexpr int HEAD_SMALL_C = 4096, HEAD_SMALL_CLS = 256;
 template <int ES>
 __global__ __launch_bounds__(256) void head_small_kernel(HeadArgs a, int pooled)
 {
@@ -884,20 +843,18 @@ __global__ __launch_bounds__(256) void head_small_kernel(HeadArgs a, int pooled)
     __shared__ __attribute__((aligned(16))) unsigned char feat[ES == 1 ? HEAD_SMALL_C : 2 * HEAD_SMALL_C];    // int8 features, or floats (C <= HEAD_SMALL_C / ES)
     __shared__ int lg[HEAD_SMALL_CLS];
     __shared__ uint32_t exp2_lds[256];
-    const int tid = threadIdx.x, lane = tid & 63, b = xcd_unit(blockIdx.x, a.B);
+    const int tid = threadIdx.x, b = xcd_unit(blockIdx.x, a.B);
     if (b < 0) return;
     const int cchunks = a.C * ES / 16, CB = a.C * ES;
-    const int part = tid & 15, j0 = tid >> 4;                   // FC: the lane's share of the row of classes j0, j0 + 16, ...
-    const v4i zero4 = {0, 0, 0, 0};
-    auto weight = [&](int j, int k) { return j < a.n_cls && k < cchunks ? *(const v4i*)((const unsigned char*)a.wfc + (long long)j * CB + k * 16) : zero4; };
-    v4i w_first = weight(j0, part);
+    const v4i w_first = head_weight(a, tid >> 4, tid & 15);
+    const int b_first = head_bias(a, tid >> 4);
     if constexpr (ES == 1) exp2_lds[tid] = kExp2[tid];
     if (pooled) {
         for (int c = tid; c < a.C; c += 256) {
             int* sp = a.sums + (long long)b * a.C + c;          // int8 only
             const int s = *sp;
             *sp = 0;                                            // left zero for the next head
-            feat[c] = (unsigned char)min(max(a.gap_shift > 0 ? (s + (1 << (a.gap_shift - 1))) >> a.gap_shift : s, -128), 127);
+            feat[c] = head_feature_i8(a, s);
         }
     } else {
         const int npl = 256 / cchunks, q = tid % cchunks, pl = tid / cchunks;
@@ -932,7 +889,7 @@ __global__ __launch_bounds__(256) void head_small_kernel(HeadArgs a, int pooled)
             if constexpr (ES == 1) {
                 int s = 0;
                 for (int l = 0; l < npl; ++l) s += red[l * a.C + c];
-                feat[c] = (unsigned char)min(max(a.gap_shift > 0 ? (s + (1 << (a.gap_shift - 1))) >> a.gap_shift : s, -128), 127);
+                feat[c] = head_feature_i8(a, s);
             } else {
                 float s = 0.f;
                 for (int l = 0; l < npl; ++l) s += __int_as_float(red[l * a.C + c]);
@@ -941,81 +898,7 @@ __global__ __launch_bounds__(256) void head_small_kernel(HeadArgs a, int pooled)
         }
     }
     __syncthreads();
-    for (int j = j0; j < (a.n_cls + 15) / 16 * 16; j += 16) {
-        int ti = 0;
-        float tf = 0.f;
-        for (int k = part; k < cchunks; k += 16) {
-            const v4i w = j == j0 && k == part ? w_first : weight(j, k);
-            if constexpr (ES == 1) {
-                const v4i g = *(const v4i*)(feat + k * 16);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ti = __builtin_amdgcn_sdot4(w[e], g[e], ti, false);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) tf = fmaf(bf16_to_f32_m((uint16_t)((unsigned)w[e >> 1] >> (16 * (e & 1)))), ((const float*)feat)[k * 8 + e], tf);
-            }
-        }
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-            if constexpr (ES == 1) ti += __shfl_xor(ti, o, 64);
-            else tf += __shfl_xor(tf, o, 64);
-        }
-        if (part == 0 && j < a.n_cls) {
-            const int bias = ((const int*)a.bfc)[j];
-            const int v = ES == 1 ? ti + bias : __float_as_int(a.logit_scale * (tf + __int_as_float(bias)));
-            lg[j] = v;
-            ((int*)a.logits)[(long long)b * a.n_cls + j] = v;
-        }
-    }
-    __syncthreads();
-    if (tid >= 64) return;
-    // ---- one wavefront decides: softmax_kernel's arithmetic
-    constexpr int PER = HEAD_SMALL_CLS / 64;
-    int vi[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) vi[i] = lane + 64 * i < a.n_cls ? lg[lane + 64 * i] : (ES == 1 ? INT32_MIN : __float_as_int(-INFINITY));
-    int arg = INT32_MAX;
-    if constexpr (ES == 1) {
-        int m = INT32_MIN;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) m = max(m, vi[i]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-        long long S = 0;
-        const int f = a.frac_bits;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int j = lane + 64 * i;
-            if (j >= a.n_cls) continue;
-            if (vi[i] == m) arg = min(arg, j);
-            S += softmax_term_i8(m, vi[i], f, exp2_lds);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            S += __shfl_xor(S, o, 64);
-            arg = min(arg, __shfl_xor(arg, o, 64));
-        }
-        if (lane == 0) head_decide_i8(a, b, arg, S);
-    } else {
-        float m = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) m = fmaxf(m, __int_as_float(vi[i]));
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-        float den = 0.f;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int j = lane + 64 * i;
-            if (j >= a.n_cls) continue;
-            const float z = __int_as_float(vi[i]);
-            if (z == m) arg = min(arg, j);
-            den += expf(z - m);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            den += __shfl_xor(den, o, 64);
-            arg = min(arg, __shfl_xor(arg, o, 64));
-        }
-        if (lane == 0) head_decide_bf16(a, b, arg, den);
-    }
+    head_logits_decide<ES, 256>(a, b, feat, lg, exp2_lds, tid, w_first, b_first);
 }
 
 bool head_small(const HeadArgs& a, int dtype, bool pooled)

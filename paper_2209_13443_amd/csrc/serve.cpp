@@ -98,9 +98,12 @@ struct GpuExec {
     std::vector<uint8_t> busy[8];                // per level and slot: taken
     // in_base, out_base: first slot of a consecutive run, or -1: the table says
     struct Step { SlotTab in, out; int b = 0, stage = -1, dst = -1, ring = 0, in_base = 0, out_base = 0; bool has_out = false; } step_of[4];
+    bool small[8] = {};                          // the segments that run with their exit head as one launch, decided once per call
+    const int32_t* admitted[4] = {};             // the lane's latest admission (pinned ids), read by a first segment that runs as one launch
 
     explicit GpuExec(ee_ctx* c, const void* input_pool, bool zero_copy = false) : ctx(c), pool((const unsigned char*)input_pool), zc(zero_copy)
     {
+        for (size_t s = 0; s < ctx->seg.size() && s < 8; ++s) small[s] = ctx->seg_fused((int)s);
         if (!zc) return;
         for (size_t s = 1; s < ctx->in_buf.size() && s < 8; ++s) {
             row2slot[s].assign((size_t)ctx->zc_slots, 0);
@@ -148,6 +151,8 @@ struct GpuExec {
         st.has_out = stage + 1 < E;
         if (st.has_out && !take_slots(stage + 1, b, st.out, st.out_base)) return EE_ERR_OVERFLOW;      // cannot happen: five blocks cover what can be held
         // the tables that are needed go to the lane's device buffer in one tiny launch ahead of the step's kernels
+        // (a small segment's launch carries its rows by value)
+        if (small[stage] && b <= EE_SEG_ROWS) return EE_OK;
         if ((st.in_base < 0 || st.out_base < 0) && launch_upload_slots(st.in, st.out, ctx->d_slots, ctx->stream) != hipSuccess) return EE_ERR_DEVICE;
         ctx->zc_in = st.in_base < 0 ? ctx->d_slots : nullptr;
         ctx->zc_out = st.out_base < 0 ? ctx->d_slots + EE_ZC_MAX_B : nullptr;
@@ -186,9 +191,30 @@ struct GpuExec {
         if (!zc || stage + 1 >= (int)ctx->in_buf.size()) return ctx->out_buf[stage];
         return (unsigned char*)ctx->in_buf[stage + 1] + (int64_t)std::max(0, step_of[lane].out_base) * ctx->stage_out_bytes(stage);
     }
+    // a segment that runs with its exit head as one launch: the first one reads the admitted requests straight out of the pool
+    int run_small(int lane, int stage, int b, int src_off)
+    {
+        const Step& st = step_of[lane];
+        const bool slots = zc && stage > 0, out_slots = zc && st.has_out;
+        const HeadArgs h = ctx->head_args(stage, b, nullptr, ctx->net.exits[stage].thr, ctx->d_label, ctx->d_conf, ctx->d_score, ctx->d_flag, true, nullptr);
+        int rc;
+        if (b <= EE_SEG_ROWS) {
+            SegRows rows;
+            for (int k = 0; k < b; ++k) {
+                rows.src[k] = stage == 0 ? admitted[lane][k] : slots ? st.in.s[k] : src_off + k;
+                rows.dst[k] = out_slots ? st.out.s[k] : k;
+            }
+            rc = ctx->run_segment(stage, b, stage == 0 ? (const void*)pool : ctx->in_buf[stage], out_slots ? ctx->in_buf[stage + 1] : ctx->out_buf[stage], &rows, nullptr, nullptr, nullptr, &h);
+        } else {
+            rc = ctx->run_segment(stage, b, stage == 0 ? (const void*)pool : step_in(lane, stage, src_off), step_out(lane, stage), nullptr, stage == 0 ? admitted[lane] : nullptr, ctx->zc_in, ctx->zc_out, &h);
+        }
+        ctx->zc_in = ctx->zc_out = nullptr;
+        return rc;
+    }
     int run_step(int lane, int stage, int b, int src_off, int ring_rows)
     {
         if (zc) { const int rc = zc_begin(lane, stage, b, src_off, ring_rows); if (rc) return rc; }
+        if (small[stage]) return run_small(lane, stage, b, src_off);
         ctx->gap_fuse_dst = ctx->sums;                   // the segment's last layer pools for the exit head where it can
         int rc = ctx->run_stage(stage, b, step_in(lane, stage, src_off), step_out(lane, stage), stage == 0 && ctx->admission_fold() != nullptr);
         ctx->gap_fuse_dst = nullptr;
@@ -206,6 +232,8 @@ struct GpuExec {
         int32_t* h_ids = ctx->h_ids[ctx->ids_turn];
         ctx->ids_turn ^= 1;
         std::memcpy(h_ids, ids, sizeof(int32_t) * (size_t)b);
+        admitted[lane] = h_ids;
+        if (small[0]) return EE_OK;                      // the segment's launch reads the pool itself
         const int64_t sb = ctx->stage_in_bytes(0);
         hipError_t e;
         if (const OpPlan* p = ctx->admission_fold()) {

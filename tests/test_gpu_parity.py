@@ -424,6 +424,60 @@ def test_small_exit_heads(torch, ee, orc, h, w, c, n_cls, dtype):
     eng.close()
 
 
+def launches_of(eng, f):
+    eng.profile(True)
+    eng.profile_read()
+    f()
+    n = sum(c["launches"] for c in eng.profile_read().values())
+    eng.profile(False)
+    return n
+
+
+SMALL_SEGMENTS = {  # networks whose every segment runs with its exit head as one launch: the folded first layer; residuals of the segment's input and of a
+    # convolution of it, 1x1 and 3x3, one pixel, channels that fill no block of 32, images that are no whole blocks of 32 pixels
+    "tiny": lambda: W.load_net("tiny_i8"), "bneck_5x7": lambda: W.bottleneck_net(5, 7, 64, mid=16, stages=3, seed=1), "bneck_1x1": lambda: W.bottleneck_net(1, 1, 64, mid=32, stages=2, seed=2),
+    "bneck_9x9": lambda: W.bottleneck_net(9, 9, 64, mid=32, stages=2, seed=3),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SMALL_SEGMENTS))
+def test_small_segments_in_one_launch(torch, ee, orc, name):
+    """A segment and its exit head as one launch against the oracle, bit for bit: the segment alone (1, some and more than 64 samples), and served under
+    the three policies, with and without zero-copy compaction, with the rows by value (up to 64 samples) and out of tables (more)."""
+    blob = SMALL_SEGMENTS[name]()
+    n, b_max = 260, 100
+    x = W.input_pool(blob, n)
+    act = x[:24]
+    for s in range(blob.n_stages - 1):                                     # thresholds that split the requests
+        act = orc.stage_forward(blob, s, act)
+        blob.exits[s]["frac_bits"] = 12 if name != "tiny" else blob.exits[s]["frac_bits"]
+        blob.exits[s]["thr"] = float(np.median(orc.exit_head(blob, s, act, 0.5)[1]))
+    eng = ee.Engine(blob, b_max)
+    for b in (100, 1, 13):
+        act = x[:b]
+        for s in range(blob.n_stages):
+            say(f"[case] {name} segment {s} b={b}")
+            ref = orc.stage_forward(blob, s, act)
+            got = []
+            assert launches_of(eng, lambda: got.append(eng.stage_forward(s, dev(torch, act), ref.shape[1:]))) == 1
+            assert np.array_equal(host(got[0], ref), ref), f"{np.count_nonzero(host(got[0], ref) != ref)} of {ref.size} differ"
+            act = ref
+    assert eng.set_lanes(2) == 2
+    dpool = dev(torch, x)
+    lut = synthetic_lut(blob.n_stages, b_max)
+    arrivals = np.zeros(n, np.int64)
+    for refill, lanes, bm in ((0, 1, 100), (1, 1, 100), (2, 2, 100), (2, 1, 8), (1, 1, 64)):
+        say(f"[case] {name} served refill={refill} lanes={lanes} b_max={bm}")
+        ref, rst, rev = orc.serve_stream(blob, arrivals, x, bm, lut[:, :bm], refill=refill, lanes=lanes, max_events=5000, min_incr=max(1, bm // 2))
+        for zc in (0, 1) if eng.zero_copy_supported() else (0,):
+            got, gst, gev = eng.serve_stream(arrivals, dpool, lut[:, :bm], b_max=bm, clock=1, refill=refill, lanes=lanes, max_events=5000, min_incr=max(1, bm // 2), zero_copy=zc)
+            for f in ("exit_idx", "label", "score", "latency_ns"):
+                assert np.array_equal(got[f], ref[f]), (f, refill, lanes, bm, zc)
+            assert gst == rst and np.array_equal(gev, rev)
+    assert np.count_nonzero(np.bincount(ref["exit_idx"])) > 1
+    eng.close()
+
+
 ROWS_CASES = [  # h, w, input bytes per pixel, output channels, stride, samples: no whole tile, ragged last tiles, several tiles per workgroup, every channel grouping
     (1, 1, 128, 256, 1, 1), (5, 7, 128, 512, 1, 3), (9, 11, 256, 128, 2, 5), (56, 56, 128, 256, 1, 25), (13, 6, 256, 1024, 1, 4), (28, 28, 256, 256, 2, 9),
     (14, 14, 512, 512, 1, 7), (8, 8, 512, 128, 1, 3), (10, 10, 1024, 2048, 1, 20), (7, 7, 1024, 128, 1, 2),
