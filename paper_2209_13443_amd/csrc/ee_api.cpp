@@ -351,8 +351,8 @@ int pack_bneck_shortcut(ee_ctx* ctx, const unsigned char* blob, const StageDesc&
 // The order a segment's layers are launched in.  A layer's level is one more than that of its inputs; the layers of a level (the branches of
 // a concatenating block, a block's first layer and the convolution on its shortcut) read nothing of one another and run one behind
 // the other: those that read the same tensor find it in the L2 (Inception-style network, 256 samples: 3670 -> 3560 us).  Segments
-// with layers that can be fused keep the network's order (fused layers are neighbours in it), which for residual networks is the order
-// by level anyway.
+// with layers that can be fused keep the network's order (fused layers are neighbours in it; a convolution and its pool in a chain are by level too), which
+// for residual networks is the order by level anyway.
 void plan_order(ee_ctx* ctx)
 {
     ctx->order.assign(ctx->plans.size(), 0);
@@ -363,10 +363,17 @@ void plan_order(ee_ctx* ctx)
             const OpPlan& p = ctx->plans[st.first_op + k];
             level[k] = 1 + std::max(level_of[p.d.src], p.d.res >= 0 ? level_of[p.d.res] : 0);
             level_of[p.d.dst] = std::max(level_of[p.d.dst], level[k]);
-            fused |= p.pair || p.ir;
+            fused |= p.pair || (p.ir && !p.ir_stem);
             order[k] = k;
         }
-        if (!fused) std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return level[x] < level[y]; });
+        if (!fused) {
+            std::vector<int> by_level = order;
+            std::stable_sort(by_level.begin(), by_level.end(), [&](int x, int y) { return level[x] < level[y]; });
+            bool together = true;                                         // a convolution fused with its pool is followed by it
+            for (int i = 0; i < st.n_ops; ++i)
+                if (ctx->plans[st.first_op + by_level[i]].ir_stem) together &= i + 1 < st.n_ops && by_level[i + 1] == by_level[i] + 1;
+            if (together) order = by_level;
+        }
         int group = 0;
         for (int i = 0; i < st.n_ops; ++i) {
             if (i > 0 && level[order[i]] != level[order[i - 1]]) ++group;
@@ -709,14 +716,15 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
     for (const StageDesc& st : ctx->net.stages)
         for (int k = 0; k + 3 < st.n_ops; ++k)
             if ((rc = pack_bneck_shortcut(ctx, (const unsigned char*)blob, st, k))) return fail(rc);
-    // the folded first convolution with the max-pool that alone reads it (nothing to pack: the kernel takes the layer's own weights)
+    // the folded first convolution, or a 3x3 one over 32 channels, with the max-pool that alone reads it (nothing to pack: the kernels take the
+    // layer's own weights)
     for (const StageDesc& st : ctx->net.stages)
         for (int k = 0; k + 1 < st.n_ops; ++k) {
             OpPlan& p = ctx->plans[st.first_op + k];
             const OpDesc& c = p.d;
             const OpDesc& q = ctx->plans[st.first_op + k + 1].d;
-            if (p.ir || p.impl != IMPL_MFMA_S2D || c.res >= 0 || c.dst == st.out_tensor || q.kind != OP_MAXPOOL || q.src != c.dst) continue;
-            if (q.kh != 3 || q.kw != 3 || q.stride != 2 || q.pad != 1 || q.pad_w != 1 || q.c_tot != q.c_out || q.c_off != 0 || q.dst == st.out_tensor) continue;
+            if (p.ir || (p.impl != IMPL_MFMA_S2D && p.impl != IMPL_MFMA) || c.res >= 0 || c.dst == st.out_tensor || q.kind != OP_MAXPOOL || q.src != c.dst) continue;
+            if (q.kh != 3 || q.kw != 3 || q.stride != 2 || q.pad != q.pad_w || q.c_tot != q.c_out || q.c_off != 0 || q.dst == st.out_tensor) continue;
             int readers = 0;
             for (int j = 0; j < st.n_ops; ++j) {
                 const OpDesc& o = ctx->plans[st.first_op + j].d;
@@ -724,7 +732,7 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
             }
             ConvArgs probe{};
             ctx->fill_conv_args(st.first_op + k, b_max, probe);
-            if (readers != 1 || !stem_pool_supported(probe, es, q.h_out, q.w_out)) continue;
+            if (readers != 1 || !(p.impl == IMPL_MFMA_S2D ? q.pad == 1 && stem_pool_supported(probe, es, q.h_out, q.w_out) : conv_pool_supported(probe, es, q.h_out, q.w_out, q.pad))) continue;
             p.ir = true;
             p.ir_stem = true;
         }
@@ -1458,18 +1466,19 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             const bool fuse = ir_wanted(st.first_op + k, b);
             if (fuse && p.ir_stem) {
                 const OpPlan& q2 = plans[st.first_op + k + 1];
-                if (!(first_packed && k == 0)) {                                 // the folded copy of the input, as in front of the layer alone
+                const bool folded = p.impl == IMPL_MFMA_S2D;
+                if (folded && !(first_packed && k == 0)) {                                 // the folded copy of the input, as in front of the layer alone
                     const double pb = (double)b * ((double)d.h_in * d.w_in * d.c_in + (double)p.Hp * p.Wp * 16) * es;
                     e = timed(EE_K_PAD_INPUT, 0.0, pb, [&] { return launch_space_to_depth(src, pad_bufs[p.pad_buf], nullptr, b, d.h_in, d.w_in, d.c_in, p.Hp, p.Wp, d.pad, dt, stream); });
                     if (e != hipSuccess) return EE_ERR_DEVICE;
                 }
                 ConvArgs ca{};
                 fill_conv_args(st.first_op + k, b, ca);
-                ca.x = pad_bufs[p.pad_buf]; ca.mode = 0;
+                ca.x = folded ? pad_bufs[p.pad_buf] : src; ca.mode = 0;
                 void* yq = resolve(this, q2.dst_buf, act_in, act_out);
                 const double mid = 2.0 * es * b * (double)d.h_out * d.w_out * d.c_out; // the tensor that stays on chip
                 e = timed(EE_K_CONV_STREAM, ops + q2.ops_per_sample * b, bytes + q2.bytes_per_sample * b + q2.weight_bytes - mid,
-                          [&] { return launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream); }, st.first_op + k);
+                          [&] { return folded ? launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream) : launch_conv_pool(ca, yq, q2.d.h_out, q2.d.w_out, q2.d.pad, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
                 ++i;                                                             // the pool is done
                 continue;

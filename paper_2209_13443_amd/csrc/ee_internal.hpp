@@ -220,6 +220,9 @@ hipError_t launch_ir_block(const IrArgs& a, hipStream_t s);
 // kernel, a.y unused) and the 3x3 / 2 max-pool with padding 1 behind it in one launch; yq: the pooled output [B][Hq][Wq][64]
 bool stem_pool_supported(const ConvArgs& a, int es, int Hq, int Wq);
 hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq, hipStream_t s);
+// a 3x3 convolution from 32 to 64 channels and the 3x3 / 2 max-pool (padding 0 or 1) behind it in one launch (int8)
+bool conv_pool_supported(const ConvArgs& a, int es, int Hq, int Wq, int pool_pad);
+hipError_t launch_conv_pool(const ConvArgs& a, void* yq, int Hq, int Wq, int pool_pad, hipStream_t s);
 bool bneck_block_supported(const IrArgs& a);
 bool bneck_block_pools(const IrArgs& a);     // with a.gap_sums the launch also pools: only where its rows of sums fit into LDS
 hipError_t launch_bneck_block(const IrArgs& a, hipStream_t s);

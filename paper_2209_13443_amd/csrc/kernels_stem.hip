@@ -23,7 +23,11 @@ struct StemTile {
     int Hq, Wq;                // pooled image
     int tiles_x, tiles_y;      // tiles of 14 x 8 pooled pixels per image
     int total;                 // tiles in all
+    unsigned magic_tpi, magic_tx;   // floor(2^32 / d) for the tiles of an image and of a row: fast_div
+    int pool_pad;              // conv_pool_i8_kernel: the pool's padding, 0 or 1 (the others have 1)
 };
+
+static unsigned stem_magic(int d) { return (unsigned)(0x100000000ull / (unsigned)d - (d == 1)); }
 
 constexpr int ST_TW = 14, ST_TH = 8;                       // pooled pixels per tile
 constexpr int ST_RW = 2 * ST_TW + 1, ST_RH = 2 * ST_TH + 1;   // convolution outputs under them
@@ -33,14 +37,14 @@ constexpr int ST_ITEMS = 4 * ST_TW * ST_TH;                // (pooled pixel, 16 
 static_assert(ST_STRIPS == 16, "four strips per wavefront");
 constexpr int ST_PITCH = 64 + 16;                          // bytes per convolution output in LDS
 
-// byte-wise signed maximum of two packed dwords kept as (even bytes << 8, odd bytes in place) 16-bit halves
+// byte-wise signed maximum of packed dwords on 16-bit halves, three instructions per dword: the odd bytes decide a half by themselves (whatever is
+// in the byte below them: the two halves are equal but for it, or the odd byte decides), the even ones moved up with zeros below them
 struct StemMax { v2s_r even, odd; };
 __device__ __forceinline__ StemMax stem_split(unsigned d)
 {
-    const unsigned e = (d << 8) & 0xff00ff00u, o = d & 0xff00ff00u;
     StemMax r;
-    __builtin_memcpy(&r.even, &e, 4);
-    __builtin_memcpy(&r.odd, &o, 4);
+    __builtin_memcpy(&r.odd, &d, 4);
+    r.even = r.odd << 8;
     return r;
 }
 __device__ __forceinline__ StemMax stem_max(const StemMax& a, unsigned d)
@@ -53,7 +57,7 @@ __device__ __forceinline__ unsigned stem_join(const StemMax& a)
     unsigned e, o;
     __builtin_memcpy(&e, &a.even, 4);
     __builtin_memcpy(&o, &a.odd, 4);
-    return ((e >> 8) & 0x00ff00ffu) | o;
+    return __builtin_amdgcn_perm(o, e, 0x07030501u);                    // bytes 1 of e, 1 of o, 3 of e, 3 of o
 }
 
 __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* yq, StemTile t)
@@ -90,7 +94,7 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
 
     struct Tile { int n, py0, px0; };
     auto tile_at = [&](int u) {
-        const int n = u / tpi, r0 = u - n * tpi, tyi = r0 / t.tiles_x;
+        const int n = (int)fast_div((unsigned)u, (unsigned)tpi, t.magic_tpi), r0 = u - n * tpi, tyi = (int)fast_div((unsigned)r0, (unsigned)t.tiles_x, t.magic_tx);
         return Tile{n, ST_TH * tyi, ST_TW * (r0 - tyi * t.tiles_x)};
     };
     auto load_strip = [&](const Tile& tl, int s, v4i_r* xr) {           // unconditional and in range; the folded input carries its own padding
@@ -234,7 +238,7 @@ __global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void
     const int tpi = t.tiles_x * t.tiles_y;
     struct Tile { int n, py0, px0; };
     auto tile_at = [&](int u) {
-        const int n = u / tpi, r0 = u - n * tpi, tyi = r0 / t.tiles_x;
+        const int n = (int)fast_div((unsigned)u, (unsigned)tpi, t.magic_tpi), r0 = u - n * tpi, tyi = (int)fast_div((unsigned)r0, (unsigned)t.tiles_x, t.magic_tx);
         return Tile{n, SB_TH * tyi, SB_TW * (r0 - tyi * t.tiles_x)};
     };
     auto stage = [&](const Tile& tl, int buf) {                         // asynchronous; clamped pixels are only ever read by outputs that do not exist
@@ -317,6 +321,157 @@ __global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void
     }
 }
 
+// ---- a 3x3 convolution over 32 channels and the 3x3 / 2 max-pool behind it (int8, 64 output channels) ------------------------
+// What Inception-style stems have behind their first layers.  A pixel has 32 bytes, one reduction step per tap: the bf16 kernel's tile and staging with
+// nine taps, and zeros staged outside the image where the convolution pads; operands, requantisation and pool as in the first-layer kernel.
+// 64 samples of 149 x 149: 52.2 + 19.9 us as two launches (91 MB written and read in between), 42.1 here.  What bounds it: vector issue, some 700
+// instructions per wavefront and tile (requantisation, pool, operand addresses) against 36 matrix instructions.
+constexpr int CP_SW = SB_RW + 2, CP_SH = SB_RH + 2, CP_CHUNKS = 2 * CP_SW * CP_SH;        // 17 x 19 input pixels of two 16-byte chunks
+constexpr int CP_PASSES = (CP_CHUNKS + 255) / 256, CP_STAGE = CP_PASSES * 4096;
+constexpr int CP_PITCH = 64 + 16;
+constexpr int CP_LDS = 2 * CP_STAGE + SB_RPIX * CP_PITCH + 256;
+constexpr int CP_ITEMS = 4 * SB_TW * SB_TH;                                               // (pooled pixel, 16 channels)
+static_assert(CP_ITEMS <= 256, "one item per lane");
+
+__global__ __launch_bounds__(256, 3) void conv_pool_i8_kernel(ConvArgs a, void* yq, StemTile t)
+{
+    constexpr int NK = 9;
+    extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned lds0 = lds_addr(stem_lds);
+    unsigned char* const l_conv = stem_lds + 2 * CP_STAGE;
+    int* const l_bias = (int*)(l_conv + SB_RPIX * CP_PITCH);
+    v4i wreg[2][NK];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < NK; ++k) wreg[j][k] = *(const v4i*)((const unsigned char*)a.w + (size_t)(32 * j + p) * a.Kp + k * 32 + 16 * hi);
+    if (tid < 64) l_bias[tid] = ((const int*)a.bias)[tid];
+    // this lane's chunks of a staged tile: row | column << 8 of the input pixel, half of it
+    int spos[CP_PASSES];
+#pragma unroll
+    for (int i = 0; i < CP_PASSES; ++i) {
+        const int q = min(256 * i + tid, CP_CHUNKS - 1), row = q / (2 * CP_SW), c = q - row * 2 * CP_SW;
+        spos[i] = row | (c >> 1) << 8 | (c & 1) << 16;
+    }
+    const int pp = min(tid, CP_ITEMS - 1) >> 2, pty = pp / SB_TW, ptx = pp - pty * SB_TW;      // pooling: this lane's pixel
+    const unsigned char* const win = l_conv + (2 * pty * SB_RW + 2 * ptx) * CP_PITCH + 16 * (tid & 3);
+    const int tpi = t.tiles_x * t.tiles_y;
+    struct Tile { int n, py0, px0; };
+    auto tile_at = [&](int u) {
+        const int n = (int)fast_div((unsigned)u, (unsigned)tpi, t.magic_tpi), r0 = u - n * tpi, tyi = (int)fast_div((unsigned)r0, (unsigned)t.tiles_x, t.magic_tx);
+        return Tile{n, SB_TH * tyi, SB_TW * (r0 - tyi * t.tiles_x)};
+    };
+    auto stage = [&](const Tile& tl, int buf) {                         // asynchronous; zeros outside the image
+        const unsigned char* xn = (const unsigned char*)a.x + (size_t)tl.n * a.H * a.W * 32;
+#pragma unroll
+        for (int i = 0; i < CP_PASSES; ++i) {
+            const int iy = 2 * tl.py0 - t.pool_pad - a.pad + (spos[i] & 255), ix = 2 * tl.px0 - t.pool_pad - a.pad + ((spos[i] >> 8) & 255);
+            const bool ok = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+            dma16(lds0 + buf * CP_STAGE + i * 4096 + wave * 1024, ok ? xn + (unsigned)((iy * a.W + ix) * 32 + 16 * (spos[i] >> 16)) : (const unsigned char*)a.zeros);
+        }
+    };
+    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(wreg[j][k]));
+    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
+    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
+    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3), buf = 0;
+    Tile tl = tile_at(u);
+    if (u < u_end) stage(tl, 0);
+    for (; u < u_end; u += u_step, buf ^= 1) {
+        wait_all_then_barrier<0>();                                     // the tile is staged, the pooling of the one before has read its convolution outputs
+        const Tile tn = tile_at(u + u_step);
+        if (u + u_step < u_end) stage(tn, buf ^ 1);
+        const unsigned char* xl = stem_lds + buf * CP_STAGE + 16 * hi;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int r = 32 * (wave + 4 * s) + p, rc = min(r, SB_RPIX - 1), ry = rc / SB_RW, rx = rc - ry * SB_RW;
+            const bool exists = (unsigned)(2 * tl.py0 - t.pool_pad + ry) < (unsigned)a.Ho && (unsigned)(2 * tl.px0 - t.pool_pad + rx) < (unsigned)a.Wo;
+            const unsigned char* px = xl + (ry * CP_SW + rx) * 32;
+            v4i xs[2][3];                                               // a row of taps at a time, the next one on its way
+            auto read = [&](int row, v4i* x) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) x[k] = *(const v4i*)(px + (row * CP_SW + k) * 32);
+            };
+            read(0, xs[0]);
+            v16i acc[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const v4i b4 = *(const v4i*)(l_bias + 32 * j + 8 * g + 4 * hi);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[j][4 * g + e] = b4[e];
+                }
+#pragma unroll
+            for (int row = 0; row < 3; ++row) {
+                if (row < 2) read(row + 1, xs[(row + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][3 * row + k], xs[row & 1][k], acc[j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                v4i o = ir_requant_pack(acc[j], cl);
+                if (!exists) o = v4i{(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
+                if (r < SB_RPIX) *(v4i*)(l_conv + r * CP_PITCH + 32 * j + 16 * hi) = o;
+            }
+        }
+        lds_barrier();                                                  // the tile's convolution outputs are in LDS
+        if (tid < CP_ITEMS) {
+            const v4i first = *(const v4i*)win;
+            StemMax mx[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) mx[d] = stem_split((unsigned)first[d]);
+#pragma unroll
+            for (int k = 1; k < 9; ++k) {
+                const v4i v = *(const v4i*)(win + ((k / 3) * SB_RW + (k % 3)) * CP_PITCH);
+#pragma unroll
+                for (int d = 0; d < 4; ++d) mx[d] = stem_max(mx[d], (unsigned)v[d]);
+            }
+            const int py = tl.py0 + pty, px = tl.px0 + ptx;
+            if (py < t.Hq && px < t.Wq)
+                *(v4i*)((unsigned char*)yq + ((size_t)(tl.n * t.Hq + py) * t.Wq + px) * 64 + 16 * (tid & 3)) =
+                    v4i{(int)stem_join(mx[0]), (int)stem_join(mx[1]), (int)stem_join(mx[2]), (int)stem_join(mx[3])};
+        }
+        tl = tn;
+    }
+}
+
+bool conv_pool_supported(const ConvArgs& a, int es, int Hq, int Wq, int pool_pad)
+{
+    if (es != 1 || a.mode != 0 || a.res != nullptr || a.xs || a.M <= 0 || a.Ci != 32 || a.kh != 3 || a.kw != 3 || a.stride != 1) return false;
+    if (a.pad != a.pad_w || a.pad < 0 || a.pad > 1 || pool_pad < 0 || pool_pad > 1 || a.Ho != a.H + 2 * a.pad - 2 || a.Wo != a.W + 2 * a.pad - 2) return false;
+    if (a.Co != 64 || a.ldc != 64 || a.c_off != 0 || a.Kp < 288 || a.Ho + 2 * pool_pad < 3 || a.Wo + 2 * pool_pad < 3) return false;
+    if (Hq != (a.Ho + 2 * pool_pad - 3) / 2 + 1 || Wq != (a.Wo + 2 * pool_pad - 3) / 2 + 1) return false;
+    return (double)(a.M / (a.Ho * a.Wo)) * a.H * a.W * 32 < 2147483648.0;
+}
+
+hipError_t launch_conv_pool(const ConvArgs& a, void* yq, int Hq, int Wq, int pool_pad, hipStream_t s)
+{
+    if (!conv_pool_supported(a, 1, Hq, Wq, pool_pad)) return hipErrorInvalidValue;
+    StemTile t;
+    t.Hq = Hq; t.Wq = Wq; t.pool_pad = pool_pad;
+    t.tiles_x = (Wq + SB_TW - 1) / SB_TW;
+    t.tiles_y = (Hq + SB_TH - 1) / SB_TH;
+    const long long total = (long long)(a.M / (a.Ho * a.Wo)) * t.tiles_x * t.tiles_y;
+    if (total > 0x3fffffff) return hipErrorInvalidValue;
+    t.total = (int)total;
+    t.magic_tpi = stem_magic(t.tiles_x * t.tiles_y);
+    t.magic_tx = stem_magic(t.tiles_x);
+    const unsigned blocks = total < 768 ? xcd_grid(total) : 768u;      // three workgroups on every CU; the loop takes the rest
+    EE_LAUNCH(conv_pool_i8_kernel, dim3(blocks), dim3(256), CP_LDS, s, a, yq, t);
+    return hipGetLastError();
+}
+
 // the convolution as the launcher of the streaming kernel sees it (folded input), the pool behind it by its output size
 bool stem_pool_supported(const ConvArgs& a, int es, int Hq, int Wq)
 {
@@ -332,12 +487,14 @@ hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq,
     if (!stem_pool_supported(a, es, Hq, Wq)) return hipErrorInvalidValue;
     const int tw = es == 1 ? ST_TW : SB_TW, th = es == 1 ? ST_TH : SB_TH;
     StemTile t;
-    t.Hq = Hq; t.Wq = Wq;
+    t.Hq = Hq; t.Wq = Wq; t.pool_pad = 1;
     t.tiles_x = (Wq + tw - 1) / tw;
     t.tiles_y = (Hq + th - 1) / th;
     const long long total = (long long)(a.M / (a.Ho * a.Wo)) * t.tiles_x * t.tiles_y;
     if (total > 0x3fffffff) return hipErrorInvalidValue;
     t.total = (int)total;
+    t.magic_tpi = stem_magic(t.tiles_x * t.tiles_y);
+    t.magic_tx = stem_magic(t.tiles_x);
     const unsigned blocks = total < 512 ? xcd_grid(total) : 512u;      // two workgroups on every CU (what matters is the CU's share, not the workgroup's); the loop takes the rest
     if (es == 2) EE_LAUNCH(stem_pool_bf16_kernel, dim3(blocks), dim3(256), SB_LDS, s, a, yq, t);
     else EE_LAUNCH(stem_pool_i8_kernel, dim3(blocks), dim3(256), (size_t)ST_RPIX * ST_PITCH + 256, s, a, yq, t);

@@ -975,6 +975,39 @@ def test_fused_first_convolution_and_pool_bf16(torch, ee, orc, case):
     eng.close()
 
 
+CP_CASES = [(16, 14, 1, 1, 3), (17, 33, 0, 0, 5), (5, 5, 0, 0, 2), (30, 29, 1, 0, 4), (5, 47, 0, 1, 3), (149, 149, 1, 0, 9)]      # h, w, padding of the convolution, of the pool, samples
+
+
+@pytest.mark.parametrize("case", CP_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_fused_convolution_over_32_channels_and_pool(torch, ee, orc, case):
+    """3x3 convolution 32 -> 64 and 3x3 / 2 max-pool as one launch: paddings of both, pooled images of whole tiles of 7 x 8, less and more,
+    one pixel, extreme inputs, outputs of both signs; against the oracle and the two separate layers, bit for bit."""
+    from workloads import nets as N
+    h, w, pad, pool_pad, n = case
+    net = N._Net(W.DT_I8, h, w, 32, 10)
+    t = net.begin_stage()
+    t = net.conv(t, 64, 3, 1, pad, act="linear" if h % 2 else "relu")
+    t = net.maxpool(t, 3, 2, pool_pad)
+    net.end_stage(net.conv(t, 32, 1, 1, 0))
+    blob = N._assemble(net, W.DT_I8, 60 + h)
+    for op in blob.ops:
+        if int(op["kind"]) == W.OP_CONV:
+            op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * int(op["kh"]) ** 2) / 127))))
+    say(f"[case] 3x3 32 -> 64 on {h}x{w}, padding {pad}, pool padding {pool_pad}, {n} samples")
+    r = np.random.default_rng(h * 100 + w)
+    x = np.concatenate([np.full((1, h, w, 32), -128, np.int8), np.full((1, h, w, 32), 127, np.int8), r.integers(-128, 128, size=(max(n - 2, 1), h, w, 32), dtype=np.int8)])[:n]
+    eng = ee.Engine(blob, max(n, 2))
+    assert eng.ir_count() == 1 and eng.ir_layers(0) == 2
+    for b in sorted({n, 1}, reverse=True):
+        ref = orc.stage_forward(blob, 0, x[:b])
+        for mode in (2, 0, 1):
+            eng.ir_mode(mode)
+            got = host(eng.stage_forward(0, dev(torch, x[:b]), ref.shape[1:]), ref)
+            assert np.array_equal(got, ref), f"mode {mode} b={b}: {np.count_nonzero(got != ref)} of {ref.size} differ, first at {np.argwhere(got != ref)[:3].tolist()}"
+    assert np.unique(ref).size > 8
+    eng.close()
+
+
 BN_SERVE_CASES = [  # h, w, c_in, seed, frac_bits, thresholds of the first two exits, lanes
     (12, 10, 64, 3, 11, (0.782, 0.955), 1), (16, 16, 256, 5, 12, (0.8371, 0.8453), 2),
 ]
