@@ -916,11 +916,17 @@ hipError_t ee_ctx::launch_conv(int op, int b, const void* src, void* dst, const 
         return dt == EE_I8 ? launch_conv_mfma_i8(a, stream) : launch_conv_mfma_bf16(a, stream);
     }
     a.x = src; a.mode = 0;
+    a.xs = xs; a.ys = ys;
+    a.gap_sums = gap_sums;
+    if (cfg == 0) cfg = conv_taps_default(a, dt == EE_I8 ? 1 : 2);
     if (cfg == 0) cfg = conv_skinny_default(a, dt == EE_I8 ? 1 : 2);
-    if (xs || ys || gap_sums) {                          // slot tables, fused pooling: the general kernel and the one for few pixels
+    if (xs || ys || gap_sums) {                          // slot tables, fused pooling: the kernels that have them
         if (p.impl != IMPL_MFMA || ((xs || ys) && b > EE_ZC_MAX_B)) return hipErrorInvalidValue;
-        a.xs = xs; a.ys = ys;
-        a.gap_sums = gap_sums;
+        if (cfg_is_taps(cfg)) {
+            const hipError_t e = dt == EE_I8 ? launch_conv_taps<1>(a, cfg, stream) : launch_conv_taps<2>(a, cfg, stream);
+            if (e != hipErrorInvalidValue) return e;     // else: not of its kind (input slots), or a tile that does not fit with the pooling's sums
+            cfg = 0;
+        }
         if (cfg == 0) cfg = conv_rows_default(a, dt == EE_I8 ? 1 : 2);
         if (cfg_is_skinny(cfg)) return dt == EE_I8 ? launch_conv_skinny<1>(a, cfg, stream) : launch_conv_skinny<2>(a, cfg, stream);
         if (cfg_is_rows(cfg) && conv_rows_supported(a, dt == EE_I8 ? 1 : 2)) return dt == EE_I8 ? launch_conv_rows<1>(a, cfg, stream) : launch_conv_rows<2>(a, cfg, stream);
@@ -931,6 +937,11 @@ hipError_t ee_ctx::launch_conv(int op, int b, const void* src, void* dst, const 
     if (cfg == 0) cfg = conv_rows_default(a, dt == EE_I8 ? 1 : 2);
     if (cfg_is_rows(cfg)) {
         const hipError_t e = dt == EE_I8 ? launch_conv_rows<1>(a, cfg, stream) : launch_conv_rows<2>(a, cfg, stream);
+        if (e != hipErrorInvalidValue || forced_conv_tile() != cfg) return e;
+        cfg = 0;                                         // forced for the whole process: layers it does not cover keep the default
+    }
+    if (cfg_is_taps(cfg)) {
+        const hipError_t e = dt == EE_I8 ? launch_conv_taps<1>(a, cfg, stream) : launch_conv_taps<2>(a, cfg, stream);
         if (e != hipErrorInvalidValue || forced_conv_tile() != cfg) return e;
         cfg = 0;                                         // forced for the whole process: layers it does not cover keep the default
     }
@@ -1190,7 +1201,9 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 // not for the layer that carries the exit head's pooling when it serves: that launch needs another kernel
                 if (p.impl == IMPL_MFMA && conv_rows_supported(probe, es) && st.first_op + k != ctx->gap_fuse_op[s])
                     for (const int cfg : {EE_CFG_ROWS32, EE_CFG_ROWS64}) cands.push_back(cfg);
-                if (p.impl == IMPL_MFMA && conv_slab_supported(probe, es))
+                if (p.impl == IMPL_MFMA && conv_taps_supported(probe, es))
+                    for (const int cfg : TAPS_CFGS) cands.push_back(cfg);
+                if (p.impl == IMPL_MFMA && conv_slab_supported(probe, es) && !conv_taps_default(probe, es))      // never the faster one there
                     staged(kbytes, [&](int cfg) { if ((cfg >> 4 & 15) > 1) cands.push_back(EE_CFG_SLAB | cfg); });
                 if ((long long)buckets[bi] * d.h_out * d.w_out <= EE_SKINNY_MAX_ROWS)          // few pixels: the kernel that splits the reduction over its wavefronts
                     for (int shape = 0; shape < 3; ++shape)                                     // 32 pixels x 32 or 64 channels, 16 x 16

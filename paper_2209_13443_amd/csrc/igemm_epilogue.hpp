@@ -69,6 +69,48 @@ __device__ __forceinline__ void igemm_init_acc(ACC& acc, const unsigned char* ld
         }
 }
 
+// Exit-head pooling of a finished int8 tile in LDS (rows of OutTile): per-sample column sums into gacc[GAP_S][BN] (zeroed, in LDS) ...
+constexpr int GAP_S = 8;                                      // samples a tile may touch (the launchers check (BM - 1) / HW + 2 <= GAP_S)
+template <int ES, int BM, int BN, int NT>
+__device__ __forceinline__ void gap_tile_sums(const ConvArgs& a, const unsigned char* ro, int* gacc, int m0, int tid)
+{
+    constexpr int CG = BN / 4, NRG = NT / CG, RG = (BM + NRG - 1) / NRG;     // dword columns, row groups, rows per group
+    const int cg = tid % CG, rg = tid / CG;
+    const unsigned hw = (unsigned)(a.Ho * a.Wo);
+    const int nfirst = (int)fast_div((unsigned)min(m0, a.M - 1), hw, a.magic_howo);
+    int cur = -1, s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+    auto flush = [&]() {
+        if (cur < 0) return;
+        int* g = gacc + (cur - nfirst) * BN + cg * 4;
+        atomicAdd(g, s0); atomicAdd(g + 1, s1); atomicAdd(g + 2, s2); atomicAdd(g + 3, s3);
+    };
+    for (int r = 0; r < RG; ++r) {
+        const int row = rg * RG + r, m = m0 + row;
+        if (row >= BM || m >= a.M) break;
+        const int n = (int)fast_div((unsigned)m, hw, a.magic_howo);
+        if (n != cur) { flush(); cur = n; s0 = s1 = s2 = s3 = 0; }
+        const int v = *(const int*)(ro + row * OutTile<ES, BN>::OROW + ((((cg * 4) >> 4) ^ OutTile<ES, BN>::oswz(row)) << 4) + ((cg * 4) & 15));
+        s0 += __builtin_amdgcn_sbfe(v, 0, 8); s1 += __builtin_amdgcn_sbfe(v, 8, 8);
+        s2 += __builtin_amdgcn_sbfe(v, 16, 8); s3 += __builtin_amdgcn_sbfe(v, 24, 8);
+    }
+    flush();
+}
+
+// ... and, behind a barrier, one global atomic per (sample, channel) of the tile into sums[n][Co].  int32 addition is exact in any order, so the sums
+// are those of the pooling kernel.
+template <int BM, int BN, int NT>
+__device__ __forceinline__ void gap_tile_flush(const ConvArgs& a, const int* gacc, int m0, int n0, int tid)
+{
+    const unsigned hw = (unsigned)(a.Ho * a.Wo);
+    const int mlast = min(m0 + BM, a.M) - 1;
+    const int nfirst = (int)fast_div((unsigned)min(m0, a.M - 1), hw, a.magic_howo), nlast = (int)fast_div((unsigned)mlast, hw, a.magic_howo);
+    const int cnt = (nlast - nfirst + 1) * BN;
+    for (int i = tid; i < cnt; i += NT) {
+        const int sl = i / BN, c = i - sl * BN;
+        if (n0 + c < a.Co) atomicAdd(a.gap_sums + (long long)(nfirst + sl) * a.Co + n0 + c, gacc[i]);
+    }
+}
+
 // Bias, residual, requantisation / clamp and packing in the accumulator layout, the tile through LDS (at ro_off; with a
 // staged residual tile the results replace it in place), then 16-byte stores along the channels.  Every wavefront of the
 // workgroup calls it (it contains a barrier); `active` says whether this wavefront holds accumulators to write.
@@ -86,10 +128,7 @@ __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsi
     unsigned char* ro = lds + ro_off;
     const int* lbias = (const int*)(lds + bias_off);
     // Exit-head pooling fused into the segment's last layer (int8, a.gap_sums set by the launcher only for a layer with a
-    // staged residual tile, so that the ring in front of the tile is free now): per-sample column sums of the finished
-    // tile are added up in LDS, then one global atomic per (sample, channel) of the tile goes into sums[n][Co].  int32
-    // addition is exact in any order, so the sums are those of the pooling kernel.
-    constexpr int GAP_S = 8;                                  // samples a tile may touch (the launcher checks (BM - 1) / HW + 2 <= GAP_S)
+    // staged residual tile, so that the ring in front of the tile is free now)
     int* gacc = (int*)lds;                                    // [GAP_S][BN]
     const bool fuse_gap = ES == 1 && a.gap_sums != nullptr && wide && has_res && ro_off >= GAP_S * BN * 4;
     if (fuse_gap)
@@ -184,26 +223,7 @@ __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsi
     if (wide) {
         lds_barrier();
         if (fuse_gap) {
-            constexpr int CG = BN / 4, NRG = NT / CG, RG = (BM + NRG - 1) / NRG;     // dword columns, row groups, rows per group
-            const int cg = tid % CG, rg = tid / CG;
-            const unsigned hw = (unsigned)(a.Ho * a.Wo);
-            const int nfirst = (int)fast_div((unsigned)min(m0, a.M - 1), hw, a.magic_howo);
-            int cur = -1, s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-            auto flush = [&]() {
-                if (cur < 0) return;
-                int* g = gacc + (cur - nfirst) * BN + cg * 4;
-                atomicAdd(g, s0); atomicAdd(g + 1, s1); atomicAdd(g + 2, s2); atomicAdd(g + 3, s3);
-            };
-            for (int r = 0; r < RG; ++r) {
-                const int row = rg * RG + r, m = m0 + row;
-                if (row >= BM || m >= a.M) break;
-                const int n = (int)fast_div((unsigned)m, hw, a.magic_howo);
-                if (n != cur) { flush(); cur = n; s0 = s1 = s2 = s3 = 0; }
-                const int v = *(const int*)(ro + row * OROW + ((((cg * 4) >> 4) ^ oswz(row)) << 4) + ((cg * 4) & 15));
-                s0 += __builtin_amdgcn_sbfe(v, 0, 8); s1 += __builtin_amdgcn_sbfe(v, 8, 8);
-                s2 += __builtin_amdgcn_sbfe(v, 16, 8); s3 += __builtin_amdgcn_sbfe(v, 24, 8);
-            }
-            flush();
+            gap_tile_sums<ES, BM, BN, NT>(a, ro, gacc, m0, tid);
         }
 #pragma unroll
         for (int j = 0; j < NO; ++j) {
@@ -213,14 +233,7 @@ __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsi
         }
         if (fuse_gap) {
             lds_barrier();
-            const unsigned hw = (unsigned)(a.Ho * a.Wo);
-            const int mlast = min(m0 + BM, a.M) - 1;
-            const int nfirst = (int)fast_div((unsigned)min(m0, a.M - 1), hw, a.magic_howo), nlast = (int)fast_div((unsigned)mlast, hw, a.magic_howo);
-            const int cnt = (nlast - nfirst + 1) * BN;
-            for (int i = tid; i < cnt; i += NT) {
-                const int sl = i / BN, c = i - sl * BN;
-                if (n0 + c < a.Co) atomicAdd(a.gap_sums + (long long)(nfirst + sl) * a.Co + n0 + c, gacc[i]);
-            }
+            gap_tile_flush<BM, BN, NT>(a, gacc, m0, n0, tid);
         }
     }
 }

@@ -1,0 +1,370 @@
+// Stride-1 "same" convolutions over pixels of whole 128-byte runs on the matrix cores, the activations of a tile resident in LDS and the weights
+// streamed from global memory straight into registers: no barrier and no copy between the first matrix instruction and the last.
+//
+// Output row m and input pixel m coincide (kernels_slab.hip), so the input rows of a tile are one contiguous run, copied to LDS once and read at shifted
+// addresses by every tap.  What bounds the staged kernels on these layers is the path that fills LDS (64 bytes/clk and CU; 128 x 128 tiles in 128-byte steps
+// need 1.2 times the matrix time for it, smaller tiles more) and a barrier per step.  Here a wavefront owns 32 output channels and multiplies them with every
+// pixel of the tile: its weights are one contiguous KiB per 32 bytes of the reduction (ConvArgs::wo), loaded 8 steps ahead into registers and used for 2 to 7
+// matrix instructions; the activations are the only LDS traffic, one 1 KiB read per matrix instruction, 128 bytes/clk of about 190; and nothing makes
+// wavefronts wait for one another.  Slab rows are padded by 16 bytes, an odd number of chunks, which spreads 16 rows over all banks and makes the position inside a
+// pixel a compile-time offset of the read.  Taps outside the image read a row of zeros.
+// Four wavefronts (128 channels) per workgroup, two or three of which share a CU; eight (256 channels) where the slab fills it.  Where the tiles are few (at most
+// one or two workgroups per CU) the reduction itself is the chain: 2 or 4 wavefronts share it, a slice of (r, s, c) each, and add up through LDS.  With one
+// wavefront per block of channels the sums run in the order of the staged kernel, so bf16 results are the same bits.
+// Writes slots and pools for the exit head; does not read slots.
+// Measured, best configuration of the other kernels -> this one, 3x3, us:
+//   256 samples: bf16 28x28, 128 -> 128 71.1 -> 45.8, 14x14, 256 -> 256 66.9 -> 43.6 (1.36 PFLOP/s, the rate of a large matrix product here), 7x7, 512 -> 512
+//     63.1 -> 47.1; int8 35.1 -> 28.7, 31.2 -> 26.2, 33.4 -> 27.2
+//   64 samples: bf16 21.0 -> 17.2, 20.1 -> 16.9, 25.2 -> 17.2; int8 11.9 -> 11.6, 11.1 -> 10.6, 13.8 -> 10.4
+//   int8, residual, 32 samples: 28x28, 128 -> 128 8.8 -> 7.9, 14x14, 256 -> 256 9.0 -> 7.4, 7x7, 512 -> 512 11.7 -> 7.5
+#include <algorithm>
+#include <type_traits>
+
+#include "ee_internal.hpp"
+#include "igemm_device.hpp"
+#include "igemm_epilogue.hpp"
+#include "ir_device.hpp"
+
+namespace ee {
+
+constexpr unsigned taps_part_bytes(int tm, int nw, int kp) { return kp == 1 ? 0 : (unsigned)((tm < kp ? tm : kp) * (kp - 1) * nw * ((tm + kp - 1) / kp) * 4096); }
+
+// ES: element bytes; TM: blocks of 32 pixels of a tile, all of them multiplied by every wavefront; NW: blocks of 32 output channels; KP: wavefronts that
+// share the reduction of a block of channels
+template <int ES, int TM, int NW, int KP>
+__global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, unsigned magic_p, unsigned slab_bytes, unsigned gap_off)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr int BM = 32 * TM, BN = 32 * NW, NT = 64 * NW * KP;
+    using T = OutTile<ES, BN>;
+    constexpr int OROW = T::OROW, CR = T::CR, NO = (BM * CR + NT - 1) / NT;    // output tile: bytes and chunks per row, chunks per lane
+    constexpr int U = 4, WR = 2 * U;                                    // steps (32 bytes of the reduction) per group, weight operands in flight
+    constexpr int FD = TM >= 4 ? 1 : 3, NS = TM >= 4 ? 2 : 4;                    // activation operands are read FD steps ahead into NS register sets used in turn
+    constexpr unsigned PART_BYTES = taps_part_bytes(TM, NW, KP);        // partial sums, over the slab
+    constexpr int OWN = (TM + KP - 1) / KP;                             // blocks of pixels a wavefront finishes: wavefront `part` those with i % KP == part
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    using acc_t = typename std::conditional<ES == 1, v16i, v16f>::type;
+    preload(a);
+    const int xcd = blockIdx.x & 7, wslot = blockIdx.x >> 3;
+    const int mslot = (int)fast_div((unsigned)wslot, (unsigned)gn, magic_gn);
+    const int mt = xcd_unit((unsigned)(mslot << 3 | xcd), gm), nt = wslot - mslot * gn;
+    if (mt < 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, frow = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = mt * BM, n0 = nt * BN;
+    const int CiB = a.Ci * ES, pitch = CiB + 16, P = pitch >> 4;        // an odd number of chunks per slab row spreads 16 rows over all banks
+    const unsigned lds0 = lds_addr(lds);
+    const bool has_res = a.res != nullptr;
+
+    // ---- weights of the first steps ------------------------------------------------------------------------------
+    const int steps = a.kh * a.kw * (CiB >> 5), groups = steps / U;
+    const int part = wave / NW, wn = wave % NW;                         // this wavefront's share of the reduction, its block of channels
+    const int g0 = KP == 1 ? 0 : groups * part / KP, g1 = KP == 1 ? groups : groups * (part + 1) / KP;
+    const int co_blocks = (a.Co + 127) / 128 * 4, cb = min(n0 / 32 + wn, co_blocks - 1);
+    const unsigned char* const wbase = (const unsigned char*)a.wo + (size_t)cb * (size_t)(a.Kp * ES / 32) * 1024;
+    auto weight = [&](int s) { return *(const v4i*)(wbase + (size_t)(unsigned)min(s, steps - 1) * 1024 + lane * 16); };
+    v4i wr[WR];
+#pragma unroll
+    for (int s = 0; s < WR; ++s) wr[s] = weight(g0 * U + s);
+
+    // ---- LDS: zeros for the taps outside the image | slab rows of P chunks | residual tile.  The slab is input rows m0 - halo_lo .. m0 + BM + halo_hi - 1,
+    // clamped into the tensor (a clamped row is only ever the source of taps that the validity mask rejects)
+    const int halo_lo = a.pad * a.W + a.pad_w;
+    const unsigned ro_off = has_res ? max((unsigned)CiB + slab_bytes, PART_BYTES) : PART_BYTES;
+    for (unsigned q = tid; q < slab_bytes / 16; q += NT) {
+        const unsigned row = fast_div(q, (unsigned)P, magic_p), pos = q - row * (unsigned)P;
+        const int g = clamp_i32(m0 - halo_lo + (int)row, 0, a.M - 1);
+        dma16(lds0 + (unsigned)CiB + __builtin_amdgcn_readfirstlane(q) * 16u, a.x, __umul24((unsigned)g, (unsigned)CiB) + (pos == (unsigned)P - 1 ? 0u : pos * 16u));
+    }
+    if (has_res)
+#pragma unroll
+        for (int j = 0; j < NO; ++j) {
+            const int q = tid + NT * j, row = q / CR, chunk = (q % CR) ^ T::oswz(row);
+            const int m = min(m0 + row, a.M - 1), ch = n0 + chunk * (16 / ES);
+            if (NT * j + 64 * wave < BM * CR)                           // wave-uniform
+                dma16(lds0 + ro_off + (unsigned)(NT * j + 64 * wave) * 16u, (const unsigned char*)a.res + ((size_t)(unsigned)m * a.Co + (ch < a.Co ? ch : 0)) * ES);
+        }
+    for (int i = tid; i < CiB / 16; i += NT) *(v4i*)(lds + i * 16) = v4i{0, 0, 0, 0};
+
+    // ---- operand addresses: bit t of vmask[i] says whether tap t of the lane's pixel of block i lies inside the image ------------------
+    unsigned vmask[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        int m = m0 + 32 * i + frow;
+        const bool live = m < a.M;
+        m = live ? m : a.M - 1;
+        const unsigned n = fast_div((unsigned)m, (unsigned)(a.Ho * a.Wo), a.magic_howo), rem = (unsigned)m - n * (unsigned)(a.Ho * a.Wo);
+        const unsigned oy = fast_div(rem, (unsigned)a.Wo, a.magic_wo), ox = rem - oy * a.Wo;
+        const int iy0 = (int)oy - a.pad, ix0 = (int)ox - a.pad_w;
+        const int s_lo = max(0, -ix0), s_hi = min(a.kw, a.W - ix0), r_lo = max(0, -iy0), r_hi = min(a.kh, a.H - iy0);
+        const unsigned colmask = s_hi > s_lo ? ((1u << s_hi) - 1u) & ~((1u << s_lo) - 1u) : 0u;
+        const unsigned rowsel = r_hi > r_lo ? a.tap_rows & ((1u << (r_hi * a.kw)) - 1u) & ~((1u << (r_lo * a.kw)) - 1u) : 0u;
+        vmask[i] = live ? colmask * rowsel : 0u;
+    }
+    int r_tap = 0, r_ts = 0, r_row = 0, r_cb = 0;                       // the reader's tap, its column, the slab row of the tile's first pixel under it, bytes inside the pixel
+    const unsigned lane_off = (unsigned)(frow * pitch + hi * 16);
+    unsigned pa[TM];
+    auto set_tap = [&]() {
+        const unsigned at = (unsigned)CiB + (unsigned)(r_row * pitch) + lane_off;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) pa[i] = (vmask[i] >> r_tap) & 1u ? at + (unsigned)(32 * i * pitch) : (unsigned)(hi * 16);
+    };
+    auto advance = [&]() {                                              // one group further along (r, s, c); behind the last tap every lane reads zeros
+        r_cb += 32 * U;
+        if (r_cb == CiB) {
+            r_cb = 0;
+            ++r_tap;
+            ++r_row;
+            if (++r_ts == a.kw) { r_ts = 0; r_row += a.W - a.kw; }
+            set_tap();
+        } else
+#pragma unroll
+            for (int i = 0; i < TM; ++i) pa[i] += 32 * U;
+    };
+    if (KP > 1 && part > 0) {
+        r_tap = g0 * (32 * U) / CiB;
+        r_cb = g0 * (32 * U) - r_tap * CiB;
+        r_row = r_tap / a.kw * a.W;
+        r_ts = r_tap % a.kw;
+        r_row += r_ts;
+    }
+    set_tap();
+    if (KP > 1 && r_cb)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) pa[i] += (unsigned)r_cb;
+
+    acc_t acc[TM];
+    {
+        v4i bias[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bias[q] = ES == 1 && part == 0 ? *(const v4i*)((const int*)a.bias + cb * 32 + 8 * q + 4 * hi) : v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                if constexpr (ES == 1) acc[i][e] = bias[e >> 2][e & 3];
+                else acc[i][e] = 0.f;
+            }
+    }
+    wait_all_then_barrier<0>();                                         // slab, zeros and residual tile are there
+
+    // ---- main loop -------------------------------------------------------------------------------------------------
+    v4i gx[NS][TM];
+#pragma unroll
+    for (int u = 0; u < FD; ++u)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) gx[u][i] = *(const v4i*)(lds + pa[i] + u * 32);
+    // every matrix instruction is followed by one operand read of a later step, every step by one load of weights WR steps ahead
+    auto group = [&](auto half_tag, int g) {
+        constexpr int HALF = decltype(half_tag)::value;
+        static_for<U>([&](auto u_tag) {
+            constexpr int S = decltype(u_tag)::value, R = S + FD;
+            if constexpr (R == U) advance();
+            static_for<TM>([&](auto i_tag) {
+                constexpr int I = decltype(i_tag)::value;
+                if constexpr (ES == 1) acc[I] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[HALF * U + S], gx[S % NS][I], acc[I], 0, 0, 0);
+                else acc[I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, wr[HALF * U + S]), __builtin_bit_cast(v8bf, gx[S % NS][I]), acc[I], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                gx[R % NS][I] = *(const v4i*)(lds + pa[I] + (R % U) * 32);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            wr[HALF * U + S] = weight(g * U + S + WR);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    int g = g0;
+    for (; g + 1 < g1; g += 2) {
+        group(std::integral_constant<int, 0>{}, g);
+        group(std::integral_constant<int, 1>{}, g + 1);
+    }
+    if (g < g1) group(std::integral_constant<int, 0>{}, g);
+
+    // ---- results: through LDS (rows of OutTile, over the residual if there is one), then whole chunks ----
+    v4i bias[4];
+    if constexpr (ES == 2)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bias[q] = *(const v4i*)((const int*)a.bias + cb * 32 + 8 * q + 4 * hi);
+    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    lds_barrier();                                                      // every wavefront is done with the slab
+    if constexpr (KP > 1) {                                             // the other wavefronts' sums of a block, through LDS, to the one that finishes it
+        v4i* const l_part = (v4i*)lds;                                  // [part that finishes][other part][block of channels][block of its own][quad][lane]
+        auto cell = [&](int to, int from, int i, int q) { return l_part + (((((to * (KP - 1) + (from > to ? from - 1 : from)) * NW + wn) * OWN + i) * 4 + q) << 6) + lane; };
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            if (i % KP != part)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    typename std::conditional<ES == 1, v4i, v4f>::type v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = acc[i][4 * q + e];
+                    *cell(i % KP, part, i / KP, q) = __builtin_bit_cast(v4i, v);
+                }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            if (i % KP == part)
+#pragma unroll
+                for (int o = 0; o < KP; ++o)
+                    if (o != part)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const auto v = __builtin_bit_cast(typename std::conditional<ES == 1, v4i, v4f>::type, *cell(i % KP, o, i / KP, q));
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[i][4 * q + e] += v[e];
+                        }
+    }
+    auto finish = [&](auto res_tag) {
+        constexpr bool RES = decltype(res_tag)::value;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            if (KP > 1 && i % KP != part) continue;
+            unsigned char* orow = lds + ro_off + (32 * i + frow) * OROW;
+            if constexpr (ES == 1) {
+                unsigned char* cell = orow + (((2 * wn + hi) ^ T::oswz(frow)) << 4);
+                if constexpr (RES) {
+                    const v4i rv = *(const v4i*)cell;
+                    const auto s02 = __builtin_amdgcn_permlane32_swap((unsigned)rv[0], (unsigned)rv[1], false, false);
+                    const auto s13 = __builtin_amdgcn_permlane32_swap((unsigned)rv[2], (unsigned)rv[3], false, false);
+                    const unsigned rq[4] = {s02[0], s13[0], s02[1], s13[1]};             // the accumulator layout's quads
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << a.res_shift;
+                }
+                *(v4i*)cell = ir_requant_pack<!RES && KP == 1>(acc[i], cl);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    unsigned char* cell = orow + (((4 * wn + q) ^ T::oswz(frow)) << 4) + 8 * hi;
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = acc[i][4 * q + e] + __int_as_float(bias[q][e]);
+                    if constexpr (RES) {
+                        const uint2 r = *(const uint2*)cell;
+                        v[0] += __uint_as_float(r.x << 16); v[1] += __uint_as_float(r.x & 0xFFFF0000u);
+                        v[2] += __uint_as_float(r.y << 16); v[3] += __uint_as_float(r.y & 0xFFFF0000u);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = clamp_f32(v[e], a.f_lo, a.f_hi);
+                    *(uint2*)cell = uint2{pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+                }
+            }
+        }
+    };
+    if (has_res) finish(std::true_type{});
+    else finish(std::false_type{});
+    int* const gacc = (int*)(lds + gap_off);
+    const bool pool = ES == 1 && a.gap_sums != nullptr;
+    if (pool)
+        for (int i = tid; i < GAP_S * BN; i += NT) gacc[i] = 0;
+    lds_barrier();
+    if (pool) gap_tile_sums<ES, BM, BN, NT>(a, lds + ro_off, gacc, m0, tid);
+    auto out_row = [&](int m) -> long long {                            // zero-copy compaction: sample n of the output goes to slot ys[n] of y
+        if (!a.ys || m >= a.M) return m;
+        const unsigned howo = (unsigned)(a.Ho * a.Wo), n = fast_div((unsigned)m, howo, a.magic_howo);
+        return (long long)a.ys[n] * howo + ((unsigned)m - n * howo);
+    };
+#pragma unroll
+    for (int j = 0; j < NO; ++j) {
+        const int q = tid + NT * j, row = q / CR, chunk = (q % CR) ^ T::oswz(row);
+        const int m = m0 + row, ch = n0 + chunk * (16 / ES);
+        if (q < BM * CR && m < a.M && ch < a.Co) *(v4i*)((unsigned char*)a.y + ((size_t)out_row(m) * a.ldc + a.c_off + ch) * ES) = *(const v4i*)(lds + ro_off + q * 16);
+    }
+    if (pool) {
+        lds_barrier();
+        gap_tile_flush<BM, BN, NT>(a, gacc, m0, n0, tid);
+    }
+}
+
+// Stride 1, output as large as the input, 2 .. 31 taps, a pixel of whole 128-byte runs (a group of steps never straddles two taps), whole
+// 16-byte chunks in the output, a tensor below 2 GiB (so that row numbers stay below 2^24, as the address arithmetic assumes)
+bool conv_taps_supported(const ConvArgs& a, int es)
+{
+    const int cib = a.Ci * es;
+    if (a.xs || a.mode != 0 || !a.wo || a.stride != 1 || a.Ho != a.H || a.Wo != a.W) return false;
+    if (cib % 128 != 0 || cib > 2048 || a.kh * a.kw > 31 || a.kh * a.kw < 2) return false;
+    if (a.H + 2 * a.pad - a.kh + 1 != a.Ho || a.W + 2 * a.pad_w - a.kw + 1 != a.Wo) return false;
+    if ((a.Co * es) % 16 != 0 || (a.ldc * es) % 16 != 0 || (a.c_off * es) % 16 != 0) return false;
+    return (long long)a.M * cib < (1ll << 31);
+}
+
+struct TapsLds { unsigned slab, gap_off; size_t bytes; };
+static TapsLds taps_lds(const ConvArgs& a, int es, int tm, int nw, int kp)
+{
+    const int cib = a.Ci * es, nt = 64 * nw * kp;
+    const long long chunks = (32 * tm + (a.kh - 1) * (long long)a.W + (a.kw - 1)) * (cib / 16 + 1);
+    TapsLds l;
+    l.slab = (unsigned)((chunks + nt - 1) / nt * nt * 16);
+    const size_t parts = taps_part_bytes(tm, nw, kp), tile = (size_t)(32 * tm) * (32 * nw) * es, front = std::max((size_t)cib + l.slab, parts);
+    l.bytes = a.res ? front + tile : std::max(front, parts + tile);
+    l.gap_off = (unsigned)l.bytes;
+    if (a.gap_sums) l.bytes += (size_t)GAP_S * 32 * nw * 4;
+    return l;
+}
+
+// Untuned: the configuration of a layer this kernel is the faster one for, else 0.  Measured over the layers of the ResNet-50, ResNet-18 and Inception-style
+// networks at 1-256 samples; blocks are 64 x 64 tiles of the output.
+//   Few pixels, int8: up to 53 blocks (100 for reductions below 2 KiB) the few-pixel kernel is level or the faster one (7x7, 512 -> 512, 4 samples 7.2 against 7.1 us
+//     here, 17x17, 1x7, 128 -> 128, 8 samples 4.0 / 4.9; from 8 samples 9.0 / 7.3, 14x14, 256 -> 256, 5 samples 6.6 / 5.9).  Up to 256 blocks four wavefronts share
+//     the reduction of a 64 x 64 tile (7x7, 512 -> 512, 32 samples 7.5 us, 10.1 with two sharing, 11.0 with none), up to 512 two that of a 64 x 128 tile if it is
+//     long (14x14, 256 -> 256, 32 samples 7.2, 7.7 with none sharing, 8.1 with four; 28x28, 128 -> 128, 16 samples 6.0, 5.9 with none).
+//   bf16 does not share: one order of summation.  From 32 blocks on level (18.5 / 18.9 us at 32, 10.9 / 11.5 at 64), faster with more.
+//   Otherwise the tile with the least work on the busiest CU: its workgroups times (blocks of 32 pixels + 1 for start and end), three tenths more where four wavefronts
+//     have a CU to themselves.  Over 27 layers and sizes the choice is the fastest configuration or within 3 % of it but once (7 %).
+//   Channels that leave half of a 128-channel tile empty: a third slower at 64 (bf16 56x56, 64 -> 64 94 us against 72), at 192 level at 867 blocks (8.2 us both),
+//     14.5 / 12.0 at 1734.  Reductions below 896 bytes were not measured.
+int conv_taps_default(const ConvArgs& a, int es)
+{
+    const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64), kbytes = (long long)a.kh * a.kw * a.Ci * es;
+    if (blocks < (es == 2 ? 32 : kbytes < 2048 ? 101 : 54) || kbytes < 896 || !conv_taps_supported(a, es)) return 0;
+    if ((a.Co + 127) / 128 * 128 - a.Co >= 64 && (es == 2 || a.Co <= 64 || blocks < 1024)) return 0;
+    auto fits = [&](int tm, int nw, int kp) { return taps_lds(a, es, tm, nw, kp).bytes <= 160 * 1024 && (!a.gap_sums || (32 * tm - 1) / (a.Ho * a.Wo) + 2 <= GAP_S); };
+    if (es == 1 && blocks <= 256 && fits(2, 2, 4)) return taps_cfg(2, 2, 4);
+    if (es == 1 && blocks <= 512 && kbytes >= 2048 && fits(2, 4, 2)) return taps_cfg(2, 4, 2);
+    int best = 0;
+    long long least = 0;
+    auto weigh = [&](int tm, int nw) {
+        if (!fits(tm, nw, 1)) return;
+        const long long wgs = ((a.M + 32 * tm - 1) / (32 * tm)) * (long long)((a.Co + 32 * nw - 1) / (32 * nw)), rounds = (wgs + 255) / 256;
+        const bool alone = nw == 4 && (wgs <= 256 || taps_lds(a, es, tm, nw, 1).bytes > 80 * 1024);
+        const long long cost = rounds * (tm + 1) * (nw / 4) * (alone ? 13 : 10);
+        if (!best || cost < least) { best = taps_cfg(tm, nw, 1); least = cost; }
+    };
+    for (const int tm : {2, 3, 4, 5, 7}) weigh(tm, 4);
+    if (a.Co % 256 == 0)
+        for (const int tm : {4, 7}) weigh(tm, 8);
+    return best;
+}
+
+template <int ES, int TM, int NW, int KP>
+static hipError_t launch_taps_shape(const ConvArgs& a, hipStream_t s)
+{
+    constexpr int BM = 32 * TM, BN = 32 * NW;
+    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, p = a.Ci * ES / 16 + 1;
+    const TapsLds l = taps_lds(a, ES, TM, NW, KP);
+    if (l.bytes > 160 * 1024 || (a.gap_sums && (ES != 1 || (BM - 1) / (a.Ho * a.Wo) + 2 > GAP_S))) return hipErrorInvalidValue;
+    static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_taps_kernel<ES, TM, NW, KP>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (granted != hipSuccess) return granted;
+    const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1)), magic_p = (unsigned)(0x100000000ull / (unsigned)p);
+    EE_LAUNCH((conv_taps_kernel<ES, TM, NW, KP>), dim3(xcd_grid(gm) * (unsigned)gn), dim3(64 * NW * KP), l.bytes, s, a, gm, gn, magic_gn, magic_p, l.slab, l.gap_off);
+    return hipGetLastError();
+}
+
+// hipErrorInvalidValue for a layer it does not cover or a tile whose slab does not fit LDS
+template <int ES>
+hipError_t launch_conv_taps(const ConvArgs& a, int cfg, hipStream_t s)
+{
+    if (a.M <= 0) return hipSuccess;
+    if (!cfg_is_taps(cfg) || !conv_taps_supported(a, ES)) return hipErrorInvalidValue;
+#define EE_TAPS(TM_, NW_, KP_) \
+    if (cfg == taps_cfg(TM_, NW_, KP_)) return launch_taps_shape<ES, TM_, NW_, KP_>(a, s);
+    EE_TAPS(2, 4, 1) EE_TAPS(3, 4, 1) EE_TAPS(4, 4, 1) EE_TAPS(5, 4, 1) EE_TAPS(7, 4, 1)
+    EE_TAPS(2, 4, 2) EE_TAPS(4, 4, 2) EE_TAPS(2, 2, 4) EE_TAPS(4, 8, 1) EE_TAPS(7, 8, 1)
+#undef EE_TAPS
+    return hipErrorInvalidValue;
+}
+
+template hipError_t launch_conv_taps<1>(const ConvArgs&, int, hipStream_t);
+template hipError_t launch_conv_taps<2>(const ConvArgs&, int, hipStream_t);
+
+}  // namespace ee

@@ -525,6 +525,55 @@ def test_resident_weights_1x1(torch, ee, orc, case, dtype):
     eng.close()
 
 
+TAPS_CASES = [  # h, w, input bytes per pixel, output channels, kernel (rows, columns), samples: one ragged tile, tiles over several samples, images smaller than the
+    # window, an odd number of groups of steps, a slab near the limit of LDS, channels that end inside a block of 32 or leave wavefronts idle
+    (1, 1, 128, 32, (3, 3), 1), (2, 3, 128, 144, (3, 3), 5), (7, 7, 512, 512, (3, 3), 9), (14, 14, 256, 256, (3, 3), 5), (28, 28, 128, 128, (3, 3), 3), (17, 17, 384, 192, (1, 7), 3),
+    (17, 17, 128, 80, (7, 1), 2), (9, 11, 1024, 64, (3, 3), 2), (13, 6, 256, 320, (5, 5), 4), (56, 56, 128, 64, (3, 3), 2), (1, 40, 640, 96, (1, 3), 8),
+]
+TAPS_CONFIGS = [0x2231, 0x2331, 0x2431, 0x4331, 0x4431, 0x2432, 0x4432, 0x2232, 0x2332, 0x4332]      # the last three share the reduction between wavefronts
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("case", TAPS_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
+    """The stride-1 kernel with weights streamed into registers, every tile, with and without a residual: int8 against the oracle bit for bit; bf16
+    against the staged kernel bit for bit (its sums run in the same order) and the oracle under the tolerance of the tiling tests."""
+    from workloads import nets as N
+    h, w, kb, co, (kh, kw), n = case
+    i8 = dtype == "i8"
+    net = N._Net(W.DT_I8 if i8 else W.DT_BF16, h, w, kb // (1 if i8 else 2), 10)
+    t = net.begin_stage()
+    res = net.conv(t, co, (kh, kw), 1, (kh // 2, kw // 2), act="linear")
+    net.end_stage(net.conv(t, co, (kh, kw), 1, (kh // 2, kw // 2), res=res))
+    blob = N._assemble(net, net.dtype, 60 + h)
+    r = np.random.default_rng(co + kb)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * kh * kw) / 127))))
+        op["res_shift"] = int(op["shift"]) - 2 if int(op["res"]) >= 0 else 0
+        if not i8:
+            blob.op_weights(op)[1][:] = r.normal(size=co) * 0.3
+    x = W.input_pool(blob, n)
+    eng = ee.Engine(blob, n)
+    ref = orc.stage_forward(blob, 0, x)
+    staged = None
+    for cfg in [0x221] + TAPS_CONFIGS:
+        say(f"[case] {dtype} {case} cfg {cfg:#x}")
+        old = ee.tune_conv_tile(cfg)
+        try:
+            got = host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref)
+        finally:
+            ee.tune_conv_tile(old)
+        if i8:
+            assert np.array_equal(got, ref), f"{np.count_nonzero(got != ref)} of {ref.size} differ, first at {np.argwhere(got != ref)[:3].tolist()}"
+        else:
+            staged = got if staged is None else staged
+            assert cfg in TAPS_CONFIGS[-3:] or np.array_equal(got, staged), f"{np.count_nonzero(got != staged)} of {ref.size} differ, first at {np.argwhere(got != staged)[:3].tolist()}"
+            rf, g = bf16_to_f32(ref).astype(np.float64), bf16_to_f32(got).astype(np.float64)
+            assert np.all(np.abs(g - rf) <= 2e-2 * (np.abs(rf).reshape(n, -1).max(axis=1).reshape(-1, 1, 1, 1) + 1e-30))
+    assert np.unique(ref).size > 8
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 def test_resident_weights_1x1_takes_slot_tables(torch, ee, orc, dtype):
     """Zero-copy serving with the kernel forced wherever it runs (the layers that read a segment's input, bf16 also those that write its output)."""
