@@ -240,10 +240,11 @@ int ee_tune_conv_tile(int cfg);
  * output is as large as their input; tile 1: 128x128, 2: 128x64, 3: 256x64, 4: 256x128, step 2 or 3 of the
  * weights); the entry 7 alone selects the streaming kernel; groups 2 or 4 with step 1 or 2 name the kernel for few
  * output pixels (32- resp. 16-pixel tiles, step = blocks of channels, tile = log2 of the wavefronts + 1); groups with
- * step 3 and tile 1 or 2 name two more kernels: 0x4231 and 0x4232 the 1x1 one that keeps its weights in registers (tiles
+ * step 3 in words that are no tiling name two more kernels: 0x4231 and 0x4232 the 1x1 one that keeps its weights in registers (tiles
  * of 32 and 64 pixels), 0x2231, 0x2331, 0x2431, 0x4331 and 0x4431 the stride-1 one that streams its weights into registers
  * (2, 3, 4, 5 and 7 blocks of 32 pixels x 128 channels; 0x2432 and 0x4432: 4 and 7 blocks x 256 channels; 0x2232 and
- * 0x2332: 2 and 4 blocks x 128 channels, two wavefronts sharing a reduction; 0x4332: 2 blocks x 64 channels, four sharing).
+ * 0x2332: 2 and 4 blocks x 128 channels, two wavefronts sharing a reduction; 0x4234 and 0x4334: 2 and 4 blocks x 64
+ * channels; 0x4434 and 0x4332: 2 blocks x 64 channels, two and four sharing).
  * EE_ERR_ARG for bad arguments. */
 int ee_autotune(ee_ctx* ctx, int reps);
 int ee_config_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);

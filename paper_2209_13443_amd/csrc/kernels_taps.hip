@@ -1,4 +1,4 @@
-// Stride-1 "same" convolutions over pixels of whole 128-byte runs on the matrix cores, the activations of a tile resident in LDS and the weights
+// Stride-1 "same" convolutions over pixels of whole 32-byte runs (bf16: 64) on the matrix cores, the activations of a tile resident in LDS and the weights
 // streamed from global memory straight into registers: no barrier and no copy between the first matrix instruction and the last.
 //
 // Output row m and input pixel m coincide (kernels_slab.hip), so the input rows of a tile are one contiguous run, copied to LDS once and read at shifted
@@ -8,7 +8,7 @@
 // matrix instructions; the activations are the only LDS traffic, one 1 KiB read per matrix instruction, 128 bytes/clk of about 190; and nothing makes
 // wavefronts wait for one another.  Slab rows are padded by 16 bytes, an odd number of chunks, which spreads 16 rows over all banks and makes the position inside a
 // pixel a compile-time offset of the read.  Taps outside the image read a row of zeros.
-// Four wavefronts (128 channels) per workgroup, two or three of which share a CU; eight (256 channels) where the slab fills it.  Where the tiles are few (at most
+// Four wavefronts (128 channels) per workgroup, two or three of which share a CU; eight (256 channels) where the slab fills it, two where channels are few.  Where the tiles are few (at most
 // one or two workgroups per CU) the reduction itself is the chain: 2 or 4 wavefronts share it, a slice of (r, s, c) each, and add up through LDS.  With one
 // wavefront per block of channels the sums run in the order of the staged kernel, so bf16 results are the same bits.
 // Writes slots and pools for the exit head; does not read slots.
@@ -16,7 +16,8 @@
 //   256 samples: bf16 28x28, 128 -> 128 71.1 -> 45.8, 14x14, 256 -> 256 66.9 -> 43.6 (1.36 PFLOP/s, the rate of a large matrix product here), 7x7, 512 -> 512
 //     63.1 -> 47.1; int8 35.1 -> 28.7, 31.2 -> 26.2, 33.4 -> 27.2
 //   64 samples: bf16 21.0 -> 17.2, 20.1 -> 16.9, 25.2 -> 17.2; int8 11.9 -> 11.6, 11.1 -> 10.6, 13.8 -> 10.4
-//   int8, residual, 32 samples: 28x28, 128 -> 128 8.8 -> 7.9, 14x14, 256 -> 256 9.0 -> 7.4, 7x7, 512 -> 512 11.7 -> 7.5
+//   int8, residual, 32 samples: 28x28, 128 -> 128 8.8 -> 7.5, 14x14, 256 -> 256 9.0 -> 7.4, 7x7, 512 -> 512 11.7 -> 7.6
+//   int8, 64 samples: 35x35, 96 -> 96 15.7 -> 11.3, 17x17, 1x7, 160 -> 160 8.8 -> 7.7, 192 -> 192 10.0 -> 8.4, 8x8, 3x3, 448 -> 384 12.6 -> 10.0
 #include <algorithm>
 #include <type_traits>
 
@@ -30,16 +31,16 @@ namespace ee {
 constexpr unsigned taps_part_bytes(int tm, int nw, int kp) { return kp == 1 ? 0 : (unsigned)((tm < kp ? tm : kp) * (kp - 1) * nw * ((tm + kp - 1) / kp) * 4096); }
 
 // ES: element bytes; TM: blocks of 32 pixels of a tile, all of them multiplied by every wavefront; NW: blocks of 32 output channels; KP: wavefronts that
-// share the reduction of a block of channels
-template <int ES, int TM, int NW, int KP>
+// share the reduction of a block of channels; U: steps (32 bytes of the reduction) per group, a pixel is a whole number of groups
+template <int ES, int TM, int NW, int KP, int U>
 __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, unsigned magic_p, unsigned slab_bytes, unsigned gap_off)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int BM = 32 * TM, BN = 32 * NW, NT = 64 * NW * KP;
     using T = OutTile<ES, BN>;
     constexpr int OROW = T::OROW, CR = T::CR, NO = (BM * CR + NT - 1) / NT;    // output tile: bytes and chunks per row, chunks per lane
-    constexpr int U = 4, WR = 2 * U;                                    // steps (32 bytes of the reduction) per group, weight operands in flight
-    constexpr int FD = TM >= 4 ? 1 : 3, NS = TM >= 4 ? 2 : 4;                    // activation operands are read FD steps ahead into NS register sets used in turn
+    constexpr int WR = U == 1 ? 4 : 8, NG = WR / U;                     // weight operands in flight, groups they make
+    constexpr int FD = TM >= 4 || U == 1 ? 1 : U - U / 4, NS = FD == 1 ? 2 : 4;      // activation operands are read FD steps ahead into NS register sets used in turn
     constexpr unsigned PART_BYTES = taps_part_bytes(TM, NW, KP);        // partial sums, over the slab
     constexpr int OWN = (TM + KP - 1) / KP;                             // blocks of pixels a wavefront finishes: wavefront `part` those with i % KP == part
     typedef float v4f __attribute__((ext_vector_type(4)));
@@ -59,7 +60,8 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
     // ---- weights of the first steps ------------------------------------------------------------------------------
     const int steps = a.kh * a.kw * (CiB >> 5), groups = steps / U;
     const int part = wave / NW, wn = wave % NW;                         // this wavefront's share of the reduction, its block of channels
-    const int g0 = KP == 1 ? 0 : groups * part / KP, g1 = KP == 1 ? groups : groups * (part + 1) / KP;
+    const bool idle = n0 / 32 + wn >= (a.Co + 31) / 32;                 // its channels lie past the layer's
+    const int g0 = KP == 1 ? 0 : groups * part / KP, g1 = idle ? g0 : KP == 1 ? groups : groups * (part + 1) / KP;
     const int co_blocks = (a.Co + 127) / 128 * 4, cb = min(n0 / 32 + wn, co_blocks - 1);
     const unsigned char* const wbase = (const unsigned char*)a.wo + (size_t)cb * (size_t)(a.Kp * ES / 32) * 1024;
     auto weight = [&](int s) { return *(const v4i*)(wbase + (size_t)(unsigned)min(s, steps - 1) * 1024 + lane * 16); };
@@ -155,29 +157,28 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
 #pragma unroll
         for (int i = 0; i < TM; ++i) gx[u][i] = *(const v4i*)(lds + pa[i] + u * 32);
     // every matrix instruction is followed by one operand read of a later step, every step by one load of weights WR steps ahead
-    auto group = [&](auto half_tag, int g) {
-        constexpr int HALF = decltype(half_tag)::value;
+    auto group = [&](auto h_tag, int g) {
+        constexpr int H = decltype(h_tag)::value * U;
         static_for<U>([&](auto u_tag) {
             constexpr int S = decltype(u_tag)::value, R = S + FD;
             if constexpr (R == U) advance();
             static_for<TM>([&](auto i_tag) {
                 constexpr int I = decltype(i_tag)::value;
-                if constexpr (ES == 1) acc[I] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[HALF * U + S], gx[S % NS][I], acc[I], 0, 0, 0);
-                else acc[I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, wr[HALF * U + S]), __builtin_bit_cast(v8bf, gx[S % NS][I]), acc[I], 0, 0, 0);
+                if constexpr (ES == 1) acc[I] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[H + S], gx[(H + S) % NS][I], acc[I], 0, 0, 0);
+                else acc[I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, wr[H + S]), __builtin_bit_cast(v8bf, gx[(H + S) % NS][I]), acc[I], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                gx[R % NS][I] = *(const v4i*)(lds + pa[I] + (R % U) * 32);
+                gx[(H + R) % NS][I] = *(const v4i*)(lds + pa[I] + (R % U) * 32);
                 __builtin_amdgcn_sched_barrier(0);
             });
-            wr[HALF * U + S] = weight(g * U + S + WR);
+            wr[H + S] = weight(g * U + S + WR);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
     int g = g0;
-    for (; g + 1 < g1; g += 2) {
-        group(std::integral_constant<int, 0>{}, g);
-        group(std::integral_constant<int, 1>{}, g + 1);
-    }
-    if (g < g1) group(std::integral_constant<int, 0>{}, g);
+    for (; g + NG <= g1; g += NG) static_for<NG>([&](auto h_tag) { group(h_tag, g + decltype(h_tag)::value); });
+    static_for<NG - 1>([&](auto h_tag) {
+        if (g + decltype(h_tag)::value < g1) group(h_tag, g + decltype(h_tag)::value);
+    });
 
     // ---- results: through LDS (rows of OutTile, over the residual if there is one), then whole chunks ----
     v4i bias[4];
@@ -276,16 +277,16 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
     }
 }
 
-// Stride 1, output as large as the input, 2 .. 31 taps, a pixel of whole 128-byte runs (a group of steps never straddles two taps), whole
-// 16-byte chunks in the output, a tensor below 2 GiB (so that row numbers stay below 2^24, as the address arithmetic assumes)
+// Stride 1, output as large as the input, 2 .. 31 taps, a pixel of 64 bytes or more in whole groups of steps (a group never straddles two taps), whole
+// 16-byte chunks in the output, a tensor below 2 GiB and 2^24 pixels (the address arithmetic multiplies 24-bit row numbers)
 bool conv_taps_supported(const ConvArgs& a, int es)
 {
     const int cib = a.Ci * es;
     if (a.xs || a.mode != 0 || !a.wo || a.stride != 1 || a.Ho != a.H || a.Wo != a.W) return false;
-    if (cib % 128 != 0 || cib > 2048 || a.kh * a.kw > 31 || a.kh * a.kw < 2) return false;
+    if (cib % (es == 1 ? 32 : 64) != 0 || cib < 64 || cib > 2048 || a.kh * a.kw > 31 || a.kh * a.kw < 2) return false;
     if (a.H + 2 * a.pad - a.kh + 1 != a.Ho || a.W + 2 * a.pad_w - a.kw + 1 != a.Wo) return false;
     if ((a.Co * es) % 16 != 0 || (a.ldc * es) % 16 != 0 || (a.c_off * es) % 16 != 0) return false;
-    return (long long)a.M * cib < (1ll << 31);
+    return (long long)a.M * cib < (1ll << 31) && a.M < 1 << 24;
 }
 
 struct TapsLds { unsigned slab, gap_off; size_t bytes; };
@@ -303,28 +304,36 @@ static TapsLds taps_lds(const ConvArgs& a, int es, int tm, int nw, int kp)
 }
 
 // Untuned: the configuration of a layer this kernel is the faster one for, else 0.  Measured over the layers of the ResNet-50, ResNet-18 and Inception-style
-// networks at 1-256 samples; blocks are 64 x 64 tiles of the output.
-//   Few pixels, int8: up to 53 blocks (100 for reductions below 2 KiB) the few-pixel kernel is level or the faster one (7x7, 512 -> 512, 4 samples 7.2 against 7.1 us
-//     here, 17x17, 1x7, 128 -> 128, 8 samples 4.0 / 4.9; from 8 samples 9.0 / 7.3, 14x14, 256 -> 256, 5 samples 6.6 / 5.9).  Up to 256 blocks four wavefronts share
-//     the reduction of a 64 x 64 tile (7x7, 512 -> 512, 32 samples 7.5 us, 10.1 with two sharing, 11.0 with none), up to 512 two that of a 64 x 128 tile if it is
-//     long (14x14, 256 -> 256, 32 samples 7.2, 7.7 with none sharing, 8.1 with four; 28x28, 128 -> 128, 16 samples 6.0, 5.9 with none).
-//   bf16 does not share: one order of summation.  From 32 blocks on level (18.5 / 18.9 us at 32, 10.9 / 11.5 at 64), faster with more.
+// networks at 1-256 samples; blocks are 64 x 64 tiles of the output, us, best configuration of the other kernels / this one.
+//   Few pixels, int8: up to 53 blocks (100 for reductions below 2 KiB) the few-pixel kernel is level or the faster one (7x7, 512 -> 512, 4 samples 7.2 / 7.2,
+//     17x17, 1x7, 128 -> 128, 8 samples 4.0 / 4.4; from 8 samples 9.0 / 7.3, 14x14, 256 -> 256, 5 samples 6.6 / 5.7).  Up to 256 blocks wavefronts share the
+//     reduction of a 64 x 64 tile, four of them a long one (7x7, 512 -> 512, 16 samples 7.5, with two 7.8, with none 10.7), two a shorter one (14x14, 256 -> 256, 16
+//     samples 5.8, with four 6.1, with none 7.5); up to 512 two that of a 64 x 128 tile if it is long (14x14, 256 -> 256, 32 samples 7.2, with none 7.7).
+//   bf16 does not share: one order of summation.  From 32 blocks on level (18.9 / 18.5 at 32, 11.5 / 10.9 at 64), faster with more.
+//   Channels that leave half of a 128-channel tile empty: tiles of 64 channels, two wavefronts sharing up to 512 blocks (17x17, 1x7, 192 -> 192, 32 samples 7.6 / 6.0,
+//     with none 7.5), none beyond (64 samples 10.0 / 8.4; 56x56, 64 -> 64, 32 samples 9.7 / 9.0; bf16, 256 samples 72.0 / 65.4), of 128 pixels from 8192 blocks on
+//     (56x56, 64 -> 64, 256 samples 44.2 / 38.5, of 64 pixels 41.5).
 //   Otherwise the tile with the least work on the busiest CU: its workgroups times (blocks of 32 pixels + 1 for start and end), three tenths more where four wavefronts
 //     have a CU to themselves.  Over 27 layers and sizes the choice is the fastest configuration or within 3 % of it but once (7 %).
-//   Channels that leave half of a 128-channel tile empty: a third slower at 64 (bf16 56x56, 64 -> 64 94 us against 72), at 192 level at 867 blocks (8.2 us both),
-//     14.5 / 12.0 at 1734.  Reductions below 896 bytes were not measured.
+//   Reductions below 512 bytes were not measured.
 int conv_taps_default(const ConvArgs& a, int es)
 {
     const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64), kbytes = (long long)a.kh * a.kw * a.Ci * es;
-    if (blocks < (es == 2 ? 32 : kbytes < 2048 ? 101 : 54) || kbytes < 896 || !conv_taps_supported(a, es)) return 0;
-    if ((a.Co + 127) / 128 * 128 - a.Co >= 64 && (es == 2 || a.Co <= 64 || blocks < 1024)) return 0;
+    const bool half = (a.Co - 1) % 128 < 64;                            // the last 128-channel tile at most half full
+    if (kbytes < 512 || blocks < (es == 2 ? (half ? 200 : 32) : kbytes < 2048 ? 101 : 54) || !conv_taps_supported(a, es)) return 0;
+    const bool wide_groups = a.Ci * es % 128 == 0;                      // every tile exists; else 2 and 4 blocks of pixels
     auto fits = [&](int tm, int nw, int kp) { return taps_lds(a, es, tm, nw, kp).bytes <= 160 * 1024 && (!a.gap_sums || (32 * tm - 1) / (a.Ho * a.Wo) + 2 <= GAP_S); };
-    if (es == 1 && blocks <= 256 && fits(2, 2, 4)) return taps_cfg(2, 2, 4);
+    if (es == 1 && blocks <= 256 && kbytes >= 3072 && fits(2, 2, 4)) return taps_cfg(2, 2, 4);
+    if (es == 1 && blocks <= (half ? 512 : 256) && fits(2, 2, 2)) return taps_cfg(2, 2, 2);
+    if (half) {
+        if (es == 1 && blocks >= 8192 && fits(4, 2, 1)) return taps_cfg(4, 2, 1);
+        return fits(2, 2, 1) ? taps_cfg(2, 2, 1) : 0;
+    }
     if (es == 1 && blocks <= 512 && kbytes >= 2048 && fits(2, 4, 2)) return taps_cfg(2, 4, 2);
     int best = 0;
     long long least = 0;
     auto weigh = [&](int tm, int nw) {
-        if (!fits(tm, nw, 1)) return;
+        if (!fits(tm, nw, 1) || (!wide_groups && tm != 2 && tm != 4)) return;
         const long long wgs = ((a.M + 32 * tm - 1) / (32 * tm)) * (long long)((a.Co + 32 * nw - 1) / (32 * nw)), rounds = (wgs + 255) / 256;
         const bool alone = nw == 4 && (wgs <= 256 || taps_lds(a, es, tm, nw, 1).bytes > 80 * 1024);
         const long long cost = rounds * (tm + 1) * (nw / 4) * (alone ? 13 : 10);
@@ -336,18 +345,30 @@ int conv_taps_default(const ConvArgs& a, int es)
     return best;
 }
 
-template <int ES, int TM, int NW, int KP>
-static hipError_t launch_taps_shape(const ConvArgs& a, hipStream_t s)
+template <int ES, int TM, int NW, int KP, int U>
+static hipError_t launch_taps_unroll(const ConvArgs& a, hipStream_t s)
 {
     constexpr int BM = 32 * TM, BN = 32 * NW;
     const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, p = a.Ci * ES / 16 + 1;
     const TapsLds l = taps_lds(a, ES, TM, NW, KP);
     if (l.bytes > 160 * 1024 || (a.gap_sums && (ES != 1 || (BM - 1) / (a.Ho * a.Wo) + 2 > GAP_S))) return hipErrorInvalidValue;
-    static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_taps_kernel<ES, TM, NW, KP>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_taps_kernel<ES, TM, NW, KP, U>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (granted != hipSuccess) return granted;
     const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1)), magic_p = (unsigned)(0x100000000ull / (unsigned)p);
-    EE_LAUNCH((conv_taps_kernel<ES, TM, NW, KP>), dim3(xcd_grid(gm) * (unsigned)gn), dim3(64 * NW * KP), l.bytes, s, a, gm, gn, magic_gn, magic_p, l.slab, l.gap_off);
+    EE_LAUNCH((conv_taps_kernel<ES, TM, NW, KP, U>), dim3(xcd_grid(gm) * (unsigned)gn), dim3(64 * NW * KP), l.bytes, s, a, gm, gn, magic_gn, magic_p, l.slab, l.gap_off);
     return hipGetLastError();
+}
+
+template <int ES, int TM, int NW, int KP>
+static hipError_t launch_taps_shape(const ConvArgs& a, hipStream_t s)
+{
+    const int cib = a.Ci * ES;
+    if (cib % 128 == 0) return launch_taps_unroll<ES, TM, NW, KP, 4>(a, s);
+    if constexpr (TM == 2 || TM == 4) {
+        if (cib % 64 == 0) return launch_taps_unroll<ES, TM, NW, KP, 2>(a, s);
+        if constexpr (ES == 1) return launch_taps_unroll<ES, TM, NW, KP, 1>(a, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 // hipErrorInvalidValue for a layer it does not cover or a tile whose slab does not fit LDS
@@ -360,6 +381,7 @@ hipError_t launch_conv_taps(const ConvArgs& a, int cfg, hipStream_t s)
     if (cfg == taps_cfg(TM_, NW_, KP_)) return launch_taps_shape<ES, TM_, NW_, KP_>(a, s);
     EE_TAPS(2, 4, 1) EE_TAPS(3, 4, 1) EE_TAPS(4, 4, 1) EE_TAPS(5, 4, 1) EE_TAPS(7, 4, 1)
     EE_TAPS(2, 4, 2) EE_TAPS(4, 4, 2) EE_TAPS(2, 2, 4) EE_TAPS(4, 8, 1) EE_TAPS(7, 8, 1)
+    EE_TAPS(2, 2, 1) EE_TAPS(4, 2, 1) EE_TAPS(2, 2, 2)
 #undef EE_TAPS
     return hipErrorInvalidValue;
 }

@@ -526,11 +526,12 @@ def test_resident_weights_1x1(torch, ee, orc, case, dtype):
 
 
 TAPS_CASES = [  # h, w, input bytes per pixel, output channels, kernel (rows, columns), samples: one ragged tile, tiles over several samples, images smaller than the
-    # window, an odd number of groups of steps, a slab near the limit of LDS, channels that end inside a block of 32 or leave wavefronts idle
+    # window, every group of steps (pixels of whole 128, 64 and 32 bytes) and any number of them, a slab near the limit of LDS, channels that end inside a block of 32 or leave wavefronts idle
     (1, 1, 128, 32, (3, 3), 1), (2, 3, 128, 144, (3, 3), 5), (7, 7, 512, 512, (3, 3), 9), (14, 14, 256, 256, (3, 3), 5), (28, 28, 128, 128, (3, 3), 3), (17, 17, 384, 192, (1, 7), 3),
     (17, 17, 128, 80, (7, 1), 2), (9, 11, 1024, 64, (3, 3), 2), (13, 6, 256, 320, (5, 5), 4), (56, 56, 128, 64, (3, 3), 2), (1, 40, 640, 96, (1, 3), 8),
+    (56, 56, 64, 64, (3, 3), 2), (35, 35, 96, 96, (3, 3), 2), (17, 17, 160, 160, (1, 7), 3), (17, 17, 192, 192, (7, 1), 3), (8, 8, 448, 384, (3, 3), 3), (6, 5, 96, 32, (5, 1), 2),
 ]
-TAPS_CONFIGS = [0x2231, 0x2331, 0x2431, 0x4331, 0x4431, 0x2432, 0x4432, 0x2232, 0x2332, 0x4332]      # the last three share the reduction between wavefronts
+TAPS_CONFIGS = [0x2231, 0x2331, 0x2431, 0x4331, 0x4431, 0x2432, 0x4432, 0x4234, 0x4334, 0x4434, 0x2232, 0x2332, 0x4332]      # the last four share the reduction between wavefronts
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
@@ -567,7 +568,7 @@ def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
             assert np.array_equal(got, ref), f"{np.count_nonzero(got != ref)} of {ref.size} differ, first at {np.argwhere(got != ref)[:3].tolist()}"
         else:
             staged = got if staged is None else staged
-            assert cfg in TAPS_CONFIGS[-3:] or np.array_equal(got, staged), f"{np.count_nonzero(got != staged)} of {ref.size} differ, first at {np.argwhere(got != staged)[:3].tolist()}"
+            assert cfg in TAPS_CONFIGS[-4:] or np.array_equal(got, staged), f"{np.count_nonzero(got != staged)} of {ref.size} differ, first at {np.argwhere(got != staged)[:3].tolist()}"
             rf, g = bf16_to_f32(ref).astype(np.float64), bf16_to_f32(got).astype(np.float64)
             assert np.all(np.abs(g - rf) <= 2e-2 * (np.abs(rf).reshape(n, -1).max(axis=1).reshape(-1, 1, 1, 1) + 1e-30))
     assert np.unique(ref).size > 8
