@@ -1471,10 +1471,10 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
         // a bottleneck block may sit in a segment whose last layer writes slots, and may be that layer (its kernel takes the slot table)
         // (the fused first convolution + pool writes inside the segment: slots do not concern it)
         const bool ir_slots_ok = p.ir_bneck ? !(zc_in && plans[st.first_op + k + ir_last].res_buf == BUF_EXT_IN) : p.ir_stem || !zc_out;
-        // the exit head's pooling rides on the segment's last layer: a bottleneck block's kernel carries it (with a residual), the others do not
+        // the exit head's pooling rides on the segment's last layer: the blocks' kernels carry it (a bottleneck block's with a residual only)
         const bool ir_pools = gap_fuse_dst && only_op < 0 && st.first_op + k + ir_last == gap_fuse_op[(size_t)stage];
         if (p.ir && ir_mode > 0 && cfg_force == 0 && forced_conv_tile() == 0 && only_op < 0 && !xs && ir_slots_ok &&
-            !(ir_pools && !(p.ir_bneck && plans[st.first_op + k + ir_last].d.res >= 0))) {
+            !(ir_pools && (p.ir_stem || (p.ir_bneck && plans[st.first_op + k + ir_last].d.res < 0)))) {
             // this layer, the depthwise layer and the projection as one launch, where the table says it is faster
             const bool fuse = ir_wanted(st.first_op + k, b);
             if (fuse && p.ir_stem) {
@@ -1504,7 +1504,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 ia.y = resolve(this, q2.dst_buf, act_in, act_out);
                 ia.res = q2.d.res >= 0 && !p.ir_sc ? resolve(this, q2.res_buf, act_in, act_out) : nullptr;   // the kernel computes the shortcut itself
                 ia.ys = q2.dst_buf == BUF_EXT_OUT ? zc_out : nullptr;
-                ia.gap_sums = ir_pools && es == 1 && bneck_block_pools(ia) ? gap_fuse_dst : nullptr;       // else the head pools the output itself
+                ia.gap_sums = ir_pools && es == 1 && (p.ir_bneck ? bneck_block_pools(ia) : ir_block_pools(ia)) ? gap_fuse_dst : nullptr;       // else the head pools the output itself
                 double f_ops = ops, f_bytes = bytes;                             // the block's layers; the tensors between them stay on chip
                 for (int j = 1; j <= ir_last; ++j) {
                     const OpPlan& q = plans[st.first_op + k + j];

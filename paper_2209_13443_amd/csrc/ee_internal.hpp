@@ -106,7 +106,7 @@ struct IrArgs {
     int B, H, W, Cin, Kx, Ce32, Cout, Ho, Wo, stride, pad;
     int sh_e, lo_e, hi_e, sh_d, lo_d, hi_d, sh_p, lo_p, hi_p, res_shift;
     const uint16_t* ys;  // bottleneck block only; not null: sample n of the output goes to slot ys[n] of y (device memory; B <= EE_ZC_MAX_B)
-    int* gap_sums;       // bottleneck block only; not null: also add the per-sample channel sums of the output into gap_sums[n][Cout]
+    int* gap_sums;       // int8; not null: also add the per-sample channel sums of the output into gap_sums[n][Cout]
     const void* ws; const int* bs;   // bottleneck block only; not null: the residual is the 1x1 convolution of x with these operands and biases
     int sh_s, lo_s, hi_s;            // (res is null then), requantised with these
     float f_lo_e, f_hi_e, f_lo_d, f_hi_d, f_lo_p, f_hi_p, f_lo_s, f_hi_s;      // bf16 bottleneck block: the layers' bounds, the biases are floats
@@ -229,6 +229,7 @@ hipError_t launch_space_to_depth(const void* x, void* y, const int32_t* gather, 
 hipError_t launch_pad_channels(const void* x, void* y, long long rows, int c_bytes, int cp_bytes, hipStream_t s);
 hipError_t launch_depthwise(const PoolArgs& a, int dtype, hipStream_t s);
 // the fused inverted-residual block (int8); pointers may be null for ir_block_supported
+bool ir_block_pools(const IrArgs& a);                  // whether its launch can carry the exit head's pooling
 bool ir_block_supported(const IrArgs& a);
 int ir_block_out_blocks(int c_out);            // blocks of 32 output channels the kernel is instantiated with (weights are padded to it)
 hipError_t launch_ir_block(const IrArgs& a, hipStream_t s);

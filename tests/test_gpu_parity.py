@@ -179,6 +179,30 @@ def test_fused_inverted_residual_blocks_equal_separate_layers_and_oracle(torch, 
     eng.close()
 
 
+@pytest.mark.parametrize("case", [(9, 11, 16, 48), (28, 28, 32, 192), (14, 14, 96, 576), (7, 7, 160, 320), (12, 20, 16, 0), (1, 1, 16, 32)], ids=lambda c: "x".join(map(str, c)))
+def test_inverted_residual_block_pools_for_the_exit_head(torch, ee, orc, case):
+    """A segment that ends in a fused block with a residual, served: the block's launch carries the exit head's pooling (both forms of the kernel,
+    tiles with dead pixels, several tiles per image).  Label and confidence of every request are those of the separate layers, and the oracle's."""
+    h, w, ci, ce = case
+    blob = W.inverted_residual_net(h, w, ci, ce, ci, 1, seed=h + ce, blocks=1)
+    n, b_max = 24, 8
+    x = np.random.default_rng(h).integers(-128, 128, size=(n, h, w, ci), dtype=np.int8)
+    eng = ee.Engine(blob, b_max)
+    assert eng.ir_count() == 1
+    lut = synthetic_lut(blob.n_stages, b_max)
+    want = None
+    for mode in (0, 2, 2):
+        say(f"[case] pooling block {case} mode {mode}")
+        eng.ir_mode(mode)
+        got = eng.serve_stream(np.zeros(n, np.int64), dev(torch, x), lut, refill=0)[0]
+        want = got if want is None else want
+        for f in ("exit_idx", "label", "conf"):
+            assert np.array_equal(got[f], want[f]), (f, mode)
+    label, conf = orc.exit_head(blob, 0, orc.stage_forward(blob, 0, x), 0.5)[:2]
+    assert np.array_equal(want["label"], label) and np.array_equal(want["conf"], conf) and np.unique(conf).size > 8
+    eng.close()
+
+
 BN_CASES = [  # h, w, c_in, blocks, samples
     (8, 8, 64, 1, 3), (9, 11, 64, 2, 7), (5, 17, 256, 1, 7), (16, 8, 256, 2, 5), (1, 1, 64, 1, 2), (28, 28, 256, 1, 40), (56, 56, 64, 2, 6), (28, 28, 64, 2, 9),
 ]
