@@ -929,7 +929,10 @@ hipError_t ee_ctx::launch_conv(int op, int b, const void* src, void* dst, const 
         }
         if (cfg == 0) cfg = conv_rows_default(a, dt == EE_I8 ? 1 : 2);
         if (cfg_is_skinny(cfg)) return dt == EE_I8 ? launch_conv_skinny<1>(a, cfg, stream) : launch_conv_skinny<2>(a, cfg, stream);
-        if (cfg_is_rows(cfg) && conv_rows_supported(a, dt == EE_I8 ? 1 : 2)) return dt == EE_I8 ? launch_conv_rows<1>(a, cfg, stream) : launch_conv_rows<2>(a, cfg, stream);
+        if (cfg_is_rows(cfg)) {
+            const hipError_t e = dt == EE_I8 ? launch_conv_rows<1>(a, cfg, stream) : launch_conv_rows<2>(a, cfg, stream);
+            if (e != hipErrorInvalidValue) return e;     // else: not of its kind (the fused pooling)
+        }
         if ((cfg & EE_CFG_SLAB) || (cfg & 15) == 7 || cfg_is_rows(cfg)) cfg = 0;
         return dt == EE_I8 ? launch_conv_igemm<1>(a, cfg, stream) : launch_conv_igemm<2>(a, cfg, stream);
     }

@@ -599,6 +599,39 @@ def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
     eng.close()
 
 
+@pytest.mark.parametrize("case", [(7, 7, 128, 256, 1), (5, 5, 256, 512, 1), (28, 28, 128, 128, 1), (7, 7, 64, 128, 3), (6, 5, 96, 96, 3), (14, 14, 256, 256, 3), (28, 28, 128, 64, 3)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_pooling_for_the_exit_head_rides_on_the_last_layer(torch, ee, orc, case):
+    """Segments that end in a 1x1 or 3x3 layer with a residual, served with every kernel that adds up the exit head's channel sums in its own launch (blocks of
+    pixels over one, two and three samples, ragged last tiles): label and confidence of every request are the oracle's."""
+    from workloads import nets as N
+    h, w, ci, co, k = case
+    net = N._Net(W.DT_I8, h, w, ci, 10)
+    t = net.begin_stage()
+    res = net.conv(t, co, k, 1, k // 2, act="linear")
+    net.end_stage(net.conv(t, co, k, 1, k // 2, res=res))
+    blob = N._assemble(net, W.DT_I8, 90 + h)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * k * k) / 127))))
+        op["res_shift"] = int(op["shift"]) - 2 if int(op["res"]) >= 0 else 0
+    blob.exits[0]["frac_bits"] = 10
+    n, b_max = 40, 11
+    x = W.input_pool(blob, n)
+    label, conf = orc.exit_head(blob, 0, orc.stage_forward(blob, 0, x), 0.5)[:2]
+    eng = ee.Engine(blob, b_max)
+    lut = synthetic_lut(blob.n_stages, b_max)
+    for cfg in [0, 0x221] + ([0x4231, 0x4232] if k == 1 else TAPS_CONFIGS):
+        say(f"[case] pooling {case} cfg {cfg:#x}")
+        old = ee.tune_conv_tile(cfg)
+        try:
+            got = eng.serve_stream(np.zeros(n, np.int64), dev(torch, x), lut, refill=0)[0]
+        finally:
+            ee.tune_conv_tile(old)
+        assert np.array_equal(got["label"], label) and np.array_equal(got["conf"], conf), f"{cfg:#x}"
+    assert np.unique(conf).size > 8
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 def test_resident_weights_1x1_takes_slot_tables(torch, ee, orc, dtype):
     """Zero-copy serving with the kernel forced wherever it runs (the layers that read a segment's input, bf16 also those that write its output)."""
