@@ -1205,7 +1205,8 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 if (p.impl == IMPL_MFMA && conv_rows_supported(probe, es) && st.first_op + k != ctx->gap_fuse_op[s])
                     for (const int cfg : {EE_CFG_ROWS32, EE_CFG_ROWS64}) cands.push_back(cfg);
                 if (p.impl == IMPL_MFMA && conv_taps_supported(probe, es))
-                    for (const int cfg : TAPS_CFGS) cands.push_back(cfg);
+                    for (const int cfg : TAPS_CFGS)
+                        if (es == 1 || !cfg_taps_shares(cfg)) cands.push_back(cfg);      // bf16: the staged kernels' order of summation
                 if (p.impl == IMPL_MFMA && conv_slab_supported(probe, es) && !conv_taps_default(probe, es))      // never the faster one there
                     staged(kbytes, [&](int cfg) { if ((cfg >> 4 & 15) > 1) cands.push_back(EE_CFG_SLAB | cfg); });
                 if ((long long)buckets[bi] * d.h_out * d.w_out <= EE_SKINNY_MAX_ROWS)          // few pixels: the kernel that splits the reduction over its wavefronts

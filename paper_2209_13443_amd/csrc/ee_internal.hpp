@@ -183,6 +183,8 @@ inline bool cfg_is_taps(int cfg)
         if (cfg == c) return true;
     return false;
 }
+// whether wavefronts share a reduction (another order of a bf16 sum than the staged kernels')
+constexpr bool cfg_taps_shares(int cfg) { return cfg == taps_cfg(2, 4, 2) || cfg == taps_cfg(4, 4, 2) || cfg == taps_cfg(2, 2, 2) || cfg == taps_cfg(2, 2, 4); }
 bool conv_taps_supported(const ConvArgs& a, int es);
 int conv_taps_default(const ConvArgs& a, int es);      // configuration of an untuned launch it is the faster one for, else 0
 template <int ES> hipError_t launch_conv_taps(const ConvArgs& a, int cfg, hipStream_t s);

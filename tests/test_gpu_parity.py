@@ -633,6 +633,48 @@ def test_pooling_for_the_exit_head_rides_on_the_last_layer(torch, ee, orc, case)
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
+def test_streamed_weights_write_slots(torch, ee, orc, dtype):
+    """Zero-copy serving of segments that end in a 3x3 layer with a residual, with the kernel with streamed weights forced wherever it runs (one wavefront per
+    reduction, so that bf16 results are the staged kernel's bits): what every request gets is that of the copying compaction with the staged kernel."""
+    from workloads import nets as N
+    i8 = dtype == "i8"
+    net = N._Net(W.DT_I8 if i8 else W.DT_BF16, 11, 9, 64, 10)
+    for _ in range(3):
+        t = net.begin_stage()
+        u = net.conv(t, 64, 1, 1, 0)
+        res = net.conv(t, 64, 1, 1, 0, act="linear")
+        net.end_stage(net.conv(u, 64, 3, 1, 1, res=res))
+    blob = N._assemble(net, net.dtype, 17)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * int(op["kh"]) * int(op["kw"])) / 127))))
+        op["res_shift"] = max(0, int(op["shift"]) - 2) if int(op["res"]) >= 0 else 0
+    n, b_max = 64, 8
+    pool = W.input_pool(blob, n)
+    act = pool[:24]
+    for s in range(3):
+        if i8:
+            blob.exits[s]["frac_bits"] = 12
+        act = orc.stage_forward(blob, s, act)
+        blob.exits[s]["thr"] = float(np.median(orc.exit_head(blob, s, act, 0.5)[1])) if s < 2 else 0.5
+    eng = ee.Engine(blob, b_max)
+    assert eng.zero_copy_supported()
+    lut = synthetic_lut(blob.n_stages, b_max)
+    want = None
+    for cfg, zc in ((0x221, 0), (0x2231, 1), (0x4334, 1), (0x2431, 0)):
+        say(f"[case] slots {dtype} cfg {cfg:#x} zero_copy {zc}")
+        old = ee.tune_conv_tile(cfg)
+        try:
+            got = eng.serve_stream(np.zeros(n, np.int64), dev(torch, pool), lut, refill=2, zero_copy=zc)[0]
+        finally:
+            ee.tune_conv_tile(old)
+        want = got if want is None else want
+        for f in ("exit_idx", "label", "conf", "score"):
+            assert np.array_equal(got[f], want[f]), (f, cfg, zc)
+    assert np.count_nonzero(np.bincount(want["exit_idx"], minlength=3)) > 1
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
 def test_resident_weights_1x1_takes_slot_tables(torch, ee, orc, dtype):
     """Zero-copy serving with the kernel forced wherever it runs (the layers that read a segment's input, bf16 also those that write its output)."""
     blob = W.bottleneck_net(11, 9, 256, seed=3, blocks=2, stages=3, dtype=W.DT_I8 if dtype == "i8" else W.DT_BF16)
