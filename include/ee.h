@@ -282,15 +282,18 @@ int ee_pair_set(ee_ctx* ctx, int layer, const int* cfg, int n);
  * 96 output channels), 2 = fuse every block.
  * ee_ir_table / ee_ir_set: the table of the block headed by `layer`, one entry per batch bucket, 1 = fused, 0 = separate
  * (ee_ir_set: EE_ERR_ARG when `layer` heads no block).
- * Bottleneck blocks of the same three-layer shape (int8) go through the same switches and tables with a kernel of their own: a
+ * Bottleneck blocks of the same three-layer shape (int8 and bf16) go through the same switches and tables with kernels of their own: a
  * 1x1 stride-1 convolution from 64 or 256 to 64 channels, the 3x3 stride-1 convolution with padding 1 (64 -> 64) that alone
  * reads it, and the 1x1 stride-1 convolution to 256 channels (with or without residual) that alone reads that; as a segment's
- * last layers the launch also pools for the exit head and writes through the slot table of zero-copy compaction.  Where the
+ * last layers the launch also pools for the exit head (int8, with a residual; so does an inverted-residual block of stride 1) and
+ * writes through the slot table of zero-copy compaction.  Where the
  * residual is a 1x1 stride-1 convolution of the block's own 64-channel input and that convolution is the layer right in
  * front of the block, the convolution heads a block of four layers, tuned against that convolution followed by the block of
- * three.  The same switches and tables cover the first layers of a ResNet-style network (int8): a 7x7 stride-2 convolution
- * of a 3-channel image to 64 channels and the 3x3 stride-2 max-pool with padding 1 that alone reads it run as one launch (a block
- * of two layers headed by the convolution).  ee_ir_layers: the number of layers of the block headed by `layer` (2, 3 or 4), 0
+ * three.  The same switches and tables cover the first layers of a ResNet-style network (int8; bf16 where the convolution's lower
+ * clamp is not negative): a 7x7 stride-2 convolution of a 3-channel image to 64 channels and the 3x3 stride-2 max-pool with padding 1
+ * that alone reads it run as one launch (a block of two layers headed by the convolution); likewise (int8) a 3x3 stride-1 convolution
+ * of 32 to 64 channels and the 3x3 stride-2 max-pool behind it.  While blocks are fused (mode 1 or 2, no forced tile) a small int8
+ * segment - tensors and weights that one CU's LDS holds - runs as one launch, in the stream with its exit head.  ee_ir_layers: the number of layers of the block headed by `layer` (2, 3 or 4), 0
  * when it heads none. */
 int ee_ir_count(const ee_ctx* ctx);
 int ee_ir_layers(const ee_ctx* ctx, int layer);

@@ -38,7 +38,7 @@ static int skinny_waves(int cfg)
 
 bool conv_skinny_config_ok(int cfg) { return skinny_waves(cfg) >= 0; }
 
-// Untuned: the configuration of a launch this kernel is the faster one for, else 0.  Measured over the layers of the networks at 1-64
+// Untuned: the configuration of a launch this kernel is the faster one for, else 0 (asked behind conv_taps_default).  Measured over the layers of the networks at 1-64
 // samples with a cold L2: up to 400 tiles of 32 x 32 (one or two per CU) it wins or draws; beyond, operands that are used once per load
 // cost more than the staged kernel's chain.  16 x 16 tiles while those of 32 would leave half of the chip idle; four wavefronts are the
 // best or within 5 % of it, but for long reductions in a full round, where eight and twice the channels per activation load are.

@@ -279,8 +279,8 @@ static size_t slab_lds_bytes(const ConvArgs& a, int es, int bm, int bn, int ks, 
     return (front > (size_t)tile ? front : (size_t)tile) + (a.res != nullptr && (a.Co * es) % 16 == 0 ? tile : 0) + 1024;
 }
 
-// Untuned: the configuration of a layer this kernel is the faster one for, else 0.  Measured like the rule of the general kernel, from
-// two rounds of 64 x 64 tiles.  Below four rounds 128 x 64 tiles and long steps, then int8 128 x 128, bf16 128 x 64 ones.  What decides is how
+// Untuned: the configuration of a layer this kernel is the faster one for, else 0; asked behind conv_taps_default, i.e. for layers whose output is not whole
+// 16-byte chunks or whose reduction is outside what that rule covers.  Measured like the rule of the general kernel, from two rounds of 64 x 64 tiles.  Below four rounds 128 x 64 tiles and long steps, then int8 128 x 128, bf16 128 x 64 ones.  What decides is how
 // many workgroups a CU holds, and with it the slab, which grows with the pixel and the rows of the image under the window: while two fit
 // (three of the small bf16 tiles) it is up to 19 % faster than the best configuration of the general kernel (3x3 int8: 28x28, 128 -> 128, 64
 // samples 12.0 us against 13.4; 56x56, 64 -> 64 16.4 / 17.5; 20x20, 256 -> 256 17.7 / 20.2; bf16 56x56, 64 -> 64, 64 samples 25.6 / 30.1), beyond
