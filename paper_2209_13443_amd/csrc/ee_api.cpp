@@ -1352,6 +1352,13 @@ extern "C" int ee_config_set(ee_ctx* ctx, int op, const int* cfg, int n)
             if ((cfg[i] >> 17) || tile < 1 || tile > 4 || (ksel != 0 && ksel != 2 && ksel != 3) || (ns != 0 && (ns < 2 || ns > 4)) || kspl != 0) return EE_ERR_ARG;
             continue;
         }
+        if (cfg_is_rows(cfg[i]) || cfg_is_taps(cfg[i])) {                    // likewise the kernels with resident and with streamed weights
+            ConvArgs a{};
+            ctx->fill_conv_args(op, 1, a);
+            a.res = p.d.res >= 0 ? (const void*)ctx : nullptr;
+            if (!conv_rows_config_ok(a, cfg[i], ctx->net.elem_bytes()) && !conv_taps_config_ok(a, cfg[i], ctx->net.elem_bytes())) return EE_ERR_ARG;
+            continue;
+        }
         if (cfg[i] < 0 || (cfg[i] >> 16) || tile > 4 || ksel > 3 || (ns != 0 && (ns < 2 || ns > 4)) || (kspl != 0 && kspl != 2 && kspl != 4)) return EE_ERR_ARG;
     }
     p.cfg.assign(cfg, cfg + n);

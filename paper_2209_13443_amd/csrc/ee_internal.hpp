@@ -166,6 +166,7 @@ int conv_slab_default(const ConvArgs& a, int es);      // configuration of an un
 enum { EE_CFG_ROWS32 = 0x4231, EE_CFG_ROWS64 = 0x4232 };
 inline bool cfg_is_rows(int cfg) { return cfg == EE_CFG_ROWS32 || cfg == EE_CFG_ROWS64; }
 bool conv_rows_supported(const ConvArgs& a, int es);
+bool conv_rows_config_ok(const ConvArgs& a, int cfg, int es);      // cfg names this kernel and runs on that layer
 int conv_rows_default(const ConvArgs& a, int es);      // configuration of an untuned launch it is the faster one for, else 0
 template <int ES> hipError_t launch_conv_rows(const ConvArgs& a, int cfg, hipStream_t s);
 // the same layers over pixels of whole 32-byte runs (bf16: 64), the weights streamed into registers (kernels_taps.hip): tiles of tm blocks of 32 pixels x 32 channels
@@ -186,6 +187,7 @@ inline bool cfg_is_taps(int cfg)
 // whether wavefronts share a reduction (another order of a bf16 sum than the staged kernels')
 constexpr bool cfg_taps_shares(int cfg) { return cfg == taps_cfg(2, 4, 2) || cfg == taps_cfg(4, 4, 2) || cfg == taps_cfg(2, 2, 2) || cfg == taps_cfg(2, 2, 4); }
 bool conv_taps_supported(const ConvArgs& a, int es);
+bool conv_taps_config_ok(const ConvArgs& a, int cfg, int es);      // cfg names this kernel and runs on that layer: it covers it, the tile exists for its pixels and fits LDS
 int conv_taps_default(const ConvArgs& a, int es);      // configuration of an untuned launch it is the faster one for, else 0
 template <int ES> hipError_t launch_conv_taps(const ConvArgs& a, int cfg, hipStream_t s);
 enum { EE_CFG_SLAB = 0x10000 };     // configuration words with this bit name the slab kernel

@@ -214,6 +214,8 @@ bool conv_rows_supported(const ConvArgs& a, int es)
     return (long long)a.M * a.ldc * es < (1ll << 31) && (long long)a.M * a.Co * es < (1ll << 31);
 }
 
+bool conv_rows_config_ok(const ConvArgs& a, int cfg, int es) { return cfg_is_rows(cfg) && conv_rows_supported(a, es) && !(cfg == EE_CFG_ROWS64 && a.Ci * es == 1024); }
+
 // Untuned: the configuration of a layer this kernel is the faster one for, else 0.  Measured against the best configuration of the staged kernel on the 1x1
 // layers of the ResNet-50-style network; what decides is how many tiles a resident workgroup walks over, i.e. the size of the output (in 64 x 64 blocks):
 //   int8: from 2560 on it wins (28x28, 128 -> 512 + residual, 64 samples: 11.1 us against 14.7; 56x56, 256 -> 512 / 2 12.1 / 15.8; 14x14, 256 -> 1024 + residual
@@ -257,7 +259,7 @@ hipError_t launch_conv_rows(const ConvArgs& a, int cfg, hipStream_t s)
 {
     if (a.M <= 0) return hipSuccess;
     const int rb = cfg == EE_CFG_ROWS64 ? 2 : 1, kb = a.Ci * ES;
-    if (!cfg_is_rows(cfg) || !conv_rows_supported(a, ES) || (rb == 2 && kb == 1024)) return hipErrorInvalidValue;
+    if (!conv_rows_config_ok(a, cfg, ES)) return hipErrorInvalidValue;
 #define EE_ROWS(KB_, NB_, RB_) \
     if (kb == KB_ && (a.Co == 128) == (NB_ == 4) && rb == RB_ / 32) return a.res ? launch_rows_shape<ES, KB_, NB_, RB_, true>(a, s) : launch_rows_shape<ES, KB_, NB_, RB_, false>(a, s);
     EE_ROWS(128, 8, 32) EE_ROWS(128, 8, 64) EE_ROWS(128, 4, 32) EE_ROWS(128, 4, 64)

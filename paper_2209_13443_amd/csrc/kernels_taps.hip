@@ -289,6 +289,11 @@ bool conv_taps_supported(const ConvArgs& a, int es)
     return (long long)a.M * cib < (1ll << 31) && a.M < 1 << 24;
 }
 
+// the tiles that are built (TAPS_CFGS): blocks of 32 pixels, blocks of 32 channels, wavefronts that share a reduction
+#define EE_TAPS_TILES \
+    EE_TAPS(2, 4, 1) EE_TAPS(3, 4, 1) EE_TAPS(4, 4, 1) EE_TAPS(5, 4, 1) EE_TAPS(7, 4, 1) EE_TAPS(2, 4, 2) EE_TAPS(4, 4, 2) EE_TAPS(2, 2, 4) EE_TAPS(4, 8, 1) EE_TAPS(7, 8, 1) \
+    EE_TAPS(2, 2, 1) EE_TAPS(4, 2, 1) EE_TAPS(2, 2, 2)
+
 struct TapsLds { unsigned slab, gap_off; size_t bytes; };
 static TapsLds taps_lds(const ConvArgs& a, int es, int tm, int nw, int kp)
 {
@@ -301,6 +306,22 @@ static TapsLds taps_lds(const ConvArgs& a, int es, int tm, int nw, int kp)
     l.gap_off = (unsigned)l.bytes;
     if (a.gap_sums) l.bytes += (size_t)GAP_S * 32 * nw * 4;
     return l;
+}
+
+static bool taps_fits(const ConvArgs& a, int es, int tm, int nw, int kp)
+{
+    return taps_lds(a, es, tm, nw, kp).bytes <= 160 * 1024 && (!a.gap_sums || (es == 1 && (32 * tm - 1) / (a.Ho * a.Wo) + 2 <= GAP_S));
+}
+
+bool conv_taps_config_ok(const ConvArgs& a, int cfg, int es)
+{
+    if (!conv_taps_supported(a, es)) return false;
+    const bool any_tile = a.Ci * es % 128 == 0;                         // else only tiles of 2 and 4 blocks of pixels exist
+#define EE_TAPS(TM_, NW_, KP_) \
+    if (cfg == taps_cfg(TM_, NW_, KP_)) return (any_tile || TM_ == 2 || TM_ == 4) && taps_fits(a, es, TM_, NW_, KP_);
+    EE_TAPS_TILES
+#undef EE_TAPS
+    return false;
 }
 
 // Untuned: the configuration of a layer this kernel is the faster one for, else 0.  Measured over the layers of the ResNet-50, ResNet-18 and Inception-style
@@ -322,7 +343,7 @@ int conv_taps_default(const ConvArgs& a, int es)
     const bool half = (a.Co - 1) % 128 < 64;                            // the last 128-channel tile at most half full
     if (kbytes < 512 || blocks < (es == 2 ? (half ? 200 : 32) : kbytes < 2048 ? 101 : 54) || !conv_taps_supported(a, es)) return 0;
     const bool wide_groups = a.Ci * es % 128 == 0;                      // every tile exists; else 2 and 4 blocks of pixels
-    auto fits = [&](int tm, int nw, int kp) { return taps_lds(a, es, tm, nw, kp).bytes <= 160 * 1024 && (!a.gap_sums || (32 * tm - 1) / (a.Ho * a.Wo) + 2 <= GAP_S); };
+    auto fits = [&](int tm, int nw, int kp) { return taps_fits(a, es, tm, nw, kp); };
     if (es == 1 && blocks <= 256 && kbytes >= 3072 && fits(2, 2, 4)) return taps_cfg(2, 2, 4);
     if (es == 1 && blocks <= (half ? 512 : 256) && fits(2, 2, 2)) return taps_cfg(2, 2, 2);
     if (half) {
@@ -351,7 +372,6 @@ static hipError_t launch_taps_unroll(const ConvArgs& a, hipStream_t s)
     constexpr int BM = 32 * TM, BN = 32 * NW;
     const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, p = a.Ci * ES / 16 + 1;
     const TapsLds l = taps_lds(a, ES, TM, NW, KP);
-    if (l.bytes > 160 * 1024 || (a.gap_sums && (ES != 1 || (BM - 1) / (a.Ho * a.Wo) + 2 > GAP_S))) return hipErrorInvalidValue;
     static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_taps_kernel<ES, TM, NW, KP, U>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (granted != hipSuccess) return granted;
     const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1)), magic_p = (unsigned)(0x100000000ull / (unsigned)p);
@@ -376,12 +396,10 @@ template <int ES>
 hipError_t launch_conv_taps(const ConvArgs& a, int cfg, hipStream_t s)
 {
     if (a.M <= 0) return hipSuccess;
-    if (!cfg_is_taps(cfg) || !conv_taps_supported(a, ES)) return hipErrorInvalidValue;
+    if (!conv_taps_config_ok(a, cfg, ES)) return hipErrorInvalidValue;
 #define EE_TAPS(TM_, NW_, KP_) \
     if (cfg == taps_cfg(TM_, NW_, KP_)) return launch_taps_shape<ES, TM_, NW_, KP_>(a, s);
-    EE_TAPS(2, 4, 1) EE_TAPS(3, 4, 1) EE_TAPS(4, 4, 1) EE_TAPS(5, 4, 1) EE_TAPS(7, 4, 1)
-    EE_TAPS(2, 4, 2) EE_TAPS(4, 4, 2) EE_TAPS(2, 2, 4) EE_TAPS(4, 8, 1) EE_TAPS(7, 8, 1)
-    EE_TAPS(2, 2, 1) EE_TAPS(4, 2, 1) EE_TAPS(2, 2, 2)
+    EE_TAPS_TILES
 #undef EE_TAPS
     return hipErrorInvalidValue;
 }

@@ -599,6 +599,43 @@ def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
     eng.close()
 
 
+LOADED_WORDS = [  # h, input channels, output channels, kernel, stride, words that run on the layer, words that do not
+    (14, 128, 128, 3, 1, [0x2231, 0x4431, 0x4332], [0x4231, 0x4232]),
+    (14, 128, 128, 3, 2, [0x221], [0x4231, 0x4232, 0x2231, 0x4334]),              # not as large as its input
+    (14, 128, 128, 1, 1, [0x4231, 0x4232], [0x2231, 0x2432]),
+    (7, 1024, 256, 1, 1, [0x4231], [0x4232]),                                      # tiles of 64 pixels of 1 KiB do not exist
+    (14, 96, 128, 3, 1, [0x2231, 0x2431, 0x4434], [0x2331, 0x4331, 0x4432]),      # pixels of 32-byte runs: 2 and 4 blocks only
+    (28, 768, 128, 3, 1, [0x2231], [0x4431, 0x4432]),                              # 282 slab rows of 784 bytes do not fit LDS
+    (14, 128, 72, 3, 1, [0x221], [0x2231, 0x4231]),                                # output pixels of no whole 16-byte chunks
+]
+
+
+@pytest.mark.parametrize("case", LOADED_WORDS, ids=lambda c: "x".join(map(str, c[:5])))
+def test_loaded_words_are_checked_against_the_layer(torch, ee, orc, case):
+    """A stored word that names the kernel with resident or with streamed weights is accepted where it runs and refused elsewhere; a refused table
+    leaves the old one in place."""
+    from workloads import nets as N
+    h, ci, co, k, stride, good, bad = case
+    net = N._Net(W.DT_I8, h, h, ci, 10)
+    t = net.conv(net.begin_stage(), co, k, stride, k // 2)
+    net.end_stage(net.conv(t, 64, 1, 1, 0))
+    blob = N._assemble(net, W.DT_I8, 5)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * int(op["kh"]) ** 2) / 127))))
+    x = W.input_pool(blob, 3)
+    ref = orc.stage_forward(blob, 0, x)
+    eng = ee.Engine(blob, 3)
+    for cfg in good:
+        say(f"[case] loaded word {cfg:#x} on {case[:5]}")
+        eng.load_tables({"config": {"0": [cfg, cfg, cfg]}})
+        assert np.array_equal(host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref), ref)
+    for cfg in bad:
+        with pytest.raises(ee.EEError) as err:
+            eng.load_tables({"config": {"0": [good[0], good[0], cfg]}})
+        assert err.value.code == ee.EE_ERR_ARG and eng.config_table(0) == [good[-1]] * 3
+    eng.close()
+
+
 @pytest.mark.parametrize("case", [(7, 7, 128, 256, 1), (5, 5, 256, 512, 1), (28, 28, 128, 128, 1), (7, 7, 64, 128, 3), (6, 5, 96, 96, 3), (14, 14, 256, 256, 3), (28, 28, 128, 64, 3)],
                          ids=lambda c: "x".join(map(str, c)))
 def test_pooling_for_the_exit_head_rides_on_the_last_layer(torch, ee, orc, case):
