@@ -1193,6 +1193,8 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 ConvArgs probe{};
                 ctx->fill_conv_args(st.first_op + k, buckets[bi], probe);
                 probe.res = res;
+                // the layer that carries the exit head's pooling when it serves: only kernels, and of the one with streamed weights only tiles, that pool
+                if (st.first_op + k == ctx->gap_fuse_op[s]) probe.gap_sums = ctx->sums;
                 std::vector<int> cands;
                 staged(kbytes, [&](int cfg) {
                     cands.push_back(cfg);
@@ -1201,12 +1203,11 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                         for (int kspl = 2; kspl <= (tile == 3 ? 4 : 2); kspl *= 2) cands.push_back(cfg | kspl << 12);
                 });
                 if (conv_stream_supported(probe, es)) cands.push_back(7);               // it has one configuration
-                // not for the layer that carries the exit head's pooling when it serves: that launch needs another kernel
-                if (p.impl == IMPL_MFMA && conv_rows_supported(probe, es) && st.first_op + k != ctx->gap_fuse_op[s])
+                if (p.impl == IMPL_MFMA && conv_rows_supported(probe, es))
                     for (const int cfg : {EE_CFG_ROWS32, EE_CFG_ROWS64}) cands.push_back(cfg);
-                if (p.impl == IMPL_MFMA && conv_taps_supported(probe, es))
+                if (p.impl == IMPL_MFMA)
                     for (const int cfg : TAPS_CFGS)
-                        if (es == 1 || !cfg_taps_shares(cfg)) cands.push_back(cfg);      // bf16: the staged kernels' order of summation
+                        if (conv_taps_config_ok(probe, cfg, es) && (es == 1 || !cfg_taps_shares(cfg))) cands.push_back(cfg);      // bf16: the staged kernels' order of summation
                 if (p.impl == IMPL_MFMA && conv_slab_supported(probe, es) && !conv_taps_default(probe, es))      // never the faster one there
                     staged(kbytes, [&](int cfg) { if ((cfg >> 4 & 15) > 1) cands.push_back(EE_CFG_SLAB | cfg); });
                 if ((long long)buckets[bi] * d.h_out * d.w_out <= EE_SKINNY_MAX_ROWS)          // few pixels: the kernel that splits the reduction over its wavefronts

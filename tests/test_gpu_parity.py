@@ -669,6 +669,21 @@ def test_pooling_for_the_exit_head_rides_on_the_last_layer(torch, ee, orc, case)
     eng.close()
 
 
+def test_tuned_words_of_a_pooling_layer_fit_with_the_pooling(torch, ee):
+    """The layer that pools for the exit head when it serves: the tuner names no tile that covers more than 8 samples (7 blocks of 32 pixels on 5 x 5 images, the
+    fastest one without the pooling at 512 samples and more) or a kernel that does not pool, since the launch that pools could not use it."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, 5, 5, 512, 10)
+    t = net.begin_stage()
+    res = net.conv(t, 512, 1, 1, 0, act="linear")
+    net.end_stage(net.conv(t, 512, 3, 1, 1, res=res))
+    eng = ee.Engine(N._assemble(net, W.DT_I8, 3), 1024)
+    eng.autotune(reps=2)
+    words = eng.config_table(1)
+    assert len(words) == 11 and not set(words) & {0x4431, 0x4432, 0x4231, 0x4232, 7} and max(words) < 0x10000, [hex(w) for w in words]
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 def test_streamed_weights_write_slots(torch, ee, orc, dtype):
     """Zero-copy serving of segments that end in a 3x3 layer with a residual, with the kernel with streamed weights forced wherever it runs (one wavefront per
