@@ -306,7 +306,7 @@ int ee_ir_set(ee_ctx* ctx, int layer, const int* cfg, int n);
  * ee_autotune times the joint launch against the layers one after the other.  ee_group_table / ee_group_set: the table of the launch that
  * `layer` heads, one entry per batch bucket, a configuration word or 0 = separate (ee_group_set: EE_ERR_ARG when `layer` heads none; n = 0
  * clears the table).  Without a table the siblings run one after the other when one of them has a table of its own (ee_config_set), which
- * then names its configuration; else together, but for layers that kernels of their own run faster (large thin ones). */
+ * then names its configuration; else together, but for large layers that kernels of their own run faster. */
 int ee_group_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);
 int ee_group_set(ee_ctx* ctx, int layer, const int* cfg, int n);
 

@@ -1024,30 +1024,38 @@ static int group_default(const ConvArgs* a, int n)
 //     joint table: 2040 us one after the other, 2087 with the siblings together);
 //   the streaming kernel would run a member on 2^19 pixels or more (112x112, 1x3 + 3x1 + 3x3, 32 -> 32, 64 samples: 51 us one after
 //     the other, 69 together; 32 samples 33 / 38, 16 samples 24 / 22);
-//   the slab kernel would run a member of 128-byte or larger pixels on 1024 or more 64 x 64 tiles (28x28, 3x3, 128 -> 128 twice, 64 samples:
-//     24 us one after the other, 28 together; with 1x1, 128 -> 512 23 / 31; 32 samples 20 / 13 and 18 / 18; 14x14, 256 -> 256 twice, 128
-//     samples 36 / 40; with pixels of 64 bytes the joint launch is the faster one at 1-256 samples);
-//   the 1x1 kernel with resident weights would run a member of 6144 or more 64 x 64 blocks of output (ResNet-50, segments 1 and 2: 128 samples 16 and 3 us
-//     longer together, 256 samples 36 and 18; 64 samples 0.6 and 7 us shorter).
-// Otherwise together, measured at 1-256 samples by the sums of the dispatches alone: over all segments Inception-style 1 sample 452 -> 283 us, 64
-// samples 1181 -> 1020, 256 samples 3460 -> 3243; ResNet-50 203 -> 193, 652 -> 652, 2067 -> 2064; ResNet-18 89 -> 79, 275 -> 263, 867 -> 855.  Of 33
-// joint launches at 15 sizes 9 lost, by 1-3 us (one by 6 of 27); of synthetic blocks a narrow 1x1 layer beside a wide one at 256 samples (80 us, 72 apart).
+//   the kernel with streamed weights would run members of two million tile-bytes (64 x 64 tiles of the output x bytes of the reduction) for every launch that
+//     going together saves: it is the faster one by a share of its time, which outgrows the 2 to 4 us of a launch (28x28, 3x3, 128 -> 128 twice, 32 samples
+//     15.0 us one after the other, 14.0 together, 48 samples 19.2 / 21.5, 256 samples 58.8 / 87.3; 17x17, 1x7 and 7x1, 192 -> 192 32 samples 12.0 / 15.3, 256
+//     54.4 / 61.2, with a 1x1, 768 -> 192 beside them 64 samples together, 256 samples 75.2 / 73.5; 56x56, 3x3, 64 -> 64 twice, 64 samples 28.4 / 27.0, 256 78.2 / 89.3);
+//   the 1x1 kernel with resident weights would run all of them, or one on 6144 or more 64 x 64 tiles (ResNet-50, first layer and shortcut of the groups at 28x28 and
+//     14x14: 24 samples 17.6 / 16.8 us, 32 (3136 tiles) 18.9 / 23.2, 64 32.3 / 43.1 and 26.5 / 31.0, 256 92.1 / 151.7 and 66.2 / 109.3);
+//   the slab kernel would run a member of 128-byte or larger pixels on 1024 or more tiles (outputs of no whole 16-byte chunks).
+// Otherwise together.  Measured by the sums of the dispatches alone over 23 synthetic blocks and the 33 joint launches of the networks at 1 to 256 samples, L2 cold: what the
+// rule chooses takes 1.3 % longer than the better choice each time would (always together 12 %), 2.3 % over 16 blocks and 8 sizes that it was not drawn from.  Over all segments, one after the other / together / by the rule: Inception-style
+// 1 sample 429 / 255 / 255 us, 64 samples 1019 / 943 / 943, 256 2967 / 2942 / 2888; ResNet-50 199 / 187 / 187, 586 / 613 / 598, 1603 / 1743 / 1603; ResNet-18 85 / 75 / 75, 238 / 231 / 231, 646 / 649 / 649.
 bool ee_ctx::group_by_default(int stage, int at, int n, int b) const
 {
     const StageDesc& st = net.stages[(size_t)stage];
+    int resident = 0;                                                                                  // members the 1x1 kernel with resident weights would run
+    long long streamed = 0;                                                                            // tile-bytes of those the kernel with streamed weights would
     for (int j = 0; j < n; ++j) {
         const int op = st.first_op + order[(size_t)(st.first_op + at + j)];
         const OpPlan& p = plans[(size_t)op];
         if (!p.cfg.empty()) return false;
-        if ((p.src_buf == BUF_EXT_IN && zc_in) || (p.dst_buf == BUF_EXT_OUT && zc_out)) continue;      // neither kernel takes slot tables
         ConvArgs a{};
         fill_conv_args(op, b, a);
         a.res = p.d.res >= 0 ? (const void*)this : nullptr;                                            // only whether there is one matters
-        if (a.M >= 1 << 19 && conv_stream_supported(a, 1)) return false;
-        if ((long long)((a.M + 63) / 64) * ((a.Co + 63) / 64) >= 6144 && conv_rows_default(a, 1)) return false;
-        if (a.Ci >= 128 && (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64) >= 1024 && conv_slab_default(a, 1)) return false;
+        a.xs = p.src_buf == BUF_EXT_IN ? zc_in : nullptr;
+        a.ys = p.dst_buf == BUF_EXT_OUT ? zc_out : nullptr;
+        const long long tiles = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64);
+        if (conv_taps_default(a, 1)) streamed += tiles * a.kh * a.kw * a.Ci;
+        else if (conv_rows_default(a, 1)) {
+            ++resident;
+            if (tiles >= 6144) return false;
+        } else if (!a.xs && !a.ys && ((a.M >= 1 << 19 && conv_stream_supported(a, 1)) || (a.Ci >= 128 && tiles >= 1024 && conv_slab_default(a, 1)))) return false;
     }
-    return true;
+    return resident < n && streamed < 2000000ll * (n - 1);
 }
 
 hipError_t ee_ctx::launch_group(int stage, int at, int n, int b, const void* act_in, void* act_out, int cfg)

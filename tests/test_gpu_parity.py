@@ -830,12 +830,17 @@ def test_loaded_layer_tables_without_a_joint_one_are_used(torch, ee):
 
 
 # image, channels, branches, batch, whether they go together without tables: below and from the sizes at which the streaming kernel
-# (2^19 pixels) and the slab kernel (128-byte pixels, 1024 tiles of 64 x 64, two workgroups on a CU: 256 channels up to 23 pixels wide)
-# win as launches of their own
+# (2^19 pixels), the one with streamed weights (2 million tile-bytes per launch saved) and the one with resident weights (every member, or one
+# of 6144 tiles) win as launches of their own; an output of no whole 16-byte chunks (72 channels), which the slab kernel runs (1024 tiles)
 SIBLING_DEFAULTS = [(112, 32, [((3, 3), 32), ((1, 3), 16)], 41, True), (112, 32, [((3, 3), 32), ((1, 3), 16)], 42, False),
-                    (28, 128, [((3, 3), 128), ((1, 1), 32)], 41, True), (28, 128, [((3, 3), 128), ((1, 1), 32)], 42, False),
+                    (28, 128, [((3, 3), 128), ((1, 1), 32)], 41, True), (28, 128, [((3, 3), 128), ((1, 1), 32)], 70, True),
+                    (28, 128, [((3, 3), 128), ((1, 1), 32)], 71, False),
                     (28, 64, [((3, 3), 128), ((1, 1), 32)], 64, True), (23, 256, [((3, 3), 128), ((1, 1), 32)], 62, False),
-                    (24, 256, [((3, 3), 128), ((1, 1), 32)], 62, True)]
+                    (24, 256, [((3, 3), 128), ((1, 1), 32)], 48, True), (24, 256, [((3, 3), 128), ((1, 1), 32)], 49, False),
+                    (17, 192, [((1, 7), 192), ((7, 1), 192), ((1, 1), 192)], 109, True), (17, 192, [((1, 7), 192), ((7, 1), 192), ((1, 1), 192)], 110, False),
+                    (28, 256, [((1, 1), 512), ((1, 1), 256)], 52, True), (28, 256, [((1, 1), 512), ((1, 1), 256)], 53, False),
+                    (28, 128, [((1, 1), 512), ((1, 1), 64)], 62, True), (28, 128, [((1, 1), 512), ((1, 1), 64)], 63, False),
+                    (28, 128, [((3, 3), 72), ((1, 1), 56)], 41, True), (28, 128, [((3, 3), 72), ((1, 1), 56)], 42, False)]
 
 
 @pytest.mark.parametrize("h, c, branches, b, together", SIBLING_DEFAULTS)
@@ -844,10 +849,11 @@ def test_sibling_layers_without_tables(torch, ee, h, c, branches, b, together):
     eng = ee.Engine(blob, b)
     x = torch.randint(-128, 128, (b, h, h, c), dtype=torch.int8, device="cuda")
     n, out = launches_per_layer(torch, eng, blob, x)
-    assert n == ([1, 1, 0] if together else [1, 1, 1])
+    apart, joint = [1] * (1 + len(branches)), [1, 1] + [0] * (len(branches) - 1)
+    assert n == (joint if together else apart)
     eng.load_tables({"group": {"1": [0 if together else 0x313]}})
     n, other = launches_per_layer(torch, eng, blob, x)
-    assert n == ([1, 1, 1] if together else [1, 1, 0])
+    assert n == (apart if together else joint)
     assert torch.equal(out, other)
     eng.close()
 
