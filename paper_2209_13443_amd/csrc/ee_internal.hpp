@@ -78,9 +78,9 @@ struct ConvArgs {
     int Hp, Wp, kwp;     // mode 1: padded input dims and padded kernel width
     int shift, res_shift, lo, hi;
     float f_lo, f_hi;
-    int* gap_sums;       // not null (int8, conv_igemm_kernel or conv_skinny_kernel, last layer of a segment): also add the per-sample channel sums of the output into gap_sums[n][Co]
-    const uint16_t* xs;  // not null: sample n of the input is slot xs[n] of x (device memory; conv_igemm_kernel and conv_skinny_kernel only)
-    const uint16_t* ys;  // not null: sample n of the output is slot ys[n] of y (device memory; conv_igemm_kernel and conv_skinny_kernel only)
+    int* gap_sums;       // not null (int8, conv_igemm_kernel, conv_skinny_kernel or conv_taps_kernel, last layer of a segment): also add the per-sample channel sums of the output into gap_sums[n][Co]
+    const uint16_t* xs;  // not null: sample n of the input is slot xs[n] of x (device memory; conv_igemm_kernel, conv_skinny_kernel and conv_rows_kernel only)
+    const uint16_t* ys;  // not null: sample n of the output is slot ys[n] of y (device memory; those and conv_taps_kernel)
 };
 
 // Two chained convolutions in one launch (kernels_pair.hip): c2 is the first layer (its y and res are unused, its
