@@ -206,7 +206,12 @@ typedef struct { int64_t launches; double ms; double ops; double bytes; } ee_ker
 /* enable = 1 brackets every kernel launch with a pair of HIP events; ee_profile_read synchronises,
  * adds the elapsed times up per kernel class into stats[EE_K_COUNT] (host) and, when per_layer is not
  * NULL, per layer of the network into per_layer[number of layers] (host), then resets the counters.
- * ops = 2 * MACs of the launches, bytes = their algorithmic HBM traffic (each operand once). */
+ * ops = 2 * MACs of the launches, bytes = their algorithmic HBM traffic (each operand once).
+ * A launch is booked whole under one class and one layer, also where it runs several layers: joint launches, fused pairs and fused blocks under their
+ * first layer and EE_K_CONV_MFMA (the fused first convolution + max-pool: EE_K_CONV_STREAM); a small segment that runs as one launch (see ee_ir_count) under its
+ * first layer and EE_K_CONV_MFMA, in the stream with its admission and exit head, so that EE_K_ADMIT, EE_K_GAP, EE_K_FC, EE_K_SOFTMAX and the segment's other
+ * layers then read zero.  ops are those of all the layers, bytes leave out what stays on chip.  ee_ir_mode 0 (with ee_pair_mode 0 and joint tables of zeros)
+ * gives every layer and class launches, and figures, of its own. */
 int ee_profile_enable(ee_ctx* ctx, int enable);
 /* creates event pairs ahead of time so that a timed region does not pay for their creation */
 int ee_profile_reserve(ee_ctx* ctx, int64_t n_pairs);

@@ -502,6 +502,32 @@ def test_small_segments_in_one_launch(torch, ee, orc, name):
     eng.close()
 
 
+def test_small_segments_in_the_profile(torch, ee):
+    """What the header says of the kernel timing: a small segment is booked whole under its first layer and the convolution class, exit head and admission
+    included; with the fused blocks off every class and layer has launches of its own.  The operations are the same."""
+    blob = W.load_net("tiny_i8")
+    n = 16
+    eng = ee.Engine(blob, n)
+    pool, lut = dev(torch, W.input_pool(blob, n)), synthetic_lut(blob.n_stages, n)
+    first = [sum(int(st["n_ops"]) for st in blob.stages[:s]) for s in range(blob.n_stages)]
+    seen = {}
+    for mode in (1, 0):
+        eng.ir_mode(mode)
+        eng.profile(True)
+        eng.profile_read(len(blob.ops))
+        _, stats, _ = eng.serve_stream(np.zeros(n, np.int64), pool, lut, refill=0)
+        cls, lay = eng.profile_read(len(blob.ops))
+        eng.profile(False)
+        seen[mode] = sum(c["ops"] for c in cls.values())
+        if mode:
+            assert {k for k, c in cls.items() if c["launches"]} == {"conv_mfma", "compact"} and cls["conv_mfma"]["launches"] == sum(stats["seg_runs"])
+            assert [x["launches"] for x in lay] == [stats["seg_runs"][first.index(k)] if k in first else 0 for k in range(len(lay))]
+        else:
+            assert cls["admit"]["launches"] and cls["softmax"]["launches"] == sum(stats["seg_runs"]) and all(x["launches"] for x in lay)
+    assert seen[0] == seen[1] > 0
+    eng.close()
+
+
 ROWS_CASES = [  # h, w, input bytes per pixel, output channels, stride, samples: no whole tile, ragged last tiles, several tiles per workgroup, every channel grouping
     (1, 1, 128, 256, 1, 1), (5, 7, 128, 512, 1, 3), (9, 11, 256, 128, 2, 5), (56, 56, 128, 256, 1, 25), (13, 6, 256, 1024, 1, 4), (28, 28, 256, 256, 2, 9),
     (14, 14, 512, 512, 1, 7), (8, 8, 512, 128, 1, 3), (10, 10, 1024, 2048, 1, 20), (7, 7, 1024, 128, 1, 2),
