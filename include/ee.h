@@ -139,8 +139,9 @@ typedef struct {
 } ee_serve_opts;
 
 /* 1 when the context can serve with zero_copy = 1: b_max <= 256 and every tensor that crosses a segment boundary is read
- * and written only by layers that kernels with slot tables can run (the general matrix-core convolution and the one for few
- * output pixels; a fused bottleneck block may write it); else 0. */
+ * and written only by layers that kernels with slot tables can run (the general matrix-core convolution, the one for few
+ * output pixels and the 1x1 one with resident weights; the one with streamed weights and fused bottleneck blocks may write it); else 0.
+ * Where a batch needs a slot table, a layer whose entry names another kernel runs the default one. */
 int ee_zero_copy_supported(const ee_ctx* ctx);
 
 /* refill = 2, stage pools, is an extension that is not in the paper.  Algorithm 1 keeps one active batch

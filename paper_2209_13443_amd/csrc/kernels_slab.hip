@@ -10,6 +10,9 @@
 // are bound by exactly that path (global -> LDS bytes per matrix instruction), so this form moves 0.4 - 0.6 x the
 // bytes and can afford tall tiles (256 rows), which halve the weight traffic again.
 //
+// kernels_taps.hip is the faster form wherever it runs; this one is left with the layers whose output is no whole 16-byte chunks (72 int8 channels, 100 bf16 ones),
+// and with stored tables that name it.
+//
 // Copies, swizzle, fragment layout, pipelining of a reduction step and epilogue are those of conv_igemm_kernel
 // (kernels_igemm.hip, igemm_epilogue.hpp).  Taps outside the image read a block of zeros in LDS (selected per lane
 // from a closed-form validity mask), so zero padding costs nothing and the matrix instruction count is uniform.
@@ -279,12 +282,13 @@ static size_t slab_lds_bytes(const ConvArgs& a, int es, int bm, int bn, int ks, 
     return (front > (size_t)tile ? front : (size_t)tile) + (a.res != nullptr && (a.Co * es) % 16 == 0 ? tile : 0) + 1024;
 }
 
-// Untuned: the configuration of a layer this kernel is the faster one for, else 0; asked behind conv_taps_default, i.e. for layers whose output is not whole
-// 16-byte chunks or whose reduction is outside what that rule covers.  Measured like the rule of the general kernel, from two rounds of 64 x 64 tiles.  Below four rounds 128 x 64 tiles and long steps, then int8 128 x 128, bf16 128 x 64 ones.  What decides is how
-// many workgroups a CU holds, and with it the slab, which grows with the pixel and the rows of the image under the window: while two fit
-// (three of the small bf16 tiles) it is up to 19 % faster than the best configuration of the general kernel (3x3 int8: 28x28, 128 -> 128, 64
-// samples 12.0 us against 13.4; 56x56, 64 -> 64 16.4 / 17.5; 20x20, 256 -> 256 17.7 / 20.2; bf16 56x56, 64 -> 64, 64 samples 25.6 / 30.1), beyond
-// it is up to 1.9 times as slow (int8 28x28, 256 -> 256 50.6 / 39.0, 56x56, 256 -> 64 86.0 / 46.3; bf16 28x28, 128 -> 128 27.0 / 23.2).
+// Untuned: the configuration of a layer this kernel is the faster one for, else 0; asked behind conv_taps_default, which takes every such layer whose output is whole
+// 16-byte chunks.  From two rounds of 64 x 64 tiles; below four rounds 128 x 64 tiles and long steps, then int8 128 x 128, bf16 128 x 64 ones.  What decides is
+// how many workgroups a CU holds, and with it the slab, which grows with the pixel and the rows of the image under the window: only while two fit (three of the small
+// bf16 tiles); with one it was up to 1.9 times as slow as the general kernel (int8 28x28, 256 -> 256, 64 samples 50.6 us against 39.0).  Layers it is left with, best
+// configuration of the general kernel / this choice, us: int8 28x28, 128 -> 120 64 samples 14.9 / 13.4, 256 44.2 / 39.3; 128 -> 72 13.4 / 12.2, 39.9 / 35.1; 20x20, 256 -> 200
+// 21.3 / 19.5, 66.8 / 56.9; 14x14, 256 -> 248 12.8 / 12.2, 38.2 / 34.7; bf16 28x28, 64 -> 124 256 samples 46.4 / 41.9, but 64 samples 15.4 / 17.4; 20x20, 128 -> 204 22.0 / 22.4,
+// 70.3 / 71.3 (a tuned table finds 18.7 and 57.1: 128 x 128 tiles of this kernel).
 int conv_slab_default(const ConvArgs& a, int es)
 {
     const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64), kbytes = (long long)a.kh * a.kw * a.Ci * es;
