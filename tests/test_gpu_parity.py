@@ -4,6 +4,7 @@ int8 networks must match bit for bit (activations, logits, labels, scores, exit 
 order, and on the virtual clock the whole schedule).  bf16 networks: logits within 2e-2 of the
 per-sample max-norm, confidences within 1e-3, exit decisions equal unless the oracle's confidence is
 within 1e-3 of the threshold."""
+import re
 import sys
 
 import numpy as np
@@ -457,6 +458,24 @@ def launches_of(eng, f):
     return n
 
 
+def kernels_of(torch, f):
+    """What f returns, and the kernels that it launches, by name with their template arguments, spaces left out."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        out = f()
+        torch.cuda.synchronize()
+    return out, [m.group(1).replace(" ", "") for m in (re.search(r"\bee::(\w+_kernel(?:<[^>]*>)?)", e.name) for e in p.events()) if m]
+
+
+def forced(ee, cfg, f):
+    """What f returns with cfg forced for the whole process (a layer that the named kernel does not cover takes another one)."""
+    old = ee.tune_conv_tile(cfg)
+    try:
+        return f()
+    finally:
+        ee.tune_conv_tile(old)
+
+
 SMALL_SEGMENTS = {  # networks whose every segment runs with its exit head as one launch: the folded first layer; residuals of the segment's input and of a
     # convolution of it, 1x1 and 3x3, one pixel, channels that fill no block of 32, images that are no whole blocks of 32 pixels
     "tiny": lambda: W.load_net("tiny_i8"), "bneck_5x7": lambda: W.bottleneck_net(5, 7, 64, mid=16, stages=3, seed=1), "bneck_1x1": lambda: W.bottleneck_net(1, 1, 64, mid=32, stages=2, seed=2),
@@ -556,6 +575,9 @@ def test_resident_weights_1x1(torch, ee, orc, case, dtype):
     x = W.input_pool(blob, n)
     eng = ee.Engine(blob, n)
     ref = orc.stage_forward(blob, 0, x)
+    for cfg, px in ((0x4231, 32), (0x4232, 64)):                           # the kernel runs on both layers, but for tiles of 64 pixels of 1 KiB
+        names = [k for k in forced(ee, cfg, lambda: kernels_of(torch, lambda: eng.stage_forward(0, dev(torch, x), ref.shape[1:])))[1] if k.startswith("conv_rows")]
+        assert names == [f"conv_rows_kernel<{1 if i8 else 2},{kb},{4 if co == 128 else 8},{px},{residual}>" for residual in ("false", "true") if kb < 1024 or px == 32]
     staged = None
     for cfg in (0x221, 0x4231, 0x4232):
         say(f"[case] {dtype} {case} cfg {cfg:#x}")
@@ -583,6 +605,31 @@ TAPS_CASES = [  # h, w, input bytes per pixel, output channels, kernel (rows, co
 ]
 TAPS_CONFIGS = [0x2231, 0x2331, 0x2431, 0x4331, 0x4431, 0x2432, 0x4432, 0x4234, 0x4334, 0x4434, 0x2232, 0x2332, 0x4332]      # the last four share the reduction between wavefronts
 
+# configuration word -> blocks of 32 pixels, blocks of 32 channels, wavefronts that share a reduction
+TAPS_TILES = {0x2231: (2, 4, 1), 0x2331: (3, 4, 1), 0x2431: (4, 4, 1), 0x4331: (5, 4, 1), 0x4431: (7, 4, 1), 0x2432: (4, 8, 1), 0x4432: (7, 8, 1), 0x4234: (2, 2, 1), 0x4334: (4, 2, 1),
+              0x4434: (2, 2, 2), 0x2232: (2, 4, 2), 0x2332: (4, 4, 2), 0x4332: (2, 2, 4)}
+
+
+def taps_kernel(es, cfg, kb):
+    return "conv_taps_kernel<%d,%d,%d,%d,%d>" % ((es,) + TAPS_TILES[cfg] + (4 if kb % 128 == 0 else 2 if kb % 64 == 0 else 1,))
+
+
+def taps_runs(w, kb, kh, kw, es, cfg, residual, pooled_pixels=0):
+    """Whether the kernel with streamed weights has the tile on a layer over pixels of kb bytes in rows of w: tiles of other than 2 and 4 blocks need whole runs of 128 bytes, bf16
+    ones of 64; LDS holds a pixel of zeros and the slab (rows 16 bytes longer than a pixel, whole copies of the workgroup), partial sums over them, the output tile (behind
+    them where a residual is staged) and, pooling for the exit head, 8 rows of sums for the samples a tile touches (pooled_pixels: of a sample)."""
+    tm, nw, kp = TAPS_TILES[cfg]
+    if kb % (32 * es) or (kb % 128 and tm not in (2, 4)):
+        return False
+    copies = 64 * nw * kp
+    slab = -(-(32 * tm + (kh - 1) * w + kw - 1) * (kb // 16 + 1) // copies) * copies * 16
+    parts = min(tm, kp) * (kp - 1) * nw * -(-tm // kp) * 4096 if kp > 1 else 0
+    tile, front = 32 * tm * 32 * nw * es, max(kb + slab, parts)
+    lds = front + tile if residual else max(front, parts + tile)
+    if pooled_pixels:
+        lds += 8 * 32 * nw * 4
+    return lds <= 160 * 1024 and not (pooled_pixels and (32 * tm - 1) // pooled_pixels + 2 > 8)
+
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 @pytest.mark.parametrize("case", TAPS_CASES, ids=lambda c: "x".join(map(str, c)))
@@ -606,6 +653,10 @@ def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
     x = W.input_pool(blob, n)
     eng = ee.Engine(blob, n)
     ref = orc.stage_forward(blob, 0, x)
+    for cfg in TAPS_CONFIGS:                                               # the tile runs on the layers where it exists
+        names = [k for k in forced(ee, cfg, lambda: kernels_of(torch, lambda: eng.stage_forward(0, dev(torch, x), ref.shape[1:])))[1] if k.startswith("conv_taps")]
+        runs = [taps_runs(w, kb, kh, kw, 1 if i8 else 2, cfg, residual) for residual in (False, True)]
+        assert names == [taps_kernel(1 if i8 else 2, cfg, kb) for run in runs if run], (hex(cfg), runs)
     staged = None
     for cfg in [0x221] + TAPS_CONFIGS:
         say(f"[case] {dtype} {case} cfg {cfg:#x}")
@@ -662,7 +713,7 @@ def test_loaded_words_are_checked_against_the_layer(torch, ee, orc, case):
     eng.close()
 
 
-@pytest.mark.parametrize("case", [(7, 7, 128, 256, 1), (5, 5, 256, 512, 1), (28, 28, 128, 128, 1), (7, 7, 64, 128, 3), (6, 5, 96, 96, 3), (14, 14, 256, 256, 3), (28, 28, 128, 64, 3)],
+@pytest.mark.parametrize("case", [(7, 7, 128, 256, 1), (5, 5, 256, 512, 1), (28, 28, 128, 128, 1), (7, 7, 64, 128, 3), (6, 5, 96, 96, 3), (14, 14, 256, 256, 3), (28, 28, 128, 64, 3), (5, 5, 128, 128, 3)],
                          ids=lambda c: "x".join(map(str, c)))
 def test_pooling_for_the_exit_head_rides_on_the_last_layer(torch, ee, orc, case):
     """Segments that end in a 1x1 or 3x3 layer with a residual, served with every kernel that adds up the exit head's channel sums in its own launch (blocks of
@@ -691,6 +742,13 @@ def test_pooling_for_the_exit_head_rides_on_the_last_layer(torch, ee, orc, case)
         finally:
             ee.tune_conv_tile(old)
         assert np.array_equal(got["label"], label) and np.array_equal(got["conf"], conf), f"{cfg:#x}"
+        # no kernel pools apart, and the forced one runs in each of the four batches where it exists; that with resident weights does not pool: on the first layer
+        names = forced(ee, cfg, lambda: kernels_of(torch, lambda: eng.serve_stream(np.zeros(n, np.int64), dev(torch, x), lut, refill=0)))[1]
+        assert names and not [name for name in names if name.startswith("gap_")]
+        if k == 1 and cfg in (0x4231, 0x4232):
+            assert names.count(f"conv_rows_kernel<1,{ci},{4 if co == 128 else 8},{32 if cfg == 0x4231 else 64},false>") == 4
+        elif cfg in TAPS_TILES:
+            assert names.count(taps_kernel(1, cfg, ci)) == 4 * (taps_runs(w, ci, k, k, 1, cfg, False) + taps_runs(w, ci, k, k, 1, cfg, True, h * w))
     assert np.unique(conf).size > 8
     eng.close()
 
