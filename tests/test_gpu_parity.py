@@ -476,6 +476,63 @@ def forced(ee, cfg, f):
         ee.tune_conv_tile(old)
 
 
+def scattering_order(exits, n_stages, b_max, n):
+    """n requests out of a few that leave at the given exits: of every full batch of every level the last one goes on and the others leave.  Sample slots are
+    taken in runs from the lowest one up, so what the first few batches leave behind breaks up every run of b_max of them: later full batches write through a slot table."""
+    at = [np.flatnonzero(exits == e) for e in range(n_stages)]
+    k = np.arange(n)
+    want = sum((k % b_max ** l == b_max ** l - 1).astype(int) for l in range(1, n_stages))
+    return np.array([at[e][i % len(at[e])] for i, e in zip(k, want)])
+
+
+def steps_with_tables(events, exit_idx, n_stages, n_slots, by_value=0):
+    """A one-lane stage-pool stream served zero-copy, from its events and the exits taken (first fit over a level's slots, inputs free when a step ends): per level the steps
+    whose output slots were no run, and all steps of more than by_value samples with a table for either side."""
+    waiting = [[(k, 0) for k in range(len(exit_idx))]] + [[] for _ in range(n_stages - 1)]
+    taken = [np.zeros(n_slots, bool) for _ in range(n_stages)]
+    outputs, either = [0] * (n_stages - 1), 0
+    for ev in events:
+        if ev["kind"] != 2:                                                # a step
+            continue
+        s, b = int(ev["stage"]), int(ev["b"])
+        batch, waiting[s] = waiting[s][:b], waiting[s][b:]
+        gather = s > 0 and [slot for _, slot in batch] != list(range(batch[0][1], batch[0][1] + b))
+        scatter = False
+        if s + 1 < n_stages:
+            runs = [i for i in range(n_slots - b + 1) if not taken[s + 1][i:i + b].any()]
+            slots = list(range(runs[0], runs[0] + b)) if runs else np.flatnonzero(~taken[s + 1])[:b].tolist()
+            scatter = not runs
+            outputs[s] += scatter
+            kept = [(k, slot) for (k, _), slot in zip(batch, slots) if exit_idx[k] > s]
+            waiting[s + 1] += kept
+            taken[s + 1][[slot for _, slot in kept]] = True
+        either += b > by_value and (gather or scatter)
+        if s > 0:
+            taken[s][[slot for _, slot in batch]] = False
+    return outputs, either
+
+
+def scattered_stream(torch, eng, pool, n, b_max):
+    """n requests out of the pool in scattering_order: a function that serves them and returns results and kernels; zero-copy on one lane it checks that full batches of the
+    first level, and of the deeper ones that see enough of them, wrote through slot tables."""
+    n_stages = eng.n_stages
+    lut = synthetic_lut(n_stages, b_max)
+    exits = eng.serve_stream(np.zeros(len(pool), np.int64), dev(torch, pool), lut, refill=0, b_max=b_max)[0]["exit_idx"]
+    assert all(np.count_nonzero(exits == e) for e in range(n_stages)), np.bincount(exits)
+    dpool = dev(torch, pool[scattering_order(exits, n_stages, b_max, n)])
+
+    def serve(zero_copy, lanes=1):
+        (got, _, events), names = kernels_of(torch, lambda: eng.serve_stream(np.zeros(n, np.int64), dpool, lut, b_max=b_max, refill=2, lanes=lanes, zero_copy=zero_copy, max_events=5000))
+        if zero_copy and lanes == 1:
+            by_value = 64 if names.count("segment_small_i8_kernel") == len(events) else 0        # rows in the arguments of a small segment's launch
+            outputs, either = steps_with_tables(events, got["exit_idx"], n_stages, 5 * eng.b_max, by_value)
+            levels = sum(n >= 8 * b_max ** l for l in range(1, n_stages))
+            assert levels >= 1 and all(outputs[:levels]), outputs
+            assert names.count("upload_slots_kernel") == either            # one launch uploads a step's tables
+        return got, names
+    return serve
+
+
 SMALL_SEGMENTS = {  # networks whose every segment runs with its exit head as one launch: the folded first layer; residuals of the segment's input and of a
     # convolution of it, 1x1 and 3x3, one pixel, channels that fill no block of 32, images that are no whole blocks of 32 pixels
     "tiny": lambda: W.load_net("tiny_i8"), "bneck_5x7": lambda: W.bottleneck_net(5, 7, 64, mid=16, stages=3, seed=1), "bneck_1x1": lambda: W.bottleneck_net(1, 1, 64, mid=32, stages=2, seed=2),
@@ -518,6 +575,12 @@ def test_small_segments_in_one_launch(torch, ee, orc, name):
                 assert np.array_equal(got[f], ref[f]), (f, refill, lanes, bm, zc)
             assert gst == rst and np.array_equal(gev, rev)
     assert np.count_nonzero(np.bincount(ref["exit_idx"])) > 1
+    if eng.zero_copy_supported():
+        for bm in (72, 64):                                                # output rows that are no run: out of the device's table, by value
+            say(f"[case] {name} scattered slots b_max={bm}")
+            serve = scattered_stream(torch, eng, x, 12 * bm, bm)
+            want, got = serve(0)[0], serve(1)[0]
+            assert all(np.array_equal(got[f], want[f]) for f in ("exit_idx", "label", "conf", "score"))
     eng.close()
 
 
@@ -807,12 +870,21 @@ def test_streamed_weights_write_slots(torch, ee, orc, dtype):
         for f in ("exit_idx", "label", "conf", "score"):
             assert np.array_equal(got[f], want[f]), (f, cfg, zc)
     assert np.count_nonzero(np.bincount(want["exit_idx"], minlength=3)) > 1
+    serve = scattered_stream(torch, eng, pool, 512, b_max)                 # the same with output slots that are no run, in a kernel that ends each of 73 steps
+    want = None
+    for cfg, zc in ((0x221, 0), (0x2231, 1), (0x4334, 1), (0x2431, 1)):
+        say(f"[case] scattered slots {dtype} cfg {cfg:#x} zero_copy {zc}")
+        got, names = forced(ee, cfg, lambda: serve(zc))
+        assert cfg == 0x221 or names.count(taps_kernel(1 if i8 else 2, cfg, 64 if i8 else 128)) == 73
+        want = got if want is None else want
+        for f in ("exit_idx", "label", "conf", "score"):
+            assert np.array_equal(got[f], want[f]), (f, cfg, zc)
     eng.close()
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 def test_resident_weights_1x1_takes_slot_tables(torch, ee, orc, dtype):
-    """Zero-copy serving with the kernel forced wherever it runs (the layers that read a segment's input, bf16 also those that write its output)."""
+    """Zero-copy serving with the kernel forced wherever it runs, on layers that read a segment's input through a slot table (its output slots are runs)."""
     blob = W.bottleneck_net(11, 9, 256, seed=3, blocks=2, stages=3, dtype=W.DT_I8 if dtype == "i8" else W.DT_BF16)
     n, b_max = 64, 8
     pool = W.input_pool(blob, n)
@@ -838,6 +910,40 @@ def test_resident_weights_1x1_takes_slot_tables(torch, ee, orc, dtype):
         for f in ("exit_idx", "label", "conf", "score"):
             assert np.array_equal(got[f], want[f]), (f, cfg, zc)
     assert np.count_nonzero(np.bincount(want["exit_idx"], minlength=3)) > 1
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+def test_resident_weights_1x1_writes_slots(torch, ee, orc, dtype):
+    """Zero-copy serving of segments of two 1x1 layers, of which one reads the segment's input through a slot table and the other writes its output through one (without a
+    residual: int8 launches that pool for the exit head go to another kernel): what every request gets is that of the copying compaction with the staged kernel."""
+    from workloads import nets as N
+    i8 = dtype == "i8"
+    net = N._Net(W.DT_I8 if i8 else W.DT_BF16, 11, 9, 256, 10)
+    for _ in range(3):
+        net.end_stage(net.conv(net.conv(net.begin_stage(), 128, 1, 1, 0), 256, 1, 1, 0))
+    blob = N._assemble(net, net.dtype, 19)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"])) / 127))))
+    b_max = 8
+    pool = W.input_pool(blob, 64)
+    act = pool[:24]
+    for s in range(2):
+        act = orc.stage_forward(blob, s, act)
+        blob.exits[s]["frac_bits"] = 12 if i8 else blob.exits[s]["frac_bits"]
+        blob.exits[s]["thr"] = float(np.median(orc.exit_head(blob, s, act, 0.5)[1]))
+    eng = ee.Engine(blob, b_max)
+    assert eng.zero_copy_supported()
+    serve = scattered_stream(torch, eng, pool, 512, b_max)
+    want = None
+    for cfg, zc in ((0x221, 0), (0x4231, 1), (0x4232, 1), (0x4232, 0)):
+        say(f"[case] scattered slots {dtype} cfg {cfg:#x} zero_copy {zc}")
+        got, names = forced(ee, cfg, lambda: serve(zc))
+        for ci, nb in ((256, 4), (128, 8)):                                # both layers of every step
+            assert cfg == 0x221 or names.count("conv_rows_kernel<%d,%d,%d,%d,false>" % (((1, ci) if i8 else (2, 2 * ci)) + (nb, 32 if cfg == 0x4231 else 64))) == 73
+        want = got if want is None else want
+        for f in ("exit_idx", "label", "conf", "score"):
+            assert np.array_equal(got[f], want[f]), (f, cfg, zc)
     eng.close()
 
 
@@ -1330,7 +1436,21 @@ def test_serve_stream_with_fused_bottleneck_blocks(torch, ee, orc, case):
         for f in ("exit_idx", "label", "score", "latency_ns"):
             assert np.array_equal(got[f], ref[f]), (f, mode, zc)
         assert gst == rst and np.array_equal(gev, rev)
+    serve_scattered_blocks(torch, eng, pool, b_max, lanes, "bneck_block_i8")
     eng.close()
+
+
+def serve_scattered_blocks(torch, eng, pool, b_max, lanes, kernel):
+    """Output slots that are no run: with the blocks fused, one of which ends each of the 73 steps, every request gets what the copying compaction and the layers give it."""
+    serve = scattered_stream(torch, eng, pool, 512, b_max)
+    eng.ir_mode(0)
+    want = serve(0)[0]
+    eng.ir_mode(2)
+    for n_lanes in sorted({1, lanes}):
+        got, names = serve(1, n_lanes)
+        assert sum(name.startswith(kernel) for name in names) >= 73
+        for f in ("exit_idx", "label", "conf", "score"):
+            assert np.array_equal(got[f], want[f]), (f, n_lanes)
 
 
 @pytest.mark.parametrize("case", BN_CASES, ids=lambda c: "x".join(map(str, c)))
@@ -1386,6 +1506,7 @@ def test_serve_stream_with_fused_bottleneck_blocks_bf16(torch, ee, orc, h, w, ci
         for f in ("exit_idx", "label", "conf"):
             assert np.array_equal(got[f], want[f]), (f, mode, zc)
     assert np.all(np.bincount(want["exit_idx"], minlength=3) > 0)
+    serve_scattered_blocks(torch, eng, pool, b_max, 2, "bneck_block_bf16")
     eng.close()
 
 
