@@ -442,8 +442,8 @@ void plan_buffers(ee_ctx* ctx)
 }
 
 // Small segments (int8) that run with their exit head as one launch, a workgroup per sample: a chain of convolutions of 16-channel multiples
-// (residuals from any earlier tensor of the segment), the first one possibly on the folded image, whose operands and tensors of one
-// sample fit 64 KiB of LDS (two workgroups per CU) and whose matrix instructions (at most 512: 2 us on the four SIMDs of one CU) are
+// (residuals from any earlier tensor of the segment), the first one possibly on the folded image, whose operands fit 64 KiB of LDS, all that a
+// workgroup keeps there 80 KiB (two workgroups per CU), and whose matrix instructions (at most 512: 2 us on the four SIMDs of one CU) are
 // less than the launches they replace; the head as for head_small_kernel.  Measured at 1-256 samples (kernels_segment.hip): faster at every size.
 int plan_segments(ee_ctx* ctx)
 {
@@ -532,7 +532,7 @@ int plan_segments(ee_ctx* ctx)
                 ok = d.c_out == e.c && d.h_out * d.w_out == e.h * e.w;
                 a.sums_off = take(L.blocks * 128);
             }
-            ok = ok && at <= 96 * 1024;
+            ok = ok && at <= 80 * 1024;
         }
         if (!ok) continue;
         a.tab_kib = (n_tab * (int)sizeof(SegChunk) + 1023) / 1024;
