@@ -211,6 +211,7 @@ bool conv_rows_supported(const ConvArgs& a, int es)
     if (a.mode != 0 || a.gap_sums || a.kh != 1 || a.kw != 1 || a.pad != 0 || a.pad_w != 0 || !a.wo) return false;
     if ((kb != 128 && kb != 256 && kb != 512 && kb != 1024) || a.Co % 128 != 0 || (a.Co > 128 && a.Co % 256 != 0)) return false;
     if ((a.ldc * es) % 16 != 0 || (a.c_off * es) % 16 != 0 || a.Co > 4096) return false;
+    if ((long long)(a.M / (a.Ho * a.Wo)) * a.H * a.W * kb >= (1ll << 31)) return false;
     return (long long)a.M * a.ldc * es < (1ll << 31) && (long long)a.M * a.Co * es < (1ll << 31);
 }
 
