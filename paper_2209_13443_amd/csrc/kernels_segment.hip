@@ -10,9 +10,9 @@
 //   the head: features, logits, decision, as head_small_kernel.
 // Results are those of the separate kernels bit for bit.
 //
-// Measured on a network of 32 x 32 images (three segments of two 3x3 layers, 16 / 32 / 64 channels, 10 classes): all segments and heads 1 to 256 samples
-// 90-105 us -> 53; streams of 64 requests one by one 2440 -> 1570 us, 64 in 8 slots 561 -> 390, 2000 in 64 slots on two lanes 1210 -> 680, 5000 in 256 slots
-// 875 -> 580.  What bounds it (time stamps, 8.7 us a launch): latency.  0.6 us for the launch's arguments, 1.2 for the requests, 0.7 the folding, 1.5 to 2.5 a
+// Measured on a network of 32 x 32 images (three segments of two 3x3 layers, 16 / 32 / 64 channels, 10 classes) against the layers' own launches, two
+// processes of each in turn: all segments and heads 1 to 256 samples 81-101 us -> 53; streams of 64 requests one by one 2510-2740 -> 1770 us, 64 in 8 slots
+// 557-617 -> 399, 2000 in 64 slots on two lanes 1090-1250 -> 700, 5000 in 256 slots 790-870 -> 590.  What bounds it (time stamps, 8.7 us a launch): latency.  0.6 us for the launch's arguments, 1.2 for the requests, 0.7 the folding, 1.5 to 2.5 a
 // layer (300 instructions per item in one dependent chain and two wavefronts per SIMD), 1.3 the logits and the decision.
 #include "ee_internal.hpp"
 #include "head_device.hpp"
