@@ -18,9 +18,9 @@
 // rounded to bf16 where the layers store them: the results are those of the separate layers bit for bit.
 //
 // Measured at 256 samples of 56 x 56: identity blocks 332 us as three launches, 191 fused (4.3 TB/s in and out); the first block 262 / 177 without its
-// shortcut, 373 / 159 with it.  What bounds the identity blocks: memory.  Counters, 206 samples a launch: 634 MB read, the input 1.9 times (the residual tile is
-// requested two tiles after the same pixels, when little of it can still be in the XCD's L2), 331 MB written, 5.5 TB/s over a launch; read once, the tensors alone would be 120 us
-// at that rate.  The first block reads 86 MB and writes 331 in 151 us: matrix instructions 56 us, LDS 67 us and vector issue about as much at 256 samples, in two halves per
+// shortcut, 373 / 159 with it.  What bounds the identity blocks: memory.  Counters, 208 samples a launch: 626 MB read, the input 1.9 times (the residual tile is
+// requested two tiles after the same pixels, when little of it can still be in the XCD's L2), 335 MB written, 5.6 TB/s over a launch; the tensors alone would be 120 us at
+// that rate.  The first block reads 85 MB and writes 335 in 149 us: matrix instructions 56 us, LDS 67 us and vector issue about as much at 256 samples, in two halves per
 // tile that overlap only through the second wavefront of each SIMD.  Few samples: a whole first segment (first layer included, untuned) of 1
 // sample 59 -> 42 us, 5 samples 77 -> 51, 37 samples 233 -> 140, 256 samples 1542 -> 765, so untuned launches are fused at every size.
 #include "ee_internal.hpp"
