@@ -739,6 +739,34 @@ def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
     eng.close()
 
 
+@pytest.mark.parametrize("dtype, ci, co", [("i8", 128, 72), ("bf16", 64, 100)])
+def test_untuned_slab_kernel(torch, ee, orc, dtype, ci, co):
+    """What untuned launches leave to the slab kernel: 3x3 layers whose output is no whole 16-byte chunks, its three choices of tile and step (two rounds of 64 x 64 tiles,
+    four rounds), against the oracle."""
+    from workloads import nets as N
+    i8 = dtype == "i8"
+    net = N._Net(W.DT_I8 if i8 else W.DT_BF16, 28, 28, ci, 10)
+    net.end_stage(net.conv(net.conv(net.begin_stage(), co, 3, 1, 1), 64, 1, 1, 0))
+    blob = N._assemble(net, net.dtype, 29)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * int(op["kh"]) ** 2) / 127))))
+    x = W.input_pool(blob, 48)
+    ref = orc.stage_forward(blob, 0, x)
+    eng = ee.Engine(blob, 48)
+    for b, tile in ((24, "128,64,256"), (48, "128,128,128" if i8 else "128,64,128")):
+        say(f"[case] untuned slab kernel {dtype} {b} samples")
+        out, names = kernels_of(torch, lambda: eng.stage_forward(0, dev(torch, x[:b]), ref.shape[1:]))
+        assert names[0] == f"conv_slab_kernel<{1 if i8 else 2},{tile}>", names
+        got = host(out, ref)
+        if i8:
+            assert np.array_equal(got, ref[:b]), f"{np.count_nonzero(got != ref[:b])} of {got.size} differ"
+        else:
+            rf, g = bf16_to_f32(ref[:b]).astype(np.float64), bf16_to_f32(got).astype(np.float64)
+            assert np.all(np.abs(g - rf) <= 2e-2 * (np.abs(rf).reshape(b, -1).max(axis=1).reshape(-1, 1, 1, 1) + 1e-30))
+    assert np.unique(ref).size > 8
+    eng.close()
+
+
 LOADED_WORDS = [  # h, input channels, output channels, kernel, stride, words that run on the layer, words that do not
     (14, 128, 128, 3, 1, [0x2231, 0x4431, 0x4332], [0x4231, 0x4232]),
     (14, 128, 128, 3, 2, [0x221], [0x4231, 0x4232, 0x2231, 0x4334]),              # not as large as its input
