@@ -115,8 +115,8 @@ __device__ __forceinline__ void gap_tile_flush(const ConvArgs& a, const int* gac
 // staged residual tile the results replace it in place), then 16-byte stores along the channels.  Every wavefront of the
 // workgroup calls it (it contains a barrier); `active` says whether this wavefront holds accumulators to write.
 // Layers whose pixels are not whole 16-byte chunks (wide == false) store straight from the registers.
-// The short reductions are bound by the instructions here: an int8 value costs two (clamp on the unshifted accumulator, a shift that writes
-// its byte in place: ir_requant_pack) and two more with a residual; 3.75 and 4.75 before, with the bias added here and packing permutes.
+// The short reductions are bound by the instructions here: an int8 value costs 1.75 issue slots (ReLU) or two (ir_requant_pack) and one more with a residual, which a matrix
+// instruction widens (ir_add_residual).
 template <int ES, int BM, int BN, int NT, typename ACC>
 __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsigned char* lds, unsigned ro_off, unsigned bias_off, int m0, int n0,
                                                int wm0, int wn0, int tid, bool has_res, bool wide, bool active)
@@ -144,30 +144,28 @@ __device__ __forceinline__ void igemm_epilogue(const ConvArgs& a, ACC& acc, unsi
     };
     const int swz_l = oswz(frow);
     const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
+    const v4i unit = ES == 1 && has_res ? ir_unit(frow, hi) : v4i{0, 0, 0, 0};
     auto finish = [&](auto res_tag, auto wide_tag) {
         constexpr bool RES = decltype(res_tag)::value, WIDE = decltype(wide_tag)::value;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int r = wm0 + 32 * i + frow;
             const int m = m0 + r;
-            if constexpr (ES == 1 && WIDE) {
-                // a lane's share of a block in the tile: 16 consecutive channels of its pixel, one chunk
+            if constexpr (ES == 1) {
+                if constexpr (WIDE) {
+                    // a lane's share of a block in the tile: 16 consecutive channels of its pixel, one chunk
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    unsigned char* cell = ro + r * OROW + ((((wn0 >> 4) + 2 * j + hi) ^ swz_l) << 4);
-                    if constexpr (RES) {
-                        const v4i rv = *(const v4i*)cell;
-                        const auto s02 = __builtin_amdgcn_permlane32_swap((unsigned)rv[0], (unsigned)rv[1], false, false);
-                        const auto s13 = __builtin_amdgcn_permlane32_swap((unsigned)rv[2], (unsigned)rv[3], false, false);
-                        const unsigned rq[4] = {s02[0], s13[0], s02[1], s13[1]};             // the accumulator layout's quads
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[j][i][4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << a.res_shift;
+                    for (int j = 0; j < TN; ++j) {
+                        unsigned char* cell = ro + r * OROW + ((((wn0 >> 4) + 2 * j + hi) ^ swz_l) << 4);
+                        if constexpr (RES) {
+                            const v4i rv = *(const v4i*)cell;
+                            ir_add_residual(acc[j][i], rv, a.res_shift, unit);
+                        }
+                        *(v4i*)cell = ir_requant_pack<!RES>(acc[j][i], cl, relu);
                     }
-                    *(v4i*)cell = ir_requant_pack<!RES>(acc[j][i], cl);
+                    continue;
                 }
-                continue;
             }
             unsigned char* rowp = ro + r * OROW + 4 * hi * ES;
 #pragma unroll

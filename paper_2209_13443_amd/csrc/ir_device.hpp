@@ -1,5 +1,5 @@
-// Device helpers shared by the fused-block kernels (gfx950): vector types, requantisation bounds, and the
-// clamp / shift / pack of one accumulator tile of v_mfma_i32_32x32x32_i8 into matrix-instruction operand bytes.
+// Device helpers shared by the int8 kernels (gfx950): vector types, requantisation bounds, the clamp / shift / pack of one accumulator tile of
+// v_mfma_i32_32x32x32_i8 into matrix-instruction operand bytes, the residual added by a matrix instruction.
 #pragma once
 #include "ee_internal.hpp"
 
@@ -31,7 +31,7 @@ __device__ __forceinline__ IrClamp ir_clamp(int shift, int lo, int hi)
 // halves: afterwards lane l holds channels 0-15 and lane l + 32 channels 16-31, 4 per dword in order.
 // FRESH: the accumulators come straight out of a matrix instruction (no other instruction has touched them since).
 template <bool FRESH = true>
-__device__ __forceinline__ v4i_r ir_requant_pack(const v16i_r& acc, const IrClamp& c)
+__device__ __forceinline__ v4i_r ir_requant_any(const v16i_r& acc, const IrClamp& c)
 {
     unsigned d0, d1, d2, d3;
     int t0, t1, t2, t3;
@@ -69,6 +69,56 @@ __device__ __forceinline__ v4i_r ir_requant_pack(const v16i_r& acc, const IrClam
     const auto s02 = __builtin_amdgcn_permlane32_swap(d0, d2, false, false);
     const auto s13 = __builtin_amdgcn_permlane32_swap(d1, d3, false, false);
     return v4i_r{(int)s02[0], (int)s02[1], (int)s13[0], (int)s13[1]};
+}
+
+// Bounds 0 .. 127 (ReLU) with a shift of at least 1: v_ashr_pk_u8_i32 shifts two sums, saturates them to 0 .. 255 and writes the two bytes in the time of two ordinary
+// instructions.  Shifted by one less than the layer's shift, and then halved, four bytes at a time: floor(floor(a / 2^(s-1)) / 2) = floor(a / 2^s), and 255 / 2 is 127.
+// 1.75 issue slots per value against 2 above, and in instructions the compiler schedules: no block in front of which a wavefront waits out the matrix
+// instruction.  Bounds 0 .. 96 would need a minimum per value in front, which is slower than the above.
+// Layers alone, 64 samples: 56x56, 64 -> 256 + residual 22.2 -> 20.8 us, 28x28, 512 -> 128 8.6 -> 8.3; folded 7x7 first convolution and pool 30.8 -> 30.0.
+__device__ __forceinline__ bool ir_relu(int shift, int lo, int hi) { return lo == 0 && hi == 127 && shift > 0; }
+__device__ __forceinline__ unsigned ir_relu4(int a, int b, int c, int d, int shift)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 v = {(unsigned short)__builtin_amdgcn_ashr_pk_u8_i32(a, b, shift - 1), (unsigned short)__builtin_amdgcn_ashr_pk_u8_i32(c, d, shift - 1)};
+    return __builtin_bit_cast(unsigned, v) >> 1 & 0x7f7f7f7fu;
+}
+// relu: ir_relu of the layer
+template <bool FRESH = true>
+__device__ __forceinline__ v4i_r ir_requant_pack(const v16i_r& acc, const IrClamp& c, bool relu)
+{
+    if (!relu) return ir_requant_any<FRESH>(acc, c);
+    unsigned d[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d[q] = ir_relu4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3], c.shift);
+    const auto s02 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
+    const auto s13 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+    return v4i_r{(int)s02[0], (int)s02[1], (int)s13[0], (int)s13[1]};
+}
+// four sums as four bytes of a dword, a lowest, with any bounds
+__device__ __forceinline__ unsigned ir_requant4(int a, int b, int c, int d, const IrClamp& k)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    a = min(max(a, k.lo), k.hi); b = min(max(b, k.lo), k.hi); c = min(max(c, k.lo), k.hi); d = min(max(d, k.lo), k.hi);
+    return __builtin_bit_cast(unsigned, (u16x2{(unsigned short)__builtin_amdgcn_ashr_pk_i8_i32(a, b, k.shift), (unsigned short)__builtin_amdgcn_ashr_pk_i8_i32(c, d, k.shift)}));
+}
+
+// The unit matrix as an operand of v_mfma_i32_32x32x32_i8: row (column) m = lane % 32, bytes 16 hi .. 16 hi + 15 of its reduction
+__device__ __forceinline__ v4i_r ir_unit(int m, int hi)
+{
+    v4i_r u;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) u[w] = (m >> 2) == 4 * hi + w ? 1 << (8 * (m & 3)) : 0;
+    return u;
+}
+// acc += res << shift.  res: the residual as it is stored (lane l: channels 0-15 of its pixel, lane l + 32: channels 16-31), which is a matrix-instruction operand; the unit
+// matrix times it is the residual in the accumulators' layout, widened: one matrix instruction instead of two exchanges between the halves and an extraction per value.
+__device__ __forceinline__ void ir_add_residual(v16i_r& acc, const v4i_r& res, int shift, const v4i_r& unit)
+{
+    v16i_r t = {};
+    t = __builtin_amdgcn_mfma_i32_32x32x32_i8(unit, res, t, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] += t[i] << shift;
 }
 
 }  // namespace ee

@@ -69,6 +69,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     int* const l_bs = (int*)(l_m2 + BN_M2_BYTES + BN_SLOT_BYTES);       // shortcut bias (SC)
     const IrClamp cl_s = ir_clamp(a.sh_s, a.lo_s, a.hi_s);
     const IrClamp cl1 = ir_clamp(a.sh_e, a.lo_e, a.hi_e), cl2 = ir_clamp(a.sh_d, a.lo_d, a.hi_d), cl3 = ir_clamp(a.sh_p, a.lo_p, a.hi_p);
+    const bool relu1 = ir_relu(a.sh_e, a.lo_e, a.hi_e), relu2 = ir_relu(a.sh_d, a.lo_d, a.hi_d), relu3 = ir_relu(a.sh_p, a.lo_p, a.hi_p);
 
     if (tid < 64) { l_b1[tid] = a.be[tid]; l_b2[tid] = a.bd[tid]; }
     if (tid < 256) l_b3[tid] = a.bp[tid];
@@ -154,11 +155,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
     // pooling: one more matrix instruction with the packed outputs as the A operand (rows = pixels, reduction = channels) and
     // the identity as B transposes the block: lane (channel, hi) then holds that channel's values of 16 pixels as integers
-    v4i_r ident = v4i_r{0, 0, 0, 0};
-    if constexpr (GAP) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) ident[j] = (m >> 2) == 4 * hi + j ? 1 << (8 * (m & 3)) : 0;
-    }
+    const v4i_r unit = GAP || RES ? ir_unit(m, hi) : v4i_r{0, 0, 0, 0};
     auto last_layer = [&](const v4i_r& d0, const v4i_r& d1) {           // the two reduction steps: channels 0-31 and 32-63 of the lane's pixel block
         __builtin_amdgcn_sched_barrier(0);                              // nothing of this moves into the first half
         if constexpr (SC) {
@@ -169,7 +166,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 v16i_r acc = bias16(l_bs, cb0 + c);
                 acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wsc[c][0], x0, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wsc[c][1], x1, acc, 0, 0, 0);
-                rr[c] = ir_requant_pack(acc, cl_s);                     // 16 channels per lane in pixel order: what the layer would have stored
+                rr[c] = ir_requant_any(acc, cl_s);                     // 16 channels per lane in pixel order: what the layer would have stored
             }
         }
         v4i_r out[2];
@@ -179,18 +176,9 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w3[c][0], d0, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w3[c][1], d1, acc, 0, 0, 0);
             if constexpr (RES) {
-                // the residual in the store layout, then back into the accumulator layout
-                const auto s02 = __builtin_amdgcn_permlane32_swap((unsigned)rr[c][0], (unsigned)rr[c][1], false, false);
-                const auto s13 = __builtin_amdgcn_permlane32_swap((unsigned)rr[c][2], (unsigned)rr[c][3], false, false);
-                const unsigned rq[4] = {s02[0], s13[0], s02[1], s13[1]};
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << a.res_shift;
-                out[c] = ir_requant_pack<false>(acc, cl3);              // every accumulator has been through an addition
-            } else {
-                out[c] = ir_requant_pack(acc, cl3);
+                ir_add_residual(acc, rr[c], a.res_shift, unit);
             }
+            out[c] = ir_requant_pack<!RES>(acc, cl3, relu3);
         }
         if (px_ok) {
             *(v4i_r*)((unsigned char*)a.y + pix_y) = out[0];
@@ -203,7 +191,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 v16i_r tr;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) tr[i] = 0;
-                tr = __builtin_amdgcn_mfma_i32_32x32x32_i8(o, ident, tr, 0, 0, 0);
+                tr = __builtin_amdgcn_mfma_i32_32x32x32_i8(o, unit, tr, 0, 0, 0);
                 int sum = 0;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) sum += tr[i];
@@ -314,7 +302,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                     acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[K1 + k], b[k], acc1, 0, 0, 0);
                 }
                 stage_request(it);
-                v4i_r o0 = ir_requant_pack(acc0, cl1), o1 = ir_requant_pack(acc1, cl1);
+                v4i_r o0 = ir_requant_pack(acc0, cl1, relu1), o1 = ir_requant_pack(acc1, cl1, relu1);
                 if (!in_img) { o0 = v4i_r{0, 0, 0, 0}; o1 = v4i_r{0, 0, 0, 0}; }
                 if (hp < 100) {
                     *(v4i_r*)m1 = o0;
@@ -359,7 +347,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
             for (int k = 0; k < 6; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[12 + k], b0[k], acc, 0, 0, 0);
             stage_request(it);
-            dq = ir_requant_pack(acc, cl2);
+            dq = ir_requant_pack(acc, cl2, relu2);
             *(v4i_r*)(l_m2 + ((pb * 2 + half) * 64 + lane) * 16) = dq;
             }
             __syncthreads();                                            // the halves of the second layer's output are in LDS

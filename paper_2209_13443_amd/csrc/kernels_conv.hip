@@ -53,7 +53,7 @@ __device__ __forceinline__ int requant_i8(int t, int shift, int lo, int hi)
 // channel tiles of a pixel tile run back to back on the same XCD, so the activation rows a tile
 // reads (and the halo rows its neighbours share) stay in one L2.
 template <int ES, int BM, int BN, int WM, int WN, int MODE>
-__global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a, int gm, int gn)
+__global__ __launch_bounds__(256, 2) void conv_mfma_kernel(ConvArgs a, int gm, int gn)
 {
     constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN;
     static_assert(WAVES_M * WAVES_N == 4, "4 wavefronts per workgroup");

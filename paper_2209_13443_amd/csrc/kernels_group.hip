@@ -51,7 +51,7 @@ __device__ __forceinline__ GroupMember group_member(int i)
 }
 
 template <int BM, int BN, int KS, bool PLAIN>
-__global__ __launch_bounds__(256) void conv_group_kernel(ConvGroup g, int n, int ns)
+__global__ __launch_bounds__(256, 2) void conv_group_kernel(ConvGroup g, int n, int ns)
 {
     const int slot = (int)(blockIdx.x >> 3);
     const GroupMember m = group_member(group_pick(g, n, slot));
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void conv_group_kernel(ConvGroup g, int n, int
 }
 
 template <int T, int NW, int TN, bool PLAIN>
-__global__ __launch_bounds__(64 * NW) void conv_group_skinny_kernel(ConvGroup g, int n)
+__global__ __launch_bounds__(64 * NW, 2) void conv_group_skinny_kernel(ConvGroup g, int n)
 {
     const GroupMember m = group_member(group_pick(g, n, (int)blockIdx.x));
     skinny_tile<1, T, NW, TN, PLAIN>(m.a, m.gn, m.magic_gn, m.nk, m.pitch, blockIdx.x - (unsigned)m.first);

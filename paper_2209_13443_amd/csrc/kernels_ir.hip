@@ -223,7 +223,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
 #pragma unroll
                 for (int k = 0; k < MAXK; ++k)
                     if (k < kx32) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(we[k], *(const v4i_r*)(l_x + xoff[j] + k * 32), acc, 0, 0, 0);
-                const v4i_r out = ir_requant_pack(acc, cl_e);
+                const v4i_r out = ir_requant_any(acc, cl_e);
                 if (eoff[j] >= 0) *(v4i_r*)(ebuf + eoff[j]) = out;
             }
     };
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
                 for (int r = 0; r < 3; ++r)
 #pragma unroll
                     for (int c = 0; c < 3; ++c) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wd[3 * r + c], *(const v4i_r*)(win + r * e_row + c * 32), acc, 0, 0, 0);
-                const v4i_r dq = ir_requant_pack(acc, cl_d);
+                const v4i_r dq = ir_requant_any(acc, cl_d);
 #pragma unroll
                 for (int c = 0; c < NCO; ++c) accp[s][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wp[c], dq, accp[s][c], 0, 0, 0);
             }
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
 #pragma unroll
                         for (int e = 0; e < 4; ++e) acc[4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << a.res_shift;
                 }
-                const v4i_r out = ir_requant_pack(acc, cl_p);
+                const v4i_r out = ir_requant_any(acc, cl_p);
                 if constexpr (POOL) {
                     // channel sums of the block's 32 pixels: the results are in operand layout (row = pixel), and times the unit matrix they come back with a
                     // lane per channel and the pixels in its registers

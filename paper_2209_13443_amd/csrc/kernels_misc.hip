@@ -629,7 +629,7 @@ typedef float v4f_m __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf_m __attribute__((ext_vector_type(8)));
 
 template <int ES, int NW>
-__global__ __launch_bounds__(64 * NW) void fc_kernel(HeadArgs a)
+__global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
 {
     __shared__ int part[NW][256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

@@ -24,7 +24,7 @@ namespace ee {
 // ES: element bytes.  BM: pixel rows per workgroup.  BN1: output channels of the first layer (all of them).
 // KS: bytes of the first reduction per ring stage.  BN2: output channels of the second layer per chunk.
 template <int ES, int BM, int BN1, int KS, int BN2>
-__global__ __launch_bounds__(256) void conv_pair_kernel(PairArgs p, int gm, int ns)
+__global__ __launch_bounds__(256, 2) void conv_pair_kernel(PairArgs p, int gm, int ns)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int WM = BM / 2, WN = BN1 / 2, TM = WM / 32, TN = WN / 32;

@@ -42,7 +42,7 @@ struct RowsShape {
 };
 
 template <int ES, int KB, int NB, int RB, bool RES>
-__global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT)) void conv_rows_kernel(ConvArgs a, RowsGrid g)
+__global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_kernel(ConvArgs a, RowsGrid g)
 {
     using Sh = RowsShape<ES, KB, NB, RB>;
     constexpr int RW = Sh::RW, WAVES = Sh::WAVES, NT = Sh::NT, OROW = Sh::OROW, CR = Sh::CR, S = Sh::S;
@@ -110,6 +110,8 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT)) void conv_rows_ker
     };
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(a.y, (short)0, 0x7fffffff, 0x00020000);
     const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
+    const v4i unit = ES == 1 && RES ? ir_unit(m, hi) : v4i{0, 0, 0, 0};
     const int swz = (m / R256) & XMASK;
     using acc_t = typename std::conditional<ES == 1, v16i, v16f>::type;
 
@@ -160,15 +162,9 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT)) void conv_rows_ker
                 unsigned char* cell = orow + (((2 * cb + hi) ^ (m & (CR - 1))) << 4);
                 if constexpr (RES) {
                     const v4i rv = *(const v4i*)cell;
-                    const auto s02 = __builtin_amdgcn_permlane32_swap((unsigned)rv[0], (unsigned)rv[1], false, false);
-                    const auto s13 = __builtin_amdgcn_permlane32_swap((unsigned)rv[2], (unsigned)rv[3], false, false);
-                    const unsigned rq[4] = {s02[0], s13[0], s02[1], s13[1]};             // the accumulator layout's quads
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[i][4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << a.res_shift;
+                    ir_add_residual(acc[i], rv, a.res_shift, unit);
                 }
-                *(v4i*)cell = ir_requant_pack<!RES>(acc[i], cl);
+                *(v4i*)cell = ir_requant_pack<!RES>(acc[i], cl, relu);
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {

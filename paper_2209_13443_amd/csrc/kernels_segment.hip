@@ -107,9 +107,7 @@ __global__ __launch_bounds__(512) void segment_small_i8_kernel(SegRows, const Se
         }
         lds_barrier();
     }
-    v4i ident;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ident[j] = (m >> 2) == 4 * hi + j ? 1 << (8 * (m & 3)) : 0;
+    const v4i unit = ir_unit(m, hi);
 
     // ---- the layers ------------------------------------------------------------------------------------------------------------
     for (int l = 0; l < a.n; ++l) {
@@ -123,6 +121,7 @@ __global__ __launch_bounds__(512) void segment_small_i8_kernel(SegRows, const Se
         const bool last = l == a.n - 1;
         const int px_n = L.Ho * L.Wo, items = (px_n + 31) / 32 * L.blocks;
         const IrClamp cl = ir_clamp(L.shift, L.lo, L.hi);
+        const bool relu = ir_relu(L.shift, L.lo, L.hi);
         for (int it = wave; it < items; it += 8) {
             const int pb = (int)fast_div((unsigned)it, (unsigned)L.blocks, L.magic_blocks), cb = it - pb * L.blocks;
             const int px = 32 * pb + m, pxc = min(px, px_n - 1);
@@ -182,17 +181,9 @@ __global__ __launch_bounds__(512) void segment_small_i8_kernel(SegRows, const Se
             v4i o;
             if (L.res >= 0) {
                 const v4i rv = ch < chunks ? *(const v4i*)(sg_lds + L.res + pxc * L.res_pitch + ch * 16) : v4i{0, 0, 0, 0};
-                const auto s02 = __builtin_amdgcn_permlane32_swap((unsigned)rv[0], (unsigned)rv[1], false, false);
-                const auto s13 = __builtin_amdgcn_permlane32_swap((unsigned)rv[2], (unsigned)rv[3], false, false);
-                const unsigned rq[4] = {s02[0], s13[0], s02[1], s13[1]};
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << L.res_shift;
-                o = ir_requant_pack<false>(acc, cl);
-            } else {
-                o = ir_requant_pack(acc, cl);
+                ir_add_residual(acc, rv, L.res_shift, unit);
             }
+            o = ir_requant_pack(acc, cl, relu);
             const bool mine = live && ch < chunks;
             if (mine) {
                 if (last) *(v4i*)((unsigned char*)y + dst_row * a.out_bytes + px * L.co + ch * 16) = o;
@@ -203,7 +194,7 @@ __global__ __launch_bounds__(512) void segment_small_i8_kernel(SegRows, const Se
                 v16i t;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) t[i] = 0;
-                t = __builtin_amdgcn_mfma_i32_32x32x32_i8(o, ident, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_i32_32x32x32_i8(o, unit, t, 0, 0, 0);
                 int sum = 0;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) sum += t[i];

@@ -4,7 +4,7 @@
 namespace ee {
 
 template <int ES, int T, int NW, int TN, bool PLAIN>
-__global__ __launch_bounds__(64 * NW) void conv_skinny_kernel(ConvArgs a, int gn, unsigned magic_gn, int nk, int pitch)
+__global__ __launch_bounds__(64 * NW, 2) void conv_skinny_kernel(ConvArgs a, int gn, unsigned magic_gn, int nk, int pitch)
 {
     skinny_tile<ES, T, NW, TN, PLAIN>(a, gn, magic_gn, nk, pitch, blockIdx.x);
 }

@@ -29,7 +29,7 @@ namespace ee {
 // reduction axis per weight stage (128 or 256; a pixel's bytes CiB = Ci * ES are a power of two >= 64, so a 32-byte
 // sub-step never straddles two taps).  ns: weight stages in the ring (2..4).
 template <int ES, int BM, int BN, int KS>
-__global__ __launch_bounds__(256) void conv_slab_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, int ns, int cib_log2)
+__global__ __launch_bounds__(256, 2) void conv_slab_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, int ns, int cib_log2)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;

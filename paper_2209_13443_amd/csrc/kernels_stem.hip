@@ -81,6 +81,7 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
         for (int kb = 0; kb < NKB; ++kb) asm volatile("" : "+v"(wreg[j][kb]));
     __syncthreads();
     const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
     const int tpi = t.tiles_x * t.tiles_y;
     // pooling: this lane's items (pooled pixel, channels): tid and tid + 256
     const int pch = tid & 3;
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
             }
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][kb], xr[kb], acc, 0, 0, 0);
-            v4i_r o = ir_requant_pack(acc, cl);
+            v4i_r o = ir_requant_pack(acc, cl, relu);
             if (!exists) o = v4i_r{(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
             if (r < ST_RPIX) *(v4i_r*)(stem_lds + r * ST_PITCH + 32 * j + 16 * hi) = o;
         }
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(256, 3) void conv_pool_i8_kernel(ConvArgs a, void* 
             }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                v4i o = ir_requant_pack(acc[j], cl);
+                v4i o = ir_requant_any(acc[j], cl);
                 if (!exists) o = v4i{(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
                 if (r < SB_RPIX) *(v4i*)(l_conv + r * CP_PITCH + 32 * j + 16 * hi) = o;
             }

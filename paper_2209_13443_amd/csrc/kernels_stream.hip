@@ -14,18 +14,13 @@
 // Wavefronts never wait for one another (no workgroup barrier inside the loop); every wavefront leaves the loop when
 // its strips are used up.
 #include "ee_internal.hpp"
+#include "ir_device.hpp"
 
 namespace ee {
 
 typedef int v4i_s __attribute__((ext_vector_type(4)));
 typedef int v16i_s __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ int stream_med3(int v, int lo, int hi)       // lo <= hi: v clamped to [lo, hi]
-{
-    int r;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "v"(lo), "v"(hi));
-    return r;
-}
 __device__ __forceinline__ unsigned stream_div(unsigned n, unsigned d, unsigned magic)   // n / d, magic = floor(2^32 / d) (- 1 for d == 1)
 {
     unsigned q = __umulhi(n, magic);
@@ -35,7 +30,7 @@ __device__ __forceinline__ unsigned stream_div(unsigned n, unsigned d, unsigned 
 
 // KH kernel rows of BPR 32-byte blocks each; NT tiles of 32 output channels
 template <int KH, int BPR, int NT>
-__global__ __launch_bounds__(256) void conv_stream_i8_kernel(ConvArgs a, int nstrips)
+__global__ __launch_bounds__(256, 2) void conv_stream_i8_kernel(ConvArgs a, int nstrips)
 {
     constexpr int NKB = KH * BPR, ROW_PITCH = NT * 32 + 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char stream_lds[];
@@ -51,6 +46,8 @@ __global__ __launch_bounds__(256) void conv_stream_i8_kernel(ConvArgs a, int nst
 #pragma unroll
         for (int g = 0; g < 4; ++g) breg[j][g] = *(const v4i_s*)((const int*)a.bias + 32 * j + 8 * g + 4 * hi);   // rounding constant included
     }
+    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
     const int cr = a.Co >> 4;                                         // 16-byte chunks per output pixel
     const unsigned char* xb0 = (const unsigned char*)a.x;
     const int px_per_block = 32 / a.Ci;                               // 2 (16 channels) or 1 (32 channels)
@@ -84,16 +81,13 @@ __global__ __launch_bounds__(256) void conv_stream_i8_kernel(ConvArgs a, int nst
         for (int j = 0; j < NT; ++j) {
             v16i_s acc;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0;
+            for (int v = 0; v < 16; ++v) acc[v] = breg[j][v >> 2][v & 3];
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][kb], xm[kb], acc, 0, 0, 0);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                int q[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) q[e] = stream_med3((acc[4 * g + e] + breg[j][g][e]) >> a.shift, a.lo, a.hi);
-                const unsigned lo2 = __builtin_amdgcn_perm((unsigned)q[1], (unsigned)q[0], 0x0c0c0400u), hi2 = __builtin_amdgcn_perm((unsigned)q[3], (unsigned)q[2], 0x0c0c0400u);
-                *(unsigned*)(tile + p * ROW_PITCH + 32 * j + 8 * g + 4 * hi) = __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
+                const unsigned q = relu ? ir_relu4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3], cl.shift) : ir_requant4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3], cl);
+                *(unsigned*)(tile + p * ROW_PITCH + 32 * j + 8 * g + 4 * hi) = q;
             }
         }
         // the wavefront's own tile: its LDS accesses execute in program order, only the compiler must keep that order

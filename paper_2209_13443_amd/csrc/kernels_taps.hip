@@ -214,6 +214,8 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
                             for (int e = 0; e < 4; ++e) acc[i][4 * q + e] += v[e];
                         }
     }
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
+    const v4i unit = ES == 1 && has_res ? ir_unit(frow, hi) : v4i{0, 0, 0, 0};
     auto finish = [&](auto res_tag) {
         constexpr bool RES = decltype(res_tag)::value;
 #pragma unroll
@@ -224,15 +226,9 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
                 unsigned char* cell = orow + (((2 * wn + hi) ^ T::oswz(frow)) << 4);
                 if constexpr (RES) {
                     const v4i rv = *(const v4i*)cell;
-                    const auto s02 = __builtin_amdgcn_permlane32_swap((unsigned)rv[0], (unsigned)rv[1], false, false);
-                    const auto s13 = __builtin_amdgcn_permlane32_swap((unsigned)rv[2], (unsigned)rv[3], false, false);
-                    const unsigned rq[4] = {s02[0], s13[0], s02[1], s13[1]};             // the accumulator layout's quads
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[i][4 * q + e] += __builtin_amdgcn_sbfe((int)rq[q], 8 * e, 8) << a.res_shift;
+                    ir_add_residual(acc[i], rv, a.res_shift, unit);
                 }
-                *(v4i*)cell = ir_requant_pack<!RES && KP == 1>(acc[i], cl);
+                *(v4i*)cell = ir_requant_pack<!RES && KP == 1>(acc[i], cl, relu);
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {

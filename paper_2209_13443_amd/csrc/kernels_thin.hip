@@ -13,20 +13,15 @@
 //   * the strip's 32 x Co output bytes go through LDS so that global stores are 16 bytes per lane along the
 //     channels (a whole strip is contiguous when the layer owns the whole pixel).
 #include "ee_internal.hpp"
+#include "ir_device.hpp"
 
 namespace ee {
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef int v16i_t __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ int thin_med3(int v, int lo, int hi)       // lo <= hi: v clamped to [lo, hi]
-{
-    int r;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "v"(lo), "v"(hi));
-    return r;
-}
 
-__global__ __launch_bounds__(256) void conv_thin_i8_kernel(ThinConvArgs a, int nt, int row_pitch, int units)
+__global__ __launch_bounds__(256, 2) void conv_thin_i8_kernel(ThinConvArgs a, int nt, int row_pitch, int units)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char thin_lds[];
     const int unit = xcd_unit(blockIdx.x, units);
@@ -44,24 +39,22 @@ __global__ __launch_bounds__(256) void conv_thin_i8_kernel(ThinConvArgs a, int n
     for (int d = 0; d < 4; ++d)
         if (16 * hi + 4 * d < a.Ci) xb[d] = *(const int*)(xr + 4 * d);
     unsigned char* tile = thin_lds + wave * 32 * row_pitch;
+    const IrClamp k = ir_clamp(a.shift, a.lo, a.hi);
     __syncthreads();
     for (int j = 0; j < nt; ++j) {
         // weight rows are 32 bytes, zero padded: the wavefront reads 1 KB in one piece
         const v4i_t wa = *(const v4i_t*)((const unsigned char*)a.w + (size_t)(32 * j + p) * 32 + 16 * hi);
         v16i_t acc;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0;
+        for (int g = 0; g < 4; ++g) {
+            const v4i_t b4 = *(const v4i_t*)(lbias + 32 * j + 8 * g + 4 * hi);  // the rounding constant is part of the bias
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * g + e] = b4[e];
+        }
         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wa, xb, acc, 0, 0, 0);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int cl = 32 * j + 8 * g + 4 * hi;
-            const v4i_t b4 = *(const v4i_t*)(lbias + cl);                       // the rounding constant is part of the bias
-            int q[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) q[e] = thin_med3((acc[4 * g + e] + b4[e]) >> a.shift, a.lo, a.hi);
-            const unsigned lo2 = __builtin_amdgcn_perm((unsigned)q[1], (unsigned)q[0], 0x0c0c0400u), hi2 = __builtin_amdgcn_perm((unsigned)q[3], (unsigned)q[2], 0x0c0c0400u);
-            *(unsigned*)(tile + p * row_pitch + cl) = __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
-        }
+        for (int g = 0; g < 4; ++g)
+            *(unsigned*)(tile + p * row_pitch + 32 * j + 8 * g + 4 * hi) = ir_requant4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3], k);
     }
     __syncthreads();
     const int cr = a.Co >> 4;                                         // 16-byte chunks per output pixel

@@ -610,6 +610,37 @@ def test_small_segments_in_the_profile(torch, ee):
     eng.close()
 
 
+@pytest.mark.parametrize("shift", [0, 1, 2, 9, 24])
+@pytest.mark.parametrize("lo, hi", [(0, 127), (-128, 127), (0, 96), (-9, 90)])
+def test_requantisation_bounds_and_shifts(torch, ee, orc, lo, hi, shift):
+    """Every kernel that requantises whole accumulator blocks (streamed, staged, with resident and with streamed weights, with and without a residual) at the shifts and bounds where
+    its forms part: shift 0 and 1, a shift that leaves only the bias, 0 .. 127 and others, against the oracle bit for bit."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, 9, 8, 32, 10)
+    t = net.begin_stage()
+    t = net.conv(t, 64, 3, 1, 1)
+    t = res = net.conv(t, 128, 1, 1, 0)
+    t = net.conv(t, 128, 3, 1, 1)
+    net.end_stage(net.conv(t, 128, 1, 1, 0, res=res))
+    blob = N._assemble(net, net.dtype, 60 + shift)
+    r = np.random.default_rng(100 * shift + hi)
+    for op in blob.ops:
+        w, b = blob.op_weights(op)
+        m = min(127, max(1, int(2 ** shift / np.sqrt(w.size / int(op["c_out"])))))     # results of a few hundred before the bounds
+        w[:] = r.integers(-m, m + 1, size=w.shape)
+        b[:] = r.integers(-2 ** min(30, shift + 7), 2 ** min(30, shift + 7), size=b.shape)
+        op["shift"], op["lo"], op["hi"] = shift, lo, hi
+        op["res_shift"] = min(shift, 22) if int(op["res"]) >= 0 else 0
+    x = r.integers(-128, 128, size=(5, 9, 8, 32), dtype=np.int8)
+    ref = orc.stage_forward(blob, 0, x)
+    eng = ee.Engine(blob, 5)
+    for cfg in (0, 7, 0x221, 0x212, 0x4231, 0x4232, 0x2231, 0x4234):
+        got = forced(ee, cfg, lambda: host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref))
+        assert np.array_equal(got, ref), f"cfg {cfg:#x}: {np.count_nonzero(got != ref)} of {ref.size} differ"
+    assert np.unique(ref).size > 8 and (shift == 24 or (ref.min() == lo and ref.max() == hi))      # at 24 the bias alone decides, within the bounds
+    eng.close()
+
+
 ROWS_CASES = [  # h, w, input bytes per pixel, output channels, stride, samples: no whole tile, ragged last tiles, several tiles per workgroup, every channel grouping
     (1, 1, 128, 256, 1, 1), (5, 7, 128, 512, 1, 3), (9, 11, 256, 128, 2, 5), (56, 56, 128, 256, 1, 25), (13, 6, 256, 1024, 1, 4), (28, 28, 256, 256, 2, 9),
     (14, 14, 512, 512, 1, 7), (8, 8, 512, 128, 1, 3), (10, 10, 1024, 2048, 1, 20), (7, 7, 1024, 128, 1, 2),
