@@ -266,11 +266,14 @@ int ee_config_set(ee_ctx* ctx, int layer, const int* cfg, int n);
  * one layer only, the next, a 1x1 stride-1 convolution (conv2 -> conv3 of a bottleneck block), can run as ONE
  * launch that keeps the intermediate tensor in LDS; results are those of the two separate kernels, bit for bit on
  * the int8 path.  ee_pair_count: how many layers of the network head such a pair.  ee_pair_mode: 0 = never fuse,
- * 1 = as the table says (default; nothing is fused until ee_autotune has timed every fused configuration against the
+ * 1 = as the table says (default; no pair is fused until ee_autotune has timed every fused configuration against the
  * two best separate kernels per batch bucket, or a table was loaded), 2 = fuse every pair.
+ * Where a pair ends a bottleneck block (int8; its second layer has a residual, C = 128 or 256 to 4 C channels) and the next layer, 1x1 back to C, reads the block's output, the second layer and
+ * the next can be ONE launch instead, and with them the pair's first layer when that is 3x3, stride 1, C to C channels; results are those of the separate layers, bit for bit.  In mode 1
+ * they are where the table has such an entry, and without tables of the pair or its three layers where their tiles make a round or two of workgroups.
  * ee_pair_table: like ee_config_table for the fused launch of the pair headed by `layer`; an entry is
- * rows | step << 4 | stages << 8 with rows 1: 128, 2: 64 pixels per workgroup, step 1: 64, 2: 128 bytes, or 0 = the
- * two layers run separately for that bucket.  EE_ERR_ARG for bad arguments. */
+ * rows | step << 4 | stages << 8 with rows 1: 128, 2: 64 pixels per workgroup, step 1: 64, 2: 128 bytes; 0x40000 | t (t = 1, 2: blocks of 32 pixels per wavefront) for the second layer
+ * with the one behind the pair, 0x40010 | t for all three; or 0 = the layers run separately for that bucket.  EE_ERR_ARG for bad arguments. */
 int ee_pair_count(const ee_ctx* ctx);
 int ee_pair_mode(ee_ctx* ctx, int mode);
 int ee_pair_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);

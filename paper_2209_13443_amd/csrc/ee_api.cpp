@@ -363,7 +363,7 @@ void plan_order(ee_ctx* ctx)
             const OpPlan& p = ctx->plans[st.first_op + k];
             level[k] = 1 + std::max(level_of[p.d.src], p.d.res >= 0 ? level_of[p.d.res] : 0);
             level_of[p.d.dst] = std::max(level_of[p.d.dst], level[k]);
-            fused |= p.pair || (p.ir && !p.ir_stem);
+            fused |= p.pair || p.seam || (p.ir && !p.ir_stem);
             order[k] = k;
         }
         if (!fused) {
@@ -407,6 +407,12 @@ void plan_buffers(ee_ctx* ctx)
             // likewise the head of a fused inverted-residual block, over its three layers
             if (k > 1 && ctx->plans[st.first_op + k - 2].ir && ctx->plans[st.first_op + k - 2].ir_last() == 2) read_by(ctx->plans[st.first_op + k - 2].d.src, k);
             if (k > 2 && ctx->plans[st.first_op + k - 3].ir_sc) read_by(ctx->plans[st.first_op + k - 3].d.src, k);
+            // and the layers of a seam
+            if (k > 0 && ctx->plans[st.first_op + k - 1].seam) {
+                read_by(ctx->plans[st.first_op + k - 1].d.src, k);
+                read_by(ctx->plans[st.first_op + k - 1].d.res, k);
+                if (k > 1 && ctx->plans[st.first_op + k - 2].seam_front) read_by(ctx->plans[st.first_op + k - 2].d.src, k);
+            }
             if (k > 0 && (ctx->plans[st.first_op + k - 1].ir_noexp || ctx->plans[st.first_op + k - 1].ir_stem)) read_by(ctx->plans[st.first_op + k - 1].d.src, k);
         }
         buf[0] = BUF_EXT_IN;
@@ -703,6 +709,20 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
                 readers += (o.src == p.d.dst) + (o.res == p.d.dst);
             }
             p.pair = readers == 1 && conv_pair_supported(es, p.d.c_out, p.d.kh, p.d.kw, p.ci_eff, q.d.c_out);
+        }
+    // the seams of bottleneck blocks: a pair whose second layer has a residual, and the 1x1 layer behind it that reads its output, inside the segment
+    for (const StageDesc& st : ctx->net.stages)
+        for (int k = 1; k + 1 < st.n_ops; ++k) {
+            OpPlan& f = ctx->plans[st.first_op + k - 1];
+            OpPlan& p = ctx->plans[st.first_op + k];
+            const OpPlan& q = ctx->plans[st.first_op + k + 1];
+            auto whole = [](const OpPlan& o, int kernel) {
+                const OpDesc& d = o.d;
+                return o.impl == IMPL_MFMA && d.kh == kernel && d.kw == kernel && d.stride == 1 && d.pad == kernel / 2 && d.pad_w == kernel / 2 && d.c_tot == d.c_out && d.c_off == 0;
+            };
+            p.seam = f.pair && whole(p, 1) && whole(q, 1) && p.d.res >= 0 && p.d.res != p.d.src && q.d.res < 0 && q.d.src == p.d.dst && p.d.dst != st.out_tensor &&
+                     q.d.dst != st.out_tensor && conv_seam_supported(es, p.d.c_in, p.d.c_out, q.d.c_out);
+            f.seam_front = p.seam && whole(f, 3) && f.d.src != p.d.res && f.d.c_in == f.d.c_out;
         }
     // inverted-residual blocks one fused launch can take (int8): a 1x1 stride-1 convolution without residual whose output
     // is read only by the next layer, a 3x3 depthwise layer with padding 1, whose output is read only by the layer after
@@ -1076,6 +1096,44 @@ hipError_t ee_ctx::launch_group(int stage, int at, int n, int b, const void* act
     return launch_conv_group(a, n, cfg ? cfg : group_default(a, n), stream);
 }
 
+void ee_ctx::fill_seam_args(int op, int b, bool front, SeamArgs& a) const
+{
+    const OpPlan& p = plans[(size_t)op];
+    const OpPlan& q = plans[(size_t)op + 1];
+    a.w1 = p.wo_dev; a.b1 = p.b_dev; a.w2 = q.wo_dev; a.b2 = q.b_dev;
+    a.H = p.d.h_out; a.W = p.d.w_out; a.M = b * a.H * a.W; a.C = p.d.c_in; a.N1 = p.d.c_out; a.N2 = q.d.c_out;
+    a.magic_hw = (unsigned)(0x100000000ull / (unsigned)(a.H * a.W) - (a.H * a.W == 1));
+    a.magic_w = (unsigned)(0x100000000ull / (unsigned)a.W - (a.W == 1));
+    a.pitch1 = p.Kp / 32; a.pitch2 = q.Kp / 32;
+    a.shift1 = p.d.shift; a.res_shift = p.d.res_shift; a.lo1 = p.d.lo; a.hi1 = p.d.hi; a.shift2 = q.d.shift; a.lo2 = q.d.lo; a.hi2 = q.d.hi;
+    if (!front) return;
+    const OpPlan& f = plans[(size_t)op - 1];
+    a.w0 = f.wo_dev; a.b0 = f.b_dev; a.pitch0 = f.Kp / 32;
+    a.shift0 = f.d.shift; a.lo0 = f.d.lo; a.hi0 = f.d.hi;
+}
+
+int ee_ctx::seam_wanted(int op, int b) const
+{
+    const OpPlan& p = plans[(size_t)op];
+    if (!p.seam || pair_mode != 1) return 0;
+    if ((long long)b * p.d.h_out * p.d.w_out * p.d.c_out >= 1ll << 32) return 0;      // 32-bit offsets into the wide tensor
+    const OpPlan& f = plans[(size_t)op - 1];
+    if (!f.pair_cfg.empty()) return pair_entry(f, b, true);
+    const bool front = f.seam_front;
+    if (!p.cfg.empty() || !plans[(size_t)op + 1].cfg.empty() || !f.cfg.empty()) return 0;      // a layer with a table of its own runs with it
+    SeamArgs a{};
+    fill_seam_args(op, b, front, a);
+    return conv_seam_default(a, front);
+}
+
+hipError_t ee_ctx::launch_seam(int op, int b, const void* src, const void* res, void* dst, void* dst2, int cfg)
+{
+    SeamArgs a{};
+    fill_seam_args(op, b, (cfg & EE_CFG_SEAM_FRONT) != 0, a);
+    a.x = src; a.res = res; a.y1 = dst; a.y2 = dst2;
+    return launch_conv_seam(a, cfg, stream);
+}
+
 hipError_t ee_ctx::launch_pair(int op, int b, const void* src, void* dst, const void* res, int cfg)
 {
     const OpPlan& q = plans[op + 1];
@@ -1185,6 +1243,7 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
         return [=] { if (k > 0) ctx->run_stage((int)s, b, ctx->in_buf[s], ctx->out_buf[s], false, first + k - 1); };
     };
     std::vector<std::vector<float>> best_time(ctx->plans.size());       // per layer and bucket: ms of the best configuration
+    std::vector<std::vector<float>> pair_time(ctx->plans.size());       // and of the fused pair it heads
     for (size_t s = 0; s < ctx->net.stages.size() && !rc; ++s) {
         const StageDesc& st = ctx->net.stages[s];
         for (int k = 0; k < st.n_ops && !rc; ++k) {
@@ -1250,8 +1309,36 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                     return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] { return ctx->launch_pair(st.first_op + k, buckets[bi], src, dst, res, cfg); });
                 });
                 if (found.first < best_time[st.first_op + k][bi] + best_time[st.first_op + k + 1][bi]) best[bi] = found.second;
+                pair_time[st.first_op + k].push_back(found.first);
             }
             if (!rc) p.pair_cfg = best;
+        }
+        // the seams of bottleneck blocks, without and with their 3x3 layer, against the pair or its two layers and the layer behind
+        for (int k = 1; k + 1 < st.n_ops && !rc; ++k) {
+            const int op = st.first_op + k;
+            const OpPlan& p = ctx->plans[op];
+            if (!p.seam) continue;
+            OpPlan& f = ctx->plans[op - 1];
+            const OpPlan& q = ctx->plans[op + 1];
+            auto at = [&](int buf) { return resolve(ctx, buf, ctx->in_buf[s], ctx->out_buf[s]); };
+            for (size_t bi = 0; bi < buckets.size() && !rc; ++bi) {
+                float best_ms = std::min(pair_time[op - 1][bi], best_time[op - 1][bi] + best_time[op][bi]) + best_time[op + 1][bi];
+                for (const int form : {0, (int)EE_CFG_SEAM_FRONT}) {
+                    std::vector<int> cands;
+                    for (int tm = 1; tm <= 2; ++tm)
+                        if (conv_seam_config_ok(EE_CFG_SEAM | form | tm, p.d.c_in, p.d.w_out, f.seam_front)) cands.push_back(EE_CFG_SEAM | form | tm);
+                    if (cands.empty()) continue;
+                    const auto found = fastest(cands, 2, layer_before(s, form ? k - 1 : k, buckets[bi]), [&](int cfg) {
+                        return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] {
+                            return ctx->launch_seam(op, buckets[bi], at(form ? f.src_buf : p.src_buf), at(p.res_buf), at(p.dst_buf), at(q.dst_buf), cfg);
+                        });
+                    });
+                    const float ms = found.first + (form ? 0.f : best_time[op - 1][bi]);
+                    if (ms >= best_ms) continue;
+                    best_ms = ms;
+                    f.pair_cfg[bi] = found.second;
+                }
+            }
         }
     }
     // layers that can share a launch: every configuration of that launch against the layers one after the other
@@ -1381,6 +1468,11 @@ extern "C" int ee_pair_set(ee_ctx* ctx, int op, const int* cfg, int n)
     if (!p.pair) return EE_ERR_ARG;
     for (int i = 0; i < n; ++i) {
         const int tile = cfg[i] & 15, ksel = (cfg[i] >> 4) & 15, ns = (cfg[i] >> 8) & 15;
+        if (cfg[i] > 0 && (cfg[i] & EE_CFG_SEAM)) {                          // the seam of two blocks that this pair is in
+            const OpPlan& q = ctx->plans[(size_t)op + 1];                    // there is one: the pair's second layer
+            if (!q.seam || !conv_seam_config_ok(cfg[i], q.d.c_in, q.d.w_out, p.seam_front)) return EE_ERR_ARG;
+            continue;
+        }
         if (cfg[i] < 0 || (cfg[i] >> 12) || tile > 2 || ksel > 2 || (ns != 0 && (ns < 2 || ns > 4))) return EE_ERR_ARG;
     }
     p.pair_cfg.assign(cfg, cfg + n);
@@ -1581,11 +1673,28 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             int cfg = cfg_force > 0 ? cfg_force : forced_conv_tile();
             const bool q_scatter = k + 1 < st.n_ops && ((zc_out && plans[st.first_op + k + 1].dst_buf == BUF_EXT_OUT) ||
                                                         (gap_fuse_dst && only_op < 0 && st.first_op + k + 1 == gap_fuse_op[(size_t)stage]));
+            if ((p.seam || p.seam_front) && cfg == 0 && only_op == -1 && !xs) {
+                const int at = p.seam ? k : k + 1;                                 // the layer with the residual
+                const OpPlan& w = plans[st.first_op + at];
+                const int sc = zc_in && w.res_buf == BUF_EXT_IN ? 0 : seam_wanted(st.first_op + at, b);
+                if (sc && ((sc & EE_CFG_SEAM_FRONT) != 0) == p.seam_front) {                      // the layers at the seam as one launch
+                    const OpPlan& q = plans[st.first_op + at + 1];
+                    const double wide = (double)w.d.h_out * w.d.w_out * w.d.c_out * es * b, narrow = 2.0 * d.h_out * d.w_out * d.c_out * es * b;      // the wide tensor is not read back, the one in front of it stays on chip
+                    const double f_ops = (p.seam ? 0.0 : ops) + (w.ops_per_sample + q.ops_per_sample) * b;
+                    const double f_bytes = (p.seam ? 0.0 : bytes - narrow) + (w.bytes_per_sample + q.bytes_per_sample) * b + w.weight_bytes + q.weight_bytes - wide;
+                    e = timed(EE_K_CONV_MFMA, f_ops, f_bytes, [&] {
+                        return launch_seam(st.first_op + at, b, src, resolve(this, w.res_buf, act_in, act_out), resolve(this, w.dst_buf, act_in, act_out), resolve(this, q.dst_buf, act_in, act_out), sc);
+                    }, st.first_op + k);
+                    if (e != hipSuccess) return EE_ERR_DEVICE;
+                    i += at + 1 - k;
+                    continue;
+                }
+            }
             if (p.pair && pair_mode > 0 && cfg == 0 && only_op < 0 && !xs && !ys && !q_scatter) {
                 // this layer and the next as one launch, where the table says it is the faster way
                 // (untuned never: with the configurations that untuned launches get, the two layers were faster at every batch of 1-31 samples)
                 if (pair_wanted(p, b)) {
-                    const int pc = p.pair_cfg.empty() ? 0 : p.pair_cfg[std::min<size_t>(bucket_of(b), p.pair_cfg.size() - 1)];
+                    const int pc = pair_entry(p, b, false);
                     const OpPlan& q = plans[st.first_op + k + 1];
                     void* dst2 = resolve(this, q.dst_buf, act_in, act_out);
                     const void* res2 = q.d.res >= 0 ? resolve(this, q.res_buf, act_in, act_out) : nullptr;

@@ -26,6 +26,8 @@ struct OpPlan {
     int group = 0;              // layers of a segment with the same number read nothing of one another: they may run at the same time (see plan_order)
     int group_n = 0;            // > 1: this layer and the group_n - 1 behind it in the launch order can run as one launch (int8)
     std::vector<int> group_cfg; // per batch bucket: configuration of that launch, 0 = every layer by itself; empty = not tuned
+    bool seam = false;          // the 1x1 layer with a residual at the end of a bottleneck block whose output the next layer, a 1x1 one, reads: the two can run as one launch (kernels_seam.hip)
+    bool seam_front = false;    // the 3x3 layer in front of such a layer, which alone reads it: the three can run as one launch
     int ci_eff = 0;             // input channels the matrix-core kernel sees (c_in, or c_in padded to a 16-byte multiple)
     // IMPL_MFMA_S2D: stride-2 first layer over <= 4 channels, run as a stride-1 convolution with a ks2 x ks2 kernel over the
     // zero-padded image folded into Hp x Wp super-pixels of 2 x 2 pixels x 4 channels (Hp, Wp, ks2 reuse the fields above)
@@ -162,8 +164,19 @@ struct ee_ctx {
     hipError_t launch_group(int stage, int at, int n, int b, const void* act_in, void* act_out, int cfg);
     bool pair_wanted(const ee::OpPlan& p, int b) const
     {
-        return p.pair && pair_mode > 0 && (pair_mode == 2 || (!p.pair_cfg.empty() && p.pair_cfg[std::min<size_t>(bucket_of(b), p.pair_cfg.size() - 1)] != 0));
+        return p.pair && pair_mode > 0 && (pair_mode == 2 || pair_entry(p, b, false) != 0);
     }
+    // the pair's entry in its table, if it is one for the pair itself or (seam) for the seam it is in, else 0
+    int pair_entry(const ee::OpPlan& p, int b, bool seam) const
+    {
+        const int cfg = p.pair_cfg.empty() ? 0 : p.pair_cfg[std::min<size_t>(bucket_of(b), p.pair_cfg.size() - 1)];
+        return ((cfg & ee::EE_CFG_SEAM) != 0) == seam ? cfg : 0;
+    }
+    // the configuration of the launch that runs the seam of two blocks, layer op (OpPlan::seam), the one behind it and (EE_CFG_SEAM_FRONT) the one in front of it, or 0: one by one; by
+    // the table of the pair in front or (untuned) rule
+    int seam_wanted(int op, int b) const;
+    void fill_seam_args(int op, int b, bool front, ee::SeamArgs& a) const;       // the tensors are left to the caller
+    hipError_t launch_seam(int op, int b, const void* src, const void* res, void* dst, void* dst2, int cfg);
     bool ir_wanted(int op, int b) const;                         // the fused block headed by layer op, by mode, table or (untuned) rule
     // layers op and op + 1 as one fused launch: src feeds layer op, res and dst belong to layer op + 1
     hipError_t launch_pair(int op, int b, const void* src, void* dst, const void* res, int cfg);

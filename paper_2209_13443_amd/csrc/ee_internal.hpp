@@ -93,6 +93,17 @@ struct PairArgs {
     float f_lo, f_hi;
 };
 
+// The seam of two bottleneck blocks in one launch (kernels_seam.hip): a 3x3 stride-1 layer with padding 1 (C -> C channels; w0 null: not part of the launch), the 1x1 layer with a
+// residual behind it (C -> N1) and the 1x1 layer that reads that one (N1 -> N2).  x is the first of them's input; y1 and y2 are the 1x1 layers' outputs.
+struct SeamArgs {
+    const void* x; const void* res; void* y1; void* y2;
+    const void* w0; const void* b0; const void* w1; const void* b1; const void* w2; const void* b2;    // ready operands (ConvArgs::wo) and padded biases
+    int M, H, W, C, N1, N2;
+    unsigned magic_hw, magic_w;      // floor(2^32 / (H W)), floor(2^32 / W)
+    int pitch0, pitch1, pitch2;      // operand steps of 32 bytes per block of 32 weight rows
+    int shift0, lo0, hi0, shift1, res_shift, lo1, hi1, shift2, lo2, hi2;
+};
+
 // An inverted-residual block in one launch (kernels_ir.hip): 1x1 expansion -> 3x3 depthwise -> 1x1 projection (+ residual).
 // Weights and biases are packed for it when the context is created: expansion rows of Kx bytes (c_in padded with zeros
 // to a multiple of 32) for Ce32 channels (the expanded channels padded to a multiple of 32, padding rows zero), the
@@ -157,6 +168,13 @@ int conv_igemm_default(const ConvArgs& a, int es, long long blocks);      // its
 // the fused pair (ES = element bytes); cfg 0 = chosen by shape
 template <int ES> hipError_t launch_conv_pair(const PairArgs& p, int cfg, hipStream_t s);
 bool conv_pair_supported(int es, int co2, int kh, int kw, int ci, int co3);
+// the seam of two bottleneck blocks (int8); cfg: EE_CFG_SEAM | blocks of 32 pixels per wavefront in the narrow layers (1 or 2) | EE_CFG_SEAM_FRONT: with the 3x3 layer.  Stored in the
+// table of the pair that ends the block
+enum { EE_CFG_SEAM = 0x40000, EE_CFG_SEAM_FRONT = 0x10 };
+bool conv_seam_supported(int es, int c, int n1, int n2);
+bool conv_seam_config_ok(int cfg, int c, int W, bool front);       // cfg names such a launch, it exists there (front: whether the 3x3 layer can be part of it) and fits LDS
+int conv_seam_default(const SeamArgs& a, bool front);              // configuration of an untuned launch, or 0: the layers one by one are faster
+hipError_t launch_conv_seam(const SeamArgs& a, int cfg, hipStream_t s);
 // stride-1 "same" convolutions with the activation slab of a tile resident in LDS (kernels_slab.hip); cfg as documented there
 bool conv_slab_supported(const ConvArgs& a, int es);
 template <int ES> hipError_t launch_conv_slab(const ConvArgs& a, int cfg, hipStream_t s);

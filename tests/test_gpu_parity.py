@@ -641,6 +641,67 @@ def test_requantisation_bounds_and_shifts(torch, ee, orc, lo, hi, shift):
     eng.close()
 
 
+SEAM_CASES = [  # mid channels, h, w, samples: one pixel, tiles with one pixel less, none over and one over, images ending inside a tile, the widest rows that fit
+    (128, 1, 1, 1), (256, 1, 2, 1), (128, 7, 9, 1), (128, 8, 8, 1), (128, 5, 13, 1), (256, 7, 9, 3), (256, 5, 13, 2), (128, 9, 11, 9), (256, 14, 14, 5), (128, 2, 300, 1), (256, 2, 144, 1),
+]
+
+
+@pytest.mark.parametrize("case", SEAM_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_seam_of_two_blocks_as_one_launch(torch, ee, orc, case):
+    """The layers where two bottleneck blocks meet in one launch (both tile sizes, with and without the 3x3 layer), against the oracle and the separate layers, bit for bit; with residuals from a
+    tensor of the segment and from its input, bounds that are not a ReLU's in one block, and a word where none belongs refused."""
+    mid, h, w, b = case
+    say(f"[case] seam {case}")
+    blob = W.bottleneck_net(h, w, 4 * mid, seed=mid + h, blocks=3, mid=mid)
+    for k, (lo, hi) in {1: (-20, 90), 2: (-128, 127), 3: (-7, 127)}.items():
+        blob.ops[k]["lo"], blob.ops[k]["hi"] = lo, hi
+    x = W.input_pool(blob, b)
+    ref = orc.stage_forward(blob, 0, x)
+    assert np.unique(ref).size > 8
+    eng = ee.Engine(blob, b)
+    xd = dev(torch, x)
+    heads = [1, 4]
+    taken = 0
+    for form in (0x40000, 0x40010):
+        for t in (1, 2):
+            word = [form | t] * 3
+            try:
+                eng.load_tables({"pair": {str(k): word for k in heads}})
+            except ee.EEError:
+                assert w > 28                               # rows too wide for LDS with this tile
+                continue
+            taken += 1
+            say(f"[case] seam {case} word {form | t:#x}")
+            n, got = launches_per_layer(torch, eng, blob, xd)
+            assert n == ([1, 1, 1, 0, 1, 1, 0, 1, 1] if form == 0x40000 else [1, 1, 0, 0, 1, 0, 0, 1, 1])
+            got = host(got, ref)
+            assert np.array_equal(got, ref), f"word {form | t:#x}: {np.count_nonzero(got != ref)} of {ref.size} differ"
+    assert taken == 4 if w <= 28 else taken >= 3
+    eng.pair_mode(0)
+    n, got = launches_per_layer(torch, eng, blob, xd)
+    assert n == [1] * 9 and np.array_equal(host(got, ref), ref)
+    for layer, word in ((0, 0x40001), (2, 0x40001), (7, 0x40001), (1, 0x40000), (1, 0x40003), (1, 0x40021), (1, 0x40101), (1, 0x44001)):
+        with pytest.raises(ee.EEError):
+            eng.load_tables({"pair": {str(layer): [word] * 3}})
+    eng.close()
+
+
+@pytest.mark.parametrize("mid, hw, edges", [(128, 28, [(1, 1), (20, 1), (21, 1), (83, 1), (84, 0)]), (256, 14, [(20, 0), (21, 1), (41, 1), (42, 1), (83, 1), (84, 0)])])
+def test_untuned_seams_at_the_edges_of_their_rule(torch, ee, mid, hw, edges):
+    """Without a table: which numbers of samples run the seam as one launch, and the same bytes as layer by layer on both sides of every edge."""
+    blob = W.bottleneck_net(hw, hw, 4 * mid, seed=3, blocks=2, mid=mid)
+    eng = ee.Engine(blob, 84)
+    x = dev(torch, W.input_pool(blob, 84))
+    for b, fused in edges:
+        say(f"[case] untuned seam {mid} {hw} {b}")
+        eng.pair_mode(1)
+        n, got = launches_per_layer(torch, eng, blob, x[:b])
+        assert n == ([1, 1, 0, 0, 1, 1] if fused else [1] * 6), b
+        eng.pair_mode(0)
+        assert torch.equal(got, eng.stage_forward(0, x[:b], blob.stage_out_shape(0))), b
+    eng.close()
+
+
 ROWS_CASES = [  # h, w, input bytes per pixel, output channels, stride, samples: no whole tile, ragged last tiles, several tiles per workgroup, every channel grouping
     (1, 1, 128, 256, 1, 1), (5, 7, 128, 512, 1, 3), (9, 11, 256, 128, 2, 5), (56, 56, 128, 256, 1, 25), (13, 6, 256, 1024, 1, 4), (28, 28, 256, 256, 2, 9),
     (14, 14, 512, 512, 1, 7), (8, 8, 512, 128, 1, 3), (10, 10, 1024, 2048, 1, 20), (7, 7, 1024, 128, 1, 2),
