@@ -187,15 +187,17 @@ std::vector<unsigned char> ir_rounded_bias(const unsigned char* blob, const OpDe
     return out;
 }
 
-// depthwise weights [C][3][3] as ready matrix-instruction operands [group][tap][lane][16]: row m = lane % 32 of diag(w) lies
-// in the lane whose 16 reduction bytes hold byte m
+// depthwise weights [C][3][3] as ready matrix-instruction operands [group][5][lane][16].  The first is diag(w) of tap 0, dense: row m = lane % 32 lies in the lane whose 16 reduction
+// bytes hold byte m.  The k-th of the others is two diagonals side by side, of taps 2k - 1 and 2k, as the 4:2 sparse operand of v_smfmac_i32_32x32x64_i8 (two of every four reduction
+// bytes are kept): lane m + 32 h holds row m of tap 2k - 1 + h, byte m among the two kept ones of its four as the first, or the second where it is the fourth.
 std::vector<unsigned char> ir_diag_operands(const unsigned char* w, int C, int C32)
 {
-    std::vector<unsigned char> wd((size_t)(C32 / 32) * 9 * 64 * 16, 0);
+    std::vector<unsigned char> wd((size_t)(C32 / 32) * 5 * 64 * 16, 0);
     for (int c = 0; c < C; ++c)
         for (int t = 0; t < 9; ++t) {
-            const int g = c / 32, m = c % 32, lane = m + 32 * (m / 16);
-            wd[(((size_t)g * 9 + t) * 64 + lane) * 16 + m % 16] = w[(size_t)c * 9 + t];
+            const int g = c / 32, m = c % 32, k = (t + 1) / 2;
+            const int lane = m + 32 * (t == 0 ? m / 16 : (t - 1) % 2), byte = t == 0 ? m % 16 : m / 4 * 2 + (m % 4 == 3);
+            wd[(((size_t)g * 5 + k) * 64 + lane) * 16 + byte] = w[(size_t)c * 9 + t];
         }
     return wd;
 }

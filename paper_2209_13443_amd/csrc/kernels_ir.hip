@@ -62,7 +62,9 @@ struct IrTile {
 };
 
 constexpr int IR_BATCH = 8, IR_BATCHES = 2;   // 8-byte loads per lane that stage a tile, in batches: ih * iw * cpp <= 4096
-constexpr int IR_MAXCB = 3;                   // blocks of 32 staged pixels per wavefront in the expansion: ih * iw <= 384
+// blocks of 32 staged pixels per wavefront in the expansion: ih * iw <= 384, or, where the wavefronts share the channel groups, 96 (stride 2: 160, a block of 4 x 8 output pixels)
+constexpr int ir_maxcb(int gp, int stride) { return gp && stride == 2 ? 5 : 3; }
+constexpr int IR_SHARED_LDS = 96 * 1024;      // LDS bytes where the wavefronts share the channel groups (their registers leave one workgroup to a CU)
 constexpr int IR_FILL = 4;                    // 16-byte loads per lane that fill a buffer without expansion: ih * iw * 2 <= 1024
 constexpr int IR_MAXK = 5;                    // reduction steps of 32 input channels: c_in <= 160 (template parameter MAXK: 1, 2 or 5)
 
@@ -75,6 +77,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
 {
     constexpr int NW = GP ? GP : 4, NT = 64 * NW;                      // wavefronts and lanes per workgroup
     constexpr bool EXP = MAXK > 0;
+    constexpr int MAXCB = ir_maxcb(GP, STRIDE);
     extern __shared__ __attribute__((aligned(16))) unsigned char ir_lds[];
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -155,9 +158,9 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     // ---- the staged pixels inside the image, in blocks of 32 for the expansion -----------------------------------------
     const int ncb = (npix + 31) >> 5;
     const float inv_sw = __builtin_amdgcn_rcpf((float)sw);              // hp < 2^9: (hp + 1/2) / sw is further from a whole number than the product's error
-    int xoff[IR_MAXCB], eoff[IR_MAXCB];                                 // this lane's pixel in the wavefront's j-th block: byte offsets (eoff < 0: none)
+    int xoff[MAXCB], eoff[MAXCB];                                 // this lane's pixel in the wavefront's j-th block: byte offsets (eoff < 0: none)
 #pragma unroll
-    for (int j = 0; j < IR_MAXCB; ++j) {
+    for (int j = 0; j < MAXCB; ++j) {
         const int hp = (GP ? j : wave + 4 * j) * 32 + m, hpc = min(hp, max(npix - 1, 0));
         const int ry = (int)(((float)hpc + 0.5f) * inv_sw), rx = hpc - ry * sw;
         xoff[j] = ((y0 + ry) * t.iw + x0 + rx) * t.xp + 16 * hi;
@@ -178,9 +181,10 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     }
 
     const unsigned char* const we_lane = (const unsigned char*)a.we + (size_t)m * a.Kx + 16 * hi;       // + g * 32 * Kx + k * 32
-    const unsigned char* const wd_lane = (const unsigned char*)a.wd + (size_t)lane * 16;               // + (g * 9 + tap) * 1024
+    const unsigned char* const wd_lane = (const unsigned char*)a.wd + (size_t)lane * 16;               // + (g * 5 + k) * 1024
     const unsigned char* const wp_lane = (const unsigned char*)a.wp + (size_t)m * a.Ce32 + 16 * hi;     // + cob * 32 * Ce32 + g * 32
-    v4i_r we[EXP ? MAXK : 1], wd[9], wp[NCO];
+    v4i_r we[EXP ? MAXK : 1], wd[5], wp[NCO];
+    const int sparse = 0x11111111 * ((m & 3) == 3 ? 12 : 12 | (m & 3));   // which two of four reduction bytes the lane's row keeps: its own and (of no weight) another
     v16i_r accp[MAXB][NCO];
 #pragma unroll
     for (int s = 0; s < MAXB; ++s)
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     };
     auto load_wd_wp = [&](int g) {
 #pragma unroll
-        for (int k = 0; k < 9; ++k) wd[k] = *(const v4i_r*)(wd_lane + (size_t)(g * 9 + k) * 1024);
+        for (int k = 0; k < 5; ++k) wd[k] = *(const v4i_r*)(wd_lane + (size_t)(g * 5 + k) * 1024);
 #pragma unroll
         for (int c = 0; c < NCO; ++c) wp[c] = *(const v4i_r*)(wp_lane + (size_t)c * 32 * a.Ce32 + g * 32);
     };
@@ -216,12 +220,13 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
         return acc;
     };
     auto expand = [&](int g, unsigned char* ebuf) {
+        const v16i_r bias = bias16(l_be, g);                            // once: read in front of every block it was a quarter of the kernel's LDS traffic
 #pragma unroll
-        for (int j = 0; j < IR_MAXCB; ++j)
+        for (int j = 0; j < MAXCB; ++j)
             if ((GP ? j : wave + 4 * j) < ncb) {                        // wave-uniform
-                v16i_r acc = bias16(l_be, g);
+                v16i_r acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(we[0], *(const v4i_r*)(l_x + xoff[j]), bias, 0, 0, 0);
 #pragma unroll
-                for (int k = 0; k < MAXK; ++k)
+                for (int k = 1; k < MAXK; ++k)
                     if (k < kx32) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(we[k], *(const v4i_r*)(l_x + xoff[j] + k * 32), acc, 0, 0, 0);
                 const v4i_r out = ir_requant_any(acc, cl_e);
                 if (eoff[j] >= 0) *(v4i_r*)(ebuf + eoff[j]) = out;
@@ -262,15 +267,16 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
         }
     };
     auto dw_project = [&](int g, const unsigned char* ebuf) {
+        const v16i_r bias = bias16(l_bd, g);
 #pragma unroll
         for (int s = 0; s < MAXB; ++s)
             if ((GP ? s : dwave + 4 * s) < nblocks) {                   // wave-uniform
-                v16i_r acc = bias16(l_bd, g);
                 const unsigned char* win = ebuf + woff[s];
+                auto tap = [&](int t) { return *(const v4i_r*)(win + t / 3 * e_row + t % 3 * 32); };
+                v16i_r acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wd[0], tap(0), bias, 0, 0, 0);
 #pragma unroll
-                for (int r = 0; r < 3; ++r)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wd[3 * r + c], *(const v4i_r*)(win + r * e_row + c * 32), acc, 0, 0, 0);
+                for (int k = 1; k < 5; ++k)
+                    acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(wd[k], __builtin_shufflevector(tap(2 * k - 1), tap(2 * k), 0, 1, 2, 3, 4, 5, 6, 7), acc, sparse, 0, 0);
                 const v4i_r dq = ir_requant_any(acc, cl_d);
 #pragma unroll
                 for (int c = 0; c < NCO; ++c) accp[s][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wp[c], dq, accp[s][c], 0, 0, 0);
@@ -400,11 +406,36 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
         t.x_bytes = expands ? t.ih * t.iw * t.xp + 128 : 0;             // the last pixel's reduction bytes may be read past its channels
         t.e_bytes = t.ih * (t.iw * 32 + 16);
         if (t.pbw * t.pbh > 4 * maxb || 8 * a.Ce32 + t.x_bytes + 2 * t.e_bytes > 64 * 1024) return false;
-        return expands ? t.ih * t.iw <= 128 * IR_MAXCB && t.ih * t.iw * t.cpp <= 256 * IR_BATCH * IR_BATCHES
+        return expands ? t.ih * t.iw <= 128 * ir_maxcb(0, a.stride) && t.ih * t.iw * t.cpp <= 256 * IR_BATCH * IR_BATCHES
                        : t.ih * t.iw * 2 <= 256 * IR_FILL;
     };
     if (!fits()) return false;
-    for (;;) {                                                          // grow the shorter side in pixels while the tile fits
+    // Few tiles: the wavefronts share the channel groups of a tile of one block, or two where one-block tiles would not all run at once (a workgroup to a CU).  Back to back, the
+    // pixels shared out / the groups, us: 14x14 stride 2, 96 -> 576 -> 160, 1 to 128 samples 19.7 / 10.6; 28x28, 32 -> 192 -> 32, 8 samples 7.9 / 6.2, 48 (672 tiles) 14.3 / 10.9,
+    // 96 15.6 / 17.7; stride 2, 56x56, 24 -> 144 -> 32, 8 samples (224) 8.1 / 6.1, 16 9.3 / 10.0; 28x28, 32 -> 192 -> 64, 32 samples (224) 8.2 / 6.6, 48 9.3 / 10.7; 14x14,
+    // 64 -> 384 -> 64, 128 samples (512) 17.9 / 14.5, 256 20.3 / 26.4, 40 samples in 280 tiles of one block 11.2, in 160 of two 8.3.
+    t.gp = 0;
+    if (a.Ce32 >= (a.Kx == 32 ? 160 : 128) && (a.Kx == 32 || nco >= 2)) {       // the forms that are instantiated
+        const int nw = a.Ce32 >= (a.Kx == 32 ? 160 : 320) ? 8 : 4;
+        const long long limit = nco == 5 ? 2048 : nco >= 2 && a.stride == 1 ? 512 : nco == 1 && a.stride == 1 ? 768 : 256;
+        auto shared_tiles = [&](int blocks) -> long long {                      // how many tiles of that many blocks there are, 0: they do not fit
+            t.pbw = t.pbh = 1;
+            if (blocks == 2) (by_max > 1 && (bx_max == 1 || t.nbh <= t.nbw) ? t.pbh : t.pbw) = 2;
+            if (t.pbw > bx_max || !fits() || 8 * a.Ce32 + t.x_bytes + nw * t.e_bytes + maxb * nco * 4096 > IR_SHARED_LDS) return 0;
+            const int px = t.ih * t.iw;
+            if (expands ? px > 32 * ir_maxcb(nw, a.stride) || px * t.cpp > 64 * nw * IR_BATCH * IR_BATCHES : px * 2 > 64 * IR_FILL) return 0;
+            return (long long)a.B * ((bx_max + t.pbw - 1) / t.pbw) * ((by_max + t.pbh - 1) / t.pbh);
+        };
+        const long long one = shared_tiles(1);
+        long long n = one;
+        if (maxb == 2 && (one == 0 || one > 256)) {
+            n = shared_tiles(2);
+            if (n == 0) n = shared_tiles(1);
+        }
+        if (n > 0 && n <= limit) t.gp = nw;
+        else t.pbw = t.pbh = 1;
+    }
+    while (!t.gp) {                                                     // grow the shorter side in pixels while the tile fits
         const bool can_x = t.pbw < bx_max, can_y = t.pbh < by_max;
         const bool prefer_y = can_y && (!can_x || t.pbh * t.nbh <= t.pbw * t.nbw);
         bool grown = false;
@@ -429,12 +460,6 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
     t.magic_nbw = 65536 / t.nbw + 1;
     t.magic_pbw = 65536 / t.pbw + 1;
     t.total = (int)total;
-    // small images: the wavefronts share the channel groups (instantiated for 2 or more output blocks and 2 or more reduction steps)
-    const int nw = a.Ce32 >= 320 ? 8 : 4;                               // ten or more groups: eight wavefronts
-    t.gp = nco >= 2 && a.Ce32 >= 128 && t.pbw * t.pbh <= maxb && total <= 2048 && 8 * a.Ce32 + t.x_bytes + nw * t.e_bytes + maxb * nco * 4096 <= 64 * 1024 &&
-                   (expands ? a.Kx >= 64 && t.ih * t.iw <= 32 * IR_MAXCB && t.ih * t.iw * t.cpp <= 64 * nw * IR_BATCH * IR_BATCHES
-                            : t.ih * t.iw * 2 <= 64 * IR_FILL)
-               ? nw : 0;
     return true;
 }
 
@@ -452,9 +477,17 @@ static void ir_launch5(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t
 {
     if constexpr (STRIDE == 1) {
         if (a.gap_sums) {
+            if (lds > 64 * 1024) {
+                static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&ir_block_i8_kernel<1, NCO, MAXB, MAXK, GP, true>), hipFuncAttributeMaxDynamicSharedMemorySize, IR_SHARED_LDS);
+                if (granted != hipSuccess) return;
+            }
             EE_LAUNCH((ir_block_i8_kernel<1, NCO, MAXB, MAXK, GP, true>), dim3(xcd_grid(t.total)), dim3(GP ? 64 * GP : 256), lds, s, a, t);
             return;
         }
+    }
+    if (lds > 64 * 1024) {
+        static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP, false>), hipFuncAttributeMaxDynamicSharedMemorySize, IR_SHARED_LDS);
+        if (granted != hipSuccess) return;
     }
     EE_LAUNCH((ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP, false>), dim3(xcd_grid(t.total)), dim3(GP ? 64 * GP : 256), lds, s, a, t);
 }
@@ -477,13 +510,14 @@ static void ir_launch(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t 
             else ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 4>(a, t, lds, s);
             return;
         }
-        if (t.gp == 8) {
+        if (t.gp == 8 && kx32 > 1) {
             if (kx32 <= 2) ir_launch5<STRIDE, NCO, MAXB, 2, 8>(a, t, lds, s);
             else ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 8>(a, t, lds, s);
             return;
         }
     }
-    if (kx32 <= 1) ir_launch5<STRIDE, NCO, MAXB, 1, 0>(a, t, lds, s);
+    if (kx32 <= 1 && t.gp == 8) ir_launch5<STRIDE, NCO, MAXB, 1, 8>(a, t, lds, s);
+    else if (kx32 <= 1) ir_launch5<STRIDE, NCO, MAXB, 1, 0>(a, t, lds, s);
     else if (kx32 <= 2) ir_launch5<STRIDE, NCO, MAXB, 2, 0>(a, t, lds, s);
     else ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 0>(a, t, lds, s);
 }

@@ -180,6 +180,35 @@ def test_fused_inverted_residual_blocks_equal_separate_layers_and_oracle(torch, 
     eng.close()
 
 
+IR_SHARED_CASES = [  # h, w, c_in, expanded, c_out, stride, (samples, wavefronts that share the channel groups or 0: the pixels) at the edges of the rule
+    (14, 14, 96, 576, 160, 2, [(1, 8), (5, 8)]), (28, 28, 32, 192, 32, 1, [(9, 8), (10, 8), (54, 8), (55, 0)]), (28, 28, 32, 192, 64, 2, [(36, 8), (37, 0)]),
+    (14, 14, 64, 384, 64, 1, [(36, 8), (37, 8), (128, 8), (129, 0)]), (13, 14, 24, 160, 32, 2, [(3, 8)]), (13, 11, 32, 192, 32, 1, [(1, 8)]), (5, 6, 64, 128, 48, 1, [(2, 4)]),
+    (15, 17, 64, 256, 144, 2, [(2, 4)]), (9, 9, 32, 128, 16, 1, [(2, 0)]),
+]
+
+
+@pytest.mark.parametrize("case", IR_SHARED_CASES, ids=lambda c: "x".join(map(str, c[:6])))
+def test_wavefronts_that_share_the_channel_groups(torch, ee, orc, case):
+    """Which form of the fused block a number of tiles gets, the forms' results on both sides of every edge against the separate layers, and the first and last samples against the oracle."""
+    h, w, ci, ce, co, stride, edges = case
+    blob = W.inverted_residual_net(h, w, ci, ce, co, stride, seed=h + co)
+    n = max(b for b, _ in edges)
+    x = np.random.default_rng(ce).integers(-128, 128, size=(n, h, w, ci), dtype=np.int8)
+    eng = ee.Engine(blob, n)
+    xd = dev(torch, x)
+    for b, form in edges:
+        say(f"[case] shared channel groups {case[:6]} {b} samples")
+        eng.ir_mode(2)
+        out, names = kernels_of(torch, lambda: eng.stage_forward(0, xd[:b], blob.stage_out_shape(0)))
+        assert len(names) == 1 and names[0].startswith("ir_block_i8_kernel<") and names[0].split(",")[4].strip() == str(form), names
+        eng.ir_mode(0)
+        assert torch.equal(out, eng.stage_forward(0, xd[:b], blob.stage_out_shape(0))), b
+        ends = sorted({0, b - 1})
+        ref = orc.stage_forward(blob, 0, x[ends])
+        assert np.array_equal(host(out[ends], ref), ref) and np.unique(ref).size > 8
+    eng.close()
+
+
 @pytest.mark.parametrize("case", [(9, 11, 16, 48), (28, 28, 32, 192), (14, 14, 96, 576), (7, 7, 160, 320), (12, 20, 16, 0), (1, 1, 16, 32)], ids=lambda c: "x".join(map(str, c)))
 def test_inverted_residual_block_pools_for_the_exit_head(torch, ee, orc, case):
     """A segment that ends in a fused block with a residual, served: the block's launch carries the exit head's pooling (both forms of the kernel,
