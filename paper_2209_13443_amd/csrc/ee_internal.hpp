@@ -107,7 +107,7 @@ struct SeamArgs {
 // An inverted-residual block in one launch (kernels_ir.hip): 1x1 expansion -> 3x3 depthwise -> 1x1 projection (+ residual).
 // Weights and biases are packed for it when the context is created: expansion rows of Kx bytes (c_in padded with zeros
 // to a multiple of 32) for Ce32 channels (the expanded channels padded to a multiple of 32, padding rows zero), the
-// depthwise weights as ready matrix-instruction operands [Ce32 / 32][tap][lane][16] (diagonal matrices), projection rows
+// depthwise weights as ready matrix-instruction operands [Ce32 / 32][5][lane][16] (diagonal matrices, ir_diag_operands), projection rows
 // of Ce32 bytes for NCO * 32 output channels; be and bd include the rounding constants of their shifts.
 struct IrArgs {
     const void* x; const void* res; void* y;

@@ -15,11 +15,12 @@
 //                   wavefronts), written to one of two LDS buffers laid out like the tile (32 bytes per pixel, 16 bytes
 //                   of padding per row); pixels outside the image are zero there from the start and stay zero: the
 //                   depthwise layer pads its input, the *expanded* tensor, with zeros;
-//       depthwise   per block of 32 output pixels nine matrix instructions, one per tap, whose A operand is the
-//                   diagonal matrix diag(w_d[c][tap]) of the group's channels and whose B operand is the 32 channels of
-//                   the tap's input pixels (one 16-byte LDS read per lane): a multiply-add per output and tap costs a
-//                   thirty-second of the instruction, and it is still several times cheaper than byte transposes and
-//                   dot products on the vector ALU;
+//       depthwise   per block of 32 output pixels one dense matrix instruction for the first tap, whose A operand is the diagonal matrix diag(w_d[c][tap]) of the group's channels and
+//                   whose B operand is the 32 channels of the tap's input pixels (one 16-byte LDS read per lane), and four sparse ones (v_smfmac_i32_32x32x64_i8, as fast as a dense
+//                   one of half the reduction) for two taps each: two diagonals side by side keep one of every four reduction bytes, and a 4:2 sparse operand has room for two.  A
+//                   multiply-add per output and tap costs a sixty-fourth of the instruction, and it is still several times cheaper than byte transposes and dot products on the
+//                   vector ALU.  With nine dense ones, and the biases read from LDS in front of every block, the launches took 4-9 % longer (7x7, 160 -> 960 -> 160, 64 samples 13.4 us,
+//                   now 12.5; 14x14, 64 -> 384 -> 64 8.9, now 8.4);
 //       projection  the requantised depthwise outputs of a block are, after one exchange between the two halves of
 //                   the wavefront (v_permlane32_swap), exactly the B operand (32 reduction channels x 32 pixels) of
 //                   the projection, whose accumulators (NCO blocks of 32 output channels per pixel block) stay in
@@ -29,16 +30,14 @@
 //   * Epilogue: projection bias, residual, requantisation, 16-byte stores; for the block that ends a segment also the exit head's pooling (a.gap_sums): a
 //     tile lies in one image, so its channel sums go out with an atomic addition per channel (int32, exact in any order).  Without it the block ran as three launches,
 //     the last with the pooling (serving MobileNetV2, 64 slots, 4,096 requests: 14.65 -> 14.02 ms).
-// Small images (a tile is at most MAXB blocks and 96 staged pixels; few workgroups, many channel groups) run the second
-// form, GP: the four or eight wavefronts of a workgroup share the tile's *channel groups* instead of its pixels.  Each wavefront
+// Few tiles (ir_block_plan) run the second form, GP: tiles of one or two blocks whose four or eight wavefronts share the *channel groups* instead of the pixels.  Each wavefront
 // expands, filters and projects every pixel of the tile for the groups g = wavefront, wavefront + 4 (or 8), ... through a buffer
 // of its own, with no barrier inside the loop; the partial projection sums are added in LDS (integer adds,
 // exact in any order) and the epilogue is shared out by (pixel block, output block).
-// What bounds it: the blocks on large images issue vector instructions for 40-50 % of their time and matrix instructions for
-// 13-26 % (64 images, 2.3 GHz; 112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels: 8.3 M vector and 0.28 M matrix instructions in 29.7 us; 56 x 56,
-// 24 -> 144 -> 24: 5.7 M and 0.45 M in 24.1 us); those on small images wait for their chain of loads, matrix instructions and barriers.
-// With integer divisions, buffers cleared by every tile and output blocks dealt out regardless of the expansion the first took 32.6 us
-// back to back, now 28.5, and 112 x 112, 32 -> 16 without expansion 26.0, now 20.6.
+// What bounds it: blocks on large images the way from a workgroup's start to its first group: copies of the kernel without the groups' loop take 16.7 of 30 us (112 x 112 -> 56 x 56,
+// 16 -> 96 -> 24 channels, 64 images), 9.4 of 22.5 (56 x 56, 24 -> 144 -> 24); the groups themselves use the vector ALU, LDS and matrix cores about alike (5-6 us each of the latter).  Those on small
+// images wait for their chain of loads, matrix instructions and barriers; 7 x 7, 160 -> 960 -> 160 for the 450 KB of weights that a workgroup reads through its CU's path, 3.9 of 11.7 us.
+// (Loading the first group's weights in front of the input, and the next group's ahead in GP, was 0-8 % slower everywhere: weights queue in front of the input.)
 // Every accumulation is int32 and exact, rounding points are those of the three separate layers: results are equal
 // bit for bit.
 #include "ee_internal.hpp"
