@@ -56,6 +56,17 @@ std::vector<unsigned char> bn_operands(const unsigned char* w, int rows, int row
     return out;
 }
 
+// the same for the exit head's 16-row matrix instructions: [row block of 16][step of 64 bytes][lane][16], lane m + 16 q holds bytes 16 q .. 16 q + 15 of the step of row m; zeros outside
+std::vector<unsigned char> head_operands(const unsigned char* w, int rows, int row_bytes)
+{
+    const int steps = (row_bytes + 63) / 64;
+    std::vector<unsigned char> out((size_t)((rows + 15) / 16) * steps * 1024, 0);
+    for (int r = 0; r < rows; ++r)
+        for (int k = 0; k < row_bytes / 16; ++k)
+            std::memcpy(&out[(((size_t)(r / 16) * steps + k / 4) * 64 + r % 16 + 16 * (k % 4)) * 16], w + (size_t)r * row_bytes + 16 * k, 16);
+    return out;
+}
+
 // Packs one layer's weights for its kernel and uploads them with the (padded) bias.
 int pack_op(ee_ctx* ctx, const unsigned char* blob, OpPlan& p)
 {
@@ -768,6 +779,7 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
     int c_max = 0;
     const int n_st = (int)ctx->net.stages.size();
     ctx->wfc_dev.resize(n_st);
+    ctx->wfo_dev.resize(n_st);
     ctx->bfc_dev.resize(n_st);
     for (int s = 0; s < n_st; ++s) {
         const ExitDesc& e = ctx->net.exits[s];
@@ -775,7 +787,8 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
         c_max = std::max(c_max, e.c);
         std::vector<unsigned char> w(base + e.w_off, base + e.w_off + (size_t)e.n_cls * e.c * es);
         std::vector<unsigned char> b(base + e.b_off, base + e.b_off + 4 * (size_t)e.n_cls);
-        if ((rc = upload(ctx, &ctx->wfc_dev[s], w)) || (rc = upload(ctx, &ctx->bfc_dev[s], b))) return fail(rc);
+        if (head_small_weights(e.c * es, e.n_cls) && (rc = upload(ctx, &ctx->wfc_dev[s], w))) return fail(rc);
+        if ((rc = upload(ctx, &ctx->wfo_dev[s], head_operands(w.data(), e.n_cls, e.c * es))) || (rc = upload(ctx, &ctx->bfc_dev[s], b))) return fail(rc);
         if (ctx->stage_out_bytes(s) % 16 != 0 || ctx->stage_in_bytes(s) % 16 != 0) return fail(EE_ERR_UNSUPPORTED);
     }
     ctx->c_max = (size_t)c_max;
@@ -1755,7 +1768,7 @@ HeadArgs ee_ctx::head_args(int stage, int b, const void* act, float thr, int32_t
     a.exp2 = exp2_dev; a.es = net.elem_bytes();
     a.act = act; a.B = b; a.HW = e.h * e.w; a.C = e.c; a.n_cls = e.n_cls;
     a.gap_shift = e.gap_shift; a.frac_bits = e.frac_bits; a.logit_scale = e.logit_scale;
-    a.wfc = wfc_dev[stage]; a.bfc = bfc_dev[stage];
+    a.wfc = wfc_dev[stage]; a.wfo = wfo_dev[stage]; a.bfc = bfc_dev[stage];
     a.sums = own ? own->sums : sums; a.gap_partial = own ? own->gap_partial : gap_partial; a.logits = own ? own->logits : logits;
     a.thr = thr;
     a.s_thr = !(thr > 0.0f) ? INT64_MAX : (thr > 1.0f ? 0 : (int64_t)std::floor(1073741824.0 / (double)thr));

@@ -84,7 +84,7 @@ struct ee_ctx {
     std::vector<size_t> pool_sample_bytes;
     std::vector<void*> pad_bufs;                 // zero-padded 4-channel input copies (first layers)
     std::vector<void*> owned;                    // every device allocation, for ee_destroy
-    std::vector<void*> wfc_dev, bfc_dev;         // exit heads
+    std::vector<void*> wfc_dev, wfo_dev, bfc_dev;         // exit heads
     uint32_t* exp2_dev = nullptr;                // the integer softmax's table
     // segments small enough to run with their exit head as one launch (int8): the launch's plan, n = 0 for the others
     std::vector<ee::SegPlan> seg;

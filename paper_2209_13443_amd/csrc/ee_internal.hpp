@@ -276,7 +276,7 @@ hipError_t launch_avgpool(const PoolArgs& a, int dtype, hipStream_t s);
 struct HeadArgs {
     const void* act; int B, HW, C, n_cls;
     int gap_shift, frac_bits; float logit_scale;
-    const void* wfc; const void* bfc;
+    const void* wfc; const void* wfo; const void* bfc;      // weights as rows (heads that head_small may take, else null) and as ready operands (head_operands)
     int32_t* sums;       // [B][C] int32 sums (i8) or float means (bf16)
     int32_t* gap_partial;   // bf16: [(B + 1024)][C] partial rows of the pooling splits
     void* logits;        // [B][n_cls] int32 / float scratch
@@ -331,6 +331,7 @@ hipError_t launch_head_fc(const HeadArgs& a, int dtype, hipStream_t s);
 hipError_t launch_head_softmax(const HeadArgs& a, int dtype, hipStream_t s);
 // all of it in one launch, for heads small enough (pooled: a.sums holds the sums already)
 bool head_small(const HeadArgs& a, int dtype, bool pooled);
+bool head_small_weights(long long row_bytes, int n_cls);      // its condition on the weights
 hipError_t launch_head_small(const HeadArgs& a, int dtype, bool pooled, hipStream_t s);
 
 // A small segment and its exit head in one launch (int8, kernels_segment.hip).  Tensors of one sample live in LDS: offsets and bytes per pixel.

@@ -618,7 +618,7 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
 
 // ---- exit head, step 2: FC ------------------------------------------------------------------------------
 // logits[b][j] = b_j + sum_c g[b][c] * W[j][c] as a 16 x 16 matrix-core tile per workgroup: rows = 16
-// classes (A operand, weight rows read straight from global memory, 16 bytes per lane), columns = 16
+// classes (A operand, ready operands of 1 KB a step: with rows read 64 bytes at a time the 2048-channel bf16 head of 16 samples took 9.7 us, now 6.8), columns = 16
 // samples (B operand, the pooled features: requantised on the fly for int8; split into a bf16 head and
 // a bf16 remainder for bf16 so that the float mean loses nothing that matters).  The NW wavefronts take
 // every NWth 64-byte step of the reduction and add their partial tiles through LDS.  Bound by latency: NW is chosen so that
@@ -628,36 +628,41 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
 typedef float v4f_m __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf_m __attribute__((ext_vector_type(8)));
 
-template <int ES, int NW>
+// TC: tiles of 16 classes per workgroup
+template <int ES, int NW, int TC>
 __global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
 {
-    __shared__ int part[NW][256];
+    constexpr int U = TC == 1 ? 4 : 2;                          // steps in flight per wavefront
+    __shared__ int part[NW][TC * 256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j0 = blockIdx.x * 16, b0 = blockIdx.y * 16;
+    const int j0 = blockIdx.x * 16 * TC, b0 = blockIdx.y * 16;
     const int r = lane & 15, kq = lane >> 4;
-    const int j = j0 + r, b = b0 + r;
+    const int b = b0 + r;
     const int CB = a.C * ES;                                   // bytes per weight row (a multiple of 16)
-    const int nsteps = (CB + 63) / 64;
-    const unsigned char* wrow = (const unsigned char*)a.wfc + (long long)min(j, a.n_cls - 1) * CB;
-    const bool jin = j < a.n_cls, bin = b < a.B;
-    const v4i zero4 = {0, 0, 0, 0};
-    v4i acci = zero4;
-    v4f_m accf = {0.f, 0.f, 0.f, 0.f};
-    const int jj = j0 + 4 * kq + (wave & 3);                    // a thread of the first four wavefronts finishes element (class jj, sample r)
-    const int bias = ((const int*)a.bfc)[min(jj, a.n_cls - 1)];
-    for (int s0 = wave; s0 < nsteps; s0 += 4 * NW) {
-        v4i wv[4], gv[4][4];
+    const int nsteps = (CB + 63) / 64, last_tile = (a.n_cls + 15) / 16 - 1;
+    const v4i* wtile[TC];                                       // ready operands: 1 KB per step, one contiguous load
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {                           // all loads of 4 steps first
+    for (int t = 0; t < TC; ++t) wtile[t] = (const v4i*)a.wfo + (long long)min((int)blockIdx.x * TC + t, last_tile) * nsteps * 64 + lane;
+    const bool bin = b < a.B;
+    const v4i zero4 = {0, 0, 0, 0};
+    v4i acci[TC];
+    v4f_m accf[TC];
+#pragma unroll
+    for (int t = 0; t < TC; ++t) { acci[t] = zero4; accf[t] = v4f_m{0.f, 0.f, 0.f, 0.f}; }
+    for (int s0 = wave; s0 < nsteps; s0 += U * NW) {
+        v4i wv[U][TC], gv[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                           // all loads of U steps first
             const int kb = (s0 + NW * u) * 64 + kq * 16;
             const bool kin = kb < CB;
-            wv[u] = kin && jin ? *(const v4i*)(wrow + kb) : zero4;
+#pragma unroll
+            for (int t = 0; t < TC; ++t) wv[u][t] = wtile[t][min(s0 + NW * u, nsteps - 1) * 64];      // a step past the last meets features of zero
             const int* sp = a.sums + (long long)min(b, a.B - 1) * a.C + kb / ES;
 #pragma unroll
             for (int q = 0; q < (ES == 1 ? 4 : 2); ++q) gv[u][q] = kin && bin ? *(const v4i*)(sp + 4 * q) : zero4;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             if constexpr (ES == 1) {
                 v4i g8 = zero4;
 #pragma unroll
@@ -667,7 +672,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
                     g = min(max(g, -128), 127);
                     g8[e >> 2] |= (g & 0xFF) << (8 * (e & 3));
                 }
-                acci = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv[u], g8, acci, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < TC; ++t) acci[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv[u][t], g8, acci[t], 0, 0, 0);
             } else {
                 v4i hi = zero4, lo = zero4;
 #pragma unroll
@@ -678,39 +684,61 @@ __global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
                     hi[e >> 1] |= (int)((unsigned)h << (16 * (e & 1)));
                     lo[e >> 1] |= (int)((unsigned)l << (16 * (e & 1)));
                 }
-                accf = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_m, wv[u]), __builtin_bit_cast(v8bf_m, hi), accf, 0, 0, 0);
-                accf = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_m, wv[u]), __builtin_bit_cast(v8bf_m, lo), accf, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < TC; ++t) {
+                    accf[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_m, wv[u][t]), __builtin_bit_cast(v8bf_m, hi), accf[t], 0, 0, 0);
+                    accf[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_m, wv[u][t]), __builtin_bit_cast(v8bf_m, lo), accf[t], 0, 0, 0);
+                }
             }
         }
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) part[wave][v * 64 + lane] = ES == 1 ? acci[v] : __float_as_int(accf[v]);
+    for (int t = 0; t < TC; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave][t * 256 + v * 64 + lane] = ES == 1 ? acci[t][v] : __float_as_int(accf[t][v]);
     __syncthreads();
-    if (threadIdx.x >= 256 || jj >= a.n_cls || !bin) return;
-    if constexpr (ES == 1) {
-        int t = bias;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) t += part[w][threadIdx.x];
-        ((int*)a.logits)[(long long)b * a.n_cls + jj] = t;
-    } else {
-        float t = 0.f;
+    for (int i = threadIdx.x; i < TC * 256; i += 64 * NW) {     // element i: class j0 + 16 (i / 256) + 4 kq + (i / 64) % 4 of sample r
+        const int jj = j0 + i / 256 * 16 + 4 * kq + (i / 64) % 4;
+        if (jj >= a.n_cls || !bin) continue;
+        const int bias = ((const int*)a.bfc)[jj];
+        if constexpr (ES == 1) {
+            int t = bias;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) t += __int_as_float(part[w][threadIdx.x]);
-        ((float*)a.logits)[(long long)b * a.n_cls + jj] = a.logit_scale * (t + __int_as_float(bias));
+            for (int w = 0; w < NW; ++w) t += part[w][i];
+            ((int*)a.logits)[(long long)b * a.n_cls + jj] = t;
+        } else {
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) t += __int_as_float(part[w][i]);
+            ((float*)a.logits)[(long long)b * a.n_cls + jj] = a.logit_scale * (t + __int_as_float(bias));
+        }
     }
+}
+
+template <int ES, int NW>
+static void launch_fc(const HeadArgs& a, hipStream_t s)
+{
+    const int tiles = (a.n_cls + 15) / 16, rows = (a.B + 15) / 16;
+    // As many tiles per workgroup as leave a workgroup for every CU: a workgroup reads its samples' features whatever the number of its tiles.  1000 classes, us with 1 / 2 / 4 tiles:
+    // 2048 channels, 64 samples (252 workgroups of one tile) int8 7.0 / 8.1 / 9.7, bf16 8.7 / 7.7 / 10.4; 128 (504) 11.0 / 7.8 / 9.2, 12.2 / 8.8 / 9.9; 256 (1008) 18.9 / 11.4 / 8.8,
+    // 19.4 / 12.2 / 10.0; 256 channels, 256 samples 6.1 / 4.8 / 4.8, 5.8 / 5.0 / 5.0.
+    const int tc = tiles * rows <= 256 ? 1 : (tiles + 1) / 2 * rows <= 256 ? 2 : 4;
+    if (tc == 1) EE_LAUNCH((fc_kernel<ES, NW, 1>), dim3(tiles, rows), dim3(64 * NW), 0, s, a);
+    else if (tc == 2) EE_LAUNCH((fc_kernel<ES, NW, 2>), dim3((tiles + 1) / 2, rows), dim3(64 * NW), 0, s, a);
+    else EE_LAUNCH((fc_kernel<ES, NW, 4>), dim3((tiles + 3) / 4, rows), dim3(64 * NW), 0, s, a);
 }
 
 hipError_t launch_head_fc(const HeadArgs& a, int dtype, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
-    dim3 grid((a.n_cls + 15) / 16, (a.B + 15) / 16);
     const bool wide = a.C * (dtype == EE_I8 ? 1 : 2) > 1024;      // more than the 16 steps four wavefronts have in flight
     if (dtype == EE_I8) {
-        if (wide) EE_LAUNCH((fc_kernel<1, 8>), grid, dim3(512), 0, s, a);
-        else EE_LAUNCH((fc_kernel<1, 4>), grid, dim3(256), 0, s, a);
+        if (wide) launch_fc<1, 8>(a, s);
+        else launch_fc<1, 4>(a, s);
     } else {
-        if (wide) EE_LAUNCH((fc_kernel<2, 8>), grid, dim3(512), 0, s, a);
-        else EE_LAUNCH((fc_kernel<2, 4>), grid, dim3(256), 0, s, a);
+        if (wide) launch_fc<2, 8>(a, s);
+        else launch_fc<2, 4>(a, s);
     }
     return hipGetLastError();
 }
@@ -901,10 +929,12 @@ __global__ __launch_bounds__(256) void head_small_kernel(HeadArgs a, int pooled)
     head_logits_decide<ES, 256>(a, b, feat, lg, exp2_lds, tid, w_first, b_first);
 }
 
+bool head_small_weights(long long row, int n_cls) { return n_cls <= HEAD_SMALL_CLS && row <= HEAD_SMALL_C && row * n_cls <= 32 * 1024; }
+
 bool head_small(const HeadArgs& a, int dtype, bool pooled)
 {
     const long long es = dtype == EE_I8 ? 1 : 2, row = a.C * es;
-    return a.n_cls <= HEAD_SMALL_CLS && row <= HEAD_SMALL_C && row * a.n_cls <= 32 * 1024 && (pooled ? dtype == EE_I8 : row * a.HW <= 32 * 1024);
+    return head_small_weights(row, a.n_cls) && (pooled ? dtype == EE_I8 : row * a.HW <= 32 * 1024);
 }
 
 hipError_t launch_head_small(const HeadArgs& a, int dtype, bool pooled, hipStream_t s)

@@ -478,6 +478,35 @@ def test_small_exit_heads(torch, ee, orc, h, w, c, n_cls, dtype):
     eng.close()
 
 
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("c, n_cls", [(48, 1000), (528, 999), (2048, 257)])
+def test_class_tiles_per_workgroup_of_the_fc(torch, ee, orc, c, n_cls, dtype):
+    """The FC with one, two and four tiles of classes per workgroup (as many as leave a workgroup per CU), batches on both sides of each, class counts and reductions that end inside a tile and inside a
+    step: logits and decisions against the oracle."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8 if dtype == "i8" else W.DT_BF16, 2, 1, c, n_cls)
+    net.begin_stage()
+    net.end_stage(net.maxpool(0, 3, 1, 1))
+    blob = N._assemble(net, net.dtype, 11)
+    tiles = -(-n_cls // 16)
+    edges = {1: 1, 16 * (256 // tiles): 1, 16 * (256 // tiles) + 1: 2, 16 * (256 // (-(-tiles // 2))): 2, 16 * (256 // (-(-tiles // 2))) + 1: 4}
+    n = max(edges)
+    eng = ee.Engine(blob, n)
+    act = W.input_pool(blob, n)
+    for b, tc in edges.items():
+        say(f"[case] fc tiles {dtype} {c} {n_cls} b={b}")
+        (glab, gconf, gscore, gflag), names = kernels_of(torch, lambda: eng.exit_head(0, dev(torch, act[:b]), 0.5))
+        assert [x for x in names if x.startswith("fc_kernel")] == [f"fc_kernel<{1 if dtype == 'i8' else 2},{8 if c * (1 if dtype == 'i8' else 2) > 1024 else 4},{tc}>"], names
+        glog = eng.last_logits(b, n_cls)
+        ends = sorted({0, b // 2, b - 1})
+        lab, conf, score, flag, logits = orc.exit_head(blob, 0, act[ends], 0.5, want_logits=True)
+        if dtype == "i8":
+            assert np.array_equal(glog[ends], logits) and np.array_equal(glab.cpu().numpy()[ends], lab) and np.array_equal(gscore.cpu().numpy()[ends], score)
+        else:                                               # as in the test above
+            assert np.all(np.abs(glog[ends] - logits) <= 1e-3 * np.abs(logits).max() + 1e-6) and np.all(np.abs(gconf.cpu().numpy()[ends] - conf) <= 1e-3)
+    eng.close()
+
+
 def launches_of(eng, f):
     eng.profile(True)
     eng.profile_read()
