@@ -45,6 +45,7 @@ constexpr int BN_SLOT_BYTES = 2 * EE_ZC_MAX_B;   // the output slot of every sam
 template <int K1, bool RES, bool GAP, bool SC>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void bneck_block_i8_kernel(IrArgs a, BnTile t)
 {
+    request_args<sizeof(IrArgs) + sizeof(BnTile)>();
     constexpr int CIN = 32 * K1, CPP = 2 * K1;                         // 16-byte chunks per input pixel
     constexpr int NCH = 100 * CPP, NL = (NCH + 511) / 512;             // chunks per tile, loads per lane (all eight wavefronts stage)
     constexpr int NXB = SC ? 3 : 2;                                    // buffers of staged pixels

@@ -52,6 +52,7 @@ static_assert(b16_lds(4, false) <= 160 * 1024 && b16_lds(1, true) <= 160 * 1024 
 template <int NC, bool SC>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void bneck_block_bf16_kernel(IrArgs a, Bn16Tile t)
 {
+    request_args<sizeof(IrArgs) + sizeof(Bn16Tile)>();
     static_assert(!SC || NC == 1, "the shortcut convolution reads 64 channels");
     constexpr int PB = NC * 128, RING = b16_ring(NC, SC);               // bytes per input pixel, pieces per front wavefront
     extern __shared__ __attribute__((aligned(16))) unsigned char b16_raw[];

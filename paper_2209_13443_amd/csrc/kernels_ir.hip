@@ -74,6 +74,7 @@ constexpr int IR_MAXK = 5;                    // reduction steps of 32 input cha
 template <int STRIDE, int NCO, int MAXB, int MAXK, int GP, bool POOL>
 __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) ? (MAXK == 1 ? 4 : 3) : 2) void ir_block_i8_kernel(IrArgs a, IrTile t)
 {
+    request_args<sizeof(IrArgs) + sizeof(IrTile)>();
     constexpr int NW = GP ? GP : 4, NT = 64 * NW;                      // wavefronts and lanes per workgroup
     constexpr bool EXP = MAXK > 0;
     constexpr int MAXCB = ir_maxcb(GP, STRIDE);
@@ -111,6 +112,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
             bias_d = *(const v4i_r*)((const unsigned char*)a.bd + tid * 16);
         }
         const unsigned char* x = (const unsigned char*)a.x + (size_t)n * a.H * a.W * a.Cin;
+        asm volatile("" : "+s"(x));                                     // in registers: else the pointer is fetched anew, and waited for, in front of every load below
         const int nchunks = EXP ? t.ih * t.iw * t.cpp : 0;
         v2i_r stage[IR_BATCH];
         unsigned dst[IR_BATCH];                                         // LDS byte offset, ~0u: nothing to write

@@ -26,6 +26,7 @@ __device__ __forceinline__ int byte_of(int word, int e) { return (int)(signed ch
 template <int ES>
 __global__ __launch_bounds__(256) void depthwise_kernel(PoolArgs a, int units)
 {
+    request_args<sizeof(PoolArgs)>();
     const int cchunks = a.C * ES / 16, unit = xcd_unit(blockIdx.x, units);
     const long long idx = (long long)unit * 256 + threadIdx.x;
     if (unit < 0) return;
@@ -234,6 +235,7 @@ hipError_t launch_depthwise(const PoolArgs& a, int dtype, hipStream_t s)
 template <int ES>
 __global__ __launch_bounds__(256) void maxpool_kernel(PoolArgs a, int units)
 {
+    request_args<sizeof(PoolArgs)>();
     const int cchunks = a.C * ES / 16, unit = xcd_unit(blockIdx.x, units);
     const long long idx = (long long)unit * 256 + threadIdx.x;
     if (unit < 0) return;
@@ -287,6 +289,7 @@ __global__ __launch_bounds__(256) void maxpool_kernel(PoolArgs a, int units)
 template <int ES>
 __global__ __launch_bounds__(256) void avgpool_kernel(PoolArgs a, unsigned magic, int units)
 {
+    request_args<sizeof(PoolArgs)>();
     const int cchunks = a.C * ES / 16, unit = xcd_unit(blockIdx.x, units);
     const long long idx = (long long)unit * 256 + threadIdx.x;
     if (unit < 0) return;
@@ -361,6 +364,7 @@ __device__ __forceinline__ unsigned pk_add_i16(unsigned a, unsigned b)
 template <int STRIDE, bool AVG>
 __global__ __launch_bounds__(256) void pool3x3_i8_kernel(PoolArgs a, int groups_x, int units)
 {
+    request_args<sizeof(PoolArgs)>();
     constexpr int PX = 4, COLS = (PX - 1) * STRIDE + 3;
     const int cchunks = a.C / 16, unit = xcd_unit(blockIdx.x, units);
     const long long idx = (long long)unit * 256 + threadIdx.x;
@@ -486,6 +490,7 @@ hipError_t launch_avgpool(const PoolArgs& a, int dtype, hipStream_t s)
 template <int ES>
 __global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block, int S)
 {
+    request_args<sizeof(HeadArgs)>();
     constexpr int NE = 16 / ES, U = 8;
     __shared__ int red[256 * NE];
     const int cchunks = a.C * ES / 16;
@@ -554,6 +559,7 @@ __global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block,
 // bf16: sums[b][c] = (partial[b][0][c] + ... + partial[b][S-1][c]) / HW, 4 channels per lane
 __global__ __launch_bounds__(256) void gap_reduce_kernel(HeadArgs a, int S)
 {
+    request_args<sizeof(HeadArgs)>();
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;       // (b, c / 4)
     const int c4 = a.C / 4;
     if (idx >= (long long)a.B * c4) return;
@@ -776,6 +782,7 @@ __device__ __forceinline__ T block_reduce(T v, T* scratch, bool is_max)
 template <int ES>
 __global__ __launch_bounds__(256) void softmax_kernel(HeadArgs a)
 {
+    request_args<sizeof(HeadArgs)>();
     __shared__ long long scratch[8];
     __shared__ int scratch_arg[4];
     __shared__ uint32_t exp2_lds[256];
@@ -866,6 +873,7 @@ hipError_t launch_head_softmax(const HeadArgs& a, int dtype, hipStream_t s)
 template <int ES>
 __global__ __launch_bounds__(256) void head_small_kernel(HeadArgs a, int pooled)
 {
+    request_args<sizeof(HeadArgs)>();
     constexpr int NE = 16 / ES, U = 4;
     __shared__ __attribute__((aligned(16))) int red[256 * NE];
     __shared__ __attribute__((aligned(16))) unsigned char feat[ES == 1 ? HEAD_SMALL_C : 2 * HEAD_SMALL_C];    // int8 features, or floats (C <= HEAD_SMALL_C / ES)

@@ -26,6 +26,7 @@ namespace ee {
 template <int ES, int BM, int BN1, int KS, int BN2>
 __global__ __launch_bounds__(256, 2) void conv_pair_kernel(PairArgs p, int gm, int ns)
 {
+    request_args<sizeof(PairArgs)>();
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int WM = BM / 2, WN = BN1 / 2, TM = WM / 32, TN = WN / 32;
     constexpr int CPRW = KS / 16, NT = 256, RPP = NT / CPRW;

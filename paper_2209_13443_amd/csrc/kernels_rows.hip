@@ -44,6 +44,7 @@ struct RowsShape {
 template <int ES, int KB, int NB, int RB, bool RES>
 __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_kernel(ConvArgs a, RowsGrid g)
 {
+    request_args<sizeof(ConvArgs) + sizeof(RowsGrid)>();
     using Sh = RowsShape<ES, KB, NB, RB>;
     constexpr int RW = Sh::RW, WAVES = Sh::WAVES, NT = Sh::NT, OROW = Sh::OROW, CR = Sh::CR, S = Sh::S;
     constexpr int NS = KB / 32;                                         // matrix instructions of a reduction

@@ -49,6 +49,7 @@ __device__ __forceinline__ void seam_barrier() { asm volatile("s_barrier" ::: "m
 template <int NB, int TM, bool FRONT>
 __global__ __launch_bounds__(768, 3) void conv_seam_kernel(SeamArgs a, int over_bytes, unsigned slab_bytes)
 {
+    request_args<sizeof(SeamArgs)>();
     using Sh = SeamShape<NB, TM>;
     constexpr int CB = Sh::C, PB = Sh::PB, BM = Sh::BM, NP = Sh::NP, NI = Sh::NI, OROW = Sh::OROW, PITCH = Sh::PITCH;
     constexpr int S0 = Sh::S0, S0T = Sh::S0T, S1 = Sh::S1, S2 = Sh::S2, SC = S1 + S2;

@@ -62,6 +62,7 @@ __device__ __forceinline__ unsigned stem_join(const StemMax& a)
 
 __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* yq, StemTile t)
 {
+    request_args<sizeof(ConvArgs) + sizeof(StemTile)>();
     constexpr int NKB = 8, NT = 2;                                      // 32-byte blocks of the reduction (4 rows x 2), blocks of 32 output channels
     extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
     const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
@@ -208,6 +209,7 @@ static_assert(2 * SB_LDS <= 160 * 1024, "two workgroups per CU");
 
 __global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void* yq, StemTile t)
 {
+    request_args<sizeof(ConvArgs) + sizeof(StemTile)>();
     constexpr int NK = 16;                                              // taps = reduction steps of 16 channels
     extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
     const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
@@ -336,6 +338,7 @@ static_assert(CP_ITEMS <= 256, "one item per lane");
 
 __global__ __launch_bounds__(256, 3) void conv_pool_i8_kernel(ConvArgs a, void* yq, StemTile t)
 {
+    request_args<sizeof(ConvArgs) + sizeof(StemTile)>();
     constexpr int NK = 9;
     extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
     const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;

@@ -32,6 +32,7 @@ __device__ __forceinline__ unsigned stream_div(unsigned n, unsigned d, unsigned 
 template <int KH, int BPR, int NT>
 __global__ __launch_bounds__(256, 2) void conv_stream_i8_kernel(ConvArgs a, int nstrips)
 {
+    request_args<sizeof(ConvArgs)>();
     constexpr int NKB = KH * BPR, ROW_PITCH = NT * 32 + 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char stream_lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

@@ -23,6 +23,7 @@ typedef int v16i_t __attribute__((ext_vector_type(16)));
 
 __global__ __launch_bounds__(256, 2) void conv_thin_i8_kernel(ThinConvArgs a, int nt, int row_pitch, int units)
 {
+    request_args<sizeof(ThinConvArgs)>();
     extern __shared__ __attribute__((aligned(16))) unsigned char thin_lds[];
     const int unit = xcd_unit(blockIdx.x, units);
     if (unit < 0) return;
