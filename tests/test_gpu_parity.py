@@ -507,6 +507,29 @@ def test_class_tiles_per_workgroup_of_the_fc(torch, ee, orc, c, n_cls, dtype):
     eng.close()
 
 
+@pytest.mark.parametrize("h, w, c, edges", [(7, 7, 2048, {1: 64, 9: 64}), (5, 13, 1032, {3: 64}), (14, 14, 1024, {2: 32}), (28, 28, 504, {1: 8, 33: 16}), (56, 56, 256, {2: 4, 33: 8, 65: 16}),
+                                            (64, 64, 24, {3: 4}), (64, 65, 24, {3: None})], ids=str)
+def test_bf16_pooling_by_slices_of_channels(torch, ee, orc, h, w, c, edges):
+    """The bf16 head's pooling, one workgroup per sample and slice of channels, in every width, slices that end behind the last channel, and the images past its limit: logits against the oracle (double
+    sums), which the pooled means reach within float rounding."""
+    from workloads import nets as N
+    net = N._Net(W.DT_BF16, h, w, c, 300)
+    net.begin_stage()
+    net.end_stage(net.maxpool(0, 3, 1, 1))
+    blob = N._assemble(net, net.dtype, 13)
+    eng = ee.Engine(blob, max(edges))
+    act = W.input_pool(blob, max(edges))
+    for b, sch in edges.items():
+        say(f"[case] pooling by slices {h}x{w}x{c} b={b}")
+        (glab, gconf, _, _), names = kernels_of(torch, lambda: eng.exit_head(0, dev(torch, act[:b]), 0.5))
+        assert names[0] == (f"gap_slice_kernel<{sch}>" if sch else "gap_kernel<2>"), names
+        glog = eng.last_logits(b, 300)
+        ends = sorted({0, b // 2, b - 1})
+        _, conf, _, _, logits = orc.exit_head(blob, 0, act[ends], 0.5, want_logits=True)
+        assert np.all(np.abs(glog[ends] - logits) <= 1e-3 * np.abs(logits).max() + 1e-6) and np.all(np.abs(gconf.cpu().numpy()[ends] - conf) <= 1e-3)      # as above
+    eng.close()
+
+
 def launches_of(eng, f):
     eng.profile(True)
     eng.profile_read()
