@@ -31,22 +31,20 @@ __global__ __launch_bounds__(512) void segment_small_i8_kernel(SegRows, const Se
     extern __shared__ __attribute__((aligned(16))) unsigned char sg_lds[];
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Two round trips to memory in front of the first load of data: the arguments with the table of rows, then a line of every part of the plan that the layers read.  With the count of samples,
+    // the other arguments, the row and the plan waited for one after the other 64 requests in 8 slots (24 steps) took 385 us, now 377.
+    request_args<sizeof(SegRows) + 72 + sizeof(HeadArgs)>();
+    const auto& a = *(SegPlanPtr)plan;
+    {
+        const __attribute__((address_space(4))) int* p = (const __attribute__((address_space(4))) int*)plan;
+        const int x = [&]<int... LINE>(std::integer_sequence<int, LINE...>) { return (p[16 * LINE] ^ ...); }(std::make_integer_sequence<int, (int)(__builtin_offsetof(SegPlan, tab) + 63) / 64>{});
+        asm volatile("" ::"s"(x));
+    }
     const int b = xcd_unit(blockIdx.x, B);
     if (b < 0) return;
-    const auto& a = *(SegPlanPtr)plan;
-    // the arguments needed later are requested now, together; then a line of every layer's description, so that the layers find them in the scalar cache
-    asm volatile("" ::"s"(x), "s"(y), "s"(by_value), "s"(ids), "s"(xs), "s"(ys), "s"(head), "s"(h.wfc), "s"(h.bfc), "s"(h.exp2), "s"(h.C), "s"(h.n_cls), "s"(h.gap_shift), "s"(h.frac_bits));
-    asm volatile("" ::"s"(h.label), "s"(h.conf), "s"(h.score), "s"(h.flag), "s"(h.host_out), "s"(h.tag), "s"(h.s_thr), "s"(h.last), "s"(h.logits));
     const __attribute__((address_space(4))) int* tab = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
     const long long src_row = by_value ? tab[b] : ids ? ids[b] : xs ? (int)xs[b] : b;
     const long long dst_row = by_value ? tab[EE_SEG_ROWS + b] : ys ? (int)ys[b] : b;
-    {
-        int t0[EE_SEG_LAYERS], t1[EE_SEG_LAYERS];
-#pragma unroll
-        for (int l = 0; l < EE_SEG_LAYERS; ++l) { t0[l] = a.layer[l].w_off; t1[l] = a.layer[l].hi; }
-#pragma unroll
-        for (int l = 0; l < EE_SEG_LAYERS; ++l) asm volatile("" ::"s"(t0[l]), "s"(t1[l]));
-    }
     const unsigned lds0 = lds_addr(sg_lds);
     int* const l_sums = (int*)(sg_lds + a.sums_off);
     unsigned char* const l_feat = sg_lds + a.feat_off;
