@@ -2,6 +2,7 @@
 // pool, FC, softmax top-1 and the exit decision), slot compaction / refill and admission.
 // All of them move 16 bytes per lane per access along the channel (NHWC) or sample axis so
 // that a wavefront touches whole cache lines.
+#include <type_traits>
 #include <algorithm>
 
 #include "ee_internal.hpp"
@@ -556,21 +557,22 @@ __global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block,
     }
 }
 
-// bf16, images of up to 4096 pixels: a workgroup per (sample, SCH chunks of 16 bytes of its channels) adds up every pixel, so that nothing is left to a second launch.  Sums in a fixed order: 1024 / SCH lanes
-// per chunk take every pixel of their turn, a tree over the wavefront, then the 16 wavefronts in turn.
-template <int SCH>
+// Images of up to 4096 pixels: a workgroup per (sample, SCH chunks of 16 bytes of its channels) adds up every pixel, so that nothing is left to a second launch (bf16) or to atomics (int8).  Sums in a
+// fixed order: 1024 / SCH lanes per chunk take every pixel of their turn, a tree over the wavefront, then the 16 wavefronts in turn.
+template <int ES, int SCH>
 __global__ __launch_bounds__(1024) void gap_slice_kernel(HeadArgs a, int slices)
 {
     request_args<sizeof(HeadArgs)>();
-    constexpr int NPL = 1024 / SCH, U = 8;
-    __shared__ float red[16][SCH * 8];
+    using T = std::conditional_t<ES == 1, int, float>;
+    constexpr int NE = 16 / ES, NPL = 1024 / SCH, U = 8;
+    __shared__ T red[16][SCH * NE];
     const int unit = xcd_unit(blockIdx.x, a.B * slices);
     if (unit < 0) return;
     const int b = unit / slices, tid = threadIdx.x, q = tid % SCH, pl = tid / SCH;
-    const int cchunks = a.C / 8, chunk = (unit - b * slices) * SCH + q;
+    const int cchunks = a.C / NE, chunk = (unit - b * slices) * SCH + q;
     const long long bs = a.slots ? (long long)a.slots[b] : (long long)b;
-    const v4i* row = (const v4i*)((const unsigned char*)a.act + bs * a.HW * a.C * 2) + min(chunk, cchunks - 1);
-    float acc[8] = {};
+    const v4i* row = (const v4i*)((const unsigned char*)a.act + bs * a.HW * a.C * ES) + min(chunk, cchunks - 1);
+    T acc[NE] = {};
     for (int p = pl; p < a.HW; p += U * NPL) {
         v4i xv[U];
 #pragma unroll
@@ -579,22 +581,26 @@ __global__ __launch_bounds__(1024) void gap_slice_kernel(HeadArgs a, int slices)
         for (int u = 0; u < U; ++u)
             if (p + u * NPL < a.HW)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] += bf16_to_f32_m((uint16_t)((unsigned)xv[u][e >> 1] >> (16 * (e & 1))));
+                for (int e = 0; e < NE; ++e) {
+                    if constexpr (ES == 1) acc[e] += __builtin_amdgcn_sbfe(xv[u][e >> 2], 8 * (e & 3), 8);
+                    else acc[e] += bf16_to_f32_m((uint16_t)((unsigned)xv[u][e >> 1] >> (16 * (e & 1))));
+                }
     }
 #pragma unroll
     for (int o = SCH; o < 64; o <<= 1)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+        for (int e = 0; e < NE; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
     if ((tid & 63) < SCH)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) red[tid >> 6][q * 8 + e] = acc[e];
+        for (int e = 0; e < NE; ++e) red[tid >> 6][q * NE + e] = acc[e];
     __syncthreads();
-    const int c = (unit - b * slices) * SCH * 8 + tid;
-    if (tid >= SCH * 8 || c >= a.C) return;
-    float s = red[0][tid];
+    const int c = (unit - b * slices) * SCH * NE + tid;
+    if (tid >= SCH * NE || c >= a.C) return;
+    T s = red[0][tid];
 #pragma unroll
     for (int w = 1; w < 16; ++w) s += red[w][tid];
-    a.sums[(long long)b * a.C + c] = __float_as_int(s / (float)a.HW);
+    if constexpr (ES == 1) a.sums[(long long)b * a.C + c] = s;
+    else a.sums[(long long)b * a.C + c] = __float_as_int(s / (float)a.HW);
 }
 
 // bf16: sums[b][c] = (partial[b][0][c] + ... + partial[b][S-1][c]) / HW, 4 channels per lane
@@ -640,29 +646,42 @@ int head_gap_splits(int B, int HW)
     return (HW + ppb - 1) / ppb;
 }
 
+// Slices of channels while a workgroup's pixels are no more than it reads in about the time of a launch: the widest of up to 128 KB, and up to 256 bytes of a pixel rather than more than a workgroup
+// per CU.  bf16, the two kernels / this one, us: 56x56x256, 5 samples 7.3 / 5.8 (in slices of 64 bytes; 7.2 in 128, 11.0 in 256), 64 22.1 / 18.1, 256 76.9 / 72.9; 28x28x512, 5 samples
+// 7.8 / 4.5, 256 35.9 / 31.1; 14x14x1024, 5 samples 7.2 / 4.2, 64 10.0 / 6.4; 7x7x2048, 5 samples 7.3 / 3.7.
+template <int ES>
+static void launch_gap_slices(const HeadArgs& a, hipStream_t s)
+{
+    const int cchunks = a.C * ES / 16;
+    int sch = 64;                                                       // chunks of 16 bytes per workgroup
+    while (sch > 4 && (a.HW * sch * 16 > 128 * 1024 || sch / 2 >= cchunks)) sch /= 2;
+    auto slices = [&] { return (cchunks + sch - 1) / sch; };
+    while (sch < 16 && a.B * slices() > 256) sch *= 2;
+#define EE_SLICE(SCH) if (sch == SCH) EE_LAUNCH((gap_slice_kernel<ES, SCH>), dim3(xcd_grid(a.B * slices())), dim3(1024), 0, s, a, slices())
+    EE_SLICE(4);
+    EE_SLICE(8);
+    EE_SLICE(16);
+    EE_SLICE(32);
+    EE_SLICE(64);
+#undef EE_SLICE
+}
+
 hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
     const int ppb = gap_pixels_per_block(a.B, a.HW);
     const int splits = (a.HW + ppb - 1) / ppb;
     if (dtype == EE_I8) {
+        // few pixels of many channels: us with atomics / by slices, 7x7x2048 1 to 64 samples 4.9-5.2 / 4.0-4.3, 256 8.9 / 6.7; 14x14x1024, 5 samples 4.7 / 4.5, 64 6.4 / 4.8; but 14x14x96 3.7 / 5.3,
+        // 17x17x768 4.6 / 5.2 (37 samples and more 6.0 / 5.3), 28x28x512 4.3 / 5.8
+        if (a.C >= 1024 && a.HW <= 256) {
+            launch_gap_slices<1>(a, s);
+            return hipGetLastError();
+        }
         EE_LAUNCH(gap_kernel<1>, dim3(xcd_grid(a.B * splits)), dim3(256), 0, s, a, ppb, splits);
     } else {
-        // Slices of channels while a workgroup's pixels are no more than it reads in about the time of the second launch: the widest of up to 128 KB, and up to 256 bytes of a pixel rather than
-        // more than a workgroup per CU.  Pooling, the two kernels / this one, us: 56x56x256, 5 samples 7.3 / 5.8 (in slices of 64 bytes; 7.2 in 128, 11.0 in 256), 64 22.1 / 18.1,
-        // 256 76.9 / 72.9; 28x28x512, 5 samples 7.8 / 4.5, 256 35.9 / 31.1; 14x14x1024, 5 samples 7.2 / 4.2, 64 10.0 / 6.4; 7x7x2048, 5 samples 7.3 / 3.7.
         if (splits > 1 && a.HW <= 4096) {
-            int sch = 64;                                                   // chunks of 16 bytes per workgroup
-            while (sch > 4 && (a.HW * sch * 16 > 128 * 1024 || sch / 2 >= a.C / 8)) sch /= 2;
-            auto slices = [&] { return (a.C / 8 + sch - 1) / sch; };
-            while (sch < 16 && a.B * slices() > 256) sch *= 2;
-#define EE_SLICE(SCH) if (sch == SCH) EE_LAUNCH((gap_slice_kernel<SCH>), dim3(xcd_grid(a.B * slices())), dim3(1024), 0, s, a, slices())
-            EE_SLICE(4);
-            EE_SLICE(8);
-            EE_SLICE(16);
-            EE_SLICE(32);
-            EE_SLICE(64);
-#undef EE_SLICE
+            launch_gap_slices<2>(a, s);
             return hipGetLastError();
         }
         // two kernels when the pooling is split: a timed launch takes the first one's begin and the second one's end

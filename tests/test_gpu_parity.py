@@ -522,11 +522,29 @@ def test_bf16_pooling_by_slices_of_channels(torch, ee, orc, h, w, c, edges):
     for b, sch in edges.items():
         say(f"[case] pooling by slices {h}x{w}x{c} b={b}")
         (glab, gconf, _, _), names = kernels_of(torch, lambda: eng.exit_head(0, dev(torch, act[:b]), 0.5))
-        assert names[0] == (f"gap_slice_kernel<{sch}>" if sch else "gap_kernel<2>"), names
+        assert names[0] == (f"gap_slice_kernel<2,{sch}>" if sch else "gap_kernel<2>"), names
         glog = eng.last_logits(b, 300)
         ends = sorted({0, b // 2, b - 1})
         _, conf, _, _, logits = orc.exit_head(blob, 0, act[ends], 0.5, want_logits=True)
         assert np.all(np.abs(glog[ends] - logits) <= 1e-3 * np.abs(logits).max() + 1e-6) and np.all(np.abs(gconf.cpu().numpy()[ends] - conf) <= 1e-3)      # as above
+    eng.close()
+
+
+@pytest.mark.parametrize("h, w, c, sliced", [(7, 7, 2048, 64), (1, 1, 1024, 64), (16, 16, 1040, 32), (16, 16, 1008, 0), (16, 17, 1024, 0)])
+def test_int8_pooling_by_slices_of_channels(torch, ee, orc, h, w, c, sliced):
+    """The int8 head's pooling by slices at the edges of its rule, slices that end behind the last channel, and heads one after the other on the same sums: everything against the oracle."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, h, w, c, 300)
+    net.begin_stage()
+    net.end_stage(net.maxpool(0, 3, 1, 1))
+    blob = N._assemble(net, net.dtype, 17)
+    eng = ee.Engine(blob, 9)
+    act = W.input_pool(blob, 9)
+    for b in (9, 1, 5):
+        lab, _, score, flag, logits = orc.exit_head(blob, 0, act[:b], 0.5, want_logits=True)
+        (glab, _, gscore, gflag), names = kernels_of(torch, lambda: eng.exit_head(0, dev(torch, act[:b]), 0.5))
+        assert names[0] == (f"gap_slice_kernel<1,{sliced}>" if sliced else "gap_kernel<1>"), names
+        assert np.array_equal(eng.last_logits(b, 300), logits) and np.array_equal(glab.cpu().numpy(), lab) and np.array_equal(gscore.cpu().numpy(), score) and np.array_equal(gflag.cpu().numpy(), flag)
     eng.close()
 
 
