@@ -6,7 +6,7 @@
 // A workgroup (4 wavefronts) owns a tile of output pixels of one image: blocks of 32 pixels (NBH rows x NBW columns,
 // NBH * NBW <= 32), at most MAXB blocks per wavefront.
 //   * The block's input pixels under the tile (with the one-pixel frame of the 3x3 window) are staged once in LDS,
-//     8 bytes per lane and load, a pixel's channels followed by padding up to the reduction length (a multiple of 32)
+//     8 or 16 bytes per lane and load, a pixel's channels followed by padding up to the reduction length (a multiple of 32)
 //     plus 16 bytes (an odd number of 16-byte chunks per pixel spreads consecutive pixels over the banks).  Bytes behind
 //     a pixel's channels are never written: the expansion weights are zero there.
 //   * For every group g of 32 expanded channels:
@@ -50,7 +50,7 @@ struct IrTile {
     int pbw, pbh;          // blocks per workgroup tile along x and y
     int tiles_x, tiles_y;
     int iw, ih;            // staged pixels under a tile
-    int cpp;               // 8-byte chunks per input pixel
+    int cpp, wide;         // chunks per input pixel, of 16 bytes (wide) or 8
     unsigned magic_cpp, magic_iw;   // floor(2^32 / d) + 1: n / d for n < 2^16
     unsigned magic_tx, magic_ty;    // the same for tiles_x, tiles_y (n * d < 2^32: checked by ir_block_plan)
     int magic_nbw, magic_pbw;       // floor(2^16 / d) + 1: n / d for n < 2^8
@@ -60,7 +60,7 @@ struct IrTile {
     int gp;                // 4 or 8: that many wavefronts share the channel groups (small images), 0: four share the pixels
 };
 
-constexpr int IR_BATCH = 8, IR_BATCHES = 2;   // 8-byte loads per lane that stage a tile, in batches: ih * iw * cpp <= 4096
+constexpr int IR_BATCH = 8, IR_BATCHES = 2;   // loads per lane that stage a tile, in batches: ih * iw * cpp <= 4096
 // blocks of 32 staged pixels per wavefront in the expansion: ih * iw <= 384, or, where the wavefronts share the channel groups, 96 (stride 2: 160, a block of 4 x 8 output pixels)
 constexpr int ir_maxcb(int gp, int stride) { return gp && stride == 2 ? 5 : 3; }
 constexpr int IR_SHARED_LDS = 96 * 1024;      // LDS bytes where the wavefronts share the channel groups (their registers leave one workgroup to a CU)
@@ -114,46 +114,54 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
         const unsigned char* x = (const unsigned char*)a.x + (size_t)n * a.H * a.W * a.Cin;
         asm volatile("" : "+s"(x));                                     // in registers: else the pointer is fetched anew, and waited for, in front of every load below
         const int nchunks = EXP ? t.ih * t.iw * t.cpp : 0;
-        v2i_r stage[IR_BATCH];
-        unsigned dst[IR_BATCH];                                         // LDS byte offset, ~0u: nothing to write
+        auto stage_chunks = [&](auto zero) {                            // in chunks of 8 or 16 bytes
+            using V = decltype(zero);
+            constexpr int CB = sizeof(V);
+            V stage[IR_BATCH];
+            unsigned dst[IR_BATCH];                                     // LDS byte offset, ~0u: nothing to write
 #pragma unroll
-        for (int batch = 0; batch < IR_BATCHES; ++batch) {
-            if (batch > 0 && NT * IR_BATCH * batch >= nchunks) break;   // wave-uniform
+            for (int batch = 0; batch < IR_BATCHES; ++batch) {
+                if (batch > 0 && NT * IR_BATCH * batch >= nchunks) break;   // wave-uniform
 #pragma unroll
-            for (int i = 0; i < IR_BATCH; ++i) {
-                dst[i] = ~0u;
-                stage[i] = v2i_r{0, 0};
-                const int e0 = NT * (batch * IR_BATCH + i);
-                if (e0 < nchunks) {                                     // wave-uniform
-                    const int e = min(e0 + tid, nchunks - 1);
-                    const int q = t.cpp == 1 ? e : (int)__umulhi((unsigned)e, t.magic_cpp), ch = e - q * t.cpp;   // 2^32 / 1 + 1 does not fit the magic number
-                    const int py = (int)__umulhi((unsigned)q, t.magic_iw), px = q - py * t.iw;
-                    const int iy = iy0 + py, ix = ix0 + px;
-                    const bool ok = e0 + tid < nchunks && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-                    // the load is unconditional and in range (a chunk that is not wanted reads the image's first bytes)
-                    stage[i] = *(const v2i_r*)(x + (ok ? (unsigned)((iy * a.W + ix) * a.Cin + 8 * ch) : 0u));
-                    if (ok) dst[i] = (unsigned)(q * t.xp + 8 * ch);
+                for (int i = 0; i < IR_BATCH; ++i) {
+                    dst[i] = ~0u;
+                    stage[i] = V{};
+                    const int e0 = NT * (batch * IR_BATCH + i);
+                    if (e0 < nchunks) {                                     // wave-uniform
+                        const int e = min(e0 + tid, nchunks - 1);
+                        const int q = t.cpp == 1 ? e : (int)__umulhi((unsigned)e, t.magic_cpp), ch = e - q * t.cpp;   // 2^32 / 1 + 1 does not fit the magic number
+                        const int py = (int)__umulhi((unsigned)q, t.magic_iw), px = q - py * t.iw;
+                        const int iy = iy0 + py, ix = ix0 + px;
+                        const bool ok = e0 + tid < nchunks && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+                        // the load is unconditional and in range (a chunk that is not wanted reads the image's first bytes)
+                        stage[i] = *(const V*)(x + (ok ? (unsigned)((iy * a.W + ix) * a.Cin + CB * ch) : 0u));
+                        if (ok) dst[i] = (unsigned)(q * t.xp + CB * ch);
+                    }
                 }
+                if (batch == 0) {
+                    // the buffers of expanded pixels (two, or one per wavefront) where the tile reaches over the image's edge, the only
+                    // bytes the groups do not write, and, behind them, the projection sums (GP)
+                    const int bufs = (GP ? NW : ngroups > 1 ? 2 : 1) * t.e_bytes;
+                    const int c0 = EXP && frame ? 0 : bufs, c1 = bufs + (GP ? MAXB * NCO * 4096 : 0);
+                    for (int o = c0 + tid * 16; o < c1; o += 16 * NT) *(v4i_r*)(l_e + o) = v4i_r{0, 0, 0, 0};
+                    if (bias_in) {
+                        if constexpr (EXP) *(v4i_r*)(l_be + tid * 16) = bias_e;
+                        *(v4i_r*)(l_bd + tid * 16) = bias_d;
+                    }
+                    for (int o = (NT + tid) * 16; o < 4 * a.Ce32; o += 16 * NT) {
+                        if constexpr (EXP) *(v4i_r*)(l_be + o) = *(const v4i_r*)((const unsigned char*)a.be + o);
+                        *(v4i_r*)(l_bd + o) = *(const v4i_r*)((const unsigned char*)a.bd + o);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < IR_BATCH; ++i)
+                    if (dst[i] != ~0u) *(V*)(l_x + dst[i]) = stage[i];
             }
-            if (batch == 0) {
-                // the buffers of expanded pixels (two, or one per wavefront) where the tile reaches over the image's edge, the only
-                // bytes the groups do not write, and, behind them, the projection sums (GP)
-                const int bufs = (GP ? NW : ngroups > 1 ? 2 : 1) * t.e_bytes;
-                const int c0 = EXP && frame ? 0 : bufs, c1 = bufs + (GP ? MAXB * NCO * 4096 : 0);
-                for (int o = c0 + tid * 16; o < c1; o += 16 * NT) *(v4i_r*)(l_e + o) = v4i_r{0, 0, 0, 0};
-                if (bias_in) {
-                    if constexpr (EXP) *(v4i_r*)(l_be + tid * 16) = bias_e;
-                    *(v4i_r*)(l_bd + tid * 16) = bias_d;
-                }
-                for (int o = (NT + tid) * 16; o < 4 * a.Ce32; o += 16 * NT) {
-                    if constexpr (EXP) *(v4i_r*)(l_be + o) = *(const v4i_r*)((const unsigned char*)a.be + o);
-                    *(v4i_r*)(l_bd + o) = *(const v4i_r*)((const unsigned char*)a.bd + o);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < IR_BATCH; ++i)
-                if (dst[i] != ~0u) *(v2i_r*)(l_x + dst[i]) = stage[i];
-        }
+        };
+        if constexpr (GP || MAXK > 1) {
+            if (t.wide) stage_chunks(v4i_r{});
+            else stage_chunks(v2i_r{});
+        } else stage_chunks(v2i_r{});
     }
 
     // ---- the staged pixels inside the image, in blocks of 32 for the expansion -----------------------------------------
@@ -398,11 +406,13 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
     t.nbw = a.Wo % 8 == 0 ? 8 : a.Wo % 14 == 0 ? 14 : a.Wo % 7 == 0 ? 7 : 8;
     t.nbh = 32 / t.nbw;
     const int bx_max = (a.Wo + t.nbw - 1) / t.nbw, by_max = (a.Ho + t.nbh - 1) / t.nbh;
-    t.pbw = 1; t.pbh = 1;
+    t.pbw = 1; t.pbh = 1; t.gp = 0;
     auto fits = [&] {
         t.iw = (t.pbw * t.nbw - 1) * a.stride + 3;
         t.ih = (t.pbh * t.nbh - 1) * a.stride + 3;
-        t.cpp = expands ? a.Cin / 8 : 1;
+        t.wide = a.Cin % 16 == 0 && (t.gp || a.Kx > 32);                // Where the kernel has both (14x14, 64 -> 384 -> 64, 1 sample 6.3 / 6.1 us,
+                                                                        // 7x7, 160 -> 960 -> 160 12.0 / 11.4): elsewhere a second form's code costs 24 channels 1-2 %, more than 16 and 32 gain
+        t.cpp = expands ? a.Cin / (t.wide ? 16 : 8) : 1;
         t.xp = a.Kx + 16;
         t.x_bytes = expands ? t.ih * t.iw * t.xp + 128 : 0;             // the last pixel's reduction bytes may be read past its channels
         t.e_bytes = t.ih * (t.iw * 32 + 16);
@@ -415,12 +425,11 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
     // pixels shared out / the groups, us: 14x14 stride 2, 96 -> 576 -> 160, 1 to 128 samples 19.7 / 10.6; 28x28, 32 -> 192 -> 32, 8 samples 7.9 / 6.2, 48 (672 tiles) 14.3 / 10.9,
     // 96 15.6 / 17.7; stride 2, 56x56, 24 -> 144 -> 32, 8 samples (224) 8.1 / 6.1, 16 9.3 / 10.0; 28x28, 32 -> 192 -> 64, 32 samples (224) 8.2 / 6.6, 48 9.3 / 10.7; 14x14,
     // 64 -> 384 -> 64, 128 samples (512) 17.9 / 14.5, 256 20.3 / 26.4, 40 samples in 280 tiles of one block 11.2, in 160 of two 8.3.
-    t.gp = 0;
     if (a.Ce32 >= (a.Kx == 32 ? 160 : 128) && (a.Kx == 32 || nco >= 2)) {       // the forms that are instantiated
         const int nw = a.Ce32 >= (a.Kx == 32 ? 160 : 320) ? 8 : 4;
         const long long limit = nco == 5 ? 2048 : nco >= 2 && a.stride == 1 ? 512 : nco == 1 && a.stride == 1 ? 768 : 256;
         auto shared_tiles = [&](int blocks) -> long long {                      // how many tiles of that many blocks there are, 0: they do not fit
-            t.pbw = t.pbh = 1;
+            t.pbw = t.pbh = 1; t.gp = nw;
             if (blocks == 2) (by_max > 1 && (bx_max == 1 || t.nbh <= t.nbw) ? t.pbh : t.pbw) = 2;
             if (t.pbw > bx_max || !fits() || 8 * a.Ce32 + t.x_bytes + nw * t.e_bytes + maxb * nco * 4096 > IR_SHARED_LDS) return 0;
             const int px = t.ih * t.iw;
@@ -433,8 +442,7 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
             n = shared_tiles(2);
             if (n == 0) n = shared_tiles(1);
         }
-        if (n > 0 && n <= limit) t.gp = nw;
-        else t.pbw = t.pbh = 1;
+        if (n == 0 || n > limit) t.pbw = t.pbh = 1, t.gp = 0;
     }
     while (!t.gp) {                                                     // grow the shorter side in pixels while the tile fits
         const bool can_x = t.pbw < bx_max, can_y = t.pbh < by_max;
