@@ -29,12 +29,18 @@ struct StemTile {
 
 static unsigned stem_magic(int d) { return (unsigned)(0x100000000ull / (unsigned)d - (d == 1)); }
 
-constexpr int ST_TW = 14, ST_TH = 8;                       // pooled pixels per tile
-constexpr int ST_RW = 2 * ST_TW + 1, ST_RH = 2 * ST_TH + 1;   // convolution outputs under them
-constexpr int ST_RPIX = ST_RW * ST_RH;                     // 493
-constexpr int ST_STRIPS = (ST_RPIX + 31) / 32;             // 16: four per wavefront
-constexpr int ST_ITEMS = 4 * ST_TW * ST_TH;                // (pooled pixel, 16 channels) per tile
-static_assert(ST_STRIPS == 16, "four strips per wavefront");
+// A tile of TW x TH pooled pixels: the convolution outputs under it in strips of 32, whole ones per wavefront
+template <int TW, int TH>
+struct StemShape {
+    static constexpr int RW = 2 * TW + 1, RH = 2 * TH + 1, RPIX = RW * RH, STRIPS = (RPIX + 31) / 32, PER = STRIPS / 4;
+    static constexpr int ITEMS = 4 * TW * TH;                           // (pooled pixel, 16 channels)
+    static_assert(STRIPS % 4 == 0, "whole strips per wavefront");
+    static constexpr size_t lds_bytes() { return (size_t)RPIX * (64 + 16) + 256; }
+};
+constexpr int ST_TW = 14, ST_TH = 8;                       // 493 outputs, four strips per wavefront
+// where there is a CU for every small tile: 117 outputs, one strip per wavefront.  224 x 224, with the folded copy in front: 1 sample 10.0 us in large tiles, 7.9 in small ones, 2 and 3 samples (280 and 420
+// small tiles, two to a CU) 10.1 in either
+constexpr int ST_SMALL_TW = 6, ST_SMALL_TH = 4;
 constexpr int ST_PITCH = 64 + 16;                          // bytes per convolution output in LDS
 
 // byte-wise signed maximum of packed dwords on 16-bit halves, three instructions per dword: the odd bytes decide a half by themselves (whatever is
@@ -60,8 +66,12 @@ __device__ __forceinline__ unsigned stem_join(const StemMax& a)
     return __builtin_amdgcn_perm(o, e, 0x07030501u);                    // bytes 1 of e, 1 of o, 3 of e, 3 of o
 }
 
+template <int TW, int TH>
 __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* yq, StemTile t)
 {
+    using Sh = StemShape<TW, TH>;
+    constexpr int RW = Sh::RW, RPIX = Sh::RPIX, ITEMS = Sh::ITEMS, PER = Sh::PER;
+    static_assert(PER == 4 || PER == 1, "the loop below");
     request_args<sizeof(ConvArgs) + sizeof(StemTile)>();
     constexpr int NKB = 8, NT = 2;                                      // 32-byte blocks of the reduction (4 rows x 2), blocks of 32 output channels
     extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
@@ -73,35 +83,17 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) wreg[j][kb] = *(const v4i_r*)(wb + (size_t)(32 * j + p) * a.Kp + kb * 32 + 16 * hi);
-    int* const l_bias = (int*)(stem_lds + ST_RPIX * ST_PITCH);         // 64 biases behind the tile's image (rounding constant included)
+    int* const l_bias = (int*)(stem_lds + RPIX * ST_PITCH);         // 64 biases behind the tile's image (rounding constant included)
     if (tid < 64) l_bias[tid] = ((const int*)a.bias)[tid];
-    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) asm volatile("" : "+v"(wreg[j][kb]));
-    __syncthreads();
-    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
-    const bool relu = ir_relu(a.shift, a.lo, a.hi);
     const int tpi = t.tiles_x * t.tiles_y;
-    // pooling: this lane's items (pooled pixel, channels): tid and tid + 256
-    const int pch = tid & 3;
-    int pty[2], ptx[2], poff[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int pp = min(tid + 256 * i, ST_ITEMS - 1) >> 2;
-        pty[i] = pp / ST_TW; ptx[i] = pp - pty[i] * ST_TW;
-        poff[i] = ((2 * pty[i]) * ST_RW + 2 * ptx[i]) * ST_PITCH + 16 * pch;
-    }
-
     struct Tile { int n, py0, px0; };
     auto tile_at = [&](int u) {
         const int n = (int)fast_div((unsigned)u, (unsigned)tpi, t.magic_tpi), r0 = u - n * tpi, tyi = (int)fast_div((unsigned)r0, (unsigned)t.tiles_x, t.magic_tx);
-        return Tile{n, ST_TH * tyi, ST_TW * (r0 - tyi * t.tiles_x)};
+        return Tile{n, TH * tyi, TW * (r0 - tyi * t.tiles_x)};
     };
     auto load_strip = [&](const Tile& tl, int s, v4i_r* xr) {           // unconditional and in range; the folded input carries its own padding
         const unsigned char* xn = (const unsigned char*)a.x + (size_t)tl.n * a.H * a.W * 16;
-        const int r = min(32 * s + p, ST_RPIX - 1), ry = r / ST_RW, rx = r - ry * ST_RW;
+        const int r = min(32 * s + p, RPIX - 1), ry = r / RW, rx = r - ry * RW;
         const int cy = min(max(2 * tl.py0 - 1 + ry, 0), a.Ho - 1), cx = min(max(2 * tl.px0 - 1 + rx, 0), a.Wo - 1);
         // the four rows and four columns under the clamped output are inside the folded image (it has three rows and columns more than
         // the convolution's output: checked by the launcher), so the eight operands lie at fixed offsets from the first
@@ -110,8 +102,31 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) xr[kb] = *(const v4i_r*)(first + (kb >> 1) * row + (kb & 1) * 32);
     };
+    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
+    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
+    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3);
+    v4i_r xs[PER][NKB];
+    if (PER == 1 && u < u_end) load_strip(tile_at(u), wave, xs[0]);     // its latency lies under the weights'
+    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) asm volatile("" : "+v"(wreg[j][kb]));
+    __syncthreads();
+    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
+    // pooling: this lane's items (pooled pixel, channels): tid and tid + 256
+    const int pch = tid & 3;
+    int pty[2], ptx[2], poff[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int pp = min(tid + 256 * i, ITEMS - 1) >> 2;
+        pty[i] = pp / TW; ptx[i] = pp - pty[i] * TW;
+        poff[i] = ((2 * pty[i]) * RW + 2 * ptx[i]) * ST_PITCH + 16 * pch;
+    }
+
     auto compute_strip = [&](const Tile& tl, int s, const v4i_r* xr) {
-        const int r = 32 * s + p, rc = min(r, ST_RPIX - 1), ry = rc / ST_RW, rx = rc - ry * ST_RW;
+        const int r = 32 * s + p, rc = min(r, RPIX - 1), ry = rc / RW, rx = rc - ry * RW;
         const bool exists = (unsigned)(2 * tl.py0 - 1 + ry) < (unsigned)a.Ho && (unsigned)(2 * tl.px0 - 1 + rx) < (unsigned)a.Wo;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
@@ -126,19 +141,15 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
             for (int kb = 0; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][kb], xr[kb], acc, 0, 0, 0);
             v4i_r o = ir_requant_pack(acc, cl, relu);
             if (!exists) o = v4i_r{(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
-            if (r < ST_RPIX) *(v4i_r*)(stem_lds + r * ST_PITCH + 32 * j + 16 * hi) = o;
+            if (r < RPIX) *(v4i_r*)(stem_lds + r * ST_PITCH + 32 * j + 16 * hi) = o;
         }
     };
-    // strips wave, wave + 4, wave + 8, wave + 12 of a tile through four operand sets; a strip's operands are requested two strips
+    // four strips: wave, wave + 4, wave + 8, wave + 12 of a tile through four operand sets; a strip's operands are requested two strips
     // before it is computed, the first two of the next tile behind this tile's last two
-    v4i_r xs[4][NKB];
-    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
-    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
-    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3);
-    if (u < u_end) {
+    if (PER == 4 && u < u_end) {
         const Tile t0 = tile_at(u);
         load_strip(t0, wave, xs[0]);
-        load_strip(t0, wave + 4, xs[1]);
+        load_strip(t0, wave + 4, xs[1 % PER]);
     }
     for (; u < u_end; u += u_step) {
         const Tile tl = tile_at(u);
@@ -146,25 +157,30 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
         const Tile tn = tile_at(more ? u + u_step : u);
         const int n = tl.n, py0 = tl.py0, px0 = tl.px0;
         __builtin_amdgcn_sched_barrier(0);
-        load_strip(tl, wave + 8, xs[2]);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_strip(tl, wave, xs[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        load_strip(tl, wave + 12, xs[3]);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_strip(tl, wave + 4, xs[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        load_strip(tn, wave, xs[0]);                                    // past the last tile: this tile's once more (a fixed number of loads)
-        __builtin_amdgcn_sched_barrier(0);
-        compute_strip(tl, wave + 8, xs[2]);
-        __builtin_amdgcn_sched_barrier(0);
-        load_strip(tn, wave + 4, xs[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_strip(tl, wave + 12, xs[3]);
+        if constexpr (PER == 4) {
+            load_strip(tl, wave + 8, xs[2]);
+            __builtin_amdgcn_sched_barrier(0);
+            compute_strip(tl, wave, xs[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_strip(tl, wave + 12, xs[3]);
+            __builtin_amdgcn_sched_barrier(0);
+            compute_strip(tl, wave + 4, xs[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_strip(tn, wave, xs[0]);                                // past the last tile: this tile's once more (a fixed number of loads)
+            __builtin_amdgcn_sched_barrier(0);
+            compute_strip(tl, wave + 8, xs[2]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_strip(tn, wave + 4, xs[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            compute_strip(tl, wave + 12, xs[3]);
+        } else {
+            compute_strip(tl, wave, xs[0]);
+            load_strip(tn, wave, xs[0]);
+        }
         __syncthreads();                                                // the tile's convolution outputs are in LDS
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            if (tid + 256 * i >= ST_ITEMS) continue;
+            if (tid + 256 * i >= ITEMS) continue;
             const unsigned char* win = stem_lds + poff[i];
             const v4i_r first = *(const v4i_r*)win;
             StemMax mx[4];
@@ -172,7 +188,7 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
             for (int d = 0; d < 4; ++d) mx[d] = stem_split((unsigned)first[d]);
 #pragma unroll
             for (int k = 1; k < 9; ++k) {
-                const v4i_r v = *(const v4i_r*)(win + ((k / 3) * ST_RW + (k % 3)) * ST_PITCH);
+                const v4i_r v = *(const v4i_r*)(win + ((k / 3) * RW + (k % 3)) * ST_PITCH);
 #pragma unroll
                 for (int d = 0; d < 4; ++d) mx[d] = stem_max(mx[d], (unsigned)v[d]);
             }
@@ -489,19 +505,24 @@ bool stem_pool_supported(const ConvArgs& a, int es, int Hq, int Wq)
 hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq, hipStream_t s)
 {
     if (!stem_pool_supported(a, es, Hq, Wq)) return hipErrorInvalidValue;
-    const int tw = es == 1 ? ST_TW : SB_TW, th = es == 1 ? ST_TH : SB_TH;
     StemTile t;
     t.Hq = Hq; t.Wq = Wq; t.pool_pad = 1;
-    t.tiles_x = (Wq + tw - 1) / tw;
-    t.tiles_y = (Hq + th - 1) / th;
-    const long long total = (long long)(a.M / (a.Ho * a.Wo)) * t.tiles_x * t.tiles_y;
+    const long long images = a.M / (a.Ho * a.Wo);
+    auto tiles = [&](int tw, int th) {
+        t.tiles_x = (Wq + tw - 1) / tw;
+        t.tiles_y = (Hq + th - 1) / th;
+        return images * t.tiles_x * t.tiles_y;
+    };
+    const bool small = es == 1 && tiles(ST_SMALL_TW, ST_SMALL_TH) <= 256;
+    const long long total = small ? tiles(ST_SMALL_TW, ST_SMALL_TH) : es == 1 ? tiles(ST_TW, ST_TH) : tiles(SB_TW, SB_TH);
     if (total > 0x3fffffff) return hipErrorInvalidValue;
     t.total = (int)total;
     t.magic_tpi = stem_magic(t.tiles_x * t.tiles_y);
     t.magic_tx = stem_magic(t.tiles_x);
     const unsigned blocks = total < 512 ? xcd_grid(total) : 512u;      // two workgroups on every CU (what matters is the CU's share, not the workgroup's); the loop takes the rest
     if (es == 2) EE_LAUNCH(stem_pool_bf16_kernel, dim3(blocks), dim3(256), SB_LDS, s, a, yq, t);
-    else EE_LAUNCH(stem_pool_i8_kernel, dim3(blocks), dim3(256), (size_t)ST_RPIX * ST_PITCH + 256, s, a, yq, t);
+    else if (small) EE_LAUNCH((stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>), dim3(blocks), dim3(256), (StemShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, a, yq, t);
+    else EE_LAUNCH((stem_pool_i8_kernel<ST_TW, ST_TH>), dim3(blocks), dim3(256), (StemShape<ST_TW, ST_TH>::lds_bytes()), s, a, yq, t);
     return hipGetLastError();
 }
 

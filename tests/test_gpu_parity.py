@@ -740,6 +740,24 @@ def test_requantisation_bounds_and_shifts(torch, ee, orc, lo, hi, shift):
     eng.close()
 
 
+@pytest.mark.parametrize("h, w, edges", [(224, 224, {1: "6,4", 2: "14,8"}), (48, 34, {2: "6,4", 42: "6,4", 43: "14,8"}), (57, 80, {16: "6,4", 17: "14,8"}), (114, 56, {11: "14,8"}),
+                                         (16, 14, {256: "6,4", 257: "14,8"})], ids=str)
+def test_first_layer_and_pool_in_both_tiles(torch, ee, orc, h, w, edges):
+    """The fused first convolution and max-pool (int8) in small tiles and in large ones, on both sides of the rule, images that end inside a tile: against the oracle, bit for bit."""
+    blob = W.stem_net(h, w, seed=h)
+    n = max(edges)
+    x = W.input_pool(blob, n)
+    eng = ee.Engine(blob, n)
+    for b, tile in edges.items():
+        say(f"[case] first layer {h}x{w} b={b}")
+        out, names = kernels_of(torch, lambda: eng.stage_forward(0, dev(torch, x[:b]), blob.stage_out_shape(0)))
+        assert f"stem_pool_i8_kernel<{tile}>" in names, names
+        ends = sorted({0, b // 2, b - 1})
+        ref = orc.stage_forward(blob, 0, x[ends])
+        assert np.array_equal(host(out[ends], ref), ref) and np.unique(ref).size > 8
+    eng.close()
+
+
 SEAM_CASES = [  # mid channels, h, w, samples: one pixel, tiles with one pixel less, none over and one over, images ending inside a tile, the widest rows that fit
     (128, 1, 1, 1), (256, 1, 2, 1), (128, 7, 9, 1), (128, 8, 8, 1), (128, 5, 13, 1), (256, 7, 9, 3), (256, 5, 13, 2), (128, 9, 11, 9), (256, 14, 14, 5), (128, 2, 300, 1), (256, 2, 144, 1),
 ]
