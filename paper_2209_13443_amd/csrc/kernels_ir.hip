@@ -276,12 +276,17 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
         }
     };
     auto dw_project = [&](int g, const unsigned char* ebuf) {
-        const v16i_r bias = bias16(l_bd, g);
+        // The bias once for all blocks, but where the kernel is held to 128 registers: there it is read in front of every block.  Sixteen more registers over the loop were four to six spilled
+        // to memory (3-4 MB each way a launch); 64 samples, us: 112x112 stride 2, 16 -> 96 -> 24 28.7 -> 25.8, 56x56, 24 -> 144 -> 24 22.0 -> 20.6, 28x28, 32 -> 192 -> 32 13.0 -> 11.5.
+        constexpr bool ONCE = GP || MAXK != 1;
+        v16i_r bias;
+        if constexpr (ONCE) bias = bias16(l_bd, g);
 #pragma unroll
         for (int s = 0; s < MAXB; ++s)
             if ((GP ? s : dwave + 4 * s) < nblocks) {                   // wave-uniform
                 const unsigned char* win = ebuf + woff[s];
                 auto tap = [&](int t) { return *(const v4i_r*)(win + t / 3 * e_row + t % 3 * 32); };
+                if constexpr (!ONCE) bias = bias16(l_bd, g);
                 v16i_r acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wd[0], tap(0), bias, 0, 0, 0);
 #pragma unroll
                 for (int k = 1; k < 5; ++k)
