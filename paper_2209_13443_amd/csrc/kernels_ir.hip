@@ -486,54 +486,45 @@ bool ir_block_supported(const IrArgs& a)
     return ir_block_plan(a, t, nco, maxb);
 }
 
+template <int STRIDE, int NCO, int MAXB, int MAXK, int GP, bool POOL>
+static hipError_t ir_launch6(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t s)
+{
+    if (lds > 64 * 1024) {                                              // a grant that failed once fails every launch that needs it
+        static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP, POOL>), hipFuncAttributeMaxDynamicSharedMemorySize, IR_SHARED_LDS);
+        if (granted != hipSuccess) return granted;
+    }
+    EE_LAUNCH((ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP, POOL>), dim3(xcd_grid(t.total)), dim3(GP ? 64 * GP : 256), lds, s, a, t);
+    return hipGetLastError();
+}
+
 template <int STRIDE, int NCO, int MAXB, int MAXK, int GP>
-static void ir_launch5(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t s)
+static hipError_t ir_launch5(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t s)
 {
     if constexpr (STRIDE == 1) {
-        if (a.gap_sums) {
-            if (lds > 64 * 1024) {
-                static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&ir_block_i8_kernel<1, NCO, MAXB, MAXK, GP, true>), hipFuncAttributeMaxDynamicSharedMemorySize, IR_SHARED_LDS);
-                if (granted != hipSuccess) return;
-            }
-            EE_LAUNCH((ir_block_i8_kernel<1, NCO, MAXB, MAXK, GP, true>), dim3(xcd_grid(t.total)), dim3(GP ? 64 * GP : 256), lds, s, a, t);
-            return;
-        }
+        if (a.gap_sums) return ir_launch6<1, NCO, MAXB, MAXK, GP, true>(a, t, lds, s);
     }
-    if (lds > 64 * 1024) {
-        static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP, false>), hipFuncAttributeMaxDynamicSharedMemorySize, IR_SHARED_LDS);
-        if (granted != hipSuccess) return;
-    }
-    EE_LAUNCH((ir_block_i8_kernel<STRIDE, NCO, MAXB, MAXK, GP, false>), dim3(xcd_grid(t.total)), dim3(GP ? 64 * GP : 256), lds, s, a, t);
+    return ir_launch6<STRIDE, NCO, MAXB, MAXK, GP, false>(a, t, lds, s);
 }
 
 template <int STRIDE, int NCO, int MAXB>
-static void ir_launch(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t s)
+static hipError_t ir_launch(const IrArgs& a, const IrTile& t, size_t lds, hipStream_t s)
 {
     const int kx32 = a.Kx >> 5;                                         // registers for the expansion weights: 1, 2 or 5 steps
     if (kx32 == 0) {                                                    // no expansion
         if constexpr (NCO >= 2) {
-            if (t.gp == 4) { ir_launch5<STRIDE, NCO, MAXB, 0, 4>(a, t, lds, s); return; }
-            if (t.gp == 8) { ir_launch5<STRIDE, NCO, MAXB, 0, 8>(a, t, lds, s); return; }
+            if (t.gp == 4) return ir_launch5<STRIDE, NCO, MAXB, 0, 4>(a, t, lds, s);
+            if (t.gp == 8) return ir_launch5<STRIDE, NCO, MAXB, 0, 8>(a, t, lds, s);
         }
-        ir_launch5<STRIDE, NCO, MAXB, 0, 0>(a, t, lds, s);
-        return;
+        return ir_launch5<STRIDE, NCO, MAXB, 0, 0>(a, t, lds, s);
     }
     if constexpr (NCO >= 2) {
-        if (t.gp == 4) {
-            if (kx32 <= 2) ir_launch5<STRIDE, NCO, MAXB, 2, 4>(a, t, lds, s);
-            else ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 4>(a, t, lds, s);
-            return;
-        }
-        if (t.gp == 8 && kx32 > 1) {
-            if (kx32 <= 2) ir_launch5<STRIDE, NCO, MAXB, 2, 8>(a, t, lds, s);
-            else ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 8>(a, t, lds, s);
-            return;
-        }
+        if (t.gp == 4) return kx32 <= 2 ? ir_launch5<STRIDE, NCO, MAXB, 2, 4>(a, t, lds, s) : ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 4>(a, t, lds, s);
+        if (t.gp == 8 && kx32 > 1) return kx32 <= 2 ? ir_launch5<STRIDE, NCO, MAXB, 2, 8>(a, t, lds, s) : ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 8>(a, t, lds, s);
     }
-    if (kx32 <= 1 && t.gp == 8) ir_launch5<STRIDE, NCO, MAXB, 1, 8>(a, t, lds, s);
-    else if (kx32 <= 1) ir_launch5<STRIDE, NCO, MAXB, 1, 0>(a, t, lds, s);
-    else if (kx32 <= 2) ir_launch5<STRIDE, NCO, MAXB, 2, 0>(a, t, lds, s);
-    else ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 0>(a, t, lds, s);
+    if (kx32 <= 1 && t.gp == 8) return ir_launch5<STRIDE, NCO, MAXB, 1, 8>(a, t, lds, s);
+    if (kx32 <= 1) return ir_launch5<STRIDE, NCO, MAXB, 1, 0>(a, t, lds, s);
+    if (kx32 <= 2) return ir_launch5<STRIDE, NCO, MAXB, 2, 0>(a, t, lds, s);
+    return ir_launch5<STRIDE, NCO, MAXB, IR_MAXK, 0>(a, t, lds, s);
 }
 
 hipError_t launch_ir_block(const IrArgs& a, hipStream_t s)
@@ -544,16 +535,15 @@ hipError_t launch_ir_block(const IrArgs& a, hipStream_t s)
     const size_t lds = (size_t)8 * a.Ce32 + t.x_bytes + (t.gp ? t.gp * (size_t)t.e_bytes + (size_t)maxb * nco * 4096 : (a.Ce32 > 32 ? 2 : 1) * (size_t)t.e_bytes);
     const int v = (a.stride - 1) * 4 + (nco == 1 ? 0 : nco == 2 ? 1 : nco == 3 ? 2 : 3);
     switch (v) {
-    case 0: ir_launch<1, 1, 2>(a, t, lds, s); break;
-    case 1: ir_launch<1, 2, 2>(a, t, lds, s); break;
-    case 2: ir_launch<1, 3, 2>(a, t, lds, s); break;
-    case 3: ir_launch<1, 5, 1>(a, t, lds, s); break;
-    case 4: ir_launch<2, 1, 2>(a, t, lds, s); break;
-    case 5: ir_launch<2, 2, 2>(a, t, lds, s); break;
-    case 6: ir_launch<2, 3, 2>(a, t, lds, s); break;
-    default: ir_launch<2, 5, 1>(a, t, lds, s); break;
+    case 0: return ir_launch<1, 1, 2>(a, t, lds, s);
+    case 1: return ir_launch<1, 2, 2>(a, t, lds, s);
+    case 2: return ir_launch<1, 3, 2>(a, t, lds, s);
+    case 3: return ir_launch<1, 5, 1>(a, t, lds, s);
+    case 4: return ir_launch<2, 1, 2>(a, t, lds, s);
+    case 5: return ir_launch<2, 2, 2>(a, t, lds, s);
+    case 6: return ir_launch<2, 3, 2>(a, t, lds, s);
+    default: return ir_launch<2, 5, 1>(a, t, lds, s);
     }
-    return hipGetLastError();
 }
 
 }  // namespace ee

@@ -3,6 +3,7 @@ argument validation, blob validation, the exp2 table, and the scheduler against 
 import ctypes as C
 import os
 import re
+import subprocess
 from decimal import Decimal, getcontext
 
 import numpy as np
@@ -232,3 +233,60 @@ def test_adaptive_batching_timeline_through_the_library(ee):
     res, st, ev = ee.schedule_sim(2, arrivals, np.ones(7, np.int32), 4, np.full((2, 4), 10, np.int64), refill=0, t_timeout_ns=20, max_events=64)
     assert res["latency_ns"].tolist() == [40, 37, 23, 22, 21, 20, 40]
     assert [(int(e["t_ns"]), int(e["b"])) for e in ev[ev["kind"] == 1]] == [(20, 2), (53, 4), (74, 1)]
+
+
+# A program of the library's own launcher with the runtime's three calls in its place: the grant of more than 64 KB of LDS answers as told, a launch is only counted.
+IR_LAUNCH_PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "ee_internal.hpp"
+
+static hipError_t grant;
+static int launches;
+static size_t lds;
+extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return grant; }
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }      // what a failed call leaves has been fetched by somebody
+extern "C" hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t bytes, hipStream_t, hipEvent_t, hipEvent_t, int)
+{
+    ++launches;
+    lds = bytes;
+    return hipSuccess;
+}
+
+int main(int, char** argv)
+{
+    grant = (hipError_t)std::atoi(argv[1]);
+    int pooled;
+    ee::IrArgs a{};
+    a.pad = 1;
+    while (std::scanf("%d %d %d %d %d %d %d %d %d", &a.B, &a.H, &a.W, &a.Cin, &a.Kx, &a.Ce32, &a.Cout, &a.stride, &pooled) == 9) {
+        a.Ho = (a.H + a.stride - 1) / a.stride;
+        a.Wo = (a.W + a.stride - 1) / a.stride;
+        a.gap_sums = pooled ? (int*)8 : nullptr;
+        launches = 0;
+        const int first = (int)ee::launch_ir_block(a, nullptr), second = (int)ee::launch_ir_block(a, nullptr);
+        std::printf("%d %d %d %zu\n", first, second, launches, lds);
+    }
+}
+"""
+# samples, h, w, c_in, c_in in whole 32, expanded in whole 32, c_out, stride, pooled
+IR_LAUNCHES = [(1, 14, 14, 96, 96, 576, 160, 2, 0), (2, 14, 14, 160, 160, 960, 160, 2, 0), (1, 7, 7, 160, 160, 960, 160, 1, 0), (1, 7, 7, 160, 160, 960, 160, 1, 1), (1, 28, 28, 32, 32, 192, 32, 1, 0)]
+
+
+def test_inverted_residual_block_without_its_lds_is_an_error_every_time(ee, tmp_path):
+    """A block that needs more than 64 KB of LDS and does not get them: every launch says so, not only the one that asked; and none of them goes out."""
+    csrc = os.path.join(ROOT, "paper_2209_13443_amd", "csrc")
+    libdir = os.path.dirname(csrc)
+    (tmp_path / "launch.hip").write_text(IR_LAUNCH_PROGRAM)
+    exe = str(tmp_path / "launch")
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++20", "-I", csrc, str(tmp_path / "launch.hip"), "-o", exe, "-L", libdir, "-lee", "-Wl,-rpath," + libdir], check=True, timeout=120)
+    calls = "".join(" ".join(map(str, c)) + "\n" for c in IR_LAUNCHES)
+
+    def launched(grant):
+        out = subprocess.run([exe, str(grant)], input=calls, capture_output=True, text=True, check=True, timeout=60, env={**os.environ, "HIP_VISIBLE_DEVICES": "-1"}).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    granted, refused = launched(0), launched(1)
+    large = [g[3] > 64 * 1024 for g in granted]
+    assert all(g[:3] == (0, 0, 2) for g in granted) and any(large) and not all(large)
+    for big, g, r in zip(large, granted, refused):
+        assert r[:3] == ((1, 1, 0) if big else (0, 0, 2)), (g, r)
