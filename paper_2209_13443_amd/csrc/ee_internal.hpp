@@ -163,6 +163,7 @@ __device__ __forceinline__ int xcd_unit(unsigned block, int units)
 // All of a launch's arguments (BYTES in all, at least), a word of every 64-byte line, requested together at the start of a kernel.  They are in memory that no cache holds when a kernel starts; left to
 // itself the compiler loads each where it is first needed, a round trip to that memory per line not asked for before: three or four of them one after the other in front of a kernel's first load.
 // MobileNetV2, one image through every segment and head (31 launches) 166.8 -> 161.2 us; bf16 ResNet-50, 5 samples (62 launches) 386.5 -> 382.5.
+// BYTES ends inside the explicit arguments: the sum of the structures a kernel begins with, or explicit_args of the kernel's own list.
 template <int BYTES>
 __device__ __forceinline__ void request_args()
 {
@@ -170,6 +171,19 @@ __device__ __forceinline__ void request_args()
     const int x = [&]<int... LINE>(std::integer_sequence<int, LINE...>) { return (k[16 * LINE] ^ ...); }(std::make_integer_sequence<int, (BYTES + 63) / 64>{});
     asm volatile("" ::"s"(x));
 }
+
+// Bytes of a kernel's arguments, laid out one after the other at their alignment
+template <typename F> struct explicit_args;
+template <typename... A>
+struct explicit_args<void(A...)> {
+    static constexpr int bytes()
+    {
+        size_t n = 0;
+        ((n = (n + alignof(A) - 1) / alignof(A) * alignof(A) + sizeof(A)), ...);
+        return (int)n;
+    }
+};
+static_assert(explicit_args<void(int, void*, short, int)>::bytes() == 24, "padding in front of an argument, none behind the last");
 
 // ---- launchers (defined in the .hip files) -------------------------------------------------------
 hipError_t launch_conv_mfma_i8(const ConvArgs& a, hipStream_t s);

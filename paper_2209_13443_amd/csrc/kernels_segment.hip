@@ -33,7 +33,7 @@ __global__ __launch_bounds__(512) void segment_small_i8_kernel(SegRows, const Se
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Two round trips to memory in front of the first load of data: the arguments with the table of rows, then a line of every part of the plan that the layers read.  With the count of samples,
     // the other arguments, the row and the plan waited for one after the other 64 requests in 8 slots (24 steps) took 385 us, now 377.
-    request_args<sizeof(SegRows) + 72 + sizeof(HeadArgs)>();
+    request_args<explicit_args<decltype(segment_small_i8_kernel)>::bytes()>();
     const auto& a = *(SegPlanPtr)plan;
     {
         const __attribute__((address_space(4))) int* p = (const __attribute__((address_space(4))) int*)plan;
