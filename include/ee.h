@@ -87,7 +87,8 @@ int ee_exit_head(ee_ctx* ctx, int stage, int b_act, const void* act, float thr,
  * in a fixed array of EE_STATIC_SCRATCH_BYTES that is part of the library image (one copy per GPU, held until
  * the process ends) instead of the context's workspace; the call allocates nothing, on the host or the device,
  * and what it clears it clears with a kernel, not a memset node.  EE_ERR_OVERFLOW when
- *   4 * b_act * (C + n_cls)  (+ 4 * b_act * splits * C for bf16 networks whose pooling is split)
+ *   4 * b_act * (C + n_cls)  (+ 4 * b_act * splits * C for bf16 heads over more than 4096 pixels, which are pooled
+ * in `splits` parts, at most 32 and at most 512 / b_act + 1)
  * rounded up to 256-byte blocks exceeds the array; EE_ERR_DEVICE when the array's address cannot be found.
  * All calls on one GPU share the array, from every context: calls that overlap on one GPU (different
  * streams or threads) race and must be serialised by the caller.  ee_last_logits does not see this call. */

@@ -598,7 +598,7 @@ int alloc_lane(ee_ctx* ctx, LaneState& L)
         if ((rc = dev_alloc(ctx, &L.out_buf[s], (size_t)ctx->stage_out_bytes(s) * b_max))) return rc;
     if ((rc = dev_alloc(ctx, &L.in0, (size_t)ctx->stage_in_bytes(0) * b_max))) return rc;
     if ((rc = dev_alloc(ctx, &L.sums, sizeof(int32_t) * (size_t)b_max * ctx->c_max))) return rc;
-    if ((rc = dev_alloc(ctx, &L.gap_partial, sizeof(int32_t) * ((size_t)b_max + 1024) * ctx->c_max))) return rc;
+    if (ctx->c_partial && (rc = dev_alloc(ctx, &L.gap_partial, sizeof(int32_t) * ((size_t)b_max + 1024) * ctx->c_partial))) return rc;
     if ((rc = dev_alloc(ctx, &L.logits, 4 * (size_t)b_max * ctx->net.n_classes))) return rc;
     if ((rc = dev_alloc(ctx, &L.d_label, sizeof(int32_t) * (size_t)b_max))) return rc;
     if ((rc = dev_alloc(ctx, &L.d_conf, sizeof(float) * (size_t)b_max))) return rc;
@@ -785,6 +785,7 @@ extern "C" int ee_create(const void* blob, size_t bytes, int b_max, int dtype, v
         const ExitDesc& e = ctx->net.exits[s];
         if ((e.c * es) % 16 != 0 || e.c * es / 16 > 256 || e.n_cls > 2048) return fail(EE_ERR_UNSUPPORTED);
         c_max = std::max(c_max, e.c);
+        if (ctx->net.dtype == EE_BF16 && e.h * e.w > GAP_SLICE_PIXELS) ctx->c_partial = std::max(ctx->c_partial, (size_t)e.c);
         std::vector<unsigned char> w(base + e.w_off, base + e.w_off + (size_t)e.n_cls * e.c * es);
         std::vector<unsigned char> b(base + e.b_off, base + e.b_off + 4 * (size_t)e.n_cls);
         if (head_small_weights(e.c * es, e.n_cls) && (rc = upload(ctx, &ctx->wfc_dev[s], w))) return fail(rc);

@@ -91,7 +91,7 @@ struct ee_ctx {
     std::vector<const ee::SegPlan*> seg_dev;     // the same in device memory
     bool seg_fused(int s) const { return seg[(size_t)s].n > 0 && ir_mode > 0 && ee::forced_conv_tile() == 0; }
     int32_t* sums = nullptr;                     // [b_max][C_max]
-    int32_t* gap_partial = nullptr;              // [(b_max + 1024)][C_max] partial rows of the pooling splits
+    int32_t* gap_partial = nullptr;              // [(b_max + 1024)][C] partial rows of the pooling splits, where an exit head has any
     void* logits = nullptr;                      // [b_max][n_cls]
     void* zero_page = nullptr;                   // zero bytes read in place of padding taps
     // stream serving workspace
@@ -124,6 +124,7 @@ struct ee_ctx {
     int lane = 0;
     std::vector<size_t> pad_buf_bytes;           // size of every padded / folded input copy, for further lanes
     size_t c_max = 0;                            // widest exit head
+    size_t c_partial = 0;                        // widest one whose pooling may keep partial rows (0: none does)
     void bind_lane(int j);                       // makes lane j's stream and buffers the ones the launchers use
     // kernel timing
     bool profiling = false;

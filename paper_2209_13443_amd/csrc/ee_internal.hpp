@@ -304,7 +304,7 @@ struct HeadArgs {
     int gap_shift, frac_bits; float logit_scale;
     const void* wfc; const void* wfo; const void* bfc;      // weights as rows (heads that head_small may take, else null) and as ready operands (head_operands)
     int32_t* sums;       // [B][C] int32 sums (i8) or float means (bf16)
-    int32_t* gap_partial;   // bf16: [(B + 1024)][C] partial rows of the pooling splits
+    int32_t* gap_partial;   // bf16: [B][head_gap_splits(B, HW)][C] partial rows where that is more than one, else not used
     void* logits;        // [B][n_cls] int32 / float scratch
     int64_t s_thr; float thr; int last;
     int32_t* label; float* conf; int64_t* score; uint8_t* flag;
@@ -350,7 +350,8 @@ inline Outcome decode_outcome(const HostOutcome& h, bool int8)
 // device address, on the current GPU, of the scratch array that is part of the library image (EE_STATIC_SCRATCH_BYTES bytes)
 hipError_t static_scratch(void** out);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
-// workgroups the pooling kernel splits a sample's pixels over (bf16 keeps one partial row per split)
+constexpr int GAP_SLICE_PIXELS = 4096;      // bf16 pooling keeps partial rows only for images of more pixels
+// parts the bf16 pooling splits a sample's pixels into: more than one are partial rows, B + 511 of them at most for the batch
 int head_gap_splits(int B, int HW);
 hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s);
 hipError_t launch_head_fc(const HeadArgs& a, int dtype, hipStream_t s);

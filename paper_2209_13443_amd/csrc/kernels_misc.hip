@@ -557,7 +557,7 @@ __global__ __launch_bounds__(256) void gap_kernel(HeadArgs a, int pix_per_block,
     }
 }
 
-// Images of up to 4096 pixels: a workgroup per (sample, SCH chunks of 16 bytes of its channels) adds up every pixel, so that nothing is left to a second launch (bf16) or to atomics (int8).  Sums in a
+// Images of up to GAP_SLICE_PIXELS pixels: a workgroup per (sample, SCH chunks of 16 bytes of its channels) adds up every pixel, so that nothing is left to a second launch (bf16) or to atomics (int8).  Sums in a
 // fixed order: 1024 / SCH lanes per chunk take every pixel of their turn, a tree over the wavefront, then the 16 wavefronts in turn.
 template <int ES, int SCH>
 __global__ __launch_bounds__(1024) void gap_slice_kernel(HeadArgs a, int slices)
@@ -639,11 +639,19 @@ static int gap_pixels_per_block(int B, int HW)
     return ppb;
 }
 
+static int gap_pixel_splits(int B, int HW)
+{
+    const int ppb = gap_pixels_per_block(B, HW);
+    return (HW + ppb - 1) / ppb;
+}
+
+// bf16: what the pooling by pixels would share out goes by slices of channels (gap_slice_kernel), which keep no partial rows
+static bool gap_slices_bf16(int B, int HW) { return HW <= GAP_SLICE_PIXELS && gap_pixel_splits(B, HW) > 1; }
+
 int head_gap_splits(int B, int HW)
 {
     if (B <= 0 || HW <= 0) return 0;
-    const int ppb = gap_pixels_per_block(B, HW);
-    return (HW + ppb - 1) / ppb;
+    return gap_slices_bf16(B, HW) ? 1 : gap_pixel_splits(B, HW);
 }
 
 // Slices of channels while a workgroup's pixels are no more than it reads in about the time of a launch: the widest of up to 128 KB, and up to 256 bytes of a pixel rather than more than a workgroup
@@ -670,7 +678,6 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
     const int ppb = gap_pixels_per_block(a.B, a.HW);
-    const int splits = (a.HW + ppb - 1) / ppb;
     if (dtype == EE_I8) {
         // few pixels of many channels: us with atomics / by slices, 7x7x2048 1 to 64 samples 4.9-5.2 / 4.0-4.3, 256 8.9 / 6.7; 14x14x1024, 5 samples 4.7 / 4.5, 64 6.4 / 4.8; but 14x14x96 3.7 / 5.3,
         // 17x17x768 4.6 / 5.2 (37 samples and more 6.0 / 5.3), 28x28x512 4.3 / 5.8
@@ -678,12 +685,14 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
             launch_gap_slices<1>(a, s);
             return hipGetLastError();
         }
+        const int splits = gap_pixel_splits(a.B, a.HW);
         EE_LAUNCH(gap_kernel<1>, dim3(xcd_grid(a.B * splits)), dim3(256), 0, s, a, ppb, splits);
     } else {
-        if (splits > 1 && a.HW <= 4096) {
+        if (gap_slices_bf16(a.B, a.HW)) {
             launch_gap_slices<2>(a, s);
             return hipGetLastError();
         }
+        const int splits = head_gap_splits(a.B, a.HW);
         // two kernels when the pooling is split: a timed launch takes the first one's begin and the second one's end
         const hipEvent_t t0 = g_launch_start, t1 = g_launch_stop;
         if (splits > 1) g_launch_stop = nullptr;

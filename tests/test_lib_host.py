@@ -235,13 +235,13 @@ def test_adaptive_batching_timeline_through_the_library(ee):
     assert [(int(e["t_ns"]), int(e["b"])) for e in ev[ev["kind"] == 1]] == [(20, 2), (53, 4), (74, 1)]
 
 
-# A program of the library's own launcher with the runtime's three calls in its place: the grant of more than 64 KB of LDS answers as told, a launch is only counted.
-IR_LAUNCH_PROGRAM = r"""
+# Programs of the library's own launchers with the runtime's three calls in their place: the grant of more than 64 KB of LDS answers as told, a launch is only counted.
+LAUNCH_PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "ee_internal.hpp"
 
-static hipError_t grant;
+static hipError_t grant = hipSuccess;
 static int launches;
 static size_t lds;
 extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return grant; }
@@ -252,7 +252,8 @@ extern "C" hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t
     lds = bytes;
     return hipSuccess;
 }
-
+"""
+IR_LAUNCH_PROGRAM = LAUNCH_PROGRAM + r"""
 int main(int, char** argv)
 {
     grant = (hipError_t)std::atoi(argv[1]);
@@ -273,20 +274,48 @@ int main(int, char** argv)
 IR_LAUNCHES = [(1, 14, 14, 96, 96, 576, 160, 2, 0), (2, 14, 14, 160, 160, 960, 160, 2, 0), (1, 7, 7, 160, 160, 960, 160, 1, 0), (1, 7, 7, 160, 160, 960, 160, 1, 1), (1, 28, 28, 32, 32, 192, 32, 1, 0)]
 
 
-def test_inverted_residual_block_without_its_lds_is_an_error_every_time(ee, tmp_path):
-    """A block that needs more than 64 KB of LDS and does not get them: every launch says so, not only the one that asked; and none of them goes out."""
+def launch_program(tmp_path, source):
+    """Compiles the program against the library; returns run(calls, *arguments): a line of numbers in per call, a tuple of numbers out."""
     csrc = os.path.join(ROOT, "paper_2209_13443_amd", "csrc")
     libdir = os.path.dirname(csrc)
-    (tmp_path / "launch.hip").write_text(IR_LAUNCH_PROGRAM)
+    (tmp_path / "launch.hip").write_text(source)
     exe = str(tmp_path / "launch")
     subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++20", "-I", csrc, str(tmp_path / "launch.hip"), "-o", exe, "-L", libdir, "-lee", "-Wl,-rpath," + libdir], check=True, timeout=120)
-    calls = "".join(" ".join(map(str, c)) + "\n" for c in IR_LAUNCHES)
 
-    def launched(grant):
-        out = subprocess.run([exe, str(grant)], input=calls, capture_output=True, text=True, check=True, timeout=60, env={**os.environ, "HIP_VISIBLE_DEVICES": "-1"}).stdout
+    def run(calls, *arguments):
+        lines = "".join(" ".join(map(str, c)) + "\n" for c in calls)
+        out = subprocess.run([exe, *arguments], input=lines, capture_output=True, text=True, check=True, timeout=60, env={**os.environ, "HIP_VISIBLE_DEVICES": "-1"}).stdout
         return [tuple(map(int, line.split())) for line in out.splitlines()]
-    granted, refused = launched(0), launched(1)
+    return run
+
+
+def test_inverted_residual_block_without_its_lds_is_an_error_every_time(ee, tmp_path):
+    """A block that needs more than 64 KB of LDS and does not get them: every launch says so, not only the one that asked; and none of them goes out."""
+    run = launch_program(tmp_path, IR_LAUNCH_PROGRAM)
+    granted, refused = run(IR_LAUNCHES, "0"), run(IR_LAUNCHES, "1")
     large = [g[3] > 64 * 1024 for g in granted]
     assert all(g[:3] == (0, 0, 2) for g in granted) and any(large) and not all(large)
     for big, g, r in zip(large, granted, refused):
         assert r[:3] == ((1, 1, 0) if big else (0, 0, 2)), (g, r)
+
+
+GAP_LAUNCH_PROGRAM = LAUNCH_PROGRAM + r"""
+int main()
+{
+    ee::HeadArgs a{};
+    while (std::scanf("%d %d %d", &a.B, &a.HW, &a.C) == 3) {
+        launches = 0;
+        const int rc = (int)ee::launch_head_gap(a, EE_BF16, nullptr);
+        std::printf("%d %d %d\n", rc, launches, ee::head_gap_splits(a.B, a.HW));
+    }
+}
+"""
+
+
+def test_partial_rows_are_counted_where_the_pooling_keeps_them(ee, tmp_path):
+    """bf16 pooling: head_gap_splits, by which the head's scratch memory is sized, says more than one part exactly where a second launch adds partial rows up (which no pooling
+    by slices of channels has), and never more rows than a lane's memory for them."""
+    calls = [(b, hw, c) for b in (1, 5, 64, 200, 511, 512, 1024) for hw in (1, 15, 17, 49, 784, 4095, 4096, 4097, 112 * 112) for c in (8, 64, 2048)]
+    for (b, hw, _), (rc, launches, splits) in zip(calls, launch_program(tmp_path, GAP_LAUNCH_PROGRAM)(calls)):
+        assert rc == 0 and launches == (2 if splits > 1 else 1) and splits >= 1 and b * splits <= b + 1024, (b, hw, launches, splits)
+        assert splits == 1 or hw > 4096

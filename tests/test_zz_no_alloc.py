@@ -87,3 +87,21 @@ def test_static_scratch_head_rejects_what_does_not_fit():
     torch.cuda.synchronize()
     assert int(got[0][0]) == -7                               # nothing was launched
     eng.close()
+
+
+@pytest.mark.parametrize("h,w,c,b", [(7, 7, 2048, 200), (65, 64, 64, 5)])
+def test_static_scratch_head_of_bf16_with_and_without_partial_rows(h, w, c, b):
+    """200 samples of 7x7x2048 fit the array, as their pooling keeps no partial rows (three for each sample would be 4.9 MB); 65x64 pixels are pooled in parts, whose rows
+    lie in the array too.  The same bits as ee_exit_head."""
+    import torch
+    import paper_2209_13443_amd as ee
+    blob = W.single_layer_net("conv", h, w, 16, 1, 1, 0, W.DT_BF16, co=c)
+    eng = ee.Engine(blob, b)
+    act = torch.rand((b, h, w, c), generator=torch.Generator().manual_seed(1)).to(torch.bfloat16).view(torch.int16).cuda()
+    ref = eng.exit_head(0, act, 0.5)
+    got = outputs(torch, b)
+    eng.exit_head_static(0, act, 0.5, *got)
+    torch.cuda.synchronize()
+    for g, r, what in zip(got, ref, ("label", "conf", "score", "flag")):
+        assert torch.equal(g, r), what
+    eng.close()
