@@ -426,13 +426,21 @@ bool ir_block_plan(const IrArgs& a, IrTile& t, int& nco, int& maxb)
                        : t.ih * t.iw * 2 <= 256 * IR_FILL;
     };
     if (!fits()) return false;
-    // Few tiles: the wavefronts share the channel groups of a tile of one block, or two where one-block tiles would not all run at once (a workgroup to a CU).  Back to back, the
-    // pixels shared out / the groups, us: 14x14 stride 2, 96 -> 576 -> 160, 1 to 128 samples 19.7 / 10.6; 28x28, 32 -> 192 -> 32, 8 samples 7.9 / 6.2, 48 (672 tiles) 14.3 / 10.9,
-    // 96 15.6 / 17.7; stride 2, 56x56, 24 -> 144 -> 32, 8 samples (224) 8.1 / 6.1, 16 9.3 / 10.0; 28x28, 32 -> 192 -> 64, 32 samples (224) 8.2 / 6.6, 48 9.3 / 10.7; 14x14,
-    // 64 -> 384 -> 64, 128 samples (512) 17.9 / 14.5, 256 20.3 / 26.4, 40 samples in 280 tiles of one block 11.2, in 160 of two 8.3.
+    // Few tiles: the wavefronts share the channel groups of a tile of one block, or two where one-block tiles would not all run at once (a workgroup to a CU, two where one output block leaves
+    // registers for them).  A tile's time is a chain of groups whatever the number of tiles, so both forms' times are steps of whole rounds and the line lies where a round of the groups' form stops
+    // paying.  Back to back, the pixels shared out / the groups, us (tiles):
+    //   one output block, stride 1: 28x28, 32 -> 192 -> 32, 8 samples 6.5 / 5.2, 32 (448) 8.7 / 7.6, 40 (560) 10.1 / 10.7, 48 (672) 12.6 / 10.8, 54 (756) 12.6 / 10.9, 64 (896) 11.4 / 13.0; 40x40,
+    //     8 samples (400) 7.1 / 6.1, 12 (600) 8.3 / 8.8; 32x32, 32 -> 160 -> 32, 24 samples (768) 8.1 / 8.9: between 512 and 768 either may be the faster one by a tenth
+    //   stride 2, to three output blocks: 56x56, 24 -> 144 -> 32, 8 samples (224) 6.9 / 5.8, 10 (280) 7.5 / 9.6; 28x28, 32 -> 192 -> 64, 32 (224) 7.7 / 6.4, 37 (259) 8.5 / 10.8
+    //   two or three output blocks, stride 1, one reduction step: 28x28, 32 -> 192 -> 64, 18 samples (252) 7.6 / 6.2, 24 (336) 8.7 / 10.6; to 96, 16 (224) 8.7 / 6.9, 24 9.5 / 12.1; more steps or
+    //     none: 14x14, 64 -> 384 -> 64, 128 (512) 17.6 / 14.4, 160 (640) 21.4 / 20.6, 256 19.9 / 27.4, 40 samples in 280 tiles of one block 11.2, in 160 of two 8.3; 128 -> 64 without expansion, 128
+    //     samples (512) 7.6 / 5.8
+    //   five output blocks, one reduction step: 28x28, 32 -> 192 -> 128, 9 samples (252) 7.8 / 6.2, 16 (448) 10.5 / 10.8, 32 (896) 11.1 / 20.5; stride 2, to 160, 36 (252) 9.1 / 7.2, 64 (448) 10.8 / 12.9;
+    //     more steps or none: 14x14 stride 2, 96 -> 576 -> 160, 1 to 128 samples 19.5 / 10.5, 384 (768) 29.5 / 28.8, 448 (896) 29.7 / 37.2; 64 -> 384 -> 160, 109 (763) 24.5 / 19.7, 128 (896) 16.3 /
+    //     25.3; 160 -> 160 without expansion 109 11.4 / 10.8, 128 10.2 / 12.0; 7x7, 160 -> 960 -> 160, 384 (768) 46.7 / 37.9, 512 (1024) 48.1 / 49.1
     if (a.Ce32 >= (a.Kx == 32 ? 160 : 128) && (a.Kx == 32 || nco >= 2)) {       // the forms that are instantiated
         const int nw = a.Ce32 >= (a.Kx == 32 ? 160 : 320) ? 8 : 4;
-        const long long limit = nco == 5 ? 2048 : nco >= 2 && a.stride == 1 ? 512 : nco == 1 && a.stride == 1 ? 768 : 256;
+        const long long limit = nco == 1 ? (a.stride == 1 ? 768 : 256) : a.Kx == 32 ? 256 : nco == 5 ? 768 : a.stride == 1 ? 512 : 256;
         auto shared_tiles = [&](int blocks) -> long long {                      // how many tiles of that many blocks there are, 0: they do not fit
             t.pbw = t.pbh = 1; t.gp = nw;
             if (blocks == 2) (by_max > 1 && (bx_max == 1 || t.nbh <= t.nbw) ? t.pbh : t.pbw) = 2;

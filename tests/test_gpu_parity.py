@@ -183,7 +183,8 @@ def test_fused_inverted_residual_blocks_equal_separate_layers_and_oracle(torch, 
 IR_SHARED_CASES = [  # h, w, c_in, expanded, c_out, stride, (samples, wavefronts that share the channel groups or 0: the pixels) at the edges of the rule
     (14, 14, 96, 576, 160, 2, [(1, 8), (5, 8)]), (28, 28, 32, 192, 32, 1, [(9, 8), (10, 8), (54, 8), (55, 0)]), (28, 28, 32, 192, 64, 2, [(36, 8), (37, 0)]),
     (14, 14, 64, 384, 64, 1, [(36, 8), (37, 8), (128, 8), (129, 0)]), (13, 14, 24, 160, 32, 2, [(3, 8)]), (13, 11, 32, 192, 32, 1, [(1, 8)]), (5, 6, 64, 128, 48, 1, [(2, 4)]),
-    (15, 17, 64, 256, 144, 2, [(2, 4)]), (9, 9, 32, 128, 16, 1, [(2, 0)]),
+    (15, 17, 64, 256, 144, 2, [(2, 4)]), (9, 9, 32, 128, 16, 1, [(2, 0)]), (28, 28, 32, 192, 64, 1, [(18, 8), (19, 0)]), (28, 28, 32, 192, 160, 2, [(36, 8), (37, 0)]),
+    (14, 14, 64, 384, 160, 1, [(109, 8), (110, 0)]), (14, 14, 160, 0, 160, 1, [(109, 4), (110, 0)]),
 ]
 
 

@@ -242,13 +242,14 @@ LAUNCH_PROGRAM = r"""
 #include "ee_internal.hpp"
 
 static hipError_t grant = hipSuccess;
-static int launches;
+static int launches, lanes;
 static size_t lds;
 extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return grant; }
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }      // what a failed call leaves has been fetched by somebody
-extern "C" hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t bytes, hipStream_t, hipEvent_t, hipEvent_t, int)
+extern "C" hipError_t hipExtLaunchKernel(const void*, dim3, dim3 block, void**, size_t bytes, hipStream_t, hipEvent_t, hipEvent_t, int)
 {
     ++launches;
+    lanes = (int)block.x;
     lds = bytes;
     return hipSuccess;
 }
@@ -266,7 +267,7 @@ int main(int, char** argv)
         a.gap_sums = pooled ? (int*)8 : nullptr;
         launches = 0;
         const int first = (int)ee::launch_ir_block(a, nullptr), second = (int)ee::launch_ir_block(a, nullptr);
-        std::printf("%d %d %d %zu\n", first, second, launches, lds);
+        std::printf("%d %d %d %zu %d\n", first, second, launches, lds, lanes);
     }
 }
 """
@@ -297,6 +298,21 @@ def test_inverted_residual_block_without_its_lds_is_an_error_every_time(ee, tmp_
     assert all(g[:3] == (0, 0, 2) for g in granted) and any(large) and not all(large)
     for big, g, r in zip(large, granted, refused):
         assert r[:3] == ((1, 1, 0) if big else (0, 0, 2)), (g, r)
+
+
+# h, w, c_in, c_in in whole 32, expanded in whole 32, c_out, stride, the most samples whose tiles the wavefronts share by channel groups: measured edges, and none beyond them
+IR_SHARED_EDGES = [(14, 14, 64, 64, 384, 160, 1, 109), (14, 14, 96, 96, 576, 160, 2, 384), (7, 7, 160, 160, 960, 160, 1, 384), (28, 28, 32, 32, 192, 128, 1, 9),
+                   (28, 28, 32, 32, 192, 160, 2, 36), (28, 28, 32, 32, 192, 64, 1, 18), (28, 28, 32, 32, 192, 96, 1, 18), (14, 14, 64, 64, 384, 64, 1, 128), (28, 28, 32, 32, 192, 64, 2, 36),
+                   (28, 28, 32, 32, 192, 32, 1, 54)]
+
+
+def test_channel_groups_are_shared_out_only_where_that_was_measured_to_be_faster(ee, tmp_path):
+    """Workgroups of eight wavefronts up to the stated number of samples, and of four at any larger one up to 1024."""
+    samples = (1, 5, 64, 128, 256, 400, 512, 700, 1024)
+    calls = [(b, *shape, 0) for *shape, most in IR_SHARED_EDGES for b in sorted({most, most + 1, *samples})]
+    most = [m for *_, m in IR_SHARED_EDGES for b in sorted({m, m + 1, *samples})]
+    for (b, *shape, _), m, (first, _, launches, lds, lanes) in zip(calls, most, launch_program(tmp_path, IR_LAUNCH_PROGRAM)(calls, "0")):
+        assert first == 0 and launches == 2 and lanes == (512 if b <= m else 256), (b, shape, lds, lanes)
 
 
 GAP_LAUNCH_PROGRAM = LAUNCH_PROGRAM + r"""
