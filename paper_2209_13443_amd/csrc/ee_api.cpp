@@ -1128,7 +1128,7 @@ void ee_ctx::fill_seam_args(int op, int b, bool front, SeamArgs& a) const
     a.shift0 = f.d.shift; a.lo0 = f.d.lo; a.hi0 = f.d.hi;
 }
 
-int ee_ctx::seam_wanted(int op, int b) const
+int ee_ctx::seam_wanted(int stage, int op, int b) const
 {
     const OpPlan& p = plans[(size_t)op];
     if (!p.seam || pair_mode != 1) return 0;
@@ -1139,7 +1139,8 @@ int ee_ctx::seam_wanted(int op, int b) const
     if (!p.cfg.empty() || !plans[(size_t)op + 1].cfg.empty() || !f.cfg.empty()) return 0;      // a layer with a table of its own runs with it
     SeamArgs a{};
     fill_seam_args(op, b, front, a);
-    return conv_seam_default(a, front);
+    const OpPlan& q = plans[(size_t)op + 1];                                          // in a segment with fused layers the launch order is the network's
+    return conv_seam_default(a, front, q.group_n > 1 && group_by_default(stage, op + 1 - net.stages[(size_t)stage].first_op, q.group_n, b));
 }
 
 hipError_t ee_ctx::launch_seam(int op, int b, const void* src, const void* res, void* dst, void* dst2, int cfg)
@@ -1260,6 +1261,7 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
     };
     std::vector<std::vector<float>> best_time(ctx->plans.size());       // per layer and bucket: ms of the best configuration
     std::vector<std::vector<float>> pair_time(ctx->plans.size());       // and of the fused pair it heads
+    std::vector<std::vector<float>> joint_time(ctx->plans.size());      // and of the layers it can share a launch with and itself, in whichever way is faster
     for (size_t s = 0; s < ctx->net.stages.size() && !rc; ++s) {
         const StageDesc& st = ctx->net.stages[s];
         for (int k = 0; k < st.n_ops && !rc; ++k) {
@@ -1329,33 +1331,6 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
             }
             if (!rc) p.pair_cfg = best;
         }
-        // the seams of bottleneck blocks, without and with their 3x3 layer, against the pair or its two layers and the layer behind
-        for (int k = 1; k + 1 < st.n_ops && !rc; ++k) {
-            const int op = st.first_op + k;
-            const OpPlan& p = ctx->plans[op];
-            if (!p.seam) continue;
-            OpPlan& f = ctx->plans[op - 1];
-            const OpPlan& q = ctx->plans[op + 1];
-            auto at = [&](int buf) { return resolve(ctx, buf, ctx->in_buf[s], ctx->out_buf[s]); };
-            for (size_t bi = 0; bi < buckets.size() && !rc; ++bi) {
-                float best_ms = std::min(pair_time[op - 1][bi], best_time[op - 1][bi] + best_time[op][bi]) + best_time[op + 1][bi];
-                for (const int form : {0, (int)EE_CFG_SEAM_FRONT}) {
-                    std::vector<int> cands;
-                    for (int tm = 1; tm <= 2; ++tm)
-                        if (conv_seam_config_ok(EE_CFG_SEAM | form | tm, p.d.c_in, p.d.w_out, f.seam_front)) cands.push_back(EE_CFG_SEAM | form | tm);
-                    if (cands.empty()) continue;
-                    const auto found = fastest(cands, 2, layer_before(s, form ? k - 1 : k, buckets[bi]), [&](int cfg) {
-                        return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] {
-                            return ctx->launch_seam(op, buckets[bi], at(form ? f.src_buf : p.src_buf), at(p.res_buf), at(p.dst_buf), at(q.dst_buf), cfg);
-                        });
-                    });
-                    const float ms = found.first + (form ? 0.f : best_time[op - 1][bi]);
-                    if (ms >= best_ms) continue;
-                    best_ms = ms;
-                    f.pair_cfg[bi] = found.second;
-                }
-            }
-        }
     }
     // layers that can share a launch: every configuration of that launch against the layers one after the other
     for (size_t s = 0; s < ctx->net.stages.size() && !rc; ++s) {
@@ -1385,8 +1360,41 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                     return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] { return ctx->launch_group((int)s, at, p.group_n, b, ctx->in_buf[s], ctx->out_buf[s], cfg); });
                 });
                 if (found.first < best_ms) best[bi] = found.second;
+                joint_time[(size_t)head].push_back(std::min(found.first, best_ms));
             }
             if (!rc) p.group_cfg = best;
+        }
+    }
+    // the seams of bottleneck blocks, without and with their 3x3 layer, against the pair or its two layers and the layer behind, by itself or in the launch that it can share
+    for (size_t s = 0; s < ctx->net.stages.size() && !rc; ++s) {
+        const StageDesc& st = ctx->net.stages[s];
+        for (int k = 1; k + 1 < st.n_ops && !rc; ++k) {
+            const int op = st.first_op + k;
+            const OpPlan& p = ctx->plans[op];
+            if (!p.seam) continue;
+            OpPlan& f = ctx->plans[op - 1];
+            const OpPlan& q = ctx->plans[op + 1];
+            auto at = [&](int buf) { return resolve(ctx, buf, ctx->in_buf[s], ctx->out_buf[s]); };
+            for (size_t bi = 0; bi < buckets.size() && !rc; ++bi) {
+                float siblings = 0.f;                                       // what shares a launch with the layer behind, one by one
+                for (int j = 1; j < q.group_n; ++j) siblings += best_time[op + 1 + j][bi];
+                float best_ms = std::min(pair_time[op - 1][bi], best_time[op - 1][bi] + best_time[op][bi]) + (q.group_n > 1 ? joint_time[op + 1][bi] : best_time[op + 1][bi]);
+                for (const int form : {0, (int)EE_CFG_SEAM_FRONT}) {
+                    std::vector<int> cands;
+                    for (int tm = 1; tm <= 2; ++tm)
+                        if (conv_seam_config_ok(EE_CFG_SEAM | form | tm, p.d.c_in, p.d.w_out, f.seam_front)) cands.push_back(EE_CFG_SEAM | form | tm);
+                    if (cands.empty()) continue;
+                    const auto found = fastest(cands, 2, layer_before(s, form ? k - 1 : k, buckets[bi]), [&](int cfg) {
+                        return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] {
+                            return ctx->launch_seam(op, buckets[bi], at(form ? f.src_buf : p.src_buf), at(p.res_buf), at(p.dst_buf), at(q.dst_buf), cfg);
+                        });
+                    });
+                    const float ms = found.first + siblings + (form ? 0.f : best_time[op - 1][bi]);
+                    if (ms >= best_ms) continue;
+                    best_ms = ms;
+                    f.pair_cfg[bi] = found.second;
+                }
+            }
         }
     }
     // fused blocks: the one launch against the block's layers with their tuned configurations.  A block of four layers (a
@@ -1655,7 +1663,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             for (int j = 0; j < p.group_n && together; ++j) {
                 const int op = st.first_op + order[(size_t)(st.first_op + i + j)];
                 const OpPlan& m = plans[(size_t)op];
-                together = !ir_wanted(op, b) && !pair_wanted(m, b) && !(gap_fuse_dst && op == gap_fuse_op[(size_t)stage]) &&
+                together = !ir_wanted(op, b) && !pair_wanted(m, b) && !(pair_mode == 1 && (pair_entry(m, b, true) & EE_CFG_SEAM_FRONT)) && !(gap_fuse_dst && op == gap_fuse_op[(size_t)stage]) &&
                            (only_block < 0 || (op >= only_block && op <= only_block + plans[(size_t)only_block].ir_last())) &&
                            !(zc_in && m.d.res >= 0 && m.res_buf == BUF_EXT_IN);
                 g_ops += m.ops_per_sample * b;
@@ -1692,7 +1700,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             if ((p.seam || p.seam_front) && cfg == 0 && only_op == -1 && !xs) {
                 const int at = p.seam ? k : k + 1;                                 // the layer with the residual
                 const OpPlan& w = plans[st.first_op + at];
-                const int sc = zc_in && w.res_buf == BUF_EXT_IN ? 0 : seam_wanted(st.first_op + at, b);
+                const int sc = zc_in && w.res_buf == BUF_EXT_IN ? 0 : seam_wanted(stage, st.first_op + at, b);
                 if (sc && ((sc & EE_CFG_SEAM_FRONT) != 0) == p.seam_front) {                      // the layers at the seam as one launch
                     const OpPlan& q = plans[st.first_op + at + 1];
                     const double wide = (double)w.d.h_out * w.d.w_out * w.d.c_out * es * b, narrow = 2.0 * d.h_out * d.w_out * d.c_out * es * b;      // the wide tensor is not read back, the one in front of it stays on chip

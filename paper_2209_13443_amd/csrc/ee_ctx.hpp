@@ -175,7 +175,7 @@ struct ee_ctx {
     }
     // the configuration of the launch that runs the seam of two blocks, layer op (OpPlan::seam), the one behind it and (EE_CFG_SEAM_FRONT) the one in front of it, or 0: one by one; by
     // the table of the pair in front or (untuned) rule
-    int seam_wanted(int op, int b) const;
+    int seam_wanted(int stage, int op, int b) const;
     void fill_seam_args(int op, int b, bool front, ee::SeamArgs& a) const;       // the tensors are left to the caller
     hipError_t launch_seam(int op, int b, const void* src, const void* res, void* dst, void* dst2, int cfg);
     bool ir_wanted(int op, int b) const;                         // the fused block headed by layer op, by mode, table or (untuned) rule

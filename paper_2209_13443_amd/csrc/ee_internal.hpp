@@ -199,7 +199,7 @@ bool conv_pair_supported(int es, int co2, int kh, int kw, int ci, int co3);
 enum { EE_CFG_SEAM = 0x40000, EE_CFG_SEAM_FRONT = 0x10 };
 bool conv_seam_supported(int es, int c, int n1, int n2);
 bool conv_seam_config_ok(int cfg, int c, int W, bool front);       // cfg names such a launch, it exists there (front: whether the 3x3 layer can be part of it) and fits LDS
-int conv_seam_default(const SeamArgs& a, bool front);              // configuration of an untuned launch, or 0: the layers one by one are faster
+int conv_seam_default(const SeamArgs& a, bool front, bool joint);  // configuration of an untuned launch, or 0: the layers one by one are faster; joint: the last of them by itself would share a launch
 hipError_t launch_conv_seam(const SeamArgs& a, int cfg, hipStream_t s);
 // stride-1 "same" convolutions with the activation slab of a tile resident in LDS (kernels_slab.hip); cfg as documented there
 bool conv_slab_supported(const ConvArgs& a, int es);

@@ -345,12 +345,17 @@ bool conv_seam_config_ok(int cfg, int c, int W, bool front)
 //   C = 256 (14x14), tiles of 32 pixels: 16 samples (98 tiles) 98.0 / 100.4, 24 (147) 119.5 / 109.9, 40 (245) 143.3 / 133.1; of 64: 48 (147) 177.7 / 158.7, 64 192.9 / 174.3, 80 (245) 208.0 / 189.0;
 //     96 (294) 249.6 / 272.9
 // Without the 3x3 layer in front (the first block's is of stride 2) 2 to 3 us a seam at C = 128 in one round, 1 to 2 at C = 256, and nothing in two rounds.
-int conv_seam_default(const SeamArgs& a, bool front)
+// It is the tiles that count and not the image: four blocks of 3x3 to 56x56 and of 4x60 and 8x64 pixels at 7 to 1024 tiles, one by one / with the seams, are within 0.03 of each other at the same number
+// of tiles (C = 128: 7 tiles 1.10, 150 1.36, 250 1.38, 500 1.32, in two rounds of large ones 1.09 to 1.16; C = 256: 150 1.09, 250 1.11, 350 1.12, 500 1.14; without the 3x3 layer 1.04 to 1.16 and 1.05).
+// Where the last of the layers has a sibling that it shares a launch with (joint), the seam leaves that one a launch of its own: C = 128, beside a 64- or 512-channel 1x1, 13 tiles 0.98 / 0.89, 75 0.91 / 1.03,
+// 147 1.13 / 1.09, 250 1.18 / 1.15, 500 1.16 / 1.19; C = 256, 150 0.94 / 0.94, 250 1.01 / 1.07, 350 (in 175 large ones) 0.98 / 1.03, 500 (250) 1.08 / 1.12; without the 3x3 layer 0.82 to 1.05.
+int conv_seam_default(const SeamArgs& a, bool front, bool joint)
 {
     const int px = a.C == 128 ? 64 : 32, small = (a.M + px - 1) / px, large = (a.M + 2 * px - 1) / (2 * px), f = front ? EE_CFG_SEAM_FRONT : 0;
     int cfg = 0;
     if (a.C == 128) cfg = small <= 256 ? EE_CFG_SEAM | 1 : large <= (front ? 512 : 256) ? EE_CFG_SEAM | 2 : 0;
     else cfg = small > 128 && small <= 256 ? EE_CFG_SEAM | 1 : small > 256 && large <= 256 ? EE_CFG_SEAM | 2 : 0;
+    if (joint && (!front || ((cfg & 15) == 1 ? small : large) < (a.C == 128 ? 128 : 192))) return 0;
     return cfg && conv_seam_config_ok(cfg | f, a.C, a.W, front) ? cfg | f : 0;
 }
 

@@ -820,6 +820,40 @@ def test_untuned_seams_at_the_edges_of_their_rule(torch, ee, mid, hw, edges):
     eng.close()
 
 
+@pytest.mark.parametrize("mid, hw, front, edges", [(128, 28, True, [(1, 0), (10, 0), (11, 1), (40, 1), (83, 1)]), (256, 14, True, [(31, 0), (32, 1), (41, 1), (42, 0), (62, 0), (63, 1)]),
+                                                   (128, 28, False, [(1, 0), (20, 0)])])
+def test_untuned_seams_beside_a_joint_launch(torch, ee, mid, hw, front, edges):
+    """A 64-channel 1x1 layer reads the block's output too and shares a launch with the layer behind the seam: the seam runs only from the number of samples on at which it is worth more than that launch, without
+    the 3x3 layer never.  The same bytes as layer by layer on both sides of every edge, and with tuned tables."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, hw, hw, 4 * mid, 10)
+    t = net.begin_stage()
+    for _ in range(2):
+        u, sibling = net.conv(t, mid, 1, 1, 0), net.conv(t, 64, 1, 1, 0)
+        t = net.conv(net.conv(u if front else sibling, mid, 3, 1, 1), 4 * mid, 1, 1, 0, res=t)
+    net.end_stage(t)
+    blob = N._assemble(net, net.dtype, 21)
+    for op in blob.ops:
+        op["shift"] = int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * int(op["kh"]) * int(op["kw"])) / 127)))
+        op["res_shift"] = int(op["shift"]) - 1 if int(op["res"]) >= 0 else 0
+    n_max = max(b for b, _ in edges)
+    eng = ee.Engine(blob, n_max)
+    x = dev(torch, W.input_pool(blob, n_max))
+    for tuned in (False, True):
+        if tuned:
+            eng.pair_mode(1)
+            eng.autotune(reps=1)
+        for b, fused in edges:
+            say(f"[case] seam beside a joint launch {mid} {hw} {front} {b} {'tuned' if tuned else ''}")
+            eng.pair_mode(1)
+            n, got = launches_per_layer(torch, eng, blob, x[:b])
+            assert tuned or n == ([1, 0, 1, 0, 0, 1, 1, 1] if fused else [1, 0, 1, 1, 1, 0, 1, 1]), b
+            eng.pair_mode(0)
+            want = eng.stage_forward(0, x[:b], blob.stage_out_shape(0))
+            assert torch.equal(got, want) and torch.unique(want).numel() > 8, b
+    eng.close()
+
+
 ROWS_CASES = [  # h, w, input bytes per pixel, output channels, stride, samples: no whole tile, ragged last tiles, several tiles per workgroup, every channel grouping
     (1, 1, 128, 256, 1, 1), (5, 7, 128, 512, 1, 3), (9, 11, 256, 128, 2, 5), (56, 56, 128, 256, 1, 25), (13, 6, 256, 1024, 1, 4), (28, 28, 256, 256, 2, 9),
     (14, 14, 512, 512, 1, 7), (8, 8, 512, 128, 1, 3), (10, 10, 1024, 2048, 1, 20), (7, 7, 1024, 128, 1, 2),
