@@ -710,11 +710,31 @@ def test_small_segments_in_the_profile(torch, ee):
     eng.close()
 
 
+def requantised(blob, lo, hi, shift, seed):
+    """The network's convolutions with that shift and those bounds, weights and biases drawn so that results reach both bounds and fall between them (at 24 the bias alone decides)."""
+    r = np.random.default_rng(seed)
+    for op in blob.ops:
+        if int(op["kind"]) not in (W.OP_CONV, W.OP_DWCONV):
+            continue
+        w, b = blob.op_weights(op)
+        m = min(127, max(1, int(2 ** shift / np.sqrt(w.size / int(op["c_out"])))))     # results of a few hundred before the bounds
+        w[:] = r.integers(-m, m + 1, size=w.shape)
+        b[:] = r.integers(-2 ** min(30, shift + 7), 2 ** min(30, shift + 7), size=b.shape)
+        op["shift"], op["lo"], op["hi"] = shift, lo, hi
+        op["res_shift"] = min(shift, 22) if int(op["res"]) >= 0 else 0
+    return blob
+
+
+# the kernel that a forced configuration is there for: one of the test network's layers runs with it, the others take what covers them
+FORCED_KERNELS = {0: "conv_skinny_kernel<1,32,4,1,true>", 7: "conv_stream_i8_kernel<3,3,2>", 0x221: "conv_igemm_kernel<1,128,128,128,1,true>", 0x212: "conv_igemm_kernel<1,128,64,64,1,true>",
+                  0x4231: "conv_rows_kernel<1,128,4,32,true>", 0x4232: "conv_rows_kernel<1,128,4,64,true>", 0x2231: "conv_taps_kernel<1,2,4,1,4>", 0x4234: "conv_taps_kernel<1,2,2,1,4>"}
+
+
 @pytest.mark.parametrize("shift", [0, 1, 2, 9, 24])
 @pytest.mark.parametrize("lo, hi", [(0, 127), (-128, 127), (0, 96), (-9, 90)])
 def test_requantisation_bounds_and_shifts(torch, ee, orc, lo, hi, shift):
-    """Every kernel that requantises whole accumulator blocks (streamed, staged, with resident and with streamed weights, with and without a residual) at the shifts and bounds where
-    its forms part: shift 0 and 1, a shift that leaves only the bias, 0 .. 127 and others, against the oracle bit for bit."""
+    """The kernels of one layer that requantise whole accumulator blocks (for few pixels and staged with and without a residual, streaming and with streamed weights without, with resident
+    weights with one) at the shifts and bounds where their forms part: shift 0 and 1, a shift that leaves only the bias, 0 .. 127 and others, against the oracle bit for bit."""
     from workloads import nets as N
     net = N._Net(W.DT_I8, 9, 8, 32, 10)
     t = net.begin_stage()
@@ -722,22 +742,57 @@ def test_requantisation_bounds_and_shifts(torch, ee, orc, lo, hi, shift):
     t = res = net.conv(t, 128, 1, 1, 0)
     t = net.conv(t, 128, 3, 1, 1)
     net.end_stage(net.conv(t, 128, 1, 1, 0, res=res))
-    blob = N._assemble(net, net.dtype, 60 + shift)
-    r = np.random.default_rng(100 * shift + hi)
-    for op in blob.ops:
-        w, b = blob.op_weights(op)
-        m = min(127, max(1, int(2 ** shift / np.sqrt(w.size / int(op["c_out"])))))     # results of a few hundred before the bounds
-        w[:] = r.integers(-m, m + 1, size=w.shape)
-        b[:] = r.integers(-2 ** min(30, shift + 7), 2 ** min(30, shift + 7), size=b.shape)
-        op["shift"], op["lo"], op["hi"] = shift, lo, hi
-        op["res_shift"] = min(shift, 22) if int(op["res"]) >= 0 else 0
-    x = r.integers(-128, 128, size=(5, 9, 8, 32), dtype=np.int8)
+    blob = requantised(N._assemble(net, net.dtype, 60 + shift), lo, hi, shift, 100 * shift + hi)
+    x = np.random.default_rng(shift).integers(-128, 128, size=(5, 9, 8, 32), dtype=np.int8)
     ref = orc.stage_forward(blob, 0, x)
     eng = ee.Engine(blob, 5)
-    for cfg in (0, 7, 0x221, 0x212, 0x4231, 0x4232, 0x2231, 0x4234):
-        got = forced(ee, cfg, lambda: host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref))
+    for cfg, kernel in FORCED_KERNELS.items():
+        got, names = forced(ee, cfg, lambda: kernels_of(torch, lambda: host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref)))
+        assert kernel in names, (hex(cfg), names)
         assert np.array_equal(got, ref), f"cfg {cfg:#x}: {np.count_nonzero(got != ref)} of {ref.size} differ"
     assert np.unique(ref).size > 8 and (shift == 24 or (ref.min() == lo and ref.max() == hi))      # at 24 the bias alone decides, within the bounds
+    eng.close()
+
+
+def small_net(h, w, c):
+    """One segment of convolutions small enough to run with its exit head as one launch."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, h, w, c, 10)
+    t = net.conv(net.begin_stage(), 32, 3, 1, 1)
+    net.end_stage(net.conv(net.conv(t, 16, 3, 1, 1), 32, 1, 1, 0, res=t))
+    return N._assemble(net, net.dtype, 5)
+
+
+FUSED_REQUANT = {  # network, tables, what its one launch of several layers (or of few input channels) is
+    "seam": (lambda: W.bottleneck_net(9, 8, 512, blocks=2, mid=128), {"pair": {"1": [0x40001] * 4}}, "conv_seam_kernel<4,1,false>"),
+    "seam with its 3x3 layer": (lambda: W.bottleneck_net(9, 8, 512, blocks=2, mid=128), {"pair": {"1": [0x40011] * 4}}, "conv_seam_kernel<4,1,true>"),
+    "wide seam": (lambda: W.bottleneck_net(5, 8, 1024, blocks=2, mid=256), {"pair": {"1": [0x40012] * 4}}, "conv_seam_kernel<8,2,true>"),
+    "bottleneck block": (lambda: W.bottleneck_net(9, 11, 256), {}, "bneck_block_i8_kernel<"),
+    "bottleneck block with its shortcut": (lambda: W.bottleneck_net(9, 11, 64), {}, "bneck_block_i8_kernel<"),
+    "inverted residual": (lambda: W.inverted_residual_net(9, 11, 32, 192, 32, 1), {}, "ir_block_i8_kernel<"),
+    "first layer and pool": (lambda: W.stem_net(30, 32), {}, "stem_pool_i8_kernel<6,4>"),
+    "small segment": (lambda: small_net(6, 7, 16), {}, "segment_small_i8_kernel"),
+    "few input channels": (lambda: W.single_layer_net("conv", 10, 12, 24, 1, 1, 0, W.DT_I8, co=96), {}, "conv_thin_i8_kernel"),
+}
+
+
+@pytest.mark.parametrize("shift", [0, 1, 24])
+@pytest.mark.parametrize("lo, hi", [(0, 127), (-128, 127), (0, 96)])
+@pytest.mark.parametrize("kind", FUSED_REQUANT)
+def test_requantisation_in_launches_of_several_layers(torch, ee, orc, kind, lo, hi, shift):
+    """The same for the kernels that a forced configuration does not reach: the launch named is among those that ran, and the segment's output is the oracle's bit for bit."""
+    net, tables, kernel = FUSED_REQUANT[kind]
+    blob = requantised(net(), lo, hi, shift, 10 * shift + hi)
+    b = 3
+    x = np.random.default_rng(shift).integers(-128, 128, size=(b,) + blob.stage_in_shape(0), dtype=np.int8)
+    ref = orc.stage_forward(blob, 0, x)
+    eng = ee.Engine(blob, b)
+    eng.load_tables(tables)
+    eng.ir_mode(2)
+    got, names = kernels_of(torch, lambda: host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref))
+    assert any(n.startswith(kernel) for n in names), names
+    assert np.array_equal(got, ref), f"{np.count_nonzero(got != ref)} of {ref.size} differ"
+    assert (np.unique(ref).size > 8 or shift == 24) and (shift == 24 or (ref.min() == lo and ref.max() == hi))
     eng.close()
 
 
