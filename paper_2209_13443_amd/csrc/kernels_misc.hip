@@ -748,7 +748,10 @@ __global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
             const int kb = (s0 + NW * u) * 64 + kq * 16;
             const bool kin = kb < CB;
 #pragma unroll
-            for (int t = 0; t < TC; ++t) wv[u][t] = wtile[t][min(s0 + NW * u, nsteps - 1) * 64];      // a step past the last meets features of zero
+            for (int t = 0; t < TC; ++t) {                      // a step past the last meets features of zero; bf16: weights of zero too, as an infinite one times zero is no number
+                wv[u][t] = wtile[t][min(s0 + NW * u, nsteps - 1) * 64];
+                if (ES == 2 && s0 + NW * u >= nsteps) wv[u][t] = zero4;
+            }
             const int* sp = a.sums + (long long)min(b, a.B - 1) * a.C + kb / ES;
 #pragma unroll
             for (int q = 0; q < (ES == 1 ? 4 : 2); ++q) gv[u][q] = kin && bin ? *(const v4i*)(sp + 4 * q) : zero4;

@@ -508,6 +508,30 @@ def test_class_tiles_per_workgroup_of_the_fc(torch, ee, orc, c, n_cls, dtype):
     eng.close()
 
 
+def test_infinite_weights_of_the_fc(torch, ee, orc):
+    """bf16: an infinite weight in the last step of a reduction that is shorter than what the wavefronts have in flight makes its class's logit infinite and no other, with every number of class tiles per
+    workgroup: logits and labels are the oracle's."""
+    from workloads import nets as N
+    net = N._Net(W.DT_BF16, 2, 1, 64, 300)
+    net.begin_stage()
+    net.end_stage(net.maxpool(0, 3, 1, 1))
+    blob = N._assemble(net, net.dtype, 19)
+    blob.exit_weights(0)[0].reshape(300, 64)[7, 40] = 0x7f80
+    edges = {1: 1, 16 * 13 + 1: 2, 16 * 25 + 1: 4}
+    eng = ee.Engine(blob, max(edges))
+    act = np.empty((max(edges), 2, 1, 64), np.uint16)
+    act[:, 0], act[:, 1] = 0x3f80, 0x3f81                    # means of 1 + 2^-8: 1 and a remainder above zero
+    _, _, _, _, logits = orc.exit_head(blob, 0, act[:1], 0.5, want_logits=True)
+    finite = np.isfinite(logits[0])
+    assert logits[0, 7] == np.inf and finite.sum() == 299
+    for b, tc in edges.items():
+        (lab, _, _, _), names = kernels_of(torch, lambda: eng.exit_head(0, dev(torch, act[:b]), 0.5))
+        assert f"fc_kernel<2,4,{tc}>" in names, names
+        got = eng.last_logits(b, 300)
+        assert np.all(got[:, 7] == np.inf) and np.all(np.abs(got[:, finite] - logits[:, finite]) <= 1e-3 * np.abs(logits[0, finite]).max()) and bool((lab == 7).all())
+    eng.close()
+
+
 @pytest.mark.parametrize("h, w, c, edges", [(7, 7, 2048, {1: 64, 9: 64}), (5, 13, 1032, {3: 64}), (14, 14, 1024, {2: 32}), (28, 28, 504, {1: 8, 33: 16}), (56, 56, 256, {2: 4, 33: 8, 65: 16}),
                                             (64, 64, 24, {3: 4}), (64, 65, 24, {3: None})], ids=str)
 def test_bf16_pooling_by_slices_of_channels(torch, ee, orc, h, w, c, edges):
