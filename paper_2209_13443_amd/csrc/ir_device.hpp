@@ -9,13 +9,6 @@ typedef int v2i_r __attribute__((ext_vector_type(2)));
 typedef int v4i_r __attribute__((ext_vector_type(4)));
 typedef int v16i_r __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ int ir_med3(int v, int lo, int hi)       // lo <= hi: v clamped to [lo, hi]
-{
-    int r;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "v"(lo), "v"(hi));
-    return r;
-}
-
 // Requantisation bounds on the unshifted accumulator: clamp(acc >> s, lo, hi) == clamp(acc, lo * 2^s, (hi + 1) * 2^s - 1) >> s
 // (the shift rounds down, so it is monotone); a bound outside int32 clamps nothing, which is then also right.
 struct IrClamp { int shift, lo, hi; };

@@ -3,7 +3,7 @@
 
 namespace ee {
 
-// Two wavefronts per SIMD as the least (here and in every kernel whose workgroup is 256 lanes): a wavefront then has at most 256 registers, and the compiler keeps the accumulators where
+// Two wavefronts per SIMD as the least (here and in the other kernels of one layer, of layers side by side and of a pair; fused blocks, seams and the convolution with its pool have bounds of their own): a wavefront then has at most 256 registers, and the compiler keeps the accumulators where
 // ordinary instructions read them; allowed 512 it put them into the other half of the file, an instruction per value away (1x1, 64 -> 256, 56x56, 64 samples 17.1 -> 15.2 us).
 template <int ES, int BM, int BN, int KS, int KSPL, bool PLAIN>
 __global__ __launch_bounds__(256 * KSPL, 2) void conv_igemm_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, int ns)

@@ -34,9 +34,9 @@
 // expands, filters and projects every pixel of the tile for the groups g = wavefront, wavefront + 4 (or 8), ... through a buffer
 // of its own, with no barrier inside the loop; the partial projection sums are added in LDS (integer adds,
 // exact in any order) and the epilogue is shared out by (pixel block, output block).
-// What bounds it: blocks on large images the way from a workgroup's start to its first group: copies of the kernel without the groups' loop take 16.7 of 30 us (112 x 112 -> 56 x 56,
-// 16 -> 96 -> 24 channels, 64 images), 9.4 of 22.5 (56 x 56, 24 -> 144 -> 24); the groups themselves use the vector ALU, LDS and matrix cores about alike (5-6 us each of the latter).  Those on small
-// images wait for their chain of loads, matrix instructions and barriers; 7 x 7, 160 -> 960 -> 160 for the 450 KB of weights that a workgroup reads through its CU's path, 3.9 of 11.7 us.
+// What bounds it: blocks on large images issue vector instructions for half of their time (112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels, 64 images: 8.1 M, 13 of 26.6 us; 56 x 56, 24 -> 144 -> 24: 5.5 M, 9
+// of 21.0) and matrix instructions for 2.7 and 3.7 us; the way from a workgroup's start to its first group and the end take 11.7 and 7.1 us by themselves (copies of the kernel without any group; 28 x 28,
+// 32 -> 192 -> 32: 4.8 of 12.0).  Those on small images wait for their chain of loads, matrix instructions and barriers; 7 x 7, 160 -> 960 -> 160 for the 450 KB of weights that a workgroup reads through its CU's path, 3.9 of 11.7 us.
 // (Loading the first group's weights in front of the input, and the next group's ahead in GP, was 0-8 % slower everywhere: weights queue in front of the input.)
 // Every accumulation is int32 and exact, rounding points are those of the three separate layers: results are equal
 // bit for bit.
@@ -71,6 +71,7 @@ constexpr int IR_MAXK = 5;                    // reduction steps of 32 input cha
 // MAXK = 0: a block without expansion (depthwise -> projection): the buffers of "expanded" pixels are filled with the
 // block's input itself, 32 channels at a time.
 // POOL: the exit head's pooling in the epilogue (a kernel of its own: with a branch the others' launches on one image took 0.15 us longer each)
+// Registers: <1, 1, 2, 1, 0, true>, held to 128, keeps two more in scratch memory (12 bytes a lane); no other form spills.
 template <int STRIDE, int NCO, int MAXB, int MAXK, int GP, bool POOL>
 __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) ? (MAXK == 1 ? 4 : 3) : 2) void ir_block_i8_kernel(IrArgs a, IrTile t)
 {

@@ -713,8 +713,8 @@ hipError_t launch_head_gap(const HeadArgs& a, int dtype, hipStream_t s)
 // classes (A operand, ready operands of 1 KB a step: with rows read 64 bytes at a time the 2048-channel bf16 head of 16 samples took 9.7 us, now 6.8), columns = 16
 // samples (B operand, the pooled features: requantised on the fly for int8; split into a bf16 head and
 // a bf16 remainder for bf16 so that the float mean loses nothing that matters).  The NW wavefronts take
-// every NWth 64-byte step of the reduction and add their partial tiles through LDS.  Bound by latency: NW is chosen so that
-// every wavefront has all its loads in flight at once (up to four steps each).
+// every NWth 64-byte step of the reduction and add their partial tiles through LDS.  Bound by latency: a wavefront
+// has the loads of four steps in flight with one tile of classes, of two with more, and NW is chosen so that one tile's reductions of up to 2 KB are all in flight at once.
 //   v_mfma_i32_16x16x64_i8 / v_mfma_f32_16x16x32_bf16, lane l: row l%16, k-bytes [16*(l/16), +16);
 //   D: column l%16, rows 4*(l/16) + v for accumulator register v = 0..3.
 typedef float v4f_m __attribute__((ext_vector_type(4)));
@@ -827,7 +827,7 @@ static void launch_fc(const HeadArgs& a, hipStream_t s)
 hipError_t launch_head_fc(const HeadArgs& a, int dtype, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
-    const bool wide = a.C * (dtype == EE_I8 ? 1 : 2) > 1024;      // more than the 16 steps four wavefronts have in flight
+    const bool wide = a.C * (dtype == EE_I8 ? 1 : 2) > 1024;      // more than the 16 steps four wavefronts have in flight with one tile of classes
     if (dtype == EE_I8) {
         if (wide) launch_fc<1, 8>(a, s);
         else launch_fc<1, 4>(a, s);

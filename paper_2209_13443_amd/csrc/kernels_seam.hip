@@ -46,6 +46,7 @@ template <int N>
 __device__ __forceinline__ void seam_wait_copies() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void seam_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// Twelve wavefronts leave 168 registers to each.  The widest form (C = 256, 64 pixels, with the 3x3 layer) keeps four more than that in scratch memory (20 bytes a lane), the others none.
 template <int NB, int TM, bool FRONT>
 __global__ __launch_bounds__(768, 3) void conv_seam_kernel(SeamArgs a, int over_bytes, unsigned slab_bytes)
 {

@@ -12,7 +12,7 @@
 //
 // Measured on a network of 32 x 32 images (three segments of two 3x3 layers, 16 / 32 / 64 channels, 10 classes) against the layers' own launches, two
 // processes of each in turn: all segments and heads 1 to 256 samples 81-101 us -> 53; streams of 64 requests one by one 2510-2740 -> 1770 us, 64 in 8 slots
-// 557-617 -> 399, 2000 in 64 slots on two lanes 1090-1250 -> 700, 5000 in 256 slots 790-870 -> 590.  What bounds it (time stamps, 8.7 us a launch): latency.  0.6 us for the launch's arguments, 1.2 for the requests, 0.7 the folding, 1.5 to 2.5 a
+// 557-617 -> 399, 2000 in 64 slots on two lanes 1090-1250 -> 700, 5000 in 256 slots 790-870 -> 590.  What bounds it (time stamps, 8.2 us a launch): latency.  0.6 us for the launch's arguments, 1.2 for the requests, 0.7 the folding, 1.5 to 2.5 a
 // layer (300 instructions per item in one dependent chain and two wavefronts per SIMD), 1.3 the logits and the decision.
 #include "ee_internal.hpp"
 #include "head_device.hpp"
@@ -32,7 +32,7 @@ __global__ __launch_bounds__(512) void segment_small_i8_kernel(SegRows, const Se
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Two round trips to memory in front of the first load of data: the arguments with the table of rows, then a line of every part of the plan that the layers read.  With the count of samples,
-    // the other arguments, the row and the plan waited for one after the other 64 requests in 8 slots (24 steps) took 385 us, now 377.
+    // the other arguments, the row and the plan waited for one after the other a launch took 8.7 us, now 8.2; a stream of 24 such steps moves by less than two of its runs differ.
     request_args<explicit_args<decltype(segment_small_i8_kernel)>::bytes()>();
     const auto& a = *(SegPlanPtr)plan;
     {
