@@ -656,7 +656,8 @@ int head_gap_splits(int B, int HW)
 
 // Slices of channels while a workgroup's pixels are no more than it reads in about the time of a launch: the widest of up to 128 KB, and up to 256 bytes of a pixel rather than more than a workgroup
 // per CU.  bf16, the two kernels / this one, us: 56x56x256, 5 samples 7.3 / 5.8 (in slices of 64 bytes; 7.2 in 128, 11.0 in 256), 64 22.1 / 18.1, 256 76.9 / 72.9; 28x28x512, 5 samples
-// 7.8 / 4.5, 256 35.9 / 31.1; 14x14x1024, 5 samples 7.2 / 4.2, 64 10.0 / 6.4; 7x7x2048, 5 samples 7.3 / 3.7.
+// 7.8 / 4.5, 256 35.9 / 31.1; 14x14x1024, 5 samples 7.2 / 4.2, 64 10.0 / 6.4; 7x7x2048, 5 samples 7.3 / 3.7.  Where the batch is some 400 MB and more both are at the rate of HBM and within 4 %, the
+// slices mostly ahead (64x64x384, 200 samples 123.8 / 115.5; behind at 64x64x512, 128 samples 98.8 / 102.7).
 template <int ES>
 static void launch_gap_slices(const HeadArgs& a, hipStream_t s)
 {
