@@ -35,8 +35,8 @@
 // of its own, with no barrier inside the loop; the partial projection sums are added in LDS (integer adds,
 // exact in any order) and the epilogue is shared out by (pixel block, output block).
 // What bounds it: blocks on large images issue vector instructions for half of their time (112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels, 64 images: 8.1 M, 13 of 26.6 us; 56 x 56, 24 -> 144 -> 24: 5.5 M, 9
-// of 21.0) and matrix instructions for 2.7 and 3.7 us; the way from a workgroup's start to its first group and the end take 11.7 and 7.1 us by themselves (copies of the kernel without any group; 28 x 28,
-// 32 -> 192 -> 32: 4.8 of 12.0).  Those on small images wait for their chain of loads, matrix instructions and barriers; 7 x 7, 160 -> 960 -> 160 for the 450 KB of weights that a workgroup reads through its CU's path, 3.9 of 11.7 us.
+// of 21.0, counted before the tile was read through a buffer, which took a third of the instructions in front of the groups away) and matrix instructions for 2.7 and 3.7 us; a third of a workgroup's life is
+// the way to its first group (6,000 of 17,000 cycles on the first of them: arguments 1,900, pixels there 3,500, barrier 6,000).  Those on small images wait for their chain of loads, matrix instructions and barriers; 7 x 7, 160 -> 960 -> 160 for the 450 KB of weights that a workgroup reads through its CU's path, 3.9 of 11.7 us.
 // (Loading the first group's weights in front of the input, and the next group's ahead in GP, was 0-8 % slower everywhere: weights queue in front of the input.)
 // Every accumulation is int32 and exact, rounding points are those of the three separate layers: results are equal
 // bit for bit.
@@ -66,6 +66,21 @@ constexpr int ir_maxcb(int gp, int stride) { return gp && stride == 2 ? 5 : 3; }
 constexpr int IR_SHARED_LDS = 96 * 1024;      // LDS bytes where the wavefronts share the channel groups (their registers leave one workgroup to a CU)
 constexpr int IR_FILL = 4;                    // 16-byte loads per lane that fill a buffer without expansion: ih * iw * 2 <= 1024
 constexpr int IR_MAXK = 5;                    // reduction steps of 32 input channels: c_in <= 160 (template parameter MAXK: 1, 2 or 5)
+
+// The block's input image n as a buffer, of which loads out of range (before the image too: offsets are unsigned) give zeros.  Where a load's address was chosen by a condition instead, the compiler made
+// two loads of it, one for the lanes on either side, and waited in front of each for the one before: a tile's chunks arrived one round trip to memory after the other.  64 samples, us: 112x112 stride 2,
+// 16 -> 96 -> 24 27.8 -> 25.9, 56x56 stride 2, 24 -> 144 -> 32 13.8 -> 12.6, 28x28, 32 -> 192 -> 32 12.3 -> 11.2; all segments 262 -> 253, of 20 samples 185 -> 178, of one 129 -> 126.
+__device__ __forceinline__ auto image(const IrArgs& a, int n)
+{
+    const int bytes = a.H * a.W * a.Cin;
+    return __builtin_amdgcn_make_buffer_rsrc((char*)a.x + (size_t)n * bytes, (short)0, bytes, 0x00020000);
+}
+template <typename V>
+__device__ __forceinline__ V image_load(__amdgpu_buffer_rsrc_t x, int at)
+{
+    if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(x, at, 0, 0));
+    else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, 0));
+}
 
 // GP = 0: four wavefronts share the pixels; GP = 4 or 8: that many wavefronts share the channel groups.
 // MAXK = 0: a block without expansion (depthwise -> projection): the buffers of "expanded" pixels are filled with the
@@ -112,31 +127,28 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
             if constexpr (EXP) bias_e = *(const v4i_r*)((const unsigned char*)a.be + tid * 16);
             bias_d = *(const v4i_r*)((const unsigned char*)a.bd + tid * 16);
         }
-        const unsigned char* x = (const unsigned char*)a.x + (size_t)n * a.H * a.W * a.Cin;
-        asm volatile("" : "+s"(x));                                     // in registers: else the pointer is fetched anew, and waited for, in front of every load below
+        const auto x = image(a, n);
         const int nchunks = EXP ? t.ih * t.iw * t.cpp : 0;
+        // A chunk e of the window lies CB * e bytes behind its first one, and (W - iw) pixels further for every row.  What the window reaches over the image's rows reads zeros (out of the buffer's
+        // range), what it reaches over their ends the next row's pixels: the expansion reads neither.  Lanes past the last chunk copy that one again.
+        const int skip = (a.W - t.iw) * a.Cin, gap = t.xp - a.Cin;
         auto stage_chunks = [&](auto zero) {                            // in chunks of 8 or 16 bytes
             using V = decltype(zero);
             constexpr int CB = sizeof(V);
+            const int origin = (iy0 * a.W + ix0) * a.Cin;
             V stage[IR_BATCH];
-            unsigned dst[IR_BATCH];                                     // LDS byte offset, ~0u: nothing to write
+            unsigned dst[IR_BATCH];                                     // LDS byte offset
 #pragma unroll
             for (int batch = 0; batch < IR_BATCHES; ++batch) {
                 if (batch > 0 && NT * IR_BATCH * batch >= nchunks) break;   // wave-uniform
 #pragma unroll
                 for (int i = 0; i < IR_BATCH; ++i) {
-                    dst[i] = ~0u;
-                    stage[i] = V{};
                     const int e0 = NT * (batch * IR_BATCH + i);
                     if (e0 < nchunks) {                                     // wave-uniform
                         const int e = min(e0 + tid, nchunks - 1);
-                        const int q = t.cpp == 1 ? e : (int)__umulhi((unsigned)e, t.magic_cpp), ch = e - q * t.cpp;   // 2^32 / 1 + 1 does not fit the magic number
-                        const int py = (int)__umulhi((unsigned)q, t.magic_iw), px = q - py * t.iw;
-                        const int iy = iy0 + py, ix = ix0 + px;
-                        const bool ok = e0 + tid < nchunks && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-                        // the load is unconditional and in range (a chunk that is not wanted reads the image's first bytes)
-                        stage[i] = *(const V*)(x + (ok ? (unsigned)((iy * a.W + ix) * a.Cin + CB * ch) : 0u));
-                        if (ok) dst[i] = (unsigned)(q * t.xp + CB * ch);
+                        const int q = t.cpp == 1 ? e : (int)__umulhi((unsigned)e, t.magic_cpp), py = (int)__umulhi((unsigned)q, t.magic_iw);      // 2^32 / 1 + 1 does not fit the magic number
+                        stage[i] = image_load<V>(x, origin + py * skip + CB * e);
+                        dst[i] = (unsigned)(CB * e + q * gap);
                     }
                 }
                 if (batch == 0) {
@@ -156,7 +168,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
                 }
 #pragma unroll
                 for (int i = 0; i < IR_BATCH; ++i)
-                    if (dst[i] != ~0u) *(V*)(l_x + dst[i]) = stage[i];
+                    if (NT * (batch * IR_BATCH + i) < nchunks) *(V*)(l_x + dst[i]) = stage[i];
             }
         };
         if constexpr (GP || MAXK > 1) {
@@ -250,30 +262,26 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     unsigned fdst[EXP ? 1 : IR_FILL];
     auto fill_load = [&](int g) {
         if constexpr (!EXP) {
-            const unsigned char* x = (const unsigned char*)a.x + (size_t)n * a.H * a.W * a.Cin;
+            const auto x = image(a, n);
             const int nch = t.ih * t.iw * 2, ft = GP ? lane : tid;
 #pragma unroll
-            for (int i = 0; i < IR_FILL; ++i) {
-                fdst[i] = ~0u;
-                fl[i] = v4i_r{0, 0, 0, 0};
-                if (FT * i < nch) {                                     // wave-uniform
+            for (int i = 0; i < IR_FILL; ++i)
+                if (FT * i < nch) {                                     // wave-uniform; lanes past the last chunk copy that one again
                     const int e = min(FT * i + ft, nch - 1), p = e >> 1, half = e & 1;
-                    const int py = (int)__umulhi((unsigned)p, t.magic_iw), px = p - py * t.iw;
-                    const int iy = iy0 + py, ix = ix0 + px;
-                    const bool in_img = FT * i + ft < nch && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-                    const bool ok = in_img && (a.Cin % 32 == 0 || g * 32 + 16 * half < a.Cin);
-                    fl[i] = *(const v4i_r*)(x + (ok ? (unsigned)((iy * a.W + ix) * a.Cin + g * 32 + 16 * half) : 0u));      // unconditional, in range
-                    if (!ok) fl[i] = v4i_r{0, 0, 0, 0};
-                    if (FT * i + ft < nch) fdst[i] = (unsigned)(py * e_row + px * 32 + 16 * half);
+                    const int py = (int)__umulhi((unsigned)p, t.magic_iw), px = p - py * t.iw, ix = ix0 + px, ch = g * 32 + 16 * half;
+                    const int at = ((iy0 + py) * a.W + ix) * a.Cin + ch;
+                    // rows outside the image lie out of the buffer's range by themselves
+                    fl[i] = image_load<v4i_r>(x, (unsigned)ix < (unsigned)a.W && ch < a.Cin ? at : (int)0x80000000u);
+                    fdst[i] = (unsigned)(py * e_row + px * 32 + 16 * half);
                 }
-            }
         }
     };
     auto fill_store = [&](unsigned char* ebuf) {
         if constexpr (!EXP) {
+            const int nch = t.ih * t.iw * 2;
 #pragma unroll
             for (int i = 0; i < IR_FILL; ++i)
-                if (fdst[i] != ~0u) *(v4i_r*)(ebuf + fdst[i]) = fl[i];
+                if (FT * i < nch) *(v4i_r*)(ebuf + fdst[i]) = fl[i];
         }
     };
     auto dw_project = [&](int g, const unsigned char* ebuf) {
