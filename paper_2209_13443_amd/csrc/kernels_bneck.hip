@@ -42,6 +42,8 @@ constexpr int BN_SLOT_BYTES = 2 * EE_ZC_MAX_B;   // the output slot of every sam
 // output are also added into a.gap_sums (the exit head's pooling); SC: the residual is a 1x1 convolution of the block's input
 // (64 -> 256 channels, the shortcut of a group's first block), computed here from the staged pixels and requantised as that layer
 // would have written it (a third buffer keeps a tile's pixels until its last layer has run)
+constexpr unsigned BN_NOWHERE = 0xffffff00u;       // bytes of the output a store reaches; offsets from there on are dropped
+
 template <int K1, bool RES, bool GAP, bool SC>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void bneck_block_i8_kernel(IrArgs a, BnTile t)
 {
@@ -72,10 +74,13 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const IrClamp cl1 = ir_clamp(a.sh_e, a.lo_e, a.hi_e), cl2 = ir_clamp(a.sh_d, a.lo_d, a.hi_d), cl3 = ir_clamp(a.sh_p, a.lo_p, a.hi_p);
     const bool relu1 = ir_relu(a.sh_e, a.lo_e, a.hi_e), relu2 = ir_relu(a.sh_d, a.lo_d, a.hi_d), relu3 = ir_relu(a.sh_p, a.lo_p, a.hi_p);
 
-    if (tid < 64) { l_b1[tid] = a.be[tid]; l_b2[tid] = a.bd[tid]; }
-    if (tid < 256) l_b3[tid] = a.bp[tid];
-    if constexpr (SC) { if (tid < 256) l_bs[tid] = a.bs[tid]; }
-    if (a.ys && tid < a.B) ((unsigned short*)l_slot)[tid] = a.ys[tid];   // B <= EE_ZC_MAX_B <= 512 with a slot table: checked by the launcher
+    // Requested by every lane, in range, and written to LDS behind the requests for weights and pixels: behind a condition each was waited for before the next was asked for.
+    const int in_b1 = a.be[tid & 63], in_b2 = a.bd[tid & 63], in_b3 = a.bp[tid & 255];
+    int in_bs = 0;
+    if constexpr (SC) in_bs = a.bs[tid & 255];
+    unsigned short in_slot = 0;
+    if (a.ys) in_slot = a.ys[min(tid, a.B - 1)];                        // B <= EE_ZC_MAX_B <= 512 with a slot table: checked by the launcher
+    __builtin_amdgcn_sched_barrier(0);
     // pooling (GAP): a tile's channel sums are gathered in LDS, a row of 256 per tile of this workgroup, and added to a.gap_sums
     // when the last tile is through: the global atomics then sit behind the loop, where no wait of the loop (for staged pixels
     // or residuals) has them in front of it
@@ -131,7 +136,15 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         xb_l1 = xb_l1 + 1 == NXB ? 0 : xb_l1 + 1;
         xb_st = xb_st + 1 == NXB ? 0 : xb_st + 1;
     };
-    unsigned pix_y = 0;
+    // Every wavefront issues its two stores, those of pixels outside the image out of the buffer's range: behind stores that a condition may skip the compiler cannot count, and the pixels staged at the
+    // top of the next iteration waited for the stores as well.
+    const auto y_buf = __builtin_amdgcn_make_buffer_rsrc(a.y, (short)0, BN_NOWHERE, 0x00020000);
+    unsigned pix_y = BN_NOWHERE;
+    auto store_pair = [&](const v4i_r& o0, const v4i_r& o1) {
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o0), y_buf, (int)pix_y, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o1), y_buf, (int)pix_y + 32, 0, 0);
+    };
     bool px_ok = false;
     int gap_n = 0, gap_row = -1;                                        // the sample of the tile in hand, its row of sums
 #pragma unroll
@@ -146,7 +159,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         px_ok = oy < a.H && ox < a.W;
         const int sp = px_ok ? (oy * a.W + ox) * 256 + cb0 * 32 + 16 * hi : 0;                  // < 2^31 with the sample: checked by the launcher
         const int slot_n = a.ys ? (int)l_slot[n] : n;                   // from LDS: a global load here would sit in front of every later wait
-        pix_y = (unsigned)(slot_n * a.H * a.W * 256 + sp);
+        pix_y = px_ok ? (unsigned)(slot_n * a.H * a.W * 256 + sp) : BN_NOWHERE;
         if constexpr (RES && !SC) {
             const unsigned char* rp = (const unsigned char*)a.res + (unsigned)(n * a.H * a.W * 256 + sp);
             rr[0] = *(const v4i_r*)rp;                                  // unconditional and in range
@@ -181,10 +194,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             }
             out[c] = ir_requant_pack<!RES>(acc, cl3, relu3);
         }
-        if (px_ok) {
-            *(v4i_r*)((unsigned char*)a.y + pix_y) = out[0];
-            *(v4i_r*)((unsigned char*)a.y + pix_y + 32) = out[1];
-        }
+        store_pair(out[0], out[1]);
         if constexpr (GAP) {
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
@@ -207,27 +217,22 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
     // ---- this lane's chunks of a staged tile: offsets from the tile's first pixel, -------------------------------------
     v4i_r st[NL];                                                   // the loaded chunks
-    int lrel[NL], lpyx[NL];                                         // global byte offset from the tile's pixel (0, 0); staged row | column << 8
+    int lrel[NL];                                                   // global byte offset from the tile's pixel (0, 0)
     unsigned ldst[NL];                                              // LDS byte offset of the chunk, ~0u: none
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
         const int e0 = 512 * i + tid, e = min(e0, NCH - 1), q = e / CPP, ch = e - q * CPP, py = q / 10, px = q - 10 * py;
         lrel[i] = ((py - 1) * a.W + (px - 1)) * CIN + 16 * ch;
-        lpyx[i] = py | px << 8;
         ldst[i] = e0 < NCH ? (unsigned)(q * t.xp + 16 * ch) : ~0u;
     }
-    auto x_load = [&](const Cursor& cu) {                           // unconditional and in range: a pixel outside the image reads the image's first one
-        const int n = cu.n, oy0 = 8 * cu.ty, ox0 = 8 * cu.tx;
-        const unsigned char* x = (const unsigned char*)a.x + (size_t)n * a.H * a.W * CIN;
-        const int base = (oy0 * a.W + ox0) * CIN;
-        // staged rows y_first .. y_last and columns x_first .. x_last lie inside the image
-        const int y_first = oy0 == 0 ? 1 : 0, y_last = min(9, a.H - oy0), x_first = ox0 == 0 ? 1 : 0, x_last = min(9, a.W - ox0);
+    // Through a buffer, whose loads out of range give zeros: a pixel outside the image reads some pixel of the tensor or zeros, and nothing of it is used; no lane computes whether it is inside.  A tile
+    // past the last one (live: false) is requested too, out of range: with the requests skipped the compiler, which counts what is in flight on every path, waited for the next tile's pixels where only
+    // the residual in front of them is needed.  64 samples, 256 -> 64 -> 256 at 56x56, with the stores that can be counted (y_buf): 34.9 -> 31.8 us.
+    const auto x_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.x), (short)0, a.B * a.H * a.W * CIN, 0x00020000);
+    auto x_load = [&](const Cursor& cu, bool live) {
+        const int base = live ? ((cu.n * a.H + 8 * cu.ty) * a.W + 8 * cu.tx) * CIN : (int)0x80000000u;
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int py = lpyx[i] & 255, px = lpyx[i] >> 8;
-            const bool ok = (unsigned)(py - y_first) <= (unsigned)(y_last - y_first) && (unsigned)(px - x_first) <= (unsigned)(x_last - x_first);
-            st[i] = *(const v4i_r*)(x + (ok ? (unsigned)(base + lrel[i]) : 0u));
-        }
+        for (int i = 0; i < NL; ++i) st[i] = __builtin_bit_cast(v4i_r, __builtin_amdgcn_raw_buffer_load_b128(x_buf, base + lrel[i], 0, 0));
     };
     auto x_store = [&](unsigned char* xb) {
 #pragma unroll
@@ -246,8 +251,13 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         for (int k = 0; k < 18; ++k) wr[k] = *(const v4i_r*)((const unsigned char*)a.wd + ((size_t)(half * 18 + k) * 64 + lane) * 16);
     }
     Cursor c_ld = first;                                                // the tile whose pixels are requested next
-    x_load(c_ld);
+    x_load(c_ld, true);
     advance(c_ld);
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < 64) { l_b1[tid] = in_b1; l_b2[tid] = in_b2; }
+    if (tid < 256) l_b3[tid] = in_b3;
+    if constexpr (SC) { if (tid < 256) l_bs[tid] = in_bs; }
+    if (a.ys && tid < a.B) ((unsigned short*)l_slot)[tid] = in_slot;
     x_store(l_x);
     // every weight has arrived before the loops, so that nothing inside them waits for a weight by count
 #pragma unroll
@@ -259,7 +269,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
         for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(wsc[k >> 1][k & 1]));
     }
-    if (1 < T) x_load(c_ld);                                            // in flight over the first iteration
+    x_load(c_ld, 1 < T);                                                // in flight over the first iteration
     advance(c_ld);
     // per iteration: tile it + 2, requested one iteration ago, goes into the buffer the first layer read one iteration ago
     // (tile it's); then the next request, in flight over a whole iteration
@@ -271,7 +281,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
     auto stage_request = [&](int it) {
         __builtin_amdgcn_sched_barrier(0);
-        if (it + 3 < T) x_load(c_ld);
+        x_load(c_ld, it + 3 < T);
         advance(c_ld);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -286,7 +296,8 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         for (int it = -1; it < T; ++it) {
             stage_write(it);
             if (it >= 0) { out_pixel(c_out); advance(c_out); }
-            if (it + 1 < T) {
+            if (it + 1 == T) stage_request(it);                         // out of range; behind the matrix instructions below in every other iteration
+            else {
                 const int oy0 = 8 * c_l1.ty, ox0 = 8 * c_l1.tx;
                 advance(c_l1);
                 const bool in_img = hp < 100 && (unsigned)(oy0 - 1 + hy) < (unsigned)a.H && (unsigned)(ox0 - 1 + hx) < (unsigned)a.W;
@@ -322,7 +333,10 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         for (int it = -1; it < T; ++it) {
             stage_write(it);
             v4i_r dq = v4i_r{0, 0, 0, 0};
-            if (it < 0) stage_request(it);
+            if (it < 0) {
+                stage_request(it);
+                store_pair(dq, dq);                                     // nowhere yet: as many in flight as in every other iteration
+            }
             if (it >= 0) {
             out_pixel(c_out);
             advance(c_out);
