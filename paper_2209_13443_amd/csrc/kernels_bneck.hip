@@ -7,17 +7,21 @@
 // One workgroup of eight wavefronts per CU walks over tiles of 8 x 8 output pixels (persistent: the weights of all three
 // layers, 68 KB, are loaded once per wavefront and stay in registers as ready matrix-instruction operands).  The wavefronts
 // have two roles, and every SIMD holds one of each, so that the matrix cores of a SIMD see the sum of both.  Per tile there
-// are two halves with a workgroup barrier behind each:
+// are two halves with a workgroup barrier between them:
 //   first half   front (wavefronts 0-3), one tile ahead: the 10 x 10 input pixels under tile i + 1 (staged in LDS one
 //                iteration before) go through the first layer, 32 pixels per wavefront, both blocks of 32 output channels
 //                per staged operand; results are requantised and written to LDS as the second layer's input (pixels outside
-//                the image as zeros: the second layer pads its input).  Before that the wavefront writes the pixels of tile
-//                i + 2, which it requested one iteration ago, to LDS and requests those of tile i + 3.
+//                the image as zeros: the second layer pads its input).
 //                back (wavefronts 4-7), on tile i: (pixel block of 8 x 4, half of the 64 middle channels) per wavefront: nine
 //                taps x two reduction steps of the 3x3 layer, requantisation, the result to LDS;
+//                both, behind their matrix instructions: the residual of tile i is requested, the pixels of tile i + 2, requested one iteration ago, go to LDS, those of tile i + 3 are requested;
 //   second half  all eight wavefronts: the last layer of tile i, (pixel block, two of the eight blocks of 32 output channels)
 //                each: bias, residual (requested in the first half), requantisation, 16-byte stores.
 // All sums are int32 and exact, rounding points are those of the three separate layers: results are equal bit for bit.
+// What bounds it, in cycles of the 64-sample launch (256 -> 64 -> 256): 5,000 to the first tile (the weights' way through the vector memory path), 3,700 a tile, of which a SIMD's matrix instructions are 1,470 and its
+// vector instructions 1,140; 12 tiles for three workgroups of four, 13 for the fourth.  With a second barrier behind the tile, staging and requests at the top of it, and every weight waited for in front of the first
+// tile it was 6,700 and 4,240.  64 samples, us, this and the other blocks of the group (with the shortcut, plain, pooling): 37.3 -> 34.3, 34.7 -> 30.7, 35.4 -> 31.6; one sample 7.7 -> 6.3, 6.2 -> 5.6, of which 4 are an
+// empty launch by the same clock.
 #include "ee_internal.hpp"
 #include "ir_device.hpp"
 
@@ -41,7 +45,7 @@ constexpr int BN_SLOT_BYTES = 2 * EE_ZC_MAX_B;   // the output slot of every sam
 // K1: reduction steps of the first layer, c_in / 32; RES: the last layer adds a residual; GAP: the per-sample channel sums of the
 // output are also added into a.gap_sums (the exit head's pooling); SC: the residual is a 1x1 convolution of the block's input
 // (64 -> 256 channels, the shortcut of a group's first block), computed here from the staged pixels and requantised as that layer
-// would have written it (a third buffer keeps a tile's pixels until its last layer has run)
+// would have written it (two more buffers keep a tile's pixels until its last layer has run in every wavefront)
 constexpr unsigned BN_NOWHERE = 0xffffff00u;       // bytes of the output a store reaches; offsets from there on are dropped
 
 template <int K1, bool RES, bool GAP, bool SC>
@@ -50,7 +54,8 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     request_args<sizeof(IrArgs) + sizeof(BnTile)>();
     constexpr int CIN = 32 * K1, CPP = 2 * K1;                         // 16-byte chunks per input pixel
     constexpr int NCH = 100 * CPP, NL = (NCH + 511) / 512;             // chunks per tile, loads per lane (all eight wavefronts stage)
-    constexpr int NXB = SC ? 3 : 2;                                    // buffers of staged pixels
+    constexpr int NXB = SC ? 4 : 2;                                    // buffers of staged pixels
+    static_assert(NL <= 6 && NL <= K1, "a chunk behind a matrix instruction");
     static_assert(!SC || (K1 == 2 && RES), "the shortcut convolution reads 64 channels and is the residual");
     extern __shared__ __attribute__((aligned(16))) unsigned char bn_lds[];
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hi = lane >> 5;
@@ -65,11 +70,11 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     int* const l_b1 = (int*)bn_lds;
     int* const l_b2 = l_b1 + 64;
     int* const l_b3 = l_b1 + 128;
-    unsigned char* const l_x = bn_lds + BN_BIAS_BYTES;                  // two buffers of staged input pixels
+    unsigned char* const l_x = bn_lds + BN_BIAS_BYTES;                  // buffers of staged input pixels
     unsigned char* const l_m1 = l_x + NXB * t.x_bytes;                  // two buffers of second-layer input
     unsigned char* const l_m2 = l_m1 + 2 * BN_M1_BYTES;
-    const unsigned short* const l_slot = (const unsigned short*)(l_m2 + BN_M2_BYTES);
-    int* const l_bs = (int*)(l_m2 + BN_M2_BYTES + BN_SLOT_BYTES);       // shortcut bias (SC)
+    const unsigned short* const l_slot = (const unsigned short*)(l_m2 + 2 * BN_M2_BYTES);
+    int* const l_bs = (int*)(l_m2 + 2 * BN_M2_BYTES + BN_SLOT_BYTES);       // shortcut bias (SC)
     const IrClamp cl_s = ir_clamp(a.sh_s, a.lo_s, a.hi_s);
     const IrClamp cl1 = ir_clamp(a.sh_e, a.lo_e, a.hi_e), cl2 = ir_clamp(a.sh_d, a.lo_d, a.hi_d), cl3 = ir_clamp(a.sh_p, a.lo_p, a.hi_p);
     const bool relu1 = ir_relu(a.sh_e, a.lo_e, a.hi_e), relu2 = ir_relu(a.sh_d, a.lo_d, a.hi_d), relu3 = ir_relu(a.sh_p, a.lo_p, a.hi_p);
@@ -123,12 +128,6 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int ty = m >> 3, tx = m & 7;
     v4i_r w3[2][2], rr[2];                                              // operands [block][step]; the residual of the lane's pixel, 16 channels per block
     v4i_r wsc[SC ? 2 : 1][2];                                           // the shortcut's operands [block][step]
-    if constexpr (SC) {
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) wsc[c][k] = *(const v4i_r*)((const unsigned char*)a.ws + ((size_t)((cb0 + c) * 2 + k) * 64 + lane) * 16);
-    }
     const int xc_off = ((4 * pb + ty + 1) * 10 + tx + 1) * t.xp + 16 * hi;   // the lane's output pixel among the staged ones
     int xb_out = NXB - 1, xb_l1 = 0, xb_st = 1;                         // buffers of tile it, it + 1, it + 2 (it = -1 at first)
     auto next_buffers = [&] {
@@ -147,10 +146,6 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
     bool px_ok = false;
     int gap_n = 0, gap_row = -1;                                        // the sample of the tile in hand, its row of sums
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) w3[c][k] = *(const v4i_r*)((const unsigned char*)a.wp + ((size_t)((cb0 + c) * 2 + k) * 64 + lane) * 16);
     auto out_pixel = [&](const Cursor& cu) {                            // where the lane's pixel of that tile goes; its residual is requested
         const int n = cu.n;
         gap_n = n;
@@ -227,56 +222,55 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     // Through a buffer, whose loads out of range give zeros: a pixel outside the image reads some pixel of the tensor or zeros, and nothing of it is used; no lane computes whether it is inside.  A tile
     // past the last one (live: false) is requested too, out of range: with the requests skipped the compiler, which counts what is in flight on every path, waited for the next tile's pixels where only
-    // the residual in front of them is needed.  64 samples, 256 -> 64 -> 256 at 56x56, with the stores that can be counted (y_buf): 34.9 -> 31.8 us.
+    // the residual in front of them is needed.  64 samples, 256 -> 64 -> 256 at 56x56, with the stores that can be counted (y_buf): 34.9 -> 31.8 us alone.
     const auto x_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.x), (short)0, a.B * a.H * a.W * CIN, 0x00020000);
     auto x_load = [&](const Cursor& cu, bool live) {
         const int base = live ? ((cu.n * a.H + 8 * cu.ty) * a.W + 8 * cu.tx) * CIN : (int)0x80000000u;
 #pragma unroll
         for (int i = 0; i < NL; ++i) st[i] = __builtin_bit_cast(v4i_r, __builtin_amdgcn_raw_buffer_load_b128(x_buf, base + lrel[i], 0, 0));
     };
-    auto x_store = [&](unsigned char* xb) {
+    // ---- prologue: the role's weights (front: the first layer's operands [block][step]; back: [tap][step] of the 3x3 layer for this half's 32 middle channels), the last layer's.  213 KB for the eight
+    // wavefronts take 4,800 cycles through the CU's vector memory path; the first tile waits only for the pixels and the front's, requested first.  The back needs its own an iteration later.
+    // Every weight has arrived before a role's loop, so that nothing inside it waits for a weight by count. ---------
+    auto load_weights = [&](auto& wr, const void* w, int first_op) {
+#pragma unroll
+        for (int k = 0; k < (int)(sizeof(wr) / sizeof(wr[0])); ++k) wr[k] = *(const v4i_r*)((const unsigned char*)w + ((size_t)(first_op + k) * 64 + lane) * 16);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                w3[c][k] = *(const v4i_r*)((const unsigned char*)a.wp + ((size_t)((cb0 + c) * 2 + k) * 64 + lane) * 16);
+                if constexpr (SC) wsc[c][k] = *(const v4i_r*)((const unsigned char*)a.ws + ((size_t)((cb0 + c) * 2 + k) * 64 + lane) * 16);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto have_weights = [&](auto& wr) {
+#pragma unroll
+        for (int k = 0; k < (int)(sizeof(wr) / sizeof(wr[0])); ++k) asm volatile("" : "+v"(wr[k]));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            asm volatile("" : "+v"(w3[k >> 1][k & 1]));
+            if constexpr (SC) { v4i_r& w = wsc[k >> 1][k & 1]; asm volatile("" : "+v"(w)); }
+        }
+    };
+    Cursor c_ld = first;                                                // the tile whose pixels are requested next
+    auto first_tile = [&] {                                             // biases and the first tile's pixels to LDS
+        if (tid < 64) { l_b1[tid] = in_b1; l_b2[tid] = in_b2; }
+        if (tid < 256) l_b3[tid] = in_b3;
+        if constexpr (SC) { if (tid < 256) l_bs[tid] = in_bs; }
+        if (a.ys && tid < a.B) ((unsigned short*)l_slot)[tid] = in_slot;
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            if (512 * (i + 1) <= NCH || ldst[i] != ~0u) *(v4i_r*)(xb + ldst[i]) = st[i];     // only the last chunk may be missing
+            if (512 * (i + 1) <= NCH || ldst[i] != ~0u) *(v4i_r*)(l_x + ldst[i]) = st[i];     // only the last chunk may be missing
     };
-    // ---- prologue: the role's weights (front: the first layer's operands [block][step]; back: [tap][step] of the 3x3 layer for
-    //      this half's 32 middle channels), requested in front of the first tile's pixels so that one wait covers both ---------
-    constexpr int NWR = 2 * K1 > 18 ? 2 * K1 : 18;
-    v4i_r wr[NWR];
-    if (front) {
-#pragma unroll
-        for (int k = 0; k < 2 * K1; ++k) wr[k] = *(const v4i_r*)((const unsigned char*)a.we + ((size_t)k * 64 + lane) * 16);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 18; ++k) wr[k] = *(const v4i_r*)((const unsigned char*)a.wd + ((size_t)(half * 18 + k) * 64 + lane) * 16);
-    }
-    Cursor c_ld = first;                                                // the tile whose pixels are requested next
     x_load(c_ld, true);
     advance(c_ld);
     __builtin_amdgcn_sched_barrier(0);
-    if (tid < 64) { l_b1[tid] = in_b1; l_b2[tid] = in_b2; }
-    if (tid < 256) l_b3[tid] = in_b3;
-    if constexpr (SC) { if (tid < 256) l_bs[tid] = in_bs; }
-    if (a.ys && tid < a.B) ((unsigned short*)l_slot)[tid] = in_slot;
-    x_store(l_x);
-    // every weight has arrived before the loops, so that nothing inside them waits for a weight by count
-#pragma unroll
-    for (int k = 0; k < NWR; ++k)
-        if (k < 18 || front) asm volatile("" : "+v"(wr[k]));
-#pragma unroll
-    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(w3[k >> 1][k & 1]));
-    if constexpr (SC) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(wsc[k >> 1][k & 1]));
-    }
-    x_load(c_ld, 1 < T);                                                // in flight over the first iteration
-    advance(c_ld);
-    // per iteration: tile it + 2, requested one iteration ago, goes into the buffer the first layer read one iteration ago
-    // (tile it's); then the next request, in flight over a whole iteration
-    // (the requests go out behind the wavefront's matrix instructions of the first half, whose results take a while anyway:
-    // at the top of the half all eight wavefronts would queue up at the memory pipeline with nothing else to issue)
-    auto stage_write = [&](int it) {
-        if (it + 2 < T) x_store(l_x + xb_st * t.x_bytes);
+    // Per iteration: tile it + 2, requested one iteration ago, goes into the buffer the first layer read one iteration ago, a chunk behind every other matrix instruction of the first half, which the
+    // wavefront would otherwise wait out; then the next request, in flight over a whole iteration.  (At the top of the half all eight wavefronts would queue up at LDS and at the memory pipeline with the
+    // matrix cores idle.)
+    auto stage_write = [&](int it, int i) {
+        if (it + 2 < T && (512 * (i + 1) <= NCH || ldst[i] != ~0u)) *(v4i_r*)(l_x + xb_st * t.x_bytes + ldst[i]) = st[i];     // only the last chunk may be missing
         __builtin_amdgcn_sched_barrier(0);
     };
     auto stage_request = [&](int it) {
@@ -287,17 +281,24 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
 
     // Each role has its own loop (a wavefront has one role for good, and the registers that live over a loop are the role's
-    // own); both loops run the same iterations with the same two barriers, so the workgroup's barriers pair up.
+    // own); both loops run the same iterations with the same barrier, so the workgroup's barriers pair up.  One barrier an iteration, between its halves: what a wavefront that runs ahead writes in the
+    // next iteration's first half, nobody reads in this one's second (two buffers of second-layer output; the pixels under a tile that the shortcut still reads lie in a buffer of their own).
     if (front) {
         const int hp = 32 * wave + m, hpc = min(hp, 99), hy = hpc / 10, hx = hpc - 10 * hy;
         const int xoff = hpc * t.xp + 16 * hi, m1off = hy * BN_M1_ROW + hx * BN_M1_PX + 16 * hi;
         Cursor c_out = first, c_l1 = first;                             // the tiles of the last layer, of the first layer
+        v4i_r wr[2 * K1];
+        load_weights(wr, a.we, 0);
+        first_tile();
+        have_weights(wr);
+        x_load(c_ld, 1 < T);                                            // in flight over the first iteration
+        advance(c_ld);
         __syncthreads();                                                // biases and the first tile's pixels are in LDS
         for (int it = -1; it < T; ++it) {
-            stage_write(it);
-            if (it >= 0) { out_pixel(c_out); advance(c_out); }
-            if (it + 1 == T) stage_request(it);                         // out of range; behind the matrix instructions below in every other iteration
-            else {
+            if (it + 1 == T) {                                          // requests out of range; behind the matrix instructions below in every other iteration
+                out_pixel(c_out);
+                stage_request(it);
+            } else {
                 const int oy0 = 8 * c_l1.ty, ox0 = 8 * c_l1.tx;
                 advance(c_l1);
                 const bool in_img = hp < 100 && (unsigned)(oy0 - 1 + hy) < (unsigned)a.H && (unsigned)(ox0 - 1 + hx) < (unsigned)a.W;
@@ -308,10 +309,13 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
                 for (int k = 0; k < K1; ++k) b[k] = *(const v4i_r*)(xb + 32 * k);
                 __builtin_amdgcn_sched_barrier(0);
+                if (it >= 0) { out_pixel(c_out); advance(c_out); }
 #pragma unroll
                 for (int k = 0; k < K1; ++k) {
                     acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[k], b[k], acc0, 0, 0, 0);
                     acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[K1 + k], b[k], acc1, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (k < NL) stage_write(it, k);
                 }
                 stage_request(it);
                 v4i_r o0 = ir_requant_pack(acc0, cl1, relu1), o1 = ir_requant_pack(acc1, cl1, relu1);
@@ -321,25 +325,30 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                     *(v4i_r*)(m1 + 32) = o1;
                 }
             }
-            __syncthreads();                                            // the halves of the second layer's output are in LDS
-            if (it >= 0) last_layer(*(const v4i_r*)(l_m2 + ((pb * 2 + 0) * 64 + lane) * 16), *(const v4i_r*)(l_m2 + ((pb * 2 + 1) * 64 + lane) * 16));
+            __syncthreads();                                            // the halves of the second layer's output are in LDS; tile it + 1 is through the first layer, tile it + 2 is staged
+            const unsigned char* const m2 = l_m2 + (it & 1) * BN_M2_BYTES;
+            if (it >= 0) last_layer(*(const v4i_r*)(m2 + ((pb * 2 + 0) * 64 + lane) * 16), *(const v4i_r*)(m2 + ((pb * 2 + 1) * 64 + lane) * 16));
+            else store_pair(v4i_r{0, 0, 0, 0}, v4i_r{0, 0, 0, 0});      // nowhere yet: as many in flight as in every other iteration
             next_buffers();
-            __syncthreads();                                            // tile it + 1 is through the first layer, tile it + 2 is staged
         }
     } else {
         const int woff = (pb * 4 + ty) * BN_M1_ROW + tx * BN_M1_PX + 16 * hi;
+        first_tile();
+        x_load(c_ld, 1 < T);
+        advance(c_ld);
         __syncthreads();                                                // biases and the first tile's pixels are in LDS
         Cursor c_out = first;
-        for (int it = -1; it < T; ++it) {
-            stage_write(it);
-            v4i_r dq = v4i_r{0, 0, 0, 0};
-            if (it < 0) {
-                stage_request(it);
-                store_pair(dq, dq);                                     // nowhere yet: as many in flight as in every other iteration
-            }
-            if (it >= 0) {
-            out_pixel(c_out);
-            advance(c_out);
+        v4i_r wr[18];
+        load_weights(wr, a.wd, half * 18);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) stage_write(-1, i);
+        stage_request(-1);
+        store_pair(v4i_r{0, 0, 0, 0}, v4i_r{0, 0, 0, 0});               // as above
+        __syncthreads();                                                // the first tile is through the first layer, the second one is staged
+        next_buffers();
+        have_weights(wr);
+        for (int it = 0; it < T; ++it) {
+            unsigned char* const m2 = l_m2 + (it & 1) * BN_M2_BYTES;
             v16i_r acc = bias16(l_b2, half);
             const unsigned char* win = l_m1 + (it & 1) * BN_M1_BYTES + woff;
             // the eighteen operands in three batches of six through two sets of registers: the third batch is requested when the
@@ -351,30 +360,36 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
             for (int k = 0; k < 6; ++k) b1[k] = tap(6 + k);
             __builtin_amdgcn_sched_barrier(0);
+            out_pixel(c_out);
+            advance(c_out);
 #pragma unroll
-            for (int k = 0; k < 6; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[k], b0[k], acc, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int k = 0; k < 6; ++k) {
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[k], b0[k], acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (k % 2 == 1 && k / 2 < NL) stage_write(it, k / 2);
+            }
 #pragma unroll
             for (int k = 0; k < 6; ++k) b0[k] = tap(12 + k);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int k = 0; k < 6; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[6 + k], b1[k], acc, 0, 0, 0);
+            for (int k = 0; k < 6; ++k) {
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[6 + k], b1[k], acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (k % 2 == 1 && 3 + k / 2 < NL) stage_write(it, 3 + k / 2);
+            }
 #pragma unroll
             for (int k = 0; k < 6; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wr[12 + k], b0[k], acc, 0, 0, 0);
             stage_request(it);
-            dq = ir_requant_pack(acc, cl2, relu2);
-            *(v4i_r*)(l_m2 + ((pb * 2 + half) * 64 + lane) * 16) = dq;
-            }
-            __syncthreads();                                            // the halves of the second layer's output are in LDS
-            if (it >= 0) {
-                const v4i_r other = *(const v4i_r*)(l_m2 + ((pb * 2 + (half ^ 1)) * 64 + lane) * 16);
-                last_layer(half ? other : dq, half ? dq : other);
-            }
+            const v4i_r dq = ir_requant_pack(acc, cl2, relu2);
+            *(v4i_r*)(m2 + ((pb * 2 + half) * 64 + lane) * 16) = dq;
+            __syncthreads();                                            // as above
+            const v4i_r other = *(const v4i_r*)(m2 + ((pb * 2 + (half ^ 1)) * 64 + lane) * 16);
+            last_layer(half ? other : dq, half ? dq : other);
             next_buffers();
-            __syncthreads();
         }
     }
-    if constexpr (GAP) {                                                // every row is complete behind the loop's last barrier
+    if constexpr (GAP) {
+        __syncthreads();                                                // every row is complete
         for (int i = tid; i < 256 * T; i += 512) atomicAdd(a.gap_sums + (size_t)l_gap_n[i >> 8] * 256 + (i & 255), l_gap[i]);
     }
 }
@@ -401,7 +416,7 @@ static bool bneck_block_plan(const IrArgs& a, BnTile& t)
 // LDS of a launch; 0: the rows of channel sums of a pooling launch do not fit
 static size_t bneck_lds_bytes(const BnTile& t, bool sc, bool gap)
 {
-    size_t lds = (size_t)BN_BIAS_BYTES + (sc ? 3 : 2) * (size_t)t.x_bytes + 2 * BN_M1_BYTES + BN_M2_BYTES + BN_SLOT_BYTES + (sc ? 1024 : 0);
+    size_t lds = (size_t)BN_BIAS_BYTES + (sc ? 4 : 2) * (size_t)t.x_bytes + 2 * BN_M1_BYTES + 2 * BN_M2_BYTES + BN_SLOT_BYTES + (sc ? 1024 : 0);
     if (gap) lds += (size_t)t.gap_rows * (1024 + 4);
     return lds <= 160 * 1024 ? lds : 0;
 }
