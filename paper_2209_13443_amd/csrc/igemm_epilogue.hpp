@@ -29,17 +29,19 @@ struct OutTile {
     static __device__ __forceinline__ int oswz(int r) { return (r / OR256) & (CR - 1); }
 };
 
-// Copies the bias of the tile's channels (256 entries from the first one) and, for a layer with a residual whose pixels
-// are whole 16-byte chunks, the residual tile into LDS.  Asynchronous: the copies are counted by vmcnt like the
-// operand copies issued behind them and are complete when the first of those is.  NT: lanes of the workgroup.
+// Copies the bias of the tile's channels (256 entries from the first one) into LDS.  Asynchronous, as the residual below: counted by vmcnt like the
+// operand copies and complete when the first copy issued behind it is.
+__device__ __forceinline__ void igemm_stage_bias(const ConvArgs& a, unsigned lds0, unsigned bias_off, int n0, int wave, int lane)
+{
+    if (wave == 0) dma16(lds0 + bias_off, (const unsigned char*)a.bias + (size_t)n0 * 4 + lane * 16);
+}
+// The residual tile of a layer whose pixels are whole 16-byte chunks.  NT: lanes of the workgroup.
 template <int ES, int BM, int BN, int NT>
-__device__ __forceinline__ void igemm_stage_bias_res(const ConvArgs& a, unsigned lds0, unsigned ro_off, unsigned bias_off, int m0, int n0,
-                                                     int tid, int wave, int lane, bool res_tile)
+__device__ __forceinline__ void igemm_stage_res(const ConvArgs& a, unsigned lds0, unsigned ro_off, int m0, int n0, int tid, int wave, bool res_tile)
 {
     using T = OutTile<ES, BN>;
     constexpr int CR = T::CR, NO = (BM * CR + NT - 1) / NT;
     const unsigned char* zp = (const unsigned char*)a.zeros;
-    if (wave == 0) dma16(lds0 + bias_off, (const unsigned char*)a.bias + (size_t)n0 * 4 + lane * 16);
     if (res_tile) {
 #pragma unroll
         for (int j = 0; j < NO; ++j) {

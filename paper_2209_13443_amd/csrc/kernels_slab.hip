@@ -76,7 +76,8 @@ __global__ __launch_bounds__(256, 2) void conv_slab_kernel(ConvArgs a, int gm, i
     const unsigned ro_off = has_res && wide ? region0 : 0;
     const unsigned bias_off = has_res && wide ? region0 + TILE_O : region0;
 
-    igemm_stage_bias_res<ES, BM, BN, NT>(a, lds0, ro_off, bias_off, m0, n0, tid, wave, lane, has_res && wide);
+    igemm_stage_bias(a, lds0, bias_off, n0, wave, lane);
+    igemm_stage_res<ES, BM, BN, NT>(a, lds0, ro_off, m0, n0, tid, wave, has_res && wide);
 
     // ---- the slab: input rows m0 - halo_lo .. m0 + BM + halo_hi - 1, clamped into the tensor (a clamped row is only
     // ever the source of taps that the validity mask rejects).  Chunk c of slab row r sits at c ^ sswz(r).
