@@ -31,7 +31,7 @@ HBM_PEAK = 8000.0                               # GB/s
 CONV_SOURCES = ("kernels_igemm.hip", "kernels_skinny.hip", "kernels_group.hip", "kernels_slab.hip", "kernels_rows.hip", "kernels_taps.hip", "kernels_pair.hip", "kernels_bneck.hip", "kernels_bneck16.hip",
                 "kernels_ir.hip", "kernels_segment.hip", "kernels_seam.hip", "head_device.hpp",
                 "igemm_kernel.hpp", "skinny_kernel.hpp", "igemm_device.hpp", "igemm_epilogue.hpp", "ir_device.hpp")
-CONV_KERNELS = "conv_igemm_kernel, conv_skinny_kernel, conv_group_kernel, conv_group_skinny_kernel, conv_slab_kernel, conv_rows_kernel, conv_taps_kernel, conv_pair_kernel, bneck_block_i8_kernel, bneck_block_bf16_kernel, ir_block_i8_kernel, segment_small_i8_kernel, conv_seam_kernel"
+CONV_KERNELS = "conv_igemm_kernel, conv_skinny_kernel, conv_skinny_taps_kernel, conv_group_kernel, conv_group_skinny_kernel, conv_group_skinny_taps_kernel, conv_slab_kernel, conv_rows_kernel, conv_taps_kernel, conv_pair_kernel, bneck_block_i8_kernel, bneck_block_bf16_kernel, ir_block_i8_kernel, segment_small_i8_kernel, conv_seam_kernel"
 
 
 def conv_sources_digest():

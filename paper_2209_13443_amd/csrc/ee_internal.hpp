@@ -74,6 +74,7 @@ struct ConvArgs {
     int Kp;              // weight row pitch in elements (reduction length, zero padded)
     unsigned magic_howo, magic_wo;   // floor(2^32 / (Ho*Wo)), floor(2^32 / Wo): division by multiply-high
     unsigned tap_rows;   // bit r*kw set for every kernel row r (kh*kw <= 31)
+    unsigned magic_spt, magic_kw;    // set by the launchers of the few-pixel kernel: floor(2^32 / steps of a tap), floor(2^32 / kw)
     int plain_step;      // set by the launcher: bytes the source of a row advances per reduction step when no tap needs a check
     int mode;            // 0: Ci % 16 == 0 loader with bounds checks; 1: 4-channel zero-padded input
     int Hp, Wp, kwp;     // mode 1: padded input dims and padded kernel width

@@ -62,7 +62,14 @@ template <int T, int NW, int TN, bool PLAIN>
 __global__ __launch_bounds__(64 * NW, 2) void conv_group_skinny_kernel(ConvGroup g, int n)
 {
     const GroupMember m = group_member(group_pick(g, n, (int)blockIdx.x));
-    skinny_tile<1, T, NW, TN, PLAIN>(m.a, m.gn, m.magic_gn, m.nk, m.pitch, blockIdx.x - (unsigned)m.first);
+    skinny_tile<1, T, NW, TN, PLAIN ? SKINNY_PLAIN : SKINNY_ANY>(m.a, m.gn, m.magic_gn, m.nk, m.pitch, blockIdx.x - (unsigned)m.first);
+}
+
+template <int T, int NW, int TN>
+__global__ __launch_bounds__(64 * NW, 2) void conv_group_skinny_taps_kernel(ConvGroup g, int n)
+{
+    const GroupMember m = group_member(group_pick(g, n, (int)blockIdx.x));
+    skinny_tile<1, T, NW, TN, SKINNY_TAPS>(m.a, m.gn, m.magic_gn, m.nk, m.pitch, blockIdx.x - (unsigned)m.first);
 }
 
 // ---- launch ------------------------------------------------------------------------------------------------
@@ -107,7 +114,7 @@ static hipError_t launch_group_skinny(const ConvArgs* a, int n, hipStream_t s)
 {
     constexpr int KB = 1024 / T;
     ConvGroup g{};
-    bool plain = true;
+    bool plain = true, taps = true;                         // every member 1x1 without padding; of whole steps to a tap
     long long total = 0;
     for (int i = 0; i < n; ++i) {
         if (!a[i].wo) return hipErrorInvalidValue;
@@ -119,11 +126,14 @@ static hipError_t launch_group_skinny(const ConvArgs* a, int n, hipStream_t s)
         m.nk = (a[i].kh * a[i].kw * a[i].Ci + KB - 1) / KB;
         m.pitch = a[i].Kp / 32;
         total += (long long)m.gm * m.gn;
-        plain &= a[i].kh == 1 && a[i].kw == 1 && a[i].pad == 0 && a[i].pad_w == 0 && a[i].Ci % KB == 0;
+        const int mode = skinny_mode(m.a, 1, T);
+        plain &= mode == SKINNY_PLAIN;
+        taps &= mode != SKINNY_ANY;
     }
     if (total > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)total), block(64 * NW);
     if (plain) EE_LAUNCH((conv_group_skinny_kernel<T, NW, TN, true>), grid, block, 0, s, g, n);
+    else if (taps) EE_LAUNCH((conv_group_skinny_taps_kernel<T, NW, TN>), grid, block, 0, s, g, n);
     else EE_LAUNCH((conv_group_skinny_kernel<T, NW, TN, false>), grid, block, 0, s, g, n);
     return hipGetLastError();
 }

@@ -6,21 +6,31 @@ namespace ee {
 template <int ES, int T, int NW, int TN, bool PLAIN>
 __global__ __launch_bounds__(64 * NW, 2) void conv_skinny_kernel(ConvArgs a, int gn, unsigned magic_gn, int nk, int pitch)
 {
-    skinny_tile<ES, T, NW, TN, PLAIN>(a, gn, magic_gn, nk, pitch, blockIdx.x);
+    request_args<sizeof(ConvArgs) + 16>();
+    skinny_tile<ES, T, NW, TN, PLAIN ? SKINNY_PLAIN : SKINNY_ANY>(a, gn, magic_gn, nk, pitch, blockIdx.x);
+}
+
+template <int ES, int T, int NW, int TN>
+__global__ __launch_bounds__(64 * NW, 2) void conv_skinny_taps_kernel(ConvArgs a, int gn, unsigned magic_gn, int nk, int pitch)
+{
+    request_args<sizeof(ConvArgs) + 16>();
+    skinny_tile<ES, T, NW, TN, SKINNY_TAPS>(a, gn, magic_gn, nk, pitch, blockIdx.x);
 }
 
 // ---- launch -----------------------------------------------------------------------------------------------------------
 template <int ES, int T, int NW, int TN>
-static hipError_t launch_skinny(const ConvArgs& a, hipStream_t s)
+static hipError_t launch_skinny(const ConvArgs& layer, hipStream_t s)
 {
+    ConvArgs a = layer;
     constexpr int KB = 1024 / T;
     const int gm = (a.M + T - 1) / T, gn = (a.Co + T * TN - 1) / (T * TN);
     const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1));
     const int nk = (a.kh * a.kw * a.Ci * ES + KB - 1) / KB, pitch = a.Kp * ES / 32;      // rows are padded to 256 bytes with zeros
     if ((long long)gm * gn > 0x7fffffff) return hipErrorInvalidValue;
-    const bool plain = a.kh == 1 && a.kw == 1 && a.pad == 0 && a.pad_w == 0 && (a.Ci * ES) % KB == 0;
+    const int mode = skinny_mode(a, ES, T);
     const dim3 grid((unsigned)(gm * gn)), block(64 * NW);
-    if (plain) EE_LAUNCH((conv_skinny_kernel<ES, T, NW, TN, true>), grid, block, 0, s, a, gn, magic_gn, nk, pitch);
+    if (mode == SKINNY_PLAIN) EE_LAUNCH((conv_skinny_kernel<ES, T, NW, TN, true>), grid, block, 0, s, a, gn, magic_gn, nk, pitch);
+    else if (mode == SKINNY_TAPS) EE_LAUNCH((conv_skinny_taps_kernel<ES, T, NW, TN>), grid, block, 0, s, a, gn, magic_gn, nk, pitch);
     else EE_LAUNCH((conv_skinny_kernel<ES, T, NW, TN, false>), grid, block, 0, s, a, gn, magic_gn, nk, pitch);
     return hipGetLastError();
 }

@@ -97,6 +97,27 @@ def test_few_pixel_convolution_bit_exact(torch, ee, orc, cfg):
         ee.tune_conv_tile(old)
 
 
+@pytest.mark.parametrize("k, stride, pad", [(1, 1, 0), (1, 2, 0), (3, 1, 1), (3, 2, 1), (5, 1, 2), (3, 1, 0)])
+@pytest.mark.parametrize("c", [16, 32, 48, 64, 96, 192])
+def test_few_pixel_convolution_forms_bit_exact(torch, ee, orc, c, k, stride, pad):
+    """Its three forms: 1x1 without padding, taps of whole steps (32 bytes, or 64 in 16-pixel tiles), anything else; from one step to 75, so that a
+    wavefront has none, one group, two, an odd and an even number of them; windows over every edge of an image of 5 x 6 pixels."""
+    blob = W.single_layer_net("conv", 5, 6, c, k, stride, pad, W.DT_I8, seed=c + k, co=48)
+    x = W.input_pool(blob, 2)
+    ref = orc.stage_forward(blob, 0, x)
+    eng = ee.Engine(blob, 2)
+    for cfg in SKINNY:
+        old = ee.tune_conv_tile(cfg)
+        try:
+            say(f"[case] cfg {cfg:#x} {c} channels k{k} s{stride} p{pad}")
+            for b in (2, 1):
+                got = host(eng.stage_forward(0, dev(torch, x[:b]), ref.shape[1:]), ref[:b])
+                assert np.array_equal(got, ref[:b]), f"cfg {cfg:#x} b={b}: {np.count_nonzero(got != ref[:b])} of {got.size} differ"
+        finally:
+            ee.tune_conv_tile(old)
+    eng.close()
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_random_networks_bit_exact(torch, ee, orc, seed):
     """Generated networks (rectangular kernels, per-axis padding, strides, residuals, depthwise, pooling, concatenated
