@@ -196,7 +196,7 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_
             }
             const v4i v = *(const v4i*)(l_o + buf * Sh::O_BYTES + i * 1024 + lane * 16);
             const unsigned off = (orow * (unsigned)a.ldc + (unsigned)(a.c_off + n0)) * ES + chunk * 16;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), rsrc, r < (unsigned)a.M ? (int)off : (int)0x80000000u, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), rsrc, r < (unsigned)a.M ? (int)off : (int)0x80000000u, 0, ES == 2 ? 2 : 0);
         }
     }
 }
