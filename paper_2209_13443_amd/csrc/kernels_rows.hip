@@ -78,13 +78,6 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_
     v4i bias[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) bias[q] = *(const v4i*)((const int*)a.bias + n0 + 32 * cb + 8 * q + 4 * hi);
-    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
-#pragma unroll
-    for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(w[s]));
-#pragma unroll
-    for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(bias[q]));
-    if (a.xs || a.ys) lds_barrier();                                    // the slot tables are in LDS
-
     auto request = [&](int u, int buf) {                                // asynchronous; rows past the end read the last one
         const int m0 = u * RB;
         const unsigned xbase = lds0 + (unsigned)(buf * Sh::X_BYTES), obase = lds0 + (unsigned)(2 * Sh::X_BYTES + buf * Sh::O_BYTES);
@@ -109,6 +102,15 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_
             }
         }
     };
+    // the first tile is on its way with the weights: int8, 64 samples, 9.4 -> 8.9, 11.0 -> 10.7 and 13.9 -> 13.6 us a layer
+    __builtin_amdgcn_sched_barrier(0);
+    if (a.xs || a.ys) lds_barrier();                                    // the slot tables are in LDS
+    request(u0, 0);
+    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
+#pragma unroll
+    for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(w[s]));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(bias[q]));
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(a.y, (short)0, 0x7fffffff, 0x00020000);
     const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
     const bool relu = ir_relu(a.shift, a.lo, a.hi);
@@ -116,7 +118,6 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_
     const int swz = (m / R256) & XMASK;
     using acc_t = typename std::conditional<ES == 1, v16i, v16f>::type;
 
-    request(u0, 0);
     int buf = 0;
     for (int u = u0; u < u_end; u += g.row_slots, buf ^= 1) {
         if (u == u0) wait_all_then_barrier<0>();
@@ -196,6 +197,7 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_
             }
             const v4i v = *(const v4i*)(l_o + buf * Sh::O_BYTES + i * 1024 + lane * 16);
             const unsigned off = (orow * (unsigned)a.ldc + (unsigned)(a.c_off + n0)) * ES + chunk * 16;
+            // bf16 past the caches: 50 to 200 MB a layer displaced the weights and narrow tensors that the next layers need (all segments, 160 samples 2,174 -> 2,137 us; int8, half of that, no change)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), rsrc, r < (unsigned)a.M ? (int)off : (int)0x80000000u, 0, ES == 2 ? 2 : 0);
         }
     }
