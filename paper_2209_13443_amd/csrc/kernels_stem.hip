@@ -77,14 +77,8 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
     extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
     const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned char* wb = (const unsigned char*)a.w;
-    v4i_r wreg[NT][NKB];
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) wreg[j][kb] = *(const v4i_r*)(wb + (size_t)(32 * j + p) * a.Kp + kb * 32 + 16 * hi);
     int* const l_bias = (int*)(stem_lds + RPIX * ST_PITCH);         // 64 biases behind the tile's image (rounding constant included)
-    if (tid < 64) l_bias[tid] = ((const int*)a.bias)[tid];
+    const int in_bias = ((const int*)a.bias)[tid & 63];
     const int tpi = t.tiles_x * t.tiles_y;
     struct Tile { int n, py0, px0; };
     auto tile_at = [&](int u) {
@@ -105,8 +99,22 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
     // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
     const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
     int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3);
+    // The first strips and the weights, as ready operands (read as rows, 32 lines an instruction), are requested together, in the other two kernels likewise: 64 samples 24.3 -> 22.4 us, one sample 6.2 -> 4.5; bf16, 5
+    // samples 13.2 -> 9.4, 256 119.8 -> 116.0; 3x3 layer and pool, 64 samples, 40.8 -> 37.0.  Four strips: wave, wave + 4, wave + 8, wave + 12 of a tile through four operand sets; a strip's operands are requested two strips
+    // before it is computed, the first two of the next tile behind this tile's last two.  (A workgroup without a tile asks for the XCD's last one.)
     v4i_r xs[PER][NKB];
-    if (PER == 1 && u < u_end) load_strip(tile_at(u), wave, xs[0]);     // its latency lies under the weights'
+    {
+        const Tile t0 = tile_at(max(min(u, t.total - 1), 0));
+        load_strip(t0, wave, xs[0]);
+        if constexpr (PER == 4) load_strip(t0, wave + 4, xs[1]);
+    }
+    v4i_r wreg[NT][NKB];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) wreg[j][kb] = *(const v4i_r*)((const unsigned char*)a.wo + ((size_t)(j * (a.Kp / 32) + kb) * 64 + lane) * 16);
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < 64) l_bias[tid] = in_bias;
     // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
 #pragma unroll
     for (int j = 0; j < NT; ++j)
@@ -144,13 +152,6 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
             if (r < RPIX) *(v4i_r*)(stem_lds + r * ST_PITCH + 32 * j + 16 * hi) = o;
         }
     };
-    // four strips: wave, wave + 4, wave + 8, wave + 12 of a tile through four operand sets; a strip's operands are requested two strips
-    // before it is computed, the first two of the next tile behind this tile's last two
-    if (PER == 4 && u < u_end) {
-        const Tile t0 = tile_at(u);
-        load_strip(t0, wave, xs[0]);
-        load_strip(t0, wave + 4, xs[1 % PER]);
-    }
     for (; u < u_end; u += u_step) {
         const Tile tl = tile_at(u);
         const bool more = u + u_step < u_end;
@@ -233,12 +234,13 @@ __global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void
     const unsigned lds0 = lds_addr(stem_lds);
     unsigned char* const l_conv = stem_lds + 2 * SB_STAGE;
     float* const l_bias = (float*)(l_conv + SB_RPIX * SB_PITCH);
+    const float in_bias = ((const float*)a.bias)[tid & 63];
     v4i wreg[2][NK];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int k = 0; k < NK; ++k) wreg[j][k] = *(const v4i*)((const unsigned char*)a.w + (size_t)(32 * j + p) * a.Kp * 2 + k * 32 + 16 * hi);
-    if (tid < 64) l_bias[tid] = ((const float*)a.bias)[tid];
+        for (int k = 0; k < NK; ++k) wreg[j][k] = *(const v4i*)((const unsigned char*)a.wo + ((size_t)(j * (a.Kp / 16) + k) * 64 + lane) * 16);
+    __builtin_amdgcn_sched_barrier(0);
     // this lane's chunks of a staged tile: row | column << 8 of the folded pixel, half of it
     int spos[SB_PASSES];
 #pragma unroll
@@ -268,16 +270,17 @@ __global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void
             dma16(lds0 + buf * SB_STAGE + i * 4096 + wave * 1024, xn + (unsigned)((cy * a.W + cx) * 32 + 16 * (spos[i] >> 16)));
         }
     };
+    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
+    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
+    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3), buf = 0;
+    Tile tl = tile_at(u);
+    if (u < u_end) stage(tl, 0);                                        // on its way with the weights
+    if (tid < 64) l_bias[tid] = in_bias;
     // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(wreg[j][k]));
-    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
-    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
-    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3), buf = 0;
-    Tile tl = tile_at(u);
-    if (u < u_end) stage(tl, 0);
     for (; u < u_end; u += u_step, buf ^= 1) {
         wait_all_then_barrier<0>();                                     // the tile is staged, the pooling of the one before has read its convolution outputs
         const Tile tn = tile_at(u + u_step);
@@ -362,12 +365,13 @@ __global__ __launch_bounds__(256, 3) void conv_pool_i8_kernel(ConvArgs a, void* 
     const unsigned lds0 = lds_addr(stem_lds);
     unsigned char* const l_conv = stem_lds + 2 * CP_STAGE;
     int* const l_bias = (int*)(l_conv + SB_RPIX * CP_PITCH);
+    const int in_bias = ((const int*)a.bias)[tid & 63];
     v4i wreg[2][NK];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int k = 0; k < NK; ++k) wreg[j][k] = *(const v4i*)((const unsigned char*)a.w + (size_t)(32 * j + p) * a.Kp + k * 32 + 16 * hi);
-    if (tid < 64) l_bias[tid] = ((const int*)a.bias)[tid];
+        for (int k = 0; k < NK; ++k) wreg[j][k] = *(const v4i*)((const unsigned char*)a.wo + ((size_t)(j * (a.Kp / 32) + k) * 64 + lane) * 16);
+    __builtin_amdgcn_sched_barrier(0);
     // this lane's chunks of a staged tile: row | column << 8 of the input pixel, half of it
     int spos[CP_PASSES];
 #pragma unroll
@@ -392,17 +396,18 @@ __global__ __launch_bounds__(256, 3) void conv_pool_i8_kernel(ConvArgs a, void* 
             dma16(lds0 + buf * CP_STAGE + i * 4096 + wave * 1024, ok ? xn + (unsigned)((iy * a.W + ix) * 32 + 16 * (spos[i] >> 16)) : (const unsigned char*)a.zeros);
         }
     };
-    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(wreg[j][k]));
     const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
     // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
     const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
     int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3), buf = 0;
     Tile tl = tile_at(u);
-    if (u < u_end) stage(tl, 0);
+    if (u < u_end) stage(tl, 0);                                        // on its way with the weights
+    if (tid < 64) l_bias[tid] = in_bias;
+    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(wreg[j][k]));
     for (; u < u_end; u += u_step, buf ^= 1) {
         wait_all_then_barrier<0>();                                     // the tile is staged, the pooling of the one before has read its convolution outputs
         const Tile tn = tile_at(u + u_step);
