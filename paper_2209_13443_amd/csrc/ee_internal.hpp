@@ -56,8 +56,8 @@ int parse_blob(const void* blob, size_t bytes, NetDesc* out);
 // tiny kernel by value, which stores them in device memory; the convolution and pooling kernels read them there.
 enum { EE_ZC_MAX_B = 256 };
 struct SlotTab { uint16_t s[EE_ZC_MAX_B]; };
-// dst[0..255] = in, dst[256..511] = out
-hipError_t launch_upload_slots(const SlotTab& in, const SlotTab& out, uint16_t* dst, hipStream_t s);
+// dst[0 .. b) = in, dst[256 .. 256 + b) = out
+hipError_t launch_upload_slots(const SlotTab& in, const SlotTab& out, int b, uint16_t* dst, hipStream_t s);
 
 // ---- kernel argument blocks --------------------------------------------------------------------
 // Implicit-GEMM convolution: rows = output pixels m = (n, oy, ox), columns = output channels,

@@ -1077,15 +1077,28 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(v4i* p, long long n16)
 }
 
 // ---- slot tables of a step: kernel arguments -> device memory ---------------------------------------------
+// It stands between the host's decision at an exit and the next segment's first layer.  1 KB of arguments costs the host 1.5 us more per launch than a few words and the kernel 1 us to fetch, so batches of up to 64
+// samples bring a quarter of them.
+struct SlotPair64 { uint16_t in[64], out[64]; };
+__global__ __launch_bounds__(64) void upload_slots_kernel(SlotPair64 t, uint16_t* dst)
+{
+    dst[threadIdx.x] = t.in[threadIdx.x];
+    dst[EE_ZC_MAX_B + threadIdx.x] = t.out[threadIdx.x];
+}
 __global__ __launch_bounds__(256) void upload_slots_kernel(SlotTab in, SlotTab out, uint16_t* dst)
 {
     dst[threadIdx.x] = in.s[threadIdx.x];
     dst[EE_ZC_MAX_B + threadIdx.x] = out.s[threadIdx.x];
 }
 
-hipError_t launch_upload_slots(const SlotTab& in, const SlotTab& out, uint16_t* dst, hipStream_t s)
+hipError_t launch_upload_slots(const SlotTab& in, const SlotTab& out, int b, uint16_t* dst, hipStream_t s)
 {
-    EE_LAUNCH(upload_slots_kernel, dim3(1), dim3(EE_ZC_MAX_B), 0, s, in, out, dst);
+    if (b <= 64) {
+        SlotPair64 t;
+        std::memcpy(t.in, in.s, sizeof t.in);
+        std::memcpy(t.out, out.s, sizeof t.out);
+        EE_LAUNCH(static_cast<void (*)(SlotPair64, uint16_t*)>(upload_slots_kernel), dim3(1), dim3(64), 0, s, t, dst);
+    } else EE_LAUNCH(static_cast<void (*)(SlotTab, SlotTab, uint16_t*)>(upload_slots_kernel), dim3(1), dim3(EE_ZC_MAX_B), 0, s, in, out, dst);
     return hipGetLastError();
 }
 

@@ -153,7 +153,7 @@ struct GpuExec {
         // the tables that are needed go to the lane's device buffer in one tiny launch ahead of the step's kernels
         // (a small segment's launch carries its rows by value)
         if (small[stage] && b <= EE_SEG_ROWS) return EE_OK;
-        if ((st.in_base < 0 || st.out_base < 0) && launch_upload_slots(st.in, st.out, ctx->d_slots, ctx->stream) != hipSuccess) return EE_ERR_DEVICE;
+        if ((st.in_base < 0 || st.out_base < 0) && launch_upload_slots(st.in, st.out, b, ctx->d_slots, ctx->stream) != hipSuccess) return EE_ERR_DEVICE;
         ctx->zc_in = st.in_base < 0 ? ctx->d_slots : nullptr;
         ctx->zc_out = st.out_base < 0 ? ctx->d_slots + EE_ZC_MAX_B : nullptr;
         return EE_OK;
