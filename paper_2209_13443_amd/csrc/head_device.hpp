@@ -27,7 +27,7 @@ __device__ __forceinline__ unsigned softmax_term_i8(int m, int v, int f, const u
     const unsigned d = (unsigned)m - (unsigned)v;                // 0 .. 2^32 - 1
     const unsigned q = d >> f, frac = d & ((1u << f) - 1u);
     const unsigned r = f >= 8 ? frac >> (f - 8) : frac << (8 - f);
-    return q >= 31 ? 0u : table[r] >> q;
+    return table[r] >> min(q, 31u);                              // (the table is below 2^31; no condition the lookup would be behind)
 }
 // the exit decision of sample b and its outcome (one lane)
 __device__ __forceinline__ void head_decide_i8(const HeadArgs& a, int b, int arg, long long S)
@@ -66,6 +66,21 @@ __device__ __forceinline__ int row_sum(int v)
     v += row_rotate<4>(v);
     v += row_rotate<2>(v);
     return v + row_rotate<1>(v);
+}
+
+// op over the 64 lanes, in every lane.  In the order of exchanges over 32, 16, 8, 4, 2 and 1 lanes (a rotation of what is already the same every 2 N lanes is that exchange), so a
+// float sum has the bits of that tree; without the round trip through the LDS unit per exchange.
+template <typename OP>
+__device__ __forceinline__ int wave_all(int v, OP op)
+{
+    const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = op((int)h[0], (int)h[1]);
+    const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = op((int)q[0], (int)q[1]);
+    v = op(v, row_rotate<8>(v));
+    v = op(v, row_rotate<4>(v));
+    v = op(v, row_rotate<2>(v));
+    return op(v, row_rotate<1>(v));
 }
 
 __device__ __forceinline__ float head_bf16_f32(uint16_t v) { return __uint_as_float((unsigned)v << 16); }
@@ -117,62 +132,47 @@ __device__ __forceinline__ void head_logits_decide(const HeadArgs& a, int b, con
     __syncthreads();
     if (tid >= 64) return;
     constexpr int PER = HEAD_SMALL_CLS / 64;
-    const int o0 = a.n_cls > 32 ? 32 : a.n_cls > 16 ? 16 : 8;      // lanes past the classes hold nothing: the first lanes' exchanges do
     int vi[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) vi[i] = lane + 64 * i < a.n_cls ? lg[lane + 64 * i] : (ES == 1 ? INT32_MIN : __float_as_int(-INFINITY));
     int arg = INT32_MAX;
+    const auto lesser = [](int x, int y) { return min(x, y); };
     if constexpr (ES == 1) {
         int m = INT32_MIN;
 #pragma unroll
         for (int i = 0; i < PER; ++i) m = max(m, vi[i]);
-        for (int o = o0; o > 8; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-        m = max(m, row_rotate<8>(m));
-        m = max(m, row_rotate<4>(m));
-        m = max(m, row_rotate<2>(m));
-        m = max(m, row_rotate<1>(m));
-        long long S = 0;
+        m = wave_all(m, [](int x, int y) { return max(x, y); });
+        unsigned long long S = 0;
         const int f = a.frac_bits;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int j = lane + 64 * i;
-            if (j >= a.n_cls) continue;
-            if (vi[i] == m) arg = min(arg, j);
-            S += softmax_term_i8(m, vi[i], f, exp2_lds);
+            if (64 * i >= a.n_cls) break;
+            const bool in = lane + 64 * i < a.n_cls;
+            const unsigned t = softmax_term_i8(m, vi[i], f, exp2_lds);
+            arg = in && vi[i] == m ? min(arg, lane + 64 * i) : arg;
+            S += in ? t : 0u;
         }
-        for (int o = o0; o > 8; o >>= 1) {
-            S += __shfl_xor(S, o, 64);
-            arg = min(arg, __shfl_xor(arg, o, 64));
-        }
-        auto step = [&](auto n) {                                // S is below 2^44: a 64-bit value travels as two dwords
-            constexpr int N = decltype(n)::value;
-            const unsigned lo = (unsigned)row_rotate<N>((int)(unsigned)S), up = (unsigned)row_rotate<N>((int)(unsigned)((unsigned long long)S >> 32));
-            S += (long long)((unsigned long long)up << 32 | lo);
-            arg = min(arg, row_rotate<N>(arg));
-        };
-        step(std::integral_constant<int, 8>{});
-        step(std::integral_constant<int, 4>{});
-        step(std::integral_constant<int, 2>{});
-        step(std::integral_constant<int, 1>{});
-        if (lane == 0) head_decide_i8(a, b, arg, S);
+        // in two parts, the lower 16 bits and the rest (a lane's sum is at most 4 * 2^30): each stays below 2^32 over the wavefront
+        const auto sum = [](int x, int y) { return (int)((unsigned)x + (unsigned)y); };
+        const unsigned lo = (unsigned)wave_all((int)((unsigned)S & 0xFFFFu), sum), up = (unsigned)wave_all((int)(unsigned)(S >> 16), sum);
+        arg = wave_all(arg, lesser);
+        if (lane == 0) head_decide_i8(a, b, arg, (long long)(((unsigned long long)up << 16) + lo));
     } else {
         float m = -INFINITY;
 #pragma unroll
         for (int i = 0; i < PER; ++i) m = fmaxf(m, __int_as_float(vi[i]));
-        for (int o = o0; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        m = __int_as_float(wave_all(__float_as_int(m), [](int x, int y) { return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y))); }));
         float den = 0.f;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int j = lane + 64 * i;
-            if (j >= a.n_cls) continue;
-            const float z = __int_as_float(vi[i]);
-            if (z == m) arg = min(arg, j);
-            den += expf(z - m);
+            if (64 * i >= a.n_cls) break;
+            const bool in = lane + 64 * i < a.n_cls;
+            const float z = __int_as_float(vi[i]), t = expf(z - m);
+            arg = in && z == m ? min(arg, lane + 64 * i) : arg;
+            den = in ? den + t : den;
         }
-        for (int o = o0; o > 0; o >>= 1) {
-            den += __shfl_xor(den, o, 64);
-            arg = min(arg, __shfl_xor(arg, o, 64));
-        }
+        den = __int_as_float(wave_all(__float_as_int(den), [](int x, int y) { return __float_as_int(__int_as_float(x) + __int_as_float(y)); }));
+        arg = wave_all(arg, lesser);
         if (lane == 0) head_decide_bf16(a, b, arg, den);
     }
 }

@@ -725,48 +725,59 @@ typedef __bf16 v8bf_m __attribute__((ext_vector_type(8)));
 template <int ES, int NW, int TC>
 __global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
 {
+    request_args<sizeof(HeadArgs)>();
     constexpr int U = TC == 1 ? 4 : 2;                          // steps in flight per wavefront
+    constexpr int Q = ES == 1 ? 4 : 2;                          // loads of a lane's features per step
+    constexpr unsigned NOWHERE = 0x80000000u;                   // an offset past every buffer: reads zeros
     __shared__ int part[NW][TC * 256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j0 = blockIdx.x * 16 * TC, b0 = blockIdx.y * 16;
     const int r = lane & 15, kq = lane >> 4;
     const int b = b0 + r;
-    const int CB = a.C * ES;                                   // bytes per weight row (a multiple of 16)
+    const int CB = a.C * ES;                                   // bytes per weight row (a multiple of 16, at most 4096)
     const int nsteps = (CB + 63) / 64, last_tile = (a.n_cls + 15) / 16 - 1;
-    const v4i* wtile[TC];                                       // ready operands: 1 KB per step, one contiguous load
-#pragma unroll
-    for (int t = 0; t < TC; ++t) wtile[t] = (const v4i*)a.wfo + (long long)min((int)blockIdx.x * TC + t, last_tile) * nsteps * 64 + lane;
     const bool bin = b < a.B;
+    // Operands through buffers: a step past the last, a channel past the last and a sample past the batch read zeros, with no condition in front of a load; behind conditions the sixteen loads of
+    // features went out one branch at a time.  Weights of zero past the last step as well, as an infinite one times zero is no number.  With the features requantised two at a time (32 instructions a
+    // step instead of 84): 1000 classes, 256 samples, 2048 channels int8 8.4 -> 7.4 us, bf16 8.9 -> 8.4; 1024 channels 6.1 -> 5.1, 5.8 -> 5.4; 8x8 pixels and 64 samples 6.9 -> 6.0.
+    const auto w_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.wfo), (short)0, (last_tile + 1) * nsteps * 1024, 0x00020000);
+    const auto g_buf = __builtin_amdgcn_make_buffer_rsrc(a.sums + (long long)b0 * a.C, (short)0, min(16, a.B - b0) * a.C * 4, 0x00020000);
+    const auto bias_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.bfc), (short)0, a.n_cls * 4, 0x00020000);
+    constexpr int NB = (TC * 256 + 64 * NW - 1) / (64 * NW);    // results per lane
+    int bias[NB];
+    auto cls_of = [&](int i) { return j0 + i / 256 * 16 + 4 * kq + (i / 64) % 4; };      // element i of the partial tiles: this class of sample r
+#pragma unroll
+    for (int n = 0; n < NB; ++n) bias[n] = __builtin_amdgcn_raw_buffer_load_b32(bias_buf, cls_of(threadIdx.x + 64 * NW * n) * 4, 0, 0);
     const v4i zero4 = {0, 0, 0, 0};
     v4i acci[TC];
     v4f_m accf[TC];
 #pragma unroll
     for (int t = 0; t < TC; ++t) { acci[t] = zero4; accf[t] = v4f_m{0.f, 0.f, 0.f, 0.f}; }
+    const int shift = max(a.gap_shift, 0), rnd = shift > 0 ? 1 << (shift - 1) : 0;
     for (int s0 = wave; s0 < nsteps; s0 += U * NW) {
-        v4i wv[U][TC], gv[U][4];
+        v4i wv[U][TC], gv[U][Q];
 #pragma unroll
         for (int u = 0; u < U; ++u) {                           // all loads of U steps first
-            const int kb = (s0 + NW * u) * 64 + kq * 16;
-            const bool kin = kb < CB;
+            const int step = s0 + NW * u;
+            const unsigned g_at = step * 64 + kq * 16 < CB ? (unsigned)(r * a.C + (step * 64 + kq * 16) / ES) * 4u : NOWHERE;
 #pragma unroll
-            for (int t = 0; t < TC; ++t) {                      // a step past the last meets features of zero; bf16: weights of zero too, as an infinite one times zero is no number
-                wv[u][t] = wtile[t][min(s0 + NW * u, nsteps - 1) * 64];
-                if (ES == 2 && s0 + NW * u >= nsteps) wv[u][t] = zero4;
+            for (int t = 0; t < TC; ++t) {
+                const unsigned w_at = step < nsteps ? (unsigned)((min((int)blockIdx.x * TC + t, last_tile) * nsteps + step) * 1024) : NOWHERE;
+                wv[u][t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(w_buf, w_at + lane * 16, 0, 0));
             }
-            const int* sp = a.sums + (long long)min(b, a.B - 1) * a.C + kb / ES;
 #pragma unroll
-            for (int q = 0; q < (ES == 1 ? 4 : 2); ++q) gv[u][q] = kin && bin ? *(const v4i*)(sp + 4 * q) : zero4;
+            for (int q = 0; q < Q; ++q) gv[u][q] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(g_buf, g_at + 16 * q, 0, 0));
         }
+        __builtin_amdgcn_sched_barrier(0);                      // (left to itself the compiler spreads them over the conversions)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if constexpr (ES == 1) {
-                v4i g8 = zero4;
+                v4i g8;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int sum = gv[u][e >> 2][e & 3];
-                    int g = a.gap_shift > 0 ? (sum + (1 << (a.gap_shift - 1))) >> a.gap_shift : sum;
-                    g = min(max(g, -128), 127);
-                    g8[e >> 2] |= (g & 0xFF) << (8 * (e & 3));
+                for (int q = 0; q < 4; ++q) {                   // v_ashr_pk_i8_i32 shifts and saturates two sums at a time
+                    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+                    g8[q] = __builtin_bit_cast(int, (u16x2{(unsigned short)__builtin_amdgcn_ashr_pk_i8_i32(gv[u][q][0] + rnd, gv[u][q][1] + rnd, shift),
+                                                           (unsigned short)__builtin_amdgcn_ashr_pk_i8_i32(gv[u][q][2] + rnd, gv[u][q][3] + rnd, shift)}));
                 }
 #pragma unroll
                 for (int t = 0; t < TC; ++t) acci[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv[u][t], g8, acci[t], 0, 0, 0);
@@ -794,12 +805,11 @@ __global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
         for (int v = 0; v < 4; ++v) part[wave][t * 256 + v * 64 + lane] = ES == 1 ? acci[t][v] : __float_as_int(accf[t][v]);
     __syncthreads();
 #pragma unroll
-    for (int i = threadIdx.x; i < TC * 256; i += 64 * NW) {     // element i: class j0 + 16 (i / 256) + 4 kq + (i / 64) % 4 of sample r
-        const int jj = j0 + i / 256 * 16 + 4 * kq + (i / 64) % 4;
-        if (jj >= a.n_cls || !bin) continue;
-        const int bias = ((const int*)a.bfc)[jj];
+    for (int n = 0; n < NB; ++n) {
+        const int i = threadIdx.x + 64 * NW * n, jj = cls_of(i);
+        if (i >= TC * 256 || jj >= a.n_cls || !bin) continue;
         if constexpr (ES == 1) {
-            int t = bias;
+            int t = bias[n];
 #pragma unroll
             for (int w = 0; w < NW; ++w) t += part[w][i];
             ((int*)a.logits)[(long long)b * a.n_cls + jj] = t;
@@ -807,7 +817,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fc_kernel(HeadArgs a)
             float t = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) t += __int_as_float(part[w][i]);
-            ((float*)a.logits)[(long long)b * a.n_cls + jj] = a.logit_scale * (t + __int_as_float(bias));
+            ((float*)a.logits)[(long long)b * a.n_cls + jj] = a.logit_scale * (t + __int_as_float(bias[n]));
         }
     }
 }
@@ -849,106 +859,109 @@ static const uint32_t kExp2Host[256] = {
 };
 const uint32_t* exp2_table_host() { return kExp2Host; }
 
-template <typename T>
-__device__ __forceinline__ T block_reduce(T v, T* scratch, bool is_max)
-{
-    for (int o = 32; o > 0; o >>= 1) {
-        T other = __shfl_xor(v, o, 64);
-        v = is_max ? (other > v ? other : v) : v + other;
-    }
-    const int wave = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) scratch[wave] = v;
-    __syncthreads();
-    T r = scratch[0];
-    for (int w = 1; w < 4; ++w) r = is_max ? (scratch[w] > r ? scratch[w] : r) : r + scratch[w];
-    return r;
-}
-
 // one workgroup per sample.  int8: m = max logit, label = lowest arg-max, S = sum_j T[frac(d_j)] >> (d_j >> f)
 // with d_j = m - a_j (a base-2 softmax denominator in Q30); exits iff S <= s_thr.  bf16: float softmax.
-// The sample's logits are read once into registers (up to 8 per lane: n_cls <= 2048); the arg-max and the
-// denominator travel through one combined reduction.
-template <int ES>
+// The sample's logits are read once into registers (PER per lane: n_cls <= 256 PER, the smallest of 1, 4 and 8, as every one costs a table lookup or an exponential also where it is no class); the
+// arg-max and the denominator travel through one combined reduction.  Bound by latency: a chain of loads, two barriers and the decision.  Exchanges between lanes without the LDS unit (wave_all), all
+// lookups in flight together and one barrier per reduction instead of two: with the FC's loads above, an exit step of 37 samples went from 436 to 429 us (four heads), one of a single sample on the
+// mobile network from 155 to 151 (three).
+template <int ES, int PER>
 __global__ __launch_bounds__(256) void softmax_kernel(HeadArgs a)
 {
     request_args<sizeof(HeadArgs)>();
-    __shared__ long long scratch[8];
-    __shared__ int scratch_arg[4];
+    __shared__ int all[4][4];
     __shared__ uint32_t exp2_lds[256];
-    const int b = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int b = blockIdx.x, wave = threadIdx.x >> 6;
     uint32_t exp2_mine = 0;
     if constexpr (ES == 1) exp2_mine = kExp2[threadIdx.x];       // on its way with the logits: the terms then look it up in LDS
-    constexpr int PER = 8;
+    const auto lg_buf = __builtin_amdgcn_make_buffer_rsrc((int*)a.logits + (long long)b * a.n_cls, (short)0, a.n_cls * 4, 0x00020000);
     int vi[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int j = threadIdx.x + 256 * i;
-        vi[i] = j < a.n_cls ? ((const int*)a.logits)[(long long)b * a.n_cls + j] : (ES == 1 ? INT32_MIN : __float_as_int(-INFINITY));
-    }
+    for (int i = 0; i < PER; ++i) vi[i] = __builtin_amdgcn_raw_buffer_load_b32(lg_buf, (threadIdx.x + 256 * i) * 4, 0, 0);
+    auto is = [&](int i) { return (int)threadIdx.x + 256 * i < a.n_cls; };
     if constexpr (ES == 1) {
-        int m = INT32_MIN;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) m = max(m, vi[i]);
-        exp2_lds[threadIdx.x] = exp2_mine;                      // complete behind the barriers of the reduction
-        m = block_reduce<int>(m, (int*)scratch, true);
-        int arg = INT32_MAX;
-        long long S = 0;
-        const int f = a.frac_bits;                              // 0 .. 30
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int j = threadIdx.x + 256 * i;
-            if (j >= a.n_cls) continue;
-            const int v = vi[i];
-            if (v == m) arg = min(arg, j);
-            S += softmax_term_i8(m, v, f, exp2_lds);
-        }
-        for (int o = 32; o > 0; o >>= 1) {                  // integer sums and minima: exact in any order
-            S += __shfl_xor(S, o, 64);
-            arg = min(arg, __shfl_xor(arg, o, 64));
-        }
-        __syncthreads();
-        if (lane == 0) { scratch[wave] = S; scratch_arg[wave] = arg; }
-        __syncthreads();
-        S = scratch[0] + scratch[1] + scratch[2] + scratch[3];
-        arg = min(min(scratch_arg[0], scratch_arg[1]), min(scratch_arg[2], scratch_arg[3]));
         // the pooled sums of this sample have been consumed by the FC: leave them zero for the next head
         for (int c = threadIdx.x; c < a.C; c += 256) a.sums[(long long)b * a.C + c] = 0;
-        if (threadIdx.x == 0) head_decide_i8(a, b, arg, S);
+        exp2_lds[threadIdx.x] = exp2_mine;                      // complete behind the barrier of the reduction
+        int m = INT32_MIN;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) m = is(i) ? max(m, vi[i]) : m;
+        m = wave_all(m, [](int x, int y) { return max(x, y); });
+        all[0][wave] = m;                                       // (every lane the same)
+        __syncthreads();
+        m = max(max(all[0][0], all[0][1]), max(all[0][2], all[0][3]));
+        int arg = INT32_MAX;
+        unsigned lo = 0, up = 0;                                // the terms' sum in two parts of 16 bits and more: each stays below 2^32 over the workgroup
+        const int f = a.frac_bits;                              // 0 .. 30
+        unsigned long long S = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const unsigned t = softmax_term_i8(m, vi[i], f, exp2_lds);
+            S += is(i) ? t : 0u;
+            arg = is(i) && vi[i] == m ? min(arg, (int)threadIdx.x + 256 * i) : arg;
+        }
+        lo = (unsigned)S & 0xFFFFu;
+        up = (unsigned)(S >> 16);                               // S <= 8 * 2^30
+        const auto sum = [](int x, int y) { return (int)((unsigned)x + (unsigned)y); };
+        lo = wave_all((int)lo, sum);                            // integer sums and minima: exact in any order
+        up = wave_all((int)up, sum);
+        arg = wave_all(arg, [](int x, int y) { return min(x, y); });
+        all[1][wave] = lo;
+        all[2][wave] = up;
+        all[3][wave] = arg;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            arg = min(min(all[3][0], all[3][1]), min(all[3][2], all[3][3]));
+            lo = all[1][0] + all[1][1] + all[1][2] + all[1][3];
+            up = all[2][0] + all[2][1] + all[2][2] + all[2][3];
+            head_decide_i8(a, b, arg, (long long)(((unsigned long long)up << 16) + lo));
+        }
     } else {
         float m = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) m = fmaxf(m, __int_as_float(vi[i]));
-        m = block_reduce<float>(m, (float*)scratch, true);
+        for (int i = 0; i < PER; ++i) m = is(i) ? fmaxf(m, __int_as_float(vi[i])) : m;
+        m = __int_as_float(wave_all(__float_as_int(m), [](int x, int y) { return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y))); }));
+        all[0][wave] = __float_as_int(m);
+        __syncthreads();
+        m = __int_as_float(all[0][0]);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) m = fmaxf(m, __int_as_float(all[0][w]));
         int arg = INT32_MAX;
         float den = 0.f;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int j = threadIdx.x + 256 * i;
-            if (j >= a.n_cls) continue;
             const float z = __int_as_float(vi[i]);
-            if (z == m) arg = min(arg, j);
-            den += expf(z - m);
+            const float t = expf(z - m);
+            den = is(i) ? den + t : den;
+            arg = is(i) && z == m ? min(arg, (int)threadIdx.x + 256 * i) : arg;
         }
-        for (int o = 32; o > 0; o >>= 1) {                  // fixed shuffle tree: the float sum is reproducible
-            den += __shfl_xor(den, o, 64);
-            arg = min(arg, __shfl_xor(arg, o, 64));
+        // a fixed tree: the float sum is reproducible
+        den = __int_as_float(wave_all(__float_as_int(den), [](int x, int y) { return __float_as_int(__int_as_float(x) + __int_as_float(y)); }));
+        arg = wave_all(arg, [](int x, int y) { return min(x, y); });
+        all[1][wave] = __float_as_int(den);
+        all[3][wave] = arg;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            den = ((__int_as_float(all[1][0]) + __int_as_float(all[1][1])) + __int_as_float(all[1][2])) + __int_as_float(all[1][3]);
+            arg = min(min(all[3][0], all[3][1]), min(all[3][2], all[3][3]));
+            head_decide_bf16(a, b, arg, den);
         }
-        __syncthreads();
-        if (lane == 0) { ((float*)scratch)[wave] = den; scratch_arg[wave] = arg; }
-        __syncthreads();
-        den = ((((float*)scratch)[0] + ((float*)scratch)[1]) + ((float*)scratch)[2]) + ((float*)scratch)[3];
-        arg = min(min(scratch_arg[0], scratch_arg[1]), min(scratch_arg[2], scratch_arg[3]));
-        if (threadIdx.x == 0) head_decide_bf16(a, b, arg, den);
     }
+}
+
+template <int ES>
+static void launch_softmax(const HeadArgs& a, hipStream_t s)
+{
+    if (a.n_cls <= 256) EE_LAUNCH((softmax_kernel<ES, 1>), dim3(a.B), dim3(256), 0, s, a);
+    else if (a.n_cls <= 1024) EE_LAUNCH((softmax_kernel<ES, 4>), dim3(a.B), dim3(256), 0, s, a);
+    else EE_LAUNCH((softmax_kernel<ES, 8>), dim3(a.B), dim3(256), 0, s, a);
 }
 
 hipError_t launch_head_softmax(const HeadArgs& a, int dtype, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
-    if (dtype == EE_I8) EE_LAUNCH(softmax_kernel<1>, dim3(a.B), dim3(256), 0, s, a);
-    else EE_LAUNCH(softmax_kernel<2>, dim3(a.B), dim3(256), 0, s, a);
+    if (dtype == EE_I8) launch_softmax<1>(a, s);
+    else launch_softmax<2>(a, s);
     return hipGetLastError();
 }
 

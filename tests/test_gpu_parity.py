@@ -529,6 +529,36 @@ def test_class_tiles_per_workgroup_of_the_fc(torch, ee, orc, c, n_cls, dtype):
     eng.close()
 
 
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("c, n_cls, per", [(512, 256, 1), (512, 257, 4), (48, 1024, 4), (48, 1025, 8), (16, 2048, 8)])
+def test_logits_per_lane_of_the_softmax(torch, ee, orc, c, n_cls, per, dtype):
+    """The softmax with one, four and eight logits per lane, class counts on both sides of each: decisions against the oracle.  Two classes share the largest logit (the lower is the label).  bf16: the float
+    denominator of up to 2048 terms in (0, 1] is within 2048 * 2^-23 of the exact one, relatively, and the logits within 1e-3 of their largest, as above."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8 if dtype == "i8" else W.DT_BF16, 2, 1, c, n_cls)
+    net.begin_stage()
+    net.end_stage(net.maxpool(0, 3, 1, 1))
+    blob = N._assemble(net, net.dtype, 23)
+    act = W.input_pool(blob, 3)
+    wfc, bias = blob.exit_weights(0)[:2]
+    first, last = n_cls // 3, n_cls - 1
+    top = int(orc.exit_head(blob, 0, act[:1], 0.5, want_logits=True)[4][0].argmax())
+    wfc = wfc.reshape(n_cls, c)
+    for j in (first, last):
+        wfc[j], bias[j] = wfc[top], bias[top]
+    eng = ee.Engine(blob, 3)
+    lab, conf, score, flag, logits = orc.exit_head(blob, 0, act, 0.5, want_logits=True)
+    assert logits[0, first] == logits[0, last] == logits[0].max()
+    (glab, gconf, gscore, gflag), names = kernels_of(torch, lambda: eng.exit_head(0, dev(torch, act), 0.5))
+    assert [x for x in names if x.startswith("softmax_kernel")] == [f"softmax_kernel<{1 if dtype == 'i8' else 2},{per}>"], names
+    if dtype == "i8":
+        assert np.array_equal(glab.cpu().numpy(), lab) and np.array_equal(gscore.cpu().numpy(), score) and np.array_equal(gflag.cpu().numpy(), flag)
+        assert np.allclose(gconf.cpu().numpy(), conf, rtol=1e-6, atol=0)
+    else:
+        assert int(glab[0]) == int(lab[0]) and np.all(np.abs(gconf.cpu().numpy() - conf) <= 1e-3)
+    eng.close()
+
+
 def test_infinite_weights_of_the_fc(torch, ee, orc):
     """bf16: an infinite weight in the last step of a reduction that is shorter than what the wavefronts have in flight makes its class's logit infinite and no other, with every number of class tiles per
     workgroup: logits and labels are the oracle's."""
