@@ -1581,6 +1581,14 @@ extern "C" int ee_pair_count(const ee_ctx* ctx)
 }
 
 // ---- one backbone segment ------------------------------------------------------------------------
+bool ee_ctx::first_reads_images(int b, const void* x) const
+{
+    const int op = net.stages[0].first_op;
+    const OpPlan& p = plans[(size_t)op];
+    return p.ir && p.ir_stem && p.impl == IMPL_MFMA_S2D && p.src_buf == BUF_EXT_IN && forced_conv_tile() == 0 && op + 1 != gap_fuse_op[0] && ir_wanted(op, b) &&
+           stem_image_supported(x, net.elem_bytes(), p.d.w_in, p.d.c_in);
+}
+
 int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool first_packed, int only_op, int cfg_force)
 {
     const int only_block = only_op <= -2 ? -2 - only_op : -1;      // <= -2: just the three layers of the block headed by layer -2 - only_op
@@ -1616,7 +1624,9 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             if (fuse && p.ir_stem) {
                 const OpPlan& q2 = plans[st.first_op + k + 1];
                 const bool folded = p.impl == IMPL_MFMA_S2D;
-                if (folded && !(first_packed && k == 0)) {                                 // the folded copy of the input, as in front of the layer alone
+                const bool packed = first_packed && k == 0;
+                const bool image = stage == 0 && k == 0 && first_reads_images(b, packed ? first_pool : src);
+                if (folded && !packed && !image) {                                 // the folded copy of the input, as in front of the layer alone
                     const double pb = (double)b * ((double)d.h_in * d.w_in * d.c_in + (double)p.Hp * p.Wp * 16) * es;
                     e = timed(EE_K_PAD_INPUT, 0.0, pb, [&] { return launch_space_to_depth(src, pad_bufs[p.pad_buf], nullptr, b, d.h_in, d.w_in, d.c_in, p.Hp, p.Wp, d.pad, dt, stream); });
                     if (e != hipSuccess) return EE_ERR_DEVICE;
@@ -1627,7 +1637,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 void* yq = resolve(this, q2.dst_buf, act_in, act_out);
                 const double mid = 2.0 * es * b * (double)d.h_out * d.w_out * d.c_out; // the tensor that stays on chip
                 e = timed(EE_K_CONV_STREAM, ops + q2.ops_per_sample * b, bytes + q2.bytes_per_sample * b + q2.weight_bytes - mid,
-                          [&] { return folded ? launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream) : launch_conv_pool(ca, yq, q2.d.h_out, q2.d.w_out, q2.d.pad, stream); }, st.first_op + k);
+                          [&] { return image ? launch_stem_image(ca, packed ? first_pool : src, packed ? first_ids : nullptr, d.h_in, d.w_in, d.pad, yq, q2.d.h_out, q2.d.w_out, stream) : folded ? launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream) : launch_conv_pool(ca, yq, q2.d.h_out, q2.d.w_out, q2.d.pad, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
                 ++i;                                                             // the pool is done
                 continue;
@@ -1946,7 +1956,10 @@ extern "C" int ee_measure_lut(ee_ctx* ctx, int reps, int64_t* lut_ns)
                         const HeadArgs h = ctx->head_args(s, b, ctx->out_buf[s], 2.0f, ctx->d_label, ctx->d_conf, ctx->d_score, ctx->d_flag, true, nullptr);
                         rc = ctx->run_segment(s, b, ctx->in_buf[s], ctx->out_buf[s], nullptr, s == 0 ? ctx->h_ids[0] : nullptr, nullptr, nullptr, &h);
                     } else {
-                    if (s == 0 && fold) {
+                    if (s == 0 && fold && ctx->first_reads_images(b, ctx->in_buf[0])) {
+                        ctx->first_pool = ctx->in_buf[0];
+                        ctx->first_ids = ctx->h_ids[0];
+                    } else if (s == 0 && fold) {
                         const OpDesc& d = fold->d;
                         if (launch_space_to_depth(ctx->in_buf[0], ctx->pad_bufs[fold->pad_buf], ctx->h_ids[0], b, d.h_in, d.w_in, d.c_in, fold->Hp, fold->Wp, d.pad, ctx->net.dtype, ctx->stream, true) != hipSuccess) rc = EE_ERR_DEVICE;
                     }

@@ -143,7 +143,7 @@ struct ee_ctx {
     }
 
     // internal entry points shared by the C ABI and the stream driver (no argument checks)
-    // first_packed: the first layer's folded input copy already holds these samples (admission wrote it)
+    // first_packed: the first layer's folded input copy already holds these samples (admission wrote it), or, where first_reads_images, they are requests first_ids of first_pool
     // only_op >= 0: just that layer (an index into plans; fused pairs run as separate layers then); only_op <= -2: just the
     // inverted-residual block headed by layer -2 - only_op (one launch or three, as ir_mode and the table say);
     // cfg_force > 0: that kernel configuration for every matrix-core layer instead of the table's
@@ -158,6 +158,10 @@ struct ee_ctx {
             if (plans[st.first_op + k].src_buf == ee::BUF_EXT_IN || plans[st.first_op + k].res_buf == ee::BUF_EXT_IN) return nullptr;
         return &p;
     }
+    // whether b samples of segment 0 at x are read by the launch of its first layer and pool itself: nothing is folded in front of it, and admission has nothing to do
+    bool first_reads_images(int b, const void* x) const;
+    const void* first_pool = nullptr;       // with first_packed: where the requests are
+    const int32_t* first_ids = nullptr;     // pinned
     // launches layer `op` (an index into plans) on b samples with the given kernel configuration (0 = by shape)
     hipError_t launch_conv(int op, int b, const void* src, void* dst, const void* res, int cfg, const uint16_t* xs = nullptr, const uint16_t* ys = nullptr, int32_t* gap_sums = nullptr);
     bool group_by_default(int stage, int at, int n, int b) const;    // whether those layers go together when no table for the joint launch is set

@@ -11,6 +11,8 @@
 // has at least one pixel that exists).  After a barrier the lanes take (pooled pixel, 16 channels) items, 448 per tile: nine 16-byte
 // LDS reads, byte-wise maximum on 16-bit halves, one 16-byte store.  A seventh of the convolution is computed twice (the windows'
 // overlap between tiles and the last strip's padding); results are those of the two layers bit for bit.
+#include <cstring>
+
 #include "ee_internal.hpp"
 #include "igemm_device.hpp"
 #include "ir_device.hpp"
@@ -24,6 +26,7 @@ struct StemTile {
     int tiles_x, tiles_y;      // tiles of 14 x 8 pooled pixels per image
     int total;                 // tiles in all
     unsigned magic_tpi, magic_tx;   // floor(2^32 / d) for the tiles of an image and of a row: fast_div
+    int images;
     int pool_pad;              // conv_pool_i8_kernel: the pool's padding, 0 or 1 (the others have 1)
 };
 
@@ -200,6 +203,206 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
         }
         __syncthreads();                                                // the LDS image is free for the next tile
     }
+}
+
+// ---- the same straight from the images (int8, 3 channels, rows of whole 16-byte chunks) ---------------------------------------
+// Without a folded copy of the batch and the launch that makes it.  The image rows under a tile (40 pieces of 208 bytes for 14 x 8) are copied into LDS asynchronously and a tile ahead, zeros outside
+// the image, folded there into super-pixels, and the strips read their operands from LDS: 16 bytes a lane and step at twice the rate of the path from the caches.  A lane folds two neighbouring
+// super-pixels of a row: four pixels are 12 contiguous bytes of an image row, read as four dwords around them, shifted into place (the same shift for the whole tile) and spread to 4 bytes per
+// pixel with byte permutes.  Requests of a stream: the images at ids in the pool, by value for up to 256 of them (a quarter of the arguments for 64), else read from host memory.
+// Three workgroups share a CU (51 KB of LDS, 163 registers).  What bounds it: vector issue, as above, some 630 instructions per wavefront and tile, and 64 matrix instructions, which overlap in part.
+// 224 x 224, us, the folded copy and the kernel above / this one, both with the time between launches: 1 sample 13.0 / 10.0 (of which the 1x1 layer behind them 4), 24 19.5 / 15.0, 64 34.2 / 26.5,
+// 256 104 / 83; by itself, 64 samples 20.2 / 20.8, 256 70.1 / 63.5 (with two workgroups per CU 66.8).
+struct StemImage {
+    const void* x;              // images or (ids) the pool
+    const int32_t* gather;      // more than 256 ids: device-visible memory, else null
+    int by_value;               // the table in front of the arguments holds the ids
+    int H, row_bytes, pad;      // image rows, bytes of a row, padding of the convolution
+};
+template <int N>
+struct StemIds { int32_t id[N]; };
+
+template <int TW, int TH>
+struct StemImageShape : StemShape<TW, TH> {
+    using Base = StemShape<TW, TH>;
+    static constexpr int FW = Base::RW + 3, FH = Base::RH + 3;          // folded pixels under a tile
+    static constexpr int RC = (15 + 6 * FW + 15) / 16, CHUNKS = 2 * FH * RC, PASSES = (CHUNKS + 255) / 256;    // 16-byte chunks of an image row, whatever its alignment
+    static constexpr int RAW = (CHUNKS + 63) / 64 * 1024;               // whole copies of a wavefront
+    static constexpr int PAIRS = FH * FW / 2;
+    // the tile's convolution outputs in four planes of 16 channels: neighbouring pixels are written, and the four planes of a window read, without bank conflicts
+    static constexpr int PLANE = (Base::RPIX * 16 - 64 + 255) / 256 * 256 + 64, FOLD = 4 * PLANE + 256;
+    static constexpr size_t lds_bytes() { return FOLD + FW * FH * 16 + RAW; }
+};
+
+template <int TW, int TH>
+__device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const StemTile& t, const StemImage& im, const __attribute__((address_space(4))) int* tab)
+{
+    using Sh = StemImageShape<TW, TH>;
+    constexpr int RW = Sh::RW, RPIX = Sh::RPIX, ITEMS = Sh::ITEMS, PER = Sh::PER, FW = Sh::FW, RC = Sh::RC;
+    constexpr int NKB = 8, NT = 2, NST = (ITEMS + 255) / 256;
+    constexpr unsigned NOWHERE = 0x80000000u;                           // an offset past the output: the store is dropped
+    extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int* const l_bias = (int*)(stem_lds + 4 * Sh::PLANE);               // 64 biases
+    unsigned char* const l_fold = stem_lds + Sh::FOLD;
+    const int in_bias = ((const int*)a.bias)[tid & 63];
+    unsigned char* const l_raw = l_fold + FW * Sh::FH * 16;
+    const unsigned raw0 = lds_addr(l_raw);
+    const int tpi = t.tiles_x * t.tiles_y;
+    struct Tile { int n, py0, px0; };
+    auto tile_at = [&](int u) {
+        const int n = (int)fast_div((unsigned)u, (unsigned)tpi, t.magic_tpi), r0 = u - n * tpi, tyi = (int)fast_div((unsigned)r0, (unsigned)t.tiles_x, t.magic_tx);
+        return Tile{n, TH * tyi, TW * (r0 - tyi * t.tiles_x)};
+    };
+    // folded pixel (fy, fx) of a tile is image rows 2 (2 py0 - 1 + fy) - pad and the next, columns likewise; its row's first byte may lie in front of the image
+    auto first_byte = [&](const Tile& tl) { return 3 * (4 * tl.px0 - 2 - im.pad); };
+    int srow[Sh::PASSES], scol[Sh::PASSES];                             // this lane's chunks of a staged tile: row, byte
+#pragma unroll
+    for (int i = 0; i < Sh::PASSES; ++i) {
+        const int q = min(256 * i + tid, Sh::CHUNKS - 1);
+        srow[i] = q / RC;
+        scol[i] = 16 * (q - srow[i] * RC);
+    }
+    auto stage = [&](const Tile& tl) {
+        const long long id = im.by_value ? tab[tl.n] : im.gather ? im.gather[tl.n] : tl.n;
+        const unsigned char* xn = (const unsigned char*)im.x + id * im.H * im.row_bytes;
+        const int y0 = 4 * tl.py0 - 2 - im.pad, b0 = first_byte(tl) & ~15;
+#pragma unroll
+        for (int i = 0; i < Sh::PASSES; ++i) {
+            if (256 * i + 64 * wave >= Sh::CHUNKS) break;
+            const int iy = y0 + srow[i], at = b0 + scol[i];
+            const bool ok = (unsigned)iy < (unsigned)im.H && (unsigned)at < (unsigned)im.row_bytes;
+            dma16(raw0 + i * 4096 + wave * 1024, ok ? xn + ((long long)iy * im.row_bytes + at) : (const unsigned char*)a.zeros);
+        }
+    };
+    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
+    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3);
+    Tile tl = tile_at(max(min(u, t.total - 1), 0));                     // (a workgroup without a tile asks for the XCD's last one)
+    stage(tl);
+    v4i_r wreg[NT][NKB];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) wreg[j][kb] = *(const v4i_r*)((const unsigned char*)a.wo + ((size_t)(j * (a.Kp / 32) + kb) * 64 + lane) * 16);
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < 64) l_bias[tid] = in_bias;
+    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
+    const int pch = tid & 3;
+    int pty[NST], ptx[NST], poff[NST];
+#pragma unroll
+    for (int i = 0; i < NST; ++i) {
+        const int pp = min(tid + 256 * i, ITEMS - 1) >> 2;
+        pty[i] = pp / TW; ptx[i] = pp - pty[i] * TW;
+        poff[i] = ((2 * pty[i]) * RW + 2 * ptx[i]) * 16 + pch * Sh::PLANE;
+    }
+    int spy[PER], spx[PER];                                             // this lane's output of its wavefront's strips
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int r = min(32 * (wave + 4 * k) + p, RPIX - 1);
+        spy[k] = r / RW; spx[k] = r - spy[k] * RW;
+    }
+    const auto y_buf = __builtin_amdgcn_make_buffer_rsrc(yq, (short)0, t.images * t.Hq * t.Wq * 64, 0x00020000);
+    auto read_strip = [&](int k, v4i_r* xr) {
+        const unsigned char* first = l_fold + (spy[k] * FW + spx[k] + hi) * 16;
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) xr[kb] = *(const v4i_r*)(first + (kb >> 1) * FW * 16 + (kb & 1) * 32);
+    };
+    auto compute_strip = [&](int k, const v4i_r* xr) {
+        const int r = 32 * (wave + 4 * k) + p;
+        const bool exists = (unsigned)(2 * tl.py0 - 1 + spy[k]) < (unsigned)a.Ho && (unsigned)(2 * tl.px0 - 1 + spx[k]) < (unsigned)a.Wo;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            v16i_r acc;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const v4i_r b4 = *(const v4i_r*)(l_bias + 32 * j + 8 * g + 4 * hi);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[4 * g + e] = b4[e];
+            }
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][kb], xr[kb], acc, 0, 0, 0);
+            v4i_r o = ir_requant_pack(acc, cl, relu);
+            if (!exists) o = v4i_r{(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
+            if (r < RPIX) *(v4i_r*)(stem_lds + (2 * j + hi) * Sh::PLANE + r * 16) = o;
+        }
+    };
+    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) asm volatile("" : "+v"(wreg[j][kb]));
+    wait_all_then_barrier<0>();
+    for (; u < u_end; u += u_step) {
+        {
+            const int skew = first_byte(tl) & 15;
+            const unsigned sh = (unsigned)(skew & 3) * 8;
+#pragma unroll
+            for (int i = 0; i < (Sh::PAIRS + 255) / 256; ++i) {
+                if (256 * i + 64 * wave >= Sh::PAIRS) break;
+                const int item = min(256 * i + tid, Sh::PAIRS - 1), fr = item / (FW / 2), pr = item - fr * (FW / 2);
+                unsigned px[2][4];                                      // [image row of the pair][pixel]: 3 channels and a zero byte
+#pragma unroll
+                for (int dy = 0; dy < 2; ++dy) {
+                    const unsigned* wp = (const unsigned*)(l_raw + (2 * fr + dy) * RC * 16 + (skew & ~3) + 12 * pr);
+                    const unsigned w0 = wp[0], w1 = wp[1], w2 = wp[2], w3 = wp[3];
+                    const unsigned d0 = __builtin_amdgcn_alignbit(w1, w0, sh), d1 = __builtin_amdgcn_alignbit(w2, w1, sh), d2 = __builtin_amdgcn_alignbit(w3, w2, sh);
+                    px[dy][0] = d0 & 0x00ffffffu;
+                    px[dy][1] = __builtin_amdgcn_perm(d1, d0, 0x0c050403u);         // bytes 3, 4, 5 of the twelve
+                    px[dy][2] = __builtin_amdgcn_perm(d2, d1, 0x0c040302u);         // bytes 6, 7, 8
+                    px[dy][3] = d2 >> 8;                                            // bytes 9, 10, 11
+                }
+                v4i_r* q = (v4i_r*)(l_fold + (fr * FW + 2 * pr) * 16);
+                q[0] = v4i_r{(int)px[0][0], (int)px[0][1], (int)px[1][0], (int)px[1][1]};
+                q[1] = v4i_r{(int)px[0][2], (int)px[0][3], (int)px[1][2], (int)px[1][3]};
+            }
+        }
+        lds_barrier();                                                  // the tile is folded, its image rows are free
+        const bool more = u + u_step < u_end;
+        const Tile tn = tile_at(more ? u + u_step : u);
+        stage(tn);                                                      // past the last tile: this tile's once more
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            v4i_r xs[NKB];
+            read_strip(k, xs);
+            compute_strip(k, xs);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_barrier();                                                  // the tile's convolution outputs are in LDS
+#pragma unroll
+        for (int i = 0; i < NST; ++i) {
+            const unsigned char* win = stem_lds + poff[i];
+            const v4i_r first = *(const v4i_r*)win;
+            StemMax mx[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) mx[d] = stem_split((unsigned)first[d]);
+#pragma unroll
+            for (int k = 1; k < 9; ++k) {
+                const v4i_r v = *(const v4i_r*)(win + ((k / 3) * RW + (k % 3)) * 16);
+#pragma unroll
+                for (int d = 0; d < 4; ++d) mx[d] = stem_max(mx[d], (unsigned)v[d]);
+            }
+            const int py = tl.py0 + pty[i], px = tl.px0 + ptx[i];
+            const bool ok = tid + 256 * i < ITEMS && py < t.Hq && px < t.Wq;
+            const unsigned at = ok ? (unsigned)(((tl.n * t.Hq + py) * t.Wq + px) * 64 + 16 * pch) : NOWHERE;
+            __builtin_amdgcn_raw_buffer_store_b128(v4i_r{(int)stem_join(mx[0]), (int)stem_join(mx[1]), (int)stem_join(mx[2]), (int)stem_join(mx[3])}, y_buf, at, 0, 0);
+        }
+        tl = tn;
+        wait_all_then_barrier<NST>();                                   // the next tile's image rows are there (NST stores behind them may not be), the tile's convolution outputs are free
+    }
+}
+template <int TW, int TH>
+__global__ __launch_bounds__(256, 3) void stem_pool_i8_kernel(StemIds<64>, ConvArgs a, void* yq, StemTile t, StemImage im)
+{
+    request_args<sizeof(StemIds<64>) + sizeof(ConvArgs) + sizeof(StemTile) + sizeof(StemImage)>();
+    stem_image<TW, TH>(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+template <int TW, int TH>
+__global__ __launch_bounds__(256, 3) void stem_pool_i8_kernel(StemIds<256>, ConvArgs a, void* yq, StemTile t, StemImage im)
+{
+    stem_image<TW, TH>(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // The bf16 form.  A super-pixel has 32 bytes and the reduction sixteen steps of one tap each, so a strip's operands are twice the bytes and
@@ -484,7 +687,7 @@ hipError_t launch_conv_pool(const ConvArgs& a, void* yq, int Hq, int Wq, int poo
 {
     if (!conv_pool_supported(a, 1, Hq, Wq, pool_pad)) return hipErrorInvalidValue;
     StemTile t;
-    t.Hq = Hq; t.Wq = Wq; t.pool_pad = pool_pad;
+    t.Hq = Hq; t.Wq = Wq; t.images = a.M / (a.Ho * a.Wo); t.pool_pad = pool_pad;
     t.tiles_x = (Wq + SB_TW - 1) / SB_TW;
     t.tiles_y = (Hq + SB_TH - 1) / SB_TH;
     const long long total = (long long)(a.M / (a.Ho * a.Wo)) * t.tiles_x * t.tiles_y;
@@ -507,27 +710,61 @@ bool stem_pool_supported(const ConvArgs& a, int es, int Hq, int Wq)
     return (double)(a.M / (a.Ho * a.Wo)) * a.H * a.W * 16 * es < 2147483648.0;
 }
 
+// A tile shape and what goes with it: small tiles where there is a CU for every one (int8)
+static bool stem_tiles(const ConvArgs& a, int es, int Hq, int Wq, StemTile& t, bool& small)
+{
+    t.Hq = Hq; t.Wq = Wq; t.pool_pad = 1;
+    t.images = a.M / (a.Ho * a.Wo);
+    auto tiles = [&](int tw, int th) {
+        t.tiles_x = (Wq + tw - 1) / tw;
+        t.tiles_y = (Hq + th - 1) / th;
+        return (long long)t.images * t.tiles_x * t.tiles_y;
+    };
+    small = es == 1 && tiles(ST_SMALL_TW, ST_SMALL_TH) <= 256;
+    const long long total = small ? tiles(ST_SMALL_TW, ST_SMALL_TH) : es == 1 ? tiles(ST_TW, ST_TH) : tiles(SB_TW, SB_TH);
+    if (total > 0x3fffffff) return false;
+    t.total = (int)total;
+    t.magic_tpi = stem_magic(t.tiles_x * t.tiles_y);
+    t.magic_tx = stem_magic(t.tiles_x);
+    return true;
+}
+// two workgroups on every CU (what matters is the CU's share, not the workgroup's); the loop takes the rest
+static unsigned stem_blocks(const StemTile& t, unsigned most = 512) { return t.total < (int)most ? xcd_grid(t.total) : most; }
+
 hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq, hipStream_t s)
 {
     if (!stem_pool_supported(a, es, Hq, Wq)) return hipErrorInvalidValue;
     StemTile t;
-    t.Hq = Hq; t.Wq = Wq; t.pool_pad = 1;
-    const long long images = a.M / (a.Ho * a.Wo);
-    auto tiles = [&](int tw, int th) {
-        t.tiles_x = (Wq + tw - 1) / tw;
-        t.tiles_y = (Hq + th - 1) / th;
-        return images * t.tiles_x * t.tiles_y;
+    bool small;
+    if (!stem_tiles(a, es, Hq, Wq, t, small)) return hipErrorInvalidValue;
+    using K = void (*)(ConvArgs, void*, StemTile);
+    const dim3 grid(stem_blocks(t));
+    if (es == 2) EE_LAUNCH(stem_pool_bf16_kernel, grid, dim3(256), SB_LDS, s, a, yq, t);
+    else if (small) EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>)), grid, dim3(256), (StemShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, a, yq, t);
+    else EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_TW, ST_TH>)), grid, dim3(256), (StemShape<ST_TW, ST_TH>::lds_bytes()), s, a, yq, t);
+    return hipGetLastError();
+}
+
+bool stem_image_supported(const void* x, int es, int W, int C) { return es == 1 && C == 3 && W * 3 % 16 == 0 && ((uintptr_t)x & 15) == 0; }
+
+hipError_t launch_stem_image(const ConvArgs& a, const void* x, const int32_t* ids, int H, int W, int pad, void* yq, int Hq, int Wq, hipStream_t s)
+{
+    if (!stem_pool_supported(a, 1, Hq, Wq) || !stem_image_supported(x, 1, W, 3)) return hipErrorInvalidValue;
+    StemTile t;
+    bool small;
+    if (!stem_tiles(a, 1, Hq, Wq, t, small)) return hipErrorInvalidValue;
+    const bool by_value = ids && t.images <= 256;
+    const StemImage im{x, by_value ? nullptr : ids, (int)by_value, H, 3 * W, pad};
+    const dim3 grid(stem_blocks(t, 768));
+    auto launch = [&](auto tab) {
+        using Tab = decltype(tab);
+        using K = void (*)(Tab, ConvArgs, void*, StemTile, StemImage);
+        if (by_value) std::memcpy(tab.id, ids, sizeof(int32_t) * (size_t)t.images);
+        if (small) EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>)), grid, dim3(256), (StemImageShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, tab, a, yq, t, im);
+        else EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_TW, ST_TH>)), grid, dim3(256), (StemImageShape<ST_TW, ST_TH>::lds_bytes()), s, tab, a, yq, t, im);
     };
-    const bool small = es == 1 && tiles(ST_SMALL_TW, ST_SMALL_TH) <= 256;
-    const long long total = small ? tiles(ST_SMALL_TW, ST_SMALL_TH) : es == 1 ? tiles(ST_TW, ST_TH) : tiles(SB_TW, SB_TH);
-    if (total > 0x3fffffff) return hipErrorInvalidValue;
-    t.total = (int)total;
-    t.magic_tpi = stem_magic(t.tiles_x * t.tiles_y);
-    t.magic_tx = stem_magic(t.tiles_x);
-    const unsigned blocks = total < 512 ? xcd_grid(total) : 512u;      // two workgroups on every CU (what matters is the CU's share, not the workgroup's); the loop takes the rest
-    if (es == 2) EE_LAUNCH(stem_pool_bf16_kernel, dim3(blocks), dim3(256), SB_LDS, s, a, yq, t);
-    else if (small) EE_LAUNCH((stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>), dim3(blocks), dim3(256), (StemShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, a, yq, t);
-    else EE_LAUNCH((stem_pool_i8_kernel<ST_TW, ST_TH>), dim3(blocks), dim3(256), (StemShape<ST_TW, ST_TH>::lds_bytes()), s, a, yq, t);
+    if (by_value && t.images > 64) launch(StemIds<256>{});
+    else launch(StemIds<64>{});
     return hipGetLastError();
 }
 
