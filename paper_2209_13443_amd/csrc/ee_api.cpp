@@ -1637,7 +1637,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
                 void* yq = resolve(this, q2.dst_buf, act_in, act_out);
                 const double mid = 2.0 * es * b * (double)d.h_out * d.w_out * d.c_out; // the tensor that stays on chip
                 e = timed(EE_K_CONV_STREAM, ops + q2.ops_per_sample * b, bytes + q2.bytes_per_sample * b + q2.weight_bytes - mid,
-                          [&] { return image ? launch_stem_image(ca, packed ? first_pool : src, packed ? first_ids : nullptr, d.h_in, d.w_in, d.pad, yq, q2.d.h_out, q2.d.w_out, stream) : folded ? launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream) : launch_conv_pool(ca, yq, q2.d.h_out, q2.d.w_out, q2.d.pad, stream); }, st.first_op + k);
+                          [&] { return image ? launch_stem_image(ca, es, packed ? first_pool : src, packed ? first_ids : nullptr, d.h_in, d.w_in, d.pad, yq, q2.d.h_out, q2.d.w_out, stream) : folded ? launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream) : launch_conv_pool(ca, yq, q2.d.h_out, q2.d.w_out, q2.d.pad, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
                 ++i;                                                             // the pool is done
                 continue;

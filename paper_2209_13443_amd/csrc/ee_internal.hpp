@@ -288,9 +288,9 @@ hipError_t launch_ir_block(const IrArgs& a, hipStream_t s);
 // kernel, a.y unused) and the 3x3 / 2 max-pool with padding 1 behind it in one launch; yq: the pooled output [B][Hq][Wq][64]
 bool stem_pool_supported(const ConvArgs& a, int es, int Hq, int Wq);
 hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq, hipStream_t s);
-// the same from int8 images of H x W x 3 at x (a.x unused), padded by `pad` in front, with no folded copy: sample n is image n, or ids[n] (host memory the device can read); x and its rows in whole 16-byte chunks
+// the same from images of H x W x 3 at x (a.x unused), padded by `pad` in front, with no folded copy: sample n is image n, or ids[n] (host memory the device can read); x and its rows in whole 16-byte chunks
 bool stem_image_supported(const void* x, int es, int W, int C);
-hipError_t launch_stem_image(const ConvArgs& a, const void* x, const int32_t* ids, int H, int W, int pad, void* yq, int Hq, int Wq, hipStream_t s);
+hipError_t launch_stem_image(const ConvArgs& a, int es, const void* x, const int32_t* ids, int H, int W, int pad, void* yq, int Hq, int Wq, hipStream_t s);
 // a 3x3 convolution from 32 to 64 channels and the 3x3 / 2 max-pool (padding 0 or 1) behind it in one launch (int8)
 bool conv_pool_supported(const ConvArgs& a, int es, int Hq, int Wq, int pool_pad);
 hipError_t launch_conv_pool(const ConvArgs& a, void* yq, int Hq, int Wq, int pool_pad, hipStream_t s);

@@ -222,16 +222,45 @@ struct StemImage {
 template <int N>
 struct StemIds { int32_t id[N]; };
 
+// Image rows into LDS, asynchronously: 16-byte chunks of rows of RC chunks, chunk q of the tile at 16 q.  The lane's chunks first (row, byte in the row), then for a tile whose first row is y0 and whose
+// rows begin at byte b0 (a multiple of 16, maybe in front of the image): zeros outside the image.  Whole copies of a wavefront.
+template <int RC, int CHUNKS>
+struct StemRows {
+    static constexpr int PASSES = (CHUNKS + 255) / 256, BYTES = (CHUNKS + 63) / 64 * 1024;
+    int row[PASSES], col[PASSES];
+    __device__ __forceinline__ explicit StemRows(int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            const int q = min(256 * i + tid, CHUNKS - 1);
+            row[i] = q / RC;
+            col[i] = 16 * (q - row[i] * RC);
+        }
+    }
+    __device__ __forceinline__ void request(const StemImage& im, const __attribute__((address_space(4))) int* tab, int n, int y0, int b0, unsigned lds, int wave, const void* zeros) const
+    {
+        const long long id = im.by_value ? tab[n] : im.gather ? im.gather[n] : n;
+        const unsigned char* xn = (const unsigned char*)im.x + id * im.H * im.row_bytes;
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            if (256 * i + 64 * wave >= CHUNKS) break;
+            const int iy = y0 + row[i], at = b0 + col[i];
+            const bool ok = (unsigned)iy < (unsigned)im.H && (unsigned)at < (unsigned)im.row_bytes;
+            dma16(lds + i * 4096 + wave * 1024, ok ? xn + ((long long)iy * im.row_bytes + at) : (const unsigned char*)zeros);
+        }
+    }
+};
+
 template <int TW, int TH>
 struct StemImageShape : StemShape<TW, TH> {
     using Base = StemShape<TW, TH>;
     static constexpr int FW = Base::RW + 3, FH = Base::RH + 3;          // folded pixels under a tile
-    static constexpr int RC = (15 + 6 * FW + 15) / 16, CHUNKS = 2 * FH * RC, PASSES = (CHUNKS + 255) / 256;    // 16-byte chunks of an image row, whatever its alignment
-    static constexpr int RAW = (CHUNKS + 63) / 64 * 1024;               // whole copies of a wavefront
+    static constexpr int RC = (15 + 6 * FW + 15) / 16, CHUNKS = 2 * FH * RC;   // 16-byte chunks of an image row, whatever its alignment
+    using Rows = StemRows<RC, CHUNKS>;
     static constexpr int PAIRS = FH * FW / 2;
     // the tile's convolution outputs in four planes of 16 channels: neighbouring pixels are written, and the four planes of a window read, without bank conflicts
     static constexpr int PLANE = (Base::RPIX * 16 - 64 + 255) / 256 * 256 + 64, FOLD = 4 * PLANE + 256;
-    static constexpr size_t lds_bytes() { return FOLD + FW * FH * 16 + RAW; }
+    static constexpr size_t lds_bytes() { return FOLD + FW * FH * 16 + Rows::BYTES; }
 };
 
 template <int TW, int TH>
@@ -257,25 +286,8 @@ __device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const St
     };
     // folded pixel (fy, fx) of a tile is image rows 2 (2 py0 - 1 + fy) - pad and the next, columns likewise; its row's first byte may lie in front of the image
     auto first_byte = [&](const Tile& tl) { return 3 * (4 * tl.px0 - 2 - im.pad); };
-    int srow[Sh::PASSES], scol[Sh::PASSES];                             // this lane's chunks of a staged tile: row, byte
-#pragma unroll
-    for (int i = 0; i < Sh::PASSES; ++i) {
-        const int q = min(256 * i + tid, Sh::CHUNKS - 1);
-        srow[i] = q / RC;
-        scol[i] = 16 * (q - srow[i] * RC);
-    }
-    auto stage = [&](const Tile& tl) {
-        const long long id = im.by_value ? tab[tl.n] : im.gather ? im.gather[tl.n] : tl.n;
-        const unsigned char* xn = (const unsigned char*)im.x + id * im.H * im.row_bytes;
-        const int y0 = 4 * tl.py0 - 2 - im.pad, b0 = first_byte(tl) & ~15;
-#pragma unroll
-        for (int i = 0; i < Sh::PASSES; ++i) {
-            if (256 * i + 64 * wave >= Sh::CHUNKS) break;
-            const int iy = y0 + srow[i], at = b0 + scol[i];
-            const bool ok = (unsigned)iy < (unsigned)im.H && (unsigned)at < (unsigned)im.row_bytes;
-            dma16(raw0 + i * 4096 + wave * 1024, ok ? xn + ((long long)iy * im.row_bytes + at) : (const unsigned char*)a.zeros);
-        }
-    };
+    const typename Sh::Rows rows(tid);
+    auto stage = [&](const Tile& tl) { rows.request(im, tab, tl.n, 4 * tl.py0 - 2 - im.pad, first_byte(tl) & ~15, raw0, wave, a.zeros); };
     const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
     int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3);
     Tile tl = tile_at(max(min(u, t.total - 1), 0));                     // (a workgroup without a tile asks for the XCD's last one)
@@ -310,7 +322,6 @@ __device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const St
         for (int kb = 0; kb < NKB; ++kb) xr[kb] = *(const v4i_r*)(first + (kb >> 1) * FW * 16 + (kb & 1) * 32);
     };
     auto compute_strip = [&](int k, const v4i_r* xr) {
-        const int r = 32 * (wave + 4 * k) + p;
         const bool exists = (unsigned)(2 * tl.py0 - 1 + spy[k]) < (unsigned)a.Ho && (unsigned)(2 * tl.px0 - 1 + spx[k]) < (unsigned)a.Wo;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
@@ -325,7 +336,7 @@ __device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const St
             for (int kb = 0; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][kb], xr[kb], acc, 0, 0, 0);
             v4i_r o = ir_requant_pack(acc, cl, relu);
             if (!exists) o = v4i_r{(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
-            if (r < RPIX) *(v4i_r*)(stem_lds + (2 * j + hi) * Sh::PLANE + r * 16) = o;
+            *(v4i_r*)(stem_lds + (2 * j + hi) * Sh::PLANE + (spy[k] * RW + spx[k]) * 16) = o;       // (lanes past the last output hold and write the last one)
         }
     };
     // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
@@ -546,6 +557,157 @@ __global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void
     }
 }
 
+// The bf16 form straight from the images, as the int8 one: half a super-pixel, two pixels of an image row, is 12 contiguous bytes.  The biases are read behind a strip's last operands, all four
+// ahead of their use (each waited for by itself they took some 1000 clocks of a strip).  224 x 224, us, the folded copy and the kernel above / this one, both with the time between launches and the 1x1
+// layer behind: 1 sample 14.2 / 10.3, 5 16.9 / 11.3, 64 54.5 / 43.7, 256 192 / 143; by itself, 256 samples 112.6 / 117.2, and the copy was 52.
+constexpr int SI_RC = (15 + 12 * SB_SW + 15) / 16, SI_FOLD = SB_CHUNKS * 16;                // 16-byte chunks of an image row under a tile, whatever its alignment
+using SiRows = StemRows<SI_RC, 2 * SB_SH * SI_RC>;
+constexpr int SI_LDS = SI_FOLD + SiRows::BYTES + SB_RPIX * SB_PITCH + 256;
+static_assert(2 * SI_LDS <= 160 * 1024, "two workgroups per CU");
+
+__device__ __forceinline__ void stem_image_bf16(const ConvArgs& a, void* yq, const StemTile& t, const StemImage& im, const __attribute__((address_space(4))) int* tab)
+{
+    constexpr int NK = 16;                                              // taps = reduction steps of 16 channels
+    extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned char* const l_fold = stem_lds;
+    unsigned char* const l_raw = stem_lds + SI_FOLD;
+    unsigned char* const l_conv = l_raw + SiRows::BYTES;
+    constexpr unsigned NOWHERE = 0x80000000u;                           // an offset past the output: the store is dropped
+    float* const l_bias = (float*)(l_conv + SB_RPIX * SB_PITCH);
+    const float in_bias = ((const float*)a.bias)[tid & 63];
+    v4i wreg[2][NK];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < NK; ++k) wreg[j][k] = *(const v4i*)((const unsigned char*)a.wo + ((size_t)(j * (a.Kp / 16) + k) * 64 + lane) * 16);
+    __builtin_amdgcn_sched_barrier(0);
+    const SiRows rows(tid);
+    // pooling: this lane's items (pooled pixel, channels): tid and tid + 256
+    int pty[2], ptx[2], poff[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int pp = min(tid + 256 * i, SB_ITEMS - 1) >> 3;
+        pty[i] = pp / SB_TW; ptx[i] = pp - pty[i] * SB_TW;
+        poff[i] = (2 * pty[i] * SB_RW + 2 * ptx[i]) * SB_PITCH + 16 * (tid & 7);
+    }
+    const int tpi = t.tiles_x * t.tiles_y;
+    struct Tile { int n, py0, px0; };
+    auto tile_at = [&](int u) {
+        const int n = (int)fast_div((unsigned)u, (unsigned)tpi, t.magic_tpi), r0 = u - n * tpi, tyi = (int)fast_div((unsigned)r0, (unsigned)t.tiles_x, t.magic_tx);
+        return Tile{n, SB_TH * tyi, SB_TW * (r0 - tyi * t.tiles_x)};
+    };
+    // folded pixel (fy, fx) of a tile is image rows 2 (2 py0 - 1 + fy) - pad and the next, columns likewise; its row's first byte may lie in front of the image
+    auto first_byte = [&](const Tile& tl) { return 6 * (4 * tl.px0 - 2 - im.pad); };
+    const unsigned raw0 = lds_addr(l_raw);
+    auto stage = [&](const Tile& tl) { rows.request(im, tab, tl.n, 4 * tl.py0 - 2 - im.pad, first_byte(tl) & ~15, raw0, wave, a.zeros); };
+    const auto y_buf = __builtin_amdgcn_make_buffer_rsrc(yq, (short)0, t.images * t.Hq * t.Wq * 128, 0x00020000);
+    // this XCD's tiles, shared by its workgroups; the same trip count for the whole workgroup
+    const int u_end = xcd_first((int)(blockIdx.x & 7) + 1, t.total), u_step = (int)(gridDim.x >> 3);
+    int u = xcd_first((int)(blockIdx.x & 7), t.total) + (int)(blockIdx.x >> 3);
+    Tile tl = tile_at(max(min(u, t.total - 1), 0));                     // (a workgroup without a tile asks for the XCD's last one)
+    stage(tl);                                                          // on its way with the weights
+    if (tid < 64) l_bias[tid] = in_bias;
+    // every weight has arrived before the loop, so that nothing inside it waits for a weight by count
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(wreg[j][k]));
+    wait_all_then_barrier<0>();
+    for (; u < u_end; u += u_step) {
+        {                                                               // a 16-byte half of a super-pixel (an image row's two pixels) per item
+            const int skew = first_byte(tl) & 15;
+            const unsigned sh = (unsigned)(skew & 3) * 8;
+#pragma unroll
+            for (int i = 0; i < (SB_CHUNKS + 255) / 256; ++i) {
+                if (256 * i + 64 * wave >= SB_CHUNKS) break;
+                const int item = min(256 * i + tid, SB_CHUNKS - 1), fy = item / (2 * SB_SW), c = item - fy * 2 * SB_SW;
+                const unsigned* wp = (const unsigned*)(l_raw + (2 * fy + (c & 1)) * SI_RC * 16 + (skew & ~3) + 12 * (c >> 1));
+                const unsigned w0 = wp[0], w1 = wp[1], w2 = wp[2], w3 = wp[3];
+                const unsigned d0 = __builtin_amdgcn_alignbit(w1, w0, sh), d1 = __builtin_amdgcn_alignbit(w2, w1, sh), d2 = __builtin_amdgcn_alignbit(w3, w2, sh);
+                *(v4i*)(l_fold + item * 16) = v4i{(int)d0, (int)(d1 & 0xffffu), (int)__builtin_amdgcn_alignbit(d2, d1, 16), (int)(d2 >> 16)};
+            }
+        }
+        lds_barrier();                                                  // the tile is folded, its image rows are free
+        const bool more = u + u_step < u_end;
+        const Tile tn = tile_at(more ? u + u_step : u);
+        stage(tn);                                                      // past the last tile: this tile's once more
+        const unsigned char* xl = l_fold + 16 * hi;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int r = 32 * (wave + 4 * s) + p, rc = min(r, SB_RPIX - 1), ry = rc / SB_RW, rx = rc - ry * SB_RW;
+            const bool exists = (unsigned)(2 * tl.py0 - 1 + ry) < (unsigned)a.Ho && (unsigned)(2 * tl.px0 - 1 + rx) < (unsigned)a.Wo;
+            const unsigned char* px = xl + (ry * SB_SW + rx) * 32;
+            v16f acc[2];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
+            // the operands in batches of four through two sets of registers, a batch ahead of its matrix instructions
+            v4i xs[2][4];
+            auto read = [&](int k0, v4i* x) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = *(const v4i*)(px + ((k0 >> 2) * SB_SW + k) * 32);
+            };
+            auto read_bias = [&](int j, v4i* b4) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) b4[g] = *(const v4i*)(l_bias + 32 * j + 8 * g + 4 * hi);
+            };
+            v4i bias[2][4];
+            read(0, xs[0]);
+#pragma unroll
+            for (int k0 = 0; k0 < NK; k0 += 4) {
+                if (k0 + 4 < NK) read(k0 + 4, xs[(k0 >> 2 & 1) ^ 1]);
+                else read_bias(0, bias[0]);                             // behind the last operands, in the registers they leave
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, wreg[j][k0 + k]), __builtin_bit_cast(v8bf, xs[k0 >> 2 & 1][k]), acc[j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            read_bias(1, bias[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            unsigned char* cell = l_conv + rc * SB_PITCH + 8 * hi;      // (the lane past the last output holds and writes the last one)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = clamp_f32(acc[j][4 * g + e] + __int_as_float(bias[j][g][e]), a.f_lo, a.f_hi);
+                    uint2 o = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+                    if (!exists) o = uint2{0u, 0u};
+                    *(uint2*)(cell + 64 * j + 16 * g) = o;
+                }
+        }
+        lds_barrier();                                                  // the tile's convolution outputs are in LDS
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            typedef short v8s __attribute__((ext_vector_type(8)));
+            const unsigned char* win = l_conv + poff[i];
+            v8s mx = *(const v8s*)win;
+#pragma unroll
+            for (int k = 1; k < 9; ++k) mx = __builtin_elementwise_max(mx, *(const v8s*)(win + ((k / 3) * SB_RW + (k % 3)) * SB_PITCH));
+            const int py = tl.py0 + pty[i], px = tl.px0 + ptx[i];
+            const bool ok = tid + 256 * i < SB_ITEMS && py < t.Hq && px < t.Wq;
+            const unsigned at = ok ? (unsigned)(((tl.n * t.Hq + py) * t.Wq + px) * 128 + 16 * (tid & 7)) : NOWHERE;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, mx), y_buf, at, 0, 0);
+        }
+        tl = tn;
+        wait_all_then_barrier<2>();                                     // the next tile's image rows are there (two stores behind them may not be), the tile's convolution outputs are free
+    }
+}
+__global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(StemIds<64>, ConvArgs a, void* yq, StemTile t, StemImage im)
+{
+    request_args<sizeof(StemIds<64>) + sizeof(ConvArgs) + sizeof(StemTile) + sizeof(StemImage)>();
+    stem_image_bf16(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+__global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(StemIds<256>, ConvArgs a, void* yq, StemTile t, StemImage im)
+{
+    stem_image_bf16(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+
 // ---- a 3x3 convolution over 32 channels and the 3x3 / 2 max-pool behind it (int8, 64 output channels) ------------------------
 // What Inception-style stems have behind their first layers.  A pixel has 32 bytes, one reduction step per tap: the bf16 kernel's tile and staging with
 // nine taps, and zeros staged outside the image where the convolution pads; operands, requantisation and pool as in the first-layer kernel.
@@ -739,28 +901,29 @@ hipError_t launch_stem_pool(const ConvArgs& a, int es, void* yq, int Hq, int Wq,
     if (!stem_tiles(a, es, Hq, Wq, t, small)) return hipErrorInvalidValue;
     using K = void (*)(ConvArgs, void*, StemTile);
     const dim3 grid(stem_blocks(t));
-    if (es == 2) EE_LAUNCH(stem_pool_bf16_kernel, grid, dim3(256), SB_LDS, s, a, yq, t);
+    if (es == 2) EE_LAUNCH(static_cast<K>(stem_pool_bf16_kernel), grid, dim3(256), SB_LDS, s, a, yq, t);
     else if (small) EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>)), grid, dim3(256), (StemShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, a, yq, t);
     else EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_TW, ST_TH>)), grid, dim3(256), (StemShape<ST_TW, ST_TH>::lds_bytes()), s, a, yq, t);
     return hipGetLastError();
 }
 
-bool stem_image_supported(const void* x, int es, int W, int C) { return es == 1 && C == 3 && W * 3 % 16 == 0 && ((uintptr_t)x & 15) == 0; }
+bool stem_image_supported(const void* x, int es, int W, int C) { return C == 3 && W * 3 * es % 16 == 0 && ((uintptr_t)x & 15) == 0; }
 
-hipError_t launch_stem_image(const ConvArgs& a, const void* x, const int32_t* ids, int H, int W, int pad, void* yq, int Hq, int Wq, hipStream_t s)
+hipError_t launch_stem_image(const ConvArgs& a, int es, const void* x, const int32_t* ids, int H, int W, int pad, void* yq, int Hq, int Wq, hipStream_t s)
 {
-    if (!stem_pool_supported(a, 1, Hq, Wq) || !stem_image_supported(x, 1, W, 3)) return hipErrorInvalidValue;
+    if (!stem_pool_supported(a, es, Hq, Wq) || !stem_image_supported(x, es, W, 3)) return hipErrorInvalidValue;
     StemTile t;
     bool small;
-    if (!stem_tiles(a, 1, Hq, Wq, t, small)) return hipErrorInvalidValue;
+    if (!stem_tiles(a, es, Hq, Wq, t, small)) return hipErrorInvalidValue;
     const bool by_value = ids && t.images <= 256;
-    const StemImage im{x, by_value ? nullptr : ids, (int)by_value, H, 3 * W, pad};
-    const dim3 grid(stem_blocks(t, 768));
+    const StemImage im{x, by_value ? nullptr : ids, (int)by_value, H, 3 * W * es, pad};
+    const dim3 grid(stem_blocks(t, es == 2 ? 512 : 768));
     auto launch = [&](auto tab) {
         using Tab = decltype(tab);
         using K = void (*)(Tab, ConvArgs, void*, StemTile, StemImage);
         if (by_value) std::memcpy(tab.id, ids, sizeof(int32_t) * (size_t)t.images);
-        if (small) EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>)), grid, dim3(256), (StemImageShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, tab, a, yq, t, im);
+        if (es == 2) EE_LAUNCH(static_cast<K>(stem_pool_bf16_kernel), grid, dim3(256), SI_LDS, s, tab, a, yq, t, im);
+        else if (small) EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>)), grid, dim3(256), (StemImageShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, tab, a, yq, t, im);
         else EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_TW, ST_TH>)), grid, dim3(256), (StemImageShape<ST_TW, ST_TH>::lds_bytes()), s, tab, a, yq, t, im);
     };
     if (by_value && t.images > 64) launch(StemIds<256>{});
