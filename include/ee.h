@@ -210,8 +210,8 @@ typedef struct { int64_t launches; double ms; double ops; double bytes; } ee_ker
  * NULL, per layer of the network into per_layer[number of layers] (host), then resets the counters.
  * ops = 2 * MACs of the launches, bytes = their algorithmic HBM traffic (each operand once).
  * A launch is booked whole under one class and one layer, also where it runs several layers: joint launches, fused pairs and fused blocks under their
- * first layer and EE_K_CONV_MFMA (the fused first convolution + max-pool: EE_K_CONV_STREAM, on images whose rows
- * are whole 16-byte chunks with EE_K_PAD_INPUT and in the stream EE_K_ADMIT in it); a small segment that runs as one launch (see ee_ir_count) under its
+ * first layer and EE_K_CONV_MFMA (the fused first convolution + max-pool: EE_K_CONV_STREAM);
+ * a first layer that reads the images itself (fused with its max-pool, or 3x3 / 2 int8, over 3 channels) has EE_K_PAD_INPUT and in the stream EE_K_ADMIT in its launch; a small segment that runs as one launch (see ee_ir_count) under its
  * first layer and EE_K_CONV_MFMA, in the stream with its admission and exit head, so that EE_K_ADMIT, EE_K_GAP, EE_K_FC, EE_K_SOFTMAX and the segment's other
  * layers then read zero.  ops are those of all the layers, bytes leave out what stays on chip.  ee_ir_mode 0 (with ee_pair_mode 0 and joint tables of zeros)
  * gives every layer and class launches, and figures, of its own. */

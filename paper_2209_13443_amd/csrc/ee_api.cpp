@@ -1585,8 +1585,11 @@ bool ee_ctx::first_reads_images(int b, const void* x) const
 {
     const int op = net.stages[0].first_op;
     const OpPlan& p = plans[(size_t)op];
-    return p.ir && p.ir_stem && p.impl == IMPL_MFMA_S2D && p.src_buf == BUF_EXT_IN && forced_conv_tile() == 0 && op + 1 != gap_fuse_op[0] && ir_wanted(op, b) &&
-           stem_image_supported(x, net.elem_bytes(), p.d.w_in, p.d.c_in);
+    if (p.impl != IMPL_MFMA_S2D || p.src_buf != BUF_EXT_IN || p.dst_buf == BUF_EXT_OUT || ir_mode == 0 || forced_conv_tile() != 0) return false;
+    if (p.ir && p.ir_stem && ir_wanted(op, b)) return op + 1 != gap_fuse_op[0] && stem_image_supported(x, net.elem_bytes(), p.d.w_in, p.d.c_in);
+    ConvArgs a{};
+    fill_conv_args(op, b, a);
+    return conv_stream_image_supported(a, net.elem_bytes(), x, p.d.h_in, p.d.w_in, p.d.c_in, p.d.pad);
 }
 
 int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool first_packed, int only_op, int cfg_force)
@@ -1687,6 +1690,15 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             }
         }
         if (p.impl == IMPL_MFMA || p.impl == IMPL_MFMA_C4 || p.impl == IMPL_MFMA_CPAD || p.impl == IMPL_MFMA_S2D) {
+            if (p.impl == IMPL_MFMA_S2D && stage == 0 && k == 0 && only_op < 0 && cfg_force == 0 && first_reads_images(b, first_packed ? first_pool : src)) {
+                // whatever the layer's table says: that is about launches that read the folded copy
+                ConvArgs ca{};
+                fill_conv_args(st.first_op, b, ca);
+                ca.y = dst;
+                e = timed(EE_K_CONV_STREAM, ops, bytes, [&] { return launch_conv_stream_image(ca, first_packed ? first_pool : src, first_packed ? first_ids : nullptr, d.h_in, d.w_in, d.pad, stream); }, st.first_op);
+                if (e != hipSuccess) return EE_ERR_DEVICE;
+                continue;
+            }
             if (p.impl == IMPL_MFMA_S2D && !(first_packed && k == 0)) {
                 const double pb = (double)b * ((double)d.h_in * d.w_in * d.c_in + (double)p.Hp * p.Wp * 16) * es;
                 e = timed(EE_K_PAD_INPUT, 0.0, pb, [&] { return launch_space_to_depth(src, pad_bufs[p.pad_buf], nullptr, b, d.h_in, d.w_in, d.c_in, p.Hp, p.Wp, d.pad, dt, stream); });

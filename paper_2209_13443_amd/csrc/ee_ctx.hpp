@@ -158,7 +158,7 @@ struct ee_ctx {
             if (plans[st.first_op + k].src_buf == ee::BUF_EXT_IN || plans[st.first_op + k].res_buf == ee::BUF_EXT_IN) return nullptr;
         return &p;
     }
-    // whether b samples of segment 0 at x are read by the launch of its first layer and pool itself: nothing is folded in front of it, and admission has nothing to do
+    // whether b samples of segment 0 at x are read by the launch of its first layer (and pool) itself: nothing is folded in front of it, and admission has nothing to do (never with ir_mode 0)
     bool first_reads_images(int b, const void* x) const;
     const void* first_pool = nullptr;       // with first_packed: where the requests are
     const int32_t* first_ids = nullptr;     // pinned

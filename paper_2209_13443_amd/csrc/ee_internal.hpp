@@ -257,6 +257,9 @@ enum { EE_CFG_IR_BLOCK = 0x20000 }; // ee_time_layer: the fused inverted-residua
 // streaming kernel for large, thin int8 layers (es = element bytes); hipErrorInvalidValue for a layer it does not cover
 bool conv_stream_supported(const ConvArgs& a, int es);
 hipError_t launch_conv_stream(const ConvArgs& a, hipStream_t s);
+// the folded stride-2 first layer of 2 x 2 taps (a as for the folded copy, a.x unused) from int8 images of H x W x 3 at x with no folded copy: sample n is image n, or ids[n] (host memory the device can read)
+bool conv_stream_image_supported(const ConvArgs& a, int es, const void* x, int H, int W, int C, int pad);
+hipError_t launch_conv_stream_image(const ConvArgs& a, const void* x, const int32_t* ids, int H, int W, int pad, hipStream_t s);
 // 1x1 int8 layers with at most 32 input channels: activations and weights straight from global memory into one
 // matrix instruction per 32 x 32 outputs (w: packed rows of 32 bytes, zero padded; bias with the rounding constant)
 struct ThinConvArgs {

@@ -19,6 +19,63 @@
 
 namespace ee {
 
+// ---- images read by the first layers themselves: where they are, their rows into LDS, four pixels of three channels as two super-pixels' rows ----------
+// sample n is image n of x or, for requests of a stream, image ids[n] of the pool x: ids by value in front of a kernel's arguments (ImageIds), else read from device-visible memory
+struct ImageArgs {
+    const void* x;
+    const int32_t* gather;      // ids that do not fit the arguments, else null
+    int by_value;               // the table in front of the arguments holds the ids
+    int H, row_bytes, pad;      // image rows, bytes of a row, padding of the convolution
+};
+template <int N>
+struct ImageIds { int32_t id[N]; };
+typedef const __attribute__((address_space(4))) int* ImageTab;          // the arguments, which begin with that table
+__device__ __forceinline__ const unsigned char* image_at(const ImageArgs& im, ImageTab tab, int n)
+{
+    const long long id = im.by_value ? tab[n] : im.gather ? im.gather[n] : n;
+    return (const unsigned char*)im.x + id * im.H * im.row_bytes;
+}
+
+// Image rows into LDS, asynchronously: 16-byte chunks of rows of RC chunks, chunk q of the tile at 16 q.  The lane's chunks first (row, byte in the row), then for a tile whose first row is y0 and whose
+// rows begin at byte b0 (a multiple of 16, maybe in front of the image): zeros outside the image.  Whole copies of a wavefront.
+template <int RC, int CHUNKS>
+struct ImageRows {
+    static constexpr int PASSES = (CHUNKS + 255) / 256, BYTES = (CHUNKS + 63) / 64 * 1024;
+    int row[PASSES], col[PASSES];
+    __device__ __forceinline__ explicit ImageRows(int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            const int q = min(256 * i + tid, CHUNKS - 1);
+            row[i] = q / RC;
+            col[i] = 16 * (q - row[i] * RC);
+        }
+    }
+    __device__ __forceinline__ void request(const ImageArgs& im, ImageTab tab, int n, int y0, int b0, unsigned lds, int wave, const void* zeros) const
+    {
+        const unsigned char* xn = image_at(im, tab, n);
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            if (256 * i + 64 * wave >= CHUNKS) break;
+            const int iy = y0 + row[i], at = b0 + col[i];
+            const bool ok = (unsigned)iy < (unsigned)im.H && (unsigned)at < (unsigned)im.row_bytes;
+            dma16(lds + i * 4096 + wave * 1024, ok ? xn + ((long long)iy * im.row_bytes + at) : (const unsigned char*)zeros);
+        }
+    }
+};
+
+// Four int8 pixels of three channels, 12 contiguous bytes from byte `at` of LDS memory p, as four dwords around them shifted into place: 3 channels and a zero byte each
+__device__ __forceinline__ void image_pixels(const unsigned char* p, int at, unsigned* px)
+{
+    const unsigned* wp = (const unsigned*)(p + (at & ~3));
+    const unsigned w0 = wp[0], w1 = wp[1], w2 = wp[2], w3 = wp[3], sh = (unsigned)(at & 3) * 8;
+    const unsigned d0 = __builtin_amdgcn_alignbit(w1, w0, sh), d1 = __builtin_amdgcn_alignbit(w2, w1, sh), d2 = __builtin_amdgcn_alignbit(w3, w2, sh);
+    px[0] = d0 & 0x00ffffffu;
+    px[1] = __builtin_amdgcn_perm(d1, d0, 0x0c050403u);                 // bytes 3, 4, 5 of the twelve
+    px[2] = __builtin_amdgcn_perm(d2, d1, 0x0c040302u);                 // bytes 6, 7, 8
+    px[3] = d2 >> 8;                                                    // bytes 9, 10, 11
+}
+
 typedef short v2s_r __attribute__((ext_vector_type(2)));
 
 struct StemTile {
@@ -213,50 +270,12 @@ __global__ __launch_bounds__(256, 2) void stem_pool_i8_kernel(ConvArgs a, void* 
 // Three workgroups share a CU (51 KB of LDS, 163 registers).  What bounds it: vector issue, as above, some 630 instructions per wavefront and tile, and 64 matrix instructions, which overlap in part.
 // 224 x 224, us, the folded copy and the kernel above / this one, both with the time between launches: 1 sample 13.0 / 10.0 (of which the 1x1 layer behind them 4), 24 19.5 / 15.0, 64 34.2 / 26.5,
 // 256 104 / 83; by itself, 64 samples 20.2 / 20.8, 256 70.1 / 63.5 (with two workgroups per CU 66.8).
-struct StemImage {
-    const void* x;              // images or (ids) the pool
-    const int32_t* gather;      // more than 256 ids: device-visible memory, else null
-    int by_value;               // the table in front of the arguments holds the ids
-    int H, row_bytes, pad;      // image rows, bytes of a row, padding of the convolution
-};
-template <int N>
-struct StemIds { int32_t id[N]; };
-
-// Image rows into LDS, asynchronously: 16-byte chunks of rows of RC chunks, chunk q of the tile at 16 q.  The lane's chunks first (row, byte in the row), then for a tile whose first row is y0 and whose
-// rows begin at byte b0 (a multiple of 16, maybe in front of the image): zeros outside the image.  Whole copies of a wavefront.
-template <int RC, int CHUNKS>
-struct StemRows {
-    static constexpr int PASSES = (CHUNKS + 255) / 256, BYTES = (CHUNKS + 63) / 64 * 1024;
-    int row[PASSES], col[PASSES];
-    __device__ __forceinline__ explicit StemRows(int tid)
-    {
-#pragma unroll
-        for (int i = 0; i < PASSES; ++i) {
-            const int q = min(256 * i + tid, CHUNKS - 1);
-            row[i] = q / RC;
-            col[i] = 16 * (q - row[i] * RC);
-        }
-    }
-    __device__ __forceinline__ void request(const StemImage& im, const __attribute__((address_space(4))) int* tab, int n, int y0, int b0, unsigned lds, int wave, const void* zeros) const
-    {
-        const long long id = im.by_value ? tab[n] : im.gather ? im.gather[n] : n;
-        const unsigned char* xn = (const unsigned char*)im.x + id * im.H * im.row_bytes;
-#pragma unroll
-        for (int i = 0; i < PASSES; ++i) {
-            if (256 * i + 64 * wave >= CHUNKS) break;
-            const int iy = y0 + row[i], at = b0 + col[i];
-            const bool ok = (unsigned)iy < (unsigned)im.H && (unsigned)at < (unsigned)im.row_bytes;
-            dma16(lds + i * 4096 + wave * 1024, ok ? xn + ((long long)iy * im.row_bytes + at) : (const unsigned char*)zeros);
-        }
-    }
-};
-
 template <int TW, int TH>
 struct StemImageShape : StemShape<TW, TH> {
     using Base = StemShape<TW, TH>;
     static constexpr int FW = Base::RW + 3, FH = Base::RH + 3;          // folded pixels under a tile
     static constexpr int RC = (15 + 6 * FW + 15) / 16, CHUNKS = 2 * FH * RC;   // 16-byte chunks of an image row, whatever its alignment
-    using Rows = StemRows<RC, CHUNKS>;
+    using Rows = ImageRows<RC, CHUNKS>;
     static constexpr int PAIRS = FH * FW / 2;
     // the tile's convolution outputs in four planes of 16 channels: neighbouring pixels are written, and the four planes of a window read, without bank conflicts
     static constexpr int PLANE = (Base::RPIX * 16 - 64 + 255) / 256 * 256 + 64, FOLD = 4 * PLANE + 256;
@@ -264,7 +283,7 @@ struct StemImageShape : StemShape<TW, TH> {
 };
 
 template <int TW, int TH>
-__device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const StemTile& t, const StemImage& im, const __attribute__((address_space(4))) int* tab)
+__device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const StemTile& t, const ImageArgs& im, ImageTab tab)
 {
     using Sh = StemImageShape<TW, TH>;
     constexpr int RW = Sh::RW, RPIX = Sh::RPIX, ITEMS = Sh::ITEMS, PER = Sh::PER, FW = Sh::FW, RC = Sh::RC;
@@ -348,22 +367,13 @@ __device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const St
     for (; u < u_end; u += u_step) {
         {
             const int skew = first_byte(tl) & 15;
-            const unsigned sh = (unsigned)(skew & 3) * 8;
 #pragma unroll
             for (int i = 0; i < (Sh::PAIRS + 255) / 256; ++i) {
                 if (256 * i + 64 * wave >= Sh::PAIRS) break;
                 const int item = min(256 * i + tid, Sh::PAIRS - 1), fr = item / (FW / 2), pr = item - fr * (FW / 2);
-                unsigned px[2][4];                                      // [image row of the pair][pixel]: 3 channels and a zero byte
+                unsigned px[2][4];                                      // [image row of the pair][pixel]
 #pragma unroll
-                for (int dy = 0; dy < 2; ++dy) {
-                    const unsigned* wp = (const unsigned*)(l_raw + (2 * fr + dy) * RC * 16 + (skew & ~3) + 12 * pr);
-                    const unsigned w0 = wp[0], w1 = wp[1], w2 = wp[2], w3 = wp[3];
-                    const unsigned d0 = __builtin_amdgcn_alignbit(w1, w0, sh), d1 = __builtin_amdgcn_alignbit(w2, w1, sh), d2 = __builtin_amdgcn_alignbit(w3, w2, sh);
-                    px[dy][0] = d0 & 0x00ffffffu;
-                    px[dy][1] = __builtin_amdgcn_perm(d1, d0, 0x0c050403u);         // bytes 3, 4, 5 of the twelve
-                    px[dy][2] = __builtin_amdgcn_perm(d2, d1, 0x0c040302u);         // bytes 6, 7, 8
-                    px[dy][3] = d2 >> 8;                                            // bytes 9, 10, 11
-                }
+                for (int dy = 0; dy < 2; ++dy) image_pixels(l_raw, (2 * fr + dy) * RC * 16 + skew + 12 * pr, px[dy]);
                 v4i_r* q = (v4i_r*)(l_fold + (fr * FW + 2 * pr) * 16);
                 q[0] = v4i_r{(int)px[0][0], (int)px[0][1], (int)px[1][0], (int)px[1][1]};
                 q[1] = v4i_r{(int)px[0][2], (int)px[0][3], (int)px[1][2], (int)px[1][3]};
@@ -405,15 +415,15 @@ __device__ __forceinline__ void stem_image(const ConvArgs& a, void* yq, const St
     }
 }
 template <int TW, int TH>
-__global__ __launch_bounds__(256, 3) void stem_pool_i8_kernel(StemIds<64>, ConvArgs a, void* yq, StemTile t, StemImage im)
+__global__ __launch_bounds__(256, 3) void stem_pool_i8_kernel(ImageIds<64>, ConvArgs a, void* yq, StemTile t, ImageArgs im)
 {
-    request_args<sizeof(StemIds<64>) + sizeof(ConvArgs) + sizeof(StemTile) + sizeof(StemImage)>();
-    stem_image<TW, TH>(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
+    request_args<sizeof(ImageIds<64>) + sizeof(ConvArgs) + sizeof(StemTile) + sizeof(ImageArgs)>();
+    stem_image<TW, TH>(a, yq, t, im, (ImageTab)__builtin_amdgcn_kernarg_segment_ptr());
 }
 template <int TW, int TH>
-__global__ __launch_bounds__(256, 3) void stem_pool_i8_kernel(StemIds<256>, ConvArgs a, void* yq, StemTile t, StemImage im)
+__global__ __launch_bounds__(256, 3) void stem_pool_i8_kernel(ImageIds<256>, ConvArgs a, void* yq, StemTile t, ImageArgs im)
 {
-    stem_image<TW, TH>(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
+    stem_image<TW, TH>(a, yq, t, im, (ImageTab)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // The bf16 form.  A super-pixel has 32 bytes and the reduction sixteen steps of one tap each, so a strip's operands are twice the bytes and
@@ -561,11 +571,11 @@ __global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ConvArgs a, void
 // ahead of their use (each waited for by itself they took some 1000 clocks of a strip).  224 x 224, us, the folded copy and the kernel above / this one, both with the time between launches and the 1x1
 // layer behind: 1 sample 14.2 / 10.3, 5 16.9 / 11.3, 64 54.5 / 43.7, 256 192 / 143; by itself, 256 samples 112.6 / 117.2, and the copy was 52.
 constexpr int SI_RC = (15 + 12 * SB_SW + 15) / 16, SI_FOLD = SB_CHUNKS * 16;                // 16-byte chunks of an image row under a tile, whatever its alignment
-using SiRows = StemRows<SI_RC, 2 * SB_SH * SI_RC>;
+using SiRows = ImageRows<SI_RC, 2 * SB_SH * SI_RC>;
 constexpr int SI_LDS = SI_FOLD + SiRows::BYTES + SB_RPIX * SB_PITCH + 256;
 static_assert(2 * SI_LDS <= 160 * 1024, "two workgroups per CU");
 
-__device__ __forceinline__ void stem_image_bf16(const ConvArgs& a, void* yq, const StemTile& t, const StemImage& im, const __attribute__((address_space(4))) int* tab)
+__device__ __forceinline__ void stem_image_bf16(const ConvArgs& a, void* yq, const StemTile& t, const ImageArgs& im, ImageTab tab)
 {
     constexpr int NK = 16;                                              // taps = reduction steps of 16 channels
     extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
@@ -698,14 +708,14 @@ __device__ __forceinline__ void stem_image_bf16(const ConvArgs& a, void* yq, con
         wait_all_then_barrier<2>();                                     // the next tile's image rows are there (two stores behind them may not be), the tile's convolution outputs are free
     }
 }
-__global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(StemIds<64>, ConvArgs a, void* yq, StemTile t, StemImage im)
+__global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ImageIds<64>, ConvArgs a, void* yq, StemTile t, ImageArgs im)
 {
-    request_args<sizeof(StemIds<64>) + sizeof(ConvArgs) + sizeof(StemTile) + sizeof(StemImage)>();
-    stem_image_bf16(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
+    request_args<sizeof(ImageIds<64>) + sizeof(ConvArgs) + sizeof(StemTile) + sizeof(ImageArgs)>();
+    stem_image_bf16(a, yq, t, im, (ImageTab)__builtin_amdgcn_kernarg_segment_ptr());
 }
-__global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(StemIds<256>, ConvArgs a, void* yq, StemTile t, StemImage im)
+__global__ __launch_bounds__(256, 2) void stem_pool_bf16_kernel(ImageIds<256>, ConvArgs a, void* yq, StemTile t, ImageArgs im)
 {
-    stem_image_bf16(a, yq, t, im, (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr());
+    stem_image_bf16(a, yq, t, im, (ImageTab)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // ---- a 3x3 convolution over 32 channels and the 3x3 / 2 max-pool behind it (int8, 64 output channels) ------------------------
@@ -916,18 +926,149 @@ hipError_t launch_stem_image(const ConvArgs& a, int es, const void* x, const int
     bool small;
     if (!stem_tiles(a, es, Hq, Wq, t, small)) return hipErrorInvalidValue;
     const bool by_value = ids && t.images <= 256;
-    const StemImage im{x, by_value ? nullptr : ids, (int)by_value, H, 3 * W * es, pad};
+    const ImageArgs im{x, by_value ? nullptr : ids, (int)by_value, H, 3 * W * es, pad};
     const dim3 grid(stem_blocks(t, es == 2 ? 512 : 768));
     auto launch = [&](auto tab) {
         using Tab = decltype(tab);
-        using K = void (*)(Tab, ConvArgs, void*, StemTile, StemImage);
+        using K = void (*)(Tab, ConvArgs, void*, StemTile, ImageArgs);
         if (by_value) std::memcpy(tab.id, ids, sizeof(int32_t) * (size_t)t.images);
         if (es == 2) EE_LAUNCH(static_cast<K>(stem_pool_bf16_kernel), grid, dim3(256), SI_LDS, s, tab, a, yq, t, im);
         else if (small) EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_SMALL_TW, ST_SMALL_TH>)), grid, dim3(256), (StemImageShape<ST_SMALL_TW, ST_SMALL_TH>::lds_bytes()), s, tab, a, yq, t, im);
         else EE_LAUNCH((static_cast<K>(stem_pool_i8_kernel<ST_TW, ST_TH>)), grid, dim3(256), (StemImageShape<ST_TW, ST_TH>::lds_bytes()), s, tab, a, yq, t, im);
     };
-    if (by_value && t.images > 64) launch(StemIds<256>{});
-    else launch(StemIds<64>{});
+    if (by_value && t.images > 64) launch(ImageIds<256>{});
+    else launch(ImageIds<64>{});
+    return hipGetLastError();
+}
+
+// ---- a folded stride-2 first layer of 2 x 2 taps straight from the images (int8, 3 channels) ------------------------------------
+// Without a folded copy of the batch and the launch that makes it.  A workgroup takes R output rows of one image: the 2 R + 2 image rows under them are one contiguous piece of it, copied into LDS
+// asynchronously, folded there into super-pixels (a lane: two neighbouring ones, see image_pixels; pixels outside the image become zero by comparison, as they lie inside the piece), and its
+// wavefronts walk over the strips with their operands from LDS.  A lane's requantised 16 channels go straight to memory, 1 KB of contiguous bytes a wavefront.
+// R: the most of 8, 4, 2 and 1 rows that leaves two workgroups for every CU (a row of super-pixels in R + 1 is folded twice), within the LDS of four workgroups to a CU; one or four per CU instead
+// measured alike, but for 304 x 304, 13 samples (four: 9.4 us instead of 7.2).  Bound by latency on a few samples, by HBM on many (128 of 304 x 304: 129 MB written and read in 23 us).
+// 32 channels, us, the folded copy and the streaming kernel / this one, both with the time between launches and the 1x1 layer behind: 224 x 224, 1 sample 13.2 / 9.8, 24 19.2 / 14.5, 64 35.4 / 27.5,
+// 128 56.8 / 43.9; 304 x 304, 64 59.3 / 42.1.  By itself, 224 x 224 and 64 samples, 6.1 + 11.5 / 10.1.
+struct StreamBand {
+    int rows, bands, total;             // output rows of a workgroup, workgroups of an image, in all
+    int pairs;                          // pairs of super-pixels of a folded row
+    unsigned magic_bands, magic_pairs;
+    int raw;                            // bytes of LDS for the image rows: whole copies of a wavefront
+};
+constexpr int BAND_MARGIN = 16;         // in front of the image rows in LDS, and behind them
+static int band_lds(const StreamBand& t) { return 2 * BAND_MARGIN + t.raw + (t.rows + 1) * t.pairs * 32; }
+
+template <int NT>
+__device__ __forceinline__ void stream_band(const ConvArgs& a, const ImageArgs& im, const StreamBand& t, ImageTab tab)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char stem_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, p = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int unit = xcd_unit(blockIdx.x, t.total);
+    if (unit < 0) return;
+    const int n = (int)fast_div((unsigned)unit, (unsigned)t.bands, t.magic_bands), y0 = (unit - n * t.bands) * t.rows, rows = min(t.rows, a.Ho - y0);
+    const int iy0 = 2 * y0 - im.pad, ia = min(max(iy0, 0), im.H - 1), ib = max(min(iy0 + 2 * rows + 2, im.H), ia + 1);     // the rows that exist, at least one
+    const int from = (ia * im.row_bytes) & ~15, chunks = (ib * im.row_bytes - from + 15) >> 4;
+    const unsigned char* src = image_at(im, tab, n) + from;
+    unsigned char* const l_raw = stem_lds + BAND_MARGIN;
+    unsigned char* const l_fold = l_raw + t.raw + BAND_MARGIN;
+    const unsigned raw0 = lds_addr(l_raw);
+    for (int c = 64 * wave; c < chunks; c += 256)
+        dma16(raw0 + c * 16, c + lane < chunks ? src + (c + lane) * 16 : (const unsigned char*)a.zeros);
+    v4i_r wreg[NT][2];
+    v16i_r bias[NT];                                                    // rounding constant included
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) wreg[j][kb] = *(const v4i_r*)((const unsigned char*)a.w + (size_t)(32 * j + p) * a.Kp + kb * 32 + 16 * hi);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const v4i_r b4 = *(const v4i_r*)((const int*)a.bias + 32 * j + 8 * g + 4 * hi);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bias[j][4 * g + e] = b4[e];
+        }
+    }
+    const IrClamp cl = ir_clamp(a.shift, a.lo, a.hi);
+    const bool relu = ir_relu(a.shift, a.lo, a.hi);
+    const int W = im.row_bytes / 3, pitch = t.pairs * 32;
+    wait_all_then_barrier<0>();
+    for (int i = tid; i < (rows + 1) * t.pairs; i += 256) {
+        const int fr = (int)fast_div((unsigned)i, (unsigned)t.pairs, t.magic_pairs), pr = i - fr * t.pairs, ix = 4 * pr - im.pad;
+        unsigned px[2][4];
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+            const int iy = iy0 + 2 * fr + dy;
+            image_pixels(stem_lds, BAND_MARGIN + min(max(iy, ia), ib - 1) * im.row_bytes - from + 3 * min(ix, W), px[dy]);     // (past the row's end: bytes that do not count)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if ((unsigned)iy >= (unsigned)im.H || (unsigned)(ix + k) >= (unsigned)W) px[dy][k] = 0;
+        }
+        v4i_r* q = (v4i_r*)(l_fold + fr * pitch + pr * 32);
+        q[0] = v4i_r{(int)px[0][0], (int)px[0][1], (int)px[1][0], (int)px[1][1]};
+        q[1] = v4i_r{(int)px[0][2], (int)px[0][3], (int)px[1][2], (int)px[1][3]};
+    }
+    lds_barrier();
+    const int m_end = rows * a.Wo;
+    const auto y_buf = __builtin_amdgcn_make_buffer_rsrc((unsigned char*)a.y + ((long long)n * a.Ho + y0) * a.Wo * a.ldc, (short)0, m_end * a.ldc, 0x00020000);     // ends with the band: what is past it is dropped
+    for (int s = wave; s * 32 < m_end; s += 4) {
+        const int m = 32 * s + p, mc = min(m, m_end - 1), oy = (int)fast_div((unsigned)mc, (unsigned)a.Wo, a.magic_wo), ox = mc - oy * a.Wo;
+        const unsigned char* first = l_fold + oy * pitch + (ox + hi) * 16;
+        const v4i_r x0 = *(const v4i_r*)first, x1 = *(const v4i_r*)(first + pitch);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            v16i_r acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][0], x0, bias[j], 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[j][1], x1, acc, 0, 0, 0);
+            const v4i_r o = ir_requant_pack(acc, cl, relu);
+            const int ch = 32 * j + 16 * hi;
+            __builtin_amdgcn_raw_buffer_store_b128(o, y_buf, ch < a.Co ? (unsigned)(m * a.ldc + a.c_off + ch) : 0x80000000u, 0, 0);
+        }
+    }
+}
+template <int NT, int N>
+__global__ __launch_bounds__(256, 4) void conv_stream_image_i8_kernel(ImageIds<N>, ConvArgs a, ImageArgs im, StreamBand t)
+{
+    if constexpr (N == 64) request_args<sizeof(ImageIds<64>) + sizeof(ConvArgs) + sizeof(ImageArgs) + sizeof(StreamBand)>();
+    stream_band<NT>(a, im, t, (ImageTab)__builtin_amdgcn_kernarg_segment_ptr());
+}
+
+static StreamBand band_of(const ConvArgs& a, int row_bytes, int rows)
+{
+    StreamBand t;
+    t.rows = rows;
+    t.bands = (a.Ho + rows - 1) / rows;
+    t.total = a.M / (a.Ho * a.Wo) * t.bands;
+    t.pairs = (a.Wo + 2) / 2;
+    t.magic_bands = stem_magic(t.bands);
+    t.magic_pairs = stem_magic(t.pairs);
+    t.raw = (((2 * rows + 2) * row_bytes + 15 + 15) / 16 + 63) / 64 * 1024;
+    return t;
+}
+
+bool conv_stream_image_supported(const ConvArgs& a, int es, const void* x, int H, int W, int C, int pad)
+{
+    return es == 1 && C == 3 && a.Ci == 16 && a.kh == 2 && a.kw == 2 && a.stride == 1 && a.pad == 0 && a.pad_w == 0 && conv_stream_supported(a, 1) && pad >= 0 && pad <= 5 && (long long)H * W * 3 % 16 == 0 &&
+           ((uintptr_t)x & 15) == 0 && a.M / (a.Ho * a.Wo) <= 65535 && a.Ho <= 4096 && (long long)a.Wo * a.ldc <= 1 << 24 && band_lds(band_of(a, 3 * W, 1)) <= 64 * 1024;
+}
+
+hipError_t launch_conv_stream_image(const ConvArgs& a, const void* x, const int32_t* ids, int H, int W, int pad, hipStream_t s)
+{
+    if (!conv_stream_image_supported(a, 1, x, H, W, 3, pad)) return hipErrorInvalidValue;
+    const int images = a.M / (a.Ho * a.Wo);
+    StreamBand t = band_of(a, 3 * W, 1);
+    for (int rows = 8; rows > 1; rows /= 2) {
+        const StreamBand u = band_of(a, 3 * W, rows);
+        if (u.total >= 512 && band_lds(u) <= 40 * 1024) { t = u; break; }
+    }
+    const bool by_value = ids && images <= 256;
+    const ImageArgs im{x, by_value ? nullptr : ids, (int)by_value, H, 3 * W, pad};
+    auto launch = [&](auto tab) {
+        if (by_value) std::memcpy(tab.id, ids, sizeof(int32_t) * (size_t)images);
+        constexpr int N = sizeof(tab.id) / sizeof(int32_t);
+        if (a.Co > 32) EE_LAUNCH((conv_stream_image_i8_kernel<2, N>), dim3(xcd_grid(t.total)), dim3(256), band_lds(t), s, tab, a, im, t);
+        else EE_LAUNCH((conv_stream_image_i8_kernel<1, N>), dim3(xcd_grid(t.total)), dim3(256), band_lds(t), s, tab, a, im, t);
+    };
+    if (by_value && images > 64) launch(ImageIds<256>{});
+    else launch(ImageIds<64>{});
     return hipGetLastError();
 }
 

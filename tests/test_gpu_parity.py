@@ -1774,6 +1774,37 @@ def test_first_layer_and_pool_straight_from_the_requests(torch, ee, orc, h, w, d
     eng.close()
 
 
+@pytest.mark.parametrize("case", [(1, 16, 16, 1, 9), (33, 48, 32, 1, 40), (16, 299, 32, 0, 3), (61, 80, 48, 0, 70), (38, 160, 64, 1, 130), (224, 224, 32, 1, 19), (125, 64, 32, 0, 300)], ids=lambda c: "x".join(map(str, c)))
+def test_folded_first_layer_straight_from_the_requests(torch, ee, orc, case):
+    """3x3 / 2 first layers (2 x 2 taps once folded) that read the images themselves: one output row, rows of any alignment, 16 to 64 channels, padding and none, bands of one to eight output rows that end
+    with the image and inside it; the step's output against the oracle and the folded copy's, requests of a stream by ids that are 64 and 256 arguments or host memory against their own steps, bit for bit."""
+    from workloads import nets as N
+    h, w, co, pad, n = case
+    net = N._Net(W.DT_I8, h, w, 3, 10)
+    t = net.begin_stage()
+    t = net.conv(t, co, 3, 2, pad)
+    net.end_stage(net.conv(t, 32, 1, 1, 0))
+    blob = N._assemble(net, net.dtype, h + w)
+    for op in blob.ops:
+        op["shift"] = 9
+    x = np.random.default_rng(co).integers(-128, 128, size=(n, h, w, 3), dtype=np.int8)
+    eng, pool, shape = ee.Engine(blob, n), dev(torch, x), blob.stage_out_shape(0)
+    say(f"[case] folded first layer {case}")
+    for b in sorted({1, n // 3 + 1, n}):
+        got, names = kernels_of(torch, lambda: eng.stage_forward(0, pool[:b], shape))
+        ends = sorted({0, b // 2, b - 1})
+        ref = orc.stage_forward(blob, 0, x[ends])
+        assert np.array_equal(host(got[ends], ref), ref) and np.unique(ref).size > 8
+        assert any(k.startswith("conv_stream_image_i8_kernel<") for k in names) and not any(k.startswith("space_to_depth") for k in names), names
+        copied, names = forced(ee, 7, lambda: kernels_of(torch, lambda: eng.stage_forward(0, pool[:b], shape)))
+        assert any(k.startswith("conv_stream_i8_kernel<2,1,") for k in names) and any(k.startswith("space_to_depth") for k in names) and bool((copied == got).all())
+    label, conf, score, _ = (v.cpu().numpy() for v in eng.exit_head(0, got, 0.5))
+    for b_max in sorted({min(7, n), min(65, n), n}):
+        out = eng.serve_stream(np.zeros(n, np.int64), pool, synthetic_lut(blob.n_stages, b_max), b_max=b_max, refill=0)[0]
+        assert np.array_equal(out["label"], label) and np.array_equal(out["score"], score) and np.array_equal(out["conf"], conf)
+    eng.close()
+
+
 SB_CASES = [(224, 224, 5), (57, 80, 7), (32, 32, 9), (17, 16, 3), (7, 16, 2), (116, 60, 9)]      # pooled 56 x 56, 15 x 20, 8 x 8, 5 x 4, 2 x 4, 29 x 15: whole tiles of 7 x 8 and not
 
 
