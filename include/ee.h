@@ -252,7 +252,8 @@ int ee_tune_conv_tile(int cfg);
  * of 32 and 64 pixels), 0x2231, 0x2331, 0x2431, 0x4331 and 0x4431 the stride-1 one that streams its weights into registers
  * (2, 3, 4, 5 and 7 blocks of 32 pixels x 128 channels; 0x2432 and 0x4432: 4 and 7 blocks x 256 channels; 0x2232 and
  * 0x2332: 2 and 4 blocks x 128 channels, two wavefronts sharing a reduction; 0x4234 and 0x4334: 2 and 4 blocks x 64
- * channels; 0x4434 and 0x4332: 2 blocks x 64 channels, two and four sharing).
+ * channels; 0x4434 and 0x4332: 2 blocks x 64 channels, two and four sharing; on int8 layers without padding 0x2431,
+ * 0x4334 and 0x4531: 4 blocks x 128, 64 and 96 channels).
  * EE_ERR_ARG for bad arguments. */
 int ee_autotune(ee_ctx* ctx, int reps);
 int ee_config_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);

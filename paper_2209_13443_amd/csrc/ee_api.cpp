@@ -652,7 +652,7 @@ extern "C" const uint32_t* ee_exp2_table(void) { return exp2_table_host(); }
 extern "C" int ee_tune_conv_tile(int cfg)
 {
     const int tile = cfg & 15, ksel = (cfg >> 4) & 15, ns = (cfg >> 8) & 15, kspl = (cfg >> 12) & 15;
-    if (conv_skinny_config_ok(cfg)) return set_conv_tile(cfg);
+    if (conv_skinny_config_ok(cfg) || cfg_is_taps(cfg)) return set_conv_tile(cfg);
     if (cfg < 0 || (cfg >> 17) || ksel > 3 || (ns != 0 && (ns < 2 || ns > 4)) || (kspl != 0 && kspl != 2 && kspl != 4)) return EE_ERR_ARG;
     if (cfg & EE_CFG_SLAB) {
         if (tile < 1 || tile > 4 || ksel == 1 || kspl != 0) return EE_ERR_ARG;

@@ -216,13 +216,14 @@ int conv_rows_default(const ConvArgs& a, int es);      // configuration of an un
 template <int ES> hipError_t launch_conv_rows(const ConvArgs& a, int cfg, hipStream_t s);
 // the same layers over pixels of whole 32-byte runs (bf16: 64), the weights streamed into registers (kernels_taps.hip): tiles of tm blocks of 32 pixels x 32 channels
 // for each of nw wavefronts, the reduction shared by kp.  nw 4: tm 2, 3, 4, 5, 7, with kp 2 tm 2 and 4; nw 8: tm 4 and 7; nw 2: tm 2 and 4, with kp 2 and 4 tm 2
-// (tm other than 2 and 4 only for whole 128-byte runs).  Its configuration words ask for wavefront groups with 256-byte steps in combinations that the staged
+// (tm other than 2 and 4 only for whole 128-byte runs); int8 layers without padding: tm 4 with nw 2, 3 and 4.  Its configuration words ask for wavefront groups with 256-byte steps in combinations that the staged
 // kernel does not have, like those of kernels_rows.hip
 constexpr int taps_cfg(int tm, int nw, int kp)
 {
+    if (nw == 3) return 0x4531;
     return nw == 2 && kp < 4 ? (kp == 2 ? 0x4434 : tm == 2 ? 0x4234 : 0x4334) : kp == 4 ? 0x4332 : kp == 2 ? (tm == 2 ? 0x2232 : 0x2332) : nw == 8 ? (tm == 4 ? 0x2432 : 0x4432) : 0x31 | (tm <= 4 ? 0x2000 | tm << 8 : tm == 5 ? 0x4300 : 0x4400);
 }
-constexpr int TAPS_CFGS[] = {taps_cfg(2, 4, 1), taps_cfg(3, 4, 1), taps_cfg(4, 4, 1), taps_cfg(5, 4, 1), taps_cfg(7, 4, 1), taps_cfg(2, 4, 2), taps_cfg(4, 4, 2), taps_cfg(2, 2, 4), taps_cfg(4, 8, 1), taps_cfg(7, 8, 1), taps_cfg(2, 2, 1), taps_cfg(4, 2, 1), taps_cfg(2, 2, 2)};
+constexpr int TAPS_CFGS[] = {taps_cfg(2, 4, 1), taps_cfg(3, 4, 1), taps_cfg(4, 4, 1), taps_cfg(5, 4, 1), taps_cfg(7, 4, 1), taps_cfg(2, 4, 2), taps_cfg(4, 4, 2), taps_cfg(2, 2, 4), taps_cfg(4, 8, 1), taps_cfg(7, 8, 1), taps_cfg(2, 2, 1), taps_cfg(4, 2, 1), taps_cfg(2, 2, 2), taps_cfg(4, 3, 1)};
 inline bool cfg_is_taps(int cfg)
 {
     for (const int c : TAPS_CFGS)

@@ -22,11 +22,11 @@ __device__ __forceinline__ void preload(const ConvArgs& a)
 
 // The output tile in LDS: rows of BN elements, chunk c of row r at c ^ oswz(r), oswz(r) = (r / rows per 256 bytes)
 // & (chunks per row - 1): the 32 rows a wavefront touches with one 4- or 8-byte access per lane then spread over
-// the banks as evenly as the row length allows.
+// the banks as evenly as the row length allows.  Rows of 3 x 2^k chunks: & (2^k - 1).
 template <int ES, int BN>
 struct OutTile {
     static constexpr int CR = BN * ES / 16, OROW = BN * ES, OR256 = OROW >= 256 ? 1 : 256 / OROW;
-    static __device__ __forceinline__ int oswz(int r) { return (r / OR256) & (CR - 1); }
+    static __device__ __forceinline__ int oswz(int r) { return (r / OR256) & ((CR & -CR) - 1); }
 };
 
 // Copies the bias of the tile's channels (256 entries from the first one) into LDS.  Asynchronous, as the residual below: counted by vmcnt like the

@@ -12,6 +12,9 @@
 // one or two workgroups per CU) the reduction itself is the chain: 2 or 4 wavefronts share it, a slice of (r, s, c) each, and add up through LDS.  With one
 // wavefront per block of channels the sums run in the order of the staged kernel, so bf16 results are the same bits.
 // Writes slots and pools for the exit head; does not read slots.
+// Layers without padding (int8, pixels of whole 16-byte chunks): all taps exist, so lanes test nothing.  The run of input rows under a tile has what lies between its pixels in it
+// where it goes on to another row or image (its length is bounded by the host, the tile copies what it needs), and a step may straddle two taps, a half-wavefront in either.
+// 74x74, 3x3, 80 -> 192, best configuration of the other kernels -> this one, us: 16 samples 21.4 -> 17.9, 32 37.2 -> 28.3, 64 68.6 -> 48.6 (1.84 POP/s).
 // Measured, best configuration of the other kernels -> this one, 3x3, us:
 //   256 samples: bf16 28x28, 128 -> 128 71.1 -> 45.8, 14x14, 256 -> 256 66.9 -> 43.6 (1.36 PFLOP/s, the rate of a large matrix product here), 7x7, 512 -> 512
 //     63.1 -> 47.1; int8 35.1 -> 28.7, 31.2 -> 26.2, 33.4 -> 27.2
@@ -31,11 +34,14 @@ namespace ee {
 constexpr unsigned taps_part_bytes(int tm, int nw, int kp) { return kp == 1 ? 0 : (unsigned)((tm < kp ? tm : kp) * (kp - 1) * nw * ((tm + kp - 1) / kp) * 4096); }
 
 // ES: element bytes; TM: blocks of 32 pixels of a tile, all of them multiplied by every wavefront; NW: blocks of 32 output channels; KP: wavefronts that
-// share the reduction of a block of channels; U: steps (32 bytes of the reduction) per group, a pixel is a whole number of groups
-template <int ES, int TM, int NW, int KP, int U>
+// share the reduction of a block of channels; UNROLL: steps (32 bytes of the reduction) per group, a pixel is a whole number of groups; 0: a layer without padding
+template <int ES, int TM, int NW, int KP, int UNROLL>
 __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, int gm, int gn, unsigned magic_gn, unsigned magic_p, unsigned slab_bytes, unsigned gap_off)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr bool VALID = UNROLL == 0;
+    static_assert(!VALID || (ES == 1 && KP == 1), "what is behind the last tap is not cleared, a reduction begins with the first tap");
+    constexpr int U = VALID ? 1 : UNROLL;
     constexpr int BM = 32 * TM, BN = 32 * NW, NT = 64 * NW * KP;
     using T = OutTile<ES, BN>;
     constexpr int OROW = T::OROW, CR = T::CR, NO = (BM * CR + NT - 1) / NT;    // output tile: bytes and chunks per row, chunks per lane
@@ -53,12 +59,12 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
     const int tid = threadIdx.x, lane = tid & 63, frow = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m0 = mt * BM, n0 = nt * BN;
-    const int CiB = a.Ci * ES, pitch = CiB + 16, P = pitch >> 4;        // an odd number of chunks per slab row spreads 16 rows over all banks
+    const int CiB = a.Ci * ES, pitch = VALID ? CiB | 16 : CiB + 16, P = pitch >> 4;     // an odd number of chunks per slab row spreads 16 rows over all banks
     const unsigned lds0 = lds_addr(lds);
     const bool has_res = a.res != nullptr;
 
     // ---- weights of the first steps ------------------------------------------------------------------------------
-    const int steps = a.kh * a.kw * (CiB >> 5), groups = steps / U;
+    const int steps = VALID ? (a.kh * a.kw * CiB + 31) >> 5 : a.kh * a.kw * (CiB >> 5), groups = steps / U;
     const int part = wave / NW, wn = wave % NW;                         // this wavefront's share of the reduction, its block of channels
     const bool idle = n0 / 32 + wn >= (a.Co + 31) / 32;                 // its channels lie past the layer's
     const int g0 = KP == 1 ? 0 : groups * part / KP, g1 = idle ? g0 : KP == 1 ? groups : groups * (part + 1) / KP;
@@ -72,11 +78,19 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
     // ---- LDS: zeros for the taps outside the image | slab rows of P chunks | residual tile.  The slab is input rows m0 - halo_lo .. m0 + BM + halo_hi - 1,
     // clamped into the tensor (a clamped row is only ever the source of taps that the validity mask rejects)
     const int halo_lo = a.pad * a.W + a.pad_w;
+    // without padding: the input pixel of output pixel m's first tap
+    auto first_tap = [&](unsigned m) {
+        const unsigned n = fast_div(m, (unsigned)(a.Ho * a.Wo), a.magic_howo), rem = m - n * (unsigned)(a.Ho * a.Wo), oy = fast_div(rem, (unsigned)a.Wo, a.magic_wo);
+        return (int)((n * (unsigned)a.H + oy) * (unsigned)a.W + rem - oy * (unsigned)a.Wo);
+    };
+    const int row0 = VALID ? first_tap((unsigned)m0) : m0 - halo_lo;
+    const int row_end = VALID ? first_tap((unsigned)min(m0 + BM, a.M) - 1u) + (a.kh - 1) * a.W + a.kw : a.M;       // without padding the last row the tile needs, in the tensor as well
     const unsigned ro_off = has_res ? max((unsigned)CiB + slab_bytes, PART_BYTES) : PART_BYTES;
-    for (unsigned q = tid; q < slab_bytes / 16; q += NT) {
+    const unsigned slab_chunks = VALID ? min(slab_bytes / 16, (unsigned)((row_end - row0) * P + NT - 1) / NT * NT) : slab_bytes / 16;
+    for (unsigned q = tid; q < slab_chunks; q += NT) {
         const unsigned row = fast_div(q, (unsigned)P, magic_p), pos = q - row * (unsigned)P;
-        const int g = clamp_i32(m0 - halo_lo + (int)row, 0, a.M - 1);
-        dma16(lds0 + (unsigned)CiB + __builtin_amdgcn_readfirstlane(q) * 16u, a.x, __umul24((unsigned)g, (unsigned)CiB) + (pos == (unsigned)P - 1 ? 0u : pos * 16u));
+        const int g = clamp_i32(row0 + (int)row, 0, row_end - 1);
+        dma16(lds0 + (unsigned)CiB + __builtin_amdgcn_readfirstlane(q) * 16u, a.x, __umul24((unsigned)g, (unsigned)CiB) + (pos * 16u >= (unsigned)CiB ? 0u : pos * 16u));
     }
     if (has_res)
 #pragma unroll
@@ -86,15 +100,20 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
             if (NT * j + 64 * wave < BM * CR)                           // wave-uniform
                 dma16(lds0 + ro_off + (unsigned)(NT * j + 64 * wave) * 16u, (const unsigned char*)a.res + ((size_t)(unsigned)m * a.Co + (ch < a.Co ? ch : 0)) * ES);
         }
-    for (int i = tid; i < CiB / 16; i += NT) *(v4i*)(lds + i * 16) = v4i{0, 0, 0, 0};
+    if constexpr (!VALID)
+        for (int i = tid; i < CiB / 16; i += NT) *(v4i*)(lds + i * 16) = v4i{0, 0, 0, 0};
 
     // ---- operand addresses: bit t of vmask[i] says whether tap t of the lane's pixel of block i lies inside the image ------------------
-    unsigned vmask[TM];
+    unsigned vmask[TM];                                                 // without padding: the lane's pixel of block i in the slab
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         int m = m0 + 32 * i + frow;
         const bool live = m < a.M;
         m = live ? m : a.M - 1;
+        if constexpr (VALID) {
+            vmask[i] = (unsigned)CiB + (unsigned)((first_tap((unsigned)m) - row0) * pitch);
+            continue;
+        }
         const unsigned n = fast_div((unsigned)m, (unsigned)(a.Ho * a.Wo), a.magic_howo), rem = (unsigned)m - n * (unsigned)(a.Ho * a.Wo);
         const unsigned oy = fast_div(rem, (unsigned)a.Wo, a.magic_wo), ox = rem - oy * a.Wo;
         const int iy0 = (int)oy - a.pad, ix0 = (int)ox - a.pad_w;
@@ -106,12 +125,37 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
     int r_tap = 0, r_ts = 0, r_row = 0, r_cb = 0;                       // the reader's tap, its column, the slab row of the tile's first pixel under it, bytes inside the pixel
     const unsigned lane_off = (unsigned)(frow * pitch + hi * 16);
     unsigned pa[TM];
+    // Without padding a step may straddle two taps, the half-wavefronts' 16 bytes are then in different ones: the place of either, its tap, column, byte inside the pixel and offset in the slab, in scalar
+    // registers.  Behind the last tap (the weights are zero there) the lanes read their first one.
+    struct { int tap, ts, c, off; } place[2];
+    const int v_pixel = pitch - CiB, v_row = (a.W - a.kw) * pitch, ntaps = a.kh * a.kw;
+    auto set_place = [&]() {
+        const int lo = place[0].tap < ntaps ? place[0].off : 0, up = place[1].tap < ntaps ? place[1].off : 0;
+        const unsigned off = (unsigned)(hi ? up : lo);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) pa[i] = vmask[i] + off;
+    };
     auto set_tap = [&]() {
         const unsigned at = (unsigned)CiB + (unsigned)(r_row * pitch) + lane_off;
 #pragma unroll
         for (int i = 0; i < TM; ++i) pa[i] = (vmask[i] >> r_tap) & 1u ? at + (unsigned)(32 * i * pitch) : (unsigned)(hi * 16);
     };
     auto advance = [&]() {                                              // one group further along (r, s, c); behind the last tap every lane reads zeros
+        if constexpr (VALID) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                place[h].c += 32;
+                place[h].off += 32;
+                if (place[h].c >= CiB) {                                // once: a pixel has 32 bytes or more
+                    place[h].c -= CiB;
+                    place[h].off += v_pixel;
+                    ++place[h].tap;
+                    if (++place[h].ts == a.kw) { place[h].ts = 0; place[h].off += v_row; }
+                }
+            }
+            set_place();
+            return;
+        }
         r_cb += 32 * U;
         if (r_cb == CiB) {
             r_cb = 0;
@@ -123,15 +167,19 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
 #pragma unroll
             for (int i = 0; i < TM; ++i) pa[i] += 32 * U;
     };
-    if (KP > 1 && part > 0) {
+    if constexpr (VALID) {
+        place[0] = {0, 0, 0, 0};
+        place[1] = {0, 0, 16, 16};
+    } else if (KP > 1 && part > 0) {
         r_tap = g0 * (32 * U) / CiB;
         r_cb = g0 * (32 * U) - r_tap * CiB;
         r_row = r_tap / a.kw * a.W;
         r_ts = r_tap % a.kw;
         r_row += r_ts;
     }
-    set_tap();
-    if (KP > 1 && r_cb)
+    if constexpr (VALID) set_place();
+    else set_tap();
+    if (!VALID && KP > 1 && r_cb)
 #pragma unroll
         for (int i = 0; i < TM; ++i) pa[i] += (unsigned)r_cb;
 
@@ -275,26 +323,37 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
 
 // Stride 1, output as large as the input, 2 .. 31 taps, a pixel of 64 bytes or more in whole groups of steps (a group never straddles two taps), whole
 // 16-byte chunks in the output, a tensor below 2 GiB and 2^24 pixels (the address arithmetic multiplies 24-bit row numbers)
+// no padding at all, so that every tap of every pixel exists (int8)
+static constexpr bool taps_valid_tile(int tm, int nw, int kp) { return tm == 4 && nw <= 4 && kp == 1; }       // the tiles that are built for it
+static bool taps_valid(const ConvArgs& a, int es) { return es == 1 && a.pad == 0 && a.pad_w == 0 && (a.Ho != a.H || a.Wo != a.W); }
+
 bool conv_taps_supported(const ConvArgs& a, int es)
 {
     const int cib = a.Ci * es;
-    if (a.xs || a.mode != 0 || !a.wo || a.stride != 1 || a.Ho != a.H || a.Wo != a.W) return false;
-    if (cib % (es == 1 ? 32 : 64) != 0 || cib < 64 || cib > 2048 || a.kh * a.kw > 31 || a.kh * a.kw < 2) return false;
+    const bool valid = taps_valid(a, es);
+    if (a.xs || a.mode != 0 || !a.wo || a.stride != 1 || (!valid && (a.Ho != a.H || a.Wo != a.W))) return false;
+    if (cib % (valid ? 16 : es == 1 ? 32 : 64) != 0 || cib < 64 || cib > 2048 || a.kh * a.kw > 31 || a.kh * a.kw < 2) return false;
     if (a.H + 2 * a.pad - a.kh + 1 != a.Ho || a.W + 2 * a.pad_w - a.kw + 1 != a.Wo) return false;
     if ((a.Co * es) % 16 != 0 || (a.ldc * es) % 16 != 0 || (a.c_off * es) % 16 != 0) return false;
-    return (long long)a.M * cib < (1ll << 31) && a.M < 1 << 24;
+    const long long pixels = (long long)(a.M / (a.Ho * a.Wo)) * a.H * a.W;
+    return pixels * cib < (1ll << 31) && pixels < 1 << 24;
 }
 
 // the tiles that are built (TAPS_CFGS): blocks of 32 pixels, blocks of 32 channels, wavefronts that share a reduction
 #define EE_TAPS_TILES \
     EE_TAPS(2, 4, 1) EE_TAPS(3, 4, 1) EE_TAPS(4, 4, 1) EE_TAPS(5, 4, 1) EE_TAPS(7, 4, 1) EE_TAPS(2, 4, 2) EE_TAPS(4, 4, 2) EE_TAPS(2, 2, 4) EE_TAPS(4, 8, 1) EE_TAPS(7, 8, 1) \
-    EE_TAPS(2, 2, 1) EE_TAPS(4, 2, 1) EE_TAPS(2, 2, 2)
+    EE_TAPS(2, 2, 1) EE_TAPS(4, 2, 1) EE_TAPS(2, 2, 2) EE_TAPS(4, 3, 1)
 
 struct TapsLds { unsigned slab, gap_off; size_t bytes; };
 static TapsLds taps_lds(const ConvArgs& a, int es, int tm, int nw, int kp)
 {
     const int cib = a.Ci * es, nt = 64 * nw * kp;
-    const long long chunks = (32 * tm + (a.kh - 1) * (long long)a.W + (a.kw - 1)) * (cib / 16 + 1);
+    long long rows = 32 * tm + (a.kh - 1) * (long long)a.W + (a.kw - 1);
+    if (taps_valid(a, es)) {                                            // and what lies between the pixels where the tile goes on to another row or image
+        const int last = 32 * tm - 1;
+        rows += (last + a.Wo - 1) / a.Wo * (long long)(a.W - a.Wo) + (last + (long long)a.Ho * a.Wo - 1) / ((long long)a.Ho * a.Wo) * (a.H - a.Ho) * a.W;
+    }
+    const long long chunks = rows * (taps_valid(a, es) ? cib / 16 | 1 : cib / 16 + 1);
     TapsLds l;
     l.slab = (unsigned)((chunks + nt - 1) / nt * nt * 16);
     const size_t parts = taps_part_bytes(tm, nw, kp), tile = (size_t)(32 * tm) * (32 * nw) * es, front = std::max((size_t)cib + l.slab, parts);
@@ -312,9 +371,9 @@ static bool taps_fits(const ConvArgs& a, int es, int tm, int nw, int kp)
 bool conv_taps_config_ok(const ConvArgs& a, int cfg, int es)
 {
     if (!conv_taps_supported(a, es)) return false;
-    const bool any_tile = a.Ci * es % 128 == 0;                         // else only tiles of 2 and 4 blocks of pixels exist
+    const bool any_tile = a.Ci * es % 128 == 0 && !taps_valid(a, es);   // else only tiles of 2 and 4 blocks of pixels exist
 #define EE_TAPS(TM_, NW_, KP_) \
-    if (cfg == taps_cfg(TM_, NW_, KP_)) return (any_tile || TM_ == 2 || TM_ == 4) && taps_fits(a, es, TM_, NW_, KP_);
+    if (cfg == taps_cfg(TM_, NW_, KP_)) return (any_tile || TM_ == 2 || TM_ == 4) && (taps_valid(a, es) ? taps_valid_tile(TM_, NW_, KP_) : NW_ != 3) && taps_fits(a, es, TM_, NW_, KP_);
     EE_TAPS_TILES
 #undef EE_TAPS
     return false;
@@ -333,11 +392,19 @@ bool conv_taps_config_ok(const ConvArgs& a, int cfg, int es)
 //   Otherwise the tile with the least work on the busiest CU: its workgroups times (blocks of 32 pixels + 1 for start and end), three tenths more where four wavefronts
 //     have a CU to themselves.  Over 27 layers and sizes the choice is the fastest configuration or within 3 % of it but once (7 %).
 //   Reductions below 512 bytes were not measured.
+//   Without padding (int8): from 1280 blocks on and reductions of 640 bytes tiles of 128 pixels and 128 channels (56x56, 64 -> 64 without padding, 576 bytes, 64 samples 13.4 / 14.5; 30x30, 128 -> 256, 16
+//     samples in 784 blocks 8.1 / 9.1, 32 12.2 / 11.6, 64 21.7 / 20.0; 40x40, 5x5, 96 -> 96, 32 samples in 1296 18.3 / 17.1, 64 28.8 / 22.8; 35x70, 3x2, 176 -> 320 72.6 / 58.9), of 96 channels where
+//     those leave fewer empty and four workgroups share a CU's LDS (74x74, 80 -> 192, 8 samples 12.7 / 11.1, 64 68.6 / 48.6, with 128 channels 51.1; with three workgroups, 35x70 64 samples, 76.4).
 int conv_taps_default(const ConvArgs& a, int es)
 {
     const long long blocks = (long long)((a.M + 63) / 64) * ((a.Co + 63) / 64), kbytes = (long long)a.kh * a.kw * a.Ci * es;
     const bool half = (a.Co - 1) % 128 < 64;                            // the last 128-channel tile at most half full
     if (kbytes < 512 || blocks < (es == 2 ? (half ? 200 : 32) : kbytes < 2048 ? 101 : 54) || !conv_taps_supported(a, es)) return 0;
+    if (taps_valid(a, es)) {
+        if (blocks < 1280 || kbytes < 640) return 0;
+        const bool three = (a.Co + 95) / 96 * 96 < (a.Co + 127) / 128 * 128 && taps_lds(a, es, 4, 3, 1).bytes <= 40 * 1024;
+        return three ? taps_cfg(4, 3, 1) : taps_fits(a, es, 4, 4, 1) ? taps_cfg(4, 4, 1) : 0;
+    }
     const bool wide_groups = a.Ci * es % 128 == 0;                      // every tile exists; else 2 and 4 blocks of pixels
     auto fits = [&](int tm, int nw, int kp) { return taps_fits(a, es, tm, nw, kp); };
     if (es == 1 && blocks <= 256 && kbytes >= 3072 && fits(2, 2, 4)) return taps_cfg(2, 2, 4);
@@ -366,7 +433,7 @@ template <int ES, int TM, int NW, int KP, int U>
 static hipError_t launch_taps_unroll(const ConvArgs& a, hipStream_t s)
 {
     constexpr int BM = 32 * TM, BN = 32 * NW;
-    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, p = a.Ci * ES / 16 + 1;
+    const int gm = (a.M + BM - 1) / BM, gn = (a.Co + BN - 1) / BN, p = U == 0 ? a.Ci * ES / 16 | 1 : a.Ci * ES / 16 + 1;
     const TapsLds l = taps_lds(a, ES, TM, NW, KP);
     static const hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_taps_kernel<ES, TM, NW, KP, U>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (granted != hipSuccess) return granted;
@@ -379,10 +446,16 @@ template <int ES, int TM, int NW, int KP>
 static hipError_t launch_taps_shape(const ConvArgs& a, hipStream_t s)
 {
     const int cib = a.Ci * ES;
-    if (cib % 128 == 0) return launch_taps_unroll<ES, TM, NW, KP, 4>(a, s);
-    if constexpr (TM == 2 || TM == 4) {
-        if (cib % 64 == 0) return launch_taps_unroll<ES, TM, NW, KP, 2>(a, s);
-        if constexpr (ES == 1) return launch_taps_unroll<ES, TM, NW, KP, 1>(a, s);
+    if (taps_valid(a, ES)) {
+        if constexpr (ES == 1 && taps_valid_tile(TM, NW, KP)) return launch_taps_unroll<ES, TM, NW, KP, 0>(a, s);
+        else return hipErrorInvalidValue;
+    }
+    if constexpr (NW != 3) {
+        if (cib % 128 == 0) return launch_taps_unroll<ES, TM, NW, KP, 4>(a, s);
+        if constexpr (TM == 2 || TM == 4) {
+            if (cib % 64 == 0) return launch_taps_unroll<ES, TM, NW, KP, 2>(a, s);
+            if constexpr (ES == 1) return launch_taps_unroll<ES, TM, NW, KP, 1>(a, s);
+        }
     }
     return hipErrorInvalidValue;
 }

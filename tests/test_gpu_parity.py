@@ -1068,6 +1068,53 @@ def taps_runs(w, kb, kh, kw, es, cfg, residual, pooled_pixels=0):
     return lds <= 160 * 1024 and not (pooled_pixels and (32 * tm - 1) // pooled_pixels + 2 > 8)
 
 
+# (height, width, bytes per pixel, output channels, kernel, images): whole and broken 32-byte steps to a pixel, rows of an even and an odd number of chunks, tiles within a row and over
+# several rows and images, one pixel per image, kernels of one row and column, blocks of channels that are not there
+VALID_CASES = [
+    (73, 73, 80, 192, (3, 3), 2), (5, 7, 80, 32, (3, 3), 9), (3, 3, 64, 48, (3, 3), 70), (9, 4, 112, 96, (2, 3), 5), (40, 12, 128, 64, (5, 1), 3), (4, 90, 96, 256, (1, 5), 4),
+    (8, 8, 176, 160, (3, 3), 6), (74, 74, 80, 192, (3, 3), 6), (11, 34, 208, 272, (2, 2), 1), (6, 5, 1040, 32, (3, 5), 4),
+]
+
+VALID_CONFIGS = {0x2431: 4, 0x4334: 2, 0x4531: 3}          # blocks of 32 channels; tiles of 128 pixels
+
+
+def valid_runs(w, h, kb, kh, kw, cfg, residual):
+    """Whether the kernel has the tile on a layer without padding: LDS for a pixel, the slab (an odd number of chunks to a row; what lies between the pixels of a tile that goes on to
+    another row or image) and the output tile."""
+    if cfg not in VALID_CONFIGS:
+        return False
+    ho, wo, nw = h - kh + 1, w - kw + 1, VALID_CONFIGS[cfg]
+    rows = 128 + (kh - 1) * w + kw - 1 + -(-127 // wo) * (kw - 1) + -(-127 // (ho * wo)) * (kh - 1) * w
+    front, tile = kb + -(-rows * (kb // 16 | 1) // (64 * nw)) * 64 * nw * 16, 128 * 32 * nw
+    return (front + tile if residual else max(front, tile)) <= 160 * 1024
+
+
+@pytest.mark.parametrize("case", VALID_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_streamed_weights_convolution_without_padding(torch, ee, orc, case):
+    """The same kernel on layers whose output is smaller than their input, every tile, with and without a residual, against the oracle bit for bit."""
+    from workloads import nets as N
+    h, w, kb, co, (kh, kw), n = case
+    net = N._Net(W.DT_I8, h, w, kb, 10)
+    t = net.begin_stage()
+    res = net.conv(t, co, (kh, kw), 1, (0, 0), act="linear")
+    net.end_stage(net.conv(t, co, (kh, kw), 1, (0, 0), res=res))
+    blob = N._assemble(net, net.dtype, 90 + h)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * kh * kw) / 127))))
+        op["res_shift"] = int(op["shift"]) - 2 if int(op["res"]) >= 0 else 0
+    x = W.input_pool(blob, n)
+    eng = ee.Engine(blob, n)
+    ref = orc.stage_forward(blob, 0, x)
+    assert len(np.unique(ref)) > 20
+    for cfg in [0, 0x4531] + TAPS_CONFIGS:
+        say(f"[case] {case} cfg {cfg:#x}")
+        got, names = forced(ee, cfg, lambda: kernels_of(torch, lambda: eng.stage_forward(0, dev(torch, x), ref.shape[1:])))
+        assert np.array_equal(got.cpu().numpy(), ref), hex(cfg)
+        if cfg:
+            runs = sum(valid_runs(w, h, kb, kh, kw, cfg, residual) for residual in (False, True))
+            assert [k for k in names if k.startswith("conv_taps")] == ["conv_taps_kernel<1,4,%d,1,0>" % VALID_CONFIGS.get(cfg, 0)] * runs, hex(cfg)
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 @pytest.mark.parametrize("case", TAPS_CASES, ids=lambda c: "x".join(map(str, c)))
 def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
