@@ -1426,6 +1426,31 @@ def test_sibling_layers_in_one_launch_bit_exact(torch, ee, orc, cfg):
         eng.close()
 
 
+@pytest.mark.parametrize("hw, ci, c1, c2, stride", [(28, 128, 64, 256, 2), (13, 64, 160, 96, 2), (9, 96, 32, 320, 3), (12, 64, 64, 64, 1)])
+def test_siblings_that_read_one_input_take_turns(torch, ee, orc, hw, ci, c1, c2, stride):
+    """Joint launches of 1x1 layers over one input, whose tiles go out in rounds: as many tiles of pixels to each, 2 to 9 times as many to one, ratios that do not come out even, fewer tiles than XCDs."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, hw, hw, ci, 10)
+    t = net.conv(net.begin_stage(), ci, 1, 1, 0)
+    u, v = net.conv(t, c1, 1, 1, 0), net.conv(t, c2, 1, stride, 0, act="linear")
+    net.end_stage(net.conv(u, c2, 3, stride, 1, res=v))
+    blob = N._assemble(net, net.dtype, 31)
+    for op in blob.ops:
+        op["shift"] = int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * int(op["kh"]) ** 2) / 127)))
+        op["res_shift"] = int(op["shift"]) - 1 if int(op["res"]) >= 0 else 0
+    eng = ee.Engine(blob, 37)
+    x = W.input_pool(blob, 37)
+    ref = orc.stage_forward(blob, 0, x)
+    assert len(np.unique(ref)) > 20
+    for cfg in (0x211, 0x222, 0x333, 0x214):
+        eng.load_tables({"group": {"1": [cfg] * 16}})
+        for b in (1, 3, 37):
+            say(f"[case] rounds {hw} {ci} {c1} {c2} /{stride} cfg {cfg:#x} b={b}")
+            n, got = launches_per_layer(torch, eng, blob, dev(torch, x[:b]))
+            assert n == [1, 1, 0, 1] and np.array_equal(host(got, ref), ref[:b]), n
+    eng.close()
+
+
 def sibling_net(h, c, branches):
     """One segment: a 1x1 layer, then int8 branches [(kernel, channels)] over its output that fill one tensor."""
     from workloads import nets as N
