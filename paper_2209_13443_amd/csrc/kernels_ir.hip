@@ -86,9 +86,11 @@ __device__ __forceinline__ V image_load(__amdgpu_buffer_rsrc_t x, int at)
 // MAXK = 0: a block without expansion (depthwise -> projection): the buffers of "expanded" pixels are filled with the
 // block's input itself, 32 channels at a time.
 // POOL: the exit head's pooling in the epilogue (a kernel of its own: with a branch the others' launches on one image took 0.15 us longer each)
+// Without expansion and to one output block four workgroups share a CU like with one: 112x112, 32 -> 16, us, 146 registers / 128: 4 samples 4.4 / 4.5, 16 7.2 / 6.7, 32 10.9 / 10.3, 64 18.3 / 17.0, 128
+// 32.6 / 29.3 (with two or three registers in scratch memory 4.7, 7.1, 10.7, 17.3 and 29.8).
 // Registers: <1, 1, 2, 1, 0, true>, held to 128, keeps two more in scratch memory (12 bytes a lane); no other form spills.
 template <int STRIDE, int NCO, int MAXB, int MAXK, int GP, bool POOL>
-__global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) ? (MAXK == 1 ? 4 : 3) : 2) void ir_block_i8_kernel(IrArgs a, IrTile t)
+__global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) ? (MAXK == 0 && POOL ? 3 : 4) : 2) void ir_block_i8_kernel(IrArgs a, IrTile t)
 {
     request_args<sizeof(IrArgs) + sizeof(IrTile)>();
     constexpr int NW = GP ? GP : 4, NT = 64 * NW;                      // wavefronts and lanes per workgroup
@@ -203,8 +205,7 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     }
 
     const unsigned char* const we_lane = (const unsigned char*)a.we + (size_t)m * a.Kx + 16 * hi;       // + g * 32 * Kx + k * 32
-    const unsigned char* const wd_lane = (const unsigned char*)a.wd + (size_t)lane * 16;               // + (g * 5 + k) * 1024
-    const unsigned char* const wp_lane = (const unsigned char*)a.wp + (size_t)m * a.Ce32 + 16 * hi;     // + cob * 32 * Ce32 + g * 32
+    const unsigned wd_lane = (unsigned)lane * 16, wp_lane = (unsigned)(m * a.Ce32 + 16 * hi);           // behind a uniform address: one register each
     v4i_r we[EXP ? MAXK : 1], wd[5], wp[NCO];
     const int sparse = 0x11111111 * ((m & 3) == 3 ? 12 : 12 | (m & 3));   // which two of four reduction bytes the lane's row keeps: its own and (of no weight) another
     v16i_r accp[MAXB][NCO];
@@ -227,9 +228,9 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     };
     auto load_wd_wp = [&](int g) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) wd[k] = *(const v4i_r*)(wd_lane + (size_t)(g * 5 + k) * 1024);
+        for (int k = 0; k < 5; ++k) wd[k] = *(const v4i_r*)((const unsigned char*)a.wd + (size_t)(g * 5 + k) * 1024 + wd_lane);
 #pragma unroll
-        for (int c = 0; c < NCO; ++c) wp[c] = *(const v4i_r*)(wp_lane + (size_t)c * 32 * a.Ce32 + g * 32);
+        for (int c = 0; c < NCO; ++c) wp[c] = *(const v4i_r*)((const unsigned char*)a.wp + ((size_t)c * 32 * a.Ce32 + g * 32) + wp_lane);
     };
     auto bias16 = [&](const unsigned char* lb, int g) {                 // the group's bias in the accumulator layout
         v16i_r acc;
@@ -259,7 +260,6 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     // the next group can be in flight over the work on this one.
     constexpr int FT = GP ? 64 : NT;                                    // lanes that fill one buffer: a wavefront's own (GP) or the workgroup's
     v4i_r fl[EXP ? 1 : IR_FILL];
-    unsigned fdst[EXP ? 1 : IR_FILL];
     auto fill_load = [&](int g) {
         if constexpr (!EXP) {
             const auto x = image(a, n);
@@ -272,22 +272,24 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
                     const int at = ((iy0 + py) * a.W + ix) * a.Cin + ch;
                     // rows outside the image lie out of the buffer's range by themselves
                     fl[i] = image_load<v4i_r>(x, (unsigned)ix < (unsigned)a.W && ch < a.Cin ? at : (int)0x80000000u);
-                    fdst[i] = (unsigned)(py * e_row + px * 32 + 16 * half);
                 }
         }
     };
     auto fill_store = [&](unsigned char* ebuf) {
         if constexpr (!EXP) {
-            const int nch = t.ih * t.iw * 2;
+            const int nch = t.ih * t.iw * 2, ft = GP ? lane : tid;
 #pragma unroll
             for (int i = 0; i < IR_FILL; ++i)
-                if (FT * i < nch) *(v4i_r*)(ebuf + fdst[i]) = fl[i];
+                if (FT * i < nch) {                                     // the place once more: kept over the work on a group it was registers that are short
+                    const int e = min(FT * i + ft, nch - 1), py = (int)__umulhi((unsigned)(e >> 1), t.magic_iw);
+                    *(v4i_r*)(ebuf + 16 * e + py * (e_row - 32 * t.iw)) = fl[i];
+                }
         }
     };
     auto dw_project = [&](int g, const unsigned char* ebuf) {
         // The bias once for all blocks, but where the kernel is held to 128 registers: there it is read in front of every block.  Sixteen more registers over the loop were four to six spilled
         // to memory (3-4 MB each way a launch); 64 samples, us: 112x112 stride 2, 16 -> 96 -> 24 28.7 -> 25.8, 56x56, 24 -> 144 -> 24 22.0 -> 20.6, 28x28, 32 -> 192 -> 32 13.0 -> 11.5.
-        constexpr bool ONCE = GP || MAXK != 1;
+        constexpr bool ONCE = GP || MAXK > 1;
         v16i_r bias;
         if constexpr (ONCE) bias = bias16(l_bd, g);
 #pragma unroll
@@ -325,17 +327,20 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
                     for (int i = 0; i < 16; ++i) atomicAdd(l_r + ((s * NCO + c) * 16 + i) * 64 + lane, accp[s][c][i]);
         __syncthreads();                                                // all four partial sums are in
     } else {
+        constexpr bool LATE = !EXP && NCO == 1;                         // the next group's pixels behind this group's work: held over it they cost the registers of a fourth workgroup on the CU
         if constexpr (EXP) load_we(0); else fill_load(0);
         load_wd_wp(0);
         __syncthreads();                                                // staged pixels, cleared buffers and biases are in LDS
         if constexpr (EXP) expand(0, l_e); else fill_store(l_e);
         for (int g = 0; g < ngroups; ++g) {
             if (g + 1 < ngroups) {
-                if constexpr (EXP) load_we(g + 1); else fill_load(g + 1);
+                if constexpr (EXP) load_we(g + 1);
+                else if constexpr (!LATE) fill_load(g + 1);
             }
             __syncthreads();                                            // group g is in its buffer; nobody reads the other buffer any more
             dw_project(g, l_e + (g & 1) * t.e_bytes);
             if (g + 1 < ngroups) {
+                if constexpr (LATE) fill_load(g + 1);
                 load_wd_wp(g + 1);
                 if constexpr (EXP) expand(g + 1, l_e + ((g + 1) & 1) * t.e_bytes); else fill_store(l_e + ((g + 1) & 1) * t.e_bytes);
             }
@@ -351,8 +356,11 @@ __global__ __launch_bounds__(GP ? 64 * GP : 256, (NCO == 1 && !GP && MAXK <= 1) 
     for (int s = 0; s < MAXB; ++s)
         if ((GP ? s : dwave + 4 * s) < nblocks) {                       // wave-uniform
             const int b = GP ? s : dwave + 4 * s, by = (b * t.magic_pbw) >> 16, bx = b - by * t.pbw;
-            const int oy = oy0 + by * t.nbh + tyc, ox = ox0 + bx * t.nbw + txc;
-            const bool px_ok = lane_px && oy < a.Ho && ox < a.Wo;
+            int me = m;
+            if constexpr (!EXP && NCO == 1) asm volatile("" : "+v"(me));        // the lane's place in the block once more: kept over the groups it was two registers in scratch memory
+            const int ey = (me * t.magic_nbw) >> 16, ex = me - ey * t.nbw;
+            const int oy = oy0 + by * t.nbh + ey, ox = ox0 + bx * t.nbw + ex;
+            const bool px_ok = ey < t.nbh && oy < a.Ho && ox < a.Wo;
             const unsigned pix = px_ok ? (unsigned)(((n * a.Ho + oy) * a.Wo + ox) * a.Cout) : 0u;      // < 2^31: checked by the launcher
 #pragma unroll
             for (int c = 0; c < NCO; ++c) {
