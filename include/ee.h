@@ -238,9 +238,10 @@ int ee_tune_conv_tile(int cfg);
  * synchronous, overwrites the workspace activations) and keeps the fastest; until it is called the configuration
  * is chosen from the layer shape alone.  int8 results never depend on the table.  bf16 results do within their
  * rounding: wavefronts that share a reduction add their float sums in an order of their own (the kernel for few
- * output pixels, wavefront groups), and every layer rounds to bf16.  Which of them is the fastest is a
- * measurement, so two tunings may differ in the last bits of a bf16 network's activations; a stored table gives
- * the same ones each time.  ee_config_table copies layer `layer`'s entries to cfg_out[0..n) (host) and returns how
+ * output pixels, wavefront groups), and every layer rounds to bf16.  Which order a layer has in a tuned bf16 network is
+ * decided by its shape and the batch bucket alone, and ee_autotune times only what adds in that order: every tuning of a network, by
+ * whatever context, gives the same bits (for few samples others than an untuned context, which adds in one order at all sizes; a table from elsewhere
+ * may name any).  ee_config_table copies layer `layer`'s entries to cfg_out[0..n) (host) and returns how
  * many the layer has (0 = not tuned or not a matrix-core convolution); an entry is tile | step << 4 | stages << 8
  * | groups << 12 with tile 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128 (pixels x channels), step 1: 64, 2: 128, 3:
  * 256 bytes of the reduction axis per stage, groups 0: one group of 4 wavefronts, 2 or 4: that many groups sharing

@@ -1033,6 +1033,12 @@ bool ee_ctx::ir_wanted(int op, int b) const
     if (!p.ir || ir_mode == 0) return false;
     if (ir_mode == 2) return true;
     if (!p.ir_cfg.empty()) return p.ir_cfg[std::min<size_t>(bucket_of(b), p.ir_cfg.size() - 1)] != 0;
+    return ir_default(op);
+}
+
+bool ee_ctx::ir_default(int op) const
+{
+    const OpPlan& p = plans[(size_t)op];
     return p.ir_bneck || p.ir_stem || plans[(size_t)op + p.ir_last()].d.c_out <= 96;
 }
 
@@ -1254,6 +1260,14 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 for (int ns = 2; ns <= 4; ++ns)
                     if ((ksel == 1 || kbytes > 64 * (ksel - 1)) && (ns == 2 || kbytes > (ns - 1) * (32 << ksel))) add(tile | ksel << 4 | ns << 8);
     };
+    // bf16: every candidate for a layer and bucket adds the sums in one order, which its shape at the bucket's full size decides (no measurement, nor b_max): in that of the staged kernels (0) or in the
+    // few-pixel kernel's with the wavefronts of that word.  So any two tunings give the same bits.
+    auto split_of = [&](int op, size_t bi) {
+        if (es == 1) return 0;
+        ConvArgs a{};
+        ctx->fill_conv_args(op, 1 << bi, a);
+        return ctx->plans[(size_t)op].cfg_table() ? conv_skinny_order_bf16(a) : 0;
+    };
     // runs what stands in front of layer k of a segment, with the configuration found for it
     auto layer_before = [&](size_t s, int k, int b) {
         const int first = ctx->net.stages[s].first_op;
@@ -1284,7 +1298,7 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 staged(kbytes, [&](int cfg) {
                     cands.push_back(cfg);
                     const int tile = cfg & 15;
-                    if (((cfg >> 4) & 15) == 3 && tile >= 3 && kbytes >= 1024)           // wavefront groups, the combinations that exist
+                    if (es == 1 && ((cfg >> 4) & 15) == 3 && tile >= 3 && kbytes >= 1024)           // wavefront groups, the combinations that exist
                         for (int kspl = 2; kspl <= (tile == 3 ? 4 : 2); kspl *= 2) cands.push_back(cfg | kspl << 12);
                 });
                 if (conv_stream_supported(probe, es)) cands.push_back(7);               // it has one configuration
@@ -1295,7 +1309,10 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                         if (conv_taps_config_ok(probe, cfg, es) && (es == 1 || !cfg_taps_shares(cfg))) cands.push_back(cfg);      // bf16: the staged kernels' order of summation
                 if (p.impl == IMPL_MFMA && conv_slab_supported(probe, es) && !conv_taps_default(probe, es))      // never the faster one there
                     staged(kbytes, [&](int cfg) { if ((cfg >> 4 & 15) > 1) cands.push_back(EE_CFG_SLAB | cfg); });
-                if ((long long)buckets[bi] * d.h_out * d.w_out <= EE_SKINNY_MAX_ROWS)          // few pixels: the kernel that splits the reduction over its wavefronts
+                if (const int word = split_of(st.first_op + k, bi)) {                              // one way to share the reduction, one or two blocks of channels per activation
+                    cands = {word};
+                    if (conv_skinny_config_ok(word + 16) && word >> 12 == 2) cands.push_back(word + 16);
+                } else if (es == 1 && (long long)buckets[bi] * d.h_out * d.w_out <= EE_SKINNY_MAX_ROWS)          // few pixels: the kernel that splits the reduction over its wavefronts
                     for (int shape = 0; shape < 3; ++shape)                                     // 32 pixels x 32 or 64 channels, 16 x 16
                         for (int lw = 0; lw <= 4; ++lw) {
                             const int cfg = skinny_cfg(shape < 2 ? 32 : 16, shape == 1 ? 2 : 1, lw);
@@ -1326,7 +1343,8 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 const auto found = fastest(cands, 4, layer_before(s, k, buckets[bi]), [&](int cfg) {
                     return ctx->timed(EE_K_CONV_MFMA, 0.0, 0.0, [&] { return ctx->launch_pair(st.first_op + k, buckets[bi], src, dst, res, cfg); });
                 });
-                if (found.first < best_time[st.first_op + k][bi] + best_time[st.first_op + k + 1][bi]) best[bi] = found.second;
+                const bool one_order = !split_of(st.first_op + k, bi) && !split_of(st.first_op + k + 1, bi);      // the pair adds like the staged kernels
+                if (one_order && found.first < best_time[st.first_op + k][bi] + best_time[st.first_op + k + 1][bi]) best[bi] = found.second;
                 pair_time[st.first_op + k].push_back(found.first);
             }
             if (!rc) p.pair_cfg = best;
@@ -1410,6 +1428,12 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
                 std::vector<int> best(buckets.size(), 0);
                 for (size_t bi = 0; bi < buckets.size() && !rc; ++bi) {
                     float ms[2] = {0.f, 0.f};
+                    bool one_order = true;                                   // the block's kernel adds like the staged kernels; where its layers would not, it runs as untuned, whatever is faster
+                    for (int j = 0; j <= p.ir_last(); ++j) one_order &= !split_of(st.first_op + k + j, bi);
+                    if (!one_order) {
+                        best[bi] = ctx->ir_default(st.first_op + k);
+                        continue;
+                    }
                     for (int fused = 0; fused < 2 && !rc; ++fused) {
                         ctx->ir_mode = fused ? 2 : (p.ir_sc ? 1 : 0);
                         p.ir_cfg.assign(buckets.size(), 0);                  // table mode: this head stays separate, the block behind it as tuned

@@ -8,9 +8,6 @@
 namespace ee {
 
 enum Impl { IMPL_MFMA = 0, IMPL_MFMA_C4 = 1, IMPL_DIRECT = 2, IMPL_DW = 3, IMPL_POOL = 4, IMPL_MFMA_CPAD = 5, IMPL_MFMA_S2D = 6, IMPL_AVGPOOL = 7, IMPL_THIN = 8 };
-// ee_autotune tries the few-pixel kernel up to this many output pixels: every operand byte it loads feeds one instruction, so with
-// more it is never the fastest
-constexpr long long EE_SKINNY_MAX_ROWS = 8192;
 enum { BUF_EXT_IN = -1, BUF_EXT_OUT = -2 };
 
 struct OpPlan {
@@ -183,6 +180,7 @@ struct ee_ctx {
     void fill_seam_args(int op, int b, bool front, ee::SeamArgs& a) const;       // the tensors are left to the caller
     hipError_t launch_seam(int op, int b, const void* src, const void* res, void* dst, void* dst2, int cfg);
     bool ir_wanted(int op, int b) const;                         // the fused block headed by layer op, by mode, table or (untuned) rule
+    bool ir_default(int op) const;                               // the rule
     // layers op and op + 1 as one fused launch: src feeds layer op, res and dst belong to layer op + 1
     hipError_t launch_pair(int op, int b, const void* src, void* dst, const void* res, int cfg);
     void fill_ir_args(int op, int b, ee::IrArgs& a) const;      // the block headed by layer `op`; x, res and y are left to the caller

@@ -249,6 +249,9 @@ inline bool cfg_is_skinny(int cfg)
 }
 bool conv_skinny_config_ok(int cfg);
 int conv_skinny_default(const ConvArgs& a, int es);    // configuration of an untuned launch it is the faster one for, else 0
+int conv_skinny_order_bf16(const ConvArgs& a);         // the word whose wavefronts share the reduction of a tuned bf16 layer of this size, or 0: the order of the staged kernels
+// ee_autotune tries it up to this many output pixels: every operand byte it loads feeds one instruction, so with more it is never the fastest
+constexpr long long EE_SKINNY_MAX_ROWS = 8192;
 template <int ES> hipError_t launch_conv_skinny(const ConvArgs& a, int cfg, hipStream_t s);
 // several independent int8 layers in one launch with one configuration (kernels_group.hip)
 enum { EE_GROUP_MAX = 4 };

@@ -2248,6 +2248,29 @@ def test_full_size_bf16_against_the_oracle(torch, ee, orc):
     eng.close()
 
 
+@pytest.mark.parametrize("name", ["tiny_bf16", "zoo_bf16", "resnet50_small_bf16", "inception_small_bf16", "resnet50_bf16"])
+def test_tunings_of_a_bf16_network_agree(torch, ee, name):
+    """Contexts tuned apart, one of them for other batches, return the same bits at every batch size: the shapes alone decide in which order a tuned layer adds."""
+    blob = W.load_net(name)
+    engines = [ee.Engine(blob, b_max) for b_max in (256, 256, 40)]
+    for reps, eng in enumerate(engines, 1):
+        eng.autotune(reps=reps)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((256,) + tuple(blob.in_shape()), device="cuda", generator=gen).to(torch.bfloat16).view(torch.int16)
+    for b in (1, 5, 40, 256):
+        say(f"[case] tunings {name} b={b}")
+        first = None
+        for k, eng in enumerate(engines[:2 if b > 40 else 3]):
+            act, out = x[:b], []
+            for s in range(blob.n_stages):
+                act = eng.stage_forward(s, act, blob.stage_out_shape(s))
+                out += [act, *eng.exit_head(s, act, float(blob.exits[s]["thr"]))]
+            first = first or out
+            assert all(torch.equal(g, w) for g, w in zip(out, first)), f"tuning {k}: outputs {[i for i, (g, w) in enumerate(zip(out, first)) if not torch.equal(g, w)]} differ"
+    for eng in engines:
+        eng.close()
+
+
 @pytest.mark.parametrize("name", ["tiny_bf16", "zoo_bf16", "resnet50_small_bf16", "inception_small_bf16"])
 def test_bf16_within_tolerance(torch, ee, orc, name):
     blob = W.load_net(name)
