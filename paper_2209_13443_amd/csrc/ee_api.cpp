@@ -1622,13 +1622,21 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
     gap_fused = false;
     const StageDesc& st = net.stages[stage];
     const int dt = net.dtype, es = net.elem_bytes();
+    const void* const requests = first_packed ? first_pool : nullptr;      // admitted and not folded
+    auto fold = [&](const OpPlan& p, const void* x, const int32_t* gather) {      // the folded copy of the input in front of its layer
+        const OpDesc& d = p.d;
+        const double pb = (double)b * ((double)d.h_in * d.w_in * d.c_in + (double)p.Hp * p.Wp * 16) * es;
+        return timed(EE_K_PAD_INPUT, 0.0, pb, [&] { return launch_space_to_depth(x, pad_bufs[p.pad_buf], gather, b, d.h_in, d.w_in, d.c_in, p.Hp, p.Wp, d.pad, dt, stream, gather != nullptr); });
+    };
     for (int i = 0; i < st.n_ops; ++i) {
         const int k = order[(size_t)(st.first_op + i)];
         if (only_op >= 0 && st.first_op + k != only_op) continue;
         if (only_block >= 0 && (st.first_op + k < only_block || st.first_op + k > only_block + plans[(size_t)only_block].ir_last())) continue;
         OpPlan& p = plans[st.first_op + k];
         const OpDesc& d = p.d;
-        const void* src = resolve(this, p.src_buf, act_in, act_out);
+        const bool packed = first_packed && k == 0;
+        const void* src = packed && requests ? requests : resolve(this, p.src_buf, act_in, act_out);
+        const int32_t* const ids = packed && requests ? first_ids : nullptr;
         void* dst = resolve(this, p.dst_buf, act_in, act_out);
         const void* res = d.res >= 0 ? resolve(this, p.res_buf, act_in, act_out) : nullptr;
         const double ops = p.ops_per_sample * b, bytes = p.bytes_per_sample * b + p.weight_bytes;
@@ -1651,20 +1659,15 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             if (fuse && p.ir_stem) {
                 const OpPlan& q2 = plans[st.first_op + k + 1];
                 const bool folded = p.impl == IMPL_MFMA_S2D;
-                const bool packed = first_packed && k == 0;
-                const bool image = stage == 0 && k == 0 && first_reads_images(b, packed ? first_pool : src);
-                if (folded && !packed && !image) {                                 // the folded copy of the input, as in front of the layer alone
-                    const double pb = (double)b * ((double)d.h_in * d.w_in * d.c_in + (double)p.Hp * p.Wp * 16) * es;
-                    e = timed(EE_K_PAD_INPUT, 0.0, pb, [&] { return launch_space_to_depth(src, pad_bufs[p.pad_buf], nullptr, b, d.h_in, d.w_in, d.c_in, p.Hp, p.Wp, d.pad, dt, stream); });
-                    if (e != hipSuccess) return EE_ERR_DEVICE;
-                }
+                const bool image = folded && stage == 0 && k == 0 && (packed ? requests && stem_image_supported(src, es, d.w_in, d.c_in) : first_reads_images(b, src));
+                if (folded && !image && (!packed || requests) && fold(p, src, ids) != hipSuccess) return EE_ERR_DEVICE;
                 ConvArgs ca{};
                 fill_conv_args(st.first_op + k, b, ca);
                 ca.x = folded ? pad_bufs[p.pad_buf] : src; ca.mode = 0;
                 void* yq = resolve(this, q2.dst_buf, act_in, act_out);
                 const double mid = 2.0 * es * b * (double)d.h_out * d.w_out * d.c_out; // the tensor that stays on chip
                 e = timed(EE_K_CONV_STREAM, ops + q2.ops_per_sample * b, bytes + q2.bytes_per_sample * b + q2.weight_bytes - mid,
-                          [&] { return image ? launch_stem_image(ca, es, packed ? first_pool : src, packed ? first_ids : nullptr, d.h_in, d.w_in, d.pad, yq, q2.d.h_out, q2.d.w_out, stream) : folded ? launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream) : launch_conv_pool(ca, yq, q2.d.h_out, q2.d.w_out, q2.d.pad, stream); }, st.first_op + k);
+                          [&] { return image ? launch_stem_image(ca, es, src, ids, d.h_in, d.w_in, d.pad, yq, q2.d.h_out, q2.d.w_out, stream) : folded ? launch_stem_pool(ca, es, yq, q2.d.h_out, q2.d.w_out, stream) : launch_conv_pool(ca, yq, q2.d.h_out, q2.d.w_out, q2.d.pad, stream); }, st.first_op + k);
                 if (e != hipSuccess) return EE_ERR_DEVICE;
                 ++i;                                                             // the pool is done
                 continue;
@@ -1714,20 +1717,18 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             }
         }
         if (p.impl == IMPL_MFMA || p.impl == IMPL_MFMA_C4 || p.impl == IMPL_MFMA_CPAD || p.impl == IMPL_MFMA_S2D) {
-            if (p.impl == IMPL_MFMA_S2D && stage == 0 && k == 0 && only_op < 0 && cfg_force == 0 && first_reads_images(b, first_packed ? first_pool : src)) {
+            if (p.impl == IMPL_MFMA_S2D && stage == 0 && k == 0 && only_op < 0 && cfg_force == 0 && (packed ? requests != nullptr : first_reads_images(b, src))) {
                 // whatever the layer's table says: that is about launches that read the folded copy
                 ConvArgs ca{};
                 fill_conv_args(st.first_op, b, ca);
                 ca.y = dst;
-                e = timed(EE_K_CONV_STREAM, ops, bytes, [&] { return launch_conv_stream_image(ca, first_packed ? first_pool : src, first_packed ? first_ids : nullptr, d.h_in, d.w_in, d.pad, stream); }, st.first_op);
-                if (e != hipSuccess) return EE_ERR_DEVICE;
-                continue;
+                if (conv_stream_image_supported(ca, es, src, d.h_in, d.w_in, d.c_in, d.pad)) {
+                    e = timed(EE_K_CONV_STREAM, ops, bytes, [&] { return launch_conv_stream_image(ca, src, ids, d.h_in, d.w_in, d.pad, stream); }, st.first_op);
+                    if (e != hipSuccess) return EE_ERR_DEVICE;
+                    continue;
+                }
             }
-            if (p.impl == IMPL_MFMA_S2D && !(first_packed && k == 0)) {
-                const double pb = (double)b * ((double)d.h_in * d.w_in * d.c_in + (double)p.Hp * p.Wp * 16) * es;
-                e = timed(EE_K_PAD_INPUT, 0.0, pb, [&] { return launch_space_to_depth(src, pad_bufs[p.pad_buf], nullptr, b, d.h_in, d.w_in, d.c_in, p.Hp, p.Wp, d.pad, dt, stream); });
-                if (e != hipSuccess) return EE_ERR_DEVICE;
-            }
+            if (p.impl == IMPL_MFMA_S2D && (!packed || requests) && fold(p, src, ids) != hipSuccess) return EE_ERR_DEVICE;
             if (p.impl == IMPL_MFMA_CPAD) {
                 const double pb = (double)b * d.h_in * d.w_in * (d.c_in + p.ci_eff) * es;
                 e = timed(EE_K_PAD_INPUT, 0.0, pb, [&] {
@@ -1992,10 +1993,10 @@ extern "C" int ee_measure_lut(ee_ctx* ctx, int reps, int64_t* lut_ns)
                         const HeadArgs h = ctx->head_args(s, b, ctx->out_buf[s], 2.0f, ctx->d_label, ctx->d_conf, ctx->d_score, ctx->d_flag, true, nullptr);
                         rc = ctx->run_segment(s, b, ctx->in_buf[s], ctx->out_buf[s], nullptr, s == 0 ? ctx->h_ids[0] : nullptr, nullptr, nullptr, &h);
                     } else {
-                    if (s == 0 && fold && ctx->first_reads_images(b, ctx->in_buf[0])) {
-                        ctx->first_pool = ctx->in_buf[0];
-                        ctx->first_ids = ctx->h_ids[0];
-                    } else if (s == 0 && fold) {
+                    const bool image = s == 0 && fold && ctx->first_reads_images(b, ctx->in_buf[0]);
+                    ctx->first_pool = image ? ctx->in_buf[0] : nullptr;
+                    ctx->first_ids = ctx->h_ids[0];
+                    if (s == 0 && fold && !image) {
                         const OpDesc& d = fold->d;
                         if (launch_space_to_depth(ctx->in_buf[0], ctx->pad_bufs[fold->pad_buf], ctx->h_ids[0], b, d.h_in, d.w_in, d.c_in, fold->Hp, fold->Wp, d.pad, ctx->net.dtype, ctx->stream, true) != hipSuccess) rc = EE_ERR_DEVICE;
                     }

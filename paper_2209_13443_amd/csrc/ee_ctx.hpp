@@ -140,7 +140,7 @@ struct ee_ctx {
     }
 
     // internal entry points shared by the C ABI and the stream driver (no argument checks)
-    // first_packed: the first layer's folded input copy already holds these samples (admission wrote it), or, where first_reads_images, they are requests first_ids of first_pool
+    // first_packed: these samples were admitted: the first layer's folded input copy holds them, or, with first_pool, they are its requests first_ids
     // only_op >= 0: just that layer (an index into plans; fused pairs run as separate layers then); only_op <= -2: just the
     // inverted-residual block headed by layer -2 - only_op (one launch or three, as ir_mode and the table say);
     // cfg_force > 0: that kernel configuration for every matrix-core layer instead of the table's
@@ -157,7 +157,8 @@ struct ee_ctx {
     }
     // whether b samples of segment 0 at x are read by the launch of its first layer (and pool) itself: nothing is folded in front of it, and admission has nothing to do (never with ir_mode 0)
     bool first_reads_images(int b, const void* x) const;
-    const void* first_pool = nullptr;       // with first_packed: where the requests are
+    // with first_packed: what admission decided, which run_stage goes by whatever has changed since (ee_tune_conv_tile is process-wide): the requests were not folded, the first layer's launch reads them here; else null
+    const void* first_pool = nullptr;
     const int32_t* first_ids = nullptr;     // pinned
     // launches layer `op` (an index into plans) on b samples with the given kernel configuration (0 = by shape)
     hipError_t launch_conv(int op, int b, const void* src, void* dst, const void* res, int cfg, const uint16_t* xs = nullptr, const uint16_t* ys = nullptr, int32_t* gap_sums = nullptr);

@@ -19,9 +19,9 @@
 //   A: row l%32, k-bytes [16*(l/32), 16*(l/32)+16)      B: column l%32, same k-bytes
 //   D: column l%32, rows 8*(v/4) + 4*(l/32) + v%4 for accumulator register v = 0..15
 // (the k order inside an instruction is irrelevant as long as A and B agree).
-#include <type_traits>
-
+#include <atomic>
 #include <cstring>
+#include <type_traits>
 
 #include "ee_internal.hpp"
 
@@ -281,15 +281,15 @@ static hipError_t launch_tile(const ConvArgs& a, hipStream_t s)
 // Tile choice per layer and active batch size: the widest tile that still gives every CU a few
 // workgroups to overlap (the GPU face of the paper's per-layer, per-batch-size mapping problem,
 // Sec. III-A).  Tiles are output pixels x output channels.
-static int g_forced_tile = 0;    // 0 = by shape; 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128 (tuning / test control)
-int set_conv_tile(int tile) { const int old = g_forced_tile; g_forced_tile = tile; return old; }
-int forced_conv_tile() { return g_forced_tile; }
+static std::atomic<int> g_forced_tile{0};    // 0 = by shape; 1: 128x128, 2: 128x64, 3: 64x64, 4: 64x128 (tuning / test control)
+int set_conv_tile(int tile) { return g_forced_tile.exchange(tile, std::memory_order_relaxed); }
+int forced_conv_tile() { return g_forced_tile.load(std::memory_order_relaxed); }
 
 template <int ES>
 static hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t s)
 {
     if (a.M <= 0) return hipSuccess;
-    int tile = g_forced_tile & 15;
+    int tile = forced_conv_tile() & 15;
     if (tile == 0 || tile > 4) {
         auto blocks = [&](int bm, int bn) { return (long long)((a.M + bm - 1) / bm) * ((a.Co + bn - 1) / bn); };
         const long long want = 3 * 256;

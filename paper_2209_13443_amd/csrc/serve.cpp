@@ -100,6 +100,7 @@ struct GpuExec {
     struct Step { SlotTab in, out; int b = 0, stage = -1, dst = -1, ring = 0, in_base = 0, out_base = 0; bool has_out = false; } step_of[4];
     bool small[8] = {};                          // the segments that run with their exit head as one launch, decided once per call
     const int32_t* admitted[4] = {};             // the lane's latest admission (pinned ids), read by a first segment that runs as one launch and by a first layer that reads images
+    bool unfolded[4] = {};                       // decided there: that first layer will
 
     explicit GpuExec(ee_ctx* c, const void* input_pool, bool zero_copy = false) : ctx(c), pool((const unsigned char*)input_pool), zc(zero_copy)
     {
@@ -215,7 +216,7 @@ struct GpuExec {
     {
         if (zc) { const int rc = zc_begin(lane, stage, b, src_off, ring_rows); if (rc) return rc; }
         if (small[stage]) return run_small(lane, stage, b, src_off);
-        if (stage == 0) { ctx->first_pool = pool; ctx->first_ids = admitted[lane]; }
+        if (stage == 0) { ctx->first_pool = unfolded[lane] ? pool : nullptr; ctx->first_ids = admitted[lane]; }
         ctx->gap_fuse_dst = ctx->sums;                   // the segment's last layer pools for the exit head where it can
         int rc = ctx->run_stage(stage, b, step_in(lane, stage, src_off), step_out(lane, stage), stage == 0 && ctx->admission_fold() != nullptr);
         ctx->gap_fuse_dst = nullptr;
@@ -238,7 +239,7 @@ struct GpuExec {
         const int64_t sb = ctx->stage_in_bytes(0);
         hipError_t e;
         if (const OpPlan* p = ctx->admission_fold()) {
-            if (ctx->first_reads_images(b, pool)) return EE_OK;              // the launch of the first layer and its pool reads the requests itself
+            if ((unfolded[lane] = ctx->first_reads_images(b, pool))) return EE_OK;              // the launch of the first layer and its pool reads the requests itself
             // the first layer reads a zero-padded, folded copy of its input: admission writes that copy directly
             const OpDesc& d = p->d;
             const int es = ctx->net.elem_bytes();

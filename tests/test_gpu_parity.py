@@ -6,6 +6,7 @@ per-sample max-norm, confidences within 1e-3, exit decisions equal unless the or
 within 1e-3 of the threshold."""
 import re
 import sys
+import threading
 
 import numpy as np
 import pytest
@@ -1875,6 +1876,47 @@ def test_folded_first_layer_straight_from_the_requests(torch, ee, orc, case):
         out = eng.serve_stream(np.zeros(n, np.int64), pool, synthetic_lut(blob.n_stages, b_max), b_max=b_max, refill=0)[0]
         assert np.array_equal(out["label"], label) and np.array_equal(out["score"], score) and np.array_equal(out["conf"], conf)
     eng.close()
+
+
+@pytest.mark.parametrize("stem", [True, False], ids=["pool", "layer"])
+def test_who_folds_is_decided_once(torch, ee, stem):
+    """Admission leaves the requests to the first layer's launch or folds them for it; the segment does as admission did also when another thread forces a tile (process-wide) between the two: every request keeps its outcome."""
+    from workloads import nets as N
+    if stem:
+        blob = W.stem_net(96, 64, seed=4)
+    else:
+        net = N._Net(W.DT_I8, 96, 64, 3, 10)
+        t = net.conv(net.begin_stage(), 32, 3, 2, 1)
+        net.end_stage(net.conv(t, 32, 1, 1, 0))
+        blob = N._assemble(net, net.dtype, 4)
+        for op in blob.ops:
+            op["shift"] = 9
+    n = 4000
+    pool = dev(torch, np.random.default_rng(3).integers(-128, 128, size=(n, 96, 64, 3), dtype=np.int8))
+    eng, lut = ee.Engine(blob, 2), synthetic_lut(blob.n_stages, 2)
+    want = eng.serve_stream(np.zeros(n, np.int64), pool, lut, b_max=2, refill=0)[0]
+    names = kernels_of(torch, lambda: eng.serve_stream(np.zeros(8, np.int64), pool, lut, b_max=2, refill=0))[1]
+    assert np.unique(want["conf"]).size > 100 and any(k.startswith("stem_pool_i8" if stem else "conv_stream_image_i8") for k in names) and not any(k.startswith("space_to_depth") for k in names), names
+    stop, old, turns = threading.Event(), ee.tune_conv_tile(0), [0]
+
+    def force():
+        while not stop.is_set():
+            turns[0] += 1
+            ee.tune_conv_tile(3 * (turns[0] & 1))
+
+    thread = threading.Thread(target=force)
+    thread.start()
+    try:
+        for k in range(5):
+            say(f"[case] who folds {stem} pass {k}")
+            got = eng.serve_stream(np.zeros(n, np.int64), pool, lut, b_max=2, refill=0)[0]
+            assert all(np.array_equal(got[f], want[f]) for f in ("label", "score", "conf")), f"{np.count_nonzero(got['score'] != want['score'])} of {n} differ"
+    finally:
+        stop.set()
+        thread.join()
+        ee.tune_conv_tile(old)
+        eng.close()
+    assert turns[0] > 100
 
 
 SB_CASES = [(224, 224, 5), (57, 80, 7), (32, 32, 9), (17, 16, 3), (7, 16, 2), (116, 60, 9)]      # pooled 56 x 56, 15 x 20, 8 x 8, 5 x 4, 2 x 4, 29 x 15: whole tiles of 7 x 8 and not
