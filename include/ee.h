@@ -193,8 +193,8 @@ int ee_measure_lut(ee_ctx* ctx, int reps, int64_t* lut_ns);
 /* Design-time measurement of one layer alone (Sec. III-B builds its latency tables the same way, ahead of time): layer
  * `layer` of the network on `b` samples of the context's workspace, `reps` launches back to back between two HIP events
  * after two warm-up launches; *us_out = mean microseconds per launch (host), *ops_out = 2 * MACs and *bytes_out = the
- * algorithmic HBM bytes of one launch (may be NULL).  cfg = 0 uses the layer's table entry, else that kernel
- * configuration (as in ee_config_set); cfg = 0x20000 times the fused inverted-residual block headed by `layer` (its
+ * algorithmic HBM bytes of one launch (may be NULL).  cfg = 0 uses the layer's table entry as a segment does, else that kernel
+ * configuration (as in ee_config_set; a first layer that could read the images itself then reads the folded copy); cfg = 0x20000 times the fused inverted-residual block headed by `layer` (its
  * layers' operations and bytes; EE_ERR_ARG when the layer heads none).  Synchronous; overwrites workspace
  * activations.  EE_ERR_DEVICE when the configuration does not exist for this layer. */
 int ee_time_layer(ee_ctx* ctx, int layer, int b, int cfg, int reps, double* us_out, double* ops_out, double* bytes_out);
@@ -255,6 +255,8 @@ int ee_tune_conv_tile(int cfg);
  * 0x2332: 2 and 4 blocks x 128 channels, two wavefronts sharing a reduction; 0x4234 and 0x4334: 2 and 4 blocks x 64
  * channels; 0x4434 and 0x4332: 2 blocks x 64 channels, two and four sharing; on int8 layers without padding 0x2431,
  * 0x4334 and 0x4531: 4 blocks x 128, 64 and 96 channels).
+ * The streaming kernel on a first layer of 3x3, stride 2, over 3 int8 channels reads the images itself where they are whole 16-byte chunks (not with
+ * ee_ir_mode 0 or a forced tile); entries 0 and 7 are that one launch, any other entry is that kernel behind a folded copy of the batch.
  * EE_ERR_ARG for bad arguments. */
 int ee_autotune(ee_ctx* ctx, int reps);
 int ee_config_table(const ee_ctx* ctx, int layer, int* cfg_out, int n);

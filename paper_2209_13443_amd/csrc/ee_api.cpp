@@ -1291,6 +1291,15 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
             for (size_t bi = 0; bi < buckets.size() && !rc; ++bi) {
                 ConvArgs probe{};
                 ctx->fill_conv_args(st.first_op + k, buckets[bi], probe);
+                if (s == 0 && k == 0 && ctx->first_layer_streams_images(buckets[bi], src)) {      // faster than every kernel behind the folded copy
+                    probe.y = dst;
+                    const auto found = fastest({7}, 1, [] {}, [&](int) {
+                        return ctx->timed(EE_K_CONV_STREAM, 0.0, 0.0, [&] { return launch_conv_stream_image(probe, src, nullptr, d.h_in, d.w_in, d.pad, ctx->stream); });
+                    });
+                    best_time[st.first_op][bi] = found.first;
+                    best[bi] = found.second;
+                    continue;
+                }
                 probe.res = res;
                 // the layer that carries the exit head's pooling when it serves: only kernels, and of the one with streamed weights only tiles, that pool
                 if (st.first_op + k == ctx->gap_fuse_op[s]) probe.gap_sums = ctx->sums;
@@ -1605,15 +1614,24 @@ extern "C" int ee_pair_count(const ee_ctx* ctx)
 }
 
 // ---- one backbone segment ------------------------------------------------------------------------
-bool ee_ctx::first_reads_images(int b, const void* x) const
+bool ee_ctx::first_layer_streams_images(int b, const void* x) const
 {
     const int op = net.stages[0].first_op;
     const OpPlan& p = plans[(size_t)op];
     if (p.impl != IMPL_MFMA_S2D || p.src_buf != BUF_EXT_IN || p.dst_buf == BUF_EXT_OUT || ir_mode == 0 || forced_conv_tile() != 0) return false;
-    if (p.ir && p.ir_stem && ir_wanted(op, b)) return op + 1 != gap_fuse_op[0] && stem_image_supported(x, net.elem_bytes(), p.d.w_in, p.d.c_in);
     ConvArgs a{};
     fill_conv_args(op, b, a);
     return conv_stream_image_supported(a, net.elem_bytes(), x, p.d.h_in, p.d.w_in, p.d.c_in, p.d.pad);
+}
+
+bool ee_ctx::first_reads_images(int b, const void* x) const
+{
+    const int op = net.stages[0].first_op;
+    const OpPlan& p = plans[(size_t)op];
+    if (p.ir && p.ir_stem && p.impl == IMPL_MFMA_S2D && p.src_buf == BUF_EXT_IN && forced_conv_tile() == 0 && ir_wanted(op, b))
+        return op + 1 != gap_fuse_op[0] && stem_image_supported(x, net.elem_bytes(), p.d.w_in, p.d.c_in);
+    const int word = p.cfg.empty() ? 0 : p.cfg[std::min<size_t>(bucket_of(b), p.cfg.size() - 1)];      // another kernel than the streaming one reads the folded copy
+    return (word == 0 || word == 7) && first_layer_streams_images(b, x);
 }
 
 int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool first_packed, int only_op, int cfg_force)
@@ -1717,8 +1735,7 @@ int ee_ctx::run_stage(int stage, int b, const void* act_in, void* act_out, bool 
             }
         }
         if (p.impl == IMPL_MFMA || p.impl == IMPL_MFMA_C4 || p.impl == IMPL_MFMA_CPAD || p.impl == IMPL_MFMA_S2D) {
-            if (p.impl == IMPL_MFMA_S2D && stage == 0 && k == 0 && only_op < 0 && cfg_force == 0 && (packed ? requests != nullptr : first_reads_images(b, src))) {
-                // whatever the layer's table says: that is about launches that read the folded copy
+            if (p.impl == IMPL_MFMA_S2D && stage == 0 && k == 0 && cfg_force == 0 && (packed ? requests != nullptr : first_reads_images(b, src))) {
                 ConvArgs ca{};
                 fill_conv_args(st.first_op, b, ca);
                 ca.y = dst;

@@ -157,6 +157,7 @@ struct ee_ctx {
     }
     // whether b samples of segment 0 at x are read by the launch of its first layer (and pool) itself: nothing is folded in front of it, and admission has nothing to do (never with ir_mode 0)
     bool first_reads_images(int b, const void* x) const;
+    bool first_layer_streams_images(int b, const void* x) const;        // the layer's own launch can (conv_stream_image_supported), without a look at its table
     // with first_packed: what admission decided, which run_stage goes by whatever has changed since (ee_tune_conv_tile is process-wide): the requests were not folded, the first layer's launch reads them here; else null
     const void* first_pool = nullptr;
     const int32_t* first_ids = nullptr;     // pinned

@@ -1878,6 +1878,41 @@ def test_folded_first_layer_straight_from_the_requests(torch, ee, orc, case):
     eng.close()
 
 
+def test_tables_of_a_first_layer_that_reads_the_images(torch, ee):
+    """Without a table, with the tuner's and with stored entries of the streaming kernel it is one launch, in a segment and timed by itself; a stored entry of another kernel is that kernel, behind the folded copy, and so is the
+    launch with no fused launches: the same bytes, admitted or not."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, 96, 64, 3, 10)
+    t = net.conv(net.begin_stage(), 32, 3, 2, 1)
+    net.end_stage(net.conv(t, 64, 1, 1, 0))
+    blob = N._assemble(net, net.dtype, 4)
+    for op in blob.ops:
+        op["shift"] = 9
+    x, shape = dev(torch, W.input_pool(blob, 8)), blob.stage_out_shape(0)
+    eng = ee.Engine(blob, 8)
+
+    def first(f):
+        out, names = kernels_of(torch, f)
+        return out, [re.sub("_rows.*|_kernel.*", "", k) for k in names if k.startswith(("space_to_depth", "conv_stream", "conv_igemm_kernel<1,64,64,128"))]
+
+    want = eng.stage_forward(0, x, shape)
+    eng.autotune(reps=1)
+    assert eng.config_table(0) == [7] * 4
+    image, copy = ["conv_stream_image_i8"], ["space_to_depth"]
+    for mode, word, names in ((1, 7, image), (1, 0, image), (1, 0x223, copy + ["conv_igemm"]), (0, 0x223, copy + ["conv_igemm"]), (0, 7, copy + ["conv_stream_i8"])):
+        say(f"[case] first layer's table {mode} {word:#x}")
+        eng.ir_mode(mode)
+        eng.load_tables({"config": {"0": [word] * 4}})
+        got, ran = first(lambda: eng.stage_forward(0, x, shape))
+        assert ran == names and torch.equal(got, want), ran
+        assert set(first(lambda: eng.time_layer(0, 8, reps=2))[1]) == set(names)
+        out = eng.serve_stream(np.zeros(8, np.int64), x, synthetic_lut(1, 8), b_max=8, refill=0)[0]
+        assert np.array_equal(out["score"], eng.exit_head(0, want, 0.5)[2].cpu().numpy())
+    eng.ir_mode(1)
+    assert set(first(lambda: eng.time_layer(0, 8, cfg=7, reps=2))[1]) == set(copy + ["conv_stream_i8"])
+    eng.close()
+
+
 @pytest.mark.parametrize("stem", [True, False], ids=["pool", "layer"])
 def test_who_folds_is_decided_once(torch, ee, stem):
     """Admission leaves the requests to the first layer's launch or folds them for it; the segment does as admission did also when another thread forces a tile (process-wide) between the two: every request keeps its outcome."""
