@@ -134,7 +134,7 @@ static hipError_t launch_group_skinny(const ConvArgs* a, int n, hipStream_t s)
     bool plain = true, taps = true;                         // every member 1x1 without padding; of whole steps to a tap
     long long total = 0;
     for (int i = 0; i < n; ++i) {
-        if (!a[i].wo) return hipErrorInvalidValue;
+        if (!a[i].wo || !skinny_reaches(a[i], 1)) return hipErrorInvalidValue;
         GroupMember& m = g.m[i];
         m.a = a[i];
         m.gm = (a[i].M + T - 1) / T; m.gn = (a[i].Co + T * TN - 1) / (T * TN);

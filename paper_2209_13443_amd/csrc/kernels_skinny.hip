@@ -26,7 +26,7 @@ static hipError_t launch_skinny(const ConvArgs& layer, hipStream_t s)
     const int gm = (a.M + T - 1) / T, gn = (a.Co + T * TN - 1) / (T * TN);
     const unsigned magic_gn = (unsigned)(0x100000000ull / (unsigned)gn - (gn == 1));
     const int nk = (a.kh * a.kw * a.Ci * ES + KB - 1) / KB, pitch = a.Kp * ES / 32;      // rows are padded to 256 bytes with zeros
-    if ((long long)gm * gn > 0x7fffffff) return hipErrorInvalidValue;
+    if ((long long)gm * gn > 0x7fffffff || !skinny_reaches(a, ES)) return hipErrorInvalidValue;
     const int mode = skinny_mode(a, ES, T);
     const dim3 grid((unsigned)(gm * gn)), block(64 * NW);
     if (mode == SKINNY_PLAIN) EE_LAUNCH((conv_skinny_kernel<ES, T, NW, TN, true>), grid, block, 0, s, a, gn, magic_gn, nk, pitch);
@@ -54,7 +54,7 @@ bool conv_skinny_config_ok(int cfg) { return skinny_waves(cfg) >= 0; }
 // best or within 5 % of it, but for long reductions in a full round, where eight and twice the channels per activation load are.
 int conv_skinny_default(const ConvArgs& a, int es)
 {
-    if (!a.wo || a.mode != 0 || es != 1) return 0;          // bf16 by default: one order of summation, that of the staged kernels
+    if (!a.wo || a.mode != 0 || es != 1 || !skinny_reaches(a, es)) return 0;          // bf16 by default: one order of summation, that of the staged kernels
     const long long kbytes = (long long)a.kh * a.kw * a.Ci * es;
     const long long tiles = (long long)((a.M + 31) / 32) * ((a.Co + 31) / 32);
     if (tiles > (kbytes > 128 ? 400 : 200)) return 0;
@@ -69,7 +69,7 @@ int conv_skinny_default(const ConvArgs& a, int es)
 // always 32 x 32 and two 1.17, 1.00, 1.01, 1.00.
 int conv_skinny_order_bf16(const ConvArgs& a)
 {
-    if (!a.wo || a.mode != 0 || a.M > EE_SKINNY_MAX_ROWS) return 0;
+    if (!a.wo || a.mode != 0 || a.M > EE_SKINNY_MAX_ROWS || !skinny_reaches(a, 2)) return 0;
     const int kbytes = a.kh * a.kw * a.Ci * 2;
     const long long tiles = (long long)((a.M + 31) / 32) * ((a.Co + 31) / 32);
     if (tiles <= 130) return kbytes >= 128 ? skinny_cfg(16, 1, 2) : 0;

@@ -71,10 +71,10 @@ __device__ __forceinline__ void skinny_tile(const ConvArgs& a, int gn, unsigned 
     // ---- the reduction -----------------------------------------------------------------------------------------
     // operands are packed for T = 32: [32 rows][32 bytes][row + 32 * half][16]; a 16-row operand of 64 bytes is half of the rows of two of them
     const int row0 = nt * TN * T;                           // first weight row, a multiple of T
-    const auto w_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.wo), (short)0, SKINNY_NOWHERE, 0x00020000);
+    const auto w_buf = __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(a.wo) + (long long)(row0 >> 5) * pitch * 1024, (short)0, SKINNY_NOWHERE, 0x00020000);      // begins with the tile's rows
     const int w_lane = T == 32 ? lane * 16 : (hi >> 1) * 1024 + (mrow + 32 * (hi & 1)) * 16;
     auto weight = [&](int j, int k) {
-        const int r = row0 + T * j;
+        const int r = (row0 & 31) + T * j;
         const int at = T == 32 ? ((r >> 5) * pitch + k) * 1024 : ((r >> 5) * pitch + 2 * k) * 1024 + (r & 16) * 16;
         return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(w_buf, w_lane, at, 0));
     };
@@ -282,12 +282,15 @@ __device__ __forceinline__ void skinny_tile(const ConvArgs& a, int gn, unsigned 
     }
 }
 
+// whether 32-bit offsets reach the weights of a tile, at most 64 rows
+inline bool skinny_reaches(const ConvArgs& a, int es) { return (long long)a.Kp * es * 64 < 1ll << 31; }
+
 // the form a layer runs in, with its divisors set
 inline int skinny_mode(ConvArgs& a, int es, int t)
 {
     const int kb = 1024 / t, cib = a.Ci * es;
-    // the buffers reach 4 GiB (slots of zero-copy compaction lie in less than 2: ee_create)
-    if (cib % kb != 0 || ((long long)(a.M - 1) / (a.Ho * a.Wo) + 1) * a.H * a.W * cib >= 1ll << 31 || ((long long)a.Co + 128) * a.Kp * es >= 1ll << 31) return SKINNY_ANY;
+    // the input's buffer reaches 4 GiB (slots of zero-copy compaction lie in less than 2: ee_create); that of the weights begins with the tile's rows (skinny_reaches)
+    if (cib % kb != 0 || ((long long)(a.M - 1) / (a.Ho * a.Wo) + 1) * a.H * a.W * cib >= 1ll << 31) return SKINNY_ANY;
     auto magic = [](int d) { return (unsigned)(0x100000000ull / (unsigned)d - (d == 1)); };
     a.magic_spt = magic(cib / kb);
     a.magic_kw = magic(a.kw);

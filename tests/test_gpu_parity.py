@@ -119,6 +119,47 @@ def test_few_pixel_convolution_forms_bit_exact(torch, ee, orc, c, k, stride, pad
     eng.close()
 
 
+def test_few_pixel_convolution_past_4_gib_of_weights(torch, ee):
+    """Every tile reads its own weights, those behind the first 4 GiB too: a 1x1 layer of 131,136 x 32,768 weights, of zeros but for sixteen rows, and a layer that passes their channels on."""
+    from workloads import nets as N
+    ci, co = 32768, 131136
+    rows = np.array([0, 31, 32, 65535, 65536, 65599, 70001, 131071, 131072, 131073, 131088, 131103, 131104, 131119, 131120, 131135])
+    net = N._Net(W.DT_I8, 1, 1, ci, 10)
+    t = net.conv(net.begin_stage(), 128, 1, 1, 0, act="linear")
+    net.end_stage(net.conv(t, 16, 1, 1, 0, act="linear"))
+    small = N._assemble(net, net.dtype, 3)
+    data = int(small.header[0]["data_off"])
+    w1 = data
+    b1 = w1 + ci * co
+    w2 = b1 + 4 * co
+    b2 = w2 + 16 * co
+    fc = b2 + 64
+    raw = np.zeros(fc + 1024, np.uint8)                      # pages of zeros are never touched on this side
+    raw[:data] = small.raw[:data]
+    raw[:128].view(W.HEADER_DT)["total_bytes"] = raw.size
+    at = int(small.header[0]["ops_off"])
+    ops = raw[at:at + 2 * W.OP_DT.itemsize].view(W.OP_DT)
+    for op, cin, cout, w, b, shift in ((ops[0:1], ci, co, w1, b1, 8), (ops[1:2], co, 16, w2, b2, 0)):
+        op["c_in"], op["c_out"], op["c_tot"], op["w_off"], op["b_off"], op["shift"] = cin, cout, cout, w, b, shift
+    at = int(small.header[0]["exits_off"])
+    exits = raw[at:at + W.EXIT_DT.itemsize].view(W.EXIT_DT)
+    exits["w_off"], exits["b_off"] = fc, fc + 512
+    rng = np.random.default_rng(8)
+    weights = rng.integers(-2, 3, size=(16, ci), dtype=np.int8)
+    for k, r in enumerate(rows):
+        raw[w1 + int(r) * ci:w1 + (int(r) + 1) * ci] = weights[k].view(np.uint8)
+        raw[w2 + k * co + int(r)] = 1
+    x = rng.integers(-128, 128, size=(1, 1, 1, ci), dtype=np.int8)
+    want = np.clip((weights.astype(np.int64) @ x.reshape(ci).astype(np.int64) + 128) >> 8, -128, 127)
+    assert np.unique(want).size > 8
+    eng = ee.Engine(raw, 1)
+    for cfg in (0x2212, 0x2222, 0x4213):
+        say(f"[case] weights past 4 GiB {cfg:#x}")
+        got = forced(ee, cfg, lambda: eng.stage_forward(0, dev(torch, x), (1, 1, 16)).cpu().numpy())
+        assert np.array_equal(got.reshape(16), want), (cfg, got.reshape(16), want)
+    eng.close()
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_random_networks_bit_exact(torch, ee, orc, seed):
     """Generated networks (rectangular kernels, per-axis padding, strides, residuals, depthwise, pooling, concatenated
