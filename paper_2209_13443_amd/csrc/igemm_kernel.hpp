@@ -330,17 +330,18 @@ __device__ __forceinline__ void igemm_tile(const ConvArgs& a, int gm, int gn, un
         }
         step2(st_c, st_c, st_c, std::false_type{}, std::true_type{});
     } else {
-    for (; ks + ns - 1 < nk; ++ks) {
+    int due = 0;                                    // the wait in front of a step: none for the first, which has been waited for (a count that leaves out the residual's copies would wait for them here)
+    for (; ks + ns - 1 < nk; ++ks, due = ns) {
         // steps ks+1 .. ks+ns-2 may still be in flight, each LPT copies of this wavefront
-        if (ns == 2) wait_copies_then_barrier<0>();
-        else if (ns == 3) wait_copies_then_barrier<LPT>();
-        else wait_copies_then_barrier<2 * LPT>();
+        if (due == 2) wait_copies_then_barrier<0>();
+        else if (due == 3) wait_copies_then_barrier<LPT>();
+        else if (due) wait_copies_then_barrier<2 * LPT>();
         step(st_c, st_i, std::true_type{});
         st_c = st_c + 1 == ns ? 0 : st_c + 1;
         st_i = st_i + 1 == ns ? 0 : st_i + 1;
     }
-    for (; ks < nk; ++ks) {                         // the last ns-1 steps: nothing left to copy
-        wait_copies_then_barrier<0>();
+    for (; ks < nk; ++ks, due = ns) {               // the last ns-1 steps: nothing left to copy
+        if (due) wait_copies_then_barrier<0>();
         step(st_c, st_c, std::false_type{});
         st_c = st_c + 1 == ns ? 0 : st_c + 1;
     }
