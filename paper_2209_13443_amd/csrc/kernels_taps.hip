@@ -321,12 +321,12 @@ __global__ __launch_bounds__(64 * NW * KP, 2) void conv_taps_kernel(ConvArgs a, 
     }
 }
 
-// Stride 1, output as large as the input, 2 .. 31 taps, a pixel of 64 bytes or more in whole groups of steps (a group never straddles two taps), whole
-// 16-byte chunks in the output, a tensor below 2 GiB and 2^24 pixels (the address arithmetic multiplies 24-bit row numbers)
-// no padding at all, so that every tap of every pixel exists (int8)
+// no padding at all and an output smaller than the input, so that every tap of every pixel exists (int8)
 static constexpr bool taps_valid_tile(int tm, int nw, int kp) { return tm == 4 && nw <= 4 && kp == 1; }       // the tiles that are built for it
 static bool taps_valid(const ConvArgs& a, int es) { return es == 1 && a.pad == 0 && a.pad_w == 0 && (a.Ho != a.H || a.Wo != a.W); }
 
+// Stride 1, 2 .. 31 taps, whole 16-byte chunks in the output, a tensor below 2 GiB and 2^24 pixels (the address arithmetic multiplies 24-bit row numbers), and either an output as large as
+// the input and a pixel of 64 bytes or more in whole groups of steps (a group never straddles two taps), or no padding and a pixel of 64 bytes or more in whole 16-byte chunks (a step may)
 bool conv_taps_supported(const ConvArgs& a, int es)
 {
     const int cib = a.Ci * es;
@@ -403,7 +403,7 @@ int conv_taps_default(const ConvArgs& a, int es)
     if (taps_valid(a, es)) {
         if (blocks < 1280 || kbytes < 640) return 0;
         const bool three = (a.Co + 95) / 96 * 96 < (a.Co + 127) / 128 * 128 && taps_lds(a, es, 4, 3, 1).bytes <= 40 * 1024;
-        return three ? taps_cfg(4, 3, 1) : taps_fits(a, es, 4, 4, 1) ? taps_cfg(4, 4, 1) : 0;
+        return three && taps_fits(a, es, 4, 3, 1) ? taps_cfg(4, 3, 1) : taps_fits(a, es, 4, 4, 1) ? taps_cfg(4, 4, 1) : 0;
     }
     const bool wide_groups = a.Ci * es % 128 == 0;                      // every tile exists; else 2 and 4 blocks of pixels
     auto fits = [&](int tm, int nw, int kp) { return taps_fits(a, es, tm, nw, kp); };

@@ -1157,6 +1157,93 @@ def test_streamed_weights_convolution_without_padding(torch, ee, orc, case):
             assert [k for k in names if k.startswith("conv_taps")] == ["conv_taps_kernel<1,4,%d,1,0>" % VALID_CONFIGS.get(cfg, 0)] * runs, hex(cfg)
 
 
+# (height, width, bytes per pixel, output channels, kernel, images from which on, 32-channel blocks of the tile): 1280 blocks of 64 x 64 outputs and 640 bytes of reduction; 96 channels where
+# they leave fewer empty than 128 and the slab is small enough for four workgroups to a CU
+VALID_RULE = [(74, 74, 80, 192, (3, 3), 6, 3), (38, 38, 80, 128, (3, 3), 32, 4), (35, 70, 176, 192, (3, 2), 12, 4), (38, 38, 64, 128, (3, 3), None, 0), (20, 66, 128, 48, (5, 1), 78, 4)]
+
+
+@pytest.mark.parametrize("case", VALID_RULE, ids=lambda c: "x".join(map(str, c)))
+def test_untuned_convolution_without_padding(torch, ee, case):
+    """Which tile of the kernel an untuned layer without padding gets, on both sides of its rule: the bytes of the staged kernel."""
+    h, w, kb, co, (kh, kw), edge, nw = case
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, h, w, kb, 10)
+    net.end_stage(net.conv(net.begin_stage(), co, (kh, kw), 1, (0, 0), act="linear"))
+    blob = N._assemble(net, net.dtype, h)
+    blob.ops[0]["shift"] = int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(kb * kh * kw) / 127)))
+    n = edge or 40
+    x = torch.randint(-128, 128, (n, h, w, kb), dtype=torch.int8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(h))
+    eng, shape = ee.Engine(blob, n), blob.stage_out_shape(0)
+    for b in (n, n - 1):
+        say(f"[case] untuned without padding {case} {b}")
+        got, names = kernels_of(torch, lambda: eng.stage_forward(0, x[:b], shape))
+        assert [k for k in names if k.startswith("conv_taps")] == ["conv_taps_kernel<1,4,%d,1,0>" % nw] * (b == edge), names
+        want, names = forced(ee, 0x221, lambda: kernels_of(torch, lambda: eng.stage_forward(0, x[:b], shape)))
+        assert any(k.startswith("conv_igemm_kernel") for k in names) and torch.equal(got, want) and torch.unique(got).numel() > 20
+    eng.close()
+
+
+@pytest.mark.parametrize("co", [64, 96, 160, 192])
+def test_convolution_without_padding_writes_slots_and_pools(torch, ee, co):
+    """Segments that end in a 3x3 layer without padding and with a residual: output slots in order and scattered, the exit head's pooling in its launch.  Every request gets what the copying compaction with the
+    staged kernel gives it, with every tile."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, 15, 13, 64, 10)
+    for _ in range(3):
+        u = net.conv(net.begin_stage(), co, 1, 1, 0)
+        net.end_stage(net.conv(u, co, 3, 1, 0, res=net.maxpool(u, 3, 1, 0)))
+    blob = N._assemble(net, net.dtype, co)
+    for op in blob.ops:
+        op["shift"] = max(0, int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(int(op["c_in"]) * int(op["kh"]) * int(op["kw"])) / 127)))) if int(op["kind"]) == W.OP_CONV else 0
+        op["res_shift"] = max(0, int(op["shift"]) - 2) if int(op["res"]) >= 0 else 0
+    b_max = 8
+    pool = W.input_pool(blob, 64)
+    blob.exits["frac_bits"] = 12
+    act, eng = dev(torch, pool[:8]), ee.Engine(blob, b_max)
+    for s in range(3):                                                     # thresholds that split the requests
+        act = eng.stage_forward(s, act, blob.stage_out_shape(s))
+        blob.exits[s]["thr"] = float(np.median(eng.exit_head(s, act, 0.5)[1].cpu().numpy())) if s < 2 else 0.5
+    eng.close()
+    eng = ee.Engine(blob, b_max)
+    assert eng.zero_copy_supported()
+    serve = scattered_stream(torch, eng, pool, 512, b_max)
+    want = None
+    for cfg, zc in [(0x221, 0)] + [(cfg, zc) for cfg in VALID_CONFIGS for zc in (0, 1)]:
+        say(f"[case] slots without padding {co} cfg {cfg:#x} zero_copy {zc}")
+        got, names = forced(ee, cfg, lambda: serve(zc))
+        assert cfg == 0x221 or names.count("conv_taps_kernel<1,4,%d,1,0>" % VALID_CONFIGS[cfg]) == names.count("fc_kernel<1,4,1>") + sum(k.startswith("head_small") for k in names) > 60, names[:40]
+        assert not [k for k in names if k.startswith("gap_")]
+        want = got if want is None else want
+        for f in ("exit_idx", "label", "conf", "score"):
+            assert np.array_equal(got[f], want[f]), (f, cfg, zc)
+    assert np.all(np.bincount(want["exit_idx"], minlength=3) > 0)
+    eng.close()
+
+
+@pytest.mark.parametrize("co", [32, 96, 144])
+def test_convolution_without_padding_into_a_slice(torch, ee, orc, co):
+    """The same layers where they fill channels [48, 48 + co) of a wider tensor, every tile, against the oracle."""
+    from workloads import nets as N
+    net = N._Net(W.DT_I8, 13, 17, 80, 10)
+    t = net.begin_stage()
+    cat = net.new_concat(11, 16, 48 + co + 16)
+    net.conv(t, 48, (3, 2), 1, (0, 0), into=(cat, 0))
+    net.conv(t, co, (3, 2), 1, (0, 0), act="linear", into=(cat, 48))
+    net.conv(t, 16, (3, 2), 1, (0, 0), into=(cat, 48 + co))
+    net.end_stage(cat)
+    blob = N._assemble(net, net.dtype, co)
+    for op in blob.ops:
+        op["shift"] = int(np.ceil(np.log2(2.0 * 74 * 40 * np.sqrt(480) / 127)))
+    x = W.input_pool(blob, 5)
+    ref = orc.stage_forward(blob, 0, x)
+    eng = ee.Engine(blob, 5)
+    for cfg in VALID_CONFIGS:
+        say(f"[case] slice without padding {co} cfg {cfg:#x}")
+        got, names = forced(ee, cfg, lambda: kernels_of(torch, lambda: eng.stage_forward(0, dev(torch, x), ref.shape[1:])))
+        assert names.count("conv_taps_kernel<1,4,%d,1,0>" % VALID_CONFIGS[cfg]) == 3 and np.array_equal(host(got, ref), ref), hex(cfg)
+    eng.close()
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 @pytest.mark.parametrize("case", TAPS_CASES, ids=lambda c: "x".join(map(str, c)))
 def test_streamed_weights_same_size_convolution(torch, ee, orc, case, dtype):
