@@ -20,7 +20,9 @@
 namespace ee {
 
 // ---- images read by the first layers themselves: where they are, their rows into LDS, four pixels of three channels as two super-pixels' rows ----------
-// sample n is image n of x or, for requests of a stream, image ids[n] of the pool x: ids by value in front of a kernel's arguments (ImageIds), else read from device-visible memory
+// sample n is image n of x or, for requests of a stream, image ids[n] of the pool x: ids by value in front of a kernel's arguments (ImageIds), else, for more than 256, read from device-visible memory in
+// front of every tile's copies, which lie a tile ahead (224 x 224, ns a request, the folded copy and the launch behind it / this, at 256 by value, 512 and 1024: 7x7 and pool 379, 362, 367 / 274, 273, 276;
+// bf16 688, 686, 686 / 496, 495, 524; 3x3 206, 228, 197 / 119, 103, 95)
 struct ImageArgs {
     const void* x;
     const int32_t* gather;      // ids that do not fit the arguments, else null

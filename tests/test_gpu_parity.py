@@ -2006,6 +2006,40 @@ def test_folded_first_layer_straight_from_the_requests(torch, ee, orc, case):
     eng.close()
 
 
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("h, w, k, pad", [(48, 32, 7, 0), (33, 48, 8, 3), (40, 64, 7, 5), (31, 16, 8, 1), (64, 80, 7, 2)])
+def test_first_layer_and_pool_from_the_images_with_other_paddings(torch, ee, orc, h, w, k, pad, dtype):
+    """The same launch for kernels of 7 and 8 and paddings of 0 to 5 pixels (every alignment of a tile's first byte): against the oracle, int8 bit for bit and with the layers one by one; requests by ids against their steps."""
+    from workloads import nets as N
+    i8 = dtype == "i8"
+    net = N._Net(W.DT_I8 if i8 else W.DT_BF16, h, w, 3, 10)
+    t = net.conv(net.begin_stage(), 64, k, 2, pad)
+    net.end_stage(net.conv(net.maxpool(t, 3, 2, 1), 32, 1, 1, 0))
+    blob = N._assemble(net, net.dtype, h + pad)
+    for op in blob.ops:
+        op["shift"] = 11 if int(op["c_in"]) == 3 else 10 if int(op["kind"]) == W.OP_CONV else 0
+    n = 9
+    x = W.input_pool(blob, n)
+    eng, ref = ee.Engine(blob, n), orc.stage_forward(blob, 0, x)
+    say(f"[case] first layer and pool from the images {dtype} {h}x{w} k{k} p{pad}")
+    for b in (n, 1):
+        got, names = kernels_of(torch, lambda: eng.stage_forward(0, dev(torch, x[:b]), ref.shape[1:]))
+        assert any(q.startswith(f"stem_pool_{dtype}_kernel") for q in names) and not any(q.startswith("space_to_depth") for q in names), names
+        if i8:
+            assert np.array_equal(host(got, ref), ref[:b]) and np.unique(ref).size > 8
+        else:
+            r, g = bf16_to_f32(ref[:b]).astype(np.float64), bf16_to_f32(host(got, ref)).astype(np.float64)
+            assert np.all(np.abs(g - r) <= 2e-2 * np.abs(r).reshape(b, -1).max(axis=1).reshape(-1, 1, 1, 1))
+    act = eng.stage_forward(0, dev(torch, x), ref.shape[1:])
+    label, conf, score, _ = (v.cpu().numpy() for v in eng.exit_head(0, act, 0.5))
+    got = eng.serve_stream(np.zeros(n, np.int64), dev(torch, x), synthetic_lut(1, 4), b_max=4, refill=0)[0]
+    assert np.array_equal(got["label"], label) and np.array_equal(got["score"], score) and np.array_equal(got["conf"], conf)
+    if i8:
+        eng.ir_mode(0)
+        assert np.array_equal(host(eng.stage_forward(0, dev(torch, x), ref.shape[1:]), ref), ref)
+    eng.close()
+
+
 def test_tables_of_a_first_layer_that_reads_the_images(torch, ee):
     """Without a table, with the tuner's and with stored entries of the streaming kernel it is one launch, in a segment and timed by itself; a stored entry of another kernel is that kernel, behind the folded copy, and so is the
     launch with no fused launches: the same bytes, admitted or not."""
