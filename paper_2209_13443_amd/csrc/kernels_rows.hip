@@ -26,6 +26,7 @@ struct RowsGrid {
     int ng;                    // groups of NB * 32 output channels
     int row_slots;             // workgroups per XCD and channel group
     unsigned magic_ng;
+    int past_caches;           // the results are stored past the caches (rows_past_caches)
 };
 
 // ES: element bytes; KB: bytes per input pixel; NB: blocks of 32 output channels per workgroup; RB: pixels per tile; RW: blocks of 32 pixels per wavefront
@@ -186,20 +187,23 @@ __global__ __launch_bounds__((RowsShape<ES, KB, NB, RB>::NT), 2) void conv_rows_
             }
         }
         lds_barrier();                                                  // the output tile is complete
+        auto store = [&](auto policy) {
 #pragma unroll
-        for (int j = 0; j < S; ++j) {
-            const int i = wave * S + j, row = i * (1024 / OROW) + lane / CR, chunk = (lane % CR) ^ (row & (CR - 1));
-            const unsigned r = (unsigned)(u * RB + row);
-            unsigned orow = r;
-            if (a.ys) {
-                const unsigned rc = min(r, (unsigned)a.M - 1), n = fast_div(rc, howo, a.magic_howo);
-                orow = (unsigned)l_ys[n] * howo + (rc - n * howo);
+            for (int j = 0; j < S; ++j) {
+                const int i = wave * S + j, row = i * (1024 / OROW) + lane / CR, chunk = (lane % CR) ^ (row & (CR - 1));
+                const unsigned r = (unsigned)(u * RB + row);
+                unsigned orow = r;
+                if (a.ys) {
+                    const unsigned rc = min(r, (unsigned)a.M - 1), n = fast_div(rc, howo, a.magic_howo);
+                    orow = (unsigned)l_ys[n] * howo + (rc - n * howo);
+                }
+                const v4i v = *(const v4i*)(l_o + buf * Sh::O_BYTES + i * 1024 + lane * 16);
+                const unsigned off = (orow * (unsigned)a.ldc + (unsigned)(a.c_off + n0)) * ES + chunk * 16;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), rsrc, r < (unsigned)a.M ? (int)off : (int)0x80000000u, 0, decltype(policy)::value);
             }
-            const v4i v = *(const v4i*)(l_o + buf * Sh::O_BYTES + i * 1024 + lane * 16);
-            const unsigned off = (orow * (unsigned)a.ldc + (unsigned)(a.c_off + n0)) * ES + chunk * 16;
-            // bf16 past the caches: 50 to 200 MB a layer displaced the weights and narrow tensors that the next layers need (all segments, 160 samples 2,174 -> 2,137 us; int8, half of that, no change)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), rsrc, r < (unsigned)a.M ? (int)off : (int)0x80000000u, 0, ES == 2 ? 2 : 0);
-        }
+        };
+        if (ES == 2 && g.past_caches) store(std::integral_constant<int, 2>{});
+        else store(std::integral_constant<int, 0>{});
     }
 }
 
@@ -231,6 +235,12 @@ int conv_rows_default(const ConvArgs& a, int es)
     return es == 2 && blocks >= 8192 && a.Ci * es <= 512 ? EE_CFG_ROWS64 : EE_CFG_ROWS32;
 }
 
+// bf16 results of half of the L2s (32 MB) and more go past the caches: they displace the weights and narrow tensors that the next layers need.  ResNet-50, stream of 8,000 requests in 256 slots on two lanes, ms, six tunings:
+// none 70.3-70.7, all, from 32, 64 and 96 MB on 69.4-70.0, from 128 MB on 70.0-70.4.  Smaller results the next layer finds in the caches; all segments, us, none / all / from 16 MB on: 4 samples 295 / 298 / 295, 8 348 / 351 / 348,
+// 12 409 / 416 / 409, 16 451 / 461 / 451, 24 614 / 601 / 599, 32 701 / 696 / 704, 40 751 / 746 / 756, 50 882 / 890 / 893, 64 1,030 / 1,018 / 1,018, 100 1,417 / 1,452 / 1,458, 160 2,034 / 2,034 / 2,037, 200 2,551 / 2,601 / 2,603,
+// 256 3,110 / 3,138 / 3,144: between 24 and 256 samples alone no limit is the better one throughout, in streams all of them are alike.  int8, half of the bytes, is as fast either way.
+static bool rows_past_caches(const ConvArgs& a, int es) { return es == 2 && (long long)a.M * a.Co * es >= 16 << 20; }
+
 template <int ES, int KB, int NB, int RB, bool RES>
 static hipError_t launch_rows_shape(const ConvArgs& a, hipStream_t s)
 {
@@ -249,6 +259,7 @@ static hipError_t launch_rows_shape(const ConvArgs& a, hipStream_t s)
     const int per_xcd = (g.tiles + 7) / 8;
     g.row_slots = std::max(1, 32 * per_cu / g.ng);
     if (g.row_slots > per_xcd) g.row_slots = per_xcd;
+    g.past_caches = rows_past_caches(a, ES);
     EE_LAUNCH((conv_rows_kernel<ES, KB, NB, RB, RES>), dim3((unsigned)(8 * g.row_slots * g.ng)), dim3(Sh::NT), (size_t)Sh::LDS, s, a, g);
     return hipGetLastError();
 }
