@@ -14,7 +14,7 @@
 //                the image as zeros: the second layer pads its input).
 //                back (wavefronts 4-7), on tile i: (pixel block of 8 x 4, half of the 64 middle channels) per wavefront: nine
 //                taps x two reduction steps of the 3x3 layer, requantisation, the result to LDS;
-//                both, behind their matrix instructions: the residual of tile i is requested, the pixels of tile i + 2, requested one iteration ago, go to LDS, those of tile i + 3 are requested;
+//                both: in front of their matrix instructions the residual of tile i is requested, between them the pixels of tile i + 2, requested one iteration ago, go to LDS, behind them those of tile i + 3 are requested;
 //   second half  all eight wavefronts: the last layer of tile i, (pixel block, two of the eight blocks of 32 output channels)
 //                each: bias, residual (requested in the first half), requantisation, 16-byte stores.
 // All sums are int32 and exact, rounding points are those of the three separate layers: results are equal bit for bit.
@@ -42,12 +42,12 @@ constexpr int BN_BIAS_BYTES = 4 * (64 + 64 + 256);
 constexpr int BN_M2_BYTES = 4 * 1024;            // requantised second-layer outputs [pixel block][channel half][lane][16]
 constexpr int BN_SLOT_BYTES = 2 * EE_ZC_MAX_B;   // the output slot of every sample
 
+constexpr unsigned BN_NOWHERE = 0xffffff00u;       // bytes of the output a store reaches; offsets from there on are dropped
+
 // K1: reduction steps of the first layer, c_in / 32; RES: the last layer adds a residual; GAP: the per-sample channel sums of the
 // output are also added into a.gap_sums (the exit head's pooling); SC: the residual is a 1x1 convolution of the block's input
 // (64 -> 256 channels, the shortcut of a group's first block), computed here from the staged pixels and requantised as that layer
 // would have written it (two more buffers keep a tile's pixels until its last layer has run in every wavefront)
-constexpr unsigned BN_NOWHERE = 0xffffff00u;       // bytes of the output a store reaches; offsets from there on are dropped
-
 template <int K1, bool RES, bool GAP, bool SC>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void bneck_block_i8_kernel(IrArgs a, BnTile t)
 {

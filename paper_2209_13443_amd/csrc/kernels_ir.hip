@@ -34,8 +34,8 @@
 // expands, filters and projects every pixel of the tile for the groups g = wavefront, wavefront + 4 (or 8), ... through a buffer
 // of its own, with no barrier inside the loop; the partial projection sums are added in LDS (integer adds,
 // exact in any order) and the epilogue is shared out by (pixel block, output block).
-// What bounds it: blocks on large images issue vector instructions for half of their time (112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels, 64 images: 8.1 M, 13 of 26.6 us; 56 x 56, 24 -> 144 -> 24: 5.5 M, 9
-// of 21.0, counted before the tile was read through a buffer, which took a third of the instructions in front of the groups away) and matrix instructions for 2.7 and 3.7 us; a third of a workgroup's life is
+// What bounds it: blocks on large images issue vector instructions for half of their time (112 x 112 -> 56 x 56, 16 -> 96 -> 24 channels, 64 images: 7.4 M, 12.0 of 23.5 us; 56 x 56, 24 -> 144 -> 24: 5.2 M, 8.5
+// of 18.8, launches back to back) and matrix instructions for 2.7 and 3.7 us; a third of a workgroup's life is
 // the way to its first group (6,000 of 17,000 cycles on the first of them: arguments 1,900, pixels there 3,500, barrier 6,000).  Those on small images wait for their chain of loads, matrix instructions and barriers; 7 x 7, 160 -> 960 -> 160 for the 450 KB of weights that a workgroup reads through its CU's path, 3.9 of 11.7 us.
 // (Loading the first group's weights in front of the input, and the next group's ahead in GP, was 0-8 % slower everywhere: weights queue in front of the input.)
 // Every accumulation is int32 and exact, rounding points are those of the three separate layers: results are equal
