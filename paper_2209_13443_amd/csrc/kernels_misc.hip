@@ -10,9 +10,8 @@
 
 namespace ee {
 
-// The small kernels that a lane's next step waits for, a few wavefronts each (the compaction, hundreds of workgroups of copies, is none of them): they issue before the wavefronts of another lane's segment on
-// their SIMD.  MobileNetV2, two lanes of 64 slots, 4,096 requests, medians of 40 passes in five rounds of processes with the same tables, ms: none 11.96-12.11 (12.03 in the mean), these 11.71-11.86 (11.76), these and
-// the compaction 11.73-11.95 (11.83); ResNet-50 int8, 10,000 requests, 52.10-52.54 (52.29), 52.26-52.39 (52.33), 52.28-52.49 (52.38): level.
+// The small kernels that a lane's next step waits for, a few wavefronts each: they issue before the wavefronts of another lane's segment on their SIMD.  MobileNetV2, two lanes of 64 slots,
+// 4,096 requests, four comparisons: 1 to 4 % faster, 2 % in the mean (12.1 -> 11.9 ms); ResNet-50 and Inception-style streams, whose launches are longer, and single lanes: level.
 __device__ __forceinline__ void issue_first() { __builtin_amdgcn_s_setprio(3); }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -1147,6 +1146,7 @@ __global__ __launch_bounds__(256) void compact_kernel(const uint8_t* flag, const
                                                       const int32_t* refill_ids, int b_incr, long long sample_bytes, int dst_off, int ring_rows,
                                                       int* b_rem_out, int* b_merged_out)
 {
+    issue_first();
     const int chunks = (int)((sample_bytes + 16383) / 16384), unit = xcd_unit(blockIdx.x, (b_act + b_incr) * chunks);
     if (unit < 0) return;
     const int b = unit / chunks, chunk = unit - b * chunks, lane = threadIdx.x & 63;
