@@ -10,8 +10,9 @@
 
 namespace ee {
 
-// The small kernels that a lane's next step waits for, a few wavefronts each: they issue before the wavefronts of another lane's segment on their SIMD.  MobileNetV2, two lanes of 64 slots,
-// 4,096 requests, four comparisons: 1 to 4 % faster, 2 % in the mean (12.1 -> 11.9 ms); ResNet-50 and Inception-style streams, whose launches are longer, and single lanes: level.
+// The kernels that a lane's next step waits for, a few wavefronts each but for the compaction, whose hundreds of workgroups are short: they issue before the wavefronts of another lane's segment on their SIMD.
+// MobileNetV2, two lanes of 64 slots, 4,096 requests, ms, medians of 120 passes, 24 processes of each in turn on two cards, two tables: none 11.75-12.02, 11.87 in the mean, all but the compaction 11.74-11.86, 11.80,
+// all 11.58-11.88, 11.70.  ResNet-50 int8, which compacts nothing, level (52.29 / 52.33); single lanes too.
 __device__ __forceinline__ void issue_first() { __builtin_amdgcn_s_setprio(3); }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
