@@ -1263,10 +1263,11 @@ extern "C" int ee_autotune(ee_ctx* ctx, int reps)
     // bf16: every candidate for a layer and bucket adds the sums in one order, which its shape at the bucket's full size decides (no measurement, nor b_max): in that of the staged kernels (0) or in the
     // few-pixel kernel's with the wavefronts of that word.  So any two tunings give the same bits.
     auto split_of = [&](int op, size_t bi) {
-        if (es == 1) return 0;
+        const OpPlan& p = ctx->plans[(size_t)op];
+        if (es == 1 || !p.cfg_table() || ((long long)p.d.h_out * p.d.w_out << bi) > EE_SKINNY_MAX_ROWS) return 0;
         ConvArgs a{};
         ctx->fill_conv_args(op, 1 << bi, a);
-        return ctx->plans[(size_t)op].cfg_table() ? conv_skinny_order_bf16(a) : 0;
+        return conv_skinny_order_bf16(a);
     };
     // runs what stands in front of layer k of a segment, with the configuration found for it
     auto layer_before = [&](size_t s, int k, int b) {
